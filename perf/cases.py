@@ -201,3 +201,99 @@ def tolerance(case):
     # sums in another order, after three steps: gradient 4.3e-3 and 0.23 (six layers of 1024 cells; 2e-3 for the
     # paper-shaped model), against fp32 mode 4.7e-3 and 0.44: the gradient's largest elements are far above its root mean square
     return {"rel": 1.6e-2, "max": 0.9}
+
+
+def _inputs(case, seed):
+    """The inputs of prepare(), drawn in the same order from the same seed: weights, frames, labels, z of "xent", the neighbour."""
+    g = _generator(seed)
+    dtype = torch.bfloat16 if case["mode"] == 1 else torch.float32
+    n = _params(case)[0]
+    uniform = lambda: torch.empty(n, dtype=torch.float32, device=DEVICE).uniform_(-0.1, 0.1, generator=g)  # noqa: E731
+    theta = uniform()
+    shape = (case["T"], case["B"])
+    x = torch.randn(*shape, case["D"], device=DEVICE, generator=g).to(dtype).double()
+    labels = torch.randint(0, case["V"], shape, device=DEVICE, generator=g)
+    z = torch.randn(*shape, case["P"] or 2 * case["H"], device=DEVICE, generator=g).to(dtype).double() if case["call"] == "xent" else None
+    neighbour = uniform() if case.get("update") == "pair" else None
+    return theta, theta.to(dtype).double(), x, labels, z, neighbour
+
+
+def _tensors(case, theta):
+    """The flat vector as views: per layer and direction (W_x, U_h, b), the bottleneck's (W, b) or None, the softmax layer's (W, b)."""
+    off = 0
+
+    def take(*shape):
+        nonlocal off
+        k = math.prod(shape)
+        off += k
+        return theta[off - k:off].view(*shape)
+    H, zdim = case["H"], case["P"] or 2 * case["H"]
+    layers = [[(take(4 * H, d), take(4 * H, H), take(4 * H)) for _ in range(2)] for d in [case["D"]] + [2 * H] * (case["L"] - 1)]
+    bottleneck = (take(case["P"], 2 * H), take(case["P"])) if case["P"] else None
+    return layers, bottleneck, (take(case["V"], zdim), take(case["V"]))
+
+
+def _exact_forward(case, theta, x):
+    layers, bottleneck, _ = _tensors(case, theta)
+    y = x
+    for layer in layers:
+        out = []
+        for d, (wx, uh, b) in enumerate(layer):
+            ax = y @ wx.t() + b
+            h = c = None
+            hs = [None] * case["T"]
+            for t in (range(case["T"]) if d == 0 else reversed(range(case["T"]))):
+                a = ax[t] if h is None else ax[t] + h @ uh.t()
+                i, f, g, o = a.chunk(4, dim=1)
+                c = torch.sigmoid(i) * torch.tanh(g) + (0 if c is None else torch.sigmoid(f) * c)
+                h = torch.sigmoid(o) * torch.tanh(c)
+                hs[t] = h
+            out.append(torch.stack(hs))
+        y = torch.cat(out, dim=2)
+    return y if bottleneck is None else y @ bottleneck[0].t() + bottleneck[1]
+
+
+def _exact_loss(case, theta, z, labels):
+    w, b = _tensors(case, theta)[2]
+    u = (z @ w.t() + b).reshape(-1, case["V"])
+    return torch.nn.functional.cross_entropy(u, labels.reshape(-1)).reshape(1)
+
+
+def exact(case, seed):
+    """What the first run() on prepare(case, seed) returns, in 64 bits (every case here takes a few seconds at most)."""
+    call = case["call"]
+    if call in ("mix", "average"):
+        g = _generator(seed)
+        thetas = [torch.empty(case["n"], dtype=torch.float32, device=DEVICE).uniform_(-0.1, 0.1, generator=g) for _ in range(case["R"])]
+        if call == "average":
+            mean = sum(t.double() for t in thetas) / case["R"]
+            out = [mean] * case["R"]
+        else:                                    # step 0 pairs replicas 2k and 2k + 1
+            out = [m for a, b in zip(thetas[0::2], thetas[1::2]) for m in [0.5 * (a.double() + b.double())] * 2]
+        return dict(thetas=out, shadows=out if case["mode"] == 1 else None)
+    master, theta, x, labels, z, neighbour = _inputs(case, seed)
+    if call == "forward":
+        with torch.no_grad():
+            return _exact_forward(case, theta, x)
+    theta.requires_grad_()
+    if call == "xent":
+        z.requires_grad_()
+        loss = _exact_loss(case, theta, z, labels)
+        loss.backward()
+        # the call writes the softmax layer's slice of the gradient vector; the rest is as the learner made it (zero)
+        return dict(loss=loss.detach(), dz=z.grad, grad=theta.grad)
+    z = _exact_forward(case, theta, x)
+    loss = _exact_loss(case, theta, z, labels)
+    loss.backward()
+    grad = theta.grad
+    new = master.double() - 0.1 * case["B"] / 256 * grad
+    out = dict(loss=loss.detach(), z=z.detach(), grad=grad)
+    if neighbour is not None:
+        new = 0.5 * (new + neighbour.double())
+    shadow = new if case["mode"] == 1 else None
+    out.update(theta=new, shadow=shadow)
+    if case["update"] == "pair":
+        out.update(nb_theta=new, nb_shadow=shadow)
+    if case["update"] == "momentum":
+        out["velocity"] = grad                   # from a velocity of zero
+    return out
