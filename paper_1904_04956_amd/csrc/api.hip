@@ -282,7 +282,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->dax_filled = false;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
-    if (c->st == DT_BF16 && rec_waves_for(c->H, c->B) > 0) {
+    if (c->st == DT_BF16 && rec_waves_for(c->H) > 0) {
         const int NU = c->H / 32, tiles = (c->B + 31) / 32;
         int nbg = 256 / (2 * NU);
         if (nbg > tiles) nbg = tiles;

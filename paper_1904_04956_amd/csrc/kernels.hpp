@@ -67,7 +67,7 @@ struct RecBwdArgs {
     int T, B, H, nbg, tiles_per_group;
 };
 // Wavefronts per workgroup of the persistent kernels for this H, 0 if H is not supported.
-int rec_waves_for(int H, int B);
+int rec_waves_for(int H);
 // Whether launch_rec_fwd for this width honours RecFwdArgs::fill.
 bool rec_fwd_fills(int H);
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.

@@ -135,9 +135,9 @@ __device__ __forceinline__ bool wait_probe(const bf16_t* probe, bool probing, un
 
 constexpr int XPAIR = 2 * 32 * 8;                      // elements of one pair of 8-column chunks over 32 rows (1 KB)
 template <int NQ>
-__device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p, bool valid) {
+__device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) frag[q] = valid ? ld_coh_16B(p + q * XPAIR) : make_uint4(0, 0, 0, 0);
+    for (int q = 0; q < NQ; ++q) frag[q] = ld_coh_16B(p + q * XPAIR);
 }
 template <int NQ>
 __device__ __forceinline__ bool all_written(const uint4 (&frag)[NQ]) {
@@ -149,14 +149,14 @@ __device__ __forceinline__ bool all_written(const uint4 (&frag)[NQ]) {
 // The chunks in frag were loaded once; reloads them until no element of any lane is the sentinel
 // (or the wait is abandoned).  Normally the first check passes.
 template <int NQ>
-__device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* p, bool valid, bool give_up,
+__device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* p, bool give_up,
                                                unsigned* abort_word, unsigned long long limit_ticks) {
     if (give_up || all_written<NQ>(frag)) return give_up;
     const unsigned long long t0 = wall_clock64();
     unsigned it = 0;
     for (;;) {
         __builtin_amdgcn_s_sleep(1);
-        load_chunks<NQ>(frag, p, valid);
+        load_chunks<NQ>(frag, p);
         if (all_written<NQ>(frag)) return false;
         if ((++it & 31u) == 0) {
             if (ld_coh_u32(abort_word) != 0) return true;
@@ -176,21 +176,15 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 struct GroupMap { int d, u, bg, group; };
 
 // Workgroups that exchange data sit on one XCD when ids are dealt round-robin over eight XCDs
-// (a performance assumption only; correctness rests on the protocols above).
+// (a performance assumption only; correctness rests on the protocols above).  The grid holds a whole number of groups
+// per XCD (grid_groups); the workgroups of the groups that do not exist have no batch tile and leave at once.
+constexpr int grid_groups(int nbg) { return (2 * nbg + 7) & ~7; }
 __device__ __forceinline__ GroupMap map_block(int NU, int nbg) {
-    const int ngroups = 2 * nbg;
     const int x = blockIdx.x;
-    int group, u;
-    if ((ngroups & 7) == 0) {
-        const int slot = x >> 3;
-        group = (x & 7) + 8 * (slot / NU);
-        u = slot % NU;
-    } else {
-        group = x / NU;
-        u = x % NU;
-    }
+    const int slot = x >> 3;
+    const int group = (x & 7) + 8 * (slot / NU);
     GroupMap m;
-    m.group = group; m.u = u; m.d = group / nbg; m.bg = group % nbg;
+    m.group = group; m.u = slot % NU; m.d = group / nbg; m.bg = group % nbg;
     return m;
 }
 
@@ -199,9 +193,9 @@ __device__ __forceinline__ GroupMap map_block(int NU, int nbg) {
 // answers, a chunk without sentinels is correct; anything else is re-read cache-bypassing by
 // ensure_written.
 template <int NQ>
-__device__ __forceinline__ void load_chunks_cached(uint4 (&frag)[NQ], const bf16_t* p, bool valid) {
+__device__ __forceinline__ void load_chunks_cached(uint4 (&frag)[NQ], const bf16_t* p) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) frag[q] = valid ? *reinterpret_cast<const uint4*>(p + q * XPAIR) : make_uint4(0, 0, 0, 0);
+    for (int q = 0; q < NQ; ++q) frag[q] = *reinterpret_cast<const uint4*>(p + q * XPAIR);
 }
 // Element offset of column c (within a direction), row r of a tile, in the exchange order.
 __device__ __forceinline__ unsigned xoff(int c, int r) { return (unsigned)((c >> 3) * 256 + r * 8 + (c & 7)); }
@@ -224,7 +218,11 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 
 // ------------------------------------------------------------------------------ forward
 // KW = contraction elements per wavefront: H = NW * KW.
-// FULL: B is a multiple of 32, so every row of every tile exists and no access is predicated.
+// FULL: B is a multiple of 32, so every row of every tile exists.  Otherwise the rows of the last tile beyond the batch
+// repeat the batch's last row: their loads are clamped to it, they run through the recurrence and the exchange (whole
+// tiles of both) like any other row, no row's result depends on another row's, and only the row-major stores leave them
+// out.  No load is predicated: with one branch per loaded row a ragged batch took 119 us a layer where 256 whole rows
+// took 76 (H = 512, 173 sequences; the backward kernel 104 against 83).
 // MULTI: a workgroup owns several batch tiles (tiles_per_group > 1); only then is there a next item
 // whose exchanged chunks can be loaded ahead, and only then are registers set aside for them.
 template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI>
@@ -239,7 +237,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     const int d = gm.d, u = gm.u;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int ntl = tiles_in_batch(gm.bg, a.tiles_per_group, B);
+    const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     // This workgroup's share of the region to fill (the widest slice of U_h leaves no register for it: KW <= 128 only):
     // words [fill_pos, fill_end) of its share, a few words per thread and item.
     constexpr bool FILLS = KW <= 128;
@@ -277,7 +275,8 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     // Register e is batch row rb + re(e) of the tile: rb per thread, re(e) a compile-time constant.
     const int rb = 2 * EPT * wave + 4 * lh;
     auto re = [](int e) { return 8 * (e >> 2) + (e & 3); };
-    const unsigned o8b = (unsigned)(rb * 8 * H + d * 4 * H + j); // into the row-major [.][8H] tensor (a_x)
+    const unsigned o8c = (unsigned)(d * 4 * H + j);      // column in the row-major [.][8H] tensor (a_x)
+    const unsigned o8b = (unsigned)(rb * 8 * H) + o8c;
     const int NT = (B + 31) / 32;                        // 32-row tiles of the batch
     constexpr int XH = H / 16 * XPAIR;                   // exchange elements per (frame, direction, tile)
     const unsigned ohp = (unsigned)(wave * (KW / 16) * XPAIR + lane * 8);   // this lane's 16 bytes of each chunk pair
@@ -296,9 +295,9 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
         // one tile per workgroup, where the loads hide under the exchange wait, and slower with several)
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const bool ok = FULL || b0 + rb + re(e) < B;
+            const unsigned o = FULL ? o8b + (unsigned)(re(e) * 8 * H) : (unsigned)(min(rb + re(e), B - 1 - b0) * 8 * H) + o8c;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) ax[e][g] = ok ? axb[o8b + (unsigned)((re(e) * 8 + g) * H)] : 0.0f;
+            for (int g = 0; g < 4; ++g) ax[e][g] = axb[o + (unsigned)(g * H)];
         }
         // the previous cell state of this lane's four cells is one 16-byte word of the saved records (one tile: c stays in registers)
         float4 c4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -360,15 +359,12 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
             for (int g = 0; g < 4; ++g) sum[e][g] = 0.0f;
         if (n > 0) {
             // previous h of this batch tile: row l32, 8 consecutive k per lane
-            const int row = b0 + l32;
-            const bool valid = FULL || row < B;
             const bf16_t* hb = a.hx + ((size_t)(tp * 2 + d) * NT + (b0 >> 5)) * XH;   // uniform: previous frame, this tile
             const bf16_t* hp = hb + ohp;
             uint4 afrag[KSTEPS];
             if (SENTINEL) {
-                // one probe per producing workgroup of this wavefront's k-range: its last unit, last valid row
-                const int prow = FULL ? b0 + 31 : min(b0 + 31, B - 1);
-                const bf16_t* probe = hb + xoff(wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, prow - b0);
+                // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
+                const bf16_t* probe = hb + xoff(wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
                 bool got = false, gu = false;
                 if constexpr (MULTI) {
                     if (have_pre) {
@@ -384,25 +380,25 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                     // cache-bypassing loads (the first ones may have left lines with sentinels in the L1).
                     // (The widest slice has no registers for two attempts: probe first, then the data.)
                     if constexpr (KW <= 128) {
-                        load_chunks_cached<KSTEPS>(afrag, hp, valid);
+                        load_chunks_cached<KSTEPS>(afrag, hp);
                         flush_tail();
                         if (!all_written<KSTEPS>(afrag)) {
                             gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
                             asm volatile("" ::: "memory");
-                            load_chunks<KSTEPS>(afrag, hp, valid);
+                            load_chunks<KSTEPS>(afrag, hp);
                         }
                     } else {
                         gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
                         asm volatile("" ::: "memory");
-                        load_chunks_cached<KSTEPS>(afrag, hp, valid);
+                        load_chunks_cached<KSTEPS>(afrag, hp);
                     }
                 }
-                if (ensure_written<KSTEPS>(afrag, hp, valid, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+                if (ensure_written<KSTEPS>(afrag, hp, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             } else {
                 if (wait_counter(cnt + i, (unsigned)(NU * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
 #pragma unroll
                 for (int q = 0; q < KSTEPS; ++q)
-                    afrag[q] = valid ? *reinterpret_cast<const uint4*>(hp + q * XPAIR) : make_uint4(0, 0, 0, 0);
+                    afrag[q] = *reinterpret_cast<const uint4*>(hp + q * XPAIR);
             }
             f32x16_t acc[4];
 #pragma unroll
@@ -418,9 +414,8 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                 const int n2 = (item + 1) / ntl, i2 = (item + 1) - n2 * ntl;
                 const int tp2 = d ? T - n2 : n2 - 1;
                 const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
-                const bool valid2 = FULL || b02 + l32 < B;
                 const bf16_t* hb2 = a.hx + ((size_t)(tp2 * 2 + d) * NT + (b02 >> 5)) * XH;
-                load_chunks_cached<KSTEPS>(apre, hb2 + ohp, valid2);
+                load_chunks_cached<KSTEPS>(apre, hb2 + ohp);
                 have_pre = true;
             }
             // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
@@ -488,7 +483,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
         const int xrow = 2 * EPT * wave + 4 * xl + xr;    // row of the tile
         const bool xok = FULL || b0 + xrow < B;
         const unsigned xcol = (unsigned)(u * 32 + 8 * xk + 4 * xh);
-        if (xok) {
+        {
             bf16_t* xp = hxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u + (xcol & 7u));
             if (SENTINEL) st_coh_8B(xp, hq); else *reinterpret_cast<uint2*>(xp) = hq;
         }
@@ -541,7 +536,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     constexpr int KWB = 4 * H / NW;                         // gate rows per wavefront (= 4 * KW)
-    const int ntl = tiles_in_batch(gm.bg, a.tiles_per_group, B);
+    const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     if (ntl == 0) return;
 
     // U_h^T slice: output unit l32, 8 consecutive gate rows per lane
@@ -559,7 +554,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // per-thread 32-bit element offsets, added to per-item uniform bases (as in the forward kernel)
     const int rb = 2 * EPT * wave + 4 * lh;              // register e is batch row rb + re(e) of the tile
     auto re = [](int e) { return 8 * (e >> 2) + (e & 3); };
-    const unsigned o2b = (unsigned)(rb * 2 * H + d * H + j);     // into [.][2H] (dy)
+    const unsigned o2c = (unsigned)(d * H + j);          // column in the row-major [.][2H] tensor (dy)
+    const unsigned o2b = (unsigned)(rb * 2 * H) + o2c;
     const int NT = (B + 31) / 32;
     constexpr int XA = 4 * H / 16 * XPAIR;               // exchange elements per (frame, direction, tile)
     const unsigned oap = (unsigned)(wave * (KWB / 16) * XPAIR + lane * 8);   // this lane's 16 bytes of each chunk pair
@@ -570,7 +566,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // (one vector-memory instruction instead of four); with several tiles each lane loads its four values (see the
     // forward kernel's a_x for why).
     constexpr bool WIDE_DY = !MULTI;
-    struct Inputs { uint2 g[EPT]; bf16_t dy[EPT]; uint4 dyr; float c[EPT], cp[EPT], dcr[EPT]; };   // g: (i, f), (g, o) as bf16 pairs
+    struct Inputs { uint4 g01, g23; bf16_t dy[EPT]; uint4 dyr; float4 c, cp, dcr; };   // g01, g23: (i, f), (g, o) of two cells each as bf16 pairs
     auto issue_inputs = [&](int item, Inputs& in) {
         const int ni = item / ntl, i = item - ni * ntl;
         const int n = T - 1 - ni;
@@ -584,25 +580,18 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         const uint4* g4 = reinterpret_cast<const uint4*>(a.gates) + r * 2 * 256 + threadIdx.x;
         const uint4 g01 = g4[0], g23 = g4[256];
         float4 c4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), cp4 = c4, dc4 = c4;
-        if (ntl > 1 || item == 0) c4 = reinterpret_cast<const float4*>(a.c)[r * 256 + threadIdx.x];   // (one tile: the c of this frame was the item before's c_prev)
+        if constexpr (MULTI) c4 = reinterpret_cast<const float4*>(a.c)[r * 256 + threadIdx.x];   // (one tile: the c of this frame was the item before's c_prev)
         if (n > 0) cp4 = reinterpret_cast<const float4*>(a.c)[rec_index(tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
-        if (n < T - 1 && ntl > 1) dc4 = reinterpret_cast<const float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x];   // (one tile: carried in registers)
+        if (MULTI && n < T - 1 && ntl > 1) dc4 = reinterpret_cast<const float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x];   // (one tile: carried in registers)
         if constexpr (WIDE_DY) {                         // piece lane % 32: row (lane % 32) / 4 of the wavefront's eight, units 8 (lane % 4) .. + 7
-            const int row = 2 * EPT * wave + (l32 >> 2);
-            in.dyr = make_uint4(0u, 0u, 0u, 0u);
-            if (FULL || b0 + row < B) in.dyr = *reinterpret_cast<const uint4*>(dyb + (size_t)row * 2 * H + d * H + u * 32 + (l32 & 3) * 8);
+            const int row0 = 2 * EPT * wave + (l32 >> 2), row = FULL ? row0 : min(row0, B - 1 - b0);
+            in.dyr = *reinterpret_cast<const uint4*>(dyb + (size_t)row * 2 * H + d * H + u * 32 + (l32 & 3) * 8);
         }
         static_assert(EPT == 4, "a record holds four cells");
-        in.g[0] = make_uint2(g01.x, g01.y); in.g[1] = make_uint2(g01.z, g01.w);
-        in.g[2] = make_uint2(g23.x, g23.y); in.g[3] = make_uint2(g23.z, g23.w);
-        in.c[0] = c4.x; in.c[1] = c4.y; in.c[2] = c4.z; in.c[3] = c4.w;
-        in.cp[0] = cp4.x; in.cp[1] = cp4.y; in.cp[2] = cp4.z; in.cp[3] = cp4.w;
-        in.dcr[0] = dc4.x; in.dcr[1] = dc4.y; in.dcr[2] = dc4.z; in.dcr[3] = dc4.w;
+        in.g01 = g01; in.g23 = g23; in.c = c4; in.cp = cp4; in.dcr = dc4;
+        if constexpr (!WIDE_DY) {
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const bool ok = FULL || b0 + rb + re(e) < B;
-            if constexpr (!WIDE_DY) in.dy[e] = ok ? dyb[o2b + (unsigned)(re(e) * 2 * H)] : (bf16_t)0;
-            if (!ok) { in.g[e] = make_uint2(0u, 0u); in.c[e] = 0.0f; in.cp[e] = 0.0f; in.dcr[e] = 0.0f; }
+            for (int e = 0; e < EPT; ++e) in.dy[e] = dyb[FULL ? o2b + (unsigned)(re(e) * 2 * H) : (unsigned)(min(rb + re(e), B - 1 - b0) * 2 * H) + o2c];
         }
     };
 
@@ -610,12 +599,15 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     const int nitems = T * ntl;
     Inputs in0, in1;                                     // two sets used in turn, as in the forward kernel
     issue_inputs(0, in0);
+    float4 cfirst = make_float4(0.0f, 0.0f, 0.0f, 0.0f);  // (one tile) the c of the first item, later ones are carried
+    if constexpr (!MULTI) cfirst = reinterpret_cast<const float4*>(a.c)[rec_index(d ? 0 : T - 1, d, gm.bg, NT, NU, u) * 256 + threadIdx.x];
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): see the forward kernel
     // One tile per workgroup: dE/dc of the frame visited before and that frame's c_prev (this frame's c) stay in
     // registers; a wavefront can have 63 vector-memory operations in flight, and an item of this kernel issues about 50.
     float dccarry[EPT], ccarry[EPT];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) { dccarry[e] = 0.0f; ccarry[e] = 0.0f; }
+    for (int e = 0; e < EPT; ++e) dccarry[e] = 0.0f;
+    ccarry[0] = cfirst.x; ccarry[1] = cfirst.y; ccarry[2] = cfirst.z; ccarry[3] = cfirst.w;
     uint4 apre[MULTI ? 8 : 1];                           // first slab of the next item, loaded ahead (several tiles only)
     bool have_pre = false;
     // NaN once this wave has abandoned a wait, or from the start if the abort word is already raised: added to
@@ -633,7 +625,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         bf16_t dyv[EPT];
         if constexpr (WIDE_DY) {
             bf16_t* dys = reinterpret_cast<bf16_t*>(lds + NW * 4 * 64 * 4 + NW * 512) + wave * 256;   // 512 bytes per wavefront: [row][unit]
-            if (lane < 32) reinterpret_cast<uint4*>(dys)[lane] = cur.dyr;
+            const uint4 dyr = cur.dyr;                    // (read before the branch: read inside it, the compiler keeps both sets of inputs in scratch memory)
+            if (lane < 32) reinterpret_cast<uint4*>(dys)[lane] = dyr;
 #pragma unroll
             for (int e = 0; e < EPT; ++e) dyv[e] = dys[(4 * lh + e) * 32 + l32];
         } else {
@@ -641,8 +634,6 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             for (int e = 0; e < EPT; ++e) dyv[e] = cur.dy[e];
         }
         if (n < T - 1) {
-            const int row = b0 + l32;
-            const bool valid = FULL || row < B;
             const bf16_t* ab = a.dax + ((size_t)(tn * 2 + d) * NT + (b0 >> 5)) * XA;   // uniform: the frame visited before, this tile
             const bf16_t* ap = ab + oap;
             f32x16_t acc;
@@ -651,8 +642,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             if (SENTINEL) {
                 // the gate rows of this wavefront come from KWB/32 producers: probe each one's last unit,
                 // then stream the slabs of 128 gate rows with the next slab's loads in flight
-                const int prow = FULL ? b0 + 31 : min(b0 + 31, B - 1);
-                const bf16_t* probe = ab + xoff(wave * KWB + (lane & (4 * KW / 32 - 1)) * 32 + 31, prow - b0);
+                const bf16_t* probe = ab + xoff(wave * KWB + (lane & (4 * KW / 32 - 1)) * 32 + 31, 31);
                 uint4 afrag[2][8];
                 bool got = false, gu = false;
                 if constexpr (MULTI) {
@@ -664,16 +654,16 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 }
                 if (!got) {
                     // (straight for the data, the probe only if the first look fails: see the forward kernel)
-                    load_chunks_cached<8>(afrag[0], ap, valid);
+                    load_chunks_cached<8>(afrag[0], ap);
                     if (!all_written<8>(afrag[0])) {
                         gu = wait_probe(probe, lane < 4 * KW / 32, a.abort_word, a.limit_ticks);
                         asm volatile("" ::: "memory");
-                        load_chunks<8>(afrag[0], ap, valid);
+                        load_chunks<8>(afrag[0], ap);
                     }
                 }
 #pragma unroll
                 for (int sl = 0; sl < KSTEPS / 8; ++sl) {
-                    if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + (sl + 1) * 8 * XPAIR, valid);
+                    if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + (sl + 1) * 8 * XPAIR);
                     else {
                         have_pre = false;
                         if constexpr (MULTI && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
@@ -682,14 +672,13 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                             if (n2 < T - 1) {
                                 const int tn2 = d ? T - 2 - n2 : n2 + 1;
                                 const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
-                                const bool valid2 = FULL || b02 + l32 < B;
                                 const bf16_t* ab2 = a.dax + ((size_t)(tn2 * 2 + d) * NT + (b02 >> 5)) * XA;
-                                load_chunks_cached<8>(apre, ab2 + oap, valid2);
+                                load_chunks_cached<8>(apre, ab2 + oap);
                                 have_pre = true;
                             }
                         }
                     }
-                    gu = ensure_written<8>(afrag[sl & 1], ap + sl * 8 * XPAIR, valid, gu, a.abort_word, a.limit_ticks);
+                    gu = ensure_written<8>(afrag[sl & 1], ap + sl * 8 * XPAIR, gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[sl & 1][q], bfrag[sl * 8 + q], acc);
                 }
@@ -701,7 +690,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                     uint4 afrag[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
-                        afrag[q] = valid ? *reinterpret_cast<const uint4*>(ap + (q0 + q) * XPAIR) : make_uint4(0, 0, 0, 0);
+                        afrag[q] = *reinterpret_cast<const uint4*>(ap + (q0 + q) * XPAIR);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[q], bfrag[q0 + q], acc);
                 }
@@ -726,26 +715,29 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                     dh[4 * e4] += v.x; dh[4 * e4 + 1] += v.y; dh[4 * e4 + 2] += v.z; dh[4 * e4 + 3] += v.w;
                 }
         }
+        const float curdcr[EPT] = {cur.dcr.x, cur.dcr.y, cur.dcr.z, cur.dcr.w}, curc[EPT] = {cur.c.x, cur.c.y, cur.c.z, cur.c.w};
+        const float curcp[EPT] = {cur.cp.x, cur.cp.y, cur.cp.z, cur.cp.w};
+        const uint2 curg[EPT] = {make_uint2(cur.g01.x, cur.g01.y), make_uint2(cur.g01.z, cur.g01.w), make_uint2(cur.g23.x, cur.g23.y), make_uint2(cur.g23.z, cur.g23.w)};
         float dcr[EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) dcr[e] = (ntl == 1) ? dccarry[e] : cur.dcr[e];
+        for (int e = 0; e < EPT; ++e) dcr[e] = (!MULTI || ntl == 1) ? dccarry[e] : curdcr[e];
         float cthis[EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) cthis[e] = (ntl == 1 && item > 0) ? ccarry[e] : cur.c[e];
+        for (int e = 0; e < EPT; ++e) cthis[e] = !MULTI ? ccarry[e] : curc[e];
         if (KW > 128 && item + 1 < nitems) issue_inputs(item + 1, nxt);
         float dcf[EPT];
         unsigned dav[EPT][2];                             // (i, f) and (g, o) as bf16 pairs: kept for the row-major copy below
         bf16_t* dxb = a.dax + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XA;
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const float gi = bf2f((bf16_t)(cur.g[e].x & 0xFFFFu)), gf = bf2f((bf16_t)(cur.g[e].x >> 16));
-            const float gg = bf2f((bf16_t)(cur.g[e].y & 0xFFFFu)), go = bf2f((bf16_t)(cur.g[e].y >> 16));
+            const float gi = bf2f((bf16_t)(curg[e].x & 0xFFFFu)), gf = bf2f((bf16_t)(curg[e].x >> 16));
+            const float gg = bf2f((bf16_t)(curg[e].y & 0xFFFFu)), go = bf2f((bf16_t)(curg[e].y >> 16));
             const float dht = dh[e] + bf2f(dyv[e]) + poison;
             const float tc = fast_tanh(cthis[e]);
             const float dc = dht * go * (1.0f - tc * tc) + dcr[e];
             const float da_o = dht * tc * go * (1.0f - go);
             const float da_i = dc * gg * gi * (1.0f - gi);
-            const float da_f = dc * cur.cp[e] * gf * (1.0f - gf);
+            const float da_f = dc * curcp[e] * gf * (1.0f - gf);
             const float da_g = dc * gi * (1.0f - gg * gg);
             dcf[e] = dc * gf;
             dav[e][0] = (unsigned)coh_bf16(da_i) | ((unsigned)coh_bf16(da_f) << 16);
@@ -775,7 +767,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         const int xrow = 2 * EPT * wave + 4 * xl + xr;    // row of the tile
         const bool xok = FULL || b0 + xrow < B;
         const unsigned xcol = (unsigned)(2 * xq * H + u * 32 + 8 * xk);   // column of gate 2 xq within the direction; + H: gate 2 xq + 1
-        if (xok) {
+        {
             bf16_t* pa = dxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u);
             bf16_t* pb = dxb + (((xcol + (unsigned)H) >> 3) * 256u + (unsigned)xrow * 8u);
             if (SENTINEL) { st_coh_16B(pa, cga); st_coh_16B(pb, cgb); }
@@ -795,7 +787,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             reinterpret_cast<float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x] = make_float4(dcf[0], dcf[1], dcf[2], dcf[3]);
         // next item's inputs; with one tile per workgroup its carried dE/dc is the one just computed
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) { dccarry[e] = dcf[e]; ccarry[e] = cur.cp[e]; }
+        for (int e = 0; e < EPT; ++e) { dccarry[e] = dcf[e]; ccarry[e] = curcp[e]; }
     };
     if constexpr (KW <= 128) {
         for (int item = 0; item < nitems; item += 2) {
@@ -925,17 +917,12 @@ hipError_t run_bwd(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched
 }  // namespace
 
 // Supported widths: H = 128, 256, 512 and 1024, always on four wavefronts that split the contraction
-// (32, 64, 128, 256 elements each: four batch rows per thread in every variant).  At H = 1024 the U_h
-// slice fills 256 registers per lane, which leaves no room for the predicates of a ragged batch, so
-// that width needs B to be a multiple of 32.  Returns the wavefronts per workgroup, 0 if unsupported.
+// (32, 64, 128, 256 elements each: four batch rows per thread in every variant), any batch size.
+// Returns the wavefronts per workgroup, 0 if unsupported.
 // Whether the forward kernel for this width also fills RecFwdArgs::fill (the widest one has no register to spare).
 bool rec_fwd_fills(int H) { return H == 128 || H == 256 || H == 512; }
 
-int rec_waves_for(int H, int B) {
-    if (H == 128 || H == 256 || H == 512) return 4;
-    if (H == 1024 && B % 32 == 0) return 4;
-    return 0;
-}
+int rec_waves_for(int H) { return H == 128 || H == 256 || H == 512 || H == 1024 ? 4 : 0; }
 
 hipError_t launch_fill_u32(unsigned* p, int n, unsigned v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -971,28 +958,26 @@ hipError_t launch_transpose_uh(const TransposeUhArgs& a, int H, hipStream_t st) 
 
 hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched) {
     *launched = false;
-    const int grid = 2 * a.nbg * (a.H / 32);
+    const int grid = grid_groups(a.nbg) * (a.H / 32);
     switch (a.H) {
         case 128: return sentinel ? run_fwd<4, 32, true>(a, grid, st, launched) : run_fwd<4, 32, false>(a, grid, st, launched);
         case 256: return sentinel ? run_fwd<4, 64, true>(a, grid, st, launched) : run_fwd<4, 64, false>(a, grid, st, launched);
         case 512: return sentinel ? run_fwd<4, 128, true>(a, grid, st, launched) : run_fwd<4, 128, false>(a, grid, st, launched);
         case 1024:
-            if (a.B % 32 != 0) return hipSuccess;
-            return sentinel ? run_fwd_as<4, 256, true, true>(a, grid, st, launched) : run_fwd_as<4, 256, false, true>(a, grid, st, launched);
+            return sentinel ? run_fwd<4, 256, true>(a, grid, st, launched) : run_fwd<4, 256, false>(a, grid, st, launched);
         default: return hipSuccess;
     }
 }
 
 hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched) {
     *launched = false;
-    const int grid = 2 * a.nbg * (a.H / 32);
+    const int grid = grid_groups(a.nbg) * (a.H / 32);
     switch (a.H) {
         case 128: return sentinel ? run_bwd<4, 32, true>(a, grid, st, launched) : run_bwd<4, 32, false>(a, grid, st, launched);
         case 256: return sentinel ? run_bwd<4, 64, true>(a, grid, st, launched) : run_bwd<4, 64, false>(a, grid, st, launched);
         case 512: return sentinel ? run_bwd<4, 128, true>(a, grid, st, launched) : run_bwd<4, 128, false>(a, grid, st, launched);
         case 1024:
-            if (a.B % 32 != 0) return hipSuccess;
-            return sentinel ? run_bwd_as<4, 256, true, true>(a, grid, st, launched) : run_bwd_as<4, 256, false, true>(a, grid, st, launched);
+            return sentinel ? run_bwd<4, 256, true>(a, grid, st, launched) : run_bwd<4, 256, false>(a, grid, st, launched);
         default: return hipSuccess;
     }
 }

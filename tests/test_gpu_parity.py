@@ -575,6 +575,18 @@ def test_wide_cells_against_oracle_reduced_depth():
     check_step(dict(T=5, B=96, D=260, H=1024, L=2, P=64, V=1000), 1, seed=4958, lr=0.2)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=4, B=1, D=8, H=512, L=1, P=0, V=20),             # one row of the tile's 32 exists
+    dict(T=4, B=33, D=8, H=256, L=2, P=16, V=20),           # one row of the second tile
+    dict(T=3, B=45, D=24, H=1024, L=2, P=0, V=40),          # the widest slice, last tile ragged
+    dict(T=3, B=150, D=24, H=1024, L=1, P=16, V=40),        # ... with two tiles per workgroup, an odd number of tiles
+    dict(T=3, B=1055, D=24, H=128, L=1, P=16, V=40),        # more tiles than groups, the last row of the last tile missing
+])
+@pytest.mark.parametrize("sync", [0, 1])
+def test_last_tile_of_the_batch_partly_filled(dims, sync):
+    check_step(dims, 1, seed=4959, theta_scale=2.0, recurrent_sync=sync)
+
+
 def test_adpsgd_workload_first_step_full_size():
     # one learner of the ADPSGD workload (batch 128 of the paper-shaped model) against the oracle in full
     w = inputs.WORKLOADS["adpsgd16"]
