@@ -61,6 +61,7 @@ struct blstm_ctx {
     std::vector<size_t> wY, wG, wC;
     std::vector<size_t> wDA;  // dE/da of every layer: all of them feed the weight-gradient products at the end of the backward pass
     size_t wAX, wPRE, wDY[2], wDH, wDC, wLOGITS, wROWLOSS, wUHT, wCNT, wPART, wHX, wDAX, hx_bytes, dax_bytes, part_bytes, ws_bytes;
+    long long ldu;            // row distance of the logit matrix in the workspace: V rounded up to whole 16-byte words
     int Dp;                   // 0, or the first layer's input width rounded up to whole tiles (padded copies of x and W_x)
     size_t wXP, wWP;
     int rec_nbg, rec_tiles;   // batch groups per direction and 32-row tiles per group of the persistent kernels
@@ -133,13 +134,17 @@ inline char* at(void* base, size_t elems, size_t esz) { return static_cast<char*
 
 // Scratch of the softmax cross-entropy: the logit matrix [M][V] (storage type, overwritten in place by dE/du),
 // one loss term per frame, and the float partial tiles of products split along K.
-struct SoftmaxScratch { char* logits; float* row_loss; float* partial; size_t partial_bytes; };
+// ldu: distance of the matrix's rows; V rounded up to 16 bytes wherever the scratch has the room (rows of a ragged V then
+// start aligned and the products run unguarded; the row kernel leaves zeros in the padding).
+struct SoftmaxScratch { char* logits; long long ldu; float* row_loss; float* partial; size_t partial_bytes; };
+inline bool padded_rows(long long V, long long ldu) { return ldu % 8 == 0 && ldu > V; }
 
 // dW_s = du^T z with db_s as the row sums of du^T (du [M][V] in the storage type, left by the row kernel).
-GemmDesc softmax_wgrad_desc(const blstm_ctx* ctx, const char* U, const void* z, float* grad) {
+GemmDesc softmax_wgrad_desc(const blstm_ctx* ctx, const char* U, long long ldu, const void* z, float* grad) {
     GemmDesc d = gemm_desc(ctx, ctx->st, DT_F32);
     d.M = ctx->V; d.N = ctx->zdim; d.atrans = true; d.btrans = true;
-    d.seg[0] = GemmSeg{U, z, ctx->V, ctx->zdim, 0, 0, ctx->M};
+    d.seg[0] = GemmSeg{U, z, ldu, ctx->zdim, 0, 0, ctx->M};
+    d.a_pad = padded_rows(ctx->V, ldu);
     d.C = grad + ctx->off_ws; d.ldc = ctx->zdim;
     d.rowsum = grad + ctx->off_bs;                     // db_s = sum over frames of du
     return d;
@@ -161,23 +166,24 @@ int softmax_xent_run(blstm_ctx* ctx, const SoftmaxScratch& sc, const void* theta
         GemmDesc d = desc(S, S);
         d.M = M; d.N = V;
         d.seg[0] = GemmSeg{z, at(theta, ctx->off_ws, e), Z, Z, 0, 0, Z};
-        d.C = U; d.ldc = V;
+        d.C = U; d.ldc = sc.ldu; d.c_pad = padded_rows(V, sc.ldu);
         d.bias = at(theta, ctx->off_bs, e);
         RUN(PC_GEMM_LOGITS, "logits", launch_gemm(d, st));
     }
-    RUN(PC_SOFTMAX_ROWS, "softmax rows", launch_softmax_rows(U, V, labels, sc.row_loss, M, V, ctx->s, S, st));
+    RUN(PC_SOFTMAX_ROWS, "softmax rows", launch_softmax_rows(U, sc.ldu, labels, sc.row_loss, M, V, ctx->s, S, st));
     RUN(PC_MISC, "loss sum", launch_sum_to_scalar(sc.row_loss, M, loss_dev, st));
     {   // dz = du W_s
         GemmDesc d = desc(S, S);
         d.M = M; d.N = Z; d.btrans = true;
-        d.seg[0] = GemmSeg{U, at(theta, ctx->off_ws, e), V, Z, 0, 0, V};
+        d.seg[0] = GemmSeg{U, at(theta, ctx->off_ws, e), sc.ldu, Z, 0, 0, V};
+        d.a_pad = padded_rows(V, sc.ldu);
         d.C = dz; d.ldc = Z;
         RUN(PC_GEMM_SOFTMAX_BWD, "dz", launch_gemm(d, st));
     }
     if (defer) { ctx->pend_z = z; ctx->pend_grad = grad; return BLSTM_OK; }
     ctx->pend_z = nullptr;
     {   // dW_s = du^T z
-        GemmDesc d = softmax_wgrad_desc(ctx, U, z, grad);
+        GemmDesc d = softmax_wgrad_desc(ctx, U, sc.ldu, z, grad);
         d.partial = sc.partial; d.partial_bytes = sc.partial_bytes;
         RUN(PC_GEMM_SOFTMAX_BWD, "dW_s", launch_gemm(d, st));
     }
@@ -266,13 +272,14 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->wDY[1] = w;   w += up256(M * 2 * H * e);
     c->wDH = w;      w += up256(2 * B * H * 4);
     c->wDC = w;      w += up256(2 * Br * H * 4);
-    c->wLOGITS = w;  w += up256(M * (size_t)c->V * e);
+    c->ldu = (c->V + 7) & ~7;
+    c->wLOGITS = w;  w += up256(M * (size_t)c->ldu * e);
     c->wROWLOSS = w; w += up256(M * 4);
-    // A feature width that is not a whole number of tiles (the paper's 260) would put the first layer's two
-    // products on the guarded kernel, three times slower: zero-padded bf16 copies of x and of W_x of layer 0
-    // (a few MB) keep them on the unguarded one.
+    // Rows of a feature width that is not a whole number of 16-byte words (the paper's 260) would put the first layer's
+    // two products on the guarded kernel, three times slower: zero-padded bf16 copies of x and of W_x of layer 0
+    // (a few MB), padded to whole tiles, keep them on the unguarded one.
     c->Dp = 0; c->wXP = w; c->wWP = w;
-    if (c->st == DT_BF16 && c->D % 128 != 0 && c->M % 128 == 0 && (4 * c->H) % 128 == 0) {
+    if (c->st == DT_BF16 && c->D % 8 != 0) {
         c->Dp = (c->D + 127) / 128 * 128;
         c->wXP = w; w += up256(M * (size_t)c->Dp * 2);
         c->wWP = w; w += up256((size_t)2 * 4 * H * c->Dp * 2);
@@ -490,7 +497,7 @@ int softmax_xent_fwd_bwd(blstm_ctx* ctx, const void* theta, const void* z, const
     if (!ctx->ws) return fail(BLSTM_ERR_WORKSPACE, "softmax_xent_fwd_bwd: no workspace bound");
     if (!aligned16(theta) || !aligned16(z) || !aligned16(dz) || !aligned16(grad))
         return fail(BLSTM_ERR_ALIGN, "softmax_xent_fwd_bwd: pointers must be 16-byte aligned");
-    SoftmaxScratch sc{ctx->ws + ctx->wLOGITS, reinterpret_cast<float*>(ctx->ws + ctx->wROWLOSS),
+    SoftmaxScratch sc{ctx->ws + ctx->wLOGITS, ctx->ldu, reinterpret_cast<float*>(ctx->ws + ctx->wROWLOSS),
                       reinterpret_cast<float*>(ctx->ws + ctx->wPART), ctx->part_bytes};
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), ctx->defer_ws);
 }
@@ -502,8 +509,8 @@ int softmax_xent_fwd_bwd_noalloc(blstm_ctx* ctx, const void* theta, const void* 
         return fail(BLSTM_ERR_ALIGN, "softmax_xent_fwd_bwd_noalloc: pointers must be 16-byte aligned");
     // layout of the resident array: logits, row losses, split-K partial tiles (whatever is left)
     const size_t logits = up256((size_t)ctx->M * (size_t)ctx->V * ctx->esz), rows = up256((size_t)ctx->M * 4);
-    size_t part = gemm_partial_bytes(ctx->M, ctx->zdim, ctx->V, 1, ctx->st);
-    const size_t part2 = gemm_partial_bytes(ctx->V, ctx->zdim, ctx->M, 1, ctx->st);
+    size_t part = noalloc_partial_bytes(ctx->M, ctx->zdim, ctx->V, ctx->st);
+    const size_t part2 = noalloc_partial_bytes(ctx->V, ctx->zdim, ctx->M, ctx->st);
     if (part2 > part) part = part2;
     part = up256(part);
     if (logits + rows + part > BLSTM_NOALLOC_SCRATCH_BYTES)
@@ -512,8 +519,12 @@ int softmax_xent_fwd_bwd_noalloc(blstm_ctx* ctx, const void* theta, const void* 
     char* base = nullptr;
     const int rc = resident_scratch(&base);
     if (rc != BLSTM_OK) return rc;
-    SoftmaxScratch sc{base, reinterpret_cast<float*>(base + logits), reinterpret_cast<float*>(base + logits + rows),
-                      BLSTM_NOALLOC_SCRATCH_BYTES - logits - rows};
+    // (rows padded to 16 bytes where that leaves the split-K scratch above untouched)
+    const size_t padded = up256((size_t)ctx->M * (size_t)ctx->ldu * ctx->esz);
+    const bool pad = padded + rows + part <= BLSTM_NOALLOC_SCRATCH_BYTES;
+    const size_t first = pad ? padded : logits;
+    SoftmaxScratch sc{base, pad ? ctx->ldu : ctx->V, reinterpret_cast<float*>(base + first), reinterpret_cast<float*>(base + first + rows),
+                      BLSTM_NOALLOC_SCRATCH_BYTES - first - rows};
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), false);
 }
 
@@ -675,7 +686,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     if (ctx->pend_z) {
         // the softmax layer's weight gradient, left to this call: dE/du still lies in the workspace.  It joins the
         // grouped launch when it can run there (else the whole group would run product by product).
-        const GemmDesc d = softmax_wgrad_desc(ctx, ctx->ws + ctx->wLOGITS, ctx->pend_z, grad);
+        const GemmDesc d = softmax_wgrad_desc(ctx, ctx->ws + ctx->wLOGITS, ctx->ldu, ctx->pend_z, grad);
         ctx->pend_z = nullptr;
         if (gemm_group_ok(&d, 1)) wgrads.push_back(d);
         else RUN(PC_GEMM_SOFTMAX_BWD, "dW_s", launch_gemm(d, st));

@@ -26,6 +26,7 @@
 // form can share one launch (gemm_group_kernel).
 #include "common.hpp"
 #include "gemm.hpp"
+#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -63,10 +64,17 @@ struct Params {
     float* partial;                 // split-K: float [batch][splits][M][N], or null
     float* rs_partial;              // split-K: float [batch][splits][M] row sums
     int M, N, ntm, ntn, splits;
+    int Nst;                        // columns the vector stores of C may write (N, or N rounded up where C is padded)
     int c_vec;                      // C rows may be written with 16-byte (float) / 8-byte (bf16) stores, whole tiles of them
     int p_vec;                      // the same for the float partial tiles of a split
     long long sA[2], sB[2], sC, sBias, sAdd, sRowsum;
 };
+
+// How a kernel treats the edges of its operands.  WHOLE: every tile lies inside the matrices and K is a whole number of
+// slabs, nothing is checked.  EDGE: the unguarded loops with the loads of rows beyond the matrix clamped to its last
+// row (or last 16-byte group of rows), the last slab's missing part cleared in LDS, and stores that stop at the
+// matrix.  GUARDED: every load checked, any alignment.
+enum { GUARDED = 0, WHOLE = 1, EDGE = 2 };
 
 // ---- guarded element-wise fallbacks ------------------------------------------------
 // 16-bit elements, NE of them, packed two per word
@@ -276,8 +284,11 @@ __device__ __forceinline__ void mma(f32x16_t& acc, const uint4& a, const uint4& 
 // sharing a CU take turns on the matrix cores (one multiplies while another reads its fragments).
 // `lin`, `split`, `z`: tile index within the product, K range and batch index of this workgroup; xcd_remap: lin is
 // the workgroup id of a launch of this product alone and is still to be regrouped by XCD (below).
-template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, bool FAST, bool RS, int D, int NS>
+template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, int MODE, bool RS, int D, int NS>
 __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int split, const int z, const bool xcd_remap) {
+    constexpr bool FAST = MODE != GUARDED;
+    static_assert(MODE != EDGE || NS > 0 || sizeof(TI) == 4, "staged 16-bit operands are guarded or whole");
+    static_assert(MODE != EDGE || NS > 0 || WN == 2, "the staged edge form uses the 256-thread guarded loads for its last slab");
     static_assert(NS == 0 || (FAST && sizeof(TI) == 2 && D == 2), "direct mode is built for the unguarded 16-bit form");
     static_assert(D == 2 || (D == 4 && FAST && WN == 2), "the deep pipeline exists for the unguarded 128x128 tile only");
     static_assert(WN == 2 || (FAST && !RS), "the eight-wave shape exists in the unguarded form only");
@@ -434,11 +445,13 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
             const int jj = j * NWV + wv;
             if constexpr (AT) {
                 const int kt = (64 / CPR_A) * jj + lane / CPR_A, pos = lane % CPR_A;
-                const int mc = ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                int mc = ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                if constexpr (MODE == EDGE) mc = min(mc, (P.M - 1 - row0) >> 3);
                 voa[j] = (unsigned)(kt * a0.ld * ES + mc * 16);
             } else {
                 const int r = 8 * jj + (lane >> 3);
-                voa[j] = (unsigned)(r * a0.ld * ES + (((lane & 7) ^ swz(r)) << 4));
+                const int rc = MODE == EDGE ? min(r, P.M - 1 - row0) : r;
+                voa[j] = (unsigned)(rc * a0.ld * ES + (((lane & 7) ^ swz(r)) << 4));
             }
         }
 #pragma unroll
@@ -446,17 +459,19 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
             const int jj = j * NWV + wv;
             if constexpr (BT) {
                 const int kt = (64 / CPR_B) * jj + lane / CPR_B, pos = lane % CPR_B;
-                const int mc = ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                int mc = ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                if constexpr (MODE == EDGE) mc = min(mc, (P.N - 1 - col0) >> 3);
                 vob[j] = (unsigned)(kt * b0.ld * ES + mc * 16);
             } else {
                 const int r = 8 * jj + (lane >> 3);
-                vob[j] = (unsigned)(r * b0.ld * ES + (((lane & 7) ^ swz(r)) << 4));
+                const int rc = MODE == EDGE ? min(r, P.N - 1 - col0) : r;
+                vob[j] = (unsigned)(rc * b0.ld * ES + (((lane & 7) ^ swz(r)) << 4));
             }
         }
         auto dma = [](unsigned lds_addr, const char* gbase, unsigned voff) __attribute__((always_inline)) {
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(gbase) : "memory");
         };
-        auto issue = [&](int it) __attribute__((always_inline)) {
+        auto issue = [&](int it, auto may_be_part) __attribute__((always_inline)) {
             const bool s2 = it >= ntiles[0];
             const int k0 = (it - (s2 ? ntiles[0] : 0)) * BK;
             const char* pa = static_cast<const char*>(s2 ? a1.p : a0.p);
@@ -465,23 +480,68 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
             pa += AT ? ((long long)k0 * lda + row0) * ES : ((long long)row0 * lda + k0) * ES;
             pb += BT ? ((long long)k0 * ldb + col0) * ES : ((long long)col0 * ldb + k0) * ES;
             const unsigned sb = lds0 + (unsigned)(((it - it_begin) % NS) * STAGE * 16);
+            if constexpr (decltype(may_be_part)::value) {
+                const int left = (s2 ? K1 : K0) - k0;          // uniform
+                if (left < BK) {
+                    // k-rows (k slow in memory) or 16-byte chunks (k fast) that start beyond the contraction repeat the last
+                    // one; zero_tail clears their LDS slots once the loads have landed (a chunk that straddles the end lies
+                    // in rows padded with finite values, and the other operand's k-rows there are cleared)
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));           // (computed here, not ahead of the loop: its registers are all taken)
+#pragma unroll
+                    for (int j = 0; j < NIA; ++j) {
+                        const int jj = j * NWV + wv;
+                        const int over = AT ? max((64 / CPR_A) * jj + ln / CPR_A - (left - 1), 0) : max(((ln & 7) ^ swz(8 * jj + (ln >> 3))) - ((left - 1) >> 3), 0);
+                        dma(sb + (unsigned)((j * NWV + wv) * 1024), pa, voa[j] - (unsigned)over * (unsigned)(AT ? lda * ES : 16));
+                    }
+#pragma unroll
+                    for (int j = 0; j < NIB; ++j) {
+                        const int jj = j * NWV + wv;
+                        const int over = BT ? max((64 / CPR_B) * jj + ln / CPR_B - (left - 1), 0) : max(((ln & 7) ^ swz(8 * jj + (ln >> 3))) - ((left - 1) >> 3), 0);
+                        dma(sb + (unsigned)(BM * 128 + (j * NWV + wv) * 1024), pb, vob[j] - (unsigned)over * (unsigned)(BT ? ldb * ES : 16));
+                    }
+                    return;
+                }
+            }
 #pragma unroll
             for (int j = 0; j < NIA; ++j) dma(sb + (unsigned)((j * NWV + wv) * 1024), pa, voa[j]);
 #pragma unroll
             for (int j = 0; j < NIB; ++j) dma(sb + (unsigned)(BM * 128 + (j * NWV + wv) * 1024), pb, vob[j]);
+        };
+        // The slots of slab `it` beyond its contraction, cleared between the barrier behind its loads and the fragment reads
+        // (EDGE, last slab of a segment only; every thread of the workgroup takes the same branch).
+        auto zero_tail = [&](int it, uint4* a_s) __attribute__((always_inline)) {
+            if constexpr (MODE == EDGE) {
+                const bool s2 = it >= ntiles[0];
+                const int left = (s2 ? K1 : K0) - (it - (s2 ? ntiles[0] : 0)) * BK;
+                if (left >= BK) return;
+                const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
+                int t0 = tid;
+                asm volatile("" : "+v"(t0));               // (as in issue)
+                uint4* b_s = a_s + BM * CHUNKS;
+                if constexpr (AT) { for (int c = left * CPR_A + t0; c < BK * CPR_A; c += NT) a_s[c] = z4; }
+                else { for (int c = t0; c < BM * CHUNKS; c += NT) if ((c & 7) * VEC >= left) a_s[(c & ~7) | ((c & 7) ^ swz(c >> 3))] = z4; }
+                if constexpr (BT) { for (int c = left * CPR_B + t0; c < BK * CPR_B; c += NT) b_s[c] = z4; }
+                else { for (int c = t0; c < BN * CHUNKS; c += NT) if ((c & 7) * VEC >= left) b_s[(c & ~7) | ((c & 7) ^ swz(c >> 3))] = z4; }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
         };
         if constexpr (NS == 1) {
             // One LDS buffer: a slab's fragments are all read into registers, a barrier frees the buffer for the next
             // slab's loads, and the products run from registers while those loads are in flight.  Two workgroups per
             // CU take turns on the matrix cores: one multiplies while the other reads its fragments.
             uint4 fa[CHUNKS / 2][TM], fb[CHUNKS / 2][TN];
-            if (nslab > 0) issue(it_begin);
+            constexpr std::integral_constant<bool, MODE == EDGE> any{};
+            constexpr std::false_type whole{};
+            auto part = [&](int it) { return MODE == EDGE && (it >= ntiles[0] ? K1 - (it - ntiles[0]) * BK : K0 - it * BK) < BK; };
+            if (nslab > 0) issue(it_begin, any);
             for (int it = it_begin; it < it_end; ++it) {
                 asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+                zero_tail(it, smem);
 #pragma unroll
                 for (int q = 0; q < CHUNKS / 2; ++q) lfrag(smem, smem + BM * CHUNKS, q, fa[q], fb[q]);
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                if (it + 1 < it_end) issue(it + 1);
+                if (it + 1 < it_end && !part(it + 1)) issue(it + 1, whole);
 #pragma unroll
                 for (int q = 0; q < CHUNKS / 2; ++q) {
 #pragma unroll
@@ -493,12 +553,14 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
                         for (int i = 0; i < NRS; ++i) rs[i] = add_row(rs[i], fa[q][i]);
                     }
                 }
+                // (a part of a slab only now: its clamped addresses need registers that the fragments held)
+                if (MODE == EDGE && it + 1 < it_end && part(it + 1)) issue(it + 1, any);
             }
             __syncthreads();
         } else {
 #pragma unroll
         for (int u = 0; u < NS - 1; ++u)
-            if (nslab > u) issue(it_begin + u);
+            if (nslab > u) issue(it_begin + u, std::integral_constant<bool, MODE == EDGE>{});
         for (int it = it_begin; it < it_end; ++it) {
             // this wavefront's loads of slab `it` have landed when at most the loads of the younger slabs are outstanding
             if constexpr (NS == 2) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
@@ -509,7 +571,8 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
                 else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(2 * (NIA + NIB)) : "memory");
             }
             // (behind the barrier every wavefront has finished the products of slab it - 1, whose buffer the next loads overwrite)
-            if (it + NS - 1 < it_end) issue(it + NS - 1);
+            if (it + NS - 1 < it_end) issue(it + NS - 1, std::integral_constant<bool, MODE == EDGE>{});
+            zero_tail(it, smem + ((it - it_begin) % NS) * STAGE);
             const uint4* a_s = smem + ((it - it_begin) % NS) * STAGE;
             const uint4* b_s = a_s + BM * CHUNKS;
             constexpr int NF = (TM * TN <= 4) ? 2 : 1;
@@ -535,13 +598,39 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     // D sets of staging registers: the loads of slab it + D are issued while slab it is multiplied and
     // slabs it + 1 .. it + D - 1 (loaded in earlier iterations) wait in the other sets for their LDS buffer.
     uint4 ra[D][NCA], rb[D][NCB];
-    auto gload = [&](int it, uint4 (&ra)[NCA], uint4 (&rb)[NCB]) {
+    // EDGE (float): this thread's byte offsets per pass, rows clamped
+    constexpr bool STE = MODE == EDGE;
+    uint32_t voe_a[STE ? NCA : 1], voe_b[STE ? NCB : 1];
+    if constexpr (STE) {
+#pragma unroll
+        for (int i = 0; i < NCA; ++i)
+            voe_a[i] = AT ? (uint32_t)((kch * VEC + (i & 3)) * a0.ld * ES + min(rsub + (i >> 2) * PR, ((P.M + 3) & ~3) - 4 - row0) * ES)
+                          : (uint32_t)(min((tid >> 3) + RP * i, P.M - 1 - row0) * a0.ld * ES + (tid & 7) * 16);
+#pragma unroll
+        for (int i = 0; i < NCB; ++i)
+            voe_b[i] = BT ? (uint32_t)((kch * VEC + (i & 3)) * b0.ld * ES + min(rsub + (i >> 2) * PR, ((P.N + 3) & ~3) - 4 - col0) * ES)
+                          : (uint32_t)(min((tid >> 3) + RP * i, P.N - 1 - col0) * b0.ld * ES + (tid & 7) * 16);
+    }
+    auto gload = [&](int it, const bool inner, uint4 (&ra)[NCA], uint4 (&rb)[NCB]) __attribute__((always_inline)) {   // inner: surely not the last slab
         const bool s = it >= ntiles[0];
         const int k0 = (it - (s ? ntiles[0] : 0)) * BK;
         Operand oa, ob;
         oa.p = s ? a1.p : a0.p; oa.ld = s ? a1.ld : a0.ld; oa.rows = a0.rows; oa.fast = s ? a1.fast : a0.fast;
         ob.p = s ? b1.p : b0.p; ob.ld = s ? b1.ld : b0.ld; ob.rows = b0.rows; ob.fast = s ? b1.fast : b0.fast;
-        if constexpr (FAST) {
+        if constexpr (STE) {
+            const int K = s ? K1 : K0;
+            if (inner || k0 + BK <= K) {
+                const char* pa = static_cast<const char*>(oa.p) + (AT ? ((long long)k0 * oa.ld + row0) * ES : ((long long)row0 * oa.ld + k0) * ES);
+                const char* pb = static_cast<const char*>(ob.p) + (BT ? ((long long)k0 * ob.ld + col0) * ES : ((long long)col0 * ob.ld + k0) * ES);
+#pragma unroll
+                for (int i = 0; i < NCA; ++i) { const u32x4_t v = *reinterpret_cast<const u32x4_t*>(pa + voe_a[i]); ra[i] = make_uint4(v[0], v[1], v[2], v[3]); }
+#pragma unroll
+                for (int i = 0; i < NCB; ++i) { const u32x4_t v = *reinterpret_cast<const u32x4_t*>(pb + voe_b[i]); rb[i] = make_uint4(v[0], v[1], v[2], v[3]); }
+            } else {
+                if constexpr (AT) gload_rowfast<TI, NCA>(ra, oa, row0, K, k0, tid); else gload_kfast<TI, NCA>(ra, oa, row0, K, k0, tid);
+                if constexpr (BT) gload_rowfast<TI, NCB>(rb, ob, col0, K, k0, tid); else gload_kfast<TI, NCB>(rb, ob, col0, K, k0, tid);
+            }
+        } else if constexpr (FAST) {
             // (both segments of a two-segment product share their leading dimensions in this mode)
             const char* pa = static_cast<const char*>(oa.p);
             const char* pb = static_cast<const char*>(ob.p);
@@ -570,12 +659,12 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
         else sstore_kfast_off<NCB, RP>(b_s, rb, soff_k);
     };
     if (nslab > 0) {
-        gload(it_begin, ra[0], rb[0]);
+        gload(it_begin, false, ra[0], rb[0]);
         sstore(0, ra[0], rb[0]);
     }
 #pragma unroll
     for (int u = 1; u < D; ++u)
-        if (nslab > u) gload(it_begin + u, ra[u], rb[u]);
+        if (nslab > u) gload(it_begin + u, false, ra[u], rb[u]);
     __syncthreads();
     // slab j = it - it_begin lives in LDS buffer j & 1 and was staged through register set j % D
     // `steady`: slabs it + 1 and it + D exist for sure, so the loads and the LDS stores are unconditional
@@ -584,7 +673,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     auto step = [&](int it, const bool steady, uint4 (&ra_cur)[NCA], uint4 (&rb_cur)[NCB], const uint4 (&ra_nxt)[NCA],
                     const uint4 (&rb_nxt)[NCB]) __attribute__((always_inline)) {
         const int buf = (it - it_begin) & 1;
-        if (steady || it + D < it_end) gload(it + D, ra_cur, rb_cur);
+        if (steady || it + D < it_end) gload(it + D, steady, ra_cur, rb_cur);
         const uint4* a_s = smem + buf * STAGE;
         const uint4* b_s = a_s + BM * CHUNKS;
         // the 64x64 wave tile keeps two sets of fragments in flight
@@ -608,7 +697,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
         __syncthreads();
     };
     int it = it_begin;
-    for (; it + 2 * D - 1 < it_end; it += D) {
+    for (; it + 2 * D - (STE ? 0 : 1) < it_end; it += D) {   // (EDGE: the last slab is loaded outside the steady loop)
 #pragma unroll
         for (int u = 0; u < D; ++u) step(it + u, true, ra[u], rb[u], ra[(u + 1) % D], rb[(u + 1) % D]);
     }
@@ -661,7 +750,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const int col = wn * (32 * TN) + j * 32 + (lane & 31);
-                    const float bv = bz ? ld_f(bz + col0 + col) : 0.0f;
+                    const float bv = bz && (MODE != EDGE || col0 + col < P.N) ? ld_f(bz + col0 + col) : 0.0f;
 #pragma unroll
                     for (int ib = 0; ib < IBR; ++ib) {
                         const int i = h * IBR + ib;
@@ -676,17 +765,21 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
                 if (to_part) {
                     const int g = tid % GPR;
                     float* dst0 = part + (long long)row0 * P.N + col0 + 4 * g;
+                    if (MODE == EDGE && col0 + 4 * g >= P.N) continue;
 #pragma unroll 4
                     for (int pass = 0; pass < RR / RPP; ++pass) {
                         const int r = pass * RPP + tid / GPR;
+                        if (MODE == EDGE && row0 + tile_row(r, h) >= P.M) continue;
                         *reinterpret_cast<float4*>(dst0 + (long long)tile_row(r, h) * P.N) = *reinterpret_cast<const float4*>(&cs[r * BN + ((g ^ (r & 7)) << 2)]);
                     }
                 } else if (sizeof(TO) == 2 && P.c_vec == 2) {   // eight bf16 per lane: 16-byte stores
                     const int g = tid % GPR8;
                     TO* dst0 = Cz + (long long)row0 * P.ldc + col0 + 8 * g;
+                    if (MODE == EDGE && col0 + 8 * g >= P.Nst) continue;
 #pragma unroll 4
                     for (int pass = 0; pass < RR / RPP8; ++pass) {
                         const int r = pass * RPP8 + tid / GPR8;
+                        if (MODE == EDGE && row0 + tile_row(r, h) >= P.M) continue;
                         const float4 v = *reinterpret_cast<const float4*>(&cs[r * BN + (((2 * g) ^ (r & 7)) << 2)]);
                         const float4 w = *reinterpret_cast<const float4*>(&cs[r * BN + (((2 * g + 1) ^ (r & 7)) << 2)]);
                         *reinterpret_cast<uint4*>(dst0 + (long long)tile_row(r, h) * P.ldc) =
@@ -695,9 +788,11 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
                 } else {
                     const int g = tid % GPR;
                     TO* dst0 = Cz + (long long)row0 * P.ldc + col0 + 4 * g;
+                    if (MODE == EDGE && col0 + 4 * g >= P.Nst) continue;
 #pragma unroll 4
                     for (int pass = 0; pass < RR / RPP; ++pass) {
                         const int r = pass * RPP + tid / GPR;
+                        if (MODE == EDGE && row0 + tile_row(r, h) >= P.M) continue;
                         const float4 v = *reinterpret_cast<const float4*>(&cs[r * BN + ((g ^ (r & 7)) << 2)]);
                         TO* dst = dst0 + (long long)tile_row(r, h) * P.ldc;
                         if constexpr (sizeof(TO) == 4) *reinterpret_cast<float4*>(dst) = v;
@@ -754,9 +849,9 @@ constexpr int occupancy_target() {
     return D == 2 ? 2 : 1;
 }
 
-template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, bool FAST, bool RS, int D, int NS>
+template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, int MODE, bool RS, int D, int NS>
 __global__ __launch_bounds__(128 * WN, (occupancy_target<TM, TN, WN, D, NS>())) void gemm_kernel(Params P) {
-    gemm_tile<TI, TO, AT, BT, TM, TN, WN, FAST, RS, D, NS>(P, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, true);
+    gemm_tile<TI, TO, AT, BT, TM, TN, WN, MODE, RS, D, NS>(P, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, true);
 }
 
 // Several independent products of one form in one launch (the weight gradients of all layers).  All tiles of all
@@ -772,7 +867,7 @@ struct GroupParams {
     int n;
 };
 static_assert(sizeof(GroupParams) <= 4096, "kernel arguments are limited to 4 KB");
-template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, bool FAST, bool RS, int D, int NS>
+template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, int MODE, bool RS, int D, int NS>
 __global__ __launch_bounds__(128 * WN, (occupancy_target<TM, TN, WN, D, NS>())) void gemm_group_kernel(GroupParams G) {
     int x = (int)blockIdx.x;
     const int total8 = G.first[G.n] & ~7;
@@ -781,7 +876,7 @@ __global__ __launch_bounds__(128 * WN, (occupancy_target<TM, TN, WN, D, NS>())) 
     for (int k = 1; k < G.n; ++k) if (x >= G.first[k]) g = k;
     const Params& P = G.p[g];
     const int local = x - G.first[g], per = P.ntm * P.ntn;
-    gemm_tile<TI, TO, AT, BT, TM, TN, WN, FAST, RS, D, NS>(P, local % per, 0, local / per, false);
+    gemm_tile<TI, TO, AT, BT, TM, TN, WN, MODE, RS, D, NS>(P, local % per, 0, local / per, false);
 }
 
 // C[m][n] = sum over splits of partial[z][s][m][n] (+ bias[n]) in the order s = 0, 1, ...
@@ -854,93 +949,120 @@ hipError_t allow_lds(K kernel, size_t lds, bool* done) {
     return e;
 }
 
-template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, bool FAST, bool RS, int D = 2, int NS = 0>
+template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, int MODE, bool RS, int D = 2, int NS = 0>
 hipError_t launch_kernel(const Params& P, dim3 grid, hipStream_t stream) {
     constexpr size_t lds = (NS > 0 ? NS : 2) * (size_t)(64 * TM + 32 * TN * WN) * CHUNKS * 16;
     static thread_local bool attr_set = false;
-    hipError_t e = allow_lds(&gemm_kernel<TI, TO, AT, BT, TM, TN, WN, FAST, RS, D, NS>, lds, &attr_set);
+    hipError_t e = allow_lds(&gemm_kernel<TI, TO, AT, BT, TM, TN, WN, MODE, RS, D, NS>, lds, &attr_set);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemm_kernel<TI, TO, AT, BT, TM, TN, WN, FAST, RS, D, NS>), grid, dim3(128 * WN), lds, stream, P);
+    hipLaunchKernelGGL((gemm_kernel<TI, TO, AT, BT, TM, TN, WN, MODE, RS, D, NS>), grid, dim3(128 * WN), lds, stream, P);
     return hipGetLastError();
 }
 
-// ---- register-staged kernels: float operands, guarded shapes, the A^T B^T... forms the direct mode does not build ----
+// ---- register-staged kernels: float operands, and bf16 operands the direct mode does not take ----------------------
+// deep: four sets of staging registers (whole tiles of the dA^T X form, where it pays).
+template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN, bool RS>
+hipError_t launch_staged_rs(const Params& P, int mode, bool deep, dim3 grid, hipStream_t stream) {
+    if constexpr (AT && BT) {
+        if (mode == WHOLE && deep) return launch_kernel<TI, TO, AT, BT, TM, TN, WN, WHOLE, RS, 4>(P, grid, stream);
+    }
+    if (mode == WHOLE) return launch_kernel<TI, TO, AT, BT, TM, TN, WN, WHOLE, RS>(P, grid, stream);
+    if constexpr (sizeof(TI) == 4) {
+        if (mode == EDGE) return launch_kernel<TI, TO, AT, BT, TM, TN, WN, EDGE, RS>(P, grid, stream);
+    }
+    if (mode == EDGE) return hipErrorInvalidValue;
+    return launch_kernel<TI, TO, AT, BT, TM, TN, WN, GUARDED, RS>(P, grid, stream);
+}
 template <typename TI, typename TO, bool AT, bool BT, int TM, int TN, int WN>
-hipError_t launch_shape(const Params& P, bool fast, bool deep, dim3 grid, hipStream_t stream) {
+hipError_t launch_shape(const Params& P, int mode, bool deep, dim3 grid, hipStream_t stream) {
     if constexpr (WN != 2) {
-        if (P.rowsum || !fast) return hipErrorInvalidValue;   // the large tile is built unguarded and without row sums
-        return launch_kernel<TI, TO, AT, BT, TM, TN, WN, true, false>(P, grid, stream);
+        if (P.rowsum || mode != WHOLE) return hipErrorInvalidValue;   // the large tile is built for whole tiles and without row sums
+        return launch_kernel<TI, TO, AT, BT, TM, TN, WN, WHOLE, false>(P, grid, stream);
     } else {
-        if constexpr (AT && BT) {
-            if (P.rowsum) {
-                if (fast && deep) return launch_kernel<TI, TO, AT, BT, TM, TN, WN, true, true, 4>(P, grid, stream);
-                return fast ? launch_kernel<TI, TO, AT, BT, TM, TN, WN, true, true>(P, grid, stream)
-                            : launch_kernel<TI, TO, AT, BT, TM, TN, WN, false, true>(P, grid, stream);
-            }
+        if constexpr (AT && BT) {                             // row sums exist for the dA^T X form on 128x128 tiles only
+            if (P.rowsum) return launch_staged_rs<TI, TO, AT, BT, TM, TN, WN, true>(P, mode, deep, grid, stream);
         }
-        if (P.rowsum) return hipErrorInvalidValue;           // row sums exist for the dA^T X form on 128x128 tiles only
-        if constexpr (AT && BT) {                             // (the deep pipeline is built for the dA^T X form, where it pays)
-            if (fast && deep) return launch_kernel<TI, TO, AT, BT, TM, TN, WN, true, false, 4>(P, grid, stream);
-        }
-        return fast ? launch_kernel<TI, TO, AT, BT, TM, TN, WN, true, false>(P, grid, stream)
-                    : launch_kernel<TI, TO, AT, BT, TM, TN, WN, false, false>(P, grid, stream);
+        if (P.rowsum) return hipErrorInvalidValue;
+        return launch_staged_rs<TI, TO, AT, BT, TM, TN, WN, false>(P, mode, deep, grid, stream);
     }
 }
 
 template <typename TI, typename TO, int TM, int TN, int WN>
-hipError_t launch_form(const GemmDesc& d, const Params& P, bool fast, bool deep, dim3 grid, hipStream_t stream) {
-    if (!d.atrans && !d.btrans) return launch_shape<TI, TO, false, false, TM, TN, WN>(P, fast, deep, grid, stream);
-    if (!d.atrans && d.btrans) return launch_shape<TI, TO, false, true, TM, TN, WN>(P, fast, deep, grid, stream);
-    if (d.atrans && d.btrans) return launch_shape<TI, TO, true, true, TM, TN, WN>(P, fast, deep, grid, stream);
-    return launch_shape<TI, TO, true, false, TM, TN, WN>(P, fast, deep, grid, stream);
+hipError_t launch_form(const GemmDesc& d, const Params& P, int mode, bool deep, dim3 grid, hipStream_t stream) {
+    if (!d.atrans && !d.btrans) return launch_shape<TI, TO, false, false, TM, TN, WN>(P, mode, deep, grid, stream);
+    if (!d.atrans && d.btrans) return launch_shape<TI, TO, false, true, TM, TN, WN>(P, mode, deep, grid, stream);
+    if (d.atrans && d.btrans) return launch_shape<TI, TO, true, true, TM, TN, WN>(P, mode, deep, grid, stream);
+    return launch_shape<TI, TO, true, false, TM, TN, WN>(P, mode, deep, grid, stream);
 }
 
 // ---- direct-mode kernels: bf16 operands, unguarded, forms X W^T, dA W and dA^T X -------------------------------
 // variant 0: 128x128 tile, two LDS buffers, two workgroups per CU; 1: 128x128, three buffers (launches of at most one
 // workgroup per CU); 2: 256x128 tile, one buffer, fragments in registers, two workgroups per CU; 3: 256x256 tile on
 // eight wavefronts, two buffers, one workgroup per CU (the dA W form only: the softmax layer's input gradient).
-template <typename TO, bool AT, bool BT, bool RS>
+template <typename TO, bool AT, bool BT, bool RS, int MODE>
 hipError_t launch_direct_rs(const Params& P, int variant, dim3 grid, hipStream_t stream) {
-    if (variant == 2) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 2, true, RS, 2, 1>(P, grid, stream);
+    if (variant == 2) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 2, MODE, RS, 2, 1>(P, grid, stream);
     if constexpr (!AT && BT && !RS) {
-        if (variant == 3) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 4, true, false, 2, 2>(P, grid, stream);
+        if (variant == 3) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 4, MODE, false, 2, 2>(P, grid, stream);
     }
     if (variant == 3) return hipErrorInvalidValue;
     if constexpr (AT && BT) {
-        if (variant == 1) return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, true, RS, 2, 3>(P, grid, stream);
+        if (variant == 1) return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, MODE, RS, 2, 3>(P, grid, stream);
     }
-    return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, true, RS, 2, 2>(P, grid, stream);
+    return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, MODE, RS, 2, 2>(P, grid, stream);
 }
-template <typename TO>
-hipError_t launch_direct(const GemmDesc& d, const Params& P, int variant, dim3 grid, hipStream_t stream) {
+template <typename TO, int MODE>
+hipError_t launch_direct_mode(const GemmDesc& d, const Params& P, int variant, dim3 grid, hipStream_t stream) {
     if (d.atrans && d.btrans) {
         if constexpr (sizeof(TO) == 4) {                      // (row sums go with the float weight gradients)
-            if (P.rowsum) return launch_direct_rs<TO, true, true, true>(P, variant, grid, stream);
+            if (P.rowsum) return launch_direct_rs<TO, true, true, true, MODE>(P, variant, grid, stream);
         }
         if (P.rowsum) return hipErrorInvalidValue;
-        return launch_direct_rs<TO, true, true, false>(P, variant, grid, stream);
+        return launch_direct_rs<TO, true, true, false, MODE>(P, variant, grid, stream);
     }
     if (P.rowsum) return hipErrorInvalidValue;
-    if (!d.atrans && d.btrans) return launch_direct_rs<TO, false, true, false>(P, variant, grid, stream);
-    if (!d.atrans && !d.btrans) return launch_direct_rs<TO, false, false, false>(P, variant, grid, stream);
+    if (!d.atrans && d.btrans) return launch_direct_rs<TO, false, true, false, MODE>(P, variant, grid, stream);
+    if (!d.atrans && !d.btrans) return launch_direct_rs<TO, false, false, false, MODE>(P, variant, grid, stream);
     return hipErrorInvalidValue;
 }
+template <typename TO>
+hipError_t launch_direct(const GemmDesc& d, const Params& P, int mode, int variant, dim3 grid, hipStream_t stream) {
+    return mode == WHOLE ? launch_direct_mode<TO, WHOLE>(d, P, variant, grid, stream) : launch_direct_mode<TO, EDGE>(d, P, variant, grid, stream);
+}
 
-// The unguarded kernel applies when every tile is full, every segment's K is a whole number of
-// slabs, all loads may be of the widest kind, the per-thread offsets fit 32 bits, and the two
-// segments (if any) share their leading dimensions.
+inline bool direct_form(const GemmDesc& d) { return d.in_type == DT_BF16 && !d.add && !(d.atrans && !d.btrans); }
+
+// How the kernel of this tile shape runs the product.  Both unguarded forms need loads of the widest kind, per-thread
+// offsets in 32 bits and (two segments) common leading dimensions.  WHOLE: only whole tiles and slabs.  EDGE (direct
+// bf16 kernels, and float operands on the 128x128 tile): any M, N and K whose 16-byte groups lie in memory: a row-fast
+// operand's rows come in whole groups or it is padded to them; so does a k-fast bf16 operand's contraction, unless it is
+// padded and the other operand is row-fast (whose k-rows beyond the end are replaced by zeros).
 template <typename TI>
-bool can_run_fast(const GemmDesc& d, const Params& P, int tile_m, int tile_n) {
-    const int bk = CHUNKS * Vec<TI>::N;
-    if (d.M % tile_m || (d.Npad > 0 ? d.Npad : d.N) % tile_n) return false;
+int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n) {
+    constexpr int VEC = Vec<TI>::N, bk = CHUNKS * VEC;
+    const int Ne = d.Npad > 0 ? d.Npad : d.N;
+    bool whole = d.M % tile_m == 0 && Ne % tile_n == 0;
     for (int s = 0; s < d.nseg; ++s) {
-        if (d.seg[s].K % bk) return false;
-        if (!(P.A[s].fast & 1) || !(P.B[s].fast & 1)) return false;
-        if (sizeof(TI) == 2 && ((d.atrans && !(P.A[s].fast & 4)) || (d.btrans && !(P.B[s].fast & 4)))) return false;
-        if (d.seg[s].lda != d.seg[0].lda || d.seg[s].ldb != d.seg[0].ldb) return false;
-        if (d.seg[s].lda * (long long)sizeof(TI) * 64 > 0x3FFFFFFF || d.seg[s].ldb * (long long)sizeof(TI) * 64 > 0x3FFFFFFF) return false;
+        if (!(P.A[s].fast & 1) || !(P.B[s].fast & 1)) return GUARDED;
+        if (sizeof(TI) == 2 && ((d.atrans && !(P.A[s].fast & 4)) || (d.btrans && !(P.B[s].fast & 4)))) return GUARDED;
+        if (d.seg[s].lda != d.seg[0].lda || d.seg[s].ldb != d.seg[0].ldb) return GUARDED;
+        if (d.seg[s].lda * (long long)sizeof(TI) * 64 > 0x3FFFFFFF || d.seg[s].ldb * (long long)sizeof(TI) * 64 > 0x3FFFFFFF) return GUARDED;
+        if (d.seg[s].K % bk) whole = false;
     }
-    return true;
+    if (whole) return WHOLE;
+    const bool b_pad = d.b_pad || d.Npad > 0;
+    if ((d.atrans && d.M % VEC && !d.a_pad) || (d.btrans && d.N % VEC && !b_pad)) return GUARDED;
+    if (sizeof(TI) == 4) {
+        if (tile_n != 128 || tile_m != 128) return GUARDED;
+        return d.nseg == 1 || d.seg[0].K % bk == 0 ? EDGE : GUARDED;     // (only the very last slab may be a part)
+    }
+    if (!direct_form(d)) return GUARDED;
+    for (int s = 0; s < d.nseg; ++s) {
+        if (d.seg[s].K % VEC == 0) continue;
+        if (!d.atrans && !(d.a_pad && d.btrans)) return GUARDED;
+        if (!d.btrans && !(d.b_pad && d.atrans)) return GUARDED;
+    }
+    return EDGE;
 }
 
 constexpr int kTileM[3] = {128, 256, 256}, kTileN[3] = {128, 256, 128};
@@ -965,63 +1087,71 @@ Params make_params(const GemmDesc& d) {
     P.splits = 1;
     return P;
 }
-// Tile counts and store modes for a tile shape; `fast`: the unguarded kernel runs.
+// Tile counts and store modes for a tile shape and edge treatment.
 template <typename TO>
-void set_tiles(const GemmDesc& d, Params& P, int tm, int tn, bool fast) {
+void set_tiles(const GemmDesc& d, Params& P, int tm, int tn, int mode) {
     const size_t w = sizeof(TO) == 4 ? 16 : 8;
+    P.Nst = d.N;
     P.c_vec = aligned(d.C, w) && d.ldc % 4 == 0 && ((d.batch > 1 ? d.sC : 0) % 4 == 0);
     if (sizeof(TO) == 2 && P.c_vec && aligned(d.C, 16) && d.ldc % 8 == 0 && ((d.batch > 1 ? d.sC : 0) % 8 == 0)) P.c_vec = 2;   // 16-byte bf16 stores
-    if (fast && d.Npad > 0) P.c_vec = 0;                 // whole tiles are computed, the stores stop at column N
-    P.p_vec = (d.N % 4 == 0 && !(fast && d.Npad > 0)) ? 1 : 0;   // (the scratch itself is 256-byte aligned)
+    if (mode == EDGE) {                                  // the last group of columns of a row is stored whole or not at all
+        if (d.c_pad) P.Nst = (d.N + 7) & ~7;
+        if (P.c_vec == 2 && P.Nst % 8) P.c_vec = 1;
+        if (P.c_vec == 1 && P.Nst % 4) P.c_vec = 0;
+    }
+    if (mode == WHOLE && d.Npad > 0) P.c_vec = 0;        // whole tiles are computed, the stores stop at column N
+    P.p_vec = (d.N % 4 == 0 && !(mode == WHOLE && d.Npad > 0)) ? 1 : 0;   // (the scratch itself is 256-byte aligned)
     P.ntm = (d.M + tm - 1) / tm;
-    P.ntn = ((fast && d.Npad > 0 ? d.Npad : d.N) + tn - 1) / tn;
+    P.ntn = ((mode == WHOLE && d.Npad > 0 ? d.Npad : d.N) + tn - 1) / tn;
 }
 
 template <typename TI, typename TO>
 hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
     Params P = make_params<TI>(d);
     const int batch = d.batch > 0 ? d.batch : 1;
-    const bool direct_form = sizeof(TI) == 2 && !d.add && !(d.atrans && !d.btrans);
-    GemmPlan plan = make_plan(d, direct_form);
+    const bool df = direct_form(d);
+    GemmPlan plan = make_plan(d, df);
     // the plan looks at the shape only: check what it chose against the operands' alignment and fall back
-    if (plan.tile == GEMM_TILE_256X128 && !can_run_fast<TI>(d, P, 256, 128)) plan = make_plan(d, false);
-    if (plan.tile == GEMM_TILE_256 && (!can_run_fast<TI>(d, P, 256, 256) || (sizeof(TI) == 2 && !(direct_form && !d.atrans && d.btrans)))) {
+    int mode = run_mode<TI>(d, P, kTileM[plan.tile], kTileN[plan.tile]);
+    if ((plan.tile == GEMM_TILE_256X128 && mode == GUARDED) ||
+        (plan.tile == GEMM_TILE_256 && (mode == GUARDED || (sizeof(TI) == 2 && !(df && !d.atrans && d.btrans))))) {
         plan = make_plan(d, false);
         if (plan.tile == GEMM_TILE_256) { plan.tile = GEMM_TILE_128; plan.splits = 1; plan.partial_bytes = 0; plan.deep = false; }
+        mode = run_mode<TI>(d, P, 128, 128);
     }
     const int tm = kTileM[plan.tile], tn = kTileN[plan.tile];
-    const bool fast = can_run_fast<TI>(d, P, tm, tn);
-    set_tiles<TO>(d, P, tm, tn, fast);
+    set_tiles<TO>(d, P, tm, tn, mode);
     P.splits = plan.splits;
     P.partial = plan.splits > 1 ? d.partial : nullptr;
     P.rs_partial = plan.splits > 1 ? d.partial + (size_t)plan.splits * batch * d.M * d.N : nullptr;
     dim3 grid((unsigned)(P.ntm * P.ntn), (unsigned)plan.splits, (unsigned)batch);
-    const bool direct = direct_form && fast;
+    const bool direct = df && mode != GUARDED;
     const int variant = plan.tile == GEMM_TILE_256X128 ? 2 : plan.tile == GEMM_TILE_256 ? 3 : (plan.deep ? 1 : 0);
     hipError_t e;
     if (plan.splits > 1) {
         // partial tiles are float whatever the output type
         if constexpr (sizeof(TI) == 2) {
-            if (direct) e = launch_direct<float>(d, P, variant, grid, stream);
-            else e = launch_form<TI, float, 2, 2, 2>(d, P, fast, plan.deep, grid, stream);
+            if (direct) e = launch_direct<float>(d, P, mode, variant, grid, stream);
+            else e = launch_form<TI, float, 2, 2, 2>(d, P, mode, plan.deep, grid, stream);
         } else {
-            e = plan.tile == GEMM_TILE_256 ? launch_form<TI, float, 4, 2, 4>(d, P, fast, false, grid, stream)
-                                           : launch_form<TI, float, 2, 2, 2>(d, P, fast, plan.deep, grid, stream);
+            e = plan.tile == GEMM_TILE_256 ? launch_form<TI, float, 4, 2, 4>(d, P, mode, false, grid, stream)
+                                           : launch_form<TI, float, 2, 2, 2>(d, P, mode, plan.deep, grid, stream);
         }
         if (e != hipSuccess) return e;
         const long long total = (long long)d.M * d.N;
+        const int vec4 = (P.c_vec && d.N % 4 == 0) ? 1 : 0;
         unsigned blocks = (unsigned)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
         hipLaunchKernelGGL((splitk_reduce_kernel<TI, TO>), dim3(blocks, 1, batch), dim3(256), 0, stream, d.partial, plan.splits,
                            d.M, d.N, static_cast<TO*>(d.C), d.ldc, d.sC, static_cast<const TI*>(d.bias), d.sBias,
-                           P.rs_partial, d.rowsum, d.sRowsum, (P.c_vec && d.N % 4 == 0) ? 1 : 0);
+                           P.rs_partial, d.rowsum, d.sRowsum, vec4);
         return hipGetLastError();
     }
     if constexpr (sizeof(TI) == 2) {
-        if (direct) return launch_direct<TO>(d, P, variant, grid, stream);
-        return launch_form<TI, TO, 2, 2, 2>(d, P, fast, plan.deep, grid, stream);
+        if (direct) return launch_direct<TO>(d, P, mode, variant, grid, stream);
+        return launch_form<TI, TO, 2, 2, 2>(d, P, mode, plan.deep, grid, stream);
     } else {
-        return plan.tile == GEMM_TILE_256 ? launch_form<TI, TO, 4, 2, 4>(d, P, fast, false, grid, stream)
-                                          : launch_form<TI, TO, 2, 2, 2>(d, P, fast, plan.deep, grid, stream);
+        return plan.tile == GEMM_TILE_256 ? launch_form<TI, TO, 4, 2, 4>(d, P, mode, false, grid, stream)
+                                          : launch_form<TI, TO, 2, 2, 2>(d, P, mode, plan.deep, grid, stream);
     }
 }
 
@@ -1033,11 +1163,10 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     const long long t256 = (long long)((d.M + 255) / 256) * ((Ne + 255) / 256) * batch;
     const long long t128 = (long long)((d.M + 127) / 128) * ((Ne + 127) / 128) * batch;
     int ktot = 0;
-    bool whole_slabs = true;
-    for (int s = 0; s < d.nseg; ++s) { ktot += d.seg[s].K; whole_slabs = whole_slabs && d.seg[s].K % 64 == 0; }
+    for (int s = 0; s < d.nseg; ++s) ktot += d.seg[s].K;
     if (d.in_type == DT_BF16) {
-        if (allow_r && d.M % 256 == 0 && Ne % 128 == 0 && whole_slabs) {
-            const long long tr = (long long)(d.M / 256) * (Ne / 128) * batch;
+        if (allow_r) {
+            const long long tr = (long long)((d.M + 255) / 256) * ((Ne + 127) / 128) * batch;
             // Enough 256x128 tiles to put two on (nearly) every CU: the tile that moves 3/4 of the operand bytes of
             // 128x128 per flop, and the only one whose loop keeps the matrix cores above half of their rate.
             if (tr >= 480) { p.tile = GEMM_TILE_256X128; return p; }
@@ -1046,7 +1175,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
             // rounds of 512 resident workgroups to 90 %, if every part keeps 64 slabs and the float partial tiles
             // stay below an eighth of the operand bytes.
             if (tr >= 128 && d.nseg == 1 && d.partial && !d.rowsum) {
-                const int slabs = d.seg[0].K / 64;
+                const int slabs = (d.seg[0].K + 63) / 64;
                 for (int s = 1; s <= 8; ++s) {
                     const double rounds = (double)tr * s / 512.0;
                     const double eff = rounds / (double)(long long)(rounds + 0.999999);
@@ -1061,9 +1190,8 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         // A handful of large tiles and a very long contraction (the softmax layer's input gradient, dA W form): the
         // 256x256 tile, which moves half the operand bytes of 128x128 per flop, split along K over up to one
         // workgroup per CU, if every part keeps at least 24 slabs and the parts fill three quarters of the CUs.
-        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 <= 64 &&
-            d.M % 256 == 0 && Ne % 256 == 0 && whole_slabs) {
-            const int slabs = d.seg[0].K / 64;
+        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 <= 64 && Ne % 256 == 0) {
+            const int slabs = (d.seg[0].K + 63) / 64;
             int s = (int)(256 / t256);
             if (s > 16) s = 16;
             while (s > 1 && slabs / s < 24) --s;
@@ -1073,7 +1201,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     } else {
         // float operands: the 256x256 tile has one workgroup per CU, so its prologue and epilogue are exposed: it pays
         // only when the contraction is long enough to amortise them
-        if (t256 >= 512 && !d.rowsum && ktot >= 512) { p.tile = GEMM_TILE_256; return p; }
+        if (t256 >= 512 && !d.rowsum && ktot >= 512 && d.M % 256 == 0 && Ne % 256 == 0) { p.tile = GEMM_TILE_256; return p; }
     }
     // Few output tiles and a long contraction: split K.  Up to one workgroup per CU whenever each part
     // keeps at least 8 slabs; up to two per CU (the number that fit) when each part keeps at least 64,
@@ -1102,10 +1230,6 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
 
 }  // namespace
 
-GemmPlan plan_gemm(const GemmDesc& d) {
-    return make_plan(d, d.in_type == DT_BF16 && !d.add && !(d.atrans && !d.btrans));
-}
-
 size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type) {
     GemmDesc d{};
     d.M = M; d.N = N; d.batch = batch; d.nseg = 1; d.seg[0].K = K; d.in_type = in_type;
@@ -1116,6 +1240,42 @@ size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type) {
         d.atrans = form == 2; d.btrans = form >= 1;
         const size_t a = make_plan(d, true).partial_bytes;
         if (a > need) need = a;
+    }
+    return need;
+}
+
+// The split-K scratch that bounds what softmax_xent_fwd_bwd_noalloc accepts, for its product with the output M x N and the
+// contraction K.  A fixed rule of its own: how the products are really split may change (they take what scratch there
+// is), which calls fit the resident array may not.
+size_t noalloc_partial_bytes(int M, int N, int K, DType in_type) {
+    const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256), t128 = (long long)((M + 127) / 128) * ((N + 127) / 128);
+    const int bk = in_type == DT_BF16 ? 64 : 32, slabs = (K + bk - 1) / bk;
+    auto bytes = [&](int s) { return s > 1 ? (size_t)s * ((size_t)M * N + M) * sizeof(float) : (size_t)0; };
+    auto parts = [&](long long target, int most, long long tiles, int min_slabs) {
+        int s = (int)(target / tiles);
+        if (s > most) s = most;
+        while (s > 1 && slabs / s < min_slabs) --s;
+        return s < 1 ? 1 : s;
+    };
+    size_t need = 0;
+    if (t128 <= 256) {
+        const int s1 = parts(256, 8, t128, 8), s2 = parts(512, 8, t128, 64);
+        if (in_type == DT_BF16 || !(t256 >= 512 && K >= 512)) need = bytes(s1 > s2 ? s1 : s2);
+    }
+    if (in_type == DT_BF16 && M % 256 == 0 && N % 128 == 0 && K % 64 == 0) {
+        const long long tr = (long long)(M / 256) * (N / 128);
+        if (tr >= 128 && tr < 480) {
+            for (int s = 1; s <= 8; ++s) {
+                const double rounds = (double)tr * s / 512.0, eff = rounds / (double)(long long)(rounds + 0.999999);
+                if (eff < 0.9 || slabs / s < 64) continue;
+                if (!(s > 1 && (long long)16 * s * N > K) && bytes(s) > need) need = bytes(s);
+                break;
+            }
+        }
+        if (tr < 480 && t256 <= 64 && N % 256 == 0) {
+            const int s = parts(256, 16, t256, 24);
+            if (s > 1 && t256 * s >= 192 && bytes(s) > need) need = bytes(s);
+        }
     }
     return need;
 }
@@ -1136,51 +1296,69 @@ bool gemm_group_ok(const GemmDesc* descs, int n) {
         const GemmDesc& d = descs[i];
         if (!(d.in_type == DT_BF16 && d.out_type == DT_F32 && d.atrans && d.btrans && !d.add && !d.bias && d.nseg == 1 && d.M > 0 && d.N > 0)) return false;
         const Params P = make_params<bf16_t>(d);
-        if (!can_run_fast<bf16_t>(d, P, 128, 128)) return false;
+        if (run_mode<bf16_t>(d, P, 128, 128) == GUARDED) return false;
     }
     return n > 0;
 }
 
-// Products the grouped kernel cannot take run one by one.
+namespace {
+template <int TM, int MODE, int NS>
+hipError_t launch_group_kernel(const GroupParams& G, int total, hipStream_t stream) {
+    constexpr size_t lds = NS * (size_t)(64 * TM + 128) * CHUNKS * 16;
+    static thread_local bool attr_set = false;
+    hipError_t e = allow_lds(&gemm_group_kernel<bf16_t, float, true, true, TM, 2, 2, MODE, true, 2, NS>, lds, &attr_set);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_group_kernel<bf16_t, float, true, true, TM, 2, 2, MODE, true, 2, NS>), dim3((unsigned)total), dim3(256), lds, stream, G);
+    return hipGetLastError();
+}
+}  // namespace
+
+// The products the grouped kernel can take run in it, the others one by one.  Tile: 256x128 whenever its partly empty
+// edge tiles cost less than a tenth more products than 128x128 tiles would.  A group of few tiles and a long contraction
+// (narrow layers, many frames) would leave most of the device idle for the whole contraction: its products run one by
+// one, each split along K (about 8 us of launches each against 0.8 us per slab saved to an eighth).
 hipError_t launch_gemm_group(const GemmDesc* descs, int n, hipStream_t stream) {
-    if (n <= 0) return hipSuccess;
-    if (n == 1) return launch_gemm(descs[0], stream);
-    if (!gemm_group_ok(descs, n)) {
-        for (int i = 0; i < n; ++i) { hipError_t e = launch_gemm(descs[i], stream); if (e != hipSuccess) return e; }
-        return hipSuccess;
-    }
-    bool all_r = true;
-    for (int i = 0; i < n && all_r; ++i) {
-        const Params P = make_params<bf16_t>(descs[i]);
-        if (!can_run_fast<bf16_t>(descs[i], P, 256, 128)) all_r = false;
-    }
-    const int tile = all_r ? GEMM_TILE_256X128 : GEMM_TILE_128;
-    for (int i0 = 0; i0 < n; i0 += GROUP_MAX) {
+    GemmDesc in[GROUP_MAX];
+    for (int i = 0; i < n;) {
+        int m = 0;
+        for (; i < n && m < GROUP_MAX; ++i) {
+            if (gemm_group_ok(&descs[i], 1)) in[m++] = descs[i];
+            else { hipError_t e = launch_gemm(descs[i], stream); if (e != hipSuccess) return e; }
+        }
+        if (m == 0) continue;
+        if (m == 1) { hipError_t e = launch_gemm(in[0], stream); if (e != hipSuccess) return e; continue; }
+        long long t_r = 0, t_128 = 0;
+        bool whole_r = true, whole_128 = true;
+        for (int k = 0; k < m; ++k) {
+            const GemmDesc& d = in[k];
+            const Params P = make_params<bf16_t>(d);
+            const long long batch = d.batch > 0 ? d.batch : 1, ntn = (d.N + 127) / 128;
+            t_r += (d.M + 255) / 256 * ntn * batch * 2;
+            t_128 += (d.M + 127) / 128 * ntn * batch;
+            whole_r = whole_r && run_mode<bf16_t>(d, P, 256, 128) == WHOLE;
+            whole_128 = whole_128 && run_mode<bf16_t>(d, P, 128, 128) == WHOLE;
+        }
+        const int tile = t_r * 10 <= t_128 * 11 ? GEMM_TILE_256X128 : GEMM_TILE_128;
+        const int mode = (tile == GEMM_TILE_128 ? whole_128 : whole_r) ? WHOLE : EDGE;
         GroupParams G{};
-        G.n = n - i0 < GROUP_MAX ? n - i0 : GROUP_MAX;
-        int total = 0;
-        for (int k = 0; k < G.n; ++k) {
-            const GemmDesc& d = descs[i0 + k];
+        G.n = m;
+        int total = 0, longest = 0;                       // tiles; slabs of the longest contraction
+        for (int k = 0; k < m; ++k) {
+            const GemmDesc& d = in[k];
             G.p[k] = make_params<bf16_t>(d);
-            set_tiles<float>(d, G.p[k], kTileM[tile], kTileN[tile], true);
+            set_tiles<float>(d, G.p[k], kTileM[tile], kTileN[tile], mode);
+            longest = longest > (d.seg[0].K + 63) / 64 ? longest : (d.seg[0].K + 63) / 64;
             G.first[k] = total;
             total += G.p[k].ntm * G.p[k].ntn * (d.batch > 0 ? d.batch : 1);
         }
-        G.first[G.n] = total;
-        if (all_r) {
-            constexpr size_t lds = (size_t)(256 + 128) * CHUNKS * 16;
-            static thread_local bool attr_set = false;
-            hipError_t e = allow_lds(&gemm_group_kernel<bf16_t, float, true, true, 4, 2, 2, true, true, 2, 1>, lds, &attr_set);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((gemm_group_kernel<bf16_t, float, true, true, 4, 2, 2, true, true, 2, 1>), dim3((unsigned)total), dim3(256), lds, stream, G);
-        } else {
-            constexpr size_t lds = 2 * (size_t)(128 + 128) * CHUNKS * 16;
-            static thread_local bool attr_set = false;
-            hipError_t e = allow_lds(&gemm_group_kernel<bf16_t, float, true, true, 2, 2, 2, true, true, 2, 2>, lds, &attr_set);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((gemm_group_kernel<bf16_t, float, true, true, 2, 2, 2, true, true, 2, 2>), dim3((unsigned)total), dim3(256), lds, stream, G);
+        G.first[m] = total;
+        hipError_t e;
+        if (total <= 128 && longest > 16 * m) {
+            for (int k = 0; k < m; ++k) if ((e = launch_gemm(in[k], stream)) != hipSuccess) return e;
+            continue;
         }
-        hipError_t e = hipGetLastError();
+        if (tile == GEMM_TILE_256X128) e = mode == WHOLE ? launch_group_kernel<4, WHOLE, 1>(G, total, stream) : launch_group_kernel<4, EDGE, 1>(G, total, stream);
+        else e = mode == WHOLE ? launch_group_kernel<2, WHOLE, 2>(G, total, stream) : launch_group_kernel<2, EDGE, 2>(G, total, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -33,6 +33,8 @@ struct GemmDesc {
     int M, N, batch;
     int Npad;                 // 0, or a multiple of the tile width >= N up to which B(n, .) may be read (it holds zeros or
                               // anything there): the product runs on whole tiles, C keeps its N columns
+    bool a_pad, b_pad;        // rows of A / B (as they lie in memory) may be read up to the next 16-byte boundary and hold finite values there
+    bool c_pad;               // rows of C may be written up to the next multiple of eight columns
     bool atrans, btrans;
     DType in_type, out_type;  // in_type is the element type of A and B
 };
@@ -47,15 +49,16 @@ struct GemmPlan {
     int splits;
     size_t partial_bytes;     // scratch the split needs (0 when splits == 1)
 };
-GemmPlan plan_gemm(const GemmDesc& d);
 // Scratch bytes a product of this shape would use if it were given unlimited scratch.
 size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type);
+// The scratch softmax_xent_fwd_bwd_noalloc sets aside for one of its products when it decides whether a call fits.
+size_t noalloc_partial_bytes(int M, int N, int K, DType in_type);
 
 // Validates nothing (the caller's shapes are trusted); returns the launch status.
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream);
 // n independent products of the A^T B form (atrans and btrans, bf16 operands, float result, optional row sums, no
-// bias, one segment) in one launch where the shapes allow it (gemm_group_ok); otherwise one launch each.  A grouped
-// launch never splits along K and uses no scratch.
+// bias, one segment): those the grouped kernel can take (gemm_group_ok) in one launch, the others one launch each.  A
+// grouped launch never splits along K and uses no scratch.
 bool gemm_group_ok(const GemmDesc* d, int n);
 hipError_t launch_gemm_group(const GemmDesc* d, int n, hipStream_t stream);
 

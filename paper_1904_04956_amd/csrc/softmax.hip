@@ -40,10 +40,12 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(TS* u, long long ldu,
         float p = expf(ld_f(row + v) - mx) * inv;
         st_f(row + v, s * (p - ((lab_ok && v == lab) ? 1.0f : 0.0f)));
     }
+    // rows padded to whole 16-byte words: zeros in the padding (the products of dE/du may read it)
+    if ((int)threadIdx.x < 8 && V + (int)threadIdx.x < (int)min(ldu, (long long)((V + 7) & ~7))) st_f(row + V + threadIdx.x, 0.0f);
 }
 
-// bf16 rows that fit the registers of one workgroup (V <= NT * 8 * NC, V a multiple of 8, rows
-// 16-byte aligned): the row is read once with 16-byte loads, kept in registers as packed bf16,
+// bf16 rows that fit the registers of one workgroup (V <= NT * 8 * NC, rows 16-byte aligned and padded to whole 16-byte
+// words: the padding counts as -inf on the way in and is zero on the way out): the row is read once with 16-byte loads, kept in registers as packed bf16,
 // reduced, and written back as dE/du with 16-byte stores.  HBM traffic: one read and one write.
 // A long row is spread over more threads rather than more registers per thread, so that several
 // rows per CU are in flight and one row's loads and stores run under another's arithmetic.
@@ -53,7 +55,7 @@ __global__ __launch_bounds__(NT) void softmax_rows_bf16_regs_kernel(bf16_t* u, l
     __shared__ float sh[NT / 64];
     const int m = blockIdx.x;
     bf16_t* row = u + (long long)m * ldu;
-    const int nchunks = V >> 3;
+    const int nchunks = (V + 7) >> 3;
     uint4 r[NC];
     float mx = -INFINITY;
 #pragma unroll
@@ -61,6 +63,15 @@ __global__ __launch_bounds__(NT) void softmax_rows_bf16_regs_kernel(bf16_t* u, l
         const int c = threadIdx.x + NT * i;
         if (c < nchunks) {
             r[i] = *reinterpret_cast<const uint4*>(row + 8 * c);
+            if (8 * c + 8 > V) {                           // the row's last, partly padded word
+                uint32_t t[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (8 * c + 2 * q >= V) t[q] = 0xFF80FF80u;
+                    else if (8 * c + 2 * q + 1 >= V) t[q] = (t[q] & 0xFFFFu) | 0xFF800000u;
+                }
+                r[i] = make_uint4(t[0], t[1], t[2], t[3]);
+            }
             const uint32_t w[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fmaxf(bf2f((bf16_t)(w[q] & 0xFFFFu)), bf2f((bf16_t)(w[q] >> 16))));
@@ -127,8 +138,8 @@ hipError_t launch_softmax_rows(void* u, long long ldu, const int32_t* labels, fl
     if (M <= 0) return hipSuccess;
     if (store == DT_BF16) {
         bf16_t* ub = static_cast<bf16_t*>(u);
-        const bool vec = (V % 8 == 0) && (ldu % 8 == 0) && (reinterpret_cast<uintptr_t>(u) % 16 == 0);
-        const int nchunks = V / 8;
+        const bool vec = (ldu % 8 == 0) && (ldu >= ((V + 7) & ~7)) && (reinterpret_cast<uintptr_t>(u) % 16 == 0);
+        const int nchunks = (V + 7) / 8;
 #define BLSTM_SOFTMAX_REGS(NC, NT) \
     hipLaunchKernelGGL((softmax_rows_bf16_regs_kernel<NC, NT>), dim3(M), dim3(NT), 0, st, ub, ldu, labels, row_loss, V, s)
         if (vec && nchunks <= 4 * 256) BLSTM_SOFTMAX_REGS(4, 256);

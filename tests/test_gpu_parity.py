@@ -140,6 +140,23 @@ def test_shapes_bf16(dims):
     check_step(dims, 1, seed=78, theta_scale=2.0)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("dims", [
+    dict(T=3, B=43, D=24, H=64, L=2, P=40, V=1003),         # 129 frames: one row beyond a tile, one frame beyond two slabs
+    dict(T=1, B=127, D=16, H=128, L=1, P=0, V=129),         # one row short of a tile, one class beyond one
+    dict(T=2, B=4, D=8, H=8, L=1, P=8, V=17),               # eight rows in all, a contraction of four
+    dict(T=5, B=51, D=72, H=96, L=2, P=136, V=2000),        # contractions of 72, 96, 136, 192, 204, 255
+    dict(T=7, B=37, D=264, H=256, L=1, P=0, V=999),
+])
+def test_edges_of_tiles_and_slabs(dims, mode):
+    check_step(dims, mode, seed=4960, theta_scale=2.0)
+
+
+def test_edges_of_the_large_tiles_bf16():
+    # the logits on 256x128 tiles, dz on 256x256 split along a contraction of 25001, dW_s in the grouped launch
+    check_step(dict(T=21, B=150, D=40, H=32, L=1, P=256, V=25001), 1, seed=4961)
+
+
 @pytest.mark.parametrize("V", [8000, 12000, 12004, 40000, 70000])
 def test_softmax_row_widths_bf16(V):
     # one softmax row kernel per range of V (256, 512, 1024 threads per row; rows too long or too
