@@ -67,6 +67,7 @@ struct blstm_ctx {
     int rec_nbg, rec_tiles;   // batch groups per direction and 32-row tiles per group of the persistent kernels
     int rec_path;             // 0 = persistent kernels where supported, 1 = one launch per frame
     int rec_sync;             // exchange of the persistent kernels: 0 = fenced counters, 1 = sentinel-tagged data
+    bool rec32_fwd, rec32_bwd;   // float mode: the persistent kernels of recurrent_f32.hip take this shape
     bool dax_filled;          // the forward pass's persistent kernels have marked every exchange copy of dE/da "not written yet"
     bool abort_clean;         // the abort word has been zeroed since the workspace was bound
     bool test_abort;          // failure-handling tests: the next forward pass raises the abort word itself
@@ -307,6 +308,15 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         c->wHX = w;  w += c->hx_bytes * c->L;
         c->wDAX = w; w += c->dax_bytes * c->L;
     }
+    c->rec32_fwd = c->st == DT_F32 && rec32_fwd_supported(c->B, c->H);
+    c->rec32_bwd = c->st == DT_F32 && rec32_bwd_supported(c->B, c->H);
+    if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da, one for all layers
+        c->wCNT = w; w += 256;
+        c->hx_bytes = up256(rec32_hx_bytes(c->T, c->B, c->H));
+        c->dax_bytes = c->rec32_bwd ? up256(rec32_dax_bytes(c->T, c->B, c->H)) : 0;
+        c->wHX = w;  w += c->hx_bytes;
+        c->wDAX = w; w += c->dax_bytes;
+    }
     {   // split-K scratch: the largest need among the products with a small output
         const DType S = c->st;
         size_t need = 0;
@@ -385,6 +395,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     ctx->dax_filled = false;
     ctx->pend_z = nullptr;                              // (a softmax weight gradient left over from an earlier step is dropped)
     const bool persistent = ctx->rec_nbg > 0 && ctx->rec_path == 0;
+    const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
     if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {
@@ -420,14 +431,26 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             RUN(PC_GEMM_INPUT, "input projection", launch_gemm(d, st));
         }
         ctx->fwd_persistent[l] = 0;
-        if (ctx->rec_nbg > 0 && ctx->rec_path == 0) {   // all T frames of both directions in one launch
-            unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);
-            const int ncnt = 2 * ctx->rec_nbg * ctx->rec_tiles;
-            if (!ctx->abort_clean || ctx->test_abort) {
-                RUN(PC_MISC, "abort word", launch_fill_u32(cnt + ncnt, 1, ctx->test_abort ? 1u : 0u, st));
-                ctx->abort_clean = true;
-                ctx->test_abort = false;
-            }
+        unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);
+        const int ncnt = 2 * ctx->rec_nbg * ctx->rec_tiles;
+        if ((persistent || persistent32) && (!ctx->abort_clean || ctx->test_abort)) {
+            RUN(PC_MISC, "abort word", launch_fill_u32(cnt + ncnt, 1, ctx->test_abort ? 1u : 0u, st));
+            ctx->abort_clean = true;
+            ctx->test_abort = false;
+        }
+        if (persistent32) {   // all T frames of both directions in one launch, float mode
+            RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes, 0xFFFFFFFFu, st));
+            Rec32FwdArgs a{};
+            for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
+            a.ax = AX; a.y = reinterpret_cast<float*>(Y); a.c = C; a.gates = reinterpret_cast<float*>(G);
+            a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX);
+            a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
+            a.T = T; a.B = B; a.H = H;
+            bool launched = false;
+            RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec32_fwd(a, st, &launched));
+            if (launched) continue;
+        }
+        if (persistent) {   // all T frames of both directions in one launch
             if (ctx->rec_sync == 0) RUN(PC_MISC, "counters", launch_fill_u32(cnt, ncnt, 0u, st));
             RecFwdArgs a{};
             a.uh[0] = reinterpret_cast<const unsigned short*>(at(theta, ctx->off_uh[0][l], e));
@@ -619,6 +642,17 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, ctx->rec_sync == 1, st, &rec_done));
             if (!rec_done)
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
+        }
+        if (ctx->rec32_bwd && ctx->abort_clean && ctx->rec_path == 0 && ctx->rec_sync == 1) {   // (saved activations are the same on both float paths)
+            RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes, 0xFFFFFFFFu, st));
+            Rec32BwdArgs a{};
+            for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
+            a.dy = reinterpret_cast<const float*>(dY); a.gates = reinterpret_cast<const float*>(G); a.c = C;
+            a.da = reinterpret_cast<float*>(DA); a.dc = DC;
+            a.dax = reinterpret_cast<float*>(ctx->ws + ctx->wDAX);
+            a.abort_word = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT); a.limit_ticks = 200000000ull;
+            a.T = T; a.B = B; a.H = H;
+            RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec32_bwd(a, st, &rec_done));
         }
         for (int n = T - 1; n >= 0 && !rec_done; --n) {
             const int t[2] = {n, T - 1 - n};
@@ -818,7 +852,7 @@ int blstm_device_status(blstm_ctx* c, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return check_hip(e, "blstm_device_status");
-    if (!c->ws || c->rec_nbg == 0 || !c->abort_clean) return BLSTM_OK;
+    if (!c->ws || (c->rec_nbg == 0 && !c->rec32_fwd) || !c->abort_clean) return BLSTM_OK;
     unsigned* word = reinterpret_cast<unsigned*>(c->ws + c->wCNT) + 2 * c->rec_nbg * c->rec_tiles;
     unsigned v = 0;
     e = hipMemcpy(&v, word, sizeof v, hipMemcpyDeviceToHost);

@@ -73,6 +73,40 @@ bool rec_fwd_fills(int H);
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.
 hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
 hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
+// ---- persistent recurrent kernels in float (H up to 1024) ------------------------------
+struct Rec32FwdArgs {
+    const float* uh[2];           // U_h per direction, [4H][H]
+    const float* ax;              // W_x x + b for every frame, [M][8H]
+    float* y;                     // h, [M][2H]
+    float* c;                     // cell states, [M][2H]
+    float* gates;                 // gate activations, [M][8H]
+    float* hx;                    // exchange copy of h, rec32_hx_bytes, filled with 0xFF bytes before the launch
+    unsigned* abort_word;         // as in RecFwdArgs
+    unsigned long long limit_ticks;
+    int T, B, H;
+    int nu, nbg, tiles_per_group; // set by the launcher
+};
+struct Rec32BwdArgs {
+    const float* uh[2];
+    const float* dy;              // dE/dh from above, [M][2H]
+    const float* gates;
+    const float* c;
+    float* da;                    // dE/da, [M][8H]
+    float* dc;                    // carried dE/dc, [2][B][H]
+    float* dax;                   // exchange copy of dE/da, rec32_dax_bytes, filled with 0xFF bytes before the launch
+    unsigned* abort_word;
+    unsigned long long limit_ticks;
+    int T, B, H;
+    int nu, nbg, tiles_per_group; // set by the launcher
+};
+// Whether the persistent kernel takes this shape (and is the faster of the two paths).
+bool rec32_fwd_supported(int B, int H);
+bool rec32_bwd_supported(int B, int H);
+size_t rec32_hx_bytes(int T, int B, int H);
+size_t rec32_dax_bytes(int T, int B, int H);
+hipError_t launch_rec32_fwd(Rec32FwdArgs a, hipStream_t st, bool* launched);   // *launched as for launch_rec_fwd
+hipError_t launch_rec32_bwd(Rec32BwdArgs a, hipStream_t st, bool* launched);
+
 // Transposes `count` matrices U_h [4H][H] (one per layer and direction) into dst + k * 4H*H.
 struct TransposeUhArgs {
     const unsigned short* src[128];

@@ -259,6 +259,41 @@ def test_abandoned_wait_is_reported_in_band_and_recovered_from():
         lrn.close()
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=1, B=5, D=8, H=40, L=1, P=0, V=20),              # no exchange at all
+    dict(T=4, B=1, D=8, H=1, L=2, P=0, V=20),               # one row, one unit
+    dict(T=4, B=33, D=8, H=33, L=2, P=16, V=20),            # one row in the second forward tile, one unit in the last slices
+    dict(T=3, B=70, D=24, H=100, L=1, P=0, V=40),
+    dict(T=3, B=48, D=24, H=512, L=1, P=0, V=40),           # every slice whole
+    dict(T=3, B=530, D=8, H=600, L=1, P=16, V=40),          # several tiles per workgroup, the last groups short
+    dict(T=2, B=40, D=8, H=1000, L=1, P=16, V=40),          # the widest slices, one group
+    dict(T=2, B=17, D=8, H=1030, L=1, P=16, V=40),          # wider than any: one launch per frame
+])
+def test_persistent_recurrent_kernels_fp32(dims):
+    check_step(dims, 0, seed=84, theta_scale=1.0 if dims["H"] > 500 else 2.0)
+
+
+def test_abandoned_wait_fp32():
+    # as test_abandoned_wait_is_reported_in_band_and_recovered_from, float mode
+    from paper_1904_04956_amd import binding as bl
+    from paper_1904_04956_amd.harness import Learner
+    dims = dict(T=6, B=40, D=32, H=72, L=2, P=16, V=90)
+    dm, theta, x, labels = make_problem(dims, 0, 83, 2.0)
+    lrn = Learner(mode=0, **dims)
+    lrn.set_theta(theta); lrn.set_batch(x, labels)
+    lrn.calgrad(); lrn.check_status()
+    clean = (lrn.loss_value(), lrn.grad_numpy().copy())
+    bl.blstm_set_option(lrn.ctx, bl.BLSTM_OPT_TEST_ABORT, 1)
+    lrn.calgrad()
+    with pytest.raises(bl.BlstmError) as e:
+        lrn.check_status()
+    assert e.value.code == -5 and "abandoned" in str(e.value)
+    assert np.isnan(lrn.loss_value()) and np.isnan(lrn.grad_numpy()).any()
+    lrn.calgrad(); lrn.check_status()
+    assert lrn.loss_value() == clean[0] and np.array_equal(lrn.grad_numpy(), clean[1])
+    lrn.close()
+
+
 @pytest.mark.parametrize("V,mode", [(8000, 1), (70000, 1), (300, 0)])
 def test_out_of_range_label_gives_nan_loss_and_no_stray_access(V, mode):
     # a label outside [0, V) must never be used as an index: the loss turns NaN, every other frame's row is untouched
