@@ -325,6 +325,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         upd(c->V, c->zdim, c->M, 1);                              // dW_s
         if (c->P > 0) { upd(c->P, 2 * c->H, c->M, 1); upd(c->M, 2 * c->H, c->P, 1); }
         for (int l = 0; l < c->L; ++l) { upd(4 * c->H, c->din(l), c->M, 2); upd(4 * c->H, c->H, (c->T - 1) * c->B, 2); }
+        if (c->L > 1) upd(c->M, 2 * c->H, 8 * c->H, 1);           // dx
         upd(c->B, c->H, 4 * c->H, 2);                             // recurrent gradient of the step-by-step path
         c->wPART = w; c->part_bytes = up256(need);
         w += c->part_bytes;

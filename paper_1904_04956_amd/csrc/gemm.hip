@@ -358,10 +358,10 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     ntiles[0] = (P.K[0] + BK - 1) / BK;
     ntiles[1] = P.nseg > 1 ? (P.K[1] + BK - 1) / BK : 0;
     int it_begin = 0, it_end = ntiles[0] + ntiles[1];
-    if (P.splits > 1) {                                  // slabs [it_begin, it_end) of this split (one segment only)
-        const int per = (ntiles[0] + P.splits - 1) / P.splits;
+    if (P.splits > 1) {                                  // slabs [it_begin, it_end) of this split
+        const int all = it_end, per = (all + P.splits - 1) / P.splits;
         it_begin = split * per;
-        it_end = min(ntiles[0], it_begin + per);
+        it_end = min(all, it_begin + per);
         if (it_end < it_begin) it_end = it_begin;
     }
 
@@ -902,7 +902,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
         const int n4 = N >> 2;
         for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total4; i += (long long)gridDim.x * blockDim.x) {
             float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            for (int s = 0; s < splits; ++s) {
+            int s = 0;
+            for (; s + 8 <= splits; s += 8) {             // eight parts' loads in flight, added in order
+                float4 p4[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) p4[k] = *reinterpret_cast<const float4*>(part + (s + k) * total + 4 * i);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) { v.x += p4[k].x; v.y += p4[k].y; v.z += p4[k].z; v.w += p4[k].w; }
+            }
+            for (; s < splits; ++s) {
                 const float4 p4 = *reinterpret_cast<const float4*>(part + s * total + 4 * i);
                 v.x += p4.x; v.y += p4.y; v.z += p4.z; v.w += p4.w;
             }
@@ -1203,24 +1211,29 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         // only when the contraction is long enough to amortise them
         if (t256 >= 512 && !d.rowsum && ktot >= 512 && d.M % 256 == 0 && Ne % 256 == 0) { p.tile = GEMM_TILE_256; return p; }
     }
-    // Few output tiles and a long contraction: split K.  Up to one workgroup per CU whenever each part
-    // keeps at least 8 slabs; up to two per CU (the number that fit) when each part keeps at least 64,
-    // so that the float partial tiles and the reduction stay small next to the product itself.
-    if (d.nseg == 1 && !d.add && d.partial && t128 <= 256) {
+    // Few output tiles, or a last round of them that is nearly empty: split K (both segments as one range of slabs) into the
+    // number of parts whose estimated time is least, if that is a twelfth below not splitting.  A workgroup's slab takes
+    // 1.9 us on a CU in float (the matrix rate), 0.7 us in bf16 (its chain of load, fragment reads and products; two
+    // workgroups of a CU overlap, so more than one per CU costs by a third less).  Splitting adds a reduction launch and
+    // the float partial tiles' way out and back.  Measured against at most eight parts of at least eight slabs and one
+    // segment only: dz of 336 frames (6 tiles, K = 32000) 49 -> 20 us, dx in float (88 tiles, K = 4096) 300 -> 110.
+    if (!d.add && d.partial && t128 <= 1024) {
         const int bk = d.in_type == DT_BF16 ? 64 : 32;
-        const int slabs = (d.seg[0].K + bk - 1) / bk;
-        auto parts = [&](long long target, int min_slabs) {
-            int s = (int)(target / t128);
-            if (s > 8) s = 8;
-            while (s > 1 && slabs / s < min_slabs) --s;
-            return s < 1 ? 1 : s;
+        int slabs = 0;
+        for (int s = 0; s < d.nseg; ++s) slabs += (d.seg[s].K + bk - 1) / bk;
+        const double tile_bytes = (double)batch * d.M * d.N * sizeof(float);
+        auto estimate = [&](int s) {
+            const double x = (double)t128 * s / 256.0, rounds = x <= 1.0 ? 1.0 : (double)(long long)(x + 0.999999);
+            const double part = (slabs + s - 1) / s;
+            const double t = d.in_type == DT_BF16 ? 0.7 * part * (rounds > 1.0 ? 0.66 * rounds : 1.0) : 1.9 * part * rounds;
+            return s == 1 ? t : t + 4.5 + 2.0 * s * tile_bytes / 4e6;
         };
-        const int s1 = parts(256, 8), s2 = parts(512, 64);
-        const int s = s1 > s2 ? s1 : s2;
-        const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
-        if (s > 1 && need <= d.partial_bytes) {
-            p.splits = s;
-            p.partial_bytes = need;
+        double best = estimate(1) * (11.0 / 12.0);
+        for (int s = 2; s <= 32 && slabs / s >= 4; ++s) {
+            const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
+            if (need > d.partial_bytes || need > ((size_t)256 << 20)) break;
+            const double t = estimate(s);
+            if (t < best) { best = t; p.splits = s; p.partial_bytes = need; }
         }
     }
     // at most one 128x128 workgroup per CU: run the loads further ahead (three LDS buffers, or four register sets)
