@@ -259,12 +259,13 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     // workspace layout
     const size_t M = (size_t)c->M, B = (size_t)c->B, e = c->esz;
     const size_t Br = (B + 31) / 32 * 32, Mr = (size_t)c->T * Br;      // rows rounded up to whole batch tiles
+    const size_t Hr = (H + 31) / 32 * 32;                              // units rounded up to whole slices of the persistent kernels
     size_t w = 0;
     for (int l = 0; l < c->L; ++l) { c->wY.push_back(w); w += up256(M * 2 * H * e); }
     for (int l = 0; l < c->L; ++l) {
         // (whole 32-row batch tiles: the persistent kernels keep these two as per-lane records)
-        c->wG.push_back(w); w += up256(Mr * 8 * H * e);
-        c->wC.push_back(w); w += up256(Mr * 2 * H * 4);
+        c->wG.push_back(w); w += up256(Mr * 8 * Hr * e);
+        c->wC.push_back(w); w += up256(Mr * 2 * Hr * 4);
     }
     c->wAX = w;      w += up256(M * 8 * H * 4);
     c->wPRE = w;     w += up256(2 * B * 4 * H * 4);
@@ -272,7 +273,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->wDY[0] = w;   w += up256(M * 2 * H * e);
     c->wDY[1] = w;   w += up256(M * 2 * H * e);
     c->wDH = w;      w += up256(2 * B * H * 4);
-    c->wDC = w;      w += up256(2 * Br * H * 4);
+    c->wDC = w;      w += up256(2 * Br * Hr * 4);
     c->ldu = (c->V + 7) & ~7;
     c->wLOGITS = w;  w += up256(M * (size_t)c->ldu * e);
     c->wROWLOSS = w; w += up256(M * 4);
@@ -290,11 +291,8 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->dax_filled = false;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
-    if (c->st == DT_BF16 && rec_waves_for(c->H) > 0) {
-        const int NU = c->H / 32, tiles = (c->B + 31) / 32;
-        int nbg = 256 / (2 * NU);
-        if (nbg > tiles) nbg = tiles;
-        if (nbg < 1) nbg = 1;
+    if (c->st == DT_BF16 && rec_supported(c->H)) {
+        const int tiles = (c->B + 31) / 32, nbg = rec_groups(c->H, tiles);
         c->rec_nbg = nbg;
         c->rec_tiles = (tiles + nbg - 1) / nbg;
         w += up256((size_t)c->L * 2 * 4 * H * H * 2);
@@ -303,8 +301,8 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         // exchange copies of h and dE/da in MFMA-fragment order, one per layer (whole 32-row tiles),
         // contiguous so that one fill marks all of a pass's copies as "not written yet"
         const size_t Mx = (size_t)c->T * tiles * 32;
-        c->hx_bytes = up256(Mx * 2 * H * 2);
-        c->dax_bytes = up256(Mx * 8 * H * 2);
+        c->hx_bytes = up256(Mx * 2 * Hr * 2);
+        c->dax_bytes = up256(Mx * 8 * Hr * 2);
         c->wHX = w;  w += c->hx_bytes * c->L;
         c->wDAX = w; w += c->dax_bytes * c->L;
     }
@@ -575,7 +573,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     wgrads.reserve(2 * ctx->L + 2);
     bool persistent = false;                            // some layer's forward pass ran the persistent kernel
     for (int l = 0; l < ctx->L; ++l) persistent = persistent || ctx->fwd_persistent[l] != 0;
-    const bool sentinel = persistent && ctx->rec_sync == 1;
+    const bool sentinel = persistent && (ctx->rec_sync == 1 || !rec_fenced(H));
     if (persistent && !(ctx->keep_copies && ctx->uht_of == theta)) {   // U_h^T of every layer and direction in one launch
         TransposeUhArgs ta{};
         for (int l = 0; l < ctx->L; ++l)
@@ -640,7 +638,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, ctx->rec_sync == 1, st, &rec_done));
+            RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));
             if (!rec_done)
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
         }

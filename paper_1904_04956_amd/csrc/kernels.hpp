@@ -36,7 +36,7 @@ struct CellBwdArgs {
 };
 hipError_t launch_cell_bwd(const CellBwdArgs& a, DType store, hipStream_t s);
 
-// ---- persistent recurrent kernels (bf16 storage, H one of 128, 256, 512, 1024) -------------------
+// ---- persistent recurrent kernels (bf16 storage, H a multiple of 8 up to 1024) -------------------
 struct RecFwdArgs {
     const unsigned short* uh[2];  // U_h per direction, [4H][H]
     const float* ax;              // W_x x + b for every frame, [M][8H]
@@ -66,8 +66,9 @@ struct RecBwdArgs {
     unsigned long long limit_ticks;
     int T, B, H, nbg, tiles_per_group;
 };
-// Wavefronts per workgroup of the persistent kernels for this H, 0 if H is not supported.
-int rec_waves_for(int H);
+bool rec_supported(int H);                  // whether the persistent kernels take this width
+bool rec_fenced(int H);                     // whether they are built with the fenced protocol too
+int rec_groups(int H, int tiles);           // batch groups per direction for so many 32-row tiles
 // Whether launch_rec_fwd for this width honours RecFwdArgs::fill.
 bool rec_fwd_fills(int H);
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.

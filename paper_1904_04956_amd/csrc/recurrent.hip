@@ -134,10 +134,11 @@ __device__ __forceinline__ bool wait_probe(const bf16_t* probe, bool probing, un
 }
 
 constexpr int XPAIR = 2 * 32 * 8;                      // elements of one pair of 8-column chunks over 32 rows (1 KB)
+// `last`: pairs beyond it (of a width padded to the kernel's) repeat that pair, against zero weights.
 template <int NQ>
-__device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p) {
+__device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p, int last) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) frag[q] = ld_coh_16B(p + q * XPAIR);
+    for (int q = 0; q < NQ; ++q) frag[q] = ld_coh_16B(p + min(q, last) * XPAIR);
 }
 template <int NQ>
 __device__ __forceinline__ bool all_written(const uint4 (&frag)[NQ]) {
@@ -149,14 +150,14 @@ __device__ __forceinline__ bool all_written(const uint4 (&frag)[NQ]) {
 // The chunks in frag were loaded once; reloads them until no element of any lane is the sentinel
 // (or the wait is abandoned).  Normally the first check passes.
 template <int NQ>
-__device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* p, bool give_up,
+__device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* p, int last, bool give_up,
                                                unsigned* abort_word, unsigned long long limit_ticks) {
     if (give_up || all_written<NQ>(frag)) return give_up;
     const unsigned long long t0 = wall_clock64();
     unsigned it = 0;
     for (;;) {
         __builtin_amdgcn_s_sleep(1);
-        load_chunks<NQ>(frag, p);
+        load_chunks<NQ>(frag, p, last);
         if (all_written<NQ>(frag)) return false;
         if ((++it & 31u) == 0) {
             if (ld_coh_u32(abort_word) != 0) return true;
@@ -193,9 +194,9 @@ __device__ __forceinline__ GroupMap map_block(int NU, int nbg) {
 // answers, a chunk without sentinels is correct; anything else is re-read cache-bypassing by
 // ensure_written.
 template <int NQ>
-__device__ __forceinline__ void load_chunks_cached(uint4 (&frag)[NQ], const bf16_t* p) {
+__device__ __forceinline__ void load_chunks_cached(uint4 (&frag)[NQ], const bf16_t* p, int last) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) frag[q] = *reinterpret_cast<const uint4*>(p + q * XPAIR);
+    for (int q = 0; q < NQ; ++q) frag[q] = *reinterpret_cast<const uint4*>(p + min(q, last) * XPAIR);
 }
 // Element offset of column c (within a direction), row r of a tile, in the exchange order.
 __device__ __forceinline__ unsigned xoff(int c, int r) { return (unsigned)((c >> 3) * 256 + r * 8 + (c & 7)); }
@@ -225,17 +226,19 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 // took 76 (H = 512, 173 sequences; the backward kernel 104 against 83).
 // MULTI: a workgroup owns several batch tiles (tiles_per_group > 1); only then is there a next item
 // whose exchanged chunks can be loaded ahead, and only then are registers set aside for them.
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI>
+// PADDED: the layer is narrower than the kernel's NW * KW cells (any multiple of 8): U_h counts as zero beyond it, the
+// exchange holds whole slices of 32 units, and the units beyond the layer come out as zeros that are not stored row-major.
+template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
 __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
-    constexpr int H = NW * KW;                           // (the launcher picks NW and KW from a.H)
+    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks NW and KW from a.H)
     const int B = a.B, T = a.T;
-    constexpr int NU = H / 32;
+    const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
     const int d = gm.d, u = gm.u;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     // This workgroup's share of the region to fill (the widest slice of U_h leaves no register for it: KW <= 128 only):
@@ -263,8 +266,11 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int q = 0; q < KSTEPS; ++q)
-                bfrag[g][q] = *reinterpret_cast<const uint4*>(uh + (size_t)(g * H + u * 32 + l32) * H + wave * KW + q * 16 + 8 * lh);
+            for (int q = 0; q < KSTEPS; ++q) {
+                const int unit = u * 32 + l32, k = wave * KW + q * 16 + 8 * lh;
+                const bool in = !PADDED || (unit < H && k < H);
+                bfrag[g][q] = in ? *reinterpret_cast<const uint4*>(uh + (size_t)(g * H + unit) * H + k) : make_uint4(0, 0, 0, 0);
+            }
     }
     unsigned* cnt = a.cnt + (size_t)gm.group * a.tiles_per_group;
     const int j = u * 32 + l32;                          // this thread's hidden unit
@@ -275,11 +281,14 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     // Register e is batch row rb + re(e) of the tile: rb per thread, re(e) a compile-time constant.
     const int rb = 2 * EPT * wave + 4 * lh;
     auto re = [](int e) { return 8 * (e >> 2) + (e & 3); };
-    const unsigned o8c = (unsigned)(d * 4 * H + j);      // column in the row-major [.][8H] tensor (a_x)
+    const bool junit = !PADDED || j < H;                 // (a unit beyond the layer reads its last one's a_x and counts it as zero)
+    const unsigned o8c = (unsigned)(d * 4 * H + (PADDED ? min(j, H - 1) : j));   // column in the row-major [.][8H] tensor (a_x)
     const unsigned o8b = (unsigned)(rb * 8 * H) + o8c;
     const int NT = (B + 31) / 32;                        // 32-row tiles of the batch
-    constexpr int XH = H / 16 * XPAIR;                   // exchange elements per (frame, direction, tile)
-    const unsigned ohp = (unsigned)(wave * (KW / 16) * XPAIR + lane * 8);   // this lane's 16 bytes of each chunk pair
+    const int XH = NU * 2 * XPAIR;                       // exchange elements per (frame, direction, tile)
+    // this lane's 16 bytes of each chunk pair; the last pair that exists, counted from there
+    const int firstp = PADDED ? min(wave * (KW / 16), NU * 2 - 1) : wave * (KW / 16), lastp = PADDED ? NU * 2 - 1 - firstp : KW;
+    const unsigned ohp = (unsigned)(firstp * XPAIR + lane * 8);
 
     // Per-item inputs that do not depend on the exchange (a_x of the frame, previous cell state) are
     // loaded one item ahead, so that their HBM latency never sits on the frame-to-frame path.
@@ -343,7 +352,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
         const int lane_ = threadIdx.x & 63;
         const int xrow_ = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane_ >> 5) + ((lane_ >> 3) & 3);
         const unsigned xcol_ = (unsigned)(u * 32 + 8 * ((lane_ >> 1) & 3) + 4 * (lane_ & 1));
-        if (tail.xok) *reinterpret_cast<uint2*>(yb + ((unsigned)xrow_ * (unsigned)(2 * H) + (unsigned)(d * H) + xcol_)) = tail.hq;
+        if (tail.xok && (!PADDED || xcol_ < (unsigned)H)) *reinterpret_cast<uint2*>(yb + ((unsigned)xrow_ * (unsigned)(2 * H) + (unsigned)(d * H) + xcol_)) = tail.hq;
         fill_some(fill_per_item);
     };
     auto do_item = [&](const int item, const float (&ax)[EPT][4], const float (&cpl)[EPT], float (&axn)[EPT][4],
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
             uint4 afrag[KSTEPS];
             if (SENTINEL) {
                 // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
-                const bf16_t* probe = hb + xoff(wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
+                const bf16_t* probe = hb + xoff(PADDED ? min(wave * (KW / 32) + lane, NU - 1) * 32 + 31 : wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
                 bool got = false, gu = false;
                 if constexpr (MULTI) {
                     if (have_pre) {
@@ -380,25 +389,25 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                     // cache-bypassing loads (the first ones may have left lines with sentinels in the L1).
                     // (The widest slice has no registers for two attempts: probe first, then the data.)
                     if constexpr (KW <= 128) {
-                        load_chunks_cached<KSTEPS>(afrag, hp);
+                        load_chunks_cached<KSTEPS>(afrag, hp, lastp);
                         flush_tail();
                         if (!all_written<KSTEPS>(afrag)) {
                             gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
                             asm volatile("" ::: "memory");
-                            load_chunks<KSTEPS>(afrag, hp);
+                            load_chunks<KSTEPS>(afrag, hp, lastp);
                         }
                     } else {
                         gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
                         asm volatile("" ::: "memory");
-                        load_chunks_cached<KSTEPS>(afrag, hp);
+                        load_chunks_cached<KSTEPS>(afrag, hp, lastp);
                     }
                 }
-                if (ensure_written<KSTEPS>(afrag, hp, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+                if (ensure_written<KSTEPS>(afrag, hp, lastp, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             } else {
                 if (wait_counter(cnt + i, (unsigned)(NU * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
 #pragma unroll
                 for (int q = 0; q < KSTEPS; ++q)
-                    afrag[q] = *reinterpret_cast<const uint4*>(hp + q * XPAIR);
+                    afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
             f32x16_t acc[4];
 #pragma unroll
@@ -415,7 +424,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                 const int tp2 = d ? T - n2 : n2 - 1;
                 const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
                 const bf16_t* hb2 = a.hx + ((size_t)(tp2 * 2 + d) * NT + (b02 >> 5)) * XH;
-                load_chunks_cached<KSTEPS>(apre, hb2 + ohp);
+                load_chunks_cached<KSTEPS>(apre, hb2 + ohp, lastp);
                 have_pre = true;
             }
             // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
@@ -459,10 +468,10 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
         bf16_t* hxb = a.hx + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XH;
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            gi[e] = fast_sigmoid(ax[e][0] + sum[e][0]);
-            gf[e] = fast_sigmoid(ax[e][1] + sum[e][1]);
-            gg[e] = fast_tanh(ax[e][2] + sum[e][2]);
-            go[e] = fast_sigmoid(ax[e][3] + sum[e][3]);
+            gi[e] = fast_sigmoid((junit ? ax[e][0] : 0.0f) + sum[e][0]);
+            gf[e] = fast_sigmoid((junit ? ax[e][1] : 0.0f) + sum[e][1]);
+            gg[e] = fast_tanh((junit ? ax[e][2] : 0.0f) + sum[e][2]);
+            go[e] = fast_sigmoid((junit ? ax[e][3] : 0.0f) + sum[e][3]);
             cn[e] = gf[e] * cp[e] + gi[e] * gg[e];
             hn[e] = go[e] * fast_tanh(cn[e]) + poison;
         }
@@ -523,19 +532,19 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
 }
 
 // ------------------------------------------------------------------------------ backward
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI>
+template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
 __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     constexpr int EPT = 16 / NW;
     constexpr int KSTEPS = 4 * KW / 16;                  // the contraction runs over the 4H gate rows
     extern __shared__ float lds[];                       // [NW][4][64][4]
-    constexpr int H = NW * KW;                           // (the launcher picks NW and KW from a.H)
+    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks NW and KW from a.H)
     const int B = a.B, T = a.T;
-    constexpr int NU = H / 32;
+    const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
     const int d = gm.d, u = gm.u;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
-    constexpr int KWB = 4 * H / NW;                         // gate rows per wavefront (= 4 * KW)
+    static_assert(NW == 4, "a wavefront contracts one gate's rows");
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     if (ntl == 0) return;
 
@@ -544,8 +553,11 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     {
         const bf16_t* uht = a.uht[d];
 #pragma unroll
-        for (int q = 0; q < KSTEPS; ++q)
-            bfrag[q] = *reinterpret_cast<const uint4*>(uht + (size_t)(u * 32 + l32) * 4 * H + wave * KWB + q * 16 + 8 * lh);
+        for (int q = 0; q < KSTEPS; ++q) {
+            const int unit = u * 32 + l32, k = q * 16 + 8 * lh;
+            const bool in = !PADDED || (unit < H && k < H);
+            bfrag[q] = in ? *reinterpret_cast<const uint4*>(uht + (size_t)unit * 4 * H + wave * H + k) : make_uint4(0, 0, 0, 0);
+        }
     }
     unsigned* cnt = a.cnt + (size_t)gm.group * a.tiles_per_group;
     const int j = u * 32 + l32;
@@ -554,11 +566,14 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // per-thread 32-bit element offsets, added to per-item uniform bases (as in the forward kernel)
     const int rb = 2 * EPT * wave + 4 * lh;              // register e is batch row rb + re(e) of the tile
     auto re = [](int e) { return 8 * (e >> 2) + (e & 3); };
-    const unsigned o2c = (unsigned)(d * H + j);          // column in the row-major [.][2H] tensor (dy)
+    const bool junit = !PADDED || j < H;
+    const unsigned o2c = (unsigned)(d * H + (PADDED ? min(j, H - 1) : j));   // column in the row-major [.][2H] tensor (dy)
     const unsigned o2b = (unsigned)(rb * 2 * H) + o2c;
     const int NT = (B + 31) / 32;
-    constexpr int XA = 4 * H / 16 * XPAIR;               // exchange elements per (frame, direction, tile)
-    const unsigned oap = (unsigned)(wave * (KWB / 16) * XPAIR + lane * 8);   // this lane's 16 bytes of each chunk pair
+    const int HX = NU * 32;                              // columns of a gate in the exchange copy
+    const int XA = 4 * HX / 16 * XPAIR;                  // exchange elements per (frame, direction, tile)
+    const int lastp = PADDED ? NU * 2 - 1 : KSTEPS;      // a gate's last pair of chunks
+    const unsigned oap = (unsigned)(wave * (HX / 16) * XPAIR + lane * 8);   // this lane's 16 bytes of each chunk pair
 
     // Saved activations of an item, loaded one item ahead (raw bf16 for the gates and dy).
     // dy of a wavefront's cells is eight rows of 32 units: 512 contiguous-by-row bytes.  With one tile per workgroup
@@ -585,7 +600,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         if (MULTI && n < T - 1 && ntl > 1) dc4 = reinterpret_cast<const float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x];   // (one tile: carried in registers)
         if constexpr (WIDE_DY) {                         // piece lane % 32: row (lane % 32) / 4 of the wavefront's eight, units 8 (lane % 4) .. + 7
             const int row0 = 2 * EPT * wave + (l32 >> 2), row = FULL ? row0 : min(row0, B - 1 - b0);
-            in.dyr = *reinterpret_cast<const uint4*>(dyb + (size_t)row * 2 * H + d * H + u * 32 + (l32 & 3) * 8);
+            const int col = u * 32 + (l32 & 3) * 8;
+            in.dyr = *reinterpret_cast<const uint4*>(dyb + (size_t)row * 2 * H + d * H + (PADDED ? min(col, H - 8) : col));
         }
         static_assert(EPT == 4, "a record holds four cells");
         in.g01 = g01; in.g23 = g23; in.c = c4; in.cp = cp4; in.dcr = dc4;
@@ -642,8 +658,11 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             if (SENTINEL) {
                 // the gate rows of this wavefront come from KWB/32 producers: probe each one's last unit,
                 // then stream the slabs of 128 gate rows with the next slab's loads in flight
-                const bf16_t* probe = ab + xoff(wave * KWB + (lane & (4 * KW / 32 - 1)) * 32 + 31, 31);
+                const bf16_t* probe = ab + xoff(wave * HX + (PADDED ? min(lane, NU - 1) : lane & (4 * KW / 32 - 1)) * 32 + 31, 31);
                 uint4 afrag[2][8];
+                // first pair of a slab (a slab beyond the layer repeats the last pair), and the last pair counted from it
+                auto slab = [&](int sl) { return (PADDED ? min(sl * 8, lastp) : sl * 8) * XPAIR; };
+                auto left = [&](int sl) { return PADDED ? max(lastp - sl * 8, 0) : 8; };
                 bool got = false, gu = false;
                 if constexpr (MULTI) {
                     if (have_pre) {
@@ -654,16 +673,16 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 }
                 if (!got) {
                     // (straight for the data, the probe only if the first look fails: see the forward kernel)
-                    load_chunks_cached<8>(afrag[0], ap);
+                    load_chunks_cached<8>(afrag[0], ap, lastp);
                     if (!all_written<8>(afrag[0])) {
                         gu = wait_probe(probe, lane < 4 * KW / 32, a.abort_word, a.limit_ticks);
                         asm volatile("" ::: "memory");
-                        load_chunks<8>(afrag[0], ap);
+                        load_chunks<8>(afrag[0], ap, lastp);
                     }
                 }
 #pragma unroll
                 for (int sl = 0; sl < KSTEPS / 8; ++sl) {
-                    if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + (sl + 1) * 8 * XPAIR);
+                    if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + slab(sl + 1), left(sl + 1));
                     else {
                         have_pre = false;
                         if constexpr (MULTI && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
@@ -673,12 +692,12 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                                 const int tn2 = d ? T - 2 - n2 : n2 + 1;
                                 const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
                                 const bf16_t* ab2 = a.dax + ((size_t)(tn2 * 2 + d) * NT + (b02 >> 5)) * XA;
-                                load_chunks_cached<8>(apre, ab2 + oap);
+                                load_chunks_cached<8>(apre, ab2 + oap, lastp);
                                 have_pre = true;
                             }
                         }
                     }
-                    gu = ensure_written<8>(afrag[sl & 1], ap + sl * 8 * XPAIR, gu, a.abort_word, a.limit_ticks);
+                    gu = ensure_written<8>(afrag[sl & 1], ap + slab(sl), left(sl), gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[sl & 1][q], bfrag[sl * 8 + q], acc);
                 }
@@ -690,7 +709,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                     uint4 afrag[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
-                        afrag[q] = *reinterpret_cast<const uint4*>(ap + (q0 + q) * XPAIR);
+                        afrag[q] = *reinterpret_cast<const uint4*>(ap + min(q0 + q, lastp) * XPAIR);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[q], bfrag[q0 + q], acc);
                 }
@@ -732,7 +751,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         for (int e = 0; e < EPT; ++e) {
             const float gi = bf2f((bf16_t)(curg[e].x & 0xFFFFu)), gf = bf2f((bf16_t)(curg[e].x >> 16));
             const float gg = bf2f((bf16_t)(curg[e].y & 0xFFFFu)), go = bf2f((bf16_t)(curg[e].y >> 16));
-            const float dht = dh[e] + bf2f(dyv[e]) + poison;
+            const float dht = dh[e] + (junit ? bf2f(dyv[e]) : 0.0f) + poison;
             const float tc = fast_tanh(cthis[e]);
             const float dc = dht * go * (1.0f - tc * tc) + dcr[e];
             const float da_o = dht * tc * go * (1.0f - go);
@@ -766,10 +785,11 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         }
         const int xrow = 2 * EPT * wave + 4 * xl + xr;    // row of the tile
         const bool xok = FULL || b0 + xrow < B;
-        const unsigned xcol = (unsigned)(2 * xq * H + u * 32 + 8 * xk);   // column of gate 2 xq within the direction; + H: gate 2 xq + 1
+        const unsigned ucol = (unsigned)(u * 32 + 8 * xk);   // first unit; a gate has HX columns in the exchange copy and H row-major
         {
-            bf16_t* pa = dxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u);
-            bf16_t* pb = dxb + (((xcol + (unsigned)H) >> 3) * 256u + (unsigned)xrow * 8u);
+            const unsigned xc = 2 * xq * (unsigned)HX + ucol;
+            bf16_t* pa = dxb + ((xc >> 3) * 256u + (unsigned)xrow * 8u);
+            bf16_t* pb = dxb + (((xc + (unsigned)HX) >> 3) * 256u + (unsigned)xrow * 8u);
             if (SENTINEL) { st_coh_16B(pa, cga); st_coh_16B(pb, cgb); }
             else { *reinterpret_cast<uint4*>(pa) = cga; *reinterpret_cast<uint4*>(pb) = cgb; }
         }
@@ -778,8 +798,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         else signal_counter(cnt + i);
         // row-major dE/da for the weight- and input-gradient products, and the carried dE/dc
         bf16_t* dab = a.da + ((size_t)t * B + b0) * 8 * H;
-        if (xok) {
-            bf16_t* pr = dab + ((unsigned)xrow * (unsigned)(8 * H) + (unsigned)(d * 4 * H) + xcol);
+        if (xok && (!PADDED || ucol < (unsigned)H)) {
+            bf16_t* pr = dab + ((unsigned)xrow * (unsigned)(8 * H) + (unsigned)(d * 4 * H + 2 * xq * H) + ucol);
             *reinterpret_cast<uint4*>(pr) = cga;
             *reinterpret_cast<uint4*>(pr + H) = cgb;
         }
@@ -802,16 +822,16 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     }
 }
 
-// U_h [4H][H] -> U_h^T [H][4H], 32x32 tiles through LDS; blockIdx.z = 2 * layer + direction.
+// U_h [4H][H] -> U_h^T [H][4H] (H a multiple of 8), 32x32 tiles through LDS; blockIdx.z = 2 * layer + direction.
 __global__ __launch_bounds__(256) void transpose_uh_kernel(TransposeUhArgs a, int H) {
     __shared__ bf16_t tile[32][33];
     const bf16_t* src = a.src[blockIdx.z];
     bf16_t* dst = a.dst + (size_t)blockIdx.z * 4 * H * H;
     const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;     // rows of U_h (4H), columns (H)
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int rr = ty; rr < 32; rr += 8) tile[rr][tx] = src[(size_t)(r0 + rr) * H + c0 + tx];
+    if (c0 + tx < H) for (int rr = ty; rr < 32; rr += 8) tile[rr][tx] = src[(size_t)(r0 + rr) * H + c0 + tx];
     __syncthreads();
-    for (int rr = ty; rr < 32; rr += 8) dst[(size_t)(c0 + rr) * 4 * H + r0 + tx] = tile[tx][rr];
+    for (int rr = ty; rr < 32 && c0 + rr < H; rr += 8) dst[(size_t)(c0 + rr) * 4 * H + r0 + tx] = tile[tx][rr];
 }
 
 // dst[r][0..cols_p) = src[r][0..cols) followed by zeros: one thread per 8-column chunk, grid-stride.
@@ -875,54 +895,70 @@ hipError_t prepare(K kernel, int threads, size_t dyn_lds, int grid, FitCache* ca
     return hipSuccess;
 }
 
-template <int NW, int KW, bool S, bool FULL, bool MULTI>
-hipError_t run_fwd_m(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
+template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
+hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
     bool fits = false;
     static thread_local FitCache cache{false, 0};
-    hipError_t e = prepare(rec_fwd_kernel<NW, KW, S, FULL, MULTI>, 64 * NW, lds, grid, &cache, &fits);
+    hipError_t e = prepare(rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>, 64 * NW, lds, grid, &cache, &fits);
     if (e != hipSuccess || !fits) return e;
-    hipLaunchKernelGGL((rec_fwd_kernel<NW, KW, S, FULL, MULTI>), dim3(grid), dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>), dim3(grid), dim3(64 * NW), lds, st, a);
     *launched = true;
     return hipGetLastError();
 }
-template <int NW, int KW, bool S, bool FULL>
-hipError_t run_fwd_as(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    return a.tiles_per_group > 1 ? run_fwd_m<NW, KW, S, FULL, true>(a, grid, st, launched) : run_fwd_m<NW, KW, S, FULL, false>(a, grid, st, launched);
-}
-template <int NW, int KW, bool S>
-hipError_t run_fwd(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    return a.B % 32 == 0 ? run_fwd_as<NW, KW, S, true>(a, grid, st, launched) : run_fwd_as<NW, KW, S, false>(a, grid, st, launched);
-}
-template <int NW, int KW, bool S, bool FULL, bool MULTI>
-hipError_t run_bwd_m(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
+template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
+hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 64 * 16 + (size_t)NW * 2048 + (size_t)NW * 512;   // partial sums; regrouping of dE/da, 2 KB per wavefront; spreading dy, 512 bytes per wavefront
     bool fits = false;
     static thread_local FitCache cache{false, 0};
-    hipError_t e = prepare(rec_bwd_kernel<NW, KW, S, FULL, MULTI>, 64 * NW, lds, grid, &cache, &fits);
+    hipError_t e = prepare(rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>, 64 * NW, lds, grid, &cache, &fits);
     if (e != hipSuccess || !fits) return e;
-    hipLaunchKernelGGL((rec_bwd_kernel<NW, KW, S, FULL, MULTI>), dim3(grid), dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>), dim3(grid), dim3(64 * NW), lds, st, a);
     *launched = true;
     return hipGetLastError();
 }
-template <int NW, int KW, bool S, bool FULL>
-hipError_t run_bwd_as(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    return a.tiles_per_group > 1 ? run_bwd_m<NW, KW, S, FULL, true>(a, grid, st, launched) : run_bwd_m<NW, KW, S, FULL, false>(a, grid, st, launched);
+template <int KW, bool S, bool FULL, bool PADDED, typename A>
+hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {
+    return a.tiles_per_group > 1 ? run_one<4, KW, S, FULL, true, PADDED>(a, grid, st, launched) : run_one<4, KW, S, FULL, false, PADDED>(a, grid, st, launched);
 }
-template <int NW, int KW, bool S>
-hipError_t run_bwd(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    return a.B % 32 == 0 ? run_bwd_as<NW, KW, S, true>(a, grid, st, launched) : run_bwd_as<NW, KW, S, false>(a, grid, st, launched);
+// A width that is the kernel's own.
+template <int KW, typename A>
+hipError_t run_exact(const A& a, bool sentinel, int grid, hipStream_t st, bool* launched) {
+    if (sentinel) return a.B % 32 == 0 ? run_multi<KW, true, true, false>(a, grid, st, launched) : run_multi<KW, true, false, false>(a, grid, st, launched);
+    return a.B % 32 == 0 ? run_multi<KW, false, true, false>(a, grid, st, launched) : run_multi<KW, false, false, false>(a, grid, st, launched);
+}
+template <typename A>
+hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) {
+    *launched = false;
+    const int grid = grid_groups(a.nbg) * ((a.H + 31) / 32);
+    switch (a.H) {
+        case 128: return run_exact<32>(a, sentinel, grid, st, launched);
+        case 256: return run_exact<64>(a, sentinel, grid, st, launched);
+        case 512: return run_exact<128>(a, sentinel, grid, st, launched);
+        case 1024: return run_exact<256>(a, sentinel, grid, st, launched);
+    }
+    if (!sentinel || !rec_supported(a.H)) return hipSuccess;   // (padded widths: sentinel protocol only)
+#define BLSTM_PADDED(KW) if (a.H <= 4 * KW) return run_multi<KW, true, false, true>(a, grid, st, launched)
+    BLSTM_PADDED(32); BLSTM_PADDED(64); BLSTM_PADDED(96); BLSTM_PADDED(128); BLSTM_PADDED(160); BLSTM_PADDED(192); BLSTM_PADDED(224); BLSTM_PADDED(256);
+#undef BLSTM_PADDED
+    return hipSuccess;
 }
 
 }  // namespace
 
-// Supported widths: H = 128, 256, 512 and 1024, always on four wavefronts that split the contraction
-// (32, 64, 128, 256 elements each: four batch rows per thread in every variant), any batch size.
-// Returns the wavefronts per workgroup, 0 if unsupported.
-// Whether the forward kernel for this width also fills RecFwdArgs::fill (the widest one has no register to spare).
-bool rec_fwd_fills(int H) { return H == 128 || H == 256 || H == 512; }
-
-int rec_waves_for(int H) { return H == 128 || H == 256 || H == 512 || H == 1024 ? 4 : 0; }
+// Supported widths: multiples of 8 up to 1024, always on four wavefronts that split the contraction (four batch rows per
+// thread in every variant).  128, 256, 512 and 1024 have kernels of their own; the others run padded to the next multiple
+// of 128 (H = 320, 50 sequences: 70 us a layer forward and 76 backward, where two launches per frame took 640 and 540).
+bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
+bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
+// Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than
+// one workgroup per CU (32).
+int rec_groups(int H, int tiles) {
+    const int most = 4 * (32 / ((H + 31) / 32));
+    return tiles < most ? tiles : most;
+}
+// Whether the forward kernel for this width also fills RecFwdArgs::fill (the wider ones have no register to spare).
+bool rec_fwd_fills(int H) { return H <= 512; }
 
 hipError_t launch_fill_u32(unsigned* p, int n, unsigned v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -952,34 +988,11 @@ hipError_t launch_pad_cols(const PadColsArgs& a, hipStream_t st) {
 
 hipError_t launch_transpose_uh(const TransposeUhArgs& a, int H, hipStream_t st) {
     if (a.count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(transpose_uh_kernel, dim3(H / 32, 4 * H / 32, a.count), dim3(256), 0, st, a, H);
+    hipLaunchKernelGGL(transpose_uh_kernel, dim3((H + 31) / 32, 4 * H / 32, a.count), dim3(256), 0, st, a, H);
     return hipGetLastError();
 }
 
-hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched) {
-    *launched = false;
-    const int grid = grid_groups(a.nbg) * (a.H / 32);
-    switch (a.H) {
-        case 128: return sentinel ? run_fwd<4, 32, true>(a, grid, st, launched) : run_fwd<4, 32, false>(a, grid, st, launched);
-        case 256: return sentinel ? run_fwd<4, 64, true>(a, grid, st, launched) : run_fwd<4, 64, false>(a, grid, st, launched);
-        case 512: return sentinel ? run_fwd<4, 128, true>(a, grid, st, launched) : run_fwd<4, 128, false>(a, grid, st, launched);
-        case 1024:
-            return sentinel ? run_fwd<4, 256, true>(a, grid, st, launched) : run_fwd<4, 256, false>(a, grid, st, launched);
-        default: return hipSuccess;
-    }
-}
-
-hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched) {
-    *launched = false;
-    const int grid = grid_groups(a.nbg) * (a.H / 32);
-    switch (a.H) {
-        case 128: return sentinel ? run_bwd<4, 32, true>(a, grid, st, launched) : run_bwd<4, 32, false>(a, grid, st, launched);
-        case 256: return sentinel ? run_bwd<4, 64, true>(a, grid, st, launched) : run_bwd<4, 64, false>(a, grid, st, launched);
-        case 512: return sentinel ? run_bwd<4, 128, true>(a, grid, st, launched) : run_bwd<4, 128, false>(a, grid, st, launched);
-        case 1024:
-            return sentinel ? run_bwd<4, 256, true>(a, grid, st, launched) : run_bwd<4, 256, false>(a, grid, st, launched);
-        default: return hipSuccess;
-    }
-}
+hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched) { return run_width(a, sentinel, st, launched); }
+hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched) { return run_width(a, sentinel, st, launched); }
 
 }  // namespace blstm

@@ -260,6 +260,23 @@ def test_abandoned_wait_is_reported_in_band_and_recovered_from():
 
 
 @pytest.mark.parametrize("dims", [
+    dict(T=4, B=40, D=8, H=8, L=2, P=0, V=20),              # a quarter of one slice
+    dict(T=5, B=33, D=24, H=96, L=2, P=16, V=40),           # whole slices, less than the kernel's width
+    dict(T=4, B=70, D=24, H=264, L=2, P=0, V=40),           # eight units in the last slice
+    dict(T=3, B=50, D=24, H=320, L=2, P=16, V=40),
+    dict(T=3, B=290, D=24, H=504, L=1, P=16, V=40),         # two tiles per workgroup
+    dict(T=3, B=200, D=8, H=536, L=1, P=0, V=40),           # slices of the widest kernels, one group per XCD
+    dict(T=2, B=45, D=8, H=776, L=1, P=16, V=40),
+    dict(T=2, B=32, D=8, H=1000, L=1, P=0, V=40),
+    dict(T=4, B=20, D=8, H=100, L=2, P=0, V=20),            # not a multiple of 8
+])
+def test_padded_widths_of_the_persistent_kernels_bf16(dims):
+    check_step(dims, 1, seed=85, theta_scale=1.0 if dims["H"] > 500 else 2.0)
+    if dims["H"] == 264:
+        check_step(dims, 1, seed=85, theta_scale=2.0, recurrent_sync=0)
+
+
+@pytest.mark.parametrize("dims", [
     dict(T=1, B=5, D=8, H=40, L=1, P=0, V=20),              # no exchange at all
     dict(T=4, B=1, D=8, H=1, L=2, P=0, V=20),               # one row, one unit
     dict(T=4, B=33, D=8, H=33, L=2, P=16, V=20),            # one row in the second forward tile, one unit in the last slices
