@@ -80,6 +80,14 @@ struct blstm_ctx {
     char* ws;
     size_t ws_bound;
     bool have_forward;
+    // A model whose rows are not whole 16-byte words (H or P, in float mode D too) runs as a twin with these widths padded
+    // by zeros: the twin's units beyond H have zero weights both ways, stay exactly zero and change no other value.  Null
+    // otherwise.  The workspace is the twin's, then its weights, gradient, x, z and dz.
+    blstm_ctx* twin;
+    std::vector<BlockTensor> tparam;    // every tensor of the flat vector, compact here and padded there; the softmax layer's two last
+    BlockTensor tx, tz;                 // x (float mode, where D is padded) and z / dz
+    size_t tTHETA, tGRAD, tX, tZ, tDZ;
+    const void* ttheta_of;              // the weights the padded ones were made from (null: to be made)
     std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel (whose saved gates only its backward twin reads)
     // profiling
     bool prof;
@@ -218,6 +226,127 @@ int resident_scratch(char** out) {
     return BLSTM_OK;
 }
 
+// ---- models run as their padded twin ----------------------------------------------------------------------------
+inline int up_to(int v, int m) { return (v + m - 1) / m * m; }
+
+// Whether the model is run as its twin: misaligned rows put every product on the guarded kernel and, in bf16 mode, the
+// recurrence on one launch per frame.  The copies cost about six launches a step (25 us), so a model with neither frames
+// nor arithmetic enough to earn them back stays as it is (5 GFLOP a step take about 50 us on the guarded kernels).
+bool wants_twin(const blstm_ctx* c) {
+    const int m = c->st == DT_BF16 ? 8 : 4;
+    const bool h = c->H % m != 0, p = c->P % m != 0, d = c->st == DT_F32 && c->D % m != 0;
+    if (!h && !p && !d) return false;
+    if (c->st == DT_BF16 && h && c->T >= 4 && rec_supported(up_to(c->H, m))) return true;
+    return 6.0 * c->M * (double)c->nparam > 5e9;
+}
+
+int make_twin(blstm_ctx* c) {
+    const int m = c->st == DT_BF16 ? 8 : 4;
+    blstm_config cfg = c->cfg;
+    cfg.H = up_to(c->H, m); cfg.P = up_to(c->P, m);
+    if (c->st == DT_F32) cfg.D = up_to(c->D, m);
+    blstm_ctx* t = nullptr;
+    const int rc = blstm_create(&cfg, &t);
+    if (rc != BLSTM_OK) return rc;
+    c->twin = t;
+    const int H = c->H, Hp = t->H;
+    for (int l = 0; l < c->L; ++l)
+        for (int d = 0; d < 2; ++d) {
+            if (l == 0) c->tparam.push_back(BlockTensor{c->off_wx[d][l], t->off_wx[d][l], 4, H, Hp, 1, c->D, t->D});
+            else c->tparam.push_back(BlockTensor{c->off_wx[d][l], t->off_wx[d][l], 4, H, Hp, 2, H, Hp});
+            c->tparam.push_back(BlockTensor{c->off_uh[d][l], t->off_uh[d][l], 4, H, Hp, 1, H, Hp});
+            c->tparam.push_back(BlockTensor{c->off_b[d][l], t->off_b[d][l], 1, 1, 1, 4, H, Hp});
+        }
+    if (c->P > 0) {
+        c->tparam.push_back(BlockTensor{c->off_wp, t->off_wp, 1, c->P, t->P, 2, H, Hp});
+        c->tparam.push_back(BlockTensor{c->off_bp, t->off_bp, 1, 1, 1, 1, c->P, t->P});
+    }
+    const int zs = c->P > 0 ? 1 : 2, z = c->P > 0 ? c->P : H, zp = c->P > 0 ? t->P : Hp;
+    c->tparam.push_back(BlockTensor{c->off_ws, t->off_ws, 1, c->V, c->V, zs, z, zp});
+    c->tparam.push_back(BlockTensor{c->off_bs, t->off_bs, 1, 1, 1, 1, c->V, c->V});
+    c->tx = BlockTensor{0, 0, 1, c->M, c->M, 1, c->D, t->D};
+    c->tz = BlockTensor{0, 0, 1, c->M, c->M, zs, z, zp};
+    size_t w = up256(t->ws_bytes);
+    c->tTHETA = w; w += up256(t->nparam * c->esz);
+    c->tGRAD = w;  w += up256(t->nparam * 4);
+    c->tX = w;     if (t->D != c->D) w += up256((size_t)c->M * t->D * c->esz);
+    c->tZ = w;     w += up256((size_t)c->M * t->zdim * c->esz);
+    c->tDZ = w;    w += up256((size_t)c->M * t->zdim * c->esz);
+    c->ws_bytes = w;
+    return BLSTM_OK;
+}
+
+// The padded weights, made anew unless the caller vouches for them (see blstm_weights_changed).
+int twin_theta(blstm_ctx* ctx, const void* theta, hipStream_t st) {
+    if (ctx->keep_copies && ctx->ttheta_of == theta) return BLSTM_OK;
+    ctx->ttheta_of = theta;
+    blstm_weights_changed(ctx->twin);
+    return check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size(), theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
+}
+
+int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, hipStream_t st) {
+    int rc = twin_theta(ctx, theta, st);
+    if (rc != BLSTM_OK) return rc;
+    const void* xin = x;
+    if (ctx->twin->D != ctx->D) {
+        rc = check_hip(launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st), "padded x");
+        if (rc != BLSTM_OK) return rc;
+        xin = ctx->ws + ctx->tX;
+    }
+    if (ctx->twin->zdim == ctx->zdim) return blstm_forward(ctx->twin, ctx->ws + ctx->tTHETA, xin, z_out, st);
+    rc = blstm_forward(ctx->twin, ctx->ws + ctx->tTHETA, xin, ctx->ws + ctx->tZ, st);
+    if (rc != BLSTM_OK) return rc;
+    return check_hip(launch_compact_blocks(&ctx->tz, 1, ctx->ws + ctx->tZ, z_out, ctx->st, st), "z");
+}
+
+int twin_xent(blstm_ctx* ctx, const void* theta, const void* z, const int32_t* labels, float* loss_dev, void* dz, float* grad, hipStream_t st) {
+    int rc = twin_theta(ctx, theta, st);
+    if (rc != BLSTM_OK) return rc;
+    float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
+    const bool same = ctx->twin->zdim == ctx->zdim;
+    if (!same) {
+        rc = check_hip(launch_pad_blocks(&ctx->tz, 1, z, ctx->ws + ctx->tZ, ctx->st, st), "padded z");
+        if (rc != BLSTM_OK) return rc;
+    }
+    void* tdz = same ? dz : ctx->ws + ctx->tDZ;
+    rc = softmax_xent_fwd_bwd(ctx->twin, ctx->ws + ctx->tTHETA, same ? z : ctx->ws + ctx->tZ, labels, loss_dev, tdz, tg, st);
+    if (rc != BLSTM_OK) return rc;
+    if (!same) {
+        rc = check_hip(launch_compact_blocks(&ctx->tz, 1, tdz, dz, ctx->st, st), "dz");
+        if (rc != BLSTM_OK) return rc;
+    }
+    ctx->pend_grad = grad;
+    if (ctx->twin->pend_z) return BLSTM_OK;              // left to twin_backward
+    const BlockTensor* t = ctx->tparam.data() + ctx->tparam.size() - 2;
+    return check_hip(launch_compact_blocks(t, 2, tg, grad, DT_F32, st), "softmax layer's gradient");
+}
+
+int twin_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* dz, float* grad, hipStream_t st) {
+    const bool pending = ctx->twin->pend_z != nullptr;
+    if (pending && ctx->pend_grad != grad)
+        return fail(BLSTM_ERR_DIM, "blstm_backward: the softmax layer's weight gradient was left to this call for another gradient vector");
+    if (!ctx->twin->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
+    int rc = twin_theta(ctx, theta, st);
+    if (rc != BLSTM_OK) return rc;
+    float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
+    const void* tdz = dz;
+    if (ctx->twin->zdim != ctx->zdim) {
+        rc = check_hip(launch_pad_blocks(&ctx->tz, 1, dz, ctx->ws + ctx->tDZ, ctx->st, st), "padded dz");
+        if (rc != BLSTM_OK) return rc;
+        tdz = ctx->ws + ctx->tDZ;
+    }
+    const void* xin = x;
+    if (ctx->twin->D != ctx->D) {
+        rc = check_hip(launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st), "padded x");
+        if (rc != BLSTM_OK) return rc;
+        xin = ctx->ws + ctx->tX;
+    }
+    rc = blstm_backward(ctx->twin, ctx->ws + ctx->tTHETA, xin, tdz, tg, st);
+    if (rc != BLSTM_OK) return rc;
+    const int n = (int)ctx->tparam.size() - (pending ? 0 : 2);   // (the softmax layer's slice is this call's only if left to it)
+    return check_hip(launch_compact_blocks(ctx->tparam.data(), n, tg, grad, DT_F32, st), "gradient");
+}
+
 }  // namespace
 
 extern "C" {
@@ -331,6 +460,11 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->keep_copies = false; c->wxp_of = nullptr; c->uht_of = nullptr;
     c->defer_ws = false; c->pend_z = nullptr; c->pend_grad = nullptr;
     c->ws_bytes = w;
+    c->twin = nullptr; c->ttheta_of = nullptr;
+    if (wants_twin(c)) {
+        const int rc = make_twin(c);
+        if (rc != BLSTM_OK) { delete c; return rc; }
+    }
     c->ws = nullptr; c->ws_bound = 0; c->have_forward = false;
     c->prof = false; c->recs_used = 0;
     memset(c->prof_ms, 0, sizeof c->prof_ms);
@@ -341,6 +475,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
 
 void blstm_destroy(blstm_ctx* c) {
     if (!c) return;
+    blstm_destroy(c->twin);
     for (auto& r : c->recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
     delete c;
 }
@@ -377,6 +512,8 @@ int blstm_bind(blstm_ctx* c, void* workspace, size_t bytes) {
     c->abort_clean = false;
     c->wxp_of = nullptr; c->uht_of = nullptr;
     c->pend_z = nullptr;
+    c->ttheta_of = nullptr;
+    if (c->twin) return blstm_bind(c->twin, workspace, c->twin->ws_bytes);
     return BLSTM_OK;
 }
 
@@ -385,6 +522,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     if (!ctx->ws) return fail(BLSTM_ERR_WORKSPACE, "blstm_forward: no workspace bound");
     if (!aligned16(theta) || !aligned16(x) || !aligned16(z_out)) return fail(BLSTM_ERR_ALIGN, "blstm_forward: pointers must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (ctx->twin) return twin_forward(ctx, theta, x, z_out, st);
     const int T = ctx->T, B = ctx->B, H = ctx->H, M = ctx->M;
     const size_t e = ctx->esz;
     const DType S = ctx->st;
@@ -519,6 +657,7 @@ int softmax_xent_fwd_bwd(blstm_ctx* ctx, const void* theta, const void* z, const
     if (!ctx->ws) return fail(BLSTM_ERR_WORKSPACE, "softmax_xent_fwd_bwd: no workspace bound");
     if (!aligned16(theta) || !aligned16(z) || !aligned16(dz) || !aligned16(grad))
         return fail(BLSTM_ERR_ALIGN, "softmax_xent_fwd_bwd: pointers must be 16-byte aligned");
+    if (ctx->twin) return twin_xent(ctx, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream));
     SoftmaxScratch sc{ctx->ws + ctx->wLOGITS, ctx->ldu, reinterpret_cast<float*>(ctx->ws + ctx->wROWLOSS),
                       reinterpret_cast<float*>(ctx->ws + ctx->wPART), ctx->part_bytes};
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), ctx->defer_ws);
@@ -553,9 +692,10 @@ int softmax_xent_fwd_bwd_noalloc(blstm_ctx* ctx, const void* theta, const void* 
 int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* dz, float* grad, void* stream) {
     if (!ctx || !theta || !x || !dz || !grad) return fail(BLSTM_ERR_NULL, "blstm_backward: null argument");
     if (!ctx->ws) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no workspace bound");
-    if (!ctx->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
+    if (!ctx->twin && !ctx->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
     if (!aligned16(theta) || !aligned16(x) || !aligned16(dz) || !aligned16(grad))
         return fail(BLSTM_ERR_ALIGN, "blstm_backward: pointers must be 16-byte aligned");
+    if (ctx->twin) return twin_backward(ctx, theta, x, dz, grad, static_cast<hipStream_t>(stream));
     if (ctx->pend_z && ctx->pend_grad != grad)
         return fail(BLSTM_ERR_DIM, "blstm_backward: the softmax layer's weight gradient was left to this call for another gradient vector");
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -825,6 +965,11 @@ int blstm_shadow_refresh(const float* theta, void* shadow, size_t n, void* strea
 
 int blstm_set_option(blstm_ctx* c, int option, int value) {
     if (!c) return fail(BLSTM_ERR_NULL, "blstm_set_option: null argument");
+    if (c->twin) {
+        const int rc = blstm_set_option(c->twin, option, value);
+        if (rc != BLSTM_OK) return rc;
+        if (option == BLSTM_OPT_KEEP_WEIGHT_COPIES) c->ttheta_of = nullptr;
+    }
     if (option == BLSTM_OPT_RECURRENT_PATH && (value == 0 || value == 1)) { c->rec_path = value; return BLSTM_OK; }
     if (option == BLSTM_OPT_RECURRENT_SYNC && (value == 0 || value == 1)) { c->rec_sync = value; return BLSTM_OK; }
     if (option == BLSTM_OPT_KEEP_WEIGHT_COPIES && (value == 0 || value == 1)) {
@@ -842,12 +987,14 @@ int blstm_set_option(blstm_ctx* c, int option, int value) {
 
 int blstm_weights_changed(blstm_ctx* c) {
     if (!c) return fail(BLSTM_ERR_NULL, "blstm_weights_changed: null argument");
+    c->ttheta_of = nullptr;
     c->wxp_of = nullptr; c->uht_of = nullptr;
     return BLSTM_OK;
 }
 
 int blstm_device_status(blstm_ctx* c, void* stream) {
     if (!c) return fail(BLSTM_ERR_NULL, "blstm_device_status: null argument");
+    if (c->twin) return blstm_device_status(c->twin, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return check_hip(e, "blstm_device_status");
@@ -868,6 +1015,7 @@ const char* blstm_profile_name(int k) { return (k >= 0 && k < PC_COUNT) ? kProfN
 
 int blstm_profile_enable(blstm_ctx* c, int enable) {
     if (!c) return fail(BLSTM_ERR_NULL, "blstm_profile_enable: null argument");
+    if (c->twin) return blstm_profile_enable(c->twin, enable);
     c->prof = enable != 0;
     c->recs_used = 0;
     memset(c->prof_ms, 0, sizeof c->prof_ms);
@@ -877,6 +1025,7 @@ int blstm_profile_enable(blstm_ctx* c, int enable) {
 
 int blstm_profile_read(blstm_ctx* c, double* ms_out, int64_t* launches_out, int n_classes) {
     if (!c || !ms_out || !launches_out) return fail(BLSTM_ERR_NULL, "blstm_profile_read: null argument");
+    if (c->twin) return blstm_profile_read(c->twin, ms_out, launches_out, n_classes);
     for (size_t i = 0; i < c->recs_used; ++i) {
         ProfRec& r = c->recs[i];
         hipError_t e = hipEventSynchronize(r.b);

@@ -129,6 +129,18 @@ hipError_t launch_pad_cols(const PadColsArgs& a, hipStream_t st);
 // Fills bytes/16 16-byte words with the 32-bit pattern v.
 hipError_t launch_fill_bytes16(void* p, size_t bytes, unsigned v, hipStream_t st);
 
+// ---- copies between compact and zero-padded tensors ----------------------------------------------
+// A matrix of rg groups of r rows, each of cs segments of c columns, and its padded form with rp rows a group and cp
+// columns a segment (offsets in elements; padded rows are whole 16-byte words).
+struct BlockTensor {
+    size_t compact, padded;
+    int rg, r, rp, cs, c, cp;
+};
+constexpr int BLOCK_COPIES_MAX = 64;
+struct BlockCopies { BlockTensor t[BLOCK_COPIES_MAX]; };
+hipError_t launch_pad_blocks(const BlockTensor* t, int n, const void* compact, void* padded, DType type, hipStream_t st);
+hipError_t launch_compact_blocks(const BlockTensor* t, int n, const void* padded, void* compact, DType type, hipStream_t st);
+
 // ---- softmax cross-entropy over rows of the logit matrix -----------------------------
 // u [M][V] (storage type) is overwritten by dE/du = s (p - onehot); row_loss[m] = -s log p[label].
 hipError_t launch_softmax_rows(void* u, long long ldu, const int32_t* labels, float* row_loss,

@@ -276,6 +276,28 @@ def test_padded_widths_of_the_persistent_kernels_bf16(dims):
         check_step(dims, 1, seed=85, theta_scale=2.0, recurrent_sync=0)
 
 
+@pytest.mark.parametrize("defer", [False, True])
+@pytest.mark.parametrize("dims,mode", [
+    (dict(T=5, B=40, D=30, H=101, L=2, P=37, V=90), 1),     # every width misaligned
+    # two segments of three columns become two of eight.  (Two layers: with three, 36 frames and 11 classes the bf16
+    # roundings of dE/du and dE/da alone leave 4.1e-2 in b of the first layer, on the per-frame path without a twin too.)
+    (dict(T=4, B=9, D=8, H=3, L=2, P=0, V=11), 1),
+    (dict(T=21, B=60, D=33, H=64, L=1, P=67, V=9001), 1),   # the bottleneck alone
+    (dict(T=21, B=60, D=33, H=66, L=2, P=67, V=9001), 0),
+])
+def test_models_run_as_their_padded_twin(dims, mode, defer):
+    # against the oracle, and a second step with kept weight copies against the first step of a new learner on its weights
+    from paper_1904_04956_amd.harness import Learner
+    check_step(dims, mode, seed=86, theta_scale=2.0, defer_softmax_wgrad=defer)
+    dm, theta, x, labels = make_problem(dims, mode, 87, 2.0)
+    a = Learner(mode=mode, defer_softmax_wgrad=defer, **dims)
+    a.set_theta(theta); a.set_batch(x, labels); a.train_step(0.5); a.calgrad()
+    b = Learner(mode=mode, keep_weight_copies=False, defer_softmax_wgrad=defer, **dims)
+    b.set_theta(a.theta_numpy()); b.set_batch(x, labels); b.calgrad()
+    assert np.array_equal(a.grad_numpy(), b.grad_numpy()) and np.array_equal(a.z_numpy(), b.z_numpy())
+    a.close(); b.close()
+
+
 @pytest.mark.parametrize("dims", [
     dict(T=1, B=5, D=8, H=40, L=1, P=0, V=20),              # no exchange at all
     dict(T=4, B=1, D=8, H=1, L=2, P=0, V=20),               # one row, one unit
