@@ -88,7 +88,7 @@ struct blstm_ctx {
     BlockTensor tx, tz;                 // x (float mode, where D is padded) and z / dz
     size_t tTHETA, tGRAD, tX, tZ, tDZ;
     const void* ttheta_of;              // the weights the padded ones were made from (null: to be made)
-    std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel (whose saved gates only its backward twin reads)
+    std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel of recurrent.hip (1) or recurrent_small.hip (2) (whose saved gates only its backward twin reads)
     // profiling
     bool prof;
     std::vector<ProfRec> recs;
@@ -597,13 +597,18 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.gates = reinterpret_cast<unsigned short*>(G); a.c = C;
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            if (ctx->rec_sync == 1 && rec_fwd_fills(H)) {   // the backward twin's exchange copy is pre-filled on the side
+            const bool small = ctx->rec_sync == 1 && rec_small_supported(B, H);
+            if (ctx->rec_sync == 1 && (small || rec_fwd_fills(H))) {   // the backward twin's exchange copy is pre-filled on the side
                 a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l;
                 a.fill_words = ctx->dax_bytes / 16;
             }
             bool launched = false;
-            RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
-            ctx->fwd_persistent[l] = launched ? 1 : 0;
+            if (small) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
+            ctx->fwd_persistent[l] = launched ? 2 : 0;
+            if (!launched) {
+                RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
+                ctx->fwd_persistent[l] = launched ? 1 : 0;
+            }
             if (launched) continue;
         }
         for (int n = 0; n < T; ++n) {
@@ -647,7 +652,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
         RUN(PC_MISC, "copy of the LSTM output", hipMemcpyAsync(z_out, YL, (size_t)M * 2 * H * e, hipMemcpyDeviceToDevice, st));
     }
     ctx->have_forward = true;
-    ctx->dax_filled = persistent && ctx->rec_sync == 1 && rec_fwd_fills(H);
+    ctx->dax_filled = persistent && ctx->rec_sync == 1 && (rec_fwd_fills(H) || rec_small_supported(B, H));
     return BLSTM_OK;
 }
 
@@ -713,7 +718,9 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     wgrads.reserve(2 * ctx->L + 2);
     bool persistent = false;                            // some layer's forward pass ran the persistent kernel
     for (int l = 0; l < ctx->L; ++l) persistent = persistent || ctx->fwd_persistent[l] != 0;
-    const bool sentinel = persistent && (ctx->rec_sync == 1 || !rec_fenced(H));
+    bool small = false;                                 // (the small kernels and the padded widths know the sentinel protocol only)
+    for (int l = 0; l < ctx->L; ++l) small = small || ctx->fwd_persistent[l] == 2;
+    const bool sentinel = persistent && (ctx->rec_sync == 1 || small || !rec_fenced(H));
     if (persistent && !(ctx->keep_copies && ctx->uht_of == theta)) {   // U_h^T of every layer and direction in one launch
         TransposeUhArgs ta{};
         for (int l = 0; l < ctx->L; ++l)
@@ -778,7 +785,8 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));
+            if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
+            else RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));
             if (!rec_done)
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
         }

@@ -74,6 +74,12 @@ bool rec_fwd_fills(int H);
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.
 hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
 hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
+// The same for few sequences (recurrent_small.hip; sentinel protocol, nbg and tiles_per_group not used).  The saved records
+// and exchange copies have an order of their own: forward and backward go together.
+bool rec_small_supported(int B, int H);
+hipError_t launch_rec_small_fwd(const RecFwdArgs& a, hipStream_t st, bool* launched);
+hipError_t launch_rec_small_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched);
+
 // ---- persistent recurrent kernels in float (H up to 1024) ------------------------------
 struct Rec32FwdArgs {
     const float* uh[2];           // U_h per direction, [4H][H]

@@ -276,6 +276,17 @@ def test_padded_widths_of_the_persistent_kernels_bf16(dims):
         check_step(dims, 1, seed=85, theta_scale=2.0, recurrent_sync=0)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=1, B=1, D=8, H=8, L=1, P=0, V=20),               # nothing exchanged; half of the only block of columns
+    dict(T=5, B=17, D=8, H=40, L=2, P=16, V=20),            # one row in the second tile, eight units in the last slices
+    dict(T=4, B=16, D=24, H=128, L=1, P=0, V=20),
+    dict(T=4, B=64, D=24, H=512, L=2, P=0, V=20),           # one workgroup per CU, every tile whole
+    dict(T=3, B=15, D=8, H=1024, L=1, P=0, V=20),           # the widest slices
+])
+def test_kernels_for_few_sequences_bf16(dims):
+    check_step(dims, 1, seed=88, theta_scale=2.0 if dims["H"] < 500 else 1.0)
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims,mode", [
     (dict(T=5, B=40, D=30, H=101, L=2, P=37, V=90), 1),     # every width misaligned
