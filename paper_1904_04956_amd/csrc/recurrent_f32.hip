@@ -72,6 +72,24 @@ __device__ __forceinline__ bool settle(uint4 (&f)[N], const float* base, F off, 
     }
 }
 
+// Waits until the word at p, one per producing workgroup and lane with `mine` set, is written, before any data is looked at
+// (see recurrent_small.hip: with eight or more fragments a wavefront, early looks cost more than the probe).
+constexpr int PROBE_FROM = 8;
+__device__ __forceinline__ bool probe_producers(const float* p, bool mine, unsigned* abort_word, unsigned long long limit) {
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        const unsigned v = mine ? ld_agent(reinterpret_cast<const unsigned*>(p)) : 0u;
+        if (__all(v != SENT32)) return false;
+        if ((it & 31u) == 0) {
+            if (ld_agent(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
+
 // Workgroup -> (direction, group of batch tiles, unit slice).  Ids are dealt round-robin to the eight XCDs; each XCD takes
 // a contiguous eighth of the sequence, so that the slices of a group sit on as few XCDs as they fill.
 struct Place { int d, bg, u; bool real; };
@@ -147,8 +165,13 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) 
         if (n > 0) {
             const float* base = a.hx + ((size_t)(tp * 2 + d) * NT + tile) * nu * 256;
             uint4 af[NQ];
+            bool gu = false;
+            if constexpr (NQ >= PROBE_FROM) {            // lane q: the last word of the wavefront's pair q
+                if (ntl == 1) gu = probe_producers(base + min(wave * NQ + lane, nu - 1) * 256 + 255, lane < NQ, a.abort_word, a.limit_ticks);
+                asm volatile("" ::: "memory");
+            }
             fetch<NQ>(af, base, off);
-            if (settle<NQ>(af, base, off, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if (settle<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             f32x16_t acc;
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
@@ -261,11 +284,15 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
         if (ni > 0) {
             const float* base = a.dax + ((size_t)(tn * 2 + d) * NT + tile) * XT;
             uint4 af[2][SL];
+            bool gu = false;
+            if constexpr (NQ >= PROBE_FROM) {            // lane q: the last word of the gate's block q
+                if (ntl == 1) gu = probe_producers(base + (wave * nu + min(lane, nu - 1)) * 256 + 255, lane < NQ, a.abort_word, a.limit_ticks);
+                asm volatile("" ::: "memory");
+            }
             fetch<SL>(af[0], base, off);
             f32x4_t acc[2];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { acc[0][e] = 0.0f; acc[1][e] = 0.0f; }
-            bool gu = false;
 #pragma unroll
             for (int s = 0; s < NSL; ++s) {
                 if (s + 1 < NSL) fetch<SL>(af[(s + 1) & 1], base, [&](int q) { return off((s + 1) * SL + q); });

@@ -57,6 +57,30 @@ __device__ __forceinline__ bool settle(uint4 (&f)[N], const bf16_t* base, F off,
     }
 }
 
+// Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
+// was abandoned.  Looking at the data straight away saves this round trip when the first look succeeds or the
+// data is little; with eight or more fragments a wavefront, loads that come too early cost more than they save and leave
+// stale lines behind (three layers, T = 21, forward / rest of the step in us, straight against probe first: H = 512, 8
+// sequences 132 / 234 and 151 / 205 -- four fragments forward, sixteen backward --, H = 1024, 30 sequences 248 / 566 and
+// 221 / 461, H = 128, 8 sequences 100 / 138 and 117 / 153).
+constexpr int PROBE_FROM = 8;
+__device__ __forceinline__ bool probe_producers(const bf16_t* p, bool mine, unsigned* abort_word, unsigned long long limit) {
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        const unsigned v = mine ? ld_coh_u32(reinterpret_cast<const unsigned*>(p)) : 0u;
+        if (__all(!has_sentinel_half(v))) return false;
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
+// Lane 2 q + i probes the last two elements that slice i of block q writes.
+constexpr int LAST_OF_SLICE = 128 + 15 * 8 + 6;
+
 // The value of four neighbouring lanes (units 4k .. 4k + 3 of one row) as four bf16, in the first of them.
 __device__ __forceinline__ uint2 quad_bf16(float v) {
     const unsigned own = coh_bf16(v);
@@ -129,8 +153,13 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
         if (n > 0) {
             const bf16_t* base = a.hx + ((size_t)(tp * 2 + d) * NT + tile) * blocks * PAIR;
             uint4 af[NQ];
+            bool gu = false;
+            if constexpr (NQ >= PROBE_FROM) {
+                gu = probe_producers(base + min(wave * NQ + (lane >> 1), blocks - 1) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
+                asm volatile("" ::: "memory");
+            }
             look<NQ>(af, base, off);
-            if (settle<NQ>(af, base, off, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if (settle<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             f32x4_t acc[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g)
@@ -222,8 +251,13 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
         if (n < T - 1) {
             const bf16_t* base = a.dax + ((size_t)(tn * 2 + d) * NT + tile) * XT;
             uint4 af[NQ];
+            bool gu = false;
+            if constexpr (NQ >= PROBE_FROM) {
+                gu = probe_producers(base + (wave * blocks + min(lane >> 1, blocks - 1)) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
+                asm volatile("" ::: "memory");
+            }
             look<NQ>(af, base, off);
-            if (settle<NQ>(af, base, off, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if (settle<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             f32x4_t acc[2];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { acc[0][e] = 0.0f; acc[1][e] = 0.0f; }
