@@ -68,7 +68,7 @@ struct RecBwdArgs {
 };
 bool rec_supported(int H);                  // whether the persistent kernels take this width
 bool rec_fenced(int H);                     // whether they are built with the fenced protocol too
-int rec_groups(int H, int tiles);           // batch groups per direction for so many 32-row tiles
+int rec_groups(int H, int tiles, int per_cu = 1);   // batch groups per direction for so many 32-row tiles and workgroups per CU
 // Whether launch_rec_fwd for this width honours RecFwdArgs::fill.
 bool rec_fwd_fills(int H);
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.

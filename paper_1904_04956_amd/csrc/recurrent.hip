@@ -31,6 +31,7 @@
 // gradient and the updated weights; blstm_device_status reports it as well.
 #include "exchange.hpp"
 #include "kernels.hpp"
+#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -181,8 +182,10 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 // whose exchanged chunks can be loaded ahead, and only then are registers set aside for them.
 // PADDED: the layer is narrower than the kernel's NW * KW cells (any multiple of 8): U_h counts as zero beyond it, the
 // exchange holds whole slices of 32 units, and the units beyond the layer come out as zeros that are not stored row-major.
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
-__global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
+// LEAN: few enough registers for two workgroups per CU: one set of inputs, asked for behind the item's own operand, no look
+// ahead at the next operand, half of the accumulators and of the partial sums at a time.
+template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
+__global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
     // in the other, so nothing is copied (a copy would have to wait for loads issued a moment before).
     float ax0[EPT][4], cp0[EPT], ax1[EPT][4], cp1[EPT];
-    issue_inputs(0, ax0, cp0);
+    if constexpr (!LEAN) issue_inputs(0, ax0, cp0);
     // Waited for here, once: the compiler places its waits for the worst path into the loop, and with these
     // loads still in flight on the way in, that path would make every item wait for its freshly issued loads.
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0) (expcnt and lgkmcnt left alone)
@@ -280,7 +283,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
     for (int e = 0; e < EPT; ++e) ccarry[e] = 0.0f;
     // With several batch tiles per workgroup the next item's h was written a whole frame ago: its
     // chunks are loaded while this item computes (checked for the sentinel like any other load).
-    uint4 apre[MULTI ? KSTEPS : 1];
+    uint4 apre[MULTI && !LEAN ? KSTEPS : 1];
     bool have_pre = false;
     // The row-major outputs of an item (c, the gates, h for the next layer) are not on the frame-to-frame path:
     // they wait in registers until the next item has issued its loads of the exchanged h, and go out behind them.
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                 // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
                 const bf16_t* probe = hb + xoff(PADDED ? min(wave * (KW / 32) + lane, NU - 1) * 32 + 31 : wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
                 bool got = false, gu = false;
-                if constexpr (MULTI) {
+                if constexpr (MULTI && !LEAN) {
                     if (have_pre) {
 #pragma unroll
                         for (int q = 0; q < KSTEPS; ++q) afrag[q] = apre[q];
@@ -362,17 +365,23 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                 for (int q = 0; q < KSTEPS; ++q)
                     afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
-            f32x16_t acc[4];
+            if constexpr (LEAN && KW < 128) issue_inputs(item, axn, cpn);    // (in flight behind the products; the widest slice has no registers for them yet)
+            // (two gates at a time where registers are short)
+            constexpr int GP = LEAN ? 2 : 4;
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g0 = 0; g0 < 4; g0 += GP) {
+            f32x16_t acc[GP];
+#pragma unroll
+            for (int g = 0; g < GP; ++g)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[g][e] = 0.0f;
 #pragma unroll
             for (int q = 0; q < KSTEPS; ++q)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g][q], acc[g]);
+                for (int g = 0; g < GP; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g0 + g][q], acc[g]);
+            if (g0 == 0) {
             have_pre = false;
-            if constexpr (MULTI && SENTINEL && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
+            if constexpr (MULTI && !LEAN && SENTINEL && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
                 const int n2 = (item + 1) / ntl, i2 = (item + 1) - n2 * ntl;
                 const int tp2 = d ? T - n2 : n2 - 1;
                 const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
@@ -380,38 +389,48 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
                 load_chunks_cached<KSTEPS>(apre, hb2 + ohp, lastp);
                 have_pre = true;
             }
+            }
             // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < GP; ++g)
 #pragma unroll
                 for (int rq = 0; rq < 4; ++rq)
-                    l4[((wave * 4 + g) * 4 + rq) * 64 + lane] =
+                    l4[((wave * 4 + g0 + g) * 4 + rq) * 64 + lane] =
                         make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
+            }
+            if constexpr (LEAN && KW == 128) issue_inputs(item, axn, cpn);
             if (SENTINEL) lds_barrier(); else __syncthreads();
             // all partial sums of this thread's rows are read before any is added: the reads then
             // overlap instead of each waiting for its LDS round trip
             static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
-            float4 part[NW][4][EPT / 4];
+            // (in two rounds where registers are short)
+            constexpr int WR = LEAN && KW == 128 ? NW / 2 : NW;
 #pragma unroll
-            for (int w2 = 0; w2 < NW; ++w2)
+            for (int w0 = 0; w0 < NW; w0 += WR) {
+                float4 part[WR][4][EPT / 4];
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
+                for (int w2 = 0; w2 < WR; ++w2)
 #pragma unroll
-                    for (int e4 = 0; e4 < EPT / 4; ++e4) part[w2][g][e4] = l4[((w2 * 4 + g) * 4 + (EPT / 4) * wave + e4) * 64 + lane];
+                    for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int w2 = 0; w2 < NW; ++w2)
+                        for (int e4 = 0; e4 < EPT / 4; ++e4) part[w2][g][e4] = l4[(((w0 + w2) * 4 + g) * 4 + (EPT / 4) * wave + e4) * 64 + lane];
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
+                for (int w2 = 0; w2 < WR; ++w2)
 #pragma unroll
-                    for (int e4 = 0; e4 < EPT / 4; ++e4) {
-                        const float4 v = part[w2][g][e4];
-                        sum[4 * e4][g] += v.x; sum[4 * e4 + 1][g] += v.y; sum[4 * e4 + 2][g] += v.z; sum[4 * e4 + 3][g] += v.w;
-                    }
+                    for (int g = 0; g < 4; ++g)
+#pragma unroll
+                        for (int e4 = 0; e4 < EPT / 4; ++e4) {
+                            const float4 v = part[w2][g][e4];
+                            sum[4 * e4][g] += v.x; sum[4 * e4 + 1][g] += v.y; sum[4 * e4 + 2][g] += v.z; sum[4 * e4 + 3][g] += v.w;
+                        }
+                if (WR < NW) asm volatile("" ::: "memory");
+            }
         }
         // (The next item's inputs come from HBM, and a CU's vector memory pipeline returns data in order: issued
         // before the barrier above they would sit in front of another wavefront's loads of the exchanged h and
         // add their latency to the frame-to-frame path.  They are issued below, once h has gone out.)
         flush_tail();                                     // at the latest here: the loads issued below may read what it stores
+        if constexpr (LEAN) if (n == 0) issue_inputs(item, axn, cpn);
         float cp[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : cpl[e];
@@ -449,7 +468,7 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
             bf16_t* xp = hxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u + (xcol & 7u));
             if (SENTINEL) st_coh_8B(xp, hq); else *reinterpret_cast<uint2*>(xp) = hq;
         }
-        if (KW <= 128 && item + 1 < nitems) issue_inputs(item + 1, axn, cpn);
+        if (KW <= 128 && !LEAN && item + 1 < nitems) issue_inputs(item + 1, axn, cpn);
         if (SENTINEL) lds_barrier();                     // frees the LDS buffer for the next item
         else signal_counter(cnt + i);                    // barrier inside: same role
         // row-major outputs (h for the next layer, c and the gates for the backward pass): kept for flush_tail
@@ -463,7 +482,9 @@ __global__ __launch_bounds__(64 * NW) void rec_fwd_kernel(RecFwdArgs a) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) ccarry[e] = cn[e];
     };
-    if constexpr (KW <= 128) {
+    if constexpr (LEAN) {
+        for (int item = 0; item < nitems; ++item) do_item(item, ax0, cp0, ax0, cp0);
+    } else if constexpr (KW <= 128) {
         for (int item = 0; item < nitems; item += 2) {
             do_item(item, ax0, cp0, ax1, cp1);
             if (item + 1 < nitems) do_item(item + 1, ax1, cp1, ax0, cp0);
@@ -848,14 +869,14 @@ hipError_t prepare(K kernel, int threads, size_t dyn_lds, int grid, FitCache* ca
     return hipSuccess;
 }
 
-template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
+template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
     bool fits = false;
     static thread_local FitCache cache{false, 0};
-    hipError_t e = prepare(rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>, 64 * NW, lds, grid, &cache, &fits);
+    hipError_t e = prepare(rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>, 64 * NW, lds, grid, &cache, &fits);
     if (e != hipSuccess || !fits) return e;
-    hipLaunchKernelGGL((rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>), dim3(grid), dim3(64 * NW), lds, st, a);
+    hipLaunchKernelGGL((rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>), dim3(grid), dim3(64 * NW), lds, st, a);
     *launched = true;
     return hipGetLastError();
 }
@@ -872,7 +893,23 @@ hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched
 }
 template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {
-    return a.tiles_per_group > 1 ? run_one<4, KW, S, FULL, true, PADDED>(a, grid, st, launched) : run_one<4, KW, S, FULL, false, PADDED>(a, grid, st, launched);
+    if (a.tiles_per_group == 1) return run_one<4, KW, S, FULL, false, PADDED>(a, grid, st, launched);
+    if constexpr (std::is_same_v<A, RecFwdArgs> && S && (KW < 128 || (KW == 128 && !PADDED))) {
+        // Several tiles per workgroup, forward: twice the groups with two workgroups per CU, one of which computes while the
+        // other waits for its operand.  Two layers, T = 21, us, one per CU against two: H = 512, 1000 sequences 927 / 852,
+        // 2048 sequences 1831 / 1601; H = 256, 600 sequences 350 / 300.  Not where every workgroup has two tiles that would
+        // become one: nothing is left to overlap (512 sequences of 512 cells 496 / 572).  The backward kernel, whose time
+        // is the traffic of its operand, gains nothing (rest of the step 2947 / 3040).
+        A b = a;
+        const int nu = (a.H + 31) / 32, tiles = (a.B + 31) / 32;
+        if (a.tiles_per_group > 2 || 4 * tiles <= 7 * a.nbg) {
+            b.nbg = rec_groups(a.H, tiles, 2);
+            b.tiles_per_group = (tiles + b.nbg - 1) / b.nbg;
+            hipError_t e = run_one<4, KW, S, false, true, PADDED, true>(b, grid_groups(b.nbg) * nu, st, launched);
+            if (e != hipSuccess || *launched) return e;
+        }
+    }
+    return run_one<4, KW, S, FULL, true, PADDED>(a, grid, st, launched);
 }
 // A width that is the kernel's own.
 template <int KW, typename A>
@@ -906,8 +943,8 @@ bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
 // Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than
 // one workgroup per CU (32).
-int rec_groups(int H, int tiles) {
-    const int most = 4 * (32 / ((H + 31) / 32));
+int rec_groups(int H, int tiles, int per_cu) {
+    const int most = 4 * (32 * per_cu / ((H + 31) / 32));
     return tiles < most ? tiles : most;
 }
 // Whether the forward kernel for this width also fills RecFwdArgs::fill (the wider ones have no register to spare).

@@ -287,6 +287,16 @@ def test_kernels_for_few_sequences_bf16(dims):
     check_step(dims, 1, seed=88, theta_scale=2.0 if dims["H"] < 500 else 1.0)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=3, B=290, D=8, H=512, L=1, P=0, V=20),           # ten tiles: one per workgroup instead of one or two
+    dict(T=4, B=1030, D=8, H=512, L=1, P=0, V=20),          # 33 tiles over sixteen groups, the last one empty
+    dict(T=3, B=1600, D=8, H=256, L=1, P=0, V=20),
+    dict(T=3, B=1000, D=8, H=360, L=1, P=0, V=20),
+])
+def test_two_workgroups_per_cu_forward_bf16(dims):
+    check_step(dims, 1, seed=89, theta_scale=1.0)
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims,mode", [
     (dict(T=5, B=40, D=30, H=101, L=2, P=37, V=90), 1),     # every width misaligned
