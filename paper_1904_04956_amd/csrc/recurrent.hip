@@ -938,7 +938,7 @@ hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) 
 
 // Supported widths: multiples of 8 up to 1024, always on four wavefronts that split the contraction (four batch rows per
 // thread in every variant).  128, 256, 512 and 1024 have kernels of their own; the others run padded to the next multiple
-// of 128 (H = 320, 50 sequences: 70 us a layer forward and 76 backward, where two launches per frame took 640 and 540).
+// of 128 (H = 320, 50 sequences: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
 bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
 // Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than

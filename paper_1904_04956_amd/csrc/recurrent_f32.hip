@@ -217,8 +217,8 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) 
 }
 
 // ------------------------------------------------------------------------------ backward
-// H' = 16 NQ; wavefront w contracts gate w's H columns of dE/da.  H = 512, 64 sequences: 17 us a
-// frame with the weight gradients and the softmax layer of a small model (39 with launches per frame).
+// H' = 16 NQ; wavefront w contracts gate w's H columns of dE/da.  H = 512, 64 sequences: 15 us a
+// frame with the weight gradients and the softmax layer of a small model (29 with launches per frame).
 template <int NQ>
 __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) {
     constexpr int PS = 20;
