@@ -176,6 +176,7 @@ int softmax_xent_run(blstm_ctx* ctx, const SoftmaxScratch& sc, const void* theta
         d.M = M; d.N = V;
         d.seg[0] = GemmSeg{z, at(theta, ctx->off_ws, e), Z, Z, 0, 0, Z};
         d.C = U; d.ldc = sc.ldu; d.c_pad = padded_rows(V, sc.ldu);
+        d.long_parts = true;
         d.bias = at(theta, ctx->off_bs, e);
         RUN(PC_GEMM_LOGITS, "logits", launch_gemm(d, st));
     }

@@ -1165,6 +1165,14 @@ hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
     }
 }
 
+// As many parts, up to `most`, as put no more than `target` workgroups on `tiles` tiles and leave each at least min_slabs slabs.
+int parts_of(long long target, int most, long long tiles, int slabs, int min_slabs) {
+    int s = (int)(target / tiles);
+    if (s > most) s = most;
+    while (s > 1 && slabs / s < min_slabs) --s;
+    return s < 1 ? 1 : s;
+}
+
 // How a product of this shape is run.  allow_r: the 256x128 direct tile may be chosen (bf16 operands in one of its forms).
 GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     GemmPlan p{GEMM_TILE_128, false, 1, 0};
@@ -1184,7 +1192,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
             // at large batch): the same tile, split along K into the smallest number of parts that fills whole
             // rounds of 512 resident workgroups to 90 %, if every part keeps 64 slabs and the float partial tiles
             // stay below an eighth of the operand bytes.
-            if (tr >= 128 && d.nseg == 1 && d.partial && !d.rowsum) {
+            if (tr >= 128 && d.nseg == 1 && d.partial && !d.rowsum && (!d.long_parts || (d.M % 256 == 0 && Ne % 128 == 0 && ktot % 64 == 0))) {
                 const int slabs = (d.seg[0].K + 63) / 64;
                 for (int s = 1; s <= 8; ++s) {
                     const double rounds = (double)tr * s / 512.0;
@@ -1220,7 +1228,18 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     // the float partial tiles' way out and back.  Measured against at most eight parts of at least eight slabs and one
     // segment only: dz of 336 frames (6 tiles, K = 32000) 49 -> 21 us, the dA W products of the paper-shaped model in float
     // at batch 64 (dx: 88 tiles, K = 4096) 301 -> 137 us on average.
-    if (!d.add && d.partial && t128 <= 1024) {
+    // long_parts: at most eight parts of at least eight slabs, up to one workgroup per CU (of 64 slabs: up to two).  For the
+    // logits, which are rounded to bf16 and then exponentiated: one ulp of a logit of 4 is 3 % of its class's probability,
+    // so that another order of their sums shows in dz and the gradient.  Cut into parts of four slabs they moved single
+    // elements of the gradient by 5e-2 of its root mean square (84 frames, z of 1024, 500 classes).
+    if (d.long_parts) {
+        if (!d.add && d.partial && d.nseg == 1 && t128 <= 256) {
+            const int bk = d.in_type == DT_BF16 ? 64 : 32, slabs = (ktot + bk - 1) / bk;
+            const int s1 = parts_of(256, 8, t128, slabs, 8), s2 = parts_of(512, 8, t128, slabs, 64), s = s1 > s2 ? s1 : s2;
+            const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
+            if (s > 1 && need <= d.partial_bytes) { p.splits = s; p.partial_bytes = need; }
+        }
+    } else if (!d.add && d.partial && t128 <= 1024) {
         const int bk = d.in_type == DT_BF16 ? 64 : 32;
         int slabs = 0;
         for (int s = 0; s < d.nseg; ++s) slabs += (d.seg[s].K + bk - 1) / bk;
@@ -1267,15 +1286,9 @@ size_t noalloc_partial_bytes(int M, int N, int K, DType in_type) {
     const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256), t128 = (long long)((M + 127) / 128) * ((N + 127) / 128);
     const int bk = in_type == DT_BF16 ? 64 : 32, slabs = (K + bk - 1) / bk;
     auto bytes = [&](int s) { return s > 1 ? (size_t)s * ((size_t)M * N + M) * sizeof(float) : (size_t)0; };
-    auto parts = [&](long long target, int most, long long tiles, int min_slabs) {
-        int s = (int)(target / tiles);
-        if (s > most) s = most;
-        while (s > 1 && slabs / s < min_slabs) --s;
-        return s < 1 ? 1 : s;
-    };
     size_t need = 0;
     if (t128 <= 256) {
-        const int s1 = parts(256, 8, t128, 8), s2 = parts(512, 8, t128, 64);
+        const int s1 = parts_of(256, 8, t128, slabs, 8), s2 = parts_of(512, 8, t128, slabs, 64);
         if (in_type == DT_BF16 || !(t256 >= 512 && K >= 512)) need = bytes(s1 > s2 ? s1 : s2);
     }
     if (in_type == DT_BF16 && M % 256 == 0 && N % 128 == 0 && K % 64 == 0) {
@@ -1289,7 +1302,7 @@ size_t noalloc_partial_bytes(int M, int N, int K, DType in_type) {
             }
         }
         if (tr < 480 && t256 <= 64 && N % 256 == 0) {
-            const int s = parts(256, 16, t256, 24);
+            const int s = parts_of(256, 16, t256, slabs, 24);
             if (s > 1 && t256 * s >= 192 && bytes(s) > need) need = bytes(s);
         }
     }
