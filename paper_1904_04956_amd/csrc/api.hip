@@ -61,7 +61,9 @@ struct blstm_ctx {
     std::vector<size_t> wY, wG, wC;
     std::vector<size_t> wDA;  // dE/da of every layer: all of them feed the weight-gradient products at the end of the backward pass
     size_t wAX, wPRE, wDY[2], wDH, wDC, wLOGITS, wROWLOSS, wUHT, wCNT, wPART, wHX, wDAX, hx_bytes, dax_bytes, part_bytes, ws_bytes;
-    long long ldu;            // row distance of the logit matrix in the workspace: V rounded up to whole 16-byte words
+    long long ldu;            // row distance of the logit matrix (see SoftmaxScratch)
+    size_t soft_part;         // split-K scratch of the softmax block's products, the same in both entry points
+    size_t noalloc_need;      // scratch by which softmax_xent_fwd_bwd_noalloc decides whether a call fits the resident array
     int Dp;                   // 0, or the first layer's input width rounded up to whole tiles (padded copies of x and W_x)
     size_t wXP, wWP;
     int rec_nbg, rec_tiles;   // batch groups per direction and 32-row tiles per group of the persistent kernels
@@ -85,7 +87,7 @@ struct blstm_ctx {
     // otherwise.  The workspace is the twin's, then its weights, gradient, x, z and dz.
     blstm_ctx* twin;
     std::vector<BlockTensor> tparam;    // every tensor of the flat vector, compact here and padded there; the softmax layer's two last
-    BlockTensor tx, tz;                 // x (float mode, where D is padded) and z / dz
+    BlockTensor tx, tz, tu;             // x (float mode, where D is padded); z / dz of the stack and of the softmax block
     size_t tTHETA, tGRAD, tX, tZ, tDZ;
     const void* ttheta_of;              // the weights the padded ones were made from (null: to be made)
     std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel of recurrent.hip (1) or recurrent_small.hip (2) (whose saved gates only its backward twin reads)
@@ -143,8 +145,8 @@ inline char* at(void* base, size_t elems, size_t esz) { return static_cast<char*
 
 // Scratch of the softmax cross-entropy: the logit matrix [M][V] (storage type, overwritten in place by dE/du),
 // one loss term per frame, and the float partial tiles of products split along K.
-// ldu: distance of the matrix's rows; V rounded up to 16 bytes wherever the scratch has the room (rows of a ragged V then
-// start aligned and the products run unguarded; the row kernel leaves zeros in the padding).
+// ldu: distance of the matrix's rows; V rounded up to 16 bytes (rows of a ragged V then start aligned and the products run
+// unguarded; the row kernel leaves zeros in the padding), unless the resident array takes the shape without that only.
 struct SoftmaxScratch { char* logits; long long ldu; float* row_loss; float* partial; size_t partial_bytes; };
 inline bool padded_rows(long long V, long long ldu) { return ldu % 8 == 0 && ldu > V; }
 
@@ -156,6 +158,7 @@ GemmDesc softmax_wgrad_desc(const blstm_ctx* ctx, const char* U, long long ldu, 
     d.a_pad = padded_rows(ctx->V, ldu);
     d.C = grad + ctx->off_ws; d.ldc = ctx->zdim;
     d.rowsum = grad + ctx->off_bs;                     // db_s = sum over frames of du
+    d.partial_bytes = ctx->soft_part;
     return d;
 }
 
@@ -263,10 +266,14 @@ int make_twin(blstm_ctx* c) {
         c->tparam.push_back(BlockTensor{c->off_bp, t->off_bp, 1, 1, 1, 1, c->P, t->P});
     }
     const int zs = c->P > 0 ? 1 : 2, z = c->P > 0 ? c->P : H, zp = c->P > 0 ? t->P : Hp;
-    c->tparam.push_back(BlockTensor{c->off_ws, t->off_ws, 1, c->V, c->V, zs, z, zp});
+    // (the softmax block has z in one piece, padded at its end: its sums then have the order they have without a twin)
+    c->tparam.push_back(BlockTensor{c->off_ws, t->off_ws, 1, c->V, c->V, 1, c->zdim, t->zdim});
     c->tparam.push_back(BlockTensor{c->off_bs, t->off_bs, 1, 1, 1, 1, c->V, c->V});
     c->tx = BlockTensor{0, 0, 1, c->M, c->M, 1, c->D, t->D};
     c->tz = BlockTensor{0, 0, 1, c->M, c->M, zs, z, zp};
+    c->tu = BlockTensor{0, 0, 1, c->M, c->M, 1, c->zdim, t->zdim};
+    if (t->part_bytes < c->soft_part) c->soft_part = t->part_bytes;
+    t->soft_part = c->soft_part; t->ldu = c->ldu;
     size_t w = up256(t->ws_bytes);
     c->tTHETA = w; w += up256(t->nparam * c->esz);
     c->tGRAD = w;  w += up256(t->nparam * 4);
@@ -308,14 +315,14 @@ int twin_xent(blstm_ctx* ctx, const void* theta, const void* z, const int32_t* l
     float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
     const bool same = ctx->twin->zdim == ctx->zdim;
     if (!same) {
-        rc = check_hip(launch_pad_blocks(&ctx->tz, 1, z, ctx->ws + ctx->tZ, ctx->st, st), "padded z");
+        rc = check_hip(launch_pad_blocks(&ctx->tu, 1, z, ctx->ws + ctx->tZ, ctx->st, st), "padded z");
         if (rc != BLSTM_OK) return rc;
     }
     void* tdz = same ? dz : ctx->ws + ctx->tDZ;
     rc = softmax_xent_fwd_bwd(ctx->twin, ctx->ws + ctx->tTHETA, same ? z : ctx->ws + ctx->tZ, labels, loss_dev, tdz, tg, st);
     if (rc != BLSTM_OK) return rc;
     if (!same) {
-        rc = check_hip(launch_compact_blocks(&ctx->tz, 1, tdz, dz, ctx->st, st), "dz");
+        rc = check_hip(launch_compact_blocks(&ctx->tu, 1, tdz, dz, ctx->st, st), "dz");
         if (rc != BLSTM_OK) return rc;
     }
     ctx->pend_grad = grad;
@@ -452,12 +459,29 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         auto upd = [&](int m, int n, int k, int batch) { size_t b = gemm_partial_bytes(m, n, k, batch, S); if (b > need) need = b; };
         upd(c->M, c->zdim, c->V, 1);                              // dz
         upd(c->V, c->zdim, c->M, 1);                              // dW_s
+        const size_t logits = gemm_partial_bytes(c->M, c->V, c->zdim, 1, S, true);
+        if (logits > need) need = logits;
         if (c->P > 0) { upd(c->P, 2 * c->H, c->M, 1); upd(c->M, 2 * c->H, c->P, 1); }
         for (int l = 0; l < c->L; ++l) { upd(4 * c->H, c->din(l), c->M, 2); upd(4 * c->H, c->H, (c->T - 1) * c->B, 2); }
         if (c->L > 1) upd(c->M, 2 * c->H, 8 * c->H, 1);           // dx
         upd(c->B, c->H, 4 * c->H, 2);                             // recurrent gradient of the step-by-step path
         c->wPART = w; c->part_bytes = up256(need);
         w += c->part_bytes;
+        // What the resident array of softmax_xent_fwd_bwd_noalloc leaves of this for the split products, after the logits (with
+        // padded rows where that takes nothing from the products' need) and the row losses.  The other entry point keeps to
+        // it wherever that one takes the shape, so that both split alike and give the same bits.
+        size_t part = noalloc_partial_bytes(c->M, c->zdim, c->V, S);
+        const size_t part2 = noalloc_partial_bytes(c->V, c->zdim, c->M, S);
+        part = up256(part2 > part ? part2 : part);
+        const size_t rows = up256(M * 4), padded = up256(M * (size_t)c->ldu * e), compact = up256(M * (size_t)c->V * e);
+        c->noalloc_need = compact + rows + part;
+        c->soft_part = c->part_bytes;
+        if (c->noalloc_need <= BLSTM_NOALLOC_SCRATCH_BYTES) {
+            const bool pad = padded + rows + part <= BLSTM_NOALLOC_SCRATCH_BYTES;
+            if (!pad) c->ldu = c->V;
+            const size_t left = BLSTM_NOALLOC_SCRATCH_BYTES - rows - (pad ? padded : compact);
+            if (left < c->soft_part) c->soft_part = left;
+        }
     }
     c->keep_copies = false; c->wxp_of = nullptr; c->uht_of = nullptr;
     c->defer_ws = false; c->pend_z = nullptr; c->pend_grad = nullptr;
@@ -666,7 +690,7 @@ int softmax_xent_fwd_bwd(blstm_ctx* ctx, const void* theta, const void* z, const
         return fail(BLSTM_ERR_ALIGN, "softmax_xent_fwd_bwd: pointers must be 16-byte aligned");
     if (ctx->twin) return twin_xent(ctx, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream));
     SoftmaxScratch sc{ctx->ws + ctx->wLOGITS, ctx->ldu, reinterpret_cast<float*>(ctx->ws + ctx->wROWLOSS),
-                      reinterpret_cast<float*>(ctx->ws + ctx->wPART), ctx->part_bytes};
+                      reinterpret_cast<float*>(ctx->ws + ctx->wPART), ctx->soft_part};
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), ctx->defer_ws);
 }
 
@@ -675,24 +699,14 @@ int softmax_xent_fwd_bwd_noalloc(blstm_ctx* ctx, const void* theta, const void* 
     if (!ctx || !theta || !z || !labels || !loss_dev || !dz || !grad) return fail(BLSTM_ERR_NULL, "softmax_xent_fwd_bwd_noalloc: null argument");
     if (!aligned16(theta) || !aligned16(z) || !aligned16(dz) || !aligned16(grad))
         return fail(BLSTM_ERR_ALIGN, "softmax_xent_fwd_bwd_noalloc: pointers must be 16-byte aligned");
-    // layout of the resident array: logits, row losses, split-K partial tiles (whatever is left)
-    const size_t logits = up256((size_t)ctx->M * (size_t)ctx->V * ctx->esz), rows = up256((size_t)ctx->M * 4);
-    size_t part = noalloc_partial_bytes(ctx->M, ctx->zdim, ctx->V, ctx->st);
-    const size_t part2 = noalloc_partial_bytes(ctx->V, ctx->zdim, ctx->M, ctx->st);
-    if (part2 > part) part = part2;
-    part = up256(part);
-    if (logits + rows + part > BLSTM_NOALLOC_SCRATCH_BYTES)
+    if (ctx->noalloc_need > BLSTM_NOALLOC_SCRATCH_BYTES)
         return fail(BLSTM_ERR_WORKSPACE, "softmax_xent_fwd_bwd_noalloc: T*B = %d frames of V = %d classes need %zu bytes of scratch, "
-                    "the resident array holds %zu", ctx->M, ctx->V, logits + rows + part, (size_t)BLSTM_NOALLOC_SCRATCH_BYTES);
+                    "the resident array holds %zu", ctx->M, ctx->V, ctx->noalloc_need, (size_t)BLSTM_NOALLOC_SCRATCH_BYTES);
     char* base = nullptr;
     const int rc = resident_scratch(&base);
     if (rc != BLSTM_OK) return rc;
-    // (rows padded to 16 bytes where that leaves the split-K scratch above untouched)
-    const size_t padded = up256((size_t)ctx->M * (size_t)ctx->ldu * ctx->esz);
-    const bool pad = padded + rows + part <= BLSTM_NOALLOC_SCRATCH_BYTES;
-    const size_t first = pad ? padded : logits;
-    SoftmaxScratch sc{base, pad ? ctx->ldu : ctx->V, reinterpret_cast<float*>(base + first), reinterpret_cast<float*>(base + first + rows),
-                      BLSTM_NOALLOC_SCRATCH_BYTES - first - rows};
+    const size_t first = up256((size_t)ctx->M * (size_t)ctx->ldu * ctx->esz), rows = up256((size_t)ctx->M * 4);   // (logits, row losses, split-K partial tiles)
+    SoftmaxScratch sc{base, ctx->ldu, reinterpret_cast<float*>(base + first), reinterpret_cast<float*>(base + first + rows), ctx->soft_part};
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), false);
 }
 

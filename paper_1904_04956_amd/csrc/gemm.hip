@@ -1123,10 +1123,9 @@ hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
     GemmPlan plan = make_plan(d, df);
     // the plan looks at the shape only: check what it chose against the operands' alignment and fall back
     int mode = run_mode<TI>(d, P, kTileM[plan.tile], kTileN[plan.tile]);
-    if ((plan.tile == GEMM_TILE_256X128 && mode == GUARDED) ||
-        (plan.tile == GEMM_TILE_256 && (mode == GUARDED || (sizeof(TI) == 2 && !(df && !d.atrans && d.btrans))))) {
-        plan = make_plan(d, false);
-        if (plan.tile == GEMM_TILE_256) { plan.tile = GEMM_TILE_128; plan.splits = 1; plan.partial_bytes = 0; plan.deep = false; }
+    // (on the 128x128 tile with the plan's number of parts: how the sums are ordered depends on the shape, never on alignment)
+    if (plan.tile != GEMM_TILE_128 && (mode == GUARDED || (plan.tile == GEMM_TILE_256 && sizeof(TI) == 2 && !(df && !d.atrans && d.btrans)))) {
+        plan.tile = GEMM_TILE_128; plan.deep = false;
         mode = run_mode<TI>(d, P, 128, 128);
     }
     const int tm = kTileM[plan.tile], tn = kTileN[plan.tile];
@@ -1178,6 +1177,8 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     GemmPlan p{GEMM_TILE_128, false, 1, 0};
     const int batch = d.batch > 0 ? d.batch : 1;
     const int Ne = d.Npad > 0 ? d.Npad : d.N;             // (the caller sets Npad only where the unguarded kernel applies)
+    // (in whole pairs of 16-byte words: a product and its twin padded to them are planned alike)
+    const int Nr = d.in_type == DT_BF16 ? (Ne + 15) & ~15 : (Ne + 7) & ~7;
     const long long t256 = (long long)((d.M + 255) / 256) * ((Ne + 255) / 256) * batch;
     const long long t128 = (long long)((d.M + 127) / 128) * ((Ne + 127) / 128) * batch;
     int ktot = 0;
@@ -1192,14 +1193,14 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
             // at large batch): the same tile, split along K into the smallest number of parts that fills whole
             // rounds of 512 resident workgroups to 90 %, if every part keeps 64 slabs and the float partial tiles
             // stay below an eighth of the operand bytes.
-            if (tr >= 128 && d.nseg == 1 && d.partial && !d.rowsum && (!d.long_parts || (d.M % 256 == 0 && Ne % 128 == 0 && ktot % 64 == 0))) {
+            if (tr >= 128 && d.nseg == 1 && d.partial && !d.rowsum && (!d.long_parts || (d.M % 256 == 0 && Ne % 128 == 0 && (ktot + 15) / 16 % 4 == 0))) {
                 const int slabs = (d.seg[0].K + 63) / 64;
                 for (int s = 1; s <= 8; ++s) {
                     const double rounds = (double)tr * s / 512.0;
                     const double eff = rounds / (double)(long long)(rounds + 0.999999);
                     if (eff < 0.9 || slabs / s < 64) continue;
-                    const size_t need = s > 1 ? (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float) : 0;
-                    if (s > 1 && ((long long)16 * s * d.N > d.seg[0].K || need > d.partial_bytes)) break;
+                    const size_t need = s > 1 ? (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float) : 0;
+                    if (s > 1 && ((long long)16 * s * Nr > d.seg[0].K || need > d.partial_bytes)) break;
                     p.tile = GEMM_TILE_256X128; p.splits = s; p.partial_bytes = need;
                     return p;
                 }
@@ -1208,12 +1209,12 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         // A handful of large tiles and a very long contraction (the softmax layer's input gradient, dA W form): the
         // 256x256 tile, which moves half the operand bytes of 128x128 per flop, split along K over up to one
         // workgroup per CU, if every part keeps at least 24 slabs and the parts fill three quarters of the CUs.
-        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 <= 64 && Ne % 256 == 0) {
+        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 <= 64 && Nr % 256 == 0) {
             const int slabs = (d.seg[0].K + 63) / 64;
             int s = (int)(256 / t256);
             if (s > 16) s = 16;
             while (s > 1 && slabs / s < 24) --s;
-            const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
+            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
             if (s > 1 && t256 * s >= 192 && need <= d.partial_bytes) { p.tile = GEMM_TILE_256; p.splits = s; p.partial_bytes = need; return p; }
         }
     } else {
@@ -1236,14 +1237,14 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         if (!d.add && d.partial && d.nseg == 1 && t128 <= 256) {
             const int bk = d.in_type == DT_BF16 ? 64 : 32, slabs = (ktot + bk - 1) / bk;
             const int s1 = parts_of(256, 8, t128, slabs, 8), s2 = parts_of(512, 8, t128, slabs, 64), s = s1 > s2 ? s1 : s2;
-            const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
+            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
             if (s > 1 && need <= d.partial_bytes) { p.splits = s; p.partial_bytes = need; }
         }
     } else if (!d.add && d.partial && t128 <= 1024) {
         const int bk = d.in_type == DT_BF16 ? 64 : 32;
         int slabs = 0;
         for (int s = 0; s < d.nseg; ++s) slabs += (d.seg[s].K + bk - 1) / bk;
-        const double tile_bytes = (double)batch * d.M * d.N * sizeof(float);
+        const double tile_bytes = (double)batch * d.M * Nr * sizeof(float);
         auto estimate = [&](int s) {
             const double x = (double)t128 * s / 256.0, rounds = x <= 1.0 ? 1.0 : (double)(long long)(x + 0.999999);
             const double part = (slabs + s - 1) / s;
@@ -1252,7 +1253,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         };
         double best = estimate(1) * (11.0 / 12.0);
         for (int s = 2; s <= 32 && slabs / s >= 4; ++s) {
-            const size_t need = (size_t)s * batch * ((size_t)d.M * d.N + d.M) * sizeof(float);
+            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
             if (need > d.partial_bytes || need > ((size_t)256 << 20)) break;
             const double t = estimate(s);
             if (t < best) { best = t; p.splits = s; p.partial_bytes = need; }
@@ -1265,8 +1266,9 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
 
 }  // namespace
 
-size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type) {
+size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type, bool long_parts) {
     GemmDesc d{};
+    d.long_parts = long_parts;
     d.M = M; d.N = N; d.batch = batch; d.nseg = 1; d.seg[0].K = K; d.in_type = in_type;
     d.partial = reinterpret_cast<float*>(16); d.partial_bytes = ~size_t(0);
     // the largest of what the tile families would use in any operand form: alignment decides between them only at launch time

@@ -51,7 +51,7 @@ struct GemmPlan {
     size_t partial_bytes;     // scratch the split needs (0 when splits == 1)
 };
 // Scratch bytes a product of this shape would use if it were given unlimited scratch.
-size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type);
+size_t gemm_partial_bytes(int M, int N, int K, int batch, DType in_type, bool long_parts = false);
 // The scratch softmax_xent_fwd_bwd_noalloc sets aside for one of its products when it decides whether a call fits.
 size_t noalloc_partial_bytes(int M, int N, int K, DType in_type);
 

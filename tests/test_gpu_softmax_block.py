@@ -30,3 +30,51 @@ def test_a_logit_is_summed_in_chains_of_at_least_eight_slabs(entry, mode, slab, 
         assert abs(lrn.loss_value() - math.log(V)) <= 1e-5 * math.log(V)
     finally:
         lrn.close()
+
+
+@pytest.mark.parametrize("dims,mode", [
+    (dict(T=21, B=16, D=8, H=8, L=1, P=512, V=30000), 1),   # little room behind the logits for the parts of dz
+    (dict(T=21, B=16, D=8, H=8, L=1, P=1024, V=29000), 1),
+    (dict(T=4, B=21, D=8, H=8, L=1, P=1024, V=500), 1),     # logits split, in a model that splits nothing else
+    (dict(T=21, B=80, D=8, H=8, L=1, P=64, V=8103), 1),     # the array holds the rows of the logits unpadded only
+    (dict(T=21, B=80, D=8, H=8, L=1, P=64, V=4051), 0),
+    # models run as their padded twin
+    (dict(T=21, B=16, D=8, H=32, L=1, P=301, V=9001), 1),
+    (dict(T=21, B=16, D=8, H=32, L=1, P=1021, V=2500), 1),  # the twin's z is a whole number of 256-wide tiles
+    (dict(T=5, B=40, D=8, H=101, L=1, P=0, V=900), 1),      # z in two pieces
+    (dict(T=5, B=40, D=8, H=508, L=1, P=0, V=900), 1),
+    (dict(T=21, B=30, D=8, H=62, L=1, P=67, V=9001), 0),
+    (dict(T=21, B=30, D=8, H=301, L=1, P=0, V=3001), 0),
+])
+def test_both_entry_points_give_the_same_bits(dims, mode):
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    from paper_1904_04956_amd.harness import Learner
+    lrn = Learner(mode=mode, defer_softmax_wgrad=False, **dims)
+    try:
+        g = torch.Generator(device="cuda").manual_seed(4962)
+        lrn.theta_fwd.copy_(0.1 * torch.randn(lrn.n, device="cuda", generator=g))
+        lrn.z.copy_(torch.randn(lrn.z.shape, device="cuda", generator=g))
+        lrn.labels.copy_(torch.randint(0, dims["V"], lrn.labels.shape, device="cuda", generator=g))
+        out = []
+        for entry in (bl.softmax_xent_fwd_bwd, bl.softmax_xent_fwd_bwd_noalloc):
+            for t in (lrn.loss, lrn.dz, lrn.grad):
+                t.fill_(-1.0)
+            entry(lrn.ctx, lrn.theta_fwd, lrn.z, lrn.labels, lrn.loss, lrn.dz, lrn.grad)
+            out.append([t.cpu().clone() for t in (lrn.loss, lrn.dz, lrn.grad)])
+        for name, a, b in zip(("loss", "dz", "grad"), *out):
+            assert torch.equal(a, b), (name, float((a.float() - b.float()).abs().max()), float(a.float().abs().max()))
+        # and they are the softmax block's results
+        off, n = bl.blstm_param_offset(lrn.ctx, 0, 0, bl.BLSTM_WS)
+        w = lrn.theta_fwd[off:off + n].double().view(dims["V"], -1).requires_grad_()
+        b = lrn.theta_fwd[off + n:].double().requires_grad_()
+        z = lrn.z.double().view(-1, lrn.zdim).requires_grad_()
+        loss = torch.nn.functional.cross_entropy(z @ w.t() + b, lrn.labels.view(-1).long())
+        loss.backward()
+        loss = loss.detach()
+        tol = 2e-2 if mode == 1 else 1e-4
+        assert abs(lrn.loss_value() - float(loss)) <= tol * float(loss)
+        for got, ref in ((lrn.dz, z.grad), (lrn.grad[off:off + n], w.grad), (lrn.grad[off + n:], b.grad)):
+            assert float((got.double().view(-1) - ref.reshape(-1)).abs().max()) <= tol * float(ref.abs().max())
+    finally:
+        lrn.close()
