@@ -334,7 +334,6 @@ int twin_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* 
     const bool pending = ctx->twin->pend_z != nullptr;
     if (pending && ctx->pend_grad != grad)
         return fail(BLSTM_ERR_DIM, "blstm_backward: the softmax layer's weight gradient was left to this call for another gradient vector");
-    if (!ctx->twin->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
     int rc = twin_theta(ctx, theta, st);
     if (rc != BLSTM_OK) return rc;
     float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
@@ -707,13 +706,14 @@ int softmax_xent_fwd_bwd_noalloc(blstm_ctx* ctx, const void* theta, const void* 
     if (rc != BLSTM_OK) return rc;
     const size_t first = up256((size_t)ctx->M * (size_t)ctx->ldu * ctx->esz), rows = up256((size_t)ctx->M * 4);   // (logits, row losses, split-K partial tiles)
     SoftmaxScratch sc{base, ctx->ldu, reinterpret_cast<float*>(base + first), reinterpret_cast<float*>(base + first + rows), ctx->soft_part};
+    if (ctx->twin) ctx->twin->pend_z = nullptr;         // (this call writes what an earlier one may have left to the twin's backward pass)
     return softmax_xent_run(ctx, sc, theta, z, labels, loss_dev, dz, grad, static_cast<hipStream_t>(stream), false);
 }
 
 int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* dz, float* grad, void* stream) {
     if (!ctx || !theta || !x || !dz || !grad) return fail(BLSTM_ERR_NULL, "blstm_backward: null argument");
     if (!ctx->ws) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no workspace bound");
-    if (!ctx->twin && !ctx->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
+    if (!(ctx->twin ? ctx->twin : ctx)->have_forward) return fail(BLSTM_ERR_WORKSPACE, "blstm_backward: no forward pass is held in the workspace");
     if (!aligned16(theta) || !aligned16(x) || !aligned16(dz) || !aligned16(grad))
         return fail(BLSTM_ERR_ALIGN, "blstm_backward: pointers must be 16-byte aligned");
     if (ctx->twin) return twin_backward(ctx, theta, x, dz, grad, static_cast<hipStream_t>(stream));
