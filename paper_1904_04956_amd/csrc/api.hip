@@ -86,6 +86,7 @@ struct blstm_ctx {
     // by zeros: the twin's units beyond H have zero weights both ways, stay exactly zero and change no other value.  Null
     // otherwise.  The workspace is the twin's, then its weights, gradient, x, z and dz.
     blstm_ctx* twin;
+    int Hown;                           // in a twin: the model's own H; otherwise H
     std::vector<BlockTensor> tparam;    // every tensor of the flat vector, compact here and padded there; the softmax layer's two last
     BlockTensor tx, tz, tu;             // x (float mode, where D is padded); z / dz of the stack and of the softmax block
     size_t tTHETA, tGRAD, tX, tZ, tDZ;
@@ -253,6 +254,7 @@ int make_twin(blstm_ctx* c) {
     const int rc = blstm_create(&cfg, &t);
     if (rc != BLSTM_OK) return rc;
     c->twin = t;
+    t->Hown = c->H;
     const int H = c->H, Hp = t->H;
     for (int l = 0; l < c->L; ++l)
         for (int d = 0; d < 2; ++d) {
@@ -373,7 +375,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     blstm_ctx* c = new (std::nothrow) blstm_ctx();
     if (!c) return fail(BLSTM_ERR_DIM, "blstm_create: out of host memory");
     c->cfg = *cfg;
-    c->T = cfg->T; c->B = cfg->B; c->D = cfg->D; c->H = cfg->H; c->L = cfg->L; c->P = cfg->P; c->V = cfg->V;
+    c->T = cfg->T; c->B = cfg->B; c->D = cfg->D; c->H = cfg->H; c->L = cfg->L; c->P = cfg->P; c->V = cfg->V; c->Hown = cfg->H;
     c->M = (int)Mll;
     c->zdim = cfg->P > 0 ? cfg->P : 2 * cfg->H;
     c->st = cfg->mode == 1 ? DT_BF16 : DT_F32;
@@ -591,6 +593,8 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             d.C = AX; d.ldc = 8 * H; d.sC = 4 * H;
             d.bias = at(theta, ctx->off_b[0][l], e); d.sBias = (long long)(ctx->off_b[1][l] - ctx->off_b[0][l]);
             RUN(PC_GEMM_INPUT, "input projection", launch_gemm(d, st));
+            // (an infinite feature times the zero weights of a twin's own units is NaN; theirs is zero whatever x holds)
+            if (l == 0 && ctx->Hown != H) RUN(PC_MISC, "a_x of the padding", launch_zero_columns(AX, (long long)M * 8, H, ctx->Hown, st));
         }
         ctx->fwd_persistent[l] = 0;
         unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);

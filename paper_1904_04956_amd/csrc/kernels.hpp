@@ -145,6 +145,8 @@ struct BlockTensor {
 constexpr int BLOCK_COPIES_MAX = 64;
 struct BlockCopies { BlockTensor t[BLOCK_COPIES_MAX]; };
 hipError_t launch_pad_blocks(const BlockTensor* t, int n, const void* compact, void* padded, DType type, hipStream_t st);
+// Columns h .. hp - 1 of `blocks` consecutive blocks of hp floats become zero.
+hipError_t launch_zero_columns(float* p, long long blocks, int hp, int h, hipStream_t st);
 hipError_t launch_compact_blocks(const BlockTensor* t, int n, const void* padded, void* compact, DType type, hipStream_t st);
 
 // ---- softmax cross-entropy over rows of the logit matrix -----------------------------

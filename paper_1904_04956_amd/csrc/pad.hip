@@ -66,6 +66,16 @@ __global__ __launch_bounds__(256) void compact_blocks_kernel(BlockCopies a, cons
     }
 }
 
+// One thread per element to clear: columns h .. hp - 1 of every block of hp columns.
+__global__ __launch_bounds__(256) void zero_columns_kernel(float* p, long long blocks, int hp, int h) {
+    const int w = hp - h;
+    const long long n = blocks * w;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+        const long long b = i / w;
+        p[b * hp + h + (int)(i - b * w)] = 0.0f;
+    }
+}
+
 template <bool PAD, typename T>
 hipError_t run(const BlockTensor* tensors, int n, const void* src, void* dst, hipStream_t st) {
     for (int i = 0; i < n; i += BLOCK_COPIES_MAX) {
@@ -89,6 +99,12 @@ hipError_t run(const BlockTensor* tensors, int n, const void* src, void* dst, hi
 
 }  // namespace
 
+hipError_t launch_zero_columns(float* p, long long blocks, int hp, int h, hipStream_t st) {
+    const long long n = (blocks * (hp - h) + 255) / 256;
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(zero_columns_kernel, dim3((unsigned)(n < 2048 ? n : 2048)), dim3(256), 0, st, p, blocks, hp, h);
+    return hipGetLastError();
+}
 hipError_t launch_pad_blocks(const BlockTensor* t, int n, const void* compact, void* padded, DType type, hipStream_t st) {
     return type == DT_BF16 ? run<true, unsigned short>(t, n, compact, padded, st) : run<true, float>(t, n, compact, padded, st);
 }

@@ -33,3 +33,29 @@ def test_noalloc_call_takes_over_from_a_deferred_softmax_gradient(dims):
         assert not torch.equal(lrn.grad[off:], ws)
     finally:
         lrn.close()
+
+
+@pytest.mark.parametrize("dims,mode", [
+    (dict(T=5, B=40, D=30, H=101, L=2, P=40, V=90), 1),
+    (dict(T=5, B=40, D=32, H=125, L=1, P=0, V=90), 1),      # the twin has a width with kernels of its own
+    (dict(T=21, B=60, D=33, H=66, L=2, P=67, V=9001), 0),
+])
+@pytest.mark.parametrize("path", [0, 1])
+def test_infinite_features_saturate_the_gates(dims, mode, path):
+    # +-inf times a weight is +-inf: the gates saturate and z is finite, in the frames before and behind it too
+    from oracle import blstm_oracle as orc
+    from paper_1904_04956_amd.harness import Learner
+    dm, theta, x, labels = make_problem(dims, mode, 91, 2.0)
+    x[2, 3, 7] = np.inf; x[1, 4, 0] = -np.inf
+    lrn = Learner(mode=mode, recurrent_path=path, **dims)
+    try:
+        lrn.set_theta(theta); lrn.set_batch(x, labels)
+        lrn.forward(); lrn.check_status()
+        z = lrn.z_numpy()
+    finally:
+        lrn.close()
+    with np.errstate(all="ignore"):
+        ref, _ = orc.blstm_forward(dm, theta.astype(np.float64), x)
+    assert np.isfinite(ref).all()
+    assert int(np.sum(~np.isfinite(z))) == 0
+    assert np.abs(z - ref).max() <= (2e-2 if mode == 1 else 1e-4) * np.abs(ref).max()
