@@ -137,7 +137,7 @@ hipError_t launch_fill_bytes16(void* p, size_t bytes, unsigned v, hipStream_t st
 
 // ---- copies between compact and zero-padded tensors ----------------------------------------------
 // A matrix of rg groups of r rows, each of cs segments of c columns, and its padded form with rp rows a group and cp
-// columns a segment (offsets in elements; padded rows are whole 16-byte words).
+// columns a segment (offsets in elements; where there are two segments cp is a whole number of 16-byte words).
 struct BlockTensor {
     size_t compact, padded;
     int rg, r, rp, cs, c, cp;

@@ -1,6 +1,8 @@
-// Copies between compact tensors and zero-padded ones (rows that start 16-byte aligned).  Bound by memory, a wavefront along
-// a row, no division per element.  Measured on 45.6 M parameters (five layers of 583 cells): the weights padded in 93 us
-// (182 MB), the gradient compacted in 110 us (365 MB); with a division per element 209 and 305.
+// Copies between compact tensors and zero-padded ones.  Bound by memory, a wavefront along a row, no division per element.
+// Neither side need be aligned: compact rows are not, nor are padded ones of a width that is left as it is (W_x of the first
+// layer in bf16 mode, whose D is not padded), so 16-byte words are moved as bytes of any alignment.  Measured on 45.6 M
+// parameters (five layers of 583 cells): the weights padded in 93 us (182 MB), the gradient compacted in 110 us (365 MB);
+// with a division per element 209 and 305.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -24,18 +26,17 @@ __global__ __launch_bounds__(256) void pad_blocks_kernel(BlockCopies a, const T*
         // (a word lies in one segment: their padded widths are whole words, or there is one segment)
         for (int c = (threadIdx.x & 63) * VEC; c < cols; c += 64 * VEC) {
             const int seg = t.cs == 1 ? 0 : (int)((unsigned)c / (unsigned)t.cp), k = c - seg * t.cp;
-            uint4 w = make_uint4(0u, 0u, 0u, 0u);
             if (j < t.r && k + VEC <= t.c) {
-                __builtin_memcpy(&w, s + seg * t.c + k, 16);          // (any alignment)
-                *reinterpret_cast<uint4*>(d + c) = w;
+                uint4 w;
+                __builtin_memcpy(&w, s + seg * t.c + k, 16);
+                __builtin_memcpy(d + c, &w, 16);
                 continue;
             }
             T v[VEC];
 #pragma unroll
             for (int e = 0; e < VEC; ++e) v[e] = (j < t.r && k + e < t.c) ? s[seg * t.c + k + e] : (T)0;
             if (c + VEC <= cols) {
-                __builtin_memcpy(&w, v, 16);
-                *reinterpret_cast<uint4*>(d + c) = w;
+                __builtin_memcpy(d + c, v, 16);
             } else {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) if (c + e < cols) d[c + e] = v[e];

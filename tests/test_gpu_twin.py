@@ -59,3 +59,8 @@ def test_infinite_features_saturate_the_gates(dims, mode, path):
     assert np.isfinite(ref).all()
     assert int(np.sum(~np.isfinite(z))) == 0
     assert np.abs(z - ref).max() <= (2e-2 if mode == 1 else 1e-4) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("D", [7, 31, 33])                 # rows of W_x that start at any even address, one shorter than a word
+def test_feature_widths_the_twin_leaves_as_they_are(D):
+    check_step(dict(T=4, B=9, D=D, H=101, L=1, P=0, V=40), 1, seed=92, theta_scale=2.0)
