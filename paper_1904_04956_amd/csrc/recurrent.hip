@@ -31,6 +31,7 @@
 // gradient and the updated weights; blstm_device_status reports it as well.
 #include "exchange.hpp"
 #include "kernels.hpp"
+#include "residency.hpp"
 #include <type_traits>
 
 namespace blstm {
@@ -845,51 +846,25 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-// Whether `grid` workgroups of this kernel can be resident at once (the persistent kernels wait on each other).  The
-// attribute call and the occupancy query are made once per kernel instantiation and thread; the answer depends on
-// the kernel and the device only, so it is kept (cache: per instantiation, one slot).
-struct FitCache { bool known; int per_device; };
-template <typename K>
-hipError_t prepare(K kernel, int threads, size_t dyn_lds, int grid, FitCache* cache, bool* fits) {
-    if (!cache->known) {
-        int dev = 0, cus = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds);
-        if (e != hipSuccess) return e;
-        int per_cu = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, dyn_lds);
-        if (e != hipSuccess) return e;
-        cache->per_device = per_cu * cus;
-        cache->known = true;
-    }
-    *fits = cache->per_device >= grid;
-    return hipSuccess;
+// Launches `grid` workgroups of KERNEL if all can be resident at once (they wait on each other).
+template <auto KERNEL, typename A>
+hipError_t launch_resident(const A& a, int threads, size_t lds, int grid, hipStream_t st, bool* launched) {
+    int resident = 0;
+    const hipError_t e = resident_workgroups<KERNEL>(threads, lds, &resident);
+    if (e != hipSuccess || resident < grid) return e;
+    *launched = true;
+    hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(threads), lds, st, a);
+    return hipGetLastError();
 }
-
 template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
-    bool fits = false;
-    static thread_local FitCache cache{false, 0};
-    hipError_t e = prepare(rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>, 64 * NW, lds, grid, &cache, &fits);
-    if (e != hipSuccess || !fits) return e;
-    hipLaunchKernelGGL((rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>), dim3(grid), dim3(64 * NW), lds, st, a);
-    *launched = true;
-    return hipGetLastError();
+    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, st, launched);
 }
 template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 64 * 16 + (size_t)NW * 2048 + (size_t)NW * 512;   // partial sums; regrouping of dE/da, 2 KB per wavefront; spreading dy, 512 bytes per wavefront
-    bool fits = false;
-    static thread_local FitCache cache{false, 0};
-    hipError_t e = prepare(rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>, 64 * NW, lds, grid, &cache, &fits);
-    if (e != hipSuccess || !fits) return e;
-    hipLaunchKernelGGL((rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>), dim3(grid), dim3(64 * NW), lds, st, a);
-    *launched = true;
-    return hipGetLastError();
+    return launch_resident<rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {

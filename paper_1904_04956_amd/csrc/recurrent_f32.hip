@@ -19,6 +19,7 @@
 // is asked of H.  Saved activations are in the row-major layout of the per-frame path (cell.hip).
 #include "common.hpp"
 #include "kernels.hpp"
+#include "residency.hpp"
 
 namespace blstm {
 namespace {
@@ -342,18 +343,12 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
 }
 
 // Launches one instantiation if its workgroups can all be resident (they wait on each other; the ones that pad the grid
-// to whole rounds of the eight XCDs leave at once).  The occupancy answer depends on kernel and device only and is kept.
+// to whole rounds of the eight XCDs leave at once).
 template <auto KERNEL, typename A>
 hipError_t run(const A& a, hipStream_t st, bool* launched) {
-    static thread_local int resident = -1;
-    if (resident < 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, 64 * NWF, 0);
-        if (e != hipSuccess) return e;
-        resident = cus * per_cu;
-    }
+    int resident = 0;
+    const hipError_t e = resident_workgroups<KERNEL>(64 * NWF, 0, &resident);
+    if (e != hipSuccess) return e;
     const int real = 2 * a.nu * a.nbg;
     if (resident < real) return hipSuccess;
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)((real + 7) & ~7)), dim3(64 * NWF), 0, st, a);

@@ -13,6 +13,7 @@
 // recurrent.hip.  Saved activations are per-thread records: [frame][direction][tile][slice][thread].
 #include "exchange.hpp"
 #include "kernels.hpp"
+#include "residency.hpp"
 
 namespace blstm {
 namespace {
@@ -295,22 +296,16 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
     }
 }
 
-// Launches one instantiation if its workgroups can all be resident (see recurrent_f32.hip).
+// Launches one instantiation if its workgroups can all be resident.
 template <auto KERNEL, typename A>
 hipError_t run(const A& a, hipStream_t st, bool* launched) {
-    static thread_local int resident = -1;
-    if (resident < 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, 64 * NWF, 0);
-        if (e != hipSuccess) return e;
-        resident = cus * per_cu;
-    }
+    int resident = 0;
+    const hipError_t e = resident_workgroups<KERNEL>(64 * NWF, 0, &resident);
+    if (e != hipSuccess) return e;
     const int real = 2 * 2 * ((a.H + 31) / 32) * ((a.B + 15) / 16);
     if (resident < real) return hipSuccess;
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)((real + 7) & ~7)), dim3(64 * NWF), 0, st, a);
     *launched = true;
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)((real + 7) & ~7)), dim3(64 * NWF), 0, st, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,74 @@
+"""Which kernels the calls launch, without a GPU: the library runs on a stand-in for the HIP runtime that writes the
+launches down (hip_recorder.cpp), in a process of its own."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, sys
+sys.path.insert(0, {root!r})
+rec = ctypes.CDLL({recorder!r}, mode=ctypes.RTLD_GLOBAL)        # found before the real runtime
+rec.recorder_name.restype = ctypes.c_char_p
+from paper_1904_04956_amd import binding as bl
+P = 1 << 20                                                      # any aligned address: nothing is read or written
+
+
+class Model:
+    def __init__(self, mode=1, **dims):
+        self.ctx = bl.blstm_create(mode=mode, **dims)
+        bl.blstm_bind(self.ctx, P, bl.blstm_workspace_bytes(self.ctx))
+    def option(self, which, value): bl.blstm_set_option(self.ctx, which, value)
+    def forward(self): bl.blstm_forward(self.ctx, P, P, P, 0)
+    def xent(self): bl.softmax_xent_fwd_bwd(self.ctx, P, P, P, P, P, P, 0)
+    def noalloc(self): bl.softmax_xent_fwd_bwd_noalloc(self.ctx, P, P, P, P, P, P, 0)
+    def backward(self): bl.blstm_backward(self.ctx, P, P, P, P, 0)
+
+
+def launches(call):
+    rec.recorder_clear()
+    call()
+    return [rec.recorder_name(i).decode() for i in range(rec.recorder_count())]
+
+
+def count(names, part): return sum(part in n for n in names)
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    out = str(tmp_path_factory.mktemp("recorder") / "librecorder.so")
+    subprocess.run([gxx, "-O1", "-shared", "-fPIC", "-std=c++17", "-o", out, os.path.join(HERE, "hip_recorder.cpp")], check=True)
+
+    def run(code):
+        text = PRELUDE.format(root=ROOT, recorder=out) + textwrap.dedent(code) + "\nprint(json.dumps(out))\n"
+        r = subprocess.run([sys.executable, "-c", text], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+    return run
+
+
+@pytest.mark.parametrize("mode,dims", [(1, "T=4, B=16, D=8, H=512, L=1, P=0, V=20"), (1, "T=4, B=256, D=8, H=512, L=1, P=0, V=20"),
+                                       (0, "T=4, B=64, D=8, H=512, L=1, P=0, V=20")])
+def test_whether_a_grid_fits_is_asked_for_every_device(recorder, mode, dims):
+    big, little, big_again = recorder(f"""
+        rec.recorder_cus(1, 16)
+        out = []
+        for device in (0, 1, 0):
+            rec.recorder_device(device)
+            m = Model(mode={mode}, {dims})
+            f = launches(m.forward)
+            out.append([count(f, "rec_small_fwd") + count(f, "rec_fwd_kernel") + count(f, "rec32_fwd"), count(f, "cell_fwd")])
+    """)
+    assert big == big_again == [1, 0]
+    assert little == [0, 4]
