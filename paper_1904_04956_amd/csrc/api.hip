@@ -140,6 +140,28 @@ GemmDesc gemm_desc(const blstm_ctx* c, DType in, DType out) {
     return d;
 }
 
+// Which persistent kernels both passes of a bf16 layer can run with: 2 = recurrent_small.hip, 1 = recurrent.hip, 0 = neither
+// (the backward pass must follow its forward twin: what the forward one saves only it can read).
+int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
+    RecFwdArgs f{};
+    f.B = c->B; f.H = c->H; f.nbg = c->rec_nbg; f.tiles_per_group = c->rec_tiles; f.ask = true;
+    RecBwdArgs b{};
+    b.B = c->B; b.H = c->H; b.nbg = c->rec_nbg; b.tiles_per_group = c->rec_tiles; b.ask = true;
+    bool fwd = false, bwd = false;
+    *kind = 0;
+    if (sentinel && rec_small_supported(c->B, c->H)) {
+        hipError_t e = launch_rec_small_fwd(f, nullptr, &fwd);
+        if (e == hipSuccess) e = launch_rec_small_bwd(b, nullptr, &bwd);
+        if (e != hipSuccess) return check_hip(e, "persistent recurrent kernels");
+        if (fwd && bwd) { *kind = 2; return BLSTM_OK; }
+    }
+    hipError_t e = launch_rec_fwd(f, sentinel, nullptr, &fwd);
+    if (e == hipSuccess) e = launch_rec_bwd(b, sentinel, nullptr, &bwd);
+    if (e != hipSuccess) return check_hip(e, "persistent recurrent kernels");
+    if (fwd && bwd) *kind = 1;
+    return BLSTM_OK;
+}
+
 inline const char* at(const void* base, size_t elems, size_t esz) { return static_cast<const char*>(base) + elems * esz; }
 inline char* at(void* base, size_t elems, size_t esz) { return static_cast<char*>(base) + elems * esz; }
 
@@ -558,8 +580,14 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     ctx->have_forward = false;
     ctx->dax_filled = false;
     ctx->pend_z = nullptr;                              // (a softmax weight gradient left over from an earlier step is dropped)
-    const bool persistent = ctx->rec_nbg > 0 && ctx->rec_path == 0;
+    int kind = 0;                                       // the persistent bf16 kernels of this pass (see rec_kind)
+    if (ctx->rec_nbg > 0 && ctx->rec_path == 0) {
+        const int rc = rec_kind(ctx, ctx->rec_sync == 1, &kind);
+        if (rc != BLSTM_OK) return rc;
+    }
+    const bool persistent = kind > 0;
     const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
+    const bool fills = kind == 2 || (kind == 1 && ctx->rec_sync == 1 && rec_fwd_fills(H));   // the forward kernels mark the exchange copies of dE/da
     if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {
@@ -626,19 +654,16 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.gates = reinterpret_cast<unsigned short*>(G); a.c = C;
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            const bool small = ctx->rec_sync == 1 && rec_small_supported(B, H);
-            if (ctx->rec_sync == 1 && (small || rec_fwd_fills(H))) {   // the backward twin's exchange copy is pre-filled on the side
+            if (fills) {   // the backward twin's exchange copy is pre-filled on the side
                 a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l;
                 a.fill_words = ctx->dax_bytes / 16;
             }
             bool launched = false;
-            if (small) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
-            ctx->fwd_persistent[l] = launched ? 2 : 0;
-            if (!launched) {
-                RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
-                ctx->fwd_persistent[l] = launched ? 1 : 0;
-            }
-            if (launched) continue;
+            if (kind == 2) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
+            else RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
+            if (!launched) return fail(BLSTM_ERR_HIP, "blstm_forward: the persistent kernel cannot be launched");
+            ctx->fwd_persistent[l] = (char)kind;
+            continue;
         }
         for (int n = 0; n < T; ++n) {
             const int t[2] = {n, T - 1 - n};
@@ -681,7 +706,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
         RUN(PC_MISC, "copy of the LSTM output", hipMemcpyAsync(z_out, YL, (size_t)M * 2 * H * e, hipMemcpyDeviceToDevice, st));
     }
     ctx->have_forward = true;
-    ctx->dax_filled = persistent && ctx->rec_sync == 1 && (rec_fwd_fills(H) || rec_small_supported(B, H));
+    ctx->dax_filled = fills;
     return BLSTM_OK;
 }
 

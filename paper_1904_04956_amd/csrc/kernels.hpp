@@ -52,6 +52,7 @@ struct RecFwdArgs {
     void* fill;
     unsigned long long fill_words;
     int T, B, H, nbg, tiles_per_group;
+    bool ask;                     // host only: launch nothing, only say whether it would be
 };
 struct RecBwdArgs {
     const unsigned short* uht[2]; // U_h^T per direction, [H][4H]
@@ -65,6 +66,7 @@ struct RecBwdArgs {
     unsigned* abort_word;
     unsigned long long limit_ticks;
     int T, B, H, nbg, tiles_per_group;
+    bool ask;                     // as above
 };
 bool rec_supported(int H);                  // whether the persistent kernels take this width
 bool rec_fenced(int H);                     // whether they are built with the fenced protocol too

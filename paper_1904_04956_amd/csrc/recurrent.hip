@@ -846,13 +846,15 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-// Launches `grid` workgroups of KERNEL if all can be resident at once (they wait on each other).
+// Launches `grid` workgroups of KERNEL if all can be resident at once (they wait on each other), or (a.ask) only says
+// whether they can.
 template <auto KERNEL, typename A>
 hipError_t launch_resident(const A& a, int threads, size_t lds, int grid, hipStream_t st, bool* launched) {
     int resident = 0;
     const hipError_t e = resident_workgroups<KERNEL>(threads, lds, &resident);
     if (e != hipSuccess || resident < grid) return e;
     *launched = true;
+    if (a.ask) return hipSuccess;
     hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(threads), lds, st, a);
     return hipGetLastError();
 }

@@ -58,6 +58,40 @@ def recorder(tmp_path_factory):
     return run
 
 
+DIMS = "T=4, B=16, D=8, H=640, L=2, P=0, V=20"             # 80 workgroups of the small kernels, wider than the ones that fill
+
+
+def test_exchange_copies_count_as_marked_only_if_the_launched_kernels_marked_them(recorder):
+    # where the kernels for few sequences do not fit, those of recurrent.hip run: at this width they mark nothing
+    small, large = recorder(f"""
+        out = []
+        for device, small_fits in ((0, 1), (1, 0)):
+            rec.recorder_device(device)
+            rec.recorder_occupancy(b"rec_small", small_fits)
+            m = Model({DIMS})
+            f, b = launches(m.forward), launches(m.backward)
+            out.append([count(f, "rec_small_fwd"), count(f, "rec_fwd_kernel"), count(b, "rec_small_bwd"), count(b, "rec_bwd_kernel"), count(b, "fill_u128")])
+    """)
+    assert small == [2, 0, 2, 0, 0]
+    assert large == [0, 2, 0, 2, 1]
+
+
+@pytest.mark.parametrize("dims,fwd,bwd", [
+    (DIMS, "rec_small_fwd", "rec_small_bwd"),
+    ("T=4, B=600, D=8, H=512, L=1, P=0, V=20", "rec_fwd_kernel", "rec_bwd_kernel"),
+])
+def test_a_forward_kernel_runs_only_if_its_backward_twin_fits_too(recorder, dims, fwd, bwd):
+    f_twin, f_other, b_twin = recorder(f"""
+        rec.recorder_occupancy(b"rec_", 2)
+        rec.recorder_occupancy(b"{bwd}", 0)
+        m = Model({dims})
+        f = launches(m.forward)
+        b = launches(m.backward)
+        out = [count(f, "{fwd}"), count(f, "rec_fwd_kernel") + count(f, "cell_fwd"), count(b, "{bwd}")]
+    """)
+    assert f_twin == 0 and f_other > 0 and b_twin == 0
+
+
 @pytest.mark.parametrize("mode,dims", [(1, "T=4, B=16, D=8, H=512, L=1, P=0, V=20"), (1, "T=4, B=256, D=8, H=512, L=1, P=0, V=20"),
                                        (0, "T=4, B=64, D=8, H=512, L=1, P=0, V=20")])
 def test_whether_a_grid_fits_is_asked_for_every_device(recorder, mode, dims):
