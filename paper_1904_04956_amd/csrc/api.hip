@@ -312,9 +312,11 @@ int make_twin(blstm_ctx* c) {
 // softmax layer's, which only twin_xent reads, are made there in every call: it has no such promise from the caller.)
 int twin_theta(blstm_ctx* ctx, const void* theta, hipStream_t st) {
     if (ctx->keep_copies && ctx->ttheta_of == theta) return BLSTM_OK;
-    ctx->ttheta_of = theta;
+    ctx->ttheta_of = nullptr;                            // (until the copy is enqueued)
     blstm_weights_changed(ctx->twin);
-    return check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size() - 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
+    const int rc = check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size() - 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
+    if (rc == BLSTM_OK) ctx->ttheta_of = theta;
+    return rc;
 }
 
 int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, hipStream_t st) {
@@ -613,8 +615,9 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
                 // (the copy of W_x is kept while the caller vouches for the weights: see blstm_weights_changed)
                 const bool have_wp = ctx->keep_copies && ctx->wxp_of == theta;
                 pa.count = have_wp ? 1 : 3; pa.cols = Din; pa.cols_p = ctx->Dp;
-                ctx->wxp_of = theta;
+                ctx->wxp_of = have_wp ? theta : nullptr;   // (until the copy is enqueued)
                 RUN(PC_MISC, "padded copies of x and W_x", launch_pad_cols(pa, st));
+                ctx->wxp_of = theta;
                 // (rows are Dp long for the weight gradient's whole tiles; the contraction needs whole slabs of 64 only)
                 d.seg[0] = GemmSeg{XP, WP, ctx->Dp, ctx->Dp, 0, (long long)4 * H * ctx->Dp, (Din + 63) / 64 * 64};
             }

@@ -106,3 +106,26 @@ def test_whether_a_grid_fits_is_asked_for_every_device(recorder, mode, dims):
     """)
     assert big == big_again == [1, 0]
     assert little == [0, 4]
+
+
+@pytest.mark.parametrize("dims,copy,axis", [("T=4, B=16, D=8, H=101, L=2, P=0, V=20", "pad_blocks", 0),      # a twin's weights
+                                            ("T=4, B=16, D=30, H=104, L=2, P=0, V=20", "pad_cols", 1)])        # W_x of the first layer
+def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):
+    # with copies kept from call to call: a failed launch leaves none behind
+    failed, again, kept = recorder(f"""
+        m = Model({dims})
+        m.option(bl.BLSTM_OPT_KEEP_WEIGHT_COPIES, 1)
+        rec.recorder_fail(b"{copy}")
+        out = []
+        try:
+            m.forward()
+        except bl.BlstmError as e:
+            out.append(e.code)
+        rec.recorder_fail(b"")
+        for _ in range(2):
+            n = launches(m.forward)
+            out.append([rec.recorder_grid(i, 1) if {axis} else 1 for i in range(len(n)) if "{copy}" in n[i]])   # (x and the two directions' weights, or x alone)
+    """)
+    assert failed == -5
+    assert again == [3] if axis else again == [1]
+    assert kept == [1] if axis else kept == []
