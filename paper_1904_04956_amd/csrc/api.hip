@@ -314,9 +314,9 @@ int twin_theta(blstm_ctx* ctx, const void* theta, hipStream_t st) {
     if (ctx->keep_copies && ctx->ttheta_of == theta) return BLSTM_OK;
     ctx->ttheta_of = nullptr;                            // (until the copy is enqueued)
     blstm_weights_changed(ctx->twin);
-    const int rc = check_hip(launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size() - 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded weights");
-    if (rc == BLSTM_OK) ctx->ttheta_of = theta;
-    return rc;
+    RUN(PC_MISC, "padded weights", launch_pad_blocks(ctx->tparam.data(), (int)ctx->tparam.size() - 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st));
+    ctx->ttheta_of = theta;
+    return BLSTM_OK;
 }
 
 int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, hipStream_t st) {
@@ -324,36 +324,30 @@ int twin_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out, 
     if (rc != BLSTM_OK) return rc;
     const void* xin = x;
     if (ctx->twin->D != ctx->D) {
-        rc = check_hip(launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st), "padded x");
-        if (rc != BLSTM_OK) return rc;
+        RUN(PC_MISC, "padded x", launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st));
         xin = ctx->ws + ctx->tX;
     }
     if (ctx->twin->zdim == ctx->zdim) return blstm_forward(ctx->twin, ctx->ws + ctx->tTHETA, xin, z_out, st);
     rc = blstm_forward(ctx->twin, ctx->ws + ctx->tTHETA, xin, ctx->ws + ctx->tZ, st);
     if (rc != BLSTM_OK) return rc;
-    return check_hip(launch_compact_blocks(&ctx->tz, 1, ctx->ws + ctx->tZ, z_out, ctx->st, st), "z");
+    RUN(PC_MISC, "z", launch_compact_blocks(&ctx->tz, 1, ctx->ws + ctx->tZ, z_out, ctx->st, st));
+    return BLSTM_OK;
 }
 
 int twin_xent(blstm_ctx* ctx, const void* theta, const void* z, const int32_t* labels, float* loss_dev, void* dz, float* grad, hipStream_t st) {
     const BlockTensor* soft = ctx->tparam.data() + ctx->tparam.size() - 2;
-    int rc = check_hip(launch_pad_blocks(soft, 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st), "padded softmax layer");
-    if (rc != BLSTM_OK) return rc;
+    RUN(PC_MISC, "padded softmax layer", launch_pad_blocks(soft, 2, theta, ctx->ws + ctx->tTHETA, ctx->st, st));
     float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
     const bool same = ctx->twin->zdim == ctx->zdim;
-    if (!same) {
-        rc = check_hip(launch_pad_blocks(&ctx->tu, 1, z, ctx->ws + ctx->tZ, ctx->st, st), "padded z");
-        if (rc != BLSTM_OK) return rc;
-    }
+    if (!same) RUN(PC_MISC, "padded z", launch_pad_blocks(&ctx->tu, 1, z, ctx->ws + ctx->tZ, ctx->st, st));
     void* tdz = same ? dz : ctx->ws + ctx->tDZ;
-    rc = softmax_xent_fwd_bwd(ctx->twin, ctx->ws + ctx->tTHETA, same ? z : ctx->ws + ctx->tZ, labels, loss_dev, tdz, tg, st);
+    const int rc = softmax_xent_fwd_bwd(ctx->twin, ctx->ws + ctx->tTHETA, same ? z : ctx->ws + ctx->tZ, labels, loss_dev, tdz, tg, st);
     if (rc != BLSTM_OK) return rc;
-    if (!same) {
-        rc = check_hip(launch_compact_blocks(&ctx->tu, 1, tdz, dz, ctx->st, st), "dz");
-        if (rc != BLSTM_OK) return rc;
-    }
+    if (!same) RUN(PC_MISC, "dz", launch_compact_blocks(&ctx->tu, 1, tdz, dz, ctx->st, st));
     ctx->pend_grad = grad;
     if (ctx->twin->pend_z) return BLSTM_OK;              // left to twin_backward
-    return check_hip(launch_compact_blocks(soft, 2, tg, grad, DT_F32, st), "softmax layer's gradient");
+    RUN(PC_MISC, "softmax layer's gradient", launch_compact_blocks(soft, 2, tg, grad, DT_F32, st));
+    return BLSTM_OK;
 }
 
 int twin_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* dz, float* grad, hipStream_t st) {
@@ -365,20 +359,19 @@ int twin_backward(blstm_ctx* ctx, const void* theta, const void* x, const void* 
     float* tg = reinterpret_cast<float*>(ctx->ws + ctx->tGRAD);
     const void* tdz = dz;
     if (ctx->twin->zdim != ctx->zdim) {
-        rc = check_hip(launch_pad_blocks(&ctx->tz, 1, dz, ctx->ws + ctx->tDZ, ctx->st, st), "padded dz");
-        if (rc != BLSTM_OK) return rc;
+        RUN(PC_MISC, "padded dz", launch_pad_blocks(&ctx->tz, 1, dz, ctx->ws + ctx->tDZ, ctx->st, st));
         tdz = ctx->ws + ctx->tDZ;
     }
     const void* xin = x;
     if (ctx->twin->D != ctx->D) {
-        rc = check_hip(launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st), "padded x");
-        if (rc != BLSTM_OK) return rc;
+        RUN(PC_MISC, "padded x", launch_pad_blocks(&ctx->tx, 1, x, ctx->ws + ctx->tX, ctx->st, st));
         xin = ctx->ws + ctx->tX;
     }
     rc = blstm_backward(ctx->twin, ctx->ws + ctx->tTHETA, xin, tdz, tg, st);
     if (rc != BLSTM_OK) return rc;
     const int n = (int)ctx->tparam.size() - (pending ? 0 : 2);   // (the softmax layer's slice is this call's only if left to it)
-    return check_hip(launch_compact_blocks(ctx->tparam.data(), n, tg, grad, DT_F32, st), "gradient");
+    RUN(PC_MISC, "gradient", launch_compact_blocks(ctx->tparam.data(), n, tg, grad, DT_F32, st));
+    return BLSTM_OK;
 }
 
 }  // namespace
@@ -1071,7 +1064,7 @@ const char* blstm_profile_name(int k) { return (k >= 0 && k < PC_COUNT) ? kProfN
 
 int blstm_profile_enable(blstm_ctx* c, int enable) {
     if (!c) return fail(BLSTM_ERR_NULL, "blstm_profile_enable: null argument");
-    if (c->twin) return blstm_profile_enable(c->twin, enable);
+    if (c->twin) blstm_profile_enable(c->twin, enable);
     c->prof = enable != 0;
     c->recs_used = 0;
     memset(c->prof_ms, 0, sizeof c->prof_ms);
@@ -1081,7 +1074,12 @@ int blstm_profile_enable(blstm_ctx* c, int enable) {
 
 int blstm_profile_read(blstm_ctx* c, double* ms_out, int64_t* launches_out, int n_classes) {
     if (!c || !ms_out || !launches_out) return fail(BLSTM_ERR_NULL, "blstm_profile_read: null argument");
-    if (c->twin) return blstm_profile_read(c->twin, ms_out, launches_out, n_classes);
+    // (a model run as its twin: the twin's launches, and the copies around them and the noalloc calls, which are its own)
+    for (int k = 0; k < n_classes && k < PC_COUNT; ++k) { ms_out[k] = 0.0; launches_out[k] = 0; }
+    if (c->twin) {
+        const int rc = blstm_profile_read(c->twin, ms_out, launches_out, n_classes);
+        if (rc != BLSTM_OK) return rc;
+    }
     for (size_t i = 0; i < c->recs_used; ++i) {
         ProfRec& r = c->recs[i];
         hipError_t e = hipEventSynchronize(r.b);
@@ -1093,7 +1091,7 @@ int blstm_profile_read(blstm_ctx* c, double* ms_out, int64_t* launches_out, int 
         c->prof_n[r.cls] += 1;
     }
     c->recs_used = 0;
-    for (int k = 0; k < n_classes && k < PC_COUNT; ++k) { ms_out[k] = c->prof_ms[k]; launches_out[k] = c->prof_n[k]; }
+    for (int k = 0; k < n_classes && k < PC_COUNT; ++k) { ms_out[k] += c->prof_ms[k]; launches_out[k] += c->prof_n[k]; }
     return BLSTM_OK;
 }
 

@@ -8,7 +8,7 @@
 #include <vector>
 
 struct dim3 { uint32_t x, y, z; };
-struct Launch { std::string name; dim3 grid; };
+struct Launch { std::string name; dim3 grid; bool timed; };
 static std::map<const void*, std::string> g_names;
 static std::vector<Launch> g_launches;
 static std::map<int, int> g_cus;
@@ -28,7 +28,7 @@ void recorder_fail(const char* part_of_name) { g_fail = part_of_name; }   // "" 
 int recorder_count() { return (int)g_launches.size(); }
 const char* recorder_name(int i) { return g_launches[i].name.c_str(); }
 unsigned recorder_grid(int i, int axis) { const dim3& g = g_launches[i].grid; return axis == 0 ? g.x : axis == 1 ? g.y : g.z; }
-int recorder_events() { return g_events; }
+int recorder_timed(int i) { return g_launches[i].timed; }         // between the two events of a pair
 
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
@@ -42,7 +42,7 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
 int hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, void*) {
     const std::string name = g_names.count(f) ? g_names[f] : "?";
     if (!g_fail.empty() && name.find(g_fail) != std::string::npos) return g_error = 719;
-    g_launches.push_back({name, grid});
+    g_launches.push_back({name, grid, (g_events & 1) != 0});
     return 0;
 }
 int hipGetLastError() { const int e = g_error; g_error = 0; return e; }
@@ -62,7 +62,7 @@ int hipEventSynchronize(void*) { return 0; }
 int hipEventElapsedTime(float* ms, void*, void*) { *ms = 1.0f; return 0; }
 int hipGetSymbolAddress(void** p, const void*) { *p = reinterpret_cast<void*>(uintptr_t(1) << 40); return 0; }
 int hipMemcpy(void* dst, const void*, size_t n, int) { memset(dst, 0, n); return 0; }
-int hipMemcpyAsync(void*, const void*, size_t, int, void*) { g_launches.push_back({"hipMemcpyAsync", {1, 1, 1}}); return 0; }
+int hipMemcpyAsync(void*, const void*, size_t, int, void*) { g_launches.push_back({"hipMemcpyAsync", {1, 1, 1}, (g_events & 1) != 0}); return 0; }
 int hipStreamSynchronize(void*) { return 0; }
 
 }  // extern "C"

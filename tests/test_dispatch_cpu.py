@@ -129,3 +129,24 @@ def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):
     assert failed == -5
     assert again == [3] if axis else again == [1]
     assert kept == [1] if axis else kept == []
+
+
+@pytest.mark.parametrize("mode,dims", [(1, "T=4, B=16, D=8, H=104, L=2, P=0, V=20"), (1, "T=4, B=16, D=30, H=101, L=2, P=37, V=20"),
+                                       (0, "T=21, B=16, D=33, H=66, L=2, P=301, V=9001")])
+def test_profiling_times_every_launch(recorder, mode, dims):
+    n_launches, untimed, calls, n_timed = recorder(f"""
+        m = Model(mode={mode}, {dims})
+        out = [0, [], 0, 0]
+        bl.lib().blstm_profile_enable(m.ctx, 1)
+        for call in (m.forward, m.xent, m.noalloc, m.backward):
+            n = launches(call)
+            out[0] += len(n)
+            out[1] += [n[i] for i in range(len(n)) if not rec.recorder_timed(i)]
+            out[2] += 1
+        k = bl.lib().blstm_profile_classes()
+        ms, count = (ctypes.c_double * k)(), (ctypes.c_int64 * k)()
+        bl.lib().blstm_profile_read(m.ctx, ms, count, k)
+        out[3] = sum(count)
+    """)
+    assert calls == 4 and untimed == []
+    assert 0 < n_timed <= n_launches                       # (one pair of events may hold several launches)
