@@ -94,6 +94,7 @@ struct Rec32FwdArgs {
     unsigned long long limit_ticks;
     int T, B, H;
     int nu, nbg, tiles_per_group; // set by the launcher
+    bool ask;                     // as in RecFwdArgs
 };
 struct Rec32BwdArgs {
     const float* uh[2];
@@ -107,6 +108,7 @@ struct Rec32BwdArgs {
     unsigned long long limit_ticks;
     int T, B, H;
     int nu, nbg, tiles_per_group; // set by the launcher
+    bool ask;                     // as in RecFwdArgs
 };
 // Whether the persistent kernel takes this shape (and is the faster of the two paths).
 bool rec32_fwd_supported(int B, int H);

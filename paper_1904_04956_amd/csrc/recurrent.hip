@@ -846,27 +846,15 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-// Launches `grid` workgroups of KERNEL if all can be resident at once (they wait on each other), or (a.ask) only says
-// whether they can.
-template <auto KERNEL, typename A>
-hipError_t launch_resident(const A& a, int threads, size_t lds, int grid, hipStream_t st, bool* launched) {
-    int resident = 0;
-    const hipError_t e = resident_workgroups<KERNEL>(threads, lds, &resident);
-    if (e != hipSuccess || resident < grid) return e;
-    *launched = true;
-    if (a.ask) return hipSuccess;
-    hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(threads), lds, st, a);
-    return hipGetLastError();
-}
 template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
-    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, st, launched);
+    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
     const size_t lds = (size_t)NW * 4 * 64 * 16 + (size_t)NW * 2048 + (size_t)NW * 512;   // partial sums; regrouping of dE/da, 2 KB per wavefront; spreading dy, 512 bytes per wavefront
-    return launch_resident<rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, st, launched);
+    return launch_resident<rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {

@@ -342,18 +342,11 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
     }
 }
 
-// Launches one instantiation if its workgroups can all be resident (they wait on each other; the ones that pad the grid
-// to whole rounds of the eight XCDs leave at once).
+// (the workgroups that pad the grid to whole rounds of the eight XCDs leave at once)
 template <auto KERNEL, typename A>
 hipError_t run(const A& a, hipStream_t st, bool* launched) {
-    int resident = 0;
-    const hipError_t e = resident_workgroups<KERNEL>(64 * NWF, 0, &resident);
-    if (e != hipSuccess) return e;
     const int real = 2 * a.nu * a.nbg;
-    if (resident < real) return hipSuccess;
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)((real + 7) & ~7)), dim3(64 * NWF), 0, st, a);
-    *launched = true;
-    return hipGetLastError();
+    return launch_resident<KERNEL>(a, 64 * NWF, 0, (real + 7) & ~7, real, st, launched);
 }
 
 // Unit slices of `units` for H, and the batch groups that leave every XCD no more than one workgroup per CU.

@@ -296,18 +296,10 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
     }
 }
 
-// Launches one instantiation if its workgroups can all be resident, or (a.ask) only says whether they can.
 template <auto KERNEL, typename A>
 hipError_t run(const A& a, hipStream_t st, bool* launched) {
-    int resident = 0;
-    const hipError_t e = resident_workgroups<KERNEL>(64 * NWF, 0, &resident);
-    if (e != hipSuccess) return e;
     const int real = 2 * 2 * ((a.H + 31) / 32) * ((a.B + 15) / 16);
-    if (resident < real) return hipSuccess;
-    *launched = true;
-    if (a.ask) return hipSuccess;
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)((real + 7) & ~7)), dim3(64 * NWF), 0, st, a);
-    return hipGetLastError();
+    return launch_resident<KERNEL>(a, 64 * NWF, 0, (real + 7) & ~7, real, st, launched);
 }
 
 }  // namespace

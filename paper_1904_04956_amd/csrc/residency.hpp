@@ -1,11 +1,12 @@
-// How many workgroups of a kernel the current device holds at once: the persistent kernels' workgroups wait on each other,
-// so a grid of them is launched only if all fit.
+// The persistent kernels' workgroups wait on each other, so all of a grid must be resident at once: a grid is launched only
+// if the device holds it, and only behind the persistent launch before it, whatever streams the two are on.
 #pragma once
 #include <hip/hip_runtime.h>
 
 namespace blstm {
 
-// The answer depends on the kernel and the device only and is kept per kernel and thread for the device last asked about.
+// How many workgroups of a kernel the current device holds at once.  The answer depends on the kernel and the device only
+// and is kept per kernel and thread for the device last asked about.
 template <auto KERNEL>
 hipError_t resident_workgroups(int threads, size_t dyn_lds, int* count) {
     static thread_local int device = -1, held = 0;
@@ -23,6 +24,23 @@ hipError_t resident_workgroups(int threads, size_t dyn_lds, int* count) {
     }
     *count = held;
     return hipSuccess;
+}
+
+// Launches a kernel behind the last one launched here on this device (on a stream that is being captured: without that).
+hipError_t launch_in_turn(const void* kernel, int grid, int threads, size_t dyn_lds, void** args, hipStream_t st);
+
+// Launches `grid` workgroups of KERNEL (`real` of which wait on each other, the others leave at once) if those can all be
+// resident, or (a.ask) only says whether they can.
+template <auto KERNEL, typename A>
+hipError_t launch_resident(const A& a, int threads, size_t dyn_lds, int grid, int real, hipStream_t st, bool* launched) {
+    int resident = 0;
+    const hipError_t e = resident_workgroups<KERNEL>(threads, dyn_lds, &resident);
+    if (e != hipSuccess || resident < real) return e;
+    *launched = true;
+    if (a.ask) return hipSuccess;
+    A copy = a;
+    void* args[] = {&copy};
+    return launch_in_turn(reinterpret_cast<const void*>(KERNEL), grid, threads, dyn_lds, args, st);
 }
 
 }  // namespace blstm

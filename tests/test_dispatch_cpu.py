@@ -26,10 +26,10 @@ class Model:
         self.ctx = bl.blstm_create(mode=mode, **dims)
         bl.blstm_bind(self.ctx, P, bl.blstm_workspace_bytes(self.ctx))
     def option(self, which, value): bl.blstm_set_option(self.ctx, which, value)
-    def forward(self): bl.blstm_forward(self.ctx, P, P, P, 0)
-    def xent(self): bl.softmax_xent_fwd_bwd(self.ctx, P, P, P, P, P, P, 0)
-    def noalloc(self): bl.softmax_xent_fwd_bwd_noalloc(self.ctx, P, P, P, P, P, P, 0)
-    def backward(self): bl.blstm_backward(self.ctx, P, P, P, P, 0)
+    def forward(self, stream=0): bl.blstm_forward(self.ctx, P, P, P, stream)
+    def xent(self, stream=0): bl.softmax_xent_fwd_bwd(self.ctx, P, P, P, P, P, P, stream)
+    def noalloc(self, stream=0): bl.softmax_xent_fwd_bwd_noalloc(self.ctx, P, P, P, P, P, P, stream)
+    def backward(self, stream=0): bl.blstm_backward(self.ctx, P, P, P, P, stream)
 
 
 def launches(call):
@@ -150,3 +150,22 @@ def test_profiling_times_every_launch(recorder, mode, dims):
     """)
     assert calls == 4 and untimed == []
     assert 0 < n_timed <= n_launches                       # (one pair of events may hold several launches)
+
+
+@pytest.mark.parametrize("a,b", [((1, 256, 512), (1, 256, 512)), ((1, 16, 512), (0, 16, 64)), ((0, 64, 512), (0, 64, 512)), ((1, 16, 512), (1, 40, 101))])
+def test_persistent_launches_run_one_behind_the_other(recorder, a, b):
+    # two models on two streams: their workgroups wait on each other, so no two such grids may compete for the CUs
+    out_of_turn, persistent, captured = recorder(f"""
+        a, b = (Model(mode=m, T=4, B=B, D=8, H=H, L=2, P=0, V=20) for m, B, H in ({a}, {b}))
+        out = [0, 0]
+        def all_of(call, stream):
+            n = launches(lambda: call(stream))
+            out[0] += sum(not rec.recorder_in_turn(i) for i in range(len(n)))
+            out[1] += count(n, "rec_") + count(n, "rec32_")
+            return n
+        for call, stream in ((a.forward, 256), (b.forward, 512), (a.xent, 256), (a.backward, 256), (b.xent, 512), (b.backward, 512), (a.forward, 0), (b.forward, 0)):
+            all_of(call, stream)
+        rec.recorder_capturing(ctypes.c_void_p(768))       # (launched without events: nothing a capture refuses)
+        out.append(count(launches(lambda: a.forward(768)), "rec"))
+    """)
+    assert out_of_turn == 0 and persistent == 12 and captured == 2
