@@ -33,7 +33,7 @@ struct GemmDesc {
     int M, N, batch;
     int Npad;                 // 0, or a multiple of the tile width >= N up to which B(n, .) may be read (it holds zeros or
                               // anything there): the product runs on whole tiles, C keeps its N columns
-    bool a_pad, b_pad;        // rows of A / B (as they lie in memory) may be read up to the next 16-byte boundary and hold finite values there
+    bool a_pad;               // rows of A (as they lie in memory) may be read up to the next 16-byte boundary and hold finite values there
     bool c_pad;               // rows of C may be written up to the next multiple of eight columns
     bool long_parts;          // K is split, if at all, into parts of at least eight slabs (see make_plan)
     bool atrans, btrans;

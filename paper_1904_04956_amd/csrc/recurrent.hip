@@ -631,7 +631,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
             if (SENTINEL) {
-                // the gate rows of this wavefront come from KWB/32 producers: probe each one's last unit,
+                // the gate rows of this wavefront come from the NU producers: probe each one's last unit,
                 // then stream the slabs of 128 gate rows with the next slab's loads in flight
                 const bf16_t* probe = ab + xoff(wave * HX + (PADDED ? min(lane, NU - 1) : lane & (4 * KW / 32 - 1)) * 32 + 31, 31);
                 uint4 afrag[2][8];
