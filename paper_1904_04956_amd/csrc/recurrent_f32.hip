@@ -20,6 +20,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
+#include <initializer_list>
 
 namespace blstm {
 namespace {
@@ -108,8 +109,8 @@ __device__ __forceinline__ int tiles_of(int bg, int per_group, int rows, int B) 
 }
 
 // ------------------------------------------------------------------------------ forward
-// H' = 32 NQ; each wavefront contracts 8 NQ columns.  H = 512, 64 sequences: 6 us a frame with the input
-// product (65 with one launch per frame and product and one per cell step).
+// H' = 32 NQ; each wavefront contracts 8 NQ columns.  H = 512, 64 sequences: 91 us for 21 frames, 4.3 a frame (with a
+// product and a cell launch a frame 65).
 template <int NQ>
 __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) {
     constexpr int PS = 36;                               // floats per row of the partial tiles
@@ -218,8 +219,8 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) 
 }
 
 // ------------------------------------------------------------------------------ backward
-// H' = 16 NQ; wavefront w contracts gate w's H columns of dE/da.  H = 512, 64 sequences: 15 us a
-// frame with the weight gradients and the softmax layer of a small model (29 with launches per frame).
+// H' = 16 NQ; wavefront w contracts gate w's H columns of dE/da.  H = 512, 64 sequences: 160 us for 21 frames, 7.6 a
+// frame (with a product and a cell launch a frame 23).
 template <int NQ>
 __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) {
     constexpr int PS = 20;
@@ -360,13 +361,40 @@ void split(A& a, int units, int rows) {
 
 }  // namespace
 
-// A workgroup walks the tiles of its group one after the other, so with many sequences of wide cells one launch per frame
-// of the 128x128 product kernel keeps the matrix cores busier.  Measured (one layer, T = 21, us, persistent against per
-// frame), forward: H = 512, B = 2048 2897 / 3145; H = 1024, B = 256 1347 / 2492, B = 1024 5108 / 4350.  Backward (with
-// the weight gradients): H = 320, B = 2048 3475 / 3471; H = 512, B = 256 907 / 1330, B = 1024 3072 / 2595;
-// H = 1024, B = 256 2306 / 2201.  The lines lie between these in B H^2, to which the products are proportional.
-bool rec32_fwd_supported(int B, int H) { return H <= 1024 && (double)B * H * H <= 650e6; }
-bool rec32_bwd_supported(int B, int H) { return H <= 1024 && (double)B * H * H <= 180e6; }
+// Which of the two paths is the faster, by estimates of what a frame takes (us).  Persistent: the tiles a workgroup walks one
+// after the other, each a chain whose length goes with the width the kernel is built for (measured, us a tile and frame,
+// forward / backward: 2.0 / 1.9 at 64 cells, 2.7 / 2.9 at 256, 3.8 / 4.8 at 512, 5.2 / 6.2 at 768, 6.9 / 7.6 at 1024).  One
+// launch per frame: forward the chain of one round of 128x128 tiles, the cells, and the further rounds of tiles; backward
+// the launches, the cells, and the product, which is split along K.  Of 194 shapes of 64 to 1024 cells and 96 to 8192
+// sequences the estimates pick the slower path by more than 6 % in two forward (worst 12 %) and in six backward (12 %).
+// (A line at B H^2 = 650e6 and 180e6 did so in 15 and 28, worst 55 and 34 %: 1408 sequences of 576 cells forward
+// 4266 us persistent, 3063 with launches per frame.)
+namespace {
+int tiles_a_workgroup(int B, int H, int units, int rows) {
+    Rec32FwdArgs a{};
+    a.B = B; a.H = H;
+    split(a, units, rows);
+    return a.tiles_per_group;
+}
+// The built width for H (see launch_rec32_*): `unit` times the least of the built NQ.
+int built_width(int H, int unit, std::initializer_list<int> nqs) {
+    for (int nq : nqs) if (H <= unit * nq) return unit * nq;
+    return 0;
+}
+}  // namespace
+bool rec32_fwd_supported(int B, int H) {
+    if (H > 1024) return false;
+    const double persistent = tiles_a_workgroup(B, H, 8, 32) * (1.5 + 0.0049 * built_width(H, 32, {1, 2, 4, 8, 12, 16, 20, 24, 32}));
+    const long long tiles = 2LL * ((B + 127) / 128) * ((4 * H + 127) / 128);
+    const double per_frame = 32 + 0.0645 * H + 5e-5 * (double)B * H + 0.055 * H * (double)((tiles + 255) / 256 - 1);
+    return persistent <= per_frame;
+}
+bool rec32_bwd_supported(int B, int H) {
+    if (!rec32_fwd_supported(B, H)) return false;        // (its workspace is part of the forward kernel's)
+    const double persistent = tiles_a_workgroup(B, H, 16, 16) * (1.4 + 0.0063 * built_width(H, 16, {2, 4, 8, 16, 24, 32, 40, 48, 64}));
+    const double cells = (double)B * H, per_frame = 20 + 15e-6 * cells + 0.115e-6 * cells * H;
+    return persistent <= per_frame;
+}
 size_t rec32_hx_bytes(int T, int B, int H) { return (size_t)T * 2 * ((B + 31) / 32) * ((H + 7) / 8) * 1024; }
 size_t rec32_dax_bytes(int T, int B, int H) { return (size_t)T * 2 * ((B + 15) / 16) * ((H + 15) / 16) * 4096; }
 

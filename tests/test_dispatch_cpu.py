@@ -169,3 +169,18 @@ def test_persistent_launches_run_one_behind_the_other(recorder, a, b):
         out.append(count(launches(lambda: a.forward(768)), "rec"))
     """)
     assert out_of_turn == 0 and persistent == 12 and captured == 2
+
+
+@pytest.mark.parametrize("B,H,fwd,bwd", [
+    (64, 512, True, True), (256, 256, True, True), (4096, 64, True, True), (15, 1024, True, True),
+    (1408, 576, False, False), (1280, 704, False, False), (1024, 768, False, False), (4096, 384, False, False),   # were persistent, and slower for it
+    (384, 704, True, False), (8192, 128, True, False), (4096, 200, True, False),
+    (768, 1024, True, False), (2048, 512, True, False),
+])
+def test_float_recurrences_take_the_faster_path(recorder, B, H, fwd, bwd):
+    f, b = recorder(f"""
+        m = Model(mode=0, T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        f, b = launches(m.forward), launches(m.backward)
+        out = [[count(f, "rec32_fwd"), count(f, "cell_fwd")], [count(b, "rec32_bwd"), count(b, "cell_bwd")]]
+    """)
+    assert f == ([1, 0] if fwd else [0, 2]) and b == ([1, 0] if bwd else [0, 2])

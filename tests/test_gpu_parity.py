@@ -333,6 +333,14 @@ def test_persistent_recurrent_kernels_fp32(dims):
     check_step(dims, 0, seed=84, theta_scale=1.0 if dims["H"] > 500 else 2.0)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=4, B=700, D=8, H=120, L=1, P=0, V=20),           # three tiles a workgroup backward, two forward, the last ragged
+    dict(T=3, B=300, D=8, H=250, L=2, P=16, V=20),
+])
+def test_several_tiles_a_workgroup_fp32(dims):
+    check_step(dims, 0, seed=98, theta_scale=1.0)
+
+
 def test_abandoned_wait_fp32():
     # as test_abandoned_wait_is_reported_in_band_and_recovered_from, float mode
     from paper_1904_04956_amd import binding as bl
