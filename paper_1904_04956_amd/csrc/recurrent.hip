@@ -904,7 +904,11 @@ hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) 
 // Supported widths: multiples of 8 up to 1024, always on four wavefronts that split the contraction (four batch rows per
 // thread in every variant).  128, 256, 512 and 1024 have kernels of their own; the others run padded to the next multiple
 // of 128 (H = 320, 50 sequences: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
+// Padded widths above 512 only up to 3072 sequences: beyond, the tiles a workgroup walks backward cost more than the forward
+// pass gains (one layer, 21 frames, both passes, us, persistent / launches per frame: H = 576, B = 2048 3084 / 3709,
+// 3072 4687 / 4582, 4096 6686 / 5935; H = 768, 3072 6252 / 6774, 4096 8893 / 8322; H = 504, 16384 15990 / 19181).
 bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
+bool rec_takes(int B, int H) { return rec_supported(H) && (rec_fenced(H) || H <= 512 || B <= 3072); }
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
 // Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than
 // one workgroup per CU (32).

@@ -184,3 +184,12 @@ def test_float_recurrences_take_the_faster_path(recorder, B, H, fwd, bwd):
         out = [[count(f, "rec32_fwd"), count(f, "cell_fwd")], [count(b, "rec32_bwd"), count(b, "cell_bwd")]]
     """)
     assert f == ([1, 0] if fwd else [0, 2]) and b == ([1, 0] if bwd else [0, 2])
+
+
+@pytest.mark.parametrize("B,H,persistent", [(3072, 576, True), (3073, 576, False), (4096, 768, False), (16384, 504, True), (4096, 1024, True)])
+def test_padded_widths_of_many_sequences_take_the_faster_path(recorder, B, H, persistent):
+    f, b = recorder(f"""
+        m = Model(T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        out = [[count(n, "rec_fwd") + count(n, "rec_bwd"), count(n, "cell_")] for n in (launches(m.forward), launches(m.backward))]
+    """)
+    assert f == b == ([1, 0] if persistent else [0, 2])
