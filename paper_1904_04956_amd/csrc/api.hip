@@ -263,7 +263,7 @@ bool wants_twin(const blstm_ctx* c) {
     const int m = c->st == DT_BF16 ? 8 : 4;
     const bool h = c->H % m != 0, p = c->P % m != 0, d = c->st == DT_F32 && c->D % m != 0;
     if (!h && !p && !d) return false;
-    if (c->st == DT_BF16 && h && c->T >= 4 && rec_takes(c->B, up_to(c->H, m))) return true;
+    if (c->st == DT_BF16 && h && c->T >= 4 && rec_takes(c->T, c->B, up_to(c->H, m))) return true;
     return 6.0 * c->M * (double)c->nparam > 5e9;
 }
 
@@ -447,7 +447,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->dax_filled = false;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
-    if (c->st == DT_BF16 && rec_takes(c->B, c->H)) {
+    if (c->st == DT_BF16 && rec_takes(c->T, c->B, c->H)) {
         const int tiles = (c->B + 31) / 32, nbg = rec_groups(c->H, tiles);
         c->rec_nbg = nbg;
         c->rec_tiles = (tiles + nbg - 1) / nbg;
@@ -462,8 +462,8 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         c->wHX = w;  w += c->hx_bytes * c->L;
         c->wDAX = w; w += c->dax_bytes * c->L;
     }
-    c->rec32_fwd = c->st == DT_F32 && rec32_fwd_supported(c->B, c->H);
-    c->rec32_bwd = c->st == DT_F32 && rec32_bwd_supported(c->B, c->H);
+    c->rec32_fwd = c->st == DT_F32 && c->T > 1 && rec32_fwd_supported(c->B, c->H);   // (a single frame has no recurrence)
+    c->rec32_bwd = c->rec32_fwd && rec32_bwd_supported(c->B, c->H);
     if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da, one for all layers
         c->wCNT = w; w += 256;
         c->hx_bytes = up256(rec32_hx_bytes(c->T, c->B, c->H));

@@ -69,7 +69,7 @@ struct RecBwdArgs {
     bool ask;                     // as above
 };
 bool rec_supported(int H);                  // whether the persistent kernels take this width
-bool rec_takes(int B, int H);               // ... and whether they are the faster path for so many sequences
+bool rec_takes(int T, int B, int H);        // ... and whether they are the faster path for so many frames and sequences
 bool rec_fenced(int H);                     // whether they are built with the fenced protocol too
 int rec_groups(int H, int tiles, int per_cu = 1);   // batch groups per direction for so many 32-row tiles and workgroups per CU
 // Whether launch_rec_fwd for this width honours RecFwdArgs::fill.

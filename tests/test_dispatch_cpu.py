@@ -193,3 +193,13 @@ def test_padded_widths_of_many_sequences_take_the_faster_path(recorder, B, H, pe
         out = [[count(n, "rec_fwd") + count(n, "rec_bwd"), count(n, "cell_")] for n in (launches(m.forward), launches(m.backward))]
     """)
     assert f == b == ([1, 0] if persistent else [0, 2])
+
+
+@pytest.mark.parametrize("mode,H,T,persistent", [(1, 320, 1, False), (1, 320, 2, True), (1, 512, 1, True), (0, 32, 1, False), (0, 32, 2, True)])
+def test_a_single_frame_needs_no_recurrence(recorder, mode, H, T, persistent):
+    # (of bf16 widths with kernels of their own the one launch is as short as the cell's)
+    f, b = recorder(f"""
+        m = Model(mode={mode}, T={T}, B=16, D=8, H={H}, L=1, P=0, V=20)
+        out = [[count(n, "rec"), count(n, "cell_")] for n in (launches(m.forward), launches(m.backward))]
+    """)
+    assert f == b == ([1, 0] if persistent else [0, 1])
