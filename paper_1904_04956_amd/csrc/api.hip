@@ -83,8 +83,8 @@ struct blstm_ctx {
     size_t ws_bound;
     bool have_forward;
     // A model whose rows are not whole 16-byte words (H or P, in float mode D too) runs as a twin with these widths padded
-    // by zeros: the twin's units beyond H have zero weights both ways, stay exactly zero and change no other value.  Null
-    // otherwise.  The workspace is the twin's, then its weights, gradient, x, z and dz.
+    // by zeros: the twin's units beyond H have zero weights both ways (and zero a_x whatever x holds: see launch_zero_columns),
+    // stay exactly zero and change no other value.  Null otherwise.  The workspace is the twin's, then its weights, gradient, x, z and dz.
     blstm_ctx* twin;
     int Hown;                           // in a twin: the model's own H; otherwise H
     std::vector<BlockTensor> tparam;    // every tensor of the flat vector, compact here and padded there; the softmax layer's two last
@@ -257,8 +257,10 @@ int resident_scratch(char** out) {
 inline int up_to(int v, int m) { return (v + m - 1) / m * m; }
 
 // Whether the model is run as its twin: misaligned rows put every product on the guarded kernel and, in bf16 mode, the
-// recurrence on one launch per frame.  The copies cost about six launches a step (25 us), so a model with neither frames
-// nor arithmetic enough to earn them back stays as it is (5 GFLOP a step take about 50 us on the guarded kernels).
+// recurrence on one launch per frame.  The copies cost three launches a step (weights, softmax layer, gradient), one more
+// unless the softmax layer's gradient is deferred, four where the width of z is padded (z, dz, each both ways), two in float
+// mode where D is, and one behind the first layer's product where H is: four to eleven of about 4 us.  So a model with neither
+// frames nor arithmetic enough to earn them back stays as it is (5 GFLOP a step take about 50 us on the guarded kernels).
 bool wants_twin(const blstm_ctx* c) {
     const int m = c->st == DT_BF16 ? 8 : 4;
     const bool h = c->H % m != 0, p = c->P % m != 0, d = c->st == DT_F32 && c->D % m != 0;
