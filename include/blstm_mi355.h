@@ -151,11 +151,12 @@ int adpsgd_ring_partner(int R, int64_t step, int32_t* partner_out);
 /* Options.  BLSTM_OPT_RECURRENT_PATH: 0 (default) runs each layer's T recurrent frames in one
    persistent kernel where the shape allows it (mode 1: H up to 1024 after rounding up to a multiple
    of 8; mode 0: H up to 1024 and not many sequences of wide cells; grid co-resident on the device), 1 forces
-   one launch per frame everywhere.  The workgroups of a persistent kernel wait on each other.  Those that a process
-   launches on one GPU, from whatever contexts, threads and streams, run one behind the other.  Replays of a captured
-   graph that holds them, and other processes on the same GPU, are not ordered with them: two such kernels at once can
-   starve each other until their waits are abandoned after 2 s (blstm_device_status; the results are NaN).  Where that
-   can happen, set 1: launches per frame run beside anything. */
+   one launch per frame everywhere.  The workgroups of a persistent kernel wait on each other.  Of those that a process
+   launches on one GPU, from whatever contexts, threads and streams, only as many run at once as fit the device
+   together; the others wait for them.  Replays of a captured graph that holds them, and other processes on the same
+   GPU, are not ordered with them: several such kernels at once can starve each other until their waits are abandoned
+   after 2 s (blstm_device_status; the results are NaN).  Where that can happen, set 1: launches per frame run beside
+   anything. */
 #define BLSTM_OPT_RECURRENT_PATH 1
 /* BLSTM_OPT_RECURRENT_SYNC (default 1): how the workgroups of a persistent kernel exchange h / dE/da
    between frames.  0: plain accesses ordered by agent-scope release/acquire fences around a counter.

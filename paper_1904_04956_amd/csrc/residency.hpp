@@ -1,5 +1,5 @@
 // The persistent kernels' workgroups wait on each other, so all of a grid must be resident at once: a grid is launched only
-// if the device holds it, and only behind the persistent launch before it, whatever streams the two are on.
+// if the device holds it, and behind the persistent launches that it cannot run beside, whatever streams they are on.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -26,7 +26,8 @@ hipError_t resident_workgroups(int threads, size_t dyn_lds, int* count) {
     return hipSuccess;
 }
 
-// Launches a kernel behind the last one launched here on this device (on a stream that is being captured: without that).
+// Launches a kernel behind those launched here on this device that would not fit beside it (on a stream that is being captured:
+// without that).  grid: a multiple of eight.
 hipError_t launch_in_turn(const void* kernel, int grid, int threads, size_t dyn_lds, void** args, hipStream_t st);
 
 // Launches `grid` workgroups of KERNEL (`real` of which wait on each other, the others leave at once) if those can all be

@@ -4,19 +4,21 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
 struct dim3 { uint32_t x, y, z; };
-struct Launch { std::string name; dim3 grid; bool timed, in_turn; };
+struct Launch { std::string name; dim3 grid; bool timed; };
 static std::map<const void*, std::string> g_names;
 static std::vector<Launch> g_launches;
 static std::map<int, int> g_cus;
 static std::vector<std::pair<std::string, int>> g_occupancy;
 static std::string g_fail;
-// Persistent launches in the order they were made: what an event's last one is, and the last one each stream is behind.
-static int g_persistent = 0;
-static std::map<void*, int> g_event_of, g_behind;
+// Persistent launches in the order they were made: each one's workgroups and the earlier ones it is behind; the ones that are
+// complete with an event, and before whatever is next on a stream.
+static std::vector<std::pair<int, std::set<int>>> g_persistent;
+static std::map<void*, std::set<int>> g_with_event, g_before;
 static void* g_capturing = nullptr;
 static int g_device = 0, g_error = 0, g_events = 0;
 static struct { dim3 grid, block; size_t lds; void* stream; } g_config;
@@ -32,7 +34,9 @@ void recorder_fail(const char* part_of_name) { g_fail = part_of_name; }   // "" 
 int recorder_count() { return (int)g_launches.size(); }
 const char* recorder_name(int i) { return g_launches[i].name.c_str(); }
 unsigned recorder_grid(int i, int axis) { const dim3& g = g_launches[i].grid; return axis == 0 ? g.x : axis == 1 ? g.y : g.z; }
-int recorder_in_turn(int i) { return g_launches[i].in_turn; }   // behind every persistent launch before it
+int recorder_persistent() { return (int)g_persistent.size(); }
+int recorder_workgroups(int i) { return g_persistent[i].first; }
+int recorder_behind(int i, int j) { return (int)g_persistent[i].second.count(j); }
 void recorder_capturing(void* stream) { g_capturing = stream; }
 int recorder_timed(int i) { return g_launches[i].timed; }         // between the two events of a pair
 
@@ -48,21 +52,21 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
 int hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, void* stream) {
     const std::string name = g_names.count(f) ? g_names[f] : "?";
     if (!g_fail.empty() && name.find(g_fail) != std::string::npos) return g_error = 719;
-    bool in_turn = true;
     if (name.find("rec_") != std::string::npos || name.find("rec32_") != std::string::npos) {
-        in_turn = g_behind[stream] == g_persistent;
-        g_behind[stream] = ++g_persistent;
+        const int n = (int)g_persistent.size();
+        g_persistent.push_back({(int)grid.x, g_before[stream]});
+        g_before[stream].insert(n);
     }
-    g_launches.push_back({name, grid, (g_events & 1) != 0, in_turn});
+    g_launches.push_back({name, grid, (g_events & 1) != 0});
     return 0;
 }
 int hipExtLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, void* stream, void*, void* stop, int) {
     const int e = hipLaunchKernel(f, grid, block, args, lds, stream);
-    if (e == 0 && stop) g_event_of[stop] = g_persistent;
+    if (e == 0 && stop) g_with_event[stop] = g_before[stream];
     return e;
 }
 int hipStreamWaitEvent(void* stream, void* event, unsigned) {
-    if (g_event_of[event] > g_behind[stream]) g_behind[stream] = g_event_of[event];
+    g_before[stream].insert(g_with_event[event].begin(), g_with_event[event].end());
     return 0;
 }
 int hipStreamIsCapturing(void* stream, int* status) { *status = stream != nullptr && stream == g_capturing; return 0; }
@@ -84,7 +88,7 @@ int hipEventSynchronize(void*) { return 0; }
 int hipEventElapsedTime(float* ms, void*, void*) { *ms = 1.0f; return 0; }
 int hipGetSymbolAddress(void** p, const void*) { *p = reinterpret_cast<void*>(uintptr_t(1) << 40); return 0; }
 int hipMemcpy(void* dst, const void*, size_t n, int) { memset(dst, 0, n); return 0; }
-int hipMemcpyAsync(void*, const void*, size_t, int, void*) { g_launches.push_back({"hipMemcpyAsync", {1, 1, 1}, (g_events & 1) != 0, true}); return 0; }
+int hipMemcpyAsync(void*, const void*, size_t, int, void*) { g_launches.push_back({"hipMemcpyAsync", {1, 1, 1}, (g_events & 1) != 0}); return 0; }
 int hipStreamSynchronize(void*) { return 0; }
 
 }  // extern "C"

@@ -152,23 +152,62 @@ def test_profiling_times_every_launch(recorder, mode, dims):
     assert 0 < n_timed <= n_launches                       # (one pair of events may hold several launches)
 
 
-@pytest.mark.parametrize("a,b", [((1, 256, 512), (1, 256, 512)), ((1, 16, 512), (0, 16, 64)), ((0, 64, 512), (0, 64, 512)), ((1, 16, 512), (1, 40, 101))])
-def test_persistent_launches_run_one_behind_the_other(recorder, a, b):
-    # two models on two streams: their workgroups wait on each other, so no two such grids may compete for the CUs
-    out_of_turn, persistent, captured = recorder(f"""
-        a, b = (Model(mode=m, T=4, B=B, D=8, H=H, L=2, P=0, V=20) for m, B, H in ({a}, {b}))
-        out = [0, 0]
-        def all_of(call, stream):
-            n = launches(lambda: call(stream))
-            out[0] += sum(not rec.recorder_in_turn(i) for i in range(len(n)))
-            out[1] += count(n, "rec_") + count(n, "rec32_")
-            return n
-        for call, stream in ((a.forward, 256), (b.forward, 512), (a.xent, 256), (a.backward, 256), (b.xent, 512), (b.backward, 512), (a.forward, 0), (b.forward, 0)):
-            all_of(call, stream)
-        rec.recorder_capturing(ctypes.c_void_p(768))       # (launched without events: nothing a capture refuses)
-        out.append(count(launches(lambda: a.forward(768)), "rec"))
+@pytest.mark.parametrize("models,streams,together", [
+    ([(1, 256, 512)], [256, 512], 256),                    # (mode, sequences, cells); each launch fills the device
+    ([(0, 64, 512)], [256, 512], 256),
+    ([(1, 16, 512), (0, 16, 64), (1, 40, 101)], [256, 512, 768], None),
+    ([(1, 16, 512)], [256, 512, 768, 1024, 0], 256),        # 64 workgroups a launch: four fit, the fifth waits
+    ([(1, 8, 128)], [256 * k for k in range(1, 13)], 128),  # more streams than lanes: eight of 16 workgroups
+    ([(1, 256, 512), (1, 16, 512), (1, 2000, 256), (1, 8, 128)], [256, 512, 768], None),   # every stream goes from large launches to small ones and back
+])
+def test_persistent_launches_that_may_run_at_once_fit_the_device(recorder, models, streams, together):
+    # their workgroups wait on each other: grids that are not ordered never have more than the device's 256 CUs together
+    grids, behind, captured = recorder(f"""
+        made = [[Model(mode=m, T=4, B=B, D=8, H=H, L=2, P=0, V=20) for m, B, H in {models}] for s in {streams}]
+        for k in range({len(models)} + 1):
+            for i, s in enumerate({streams}):
+                m = made[i][(i + k) % {len(models)}]
+                m.forward(s); m.xent(s); m.backward(s)
+        n = rec.recorder_persistent()
+        out = [[rec.recorder_workgroups(i) for i in range(n)], [[rec.recorder_behind(i, j) for j in range(i)] for i in range(n)]]
+        rec.recorder_capturing(ctypes.c_void_p(1 << 16))   # (launched without events: nothing a capture refuses)
+        out.append(count(launches(lambda: made[0][0].forward(1 << 16)), "rec"))
     """)
-    assert out_of_turn == 0 and persistent == 12 and captured == 2
+    assert captured == 2 and all(g % 8 == 0 for g in grids)
+    small = [i for i in range(len(grids)) if grids[i] <= 256]
+    worst = _most_at_once([grids[i] for i in small], [[behind[i][j] for j in small if j < i] for i in small])
+    assert worst <= 256 and (together is None or worst == together)
+    assert _most_at_once(grids, behind) <= max(256, max(grids))   # (a larger one runs alone)
+
+
+def test_idle_streams_keep_nobody_waiting(recorder):
+    # five streams ran something earlier; three that fit the device together still run side by side
+    last, ordered = recorder("""
+        made = [Model(T=4, B=16, D=8, H=512, L=1, P=0, V=20) for s in range(8)]
+        for m, s in zip(made, range(1, 9)): m.forward(256 * s)
+        for k in range(3):
+            for s in (6, 7, 8): made[s - 1].forward(256 * s)
+        n = rec.recorder_persistent()
+        out = [[rec.recorder_workgroups(i) for i in range(n - 3, n)], [rec.recorder_behind(i, j) for i in range(n - 3, n) for j in range(n - 3, i)]]
+    """)
+    assert last == [64, 64, 64] and ordered == [0, 0, 0]
+
+
+def _most_at_once(weight, behind):
+    # the heaviest set of launches none of which is behind another: the least flow through the order that gives every launch its weight
+    from scipy.optimize import linprog
+    from scipy.sparse import lil_matrix
+    n = len(weight)
+    edges = [(j, i) for i in range(n) for j in range(i) if behind[i][j]]
+    into, outof = lil_matrix((n, 2 * n + len(edges))), lil_matrix((n, 2 * n + len(edges)))
+    for i in range(n):
+        into[i, i] = outof[i, n + i] = 1.0
+    for k, (j, i) in enumerate(edges):
+        outof[j, 2 * n + k] = into[i, 2 * n + k] = 1.0
+    cost = [1.0] * n + [0.0] * (n + len(edges))
+    r = linprog(cost, A_ub=-into.tocsr(), b_ub=[-w for w in weight], A_eq=(into - outof).tocsr(), b_eq=[0.0] * n, method="highs")
+    assert r.status == 0
+    return round(r.fun)
 
 
 @pytest.mark.parametrize("B,H,fwd,bwd", [
