@@ -66,6 +66,7 @@ struct blstm_ctx {
     size_t noalloc_need;      // scratch by which softmax_xent_fwd_bwd_noalloc decides whether a call fits the resident array
     int Dp;                   // 0, or the first layer's input width rounded up to whole tiles (padded copies of x and W_x)
     size_t wXP, wWP;
+    int rec_cnt;              // counters of the persistent kernels, the abort word behind them
     int rec_nbg, rec_tiles;   // batch groups per direction and 32-row tiles per group of the persistent kernels
     int rec_path;             // 0 = persistent kernels where supported, 1 = one launch per frame
     int rec_sync;             // exchange of the persistent kernels: 0 = fenced counters, 1 = sentinel-tagged data
@@ -91,7 +92,7 @@ struct blstm_ctx {
     BlockTensor tx, tz, tu;             // x (float mode, where D is padded); z / dz of the stack and of the softmax block
     size_t tTHETA, tGRAD, tX, tZ, tDZ;
     const void* ttheta_of;              // the weights the padded ones were made from (null: to be made)
-    std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel of recurrent.hip (1) or recurrent_small.hip (2) (whose saved gates only its backward twin reads)
+    std::vector<char> fwd_persistent;   // per layer: the forward pass ran the persistent kernel of recurrent.hip (1), recurrent_small.hip (2) or recurrent_tile.hip (3) (whose saved gates only its backward twin reads)
     // profiling
     bool prof;
     std::vector<ProfRec> recs;
@@ -140,7 +141,7 @@ GemmDesc gemm_desc(const blstm_ctx* c, DType in, DType out) {
     return d;
 }
 
-// Which persistent kernels both passes of a bf16 layer can run with: 2 = recurrent_small.hip, 1 = recurrent.hip, 0 = neither
+// Which persistent kernels both passes of a bf16 layer can run with: 3 = recurrent_tile.hip, 2 = recurrent_small.hip, 1 = recurrent.hip, 0 = none
 // (the backward pass must follow its forward twin: what the forward one saves only it can read).
 int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
     RecFwdArgs f{};
@@ -149,11 +150,18 @@ int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
     b.B = c->B; b.H = c->H; b.nbg = c->rec_nbg; b.tiles_per_group = c->rec_tiles; b.ask = true;
     bool fwd = false, bwd = false;
     *kind = 0;
-    if (sentinel && rec_small_supported(c->B, c->H)) {
+    const bool few = sentinel && rec_small_supported(c->B, c->H);
+    if (few) {
         hipError_t e = launch_rec_small_fwd(f, nullptr, &fwd);
         if (e == hipSuccess) e = launch_rec_small_bwd(b, nullptr, &bwd);
         if (e != hipSuccess) return check_hip(e, "persistent recurrent kernels");
         if (fwd && bwd) { *kind = 2; return BLSTM_OK; }
+    }
+    if (!few && rec_tile_units(c->B, c->H) > 0) {
+        hipError_t e = launch_rec_tile_fwd(f, sentinel, nullptr, &fwd);
+        if (e == hipSuccess) e = launch_rec_tile_bwd(b, sentinel, nullptr, &bwd);
+        if (e != hipSuccess) return check_hip(e, "persistent recurrent kernels");
+        if (fwd && bwd) { *kind = 3; return BLSTM_OK; }
     }
     hipError_t e = launch_rec_fwd(f, sentinel, nullptr, &fwd);
     if (e == hipSuccess) e = launch_rec_bwd(b, sentinel, nullptr, &bwd);
@@ -445,7 +453,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         c->wWP = w; w += up256((size_t)2 * 4 * H * c->Dp * 2);
     }
     // persistent recurrent kernels: transposed U_h per layer and direction, counters, abort word
-    c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false;
+    c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false;
     c->dax_filled = false;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
@@ -455,7 +463,8 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         c->rec_tiles = (tiles + nbg - 1) / nbg;
         w += up256((size_t)c->L * 2 * 4 * H * H * 2);
         c->wCNT = w;
-        w += up256(((size_t)2 * nbg * c->rec_tiles + 64) * 4);
+        c->rec_cnt = 2 * nbg * c->rec_tiles > 2 * ((c->B + 15) / 16) ? 2 * nbg * c->rec_tiles : 2 * ((c->B + 15) / 16);
+        w += up256(((size_t)c->rec_cnt + 64) * 4);
         // exchange copies of h and dE/da in MFMA-fragment order, one per layer (whole 32-row tiles),
         // contiguous so that one fill marks all of a pass's copies as "not written yet"
         const size_t Mx = (size_t)c->T * tiles * 32;
@@ -584,7 +593,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     }
     const bool persistent = kind > 0;
     const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
-    const bool fills = kind == 2 || (kind == 1 && ctx->rec_sync == 1 && rec_fwd_fills(H));   // the forward kernels mark the exchange copies of dE/da
+    const bool fills = kind >= 2 && ctx->rec_sync == 1;   // the forward kernels mark the exchange copies of dE/da
     if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {
@@ -624,7 +633,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
         }
         ctx->fwd_persistent[l] = 0;
         unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);
-        const int ncnt = 2 * ctx->rec_nbg * ctx->rec_tiles;
+        const int ncnt = ctx->rec_cnt;
         if ((persistent || persistent32) && (!ctx->abort_clean || ctx->test_abort)) {
             RUN(PC_MISC, "abort word", launch_fill_u32(cnt + ncnt, 1, ctx->test_abort ? 1u : 0u, st));
             ctx->abort_clean = true;
@@ -657,7 +666,8 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
                 a.fill_words = ctx->dax_bytes / 16;
             }
             bool launched = false;
-            if (kind == 2) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
+            if (kind == 3) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_tile_fwd(a, ctx->rec_sync == 1, st, &launched));
+            else if (kind == 2) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
             else RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
             if (!launched) return fail(BLSTM_ERR_HIP, "blstm_forward: the persistent kernel cannot be launched");
             ctx->fwd_persistent[l] = (char)kind;
@@ -816,7 +826,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
         bool rec_done = false;
         if (ctx->fwd_persistent[l]) {
             unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);
-            const int ncnt = 2 * ctx->rec_nbg * ctx->rec_tiles;
+            const int ncnt = ctx->rec_cnt;
             unsigned short* uht0 = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wUHT) + (size_t)l * 2 * 4 * H * H;
             unsigned short* uht1 = uht0 + (size_t)4 * H * H;
             if (!sentinel) RUN(PC_MISC, "counters", launch_fill_u32(cnt, ncnt, 0u, st));
@@ -828,7 +838,8 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
+            if (ctx->fwd_persistent[l] == 3) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_tile_bwd(a, sentinel, st, &rec_done));
+            else if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
             else RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));
             if (!rec_done)
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
@@ -1050,7 +1061,7 @@ int blstm_device_status(blstm_ctx* c, void* stream) {
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return check_hip(e, "blstm_device_status");
     if (!c->ws || (c->rec_nbg == 0 && !c->rec32_fwd) || !c->abort_clean) return BLSTM_OK;
-    unsigned* word = reinterpret_cast<unsigned*>(c->ws + c->wCNT) + 2 * c->rec_nbg * c->rec_tiles;
+    unsigned* word = reinterpret_cast<unsigned*>(c->ws + c->wCNT) + c->rec_cnt;
     unsigned v = 0;
     e = hipMemcpy(&v, word, sizeof v, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return check_hip(e, "blstm_device_status");

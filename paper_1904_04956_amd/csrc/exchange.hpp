@@ -1,4 +1,4 @@
-// The pieces of the sentinel protocol that the persistent bf16 kernels share (see recurrent.hip).
+// The pieces of the protocols that the persistent bf16 kernels share (see recurrent.hip).
 #pragma once
 #include "common.hpp"
 
@@ -47,5 +47,93 @@ __device__ __forceinline__ bool has_sentinel_half(unsigned w) { return ((~w - 0x
 // write-through stores (a full __syncthreads would drain the loads issued ahead for the next item
 // and the acknowledgements of the exchange stores on every item).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// ---- FENCED protocol ----------------------------------------------------------------------------
+// Waits until *cnt >= target; thread 0 polls.  One barrier inside.  Returns true (to every thread) if the
+// wait was abandoned.
+__device__ __forceinline__ bool wait_counter(unsigned* cnt, unsigned target, unsigned* abort_word, unsigned long long limit_ticks) {
+    int gave_up = 0;
+    if (threadIdx.x == 0) {
+        const unsigned long long t0 = wall_clock64();
+        unsigned it = 0;
+        while (ld_coh_u32(cnt) < target) {
+            __builtin_amdgcn_s_sleep(1);
+            if ((++it & 63u) == 0) {
+                if (ld_coh_u32(abort_word) != 0) { gave_up = 1; break; }
+                if (wall_clock64() - t0 > limit_ticks) {
+                    __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    gave_up = 1;
+                    break;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    return __syncthreads_or(gave_up) != 0;
+}
+// After the workgroup's stores: the barrier orders them before thread 0's agent-scope release.
+__device__ __forceinline__ void signal_counter(unsigned* cnt) {
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- 16-row tiles (recurrent_small.hip, recurrent_tile.hip): fragments of 32 columns of 16 rows, one KB each ----------------
+__device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ bool all_there16(const uint4 (&f)[N]) {
+    unsigned m = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
+    return __all(!has_sentinel_half(m));
+}
+// f[q] = the 16 bytes at base + off(q): ordinary loads first, past the caches until every element is written.
+// Returns true if the wait was abandoned.
+template <int N, typename F>
+__device__ __forceinline__ void look16(uint4 (&f)[N], const bf16_t* base, F off) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) f[q] = *reinterpret_cast<const uint4*>(base + off(q));
+}
+template <int N, typename F>
+__device__ __forceinline__ bool settle16(uint4 (&f)[N], const bf16_t* base, F off, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_there16<N>(f)) return gave_up;
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
+        if (all_there16<N>(f)) return false;
+        __builtin_amdgcn_s_sleep(1);
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
+
+// Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
+// was abandoned.  Looking at the data straight away saves this round trip when the first look succeeds or the
+// data is little; with eight or more fragments a wavefront, loads that come too early cost more than they save and leave
+// stale lines behind (three layers, T = 21, forward / rest of the step in us, straight against probe first: H = 512, 8
+// sequences 132 / 234 and 151 / 205 -- four fragments forward, sixteen backward --, H = 1024, 30 sequences 248 / 566 and
+// 221 / 461, H = 128, 8 sequences 100 / 138 and 117 / 153).
+constexpr int PROBE_FROM = 8;
+__device__ __forceinline__ bool probe_producers16(const bf16_t* p, bool mine, unsigned* abort_word, unsigned long long limit) {
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        const unsigned v = mine ? ld_coh_u32(reinterpret_cast<const unsigned*>(p)) : 0u;
+        if (__all(!has_sentinel_half(v))) return false;
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
 
 }  // namespace blstm

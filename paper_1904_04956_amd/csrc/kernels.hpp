@@ -71,9 +71,7 @@ struct RecBwdArgs {
 bool rec_supported(int H);                  // whether the persistent kernels take this width
 bool rec_takes(int T, int B, int H);        // ... and whether they are the faster path for so many frames and sequences
 bool rec_fenced(int H);                     // whether they are built with the fenced protocol too
-int rec_groups(int H, int tiles, int per_cu = 1);   // batch groups per direction for so many 32-row tiles and workgroups per CU
-// Whether launch_rec_fwd for this width honours RecFwdArgs::fill.
-bool rec_fwd_fills(int H);
+int rec_groups(int H, int tiles);           // batch groups per direction for so many 32-row tiles
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.
 hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
 hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
@@ -82,6 +80,11 @@ hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bo
 bool rec_small_supported(int B, int H);
 hipError_t launch_rec_small_fwd(const RecFwdArgs& a, hipStream_t st, bool* launched);
 hipError_t launch_rec_small_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched);
+// The same on 16-row tiles (recurrent_tile.hip; nbg and tiles_per_group set by the launcher, a counter per direction and tile):
+// units of a workgroup, 32 or 64, or 0 if these kernels do not take the shape.
+int rec_tile_units(int B, int H);
+hipError_t launch_rec_tile_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
+hipError_t launch_rec_tile_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
 
 // ---- persistent recurrent kernels in float (H up to 1024) ------------------------------
 struct Rec32FwdArgs {

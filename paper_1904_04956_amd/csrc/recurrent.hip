@@ -41,35 +41,6 @@ __device__ __forceinline__ f32x16_t mfma_bf16(const uint4& a, const uint4& b, f3
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// ---- FENCED protocol ----------------------------------------------------------------------------
-// Waits until *cnt >= target; thread 0 polls.  One barrier inside.  Returns true (to every thread) if the
-// wait was abandoned.
-__device__ __forceinline__ bool wait_counter(unsigned* cnt, unsigned target, unsigned* abort_word, unsigned long long limit_ticks) {
-    int gave_up = 0;
-    if (threadIdx.x == 0) {
-        const unsigned long long t0 = wall_clock64();
-        unsigned it = 0;
-        while (ld_coh_u32(cnt) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            if ((++it & 63u) == 0) {
-                if (ld_coh_u32(abort_word) != 0) { gave_up = 1; break; }
-                if (wall_clock64() - t0 > limit_ticks) {
-                    __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    gave_up = 1;
-                    break;
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    return __syncthreads_or(gave_up) != 0;
-}
-// After the workgroup's stores: the barrier orders them before thread 0's agent-scope release.
-__device__ __forceinline__ void signal_counter(unsigned* cnt) {
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // ---- SENTINEL protocol --------------------------------------------------------------------------
 // Bounded wait of one wave.  `probe` points, for the lanes with probing set, at one element of each
 // producer's block: a cheap first look before the full loads.  Returns true if the wait was
@@ -179,14 +150,11 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 // tiles of both) like any other row, no row's result depends on another row's, and only the row-major stores leave them
 // out.  No load is predicated: with one branch per loaded row a ragged batch took 119 us a layer where 256 whole rows
 // took 76 (H = 512, 173 sequences; the backward kernel 104 against 83).
-// MULTI: a workgroup owns several batch tiles (tiles_per_group > 1); only then is there a next item
-// whose exchanged chunks can be loaded ahead, and only then are registers set aside for them.
+// MULTI: a workgroup owns several batch tiles (tiles_per_group > 1).
 // PADDED: the layer is narrower than the kernel's NW * KW cells (any multiple of 8): U_h counts as zero beyond it, the
 // exchange holds whole slices of 32 units, and the units beyond the layer come out as zeros that are not stored row-major.
-// LEAN: few enough registers for two workgroups per CU: one set of inputs, asked for behind the item's own operand, no look
-// ahead at the next operand, half of the accumulators and of the partial sums at a time.
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
-__global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
+template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
+__global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
@@ -198,23 +166,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
-    // This workgroup's share of the region to fill (the widest slice of U_h leaves no register for it: KW <= 128 only):
-    // words [fill_pos, fill_end) of its share, a few words per thread and item.
-    constexpr bool FILLS = KW <= 128;
-    const unsigned long long fill_per_wg = (FILLS && a.fill) ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
-    const unsigned long long fill_begin = min(a.fill_words, (unsigned long long)blockIdx.x * fill_per_wg);
-    uint4* const fill_base = static_cast<uint4*>(a.fill) + fill_begin;                     // uniform
-    const unsigned fill_end = (unsigned)(min(a.fill_words, fill_begin + fill_per_wg) - fill_begin);   // (a share is far below 2^32 words)
-    unsigned fill_pos = threadIdx.x;
-    const int fill_per_item = ntl > 0 ? (int)((fill_per_wg + (unsigned long long)(64 * NW) * (T * ntl) - 1) / ((unsigned long long)(64 * NW) * (T * ntl))) : 0;
-    auto fill_some = [&](int words) __attribute__((always_inline)) {
-        if constexpr (FILLS)
-            for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill_base[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    };
-    if (ntl == 0) {                                      // no batch tile of its own: only its share of the fill
-        if constexpr (FILLS) while (fill_pos < fill_end) fill_some(1 << 20);
-        return;
-    }
+    if (ntl == 0) return;                                // no batch tile of its own
 
     // this wavefront's slice of U_h as B-fragments: unit row l32 of each gate, 8 consecutive k per lane
     uint4 bfrag[4][KSTEPS];
@@ -275,17 +227,13 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
     // in the other, so nothing is copied (a copy would have to wait for loads issued a moment before).
     float ax0[EPT][4], cp0[EPT], ax1[EPT][4], cp1[EPT];
-    if constexpr (!LEAN) issue_inputs(0, ax0, cp0);
+    issue_inputs(0, ax0, cp0);
     // Waited for here, once: the compiler places its waits for the worst path into the loop, and with these
     // loads still in flight on the way in, that path would make every item wait for its freshly issued loads.
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0) (expcnt and lgkmcnt left alone)
     float ccarry[EPT];                                   // one tile per workgroup: its cell state of the frame before
 #pragma unroll
     for (int e = 0; e < EPT; ++e) ccarry[e] = 0.0f;
-    // With several batch tiles per workgroup the next item's h was written a whole frame ago: its
-    // chunks are loaded while this item computes (checked for the sentinel like any other load).
-    uint4 apre[MULTI && !LEAN ? KSTEPS : 1];
-    bool have_pre = false;
     // The row-major outputs of an item (c, the gates, h for the next layer) are not on the frame-to-frame path:
     // they wait in registers until the next item has issued its loads of the exchanged h, and go out behind them.
     struct Tail { int t, b0; bool have, xok; float cn[EPT]; uint2 g[EPT]; uint2 hq; } tail;
@@ -310,7 +258,6 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         const int xrow_ = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane_ >> 5) + ((lane_ >> 3) & 3);
         const unsigned xcol_ = (unsigned)(u * 32 + 8 * ((lane_ >> 1) & 3) + 4 * (lane_ & 1));
         if (tail.xok && (!PADDED || xcol_ < (unsigned)H)) *reinterpret_cast<uint2*>(yb + ((unsigned)xrow_ * (unsigned)(2 * H) + (unsigned)(d * H) + xcol_)) = tail.hq;
-        fill_some(fill_per_item);
     };
     auto do_item = [&](const int item, const float (&ax)[EPT][4], const float (&cpl)[EPT], float (&axn)[EPT][4],
                        float (&cpn)[EPT]) __attribute__((always_inline)) {
@@ -331,34 +278,10 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             if (SENTINEL) {
                 // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
                 const bf16_t* probe = hb + xoff(PADDED ? min(wave * (KW / 32) + lane, NU - 1) * 32 + 31 : wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
-                bool got = false, gu = false;
-                if constexpr (MULTI && !LEAN) {
-                    if (have_pre) {
-#pragma unroll
-                        for (int q = 0; q < KSTEPS; ++q) afrag[q] = apre[q];
-                        got = all_written<KSTEPS>(afrag);
-                    }
-                }
-                if (!got) {
-                    // Straight for the data: this wavefront's loads queue behind its own stores of the item
-                    // before, whose acknowledgements take about as long as the other workgroups' h takes to
-                    // arrive, so the first look nearly always finds everything.  If not: the cheap probe, then
-                    // cache-bypassing loads (the first ones may have left lines with sentinels in the L1).
-                    // (The widest slice has no registers for two attempts: probe first, then the data.)
-                    if constexpr (KW <= 128) {
-                        load_chunks_cached<KSTEPS>(afrag, hp, lastp);
-                        flush_tail();
-                        if (!all_written<KSTEPS>(afrag)) {
-                            gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
-                            asm volatile("" ::: "memory");
-                            load_chunks<KSTEPS>(afrag, hp, lastp);
-                        }
-                    } else {
-                        gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
-                        asm volatile("" ::: "memory");
-                        load_chunks_cached<KSTEPS>(afrag, hp, lastp);
-                    }
-                }
+                // (no registers for two attempts: probe first, then the data)
+                const bool gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
+                asm volatile("" ::: "memory");
+                load_chunks_cached<KSTEPS>(afrag, hp, lastp);
                 if (ensure_written<KSTEPS>(afrag, hp, lastp, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             } else {
                 if (wait_counter(cnt + i, (unsigned)(NU * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
@@ -366,76 +289,51 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                 for (int q = 0; q < KSTEPS; ++q)
                     afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
-            if constexpr (LEAN && KW < 128) issue_inputs(item, axn, cpn);    // (in flight behind the products; the widest slice has no registers for them yet)
-            // (two gates at a time where registers are short)
-            constexpr int GP = LEAN ? 2 : 4;
+            f32x16_t acc[4];
 #pragma unroll
-            for (int g0 = 0; g0 < 4; g0 += GP) {
-            f32x16_t acc[GP];
-#pragma unroll
-            for (int g = 0; g < GP; ++g)
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[g][e] = 0.0f;
 #pragma unroll
             for (int q = 0; q < KSTEPS; ++q)
 #pragma unroll
-                for (int g = 0; g < GP; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g0 + g][q], acc[g]);
-            if (g0 == 0) {
-            have_pre = false;
-            if constexpr (MULTI && !LEAN && SENTINEL && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
-                const int n2 = (item + 1) / ntl, i2 = (item + 1) - n2 * ntl;
-                const int tp2 = d ? T - n2 : n2 - 1;
-                const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
-                const bf16_t* hb2 = a.hx + ((size_t)(tp2 * 2 + d) * NT + (b02 >> 5)) * XH;
-                load_chunks_cached<KSTEPS>(apre, hb2 + ohp, lastp);
-                have_pre = true;
-            }
-            }
+                for (int g = 0; g < 4; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g][q], acc[g]);
             // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
 #pragma unroll
-            for (int g = 0; g < GP; ++g)
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
                 for (int rq = 0; rq < 4; ++rq)
-                    l4[((wave * 4 + g0 + g) * 4 + rq) * 64 + lane] =
+                    l4[((wave * 4 + g) * 4 + rq) * 64 + lane] =
                         make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
-            }
-            if constexpr (LEAN && KW == 128) issue_inputs(item, axn, cpn);
             if (SENTINEL) lds_barrier(); else __syncthreads();
             // all partial sums of this thread's rows are read before any is added: the reads then
             // overlap instead of each waiting for its LDS round trip
             static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
-            // (in two rounds where registers are short)
-            constexpr int WR = LEAN && KW == 128 ? NW / 2 : NW;
+            float4 part[NW][4][EPT / 4];
 #pragma unroll
-            for (int w0 = 0; w0 < NW; w0 += WR) {
-                float4 part[WR][4][EPT / 4];
+            for (int w2 = 0; w2 < NW; ++w2)
 #pragma unroll
-                for (int w2 = 0; w2 < WR; ++w2)
+                for (int g = 0; g < 4; ++g)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
+                    for (int e4 = 0; e4 < EPT / 4; ++e4) part[w2][g][e4] = l4[((w2 * 4 + g) * 4 + (EPT / 4) * wave + e4) * 64 + lane];
 #pragma unroll
-                        for (int e4 = 0; e4 < EPT / 4; ++e4) part[w2][g][e4] = l4[(((w0 + w2) * 4 + g) * 4 + (EPT / 4) * wave + e4) * 64 + lane];
+            for (int w2 = 0; w2 < NW; ++w2)
 #pragma unroll
-                for (int w2 = 0; w2 < WR; ++w2)
+                for (int g = 0; g < 4; ++g)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
-#pragma unroll
-                        for (int e4 = 0; e4 < EPT / 4; ++e4) {
-                            const float4 v = part[w2][g][e4];
-                            sum[4 * e4][g] += v.x; sum[4 * e4 + 1][g] += v.y; sum[4 * e4 + 2][g] += v.z; sum[4 * e4 + 3][g] += v.w;
-                        }
-                if (WR < NW) asm volatile("" ::: "memory");
-            }
+                    for (int e4 = 0; e4 < EPT / 4; ++e4) {
+                        const float4 v = part[w2][g][e4];
+                        sum[4 * e4][g] += v.x; sum[4 * e4 + 1][g] += v.y; sum[4 * e4 + 2][g] += v.z; sum[4 * e4 + 3][g] += v.w;
+                    }
         }
         // (The next item's inputs come from HBM, and a CU's vector memory pipeline returns data in order: issued
         // before the barrier above they would sit in front of another wavefront's loads of the exchanged h and
         // add their latency to the frame-to-frame path.  They are issued below, once h has gone out.)
         flush_tail();                                     // at the latest here: the loads issued below may read what it stores
-        if constexpr (LEAN) if (n == 0) issue_inputs(item, axn, cpn);
         float cp[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : cpl[e];
-        if (KW > 128 && item + 1 < nitems) issue_inputs(item + 1, axn, cpn);   // (widest slice: registers are short later on)
+        if (item + 1 < nitems) issue_inputs(item + 1, axn, cpn);   // (registers are short later on)
         // cell arithmetic; h goes out first because it is all the other workgroups wait for
         float gi[EPT], gf[EPT], gg[EPT], go[EPT], cn[EPT], hn[EPT];
         bf16_t* hxb = a.hx + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XH;
@@ -469,7 +367,6 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             bf16_t* xp = hxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u + (xcol & 7u));
             if (SENTINEL) st_coh_8B(xp, hq); else *reinterpret_cast<uint2*>(xp) = hq;
         }
-        if (KW <= 128 && !LEAN && item + 1 < nitems) issue_inputs(item + 1, axn, cpn);
         if (SENTINEL) lds_barrier();                     // frees the LDS buffer for the next item
         else signal_counter(cnt + i);                    // barrier inside: same role
         // row-major outputs (h for the next layer, c and the gates for the backward pass): kept for flush_tail
@@ -483,27 +380,17 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
 #pragma unroll
         for (int e = 0; e < EPT; ++e) ccarry[e] = cn[e];
     };
-    if constexpr (LEAN) {
-        for (int item = 0; item < nitems; ++item) do_item(item, ax0, cp0, ax0, cp0);
-    } else if constexpr (KW <= 128) {
-        for (int item = 0; item < nitems; item += 2) {
-            do_item(item, ax0, cp0, ax1, cp1);
-            if (item + 1 < nitems) do_item(item + 1, ax1, cp1, ax0, cp0);
-        }
-    } else {
-        // (the widest slice of U_h leaves no room for the loop body twice: one body, and a copy at its end)
-        for (int item = 0; item < nitems; ++item) {
-            do_item(item, ax0, cp0, ax1, cp1);
+    // (the slice of U_h leaves no room for the loop body twice: one body, and a copy at its end)
+    for (int item = 0; item < nitems; ++item) {
+        do_item(item, ax0, cp0, ax1, cp1);
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) {
+        for (int e = 0; e < EPT; ++e) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) ax0[e][g] = ax1[e][g];
-                cp0[e] = cp1[e];
-            }
+            for (int g = 0; g < 4; ++g) ax0[e][g] = ax1[e][g];
+            cp0[e] = cp1[e];
         }
     }
     flush_tail();
-    if constexpr (FILLS) while (fill_pos < fill_end) fill_some(1 << 20);   // (whatever rounding left over)
 }
 
 // ------------------------------------------------------------------------------ backward
@@ -599,8 +486,6 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) dccarry[e] = 0.0f;
     ccarry[0] = cfirst.x; ccarry[1] = cfirst.y; ccarry[2] = cfirst.z; ccarry[3] = cfirst.w;
-    uint4 apre[MULTI ? 8 : 1];                           // first slab of the next item, loaded ahead (several tiles only)
-    bool have_pre = false;
     // NaN once this wave has abandoned a wait, or from the start if the abort word is already raised: added to
     // every dE/da it writes
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
@@ -638,40 +523,17 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 // first pair of a slab (a slab beyond the layer repeats the last pair), and the last pair counted from it
                 auto slab = [&](int sl) { return (PADDED ? min(sl * 8, lastp) : sl * 8) * XPAIR; };
                 auto left = [&](int sl) { return PADDED ? max(lastp - sl * 8, 0) : 8; };
-                bool got = false, gu = false;
-                if constexpr (MULTI) {
-                    if (have_pre) {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) afrag[0][q] = apre[q];
-                        got = all_written<8>(afrag[0]);
-                    }
-                }
-                if (!got) {
-                    // (straight for the data, the probe only if the first look fails: see the forward kernel)
-                    load_chunks_cached<8>(afrag[0], ap, lastp);
-                    if (!all_written<8>(afrag[0])) {
-                        gu = wait_probe(probe, lane < 4 * KW / 32, a.abort_word, a.limit_ticks);
-                        asm volatile("" ::: "memory");
-                        load_chunks<8>(afrag[0], ap, lastp);
-                    }
+                bool gu = false;
+                // (straight for the data, the probe only if the first look fails)
+                load_chunks_cached<8>(afrag[0], ap, lastp);
+                if (!all_written<8>(afrag[0])) {
+                    gu = wait_probe(probe, lane < 4 * KW / 32, a.abort_word, a.limit_ticks);
+                    asm volatile("" ::: "memory");
+                    load_chunks<8>(afrag[0], ap, lastp);
                 }
 #pragma unroll
                 for (int sl = 0; sl < KSTEPS / 8; ++sl) {
                     if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + slab(sl + 1), left(sl + 1));
-                    else {
-                        have_pre = false;
-                        if constexpr (MULTI && KW == 128) if (ntl >= 2 && item + 1 < nitems) {
-                            const int ni2 = (item + 1) / ntl, i2 = (item + 1) - ni2 * ntl;
-                            const int n2 = T - 1 - ni2;
-                            if (n2 < T - 1) {
-                                const int tn2 = d ? T - 2 - n2 : n2 + 1;
-                                const int b02 = (gm.bg * a.tiles_per_group + i2) * 32;
-                                const bf16_t* ab2 = a.dax + ((size_t)(tn2 * 2 + d) * NT + (b02 >> 5)) * XA;
-                                load_chunks_cached<8>(apre, ab2 + oap, lastp);
-                                have_pre = true;
-                            }
-                        }
-                    }
                     gu = ensure_written<8>(afrag[sl & 1], ap + slab(sl), left(sl), gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[sl & 1][q], bfrag[sl * 8 + q], acc);
@@ -718,7 +580,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         float cthis[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cthis[e] = !MULTI ? ccarry[e] : curc[e];
-        if (KW > 128 && item + 1 < nitems) issue_inputs(item + 1, nxt);
+        if (item + 1 < nitems) issue_inputs(item + 1, nxt);
         float dcf[EPT];
         unsigned dav[EPT][2];                             // (i, f) and (g, o) as bf16 pairs: kept for the row-major copy below
         bf16_t* dxb = a.dax + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XA;
@@ -768,7 +630,6 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             if (SENTINEL) { st_coh_16B(pa, cga); st_coh_16B(pb, cgb); }
             else { *reinterpret_cast<uint4*>(pa) = cga; *reinterpret_cast<uint4*>(pb) = cgb; }
         }
-        if (KW <= 128 && item + 1 < nitems) issue_inputs(item + 1, nxt);
         if (SENTINEL) lds_barrier();
         else signal_counter(cnt + i);
         // row-major dE/da for the weight- and input-gradient products, and the carried dE/dc
@@ -784,16 +645,9 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) { dccarry[e] = dcf[e]; ccarry[e] = curcp[e]; }
     };
-    if constexpr (KW <= 128) {
-        for (int item = 0; item < nitems; item += 2) {
-            do_item(item, in0, in1);
-            if (item + 1 < nitems) do_item(item + 1, in1, in0);
-        }
-    } else {
-        for (int item = 0; item < nitems; ++item) {
-            do_item(item, in0, in1);
-            in0 = in1;
-        }
+    for (int item = 0; item < nitems; ++item) {
+        do_item(item, in0, in1);
+        in0 = in1;
     }
 }
 
@@ -846,64 +700,43 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
+template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
+    constexpr int NW = 4;
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
-    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
+    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
-template <int NW, int KW, bool S, bool FULL, bool MULTI, bool PADDED>
+template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
+    constexpr int NW = 4;
     const size_t lds = (size_t)NW * 4 * 64 * 16 + (size_t)NW * 2048 + (size_t)NW * 512;   // partial sums; regrouping of dE/da, 2 KB per wavefront; spreading dy, 512 bytes per wavefront
     return launch_resident<rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {
-    if (a.tiles_per_group == 1) return run_one<4, KW, S, FULL, false, PADDED>(a, grid, st, launched);
-    if constexpr (std::is_same_v<A, RecFwdArgs> && S && (KW < 128 || (KW == 128 && !PADDED))) {
-        // Several tiles per workgroup, forward: twice the groups with two workgroups per CU, one of which computes while the
-        // other waits for its operand.  Two layers, T = 21, us, one per CU against two: H = 512, 1000 sequences 927 / 852,
-        // 2048 sequences 1831 / 1601; H = 256, 600 sequences 350 / 300.  Not where every workgroup has two tiles that would
-        // become one: nothing is left to overlap (512 sequences of 512 cells 496 / 572).  The backward kernel, whose time
-        // is the traffic of its operand, gains nothing (rest of the step 2947 / 3040).
-        A b = a;
-        const int nu = (a.H + 31) / 32, tiles = (a.B + 31) / 32;
-        if (a.tiles_per_group > 2 || 4 * tiles <= 7 * a.nbg) {
-            b.nbg = rec_groups(a.H, tiles, 2);
-            b.tiles_per_group = (tiles + b.nbg - 1) / b.nbg;
-            hipError_t e = run_one<4, KW, S, false, true, PADDED, true>(b, grid_groups(b.nbg) * nu, st, launched);
-            if (e != hipSuccess || *launched) return e;
-        }
-    }
-    return run_one<4, KW, S, FULL, true, PADDED>(a, grid, st, launched);
-}
-// A width that is the kernel's own.
-template <int KW, typename A>
-hipError_t run_exact(const A& a, bool sentinel, int grid, hipStream_t st, bool* launched) {
-    if (sentinel) return a.B % 32 == 0 ? run_multi<KW, true, true, false>(a, grid, st, launched) : run_multi<KW, true, false, false>(a, grid, st, launched);
-    return a.B % 32 == 0 ? run_multi<KW, false, true, false>(a, grid, st, launched) : run_multi<KW, false, false, false>(a, grid, st, launched);
+    return a.tiles_per_group == 1 ? run_one<KW, S, FULL, false, PADDED>(a, grid, st, launched) : run_one<KW, S, FULL, true, PADDED>(a, grid, st, launched);
 }
 template <typename A>
 hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) {
     *launched = false;
     const int grid = grid_groups(a.nbg) * ((a.H + 31) / 32);
-    switch (a.H) {
-        case 128: return run_exact<32>(a, sentinel, grid, st, launched);
-        case 256: return run_exact<64>(a, sentinel, grid, st, launched);
-        case 512: return run_exact<128>(a, sentinel, grid, st, launched);
-        case 1024: return run_exact<256>(a, sentinel, grid, st, launched);
+    if (a.H == 1024) {
+        if (sentinel) return a.B % 32 == 0 ? run_multi<256, true, true, false>(a, grid, st, launched) : run_multi<256, true, false, false>(a, grid, st, launched);
+        return a.B % 32 == 0 ? run_multi<256, false, true, false>(a, grid, st, launched) : run_multi<256, false, false, false>(a, grid, st, launched);
     }
-    if (!sentinel || !rec_supported(a.H)) return hipSuccess;   // (padded widths: sentinel protocol only)
+    if (!sentinel || a.H <= 512 || !rec_supported(a.H)) return hipSuccess;   // (padded widths: sentinel protocol only)
 #define BLSTM_PADDED(KW) if (a.H <= 4 * KW) return run_multi<KW, true, false, true>(a, grid, st, launched)
-    BLSTM_PADDED(32); BLSTM_PADDED(64); BLSTM_PADDED(96); BLSTM_PADDED(128); BLSTM_PADDED(160); BLSTM_PADDED(192); BLSTM_PADDED(224); BLSTM_PADDED(256);
+    BLSTM_PADDED(160); BLSTM_PADDED(192); BLSTM_PADDED(224); BLSTM_PADDED(256);
 #undef BLSTM_PADDED
     return hipSuccess;
 }
 
 }  // namespace
 
-// Supported widths: multiples of 8 up to 1024, always on four wavefronts that split the contraction (four batch rows per
-// thread in every variant).  128, 256, 512 and 1024 have kernels of their own; the others run padded to the next multiple
-// of 128 (H = 320, 50 sequences: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
+// Supported widths: multiples of 8 up to 1024.  The kernels of this file run those above 512 cells with more sequences than
+// recurrent_tile.hip takes there, on four wavefronts that split the contraction (four batch rows per thread in every variant).
+// 1024 has kernels of its own; the others run padded to the next multiple of 128 (H = 320, 50 sequences, when these kernels ran
+// it: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
 // Padded widths above 512 only up to 3072 sequences: beyond, the tiles a workgroup walks backward cost more than the forward
 // pass gains (one layer, 21 frames, both passes, us, persistent / launches per frame: H = 576, B = 2048 3084 / 3709,
 // 3072 4687 / 4582, 4096 6686 / 5935; H = 768, 3072 6252 / 6774, 4096 8893 / 8322; H = 504, 16384 15990 / 19181).  And not
@@ -913,13 +746,10 @@ bool rec_takes(int T, int B, int H) { return rec_supported(H) && (rec_fenced(H) 
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
 // Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than
 // one workgroup per CU (32).
-int rec_groups(int H, int tiles, int per_cu) {
-    const int most = 4 * (32 * per_cu / ((H + 31) / 32));
+int rec_groups(int H, int tiles) {
+    const int most = 4 * (32 / ((H + 31) / 32));
     return tiles < most ? tiles : most;
 }
-// Whether the forward kernel for this width also fills RecFwdArgs::fill (the wider ones have no register to spare).
-bool rec_fwd_fills(int H) { return H <= 512; }
-
 hipError_t launch_fill_u32(unsigned* p, int n, unsigned v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);

@@ -22,63 +22,6 @@ constexpr int NWF = 4;
 constexpr int PAIR = 4 * 16 * 8;                         // elements of 32 columns of a tile (1 KB)
 constexpr int PS = 20;                                   // floats per row of a partial tile
 
-__device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-template <int N>
-__device__ __forceinline__ bool all_there(const uint4 (&f)[N]) {
-    unsigned m = 0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
-    return __all(!has_sentinel_half(m));
-}
-// f[q] = the 16 bytes at base + off(q): ordinary loads first, past the caches until every element is written.
-// Returns true if the wait was abandoned.
-template <int N, typename F>
-__device__ __forceinline__ void look(uint4 (&f)[N], const bf16_t* base, F off) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) f[q] = *reinterpret_cast<const uint4*>(base + off(q));
-}
-template <int N, typename F>
-__device__ __forceinline__ bool settle(uint4 (&f)[N], const bf16_t* base, F off, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_there<N>(f)) return gave_up;
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
-        if (all_there<N>(f)) return false;
-        __builtin_amdgcn_s_sleep(1);
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
-}
-
-// Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
-// was abandoned.  Looking at the data straight away saves this round trip when the first look succeeds or the
-// data is little; with eight or more fragments a wavefront, loads that come too early cost more than they save and leave
-// stale lines behind (three layers, T = 21, forward / rest of the step in us, straight against probe first: H = 512, 8
-// sequences 132 / 234 and 151 / 205 -- four fragments forward, sixteen backward --, H = 1024, 30 sequences 248 / 566 and
-// 221 / 461, H = 128, 8 sequences 100 / 138 and 117 / 153).
-constexpr int PROBE_FROM = 8;
-__device__ __forceinline__ bool probe_producers(const bf16_t* p, bool mine, unsigned* abort_word, unsigned long long limit) {
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-        const unsigned v = mine ? ld_coh_u32(reinterpret_cast<const unsigned*>(p)) : 0u;
-        if (__all(!has_sentinel_half(v))) return false;
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
-}
 // Lane 2 q + i probes the last two elements that slice i of block q writes.
 constexpr int LAST_OF_SLICE = 128 + 15 * 8 + 6;
 
@@ -156,11 +99,11 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
             uint4 af[NQ];
             bool gu = false;
             if constexpr (NQ >= PROBE_FROM) {
-                gu = probe_producers(base + min(wave * NQ + (lane >> 1), blocks - 1) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
+                gu = probe_producers16(base + min(wave * NQ + (lane >> 1), blocks - 1) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
                 asm volatile("" ::: "memory");
             }
-            look<NQ>(af, base, off);
-            if (settle<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            look16<NQ>(af, base, off);
+            if (settle16<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             f32x4_t acc[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g)
@@ -254,11 +197,11 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
             uint4 af[NQ];
             bool gu = false;
             if constexpr (NQ >= PROBE_FROM) {
-                gu = probe_producers(base + (wave * blocks + min(lane >> 1, blocks - 1)) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
+                gu = probe_producers16(base + (wave * blocks + min(lane >> 1, blocks - 1)) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
                 asm volatile("" ::: "memory");
             }
-            look<NQ>(af, base, off);
-            if (settle<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            look16<NQ>(af, base, off);
+            if (settle16<NQ>(af, base, off, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             f32x4_t acc[2];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { acc[0][e] = 0.0f; acc[1][e] = 0.0f; }

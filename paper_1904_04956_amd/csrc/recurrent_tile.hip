@@ -1,0 +1,474 @@
+// Persistent recurrent kernels (bf16) on 16-row batch tiles: all T frames of one layer, both directions, in one launch.
+//
+// A workgroup of four wavefronts has 16 NB units (32 or 64) of its 16-row tiles.  Against 32 units of 32 rows
+// (recurrent.hip) the slice of 64 units reads half of the operand bytes per cell (backward 64 KB a frame instead of 128 KB at
+// 512 cells, the longest part of its frame), and half as many workgroups wait on each other.
+//
+// Forward: MFMA 16x16x32 with U_h as the first operand, its rows ordered so that a lane gets the four gates of NB
+// neighbouring units of one batch row: the cell arithmetic follows the products in the same registers, without partial
+// sums and without regrouping, and a_x, h and the records move in one access of NB values each.  Every wavefront needs the
+// whole of h: each checks its quarter of the fragments, stages them in LDS, multiplies them from registers, and reads the
+// other quarters behind the barrier.  Backward: the wavefronts split the contraction by the producing units, their partial
+// sums meet in LDS in the same (unit, row) order, and an exchange between lane groups (v_permlane*_swap) leaves each
+// lane with eight units of one gate: 16-byte stores.  The number of vector-memory instructions a frame is what the layout
+// is made for: one costs a CU's memory pipeline about the same whatever its width.
+//
+// Exchange copies: [frame][direction][16-row tile]([gate])[8 columns][16 rows][8], a fragment of 32 columns is one contiguous
+// KB.  A lane's units lie in one group of eight and H is a multiple of 8: they exist or not together, and what lies beyond H
+// is neither written nor read (the last columns repeat there, against zero weights).  Rows beyond the batch repeat its last
+// row and are not stored row-major.  Saved activations are per-lane records in the order of the units.
+// Both protocols, bounded waits and failures as in recurrent.hip.
+//
+// us a layer of 21 frames, forward / backward, these kernels against 32 units of 32 rows: 512 cells, 128 sequences 47 / 59
+// against 69 / 76, 173 62 / 73 against 77 / 83, 256 68 / 79 against 80 / 85, 300 126 / 136 against 158 / 146, 2048 (16
+// rows x 64 units eight times a frame) 508 / 570 against 505 / 615; 1024 cells, 64 sequences 65 / 77 against 93 / 112.
+// What bounds a frame of 256 sequences (2.1 GHz, cycles of a wavefront): forward 1900 for the exchange, 500 until the other
+// wavefronts have staged theirs, 950 products, 1100 cells (ten transcendentals each), 1600 issuing what the memory takes at
+// 5.3 TB/s (38 KB a workgroup and frame); backward 1400 issuing 64 KB of loads, 900 for the last of them, 1400 products,
+// 1500 partial sums and waiting for each other, 300 cells, 1700 issuing stores and the next inputs.
+#include "exchange.hpp"
+#include "kernels.hpp"
+#include "residency.hpp"
+
+namespace blstm {
+namespace {
+
+constexpr int NW = 4;                                    // wavefronts
+constexpr int CHUNK = 16 * 8;                            // elements of eight columns of a tile
+
+// NB floats, and as many bf16, as one access
+template <int NB> struct Packs;
+template <> struct Packs<2> { typedef float2 F; typedef unsigned W; };
+template <> struct Packs<4> { typedef float4 F; typedef uint2 W; };
+__device__ __forceinline__ float part(const float2& v, int b) { return b ? v.y : v.x; }
+__device__ __forceinline__ float part(const float4& v, int b) { return b == 0 ? v.x : b == 1 ? v.y : b == 2 ? v.z : v.w; }
+__device__ __forceinline__ float2 pack(const float (&v)[2]) { return make_float2(v[0], v[1]); }
+__device__ __forceinline__ float4 pack(const float (&v)[4]) { return make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ unsigned pack(const unsigned (&v)[1]) { return v[0]; }
+__device__ __forceinline__ uint2 pack(const unsigned (&v)[2]) { return make_uint2(v[0], v[1]); }
+__device__ __forceinline__ unsigned word(unsigned v, int) { return v; }
+__device__ __forceinline__ unsigned word(const uint2& v, int k) { return k ? v.y : v.x; }
+
+// Returns true if the wait was abandoned.  A look that came too early is followed by the cheap probe of its producers,
+// then by another look past the caches.
+template <int N, typename F>
+__device__ __forceinline__ bool settle_probe(uint4 (&f)[N], const bf16_t* base, F off, const bf16_t* probe, bool probing, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_there16<N>(f)) return gave_up;
+    for (;;) {
+        if (probe_producers16(probe, probing, abort_word, limit)) return true;
+#pragma unroll
+        for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
+        if (all_there16<N>(f)) return false;
+    }
+}
+
+// Keeps three quarters of the weights in accumulation registers, which the products read as well as the others, and the
+// others free: left to itself the compiler fills those with weights and reads the staged h one fragment at a time.
+template <int NB, int KQ>
+__device__ __forceinline__ void park(uint4 (&w)[NB][KQ]) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    if constexpr (NB * KQ > 16) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): one wait for all of them
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int q = KQ / 4; q < KQ; ++q) {
+                u4 v = __builtin_bit_cast(u4, w[b][q]);
+                asm volatile("" : "+a"(v));
+                w[b][q] = __builtin_bit_cast(uint4, v);
+            }
+    }
+}
+
+// Workgroup -> (direction, group of tiles, slice); ids are dealt round-robin to the eight XCDs, each of which gets whole groups.
+struct Spot { int d, first, ntl, u; };                   // first tile and number of tiles (0: a group that does not exist)
+__device__ __forceinline__ Spot spot(int nu, int nbg, int per_group, int ntiles) {
+    const int slot = (int)blockIdx.x >> 3, group = (slot / nu) * 8 + ((int)blockIdx.x & 7);
+    Spot p;
+    p.u = slot % nu; p.d = group / nbg;
+    p.first = (group - p.d * nbg) * per_group;
+    p.ntl = group < 2 * nbg ? min(per_group, ntiles - p.first) : 0;
+    return p;
+}
+
+// ------------------------------------------------------------------------------ forward
+// Width up to 32 KQ.  MULTI: several tiles a workgroup, walked one after the other in every frame; the next item's
+// operand, written a frame ago, is then loaded under an item's products.
+template <int NB, int KQ, bool SENTINEL, bool MULTI>
+__global__ __launch_bounds__(64 * NW, 1) void tile_rec_fwd_kernel(RecFwdArgs a) {
+    typedef typename Packs<NB>::F F;
+    typedef typename Packs<NB>::W W;
+    constexpr int FR = KQ / NW;                          // fragments a wavefront stages
+    extern __shared__ uint4 hs[];                        // [2][KQ][64]
+    const int T = a.T, B = a.B, H = a.H;
+    const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
+    const Spot sp = spot(nu, a.nbg, a.tiles_per_group, NT);
+    const int d = sp.d, ntl = MULTI ? sp.ntl : min(sp.ntl, 1);
+    // this workgroup's share of the region to fill, some words every item behind its stores
+    const unsigned long long share = a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
+    const unsigned long long first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
+    uint4* const fill = static_cast<uint4*>(a.fill) + first;
+    const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
+    unsigned fill_pos = threadIdx.x;
+    auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
+    if (ntl <= 0) { fill_some(1 << 30); return; }
+    const int nitems = T * ntl;
+    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * nitems - 1) / ((unsigned long long)(64 * NW) * nitems));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units
+    // row l16 of block b: gate l16 % 4 of unit NB (l16 / 4) + b; the wavefront's own fragments of h first
+    uint4 wf[NB][KQ];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+            const int unit = unit0 + NB * (l16 >> 2) + b, k = (q + wave * FR) % KQ * 32 + 8 * lq;
+            wf[b][q] = unit < H && k < H ? *reinterpret_cast<const uint4*>(a.uh[d] + (size_t)((l16 & 3) * H + unit) * H + k) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    park(wf);
+    unsigned off[FR];
+#pragma unroll
+    for (int i = 0; i < FR; ++i) off[i] = (unsigned)(min(4 * (wave * FR + i) + lq, chunks - 1) * CHUNK + l16 * 8);
+    auto where = [&](int i) { return off[i]; };
+    // one lane per eight columns of those fragments: the last word its producer writes there
+    const unsigned probe = (unsigned)(min(4 * wave * FR + min(lane, 4 * FR - 1), chunks - 1) * CHUNK + CHUNK - 2);
+    // this lane's cells: units j .. j + NB - 1 of row l16
+    const int j = unit0 + NB * lq, jc = min(j, H - NB);
+    const bool mine = j < H;
+    const size_t RT = (size_t)(H / NB) * 16;             // lanes' records of a (frame, direction, tile)
+    const size_t rec0 = (size_t)(jc / NB) * 16 + l16;
+    struct In { F ax[4], cp; };
+    auto inputs = [&](int item, In& in) __attribute__((always_inline)) {
+        const int n = item / ntl, tile = sp.first + item - n * ntl;
+        const int t = d ? T - 1 - n : n, tp = d ? T - n : n - 1;
+        const float* p = a.ax + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 8 * H + d * 4 * H + jc;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) in.ax[g] = *reinterpret_cast<const F*>(p + (size_t)g * H);
+        if constexpr (MULTI) {
+            in.cp = F{};
+            if (n > 0) in.cp = reinterpret_cast<const F*>(a.c)[((size_t)(tp * 2 + d) * NT + tile) * RT + rec0];
+        }
+    };
+    auto operand = [&](int item) {                       // of an item behind the first frame
+        const int n = item / ntl, tile = sp.first + item - n * ntl;
+        return a.hx + ((size_t)((d ? T - n : n - 1) * 2 + d) * NT + tile) * chunks * CHUNK;
+    };
+    In in0, in1;
+    inputs(0, in0);
+    float c[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) c[b] = 0.0f;
+    uint4 ahead[MULTI ? FR : 1];
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    auto do_item = [&](const int item, const In& cur, In& nxt, uint4* hb) __attribute__((always_inline)) {
+        const int n = item / ntl, tile = sp.first + item - n * ntl;
+        const int t = d ? T - 1 - n : n, row = tile * 16 + l16;
+        const bool look_ahead = SENTINEL && MULTI && item + 1 < nitems && item + 1 >= ntl;
+        f32x4_t acc[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
+        if (n > 0) {
+            const bf16_t* base = operand(item);
+            uint4 f[FR];
+            if constexpr (!SENTINEL) if (wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if constexpr (SENTINEL && MULTI) {
+#pragma unroll
+                for (int i = 0; i < FR; ++i) f[i] = ahead[i];
+            } else look16<FR>(f, base, where);
+            if constexpr (SENTINEL) if (settle_probe<FR>(f, base, where, base + probe, lane < 4 * FR, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+#pragma unroll
+            for (int i = 0; i < FR; ++i) hb[(wave * FR + i) * 64 + lane] = f[i];
+#pragma unroll
+            for (int q = 0; q < FR; ++q)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][q], f[q], acc[b]);
+            __builtin_amdgcn_sched_barrier(0);
+            lds_barrier();                               // one an item: the buffer is doubled
+            if constexpr (MULTI) if (look_ahead) look16<FR>(ahead, operand(item + 1), where);
+            // the others in groups of FR, a group read while the one before is multiplied
+            uint4 h[2][FR];
+            auto read = [&](int g, uint4 (&v)[FR]) __attribute__((always_inline)) {
+                const int slot = (wave + g) % NW * FR;   // (uniform)
+#pragma unroll
+                for (int i = 0; i < FR; ++i) v[i] = hb[(slot + i) * 64 + lane];
+            };
+            read(1, h[1]);
+#pragma unroll
+            for (int g = 1; g < NW; ++g) {
+                if (g + 1 < NW) read(g + 1, h[(g + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < FR; ++i)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][g * FR + i], h[g & 1][i], acc[b]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (MULTI) {
+            if (look_ahead) look16<FR>(ahead, operand(item + 1), where);
+        }
+        float gi[NB], gf[NB], gg[NB], go[NB];
+        unsigned hw[NB / 2];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            gi[b] = fast_sigmoid(part(cur.ax[0], b) + acc[b][0]);
+            gf[b] = fast_sigmoid(part(cur.ax[1], b) + acc[b][1]);
+            gg[b] = fast_tanh(part(cur.ax[2], b) + acc[b][2]);
+            go[b] = fast_sigmoid(part(cur.ax[3], b) + acc[b][3]);
+            c[b] = gf[b] * (MULTI ? part(cur.cp, b) : c[b]) + gi[b] * gg[b];
+            const unsigned h = coh_bf16(go[b] * fast_tanh(c[b]) + poison);
+            hw[b >> 1] = b & 1 ? hw[b >> 1] | (h << 16) : h;
+        }
+        if (mine) {
+            bf16_t* x = a.hx + (((size_t)(t * 2 + d) * NT + tile) * chunks + (j >> 3)) * CHUNK + l16 * 8 + (j & 7);
+            if constexpr (NB == 4) st_coh_8B(x, pack(hw));
+            else __hip_atomic_store(reinterpret_cast<unsigned*>(x), pack(hw), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
+        // What follows is not on the frame-to-frame path.  With one tile it also keeps the next look at h from coming too
+        // early: moved behind that look, or between the products, it cost 7 to 40 us a layer (512 cells, 128 and 256 sequences).
+        const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
+        if constexpr (MULTI) if (mine) reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);   // (before the next item's inputs: of a group's only tile they read it)
+        if (item + 1 < nitems) inputs(item + 1, nxt);
+        if (mine) {
+            uint4* g4 = reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2) + rec0;
+#pragma unroll
+            for (int k = 0; k < NB / 2; ++k)
+                g4[k * RT] = make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1]));
+            if constexpr (!MULTI) reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);
+            if (row < B) *reinterpret_cast<W*>(a.y + ((size_t)t * B + row) * 2 * H + d * H + j) = pack(hw);
+        }
+        fill_some(fill_each);
+    };
+    for (int item = 0; item < nitems; item += 2) {
+        do_item(item, in0, in1, hs);
+        if (item + 1 < nitems) do_item(item + 1, in1, in0, hs + KQ * 64);
+    }
+    fill_some(1 << 30);
+}
+
+// ------------------------------------------------------------------------------ backward
+// Each wavefront contracts KQ / 4 blocks of 32 columns of every gate, SL fragments of dE/da in flight ahead of the products.
+template <int NB, int KQ, bool SENTINEL, bool MULTI>
+__global__ __launch_bounds__(64 * NW, 1) void tile_rec_bwd_kernel(RecBwdArgs a) {
+    typedef typename Packs<NB>::F F;
+    typedef typename Packs<NB>::W W;
+    constexpr int BW = KQ / 4;
+    constexpr int SL = 4, NSL = KQ / SL;
+    extern __shared__ float4 ps[];                       // [2][NW][NB][64]
+    const int T = a.T, B = a.B, H = a.H;
+    const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
+    const Spot sp = spot(nu, a.nbg, a.tiles_per_group, NT);
+    const int d = sp.d, ntl = MULTI ? sp.ntl : min(sp.ntl, 1);
+    if (ntl <= 0) return;
+    const int nitems = T * ntl;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int q0 = wave * BW;
+    uint4 wf[NB][KQ];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+            const int unit = sp.u * 16 * NB + b * 16 + l16, k = (q0 + q % BW) * 32 + 8 * lq;
+            wf[b][q] = unit < H && k < H ? *reinterpret_cast<const uint4*>(a.uht[d] + (size_t)unit * 4 * H + (q / BW) * H + k) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    auto off = [&](int q) { return (unsigned)(((q / BW) * chunks + min(4 * (q0 + q % BW) + lq, chunks - 1)) * CHUNK + l16 * 8); };
+    const unsigned probe = (unsigned)((3 * chunks + min(4 * q0 + min(lane, KQ - 1), chunks - 1)) * CHUNK + CHUNK - 2);
+    const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units; the lane's: j .. j + NB - 1 of row l16
+    const int j = unit0 + NB * lq, jc = min(j, H - NB);
+    const size_t RT = (size_t)(H / NB) * 16, rec0 = (size_t)(jc / NB) * 16 + l16;
+    const size_t XT = (size_t)4 * chunks * CHUNK;        // exchange elements of a (frame, direction, tile)
+    struct In { W dy; uint4 g[NB / 2]; F c, cp, dc; };
+    auto inputs = [&](int item, In& in) __attribute__((always_inline)) {
+        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
+        const int t = d ? T - 1 - n : n, tp = d ? T - n : n - 1;
+        in.dy = *reinterpret_cast<const W*>(a.dy + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 2 * H + d * H + jc);
+        const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
+        const uint4* g4 = reinterpret_cast<const uint4*>(a.gates) + rec * (NB / 2) + rec0;
+#pragma unroll
+        for (int k = 0; k < NB / 2; ++k) in.g[k] = g4[k * RT];
+        in.cp = F{};
+        if (n > 0) in.cp = reinterpret_cast<const F*>(a.c)[((size_t)(tp * 2 + d) * NT + tile) * RT + rec0];
+        if constexpr (MULTI) {                           // (with one tile these two stay in registers)
+            in.c = reinterpret_cast<const F*>(a.c)[rec + rec0];
+            in.dc = F{};
+            if (ni > 0) in.dc = reinterpret_cast<const F*>(a.dc)[((size_t)d * NT + tile) * RT + rec0];
+        }
+    };
+    auto operand = [&](int item) {                       // of an item behind the first frame
+        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
+        return a.dax + ((size_t)((d ? T - 2 - n : n + 1) * 2 + d) * NT + tile) * XT;
+    };
+    In in0, in1;
+    inputs(0, in0);
+    float c[NB], dcn[NB];                                // one tile: this frame's cell state (then the one before's), carried dE/dc
+    {
+        F cl = F{};
+        if constexpr (!MULTI) cl = reinterpret_cast<const F*>(a.c)[((size_t)((d ? 0 : T - 1) * 2 + d) * NT + sp.first) * RT + rec0];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) { c[b] = part(cl, b); dcn[b] = 0.0f; }
+    }
+    uint4 ahead[MULTI ? SL : 1];
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    auto do_item = [&](const int item, const In& cur, In& nxt, float4* pt) __attribute__((always_inline)) {
+        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
+        const int t = d ? T - 1 - n : n, row = tile * 16 + l16;
+        const bool look_ahead = SENTINEL && MULTI && item + 1 < nitems && item + 1 >= ntl;
+        float dh[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) dh[b] = 0.0f;
+        if (ni > 0) {
+            const bf16_t* base = operand(item);
+            uint4 f[2][SL];
+            bool gu = false;
+            if constexpr (!SENTINEL) gu = wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * ni), a.abort_word, a.limit_ticks);
+            if constexpr (SENTINEL && MULTI) {
+#pragma unroll
+                for (int q = 0; q < SL; ++q) f[0][q] = ahead[q];
+            } else look16<SL>(f[0], base, off);
+            f32x4_t acc[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < NSL; ++s) {
+                if (s + 1 < NSL) look16<SL>(f[(s + 1) & 1], base, [&](int q) { return off((s + 1) * SL + q); });
+                else if constexpr (MULTI) { if (look_ahead) look16<SL>(ahead, operand(item + 1), off); }
+                if constexpr (SENTINEL) gu = settle_probe<SL>(f[s & 1], base, [&](int q) { return off(s * SL + q); }, base + probe, lane < KQ, gu, a.abort_word, a.limit_ticks);
+#pragma unroll
+                for (int q = 0; q < SL; ++q)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][s * SL + q], f[s & 1][q], acc[b]);
+            }
+            if (gu) poison = __builtin_nanf("");
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pt[(wave * NB + b) * 64 + lane] = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
+            lds_barrier();                               // one an item: the partial sums are double-buffered
+            // block b of the partial sums has units 16 b + 4 lq + e of row l16
+            F v[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if constexpr (NB == 4) v[w] = pt[(w * NB + wave) * 64 + lane];
+                else v[w] = reinterpret_cast<const F*>(pt + (w * NB + (wave >> 1)) * 64)[(((wave & 1) * 2 + (lq >> 1)) * 16 + l16) * 2 + (lq & 1)];
+            }
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) dh[b] += part(v[w], b);
+        } else if constexpr (MULTI) {
+            if (look_ahead) look16<SL>(ahead, operand(item + 1), off);
+        }
+        unsigned da[4][NB / 2];                          // a gate's units
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint4 g = cur.g[b >> 1];
+            const unsigned gif = b & 1 ? g.z : g.x, ggo = b & 1 ? g.w : g.y, dyw = word(cur.dy, b >> 1);
+            const float gi = bf2f((bf16_t)(gif & 0xFFFFu)), gf = bf2f((bf16_t)(gif >> 16));
+            const float gg = bf2f((bf16_t)(ggo & 0xFFFFu)), go = bf2f((bf16_t)(ggo >> 16));
+            const float dht = dh[b] + bf2f((bf16_t)(b & 1 ? dyw >> 16 : dyw & 0xFFFFu)) + poison;
+            const float tc = fast_tanh(MULTI ? part(cur.c, b) : c[b]), cp = part(cur.cp, b);
+            const float dc = dht * go * (1.0f - tc * tc) + (MULTI ? part(cur.dc, b) : dcn[b]);
+            const unsigned v[4] = {coh_bf16(dc * gg * gi * (1.0f - gi)), coh_bf16(dc * cp * gf * (1.0f - gf)),
+                                   coh_bf16(dc * gi * (1.0f - gg * gg)), coh_bf16(dht * tc * go * (1.0f - go))};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) da[k][b >> 1] = b & 1 ? da[k][b >> 1] | (v[k] << 16) : v[k];
+            dcn[b] = dc * gf; c[b] = cp;
+        }
+        // Eight units of one gate a lane.  NB = 2: word g of lane group lq becomes word lq of lane group g (gate lq, the
+        // wavefront's units).  NB = 4: neighbouring groups trade halves (gates 2 (lq % 2) and the next, units 8 (lq / 2) ..).
+        uint4 o[NB / 2];
+        if constexpr (NB == 2) {
+            const auto s02 = __builtin_amdgcn_permlane32_swap(da[0][0], da[2][0], false, false), s13 = __builtin_amdgcn_permlane32_swap(da[1][0], da[3][0], false, false);
+            const auto t01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false), t23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+            o[0] = make_uint4(t01[0], t01[1], t23[0], t23[1]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const auto lo = __builtin_amdgcn_permlane16_swap(da[k][0], da[k + 2][0], false, false), hi = __builtin_amdgcn_permlane16_swap(da[k][1], da[k + 2][1], false, false);
+                o[k] = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+            }
+        }
+        const int gate0 = NB == 2 ? lq : 2 * (lq & 1), u8 = NB == 2 ? unit0 : unit0 + 8 * (lq >> 1);
+        bf16_t* x = a.dax + ((size_t)(t * 2 + d) * NT + tile) * XT + (size_t)(gate0 * chunks + (u8 >> 3)) * CHUNK + l16 * 8;
+        if (u8 < H) {
+#pragma unroll
+            for (int k = 0; k < NB / 2; ++k) st_coh_16B(x + (size_t)k * chunks * CHUNK, o[k]);
+        }
+        if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
+        if constexpr (MULTI) if (j < H) reinterpret_cast<F*>(a.dc)[((size_t)d * NT + tile) * RT + rec0] = pack(dcn);   // (as in the forward kernel)
+        if (item + 1 < nitems) inputs(item + 1, nxt);
+        if (u8 < H && row < B) {
+            bf16_t* p = a.da + ((size_t)t * B + row) * 8 * H + (size_t)(d * 4 + gate0) * H + u8;
+#pragma unroll
+            for (int k = 0; k < NB / 2; ++k) *reinterpret_cast<uint4*>(p + (size_t)k * H) = o[k];
+        }
+    };
+    for (int item = 0; item < nitems; item += 2) {
+        do_item(item, in0, in1, ps);
+        if (item + 1 < nitems) do_item(item + 1, in1, in0, ps + NW * NB * 64);
+    }
+}
+
+// The groups of tiles a direction is cut into: as many as leave every XCD, which gets whole groups, one workgroup a CU.
+struct Cut { int nbg, per_group, grid, real; };
+Cut cut(int B, int H, int units) {
+    const int nu = (H + units - 1) / units, tiles = (B + 15) / 16, most = 4 * (32 / nu);
+    Cut c;
+    c.per_group = (tiles + most - 1) / most;
+    c.nbg = (tiles + c.per_group - 1) / c.per_group;
+    c.grid = (2 * c.nbg + 7) / 8 * 8 * nu;
+    c.real = 2 * c.nbg * nu;
+    return c;
+}
+
+template <int NB, int KQ, bool S, bool MULTI>
+hipError_t run(const RecFwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
+    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S, MULTI>>(a, 64 * NW, (size_t)2 * KQ * 64 * 16, c.grid, c.real, st, launched);
+}
+template <int NB, int KQ, bool S, bool MULTI>
+hipError_t run(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
+    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S, MULTI>>(a, 64 * NW, (size_t)2 * NW * NB * 64 * 16, c.grid, c.real, st, launched);
+}
+template <int NB, int KQ, typename A>
+hipError_t run_width(const A& a, const Cut& c, bool sentinel, hipStream_t st, bool* launched) {
+    if constexpr (NB == 4) {                             // (several tiles a workgroup: of 64 units only)
+        if (c.per_group > 1 && sentinel) return run<NB, KQ, true, true>(a, c, st, launched);
+        if constexpr (KQ != 12) if (c.per_group > 1) return run<NB, KQ, false, true>(a, c, st, launched);
+    }
+    if (sentinel) return run<NB, KQ, true, false>(a, c, st, launched);
+    if constexpr (KQ == 4 || KQ == 8 || KQ == 16 || KQ == 32) return run<NB, KQ, false, false>(a, c, st, launched);
+    return hipSuccess;
+}
+template <typename A>
+hipError_t launch(A a, bool sentinel, hipStream_t st, bool* launched) {
+    *launched = false;
+    const int units = rec_tile_units(a.B, a.H);
+    if (units == 0 || !(sentinel || rec_fenced(a.H))) return hipSuccess;
+    const Cut c = cut(a.B, a.H, units);
+    a.nbg = c.nbg; a.tiles_per_group = c.per_group;
+#define BLSTM_TILE(NB, KQ) if (units == 16 * NB && a.H <= 32 * KQ) return run_width<NB, KQ>(a, c, sentinel, st, launched)
+    BLSTM_TILE(2, 4); BLSTM_TILE(2, 8); BLSTM_TILE(2, 12); BLSTM_TILE(2, 16); BLSTM_TILE(2, 20); BLSTM_TILE(2, 24); BLSTM_TILE(2, 28); BLSTM_TILE(2, 32);
+    BLSTM_TILE(4, 4); BLSTM_TILE(4, 8); BLSTM_TILE(4, 12); BLSTM_TILE(4, 16);
+#undef BLSTM_TILE
+    return hipSuccess;
+}
+
+}  // namespace
+
+// Slices of 32 units while that leaves every workgroup a CU and a tile of its own, else of 64: half of the operand's bytes
+// per cell, but their weights fit the registers up to 512 cells only.  Beyond 512 cells several tiles of 32 units a
+// workgroup lose to recurrent.hip's 32 x 32 (1024 cells, 512 sequences 450 / 545 us a layer against 348 / 387; 128 sequences
+// 121 / 145 against 96 / 115).
+int rec_tile_units(int B, int H) {
+    if (!rec_supported(H)) return 0;
+    if (cut(B, H, 32).per_group == 1) return 32;
+    return H <= 512 ? 64 : 0;
+}
+hipError_t launch_rec_tile_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched) { return launch(a, sentinel, st, launched); }
+hipError_t launch_rec_tile_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched) { return launch(a, sentinel, st, launched); }
+
+}  // namespace blstm

@@ -297,6 +297,31 @@ def test_two_workgroups_per_cu_forward_bf16(dims):
     check_step(dims, 1, seed=89, theta_scale=1.0)
 
 
+@pytest.mark.parametrize("dims,syncs", [
+    (dict(T=3, B=65, D=8, H=512, L=1, P=0, V=20), (0, 1)),    # slices of 32 units; one row in the last tile
+    (dict(T=3, B=129, D=8, H=512, L=2, P=0, V=20), (0, 1)),   # of 64 units
+    (dict(T=4, B=257, D=8, H=512, L=1, P=0, V=20), (0, 1)),   # two tiles a workgroup, one in the last group
+    (dict(T=3, B=513, D=8, H=264, L=1, P=0, V=20), (1,)),     # the same with eight units in the last slice
+    (dict(T=4, B=1050, D=8, H=512, L=1, P=0, V=20), (0, 1)),  # five tiles a workgroup
+    (dict(T=3, B=600, D=8, H=72, L=2, P=0, V=20), (1,)),
+    (dict(T=2, B=40, D=8, H=1024, L=1, P=0, V=20), (0, 1)),   # the widest slices
+    (dict(T=1, B=300, D=8, H=512, L=1, P=0, V=20), (1,)),     # nothing exchanged
+])
+def test_kernels_on_sixteen_row_tiles_bf16(dims, syncs):
+    # the same problem under each protocol: against the oracle (2e-2: the storage type), and bit for bit between them
+    grads = []
+    for sync in syncs:
+        check_step(dims, 1, seed=90, theta_scale=1.0, recurrent_sync=sync)
+        from paper_1904_04956_amd.harness import Learner
+        dm, theta, x, labels = make_problem(dims, 1, 90, 1.0)
+        lrn = Learner(mode=1, recurrent_sync=sync, **dims)
+        lrn.set_theta(theta); lrn.set_batch(x, labels)
+        lrn.calgrad(); lrn.check_status()
+        grads.append(lrn.grad_numpy().copy())
+        lrn.close()
+    assert all(np.array_equal(g, grads[0]) for g in grads)
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims,mode", [
     (dict(T=5, B=40, D=30, H=101, L=2, P=37, V=90), 1),     # every width misaligned
