@@ -42,11 +42,12 @@ struct GemmDesc {
 
 // How a product is run: the tile shape, and into how many K ranges it is split.
 enum GemmTile { GEMM_TILE_128 = 0,        // 128x128, every element type and shape
-                GEMM_TILE_256 = 1,        // 256x256, float operands of large products
-                GEMM_TILE_256X128 = 2 };  // 256x128, bf16 operands loaded straight into LDS
+                GEMM_TILE_256 = 1,        // 256x256, bf16, few tiles and a long contraction
+                GEMM_TILE_256X128 = 2,    // 256x128, bf16
+                GEMM_TILE_64 = 3 };       // 64x64, float, where larger tiles fill the CUs unevenly
 struct GemmPlan {
     int tile;                 // a GemmTile
-    bool deep;                // 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)
+    bool deep;                // bf16, 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)
     int splits;
     size_t partial_bytes;     // scratch the split needs (0 when splits == 1)
 };
@@ -57,7 +58,7 @@ size_t noalloc_partial_bytes(int M, int N, int K, DType in_type);
 
 // Validates nothing (the caller's shapes are trusted); returns the launch status.
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream);
-// n independent products of the A^T B form (atrans and btrans, bf16 operands, float result, optional row sums, no
+// n independent products of the A^T B form (atrans and btrans, operands of one type, float result, optional row sums, no
 // bias, one segment): those the grouped kernel can take (gemm_group_ok) in one launch, the others one launch each.  A
 // grouped launch never splits along K and uses no scratch.
 bool gemm_group_ok(const GemmDesc* d, int n);

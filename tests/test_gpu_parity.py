@@ -152,6 +152,16 @@ def test_edges_of_tiles_and_slabs(dims, mode):
     check_step(dims, mode, seed=4960, theta_scale=2.0)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=4, B=64, D=64, H=64, L=2, P=64, V=192),          # whole 64x64 tiles
+    dict(T=5, B=13, D=36, H=68, L=1, P=20, V=52),           # one row and four columns beyond one
+    dict(T=21, B=61, D=132, H=260, L=1, P=132, V=4003),     # 1281 frames: both tiles, dz split along K, rows of logits padded
+    dict(T=8, B=128, D=128, H=256, L=2, P=128, V=2048),     # whole 128x128 tiles, grouped weight gradients of more than 256 tiles
+])
+def test_float_products_on_both_tiles(dims):
+    check_step(dims, 0, seed=4962, theta_scale=2.0)
+
+
 def test_edges_of_the_large_tiles_bf16():
     # the logits on 256x128 tiles, dz on 256x256 split along a contraction of 25001, dW_s in the grouped launch
     check_step(dict(T=21, B=150, D=40, H=32, L=1, P=256, V=25001), 1, seed=4961)
