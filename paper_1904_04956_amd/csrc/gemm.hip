@@ -25,14 +25,20 @@ int fast_flags(const void* p, long long ld, long long stride, int batch, bool ro
 // ---- direct-mode kernels: bf16 operands, unguarded, forms X W^T, dA W and dA^T X -------------------------------
 // variant 0: 128x128 tile, two LDS buffers, two workgroups per CU; 1: 128x128, three buffers (launches of at most one
 // workgroup per CU); 2: 256x128 tile, one buffer, fragments in registers, two workgroups per CU; 3: 256x256 tile on
-// eight wavefronts, two buffers, one workgroup per CU (the dA W form only: the softmax layer's input gradient).
+// eight wavefronts, two buffers, one workgroup per CU (the dA W form only: the softmax layer's input gradient).  X W^T and
+// dA W also 4: 64x64, three buffers, three workgroups per CU; 5: 128x64, three buffers, two; 6: 128x128, one buffer, three.
 template <typename TO, bool AT, bool BT, bool RS, int MODE>
 hipError_t launch_direct_rs(const Params& P, int variant, dim3 grid, hipStream_t stream) {
     if (variant == 2) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 2, MODE, RS, 1>(P, grid, stream);
     if constexpr (!AT && BT && !RS) {
         if (variant == 3) return launch_kernel<bf16_t, TO, AT, BT, 4, 2, 4, MODE, false, 2>(P, grid, stream);
     }
-    if (variant == 3) return hipErrorInvalidValue;
+    if constexpr (!AT) {
+        if (variant == 4) return launch_kernel<bf16_t, TO, AT, BT, 1, 1, 2, MODE, false, 3>(P, grid, stream);
+        if (variant == 5) return launch_kernel<bf16_t, TO, AT, BT, 2, 1, 2, MODE, false, 3>(P, grid, stream);
+        if (variant == 6) return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, MODE, false, 1>(P, grid, stream);
+    }
+    if (variant >= 3) return hipErrorInvalidValue;
     if constexpr (AT && BT) {
         if (variant == 1) return launch_kernel<bf16_t, TO, AT, BT, 2, 2, 2, MODE, RS, 3>(P, grid, stream);
     }
@@ -88,7 +94,8 @@ int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n, bool di
     return EDGE;
 }
 
-constexpr int kTileM[4] = {128, 256, 256, 64}, kTileN[4] = {128, 256, 128, 64};
+constexpr int kTileM[6] = {128, 256, 256, 64, 128, 128}, kTileN[6] = {128, 256, 128, 64, 64, 128};
+constexpr int kDirectVariant[6] = {0, 3, 2, 4, 5, 6};     // of launch_direct (0 and 1: by GemmPlan::deep)
 
 GemmPlan make_plan(const GemmDesc& d, bool allow_r);
 
@@ -155,7 +162,7 @@ hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
         typedef decltype(to) T;
         if constexpr (sizeof(TI) == 4) return launch_f32(d, P, mode, direct, plan.tile, grid, stream);
         else if (!direct) return launch_staged<TI, T>(d, P, mode, grid, stream);
-        else return launch_direct<T>(d, P, mode, plan.tile == GEMM_TILE_256X128 ? 2 : plan.tile == GEMM_TILE_256 ? 3 : (plan.deep ? 1 : 0), grid, stream);
+        else return launch_direct<T>(d, P, mode, plan.tile == GEMM_TILE_128 && plan.deep ? 1 : kDirectVariant[plan.tile], grid, stream);
     };
     if (plan.splits == 1) return launch(TO{});
     const hipError_t e = launch(float{});                  // partial tiles are float whatever the output type
@@ -214,6 +221,20 @@ void plan_f32(const GemmDesc& d, bool direct, int Ne, int Nr, GemmPlan* p) {
     }
 }
 
+// Estimated time (us) of a slab of `tiles` bf16 tiles spread over the CUs.  64x64 with three buffers: three workgroups on a CU
+// hide most of each other's load latency, 0.34 us a slab alone and 0.225 of matrix-core and LDS time each when they do not; 128x64:
+// 0.53 and 0.37, two a CU; 128x128: 0.7, a third less where two share a CU.  Measured, us, 128x128 / 128x64 / 64x64 (X W^T, K = 1024):
+// 168 x 2048 twice 15.8 / 11.8 / 9.1, 5376 x 256 15.3 / 11.2 / 9.8, 1344 x 2048 twice 21.1 / 23.5 / 22.7; (dA W, K = 2048 twice)
+// 1050 x 640, K = 1280 33.3 / 24.0 / 16.7 (split in five: 17.3), 1344 x 1024 47.0 / 36.5 / 28.2, 2688 x 1024 48.4 / 39.8 /
+// 41.6, 3633 x 1024 51.2 / 45.0 / 56.9, 5376 x 1024 57.3 / 71.6 / 72.5.
+double bf16_slab(int tile, double tiles) {
+    const double x = tiles / 256.0;
+    auto most = [](double a, double b) { return a > b ? a : b; };
+    if (tile == GEMM_TILE_64) return most(0.34, 0.225 * x);
+    if (tile == GEMM_TILE_128X64) return x <= 2.0 ? most(0.53, 0.37 * x) : 1e9;
+    return x <= 1.0 ? 0.7 : 0.462 * (double)(long long)(x + 0.999999);
+}
+
 // How a product of this shape is run.  allow_r: the 256x128 direct tile may be chosen (bf16 operands in one of its forms).
 GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     GemmPlan p{GEMM_TILE_128, false, 1, 0};
@@ -229,8 +250,12 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         if (allow_r) {
             const long long tr = (long long)((d.M + 255) / 256) * ((Ne + 127) / 128) * batch;
             // Enough 256x128 tiles to put two on (nearly) every CU: the tile that moves 3/4 of the operand bytes of
-            // 128x128 per flop, and the only one whose loop keeps the matrix cores above half of their rate.
-            if (tr >= 480) { p.tile = GEMM_TILE_256X128; return p; }
+            // 128x128 per flop, and the only one whose loop keeps the matrix cores above half of their rate.  With a contraction
+            // of up to five slabs the first slab's latency and the output are most of a tile's time, and three workgroups of 128x128
+            // per CU overlap those better while there are not many rounds of tiles (us, 256x128 / 128x128, K = 256: 336 x 32000
+            // 15.8 / 14.4, 2688 x 32000 74.9 / 65.0, 3633 x 32000 106 / 110, 5376 x 32000 142 / 147; K = 264: 5376 x 2048 twice
+            // 36.9 / 31.8, 10752 x 4096 twice 116 / 103; K = 512: 5376 x 2048 twice 35.9 / 36.1).
+            if (tr >= 480) { p.tile = !d.atrans && ktot <= 320 && tr <= 3000 ? GEMM_TILE_128S : GEMM_TILE_256X128; return p; }
             // Fewer tiles than that but a long contraction next to a narrow output (the softmax layer's input gradient
             // at large batch): the same tile, split along K into the smallest number of parts that fills whole
             // rounds of 512 resident workgroups to 90 %, if every part keeps 64 slabs and the float partial tiles
@@ -275,33 +300,35 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         plan_f32(d, allow_r, Ne, Nr, &p);
         return p;
     }
+    int slabs = 0;
+    for (int s = 0; s < d.nseg; ++s) slabs += (d.seg[s].K + 63) / 64;
+    const bool any_tile = allow_r && !d.atrans;           // X W^T and dA W come in every tile
+    auto tiles = [&](int tile) { return (double)((d.M + kTileM[tile] - 1) / kTileM[tile]) * ((Ne + kTileN[tile] - 1) / kTileN[tile]) * batch; };
+    auto need_of = [&](int s) { return s > 1 ? (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float) : (size_t)0; };
+    const double tile_bytes = (double)batch * d.M * Nr * sizeof(float);
+    auto estimate = [&](int tile, int s) {
+        const double t = bf16_slab(tile, tiles(tile) * s) * ((slabs + s - 1) / s);
+        return s == 1 ? t : t + 4.5 + 2.0 * s * tile_bytes / 4e6;
+    };
+    int most = 1;
     if (d.long_parts) {
         if (!d.add && d.partial && d.nseg == 1 && t128 <= 256) {
-            const int slabs = (ktot + 63) / 64;
             const int s1 = parts_of(256, 8, t128, slabs, 8), s2 = parts_of(512, 8, t128, slabs, 64), s = s1 > s2 ? s1 : s2;
-            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
-            if (s > 1 && need <= d.partial_bytes) { p.splits = s; p.partial_bytes = need; }
+            if (s > 1 && need_of(s) <= d.partial_bytes) p.splits = s;
         }
-    } else if (!d.add && d.partial && t128 <= 1024) {
-        int slabs = 0;
-        for (int s = 0; s < d.nseg; ++s) slabs += (d.seg[s].K + 63) / 64;
-        const double tile_bytes = (double)batch * d.M * Nr * sizeof(float);
-        auto estimate = [&](int s) {
-            const double x = (double)t128 * s / 256.0, rounds = x <= 1.0 ? 1.0 : (double)(long long)(x + 0.999999);
-            const double part = (slabs + s - 1) / s;
-            const double t = 0.7 * part * (rounds > 1.0 ? 0.66 * rounds : 1.0);
-            return s == 1 ? t : t + 4.5 + 2.0 * s * tile_bytes / 4e6;
-        };
-        double best = estimate(1) * (11.0 / 12.0);
-        for (int s = 2; s <= 32 && slabs / s >= 4; ++s) {
-            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
-            if (need > d.partial_bytes || need > ((size_t)256 << 20)) break;
-            const double t = estimate(s);
-            if (t < best) { best = t; p.splits = s; p.partial_bytes = need; }
+    } else if (!d.add && d.partial && t128 <= 1024) most = 32;
+    double best = 0.0;
+    for (int s = p.splits, last = most > s ? most : s; s <= last; ++s) {
+        if (s > 1 && most > 1 && (slabs / s < 4 || need_of(s) > d.partial_bytes || need_of(s) > ((size_t)256 << 20))) break;
+        for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
+            if (tile != GEMM_TILE_128 && !any_tile) continue;
+            double t = estimate(tile, s);
+            if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.15;   // (336 x 256, K = 32000 in 32 parts: 25.6 against 28)
+            if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
         }
     }
     // at most one 128x128 workgroup per CU: run the loads further ahead (three LDS buffers, or four register sets)
-    p.deep = t128 * p.splits <= 256;
+    p.deep = p.tile == GEMM_TILE_128 && t128 * p.splits <= 256;
     return p;
 }
 

@@ -44,7 +44,9 @@ struct GemmDesc {
 enum GemmTile { GEMM_TILE_128 = 0,        // 128x128, every element type and shape
                 GEMM_TILE_256 = 1,        // 256x256, bf16, few tiles and a long contraction
                 GEMM_TILE_256X128 = 2,    // 256x128, bf16
-                GEMM_TILE_64 = 3 };       // 64x64, float, where larger tiles fill the CUs unevenly
+                GEMM_TILE_64 = 3,         // 64x64, where larger tiles leave CUs idle or fill them unevenly
+                GEMM_TILE_128X64 = 4,     // 128x64, bf16: too many tiles for 64x64, too few for 128x128
+                GEMM_TILE_128S = 5 };     // 128x128 with one LDS buffer, bf16, short contractions
 struct GemmPlan {
     int tile;                 // a GemmTile
     bool deep;                // bf16, 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)

@@ -17,8 +17,9 @@
 //            taking turns on the matrix cores (the workhorse: 3/4 of the operand bytes of 128x128
 //            per flop, and the vector-memory path of a CU, about 45 bytes per clock from L2, is what
 //            bounds these products); 128x128 with a ring of two or three buffers for products with
-//            too few large tiles; 256x256 on eight wavefronts for a handful of tiles with a very
-//            long contraction.
+//            too few large tiles, or with one buffer and three workgroups per CU for short contractions;
+//            64x64 and 128x64 with three buffers for products that leave CUs idle with larger tiles;
+//            256x256 on eight wavefronts for a handful of tiles with a very long contraction.
 //   staged   every other case (float operands, unaligned rows): global loads into
 //            registers two or four slabs ahead, LDS stores, double-buffered LDS.
 // Both run ragged shapes with their unguarded loops (EDGE below); the guarded loads are left for unaligned rows.
@@ -206,8 +207,11 @@ __device__ __forceinline__ void gload_rowfast_fast(uint4 (&r)[NCH], const char* 
 // feeds the matrix cores transposes it (ds_read_b64_tr_b16: sixteen lanes read a 4 x 16 block of 16-bit
 // elements, lane j of them receives column j).  No transposes in registers, plain 16-byte loads and stores.
 // CPR = chunks per k-row.  A thread owns chunk tid % CPR of the k-rows tid / CPR + 16 i.
-// Swizzle: the 32-byte pair of chunks p of k-row k sits at pair p ^ ((k & 3) << 1), so that the four k-rows
-// a group of sixteen lanes reads, and the neighbouring group's, fall on different banks.
+// Swizzle: the 32-byte pair of chunks p of k-row k sits at pair p ^ tr_swz(k), so that the four k-rows
+// a group of sixteen lanes reads, and the neighbouring group's, fall on different banks (a k-row of 64 rows is half of the
+// banks wide and has four pairs).
+template <int CPR>
+__device__ __forceinline__ int tr_swz(int k) { return CPR == 8 ? (k & 2) : (k & 3) << 1; }
 template <int NCH>
 __device__ __forceinline__ void gload_tr(uint4 (&r)[NCH], const char* base, long long pass_step, uint32_t voff) {
 #pragma unroll
@@ -419,19 +423,19 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     constexpr bool TRP = FAST && sizeof(TI) == 2;
     constexpr int CPR_A = BM / VEC, CPR_B = BN / VEC;   // 16-byte chunks per k-row
     static_assert(NS > 0 || !TRP || (NT / CPR_A == 16 && NT / CPR_B == 16), "a pass of loads covers sixteen k-rows");
-    auto tr_soff = [&](int cpr) { const int kt = tid / cpr, mc = tid % cpr; return kt * cpr + ((((mc >> 1) ^ ((kt & 3) << 1)) << 1) | (mc & 1)); };
-    const int soff_ta = tr_soff(CPR_A), soff_tb = tr_soff(CPR_B);
+    auto tr_soff = [&](auto cpr) { const int kt = tid / cpr, mc = tid % cpr; return kt * cpr + ((((mc >> 1) ^ tr_swz<cpr>(kt)) << 1) | (mc & 1)); };
+    const int soff_ta = tr_soff(std::integral_constant<int, CPR_A>{}), soff_tb = tr_soff(std::integral_constant<int, CPR_B>{});
     const uint32_t voff_ta = (uint32_t)((tid / CPR_A) * a0.ld * ES + (tid % CPR_A) * 16);
     const uint32_t voff_tb = (uint32_t)((tid / CPR_B) * b0.ld * ES + (tid % CPR_B) * 16);
     int troff_a[TM], troff_b[TN];
     {
-        const int g = lane >> 4, li = lane & 15, sw = (li >> 2) << 1;
+        const int g = lane >> 4, li = lane & 15, sw_a = tr_swz<CPR_A>(li >> 2), sw_b = tr_swz<CPR_B>(li >> 2);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            troff_a[i] = (8 * (g >> 1) + (li >> 2)) * (BM * 2) + (((wm * 2 * TM + 2 * i + (g & 1)) ^ sw) << 5) + (li & 3) * 8;
+            troff_a[i] = (8 * (g >> 1) + (li >> 2)) * (BM * 2) + (((wm * 2 * TM + 2 * i + (g & 1)) ^ sw_a) << 5) + (li & 3) * 8;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-            troff_b[j] = (8 * (g >> 1) + (li >> 2)) * (BN * 2) + (((wn * 2 * TN + 2 * j + (g & 1)) ^ sw) << 5) + (li & 3) * 8;
+            troff_b[j] = (8 * (g >> 1) + (li >> 2)) * (BN * 2) + (((wn * 2 * TN + 2 * j + (g & 1)) ^ sw_b) << 5) + (li & 3) * 8;
     }
 
     // Float operands whose non-contracted index is the fast one, direct mode: the slab as it lies in memory too, [k][row], and
@@ -482,7 +486,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
             const int jj = j * NWV + wv;
             if constexpr (AT) {
                 const int kt = (64 / CPR_A) * jj + lane / CPR_A, pos = lane % CPR_A;
-                int mc = FTR ? pos ^ (((kt >> 2) & 1) << 3) : ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                int mc = FTR ? pos ^ (((kt >> 2) & 1) << 3) : ((((pos >> 1) ^ tr_swz<CPR_A>(kt))) << 1) | (pos & 1);
                 if constexpr (MODE == EDGE) mc = min(mc, (P.M - 1 - row0) / VEC);
                 voa[j] = (unsigned)(kt * a0.ld * ES + mc * 16);
             } else {
@@ -496,7 +500,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
             const int jj = j * NWV + wv;
             if constexpr (BT) {
                 const int kt = (64 / CPR_B) * jj + lane / CPR_B, pos = lane % CPR_B;
-                int mc = FTR ? pos ^ (((kt >> 2) & 1) << 3) : ((((pos >> 1) ^ ((kt & 3) << 1))) << 1) | (pos & 1);
+                int mc = FTR ? pos ^ (((kt >> 2) & 1) << 3) : ((((pos >> 1) ^ tr_swz<CPR_B>(kt))) << 1) | (pos & 1);
                 if constexpr (MODE == EDGE) mc = min(mc, (P.N - 1 - col0) / VEC);
                 vob[j] = (unsigned)(kt * b0.ld * ES + mc * 16);
             } else {

@@ -162,6 +162,17 @@ def test_float_products_on_both_tiles(dims):
     check_step(dims, 0, seed=4962, theta_scale=2.0)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=4, B=32, D=64, H=64, L=2, P=64, V=192),          # whole 64x64 tiles, both operands of dx
+    dict(T=5, B=13, D=40, H=72, L=2, P=24, V=200),          # one row and eight columns beyond one
+    dict(T=21, B=50, D=128, H=320, L=2, P=0, V=1500),       # 64x64 input gradients, 128x64 logits; 1050 rows
+    dict(T=21, B=128, D=136, H=256, L=2, P=0, V=96),        # 128x64 input gradients
+    dict(T=7, B=200, D=264, H=64, L=1, P=136, V=32008),     # short contractions on 128x128 with one buffer, a part of a slab and of a tile
+])
+def test_bf16_products_on_the_smaller_tiles(dims):
+    check_step(dims, 1, seed=1965, theta_scale=1.0)
+
+
 def test_edges_of_the_large_tiles_bf16():
     # the logits on 256x128 tiles, dz on 256x256 split along a contraction of 25001, dW_s in the grouped launch
     check_step(dict(T=21, B=150, D=40, H=32, L=1, P=256, V=25001), 1, seed=4961)
