@@ -185,6 +185,12 @@ def test_softmax_row_widths_bf16(V):
     check_step(dict(T=2, B=5, D=8, H=8, L=1, P=8, V=V), 1, seed=80, theta_scale=4.0)
 
 
+@pytest.mark.parametrize("V", [4096, 4098, 16381, 32765, 32769])
+def test_softmax_row_widths_fp32(V):
+    # the edges of the register-resident forms (256, 512 and 1024 threads per row), padded rows, and a row too long for them
+    check_step(dict(T=2, B=5, D=8, H=8, L=1, P=8, V=V), 0, seed=80, theta_scale=4.0)
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims", [
     dict(T=4, B=64, D=128, H=128, L=2, P=128, V=512),       # whole 256x128 tiles everywhere: dW_s can join the grouped launch
