@@ -247,6 +247,27 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     int ktot = 0;
     for (int s = 0; s < d.nseg; ++s) ktot += d.seg[s].K;
     if (d.in_type == DT_BF16) {
+        // Few large tiles and a very long contraction (the softmax layer's input gradient, dA W form): the 256x256 tile, which
+        // moves half the operand bytes of 128x128 per flop and reads A once where N is 256.  Up to 64 tiles: split along K over
+        // up to one workgroup per CU, if every part keeps at least 24 slabs and the parts fill three quarters of the CUs; up to
+        // 239 (beyond, 256x128 tiles fill a round unsplit): in the smallest number of parts that fills whole rounds to 90 %, if every
+        // part keeps 64 slabs.  N = 256, K = 32000, us, the best split of 256x128 / 128x128 / 256x256: 2688 rows 82 / 78 / 73 (20
+        // parts), 5376 rows 125 / 131 / 115, 43008 rows 862 / 1018 / 755 (3 parts); 1344 rows (6 tiles) 128x128 45.
+        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 < 240 && Nr % 256 == 0) {
+            const int slabs = (d.seg[0].K + 63) / 64;
+            int s = 0;
+            if (t256 <= 64) {
+                s = parts_of(256, 24, t256, slabs, 24);
+                if (t256 * s < 192) s = 0;
+            } else {
+                for (int k = 2; k <= 8 && s == 0 && slabs / k >= 64; ++k) {
+                    const double rounds = (double)t256 * k / 256.0;
+                    if (rounds / (double)(long long)(rounds + 0.999999) >= 0.9) s = k;
+                }
+            }
+            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
+            if (s > 1 && need <= d.partial_bytes) { p.tile = GEMM_TILE_256; p.splits = s; p.partial_bytes = need; return p; }
+        }
         if (allow_r) {
             const long long tr = (long long)((d.M + 255) / 256) * ((Ne + 127) / 128) * batch;
             // Enough 256x128 tiles to put two on (nearly) every CU: the tile that moves 3/4 of the operand bytes of
@@ -272,17 +293,6 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
                     return p;
                 }
             }
-        }
-        // A handful of large tiles and a very long contraction (the softmax layer's input gradient, dA W form): the
-        // 256x256 tile, which moves half the operand bytes of 128x128 per flop, split along K over up to one
-        // workgroup per CU, if every part keeps at least 24 slabs and the parts fill three quarters of the CUs.
-        if (allow_r && d.nseg == 1 && !d.rowsum && d.partial && !d.atrans && d.btrans && t256 <= 64 && Nr % 256 == 0) {
-            const int slabs = (d.seg[0].K + 63) / 64;
-            int s = (int)(256 / t256);
-            if (s > 16) s = 16;
-            while (s > 1 && slabs / s < 24) --s;
-            const size_t need = (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float);
-            if (s > 1 && t256 * s >= 192 && need <= d.partial_bytes) { p.tile = GEMM_TILE_256; p.splits = s; p.partial_bytes = need; return p; }
         }
     }
     // Few output tiles, or a last round of them that is nearly empty: split K (both segments as one range of slabs) into the
@@ -323,7 +333,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
             if (tile != GEMM_TILE_128 && !any_tile) continue;
             double t = estimate(tile, s);
-            if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.15;   // (336 x 256, K = 32000 in 32 parts: 25.6 against 28)
+            if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.3;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
             if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
         }
     }
