@@ -63,6 +63,126 @@ hipError_t launch_direct(const GemmDesc& d, const Params& P, int mode, int varia
     return mode == WHOLE ? launch_direct_mode<TO, WHOLE>(d, P, variant, grid, stream) : launch_direct_mode<TO, EDGE>(d, P, variant, grid, stream);
 }
 
+// ---- X W^T with a contraction of up to four slabs and many rows (the logits) ------------------------------------------
+// A tile of such a product is over before its loads' latency and its output are: 5376 x 32000, K = 256 took 142 us where products
+// alone take 75 and the output 60.  Here a workgroup keeps one column tile's weights in registers for the whole contraction
+// (2 x 4 NK fragments a wavefront) and walks down the rows: only X is loaded, straight into a ring of four slabs that runs
+// on across the tiles, half of the operand bytes a tile.  The weights are the first operand of the products, so that a lane
+// has four neighbouring columns of one row; an exchange between the lane halves makes them eight, and the output leaves
+// from registers in 16-byte stores that nothing waits for.  K = 256, N = 32000, in the
+// step, us, 256x128 or one-buffer 128x128 tiles against this: 2688 rows 82 / 66, 3633 114 / 85, 5376 144 / 117, 10752 280 / 218.
+// Rows and columns beyond the matrix repeat the last ones and are dropped by the stores' range check, so that every wavefront
+// issues the same number of vector-memory instructions for every tile: the waits below count on it.
+template <int NK>
+__global__ __launch_bounds__(256, 2) void gemm_resident_kernel(Params P, int parts) {
+    constexpr int SLAB = 128 * CHUNKS, BK = 64, NL = 4, NSTORE = 8;   // 16-byte words of a slab; loads a wavefront and slab, stores a wavefront and tile
+    extern __shared__ uint4 smem[];                     // [4][SLAB], then the 128 columns' bias
+    float* bias_s = reinterpret_cast<float*>(smem + 4 * SLAB);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wv >> 1, wn = wv & 1, l32 = lane & 31, half = lane >> 5;
+    const int ct = (int)blockIdx.x % P.ntn, part = (int)blockIdx.x / P.ntn;
+    const int ntiles = (P.ntm - part + parts - 1) / parts;   // row tiles part, part + parts, ..: all workgroups go down the rows together
+    if (ntiles <= 0) return;
+    const int col0 = ct * 128;
+    const bf16_t* A = static_cast<const bf16_t*>(P.A[0].p);
+    const bf16_t* W = static_cast<const bf16_t*>(P.B[0].p);
+    const long long lda = P.A[0].ld, ldb = P.B[0].ld;
+    uint4 wf[2][4 * NK];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4 * NK; ++q)
+            wf[j][q] = *reinterpret_cast<const uint4*>(W + (long long)min(col0 + wn * 64 + j * 32 + l32, P.N - 1) * ldb + (2 * q + half) * 8);
+    if (tid < 128) bias_s[tid] = P.bias && col0 + tid < P.N ? ld_f(static_cast<const bf16_t*>(P.bias) + col0 + tid) : 0.0f;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+    const int total = ntiles * NK;
+    // slab s of this workgroup's sequence (the last one again beyond its end) into its slot; lane l of load j fetches the chunk that
+    // belongs at word 64 (4 j + wv) + l of the swizzled layout
+    auto issue = [&](int s) __attribute__((always_inline)) {
+        const int sc = min(s, total - 1), it = sc / NK, row0 = (part + it * parts) * 128;
+        const char* base = reinterpret_cast<const char*>(A + (long long)row0 * lda + (sc - it * NK) * BK);
+        const unsigned slot = lds0 + (unsigned)((s & 3) * SLAB * 16);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int r = 8 * (4 * j + wv) + (lane >> 3);
+            const unsigned voff = (unsigned)(min(r, P.M - 1 - row0) * (int)lda * 2 + (((lane & 7) ^ swz(r)) << 4));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(__builtin_amdgcn_readfirstlane(slot + (unsigned)((4 * j + wv) * 1024))), "v"(voff), "s"(base) : "memory");
+        }
+    };
+    const int arow = wm * 64 + l32;
+    int roff[CHUNKS / 2];
+#pragma unroll
+    for (int q = 0; q < CHUNKS / 2; ++q) roff[q] = arow * CHUNKS + ((2 * q + half) ^ swz(arow));
+    for (int s = 0; s < 3; ++s) issue(s);
+    for (int it = 0; it < ntiles; ++it) {
+        f32x16_t acc[2][2];                             // [columns][rows]
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NK; ++q) {
+            const int s = it * NK + q;
+            // Younger than slab s's loads: those of two slabs, and the stores of the tiles that ended in the three slabs since
+            // (in the first three slabs: of none, or of some, and waiting for fewer is only longer).
+            int ended = 0;
+#pragma unroll
+            for (int j = 1; j <= 3; ++j) ended += (q - j + 3 * NK) % NK == NK - 1 ? 1 : 0;
+            if (s < 3 || ended == 0) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(2 * NL) : "memory");
+            else if (ended == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(2 * NL + NSTORE) : "memory");
+            else if (ended == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(2 * NL + 2 * NSTORE) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(2 * NL + 3 * NSTORE) : "memory");
+            issue(s + 3);                               // (into the slot of slab s - 1, which every wavefront is done with)
+            const uint4* a_s = smem + (s & 3) * SLAB;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint4 x[2] = {a_s[roff[k]], a_s[roff[k ^ 2] + 32 * CHUNKS]};
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wf[j][4 * q + k]), __builtin_bit_cast(bf16x8_t, x[i]), acc[j][i], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // register e of a lane: row l32 of C's block i, column 8 (e / 4) + 4 half + e % 4 of block j
+        const int row0 = (part + it * parts) * 128;
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(static_cast<bf16_t*>(P.C) + (long long)row0 * P.ldc, 0, min(P.M - row0, 128) * (int)P.ldc * 2, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; g += 2) {
+                const int c = wn * 64 + j * 32 + 8 * g + 4 * half, n = col0 + wn * 64 + j * 32 + 8 * (g + half);
+                const float4 b0 = *reinterpret_cast<const float4*>(bias_s + c), b1 = *reinterpret_cast<const float4*>(bias_s + c + 8);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const f32x16_t& v = acc[j][i];
+                    const unsigned x0 = pack_bf2(v[4 * g] + b0.x, v[4 * g + 1] + b0.y), x1 = pack_bf2(v[4 * g + 2] + b0.z, v[4 * g + 3] + b0.w);
+                    const unsigned y0 = pack_bf2(v[4 * g + 4] + b1.x, v[4 * g + 5] + b1.y), y1 = pack_bf2(v[4 * g + 6] + b1.z, v[4 * g + 7] + b1.w);
+                    const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false), s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+                    const u32x4_t word = {s0[0], s1[0], s0[1], s1[1]};
+                    const int off = n < P.Nst ? (wm * 64 + i * 32 + l32) * (int)P.ldc * 2 + n * 2 : -16;
+                    __builtin_amdgcn_raw_buffer_store_b128(word, out, off, 0, 0);
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (the loads beyond the end)
+}
+template <int NK>
+hipError_t launch_resident_nk(const Params& P, int parts, hipStream_t stream) {
+    constexpr size_t lds = 4 * 128 * CHUNKS * 16 + 128 * sizeof(float);
+    static thread_local bool attr_set = false;
+    hipError_t e = allow_lds(&gemm_resident_kernel<NK>, lds, &attr_set);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_resident_kernel<NK>), dim3((unsigned)(P.ntn * parts)), dim3(256), lds, stream, P, parts);
+    return hipGetLastError();
+}
+
 inline bool direct_form(const GemmDesc& d) { return !d.add && !(d.atrans && !d.btrans); }
 
 // How the kernel of this tile shape runs the product.  Both unguarded forms need loads of the widest kind, per-thread
@@ -94,10 +214,28 @@ int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n, bool di
     return EDGE;
 }
 
-constexpr int kTileM[6] = {128, 256, 256, 64, 128, 128}, kTileN[6] = {128, 256, 128, 64, 64, 128};
+constexpr int kTileM[7] = {128, 256, 256, 64, 128, 128, 128}, kTileN[7] = {128, 256, 128, 64, 64, 128, 128};
 constexpr int kDirectVariant[6] = {0, 3, 2, 4, 5, 6};     // of launch_direct (0 and 1: by GemmPlan::deep)
 
 GemmPlan make_plan(const GemmDesc& d, bool allow_r);
+
+// Parts of the rows for gemm_resident_kernel, or 0 where it does not pay: two workgroups per CU walk one part of a column tile
+// each, and loading its weights takes a workgroup about as long as one and a half tiles.  Not beyond 1 GiB of output, most
+// of which has left the last-level cache when the row kernel comes to it: 43008 x 32000 986 to 1020 us here and 1130 to 1150 in the
+// row kernel behind it, 1033 to 1146 and 1033 to 1046 with 256x128 tiles.
+int resident_parts(const GemmDesc& d) {
+    const int batch = d.batch > 0 ? d.batch : 1;
+    if (!(d.in_type == DT_BF16 && d.out_type == DT_BF16 && !d.atrans && !d.btrans && d.nseg == 1 && batch == 1 && !d.add && !d.rowsum && d.Npad == 0 && d.N >= 8 && d.ldc <= 1 << 22)) return 0;
+    if (d.seg[0].K < 64 || d.seg[0].K > 256 || d.seg[0].K % 64 || (long long)d.M * d.N > 1ll << 29) return 0;
+    const int ntm = (d.M + 127) / 128, ntn = (d.N + 127) / 128;
+    int parts = 0;
+    double best = 1.6 * ntm * ntn / 512.0;
+    for (int p = 1; p <= 512 && p * 5 <= ntm; ++p) {
+        const double t = (double)(((long long)ntn * p + 511) / 512) * ((ntm + p - 1) / p + 1.5);
+        if (t < best) { best = t; parts = p; }
+    }
+    return parts;
+}
 
 template <typename TI>
 Params make_params(const GemmDesc& d) {
@@ -151,6 +289,21 @@ hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
     if (direct && mode == GUARDED) {
         direct = false;
         mode = run_mode<TI>(d, P, 128, 128, false);
+    }
+    if (plan.tile == GEMM_TILE_RESIDENT) {
+        set_tiles<TO>(d, P, 128, 128, mode);
+        if constexpr (sizeof(TI) == 2 && sizeof(TO) == 2) {
+            if (P.c_vec == 2) {
+                const int parts = resident_parts(d);
+                switch (d.seg[0].K / 64) {
+                case 1: return launch_resident_nk<1>(P, parts, stream);
+                case 2: return launch_resident_nk<2>(P, parts, stream);
+                case 3: return launch_resident_nk<3>(P, parts, stream);
+                default: return launch_resident_nk<4>(P, parts, stream);
+                }
+            }
+        }
+        plan.tile = GEMM_TILE_128S;                        // (rows of C that take no 16-byte stores)
     }
     const int tm = kTileM[plan.tile], tn = kTileN[plan.tile];
     set_tiles<TO>(d, P, tm, tn, mode);
@@ -247,6 +400,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     int ktot = 0;
     for (int s = 0; s < d.nseg; ++s) ktot += d.seg[s].K;
     if (d.in_type == DT_BF16) {
+        if (allow_r && resident_parts(d) > 0) { p.tile = GEMM_TILE_RESIDENT; return p; }
         // Few large tiles and a very long contraction (the softmax layer's input gradient, dA W form): the 256x256 tile, which
         // moves half the operand bytes of 128x128 per flop and reads A once where N is 256.  Up to 64 tiles: split along K over
         // up to one workgroup per CU, if every part keeps at least 24 slabs and the parts fill three quarters of the CUs; up to

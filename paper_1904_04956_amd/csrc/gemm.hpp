@@ -46,7 +46,8 @@ enum GemmTile { GEMM_TILE_128 = 0,        // 128x128, every element type and sha
                 GEMM_TILE_256X128 = 2,    // 256x128, bf16
                 GEMM_TILE_64 = 3,         // 64x64, where larger tiles leave CUs idle or fill them unevenly
                 GEMM_TILE_128X64 = 4,     // 128x64, bf16: too many tiles for 64x64, too few for 128x128
-                GEMM_TILE_128S = 5 };     // 128x128 with one LDS buffer, bf16, short contractions
+                GEMM_TILE_128S = 5,       // 128x128 with one LDS buffer, bf16, short contractions
+                GEMM_TILE_RESIDENT = 6 }; // a workgroup keeps 128 columns' weights and walks down the rows, bf16, contractions of up to 256
 struct GemmPlan {
     int tile;                 // a GemmTile
     bool deep;                // bf16, 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(NT, 8) void softmax_rows_regs_kernel(TS* u, long lo
     typedef Word<TS> W;
     constexpr int N = W::N, NW = NT / 64;
     __shared__ float sh[2][NW], label_logit;
-    const int m = blockIdx.x;
+    const int m = (int)(gridDim.x - 1 - blockIdx.x);   // from the end: the logits written last are in the last-level cache still
     TS* row = u + (long long)m * ldu;
     const int nchunks = (V + N - 1) / N, nout = (int)min(ldu, (long long)((V + 7) & ~7)) / N;   // words with logits, and with padding
     const int lab = labels[m];

@@ -173,6 +173,12 @@ def test_bf16_products_on_the_smaller_tiles(dims):
     check_step(dims, 1, seed=1965, theta_scale=1.0)
 
 
+@pytest.mark.parametrize("P,V,B", [(64, 32008, 260), (128, 32003, 260), (192, 32008, 256), (256, 32000, 260), (256, 32008, 261)])
+def test_logits_with_resident_weights_bf16(P, V, B):
+    # contractions of one to four slabs, 1280 to 1305 rows (whole tiles and parts of one), whole and partial column tiles, padded rows
+    check_step(dict(T=5, B=B, D=8, H=8, L=1, P=P, V=V), 1, seed=4962, theta_scale=2.0)
+
+
 def test_edges_of_the_large_tiles_bf16():
     # the logits on 256x128 tiles, dz on 256x256 split along a contraction of 25001, dW_s in the grouped launch
     check_step(dict(T=21, B=150, D=40, H=32, L=1, P=256, V=25001), 1, seed=4961)
