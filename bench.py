@@ -40,9 +40,9 @@ PEAK_HBM = 8.0e12            # B/s
 
 # kernel name behind each timing class of the library (one class = one kernel function, by shape several instantiations)
 KERNEL_OF_CLASS = {
-    "recurrent_fwd_persistent": "rec_fwd_kernel", "recurrent_bwd_persistent": "rec_bwd_kernel",
-    "gemm_wgrad": "gemm_group_kernel", "softmax_rows": "softmax_rows_bf16_regs_kernel",
-    "gemm_input_projection": "gemm_kernel", "gemm_bottleneck": "gemm_kernel", "gemm_logits": "gemm_kernel",
+    "recurrent_fwd_persistent": "tile_rec_fwd_kernel", "recurrent_bwd_persistent": "tile_rec_bwd_kernel",
+    "gemm_wgrad": "gemm_group_kernel", "softmax_rows": "softmax_rows_regs_kernel",
+    "gemm_input_projection": "gemm_kernel", "gemm_bottleneck": "gemm_kernel", "gemm_logits": "gemm_resident_kernel",
     "gemm_softmax_bwd": "gemm_kernel", "gemm_dgrad": "gemm_kernel", "gemm_recurrent_fwd": "gemm_kernel",
     "gemm_recurrent_bwd": "gemm_kernel", "cell_fwd": "cell_fwd_kernel", "cell_bwd": "cell_bwd_kernel",
 }
