@@ -338,13 +338,15 @@ int parts_of(long long target, int most, long long tiles, int slabs, int min_sla
 }
 
 // Estimated time (us) of `units` workgroups of a float tile with `slabs` slabs each.  The matrix cores of a CU take 1.71 us for a
-// slab of 128x128 and 0.43 for one of 64x64 and are shared by the workgroups on it (measured 1.9 and 0.57, alone on a CU 2.35 and
-// 0.66).  What the small tile loses in every slab it gains where whole tiles fill the CUs unevenly: 1344 x 4096, K = 1024 is two
-// rounds of 128x128 for 1.38 rounds' work, 120 us against 113; 336 x 2048, K = 512 37 against 14; 2048 x 1024 twice, K = 1280
-// 91 against 53; 5376 x 4096 the same to 3 %.
+// slab of 128x128 and 0.43 for one of 64x64 and are shared by the workgroups on it (measured 1.9 and 0.54, alone on a CU 2.35 and
+// 0.66).  128x128 tiles come two to a CU and leave together: a last round of few of them still shares CUs, 3.8 a slab and round of
+// 512.  What the small tile loses in every slab it gains there.  X W^T, us, 128x128 / 64x64: 1344 x 2048 twice, K = 1024 122 / 102;
+// 1260 x 4096 twice, K = 2048 488 / 367, 2100 702 / 570, 1680 472 / 448, 2688 708 / 679, 840 240 / 237; 1344 x 32000, K = 256 210 / 187; 2048 x 1024 twice,
+// K = 1280 91 / 53.
 double f32_time(bool small, double units, double slabs) {
-    const double slab = small ? 0.57 : 1.9, lone = small ? 0.66 : 2.35, x = units / 256.0;
-    return slabs * (x <= 1.0 ? lone : slab * (double)(long long)(x + 0.999999));
+    const double x = units / 256.0;
+    if (small) return slabs * (x <= 1.0 ? 0.66 : 0.54 * (double)(long long)(x + 0.999999));
+    return slabs * (x <= 1.0 ? 2.35 : 3.8 * (double)(long long)(x / 2.0 + 0.999999));
 }
 // Float operands: tile and number of parts of K by the least estimated time.
 void plan_f32(const GemmDesc& d, bool direct, int Ne, int Nr, GemmPlan* p) {
