@@ -136,4 +136,15 @@ __device__ __forceinline__ bool probe_producers16(const bf16_t* p, bool mine, un
     }
 }
 
+// Returns true if the wait was abandoned.  A look that came too early is followed by the cheap probe of its producers, then by
+// looks past the caches: the probe sees one word of several stores, and the others may be a little later.
+template <int N, typename F>
+__device__ __forceinline__ bool settle_probe(uint4 (&f)[N], const bf16_t* base, F off, const bf16_t* probe, bool probing, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_there16<N>(f)) return gave_up;
+    if (probe_producers16(probe, probing, abort_word, limit)) return true;
+#pragma unroll
+    for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
+    return settle16<N>(f, base, off, false, abort_word, limit);
+}
+
 }  // namespace blstm

@@ -49,19 +49,6 @@ __device__ __forceinline__ uint2 pack(const unsigned (&v)[2]) { return make_uint
 __device__ __forceinline__ unsigned word(unsigned v, int) { return v; }
 __device__ __forceinline__ unsigned word(const uint2& v, int k) { return k ? v.y : v.x; }
 
-// Returns true if the wait was abandoned.  A look that came too early is followed by the cheap probe of its producers,
-// then by another look past the caches.
-template <int N, typename F>
-__device__ __forceinline__ bool settle_probe(uint4 (&f)[N], const bf16_t* base, F off, const bf16_t* probe, bool probing, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_there16<N>(f)) return gave_up;
-    for (;;) {
-        if (probe_producers16(probe, probing, abort_word, limit)) return true;
-#pragma unroll
-        for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
-        if (all_there16<N>(f)) return false;
-    }
-}
-
 // Keeps three quarters of the weights in accumulation registers, which the products read as well as the others, and the
 // others free: left to itself the compiler fills those with weights and reads the staged h one fragment at a time.
 template <int NB, int KQ>

@@ -1,0 +1,28 @@
+// The bounded waits of the 16-row tile kernels, one call each: prints result, abort word, loads, whether the data came whole.
+#include "exchange.hpp"
+#include <cstdio>
+#include <cstring>
+#include <string>
+using namespace blstm;
+
+int main(int argc, char** argv) {
+    const std::string what = argv[1];
+    constexpr int N = 4;
+    alignas(16) static bf16_t data[N * 8 + 8];
+    for (bf16_t& e : data) e = 0x3F80;
+    const bf16_t* probe = data + N * 8;                        // (a word of its own: the last a producer writes)
+    auto off = [](int q) { return q * 8; };
+    unsigned abort_word = 0;
+    bool gave_up = false;
+    if (what == "nothing") memset(data, 0xFF, sizeof data);                                            // nobody writes
+    if (what == "rest" || what == "rest, aborted") data[11] = 0xFFFF;                                  // the probed word is there, one other element never comes
+    if (what == "rest, aborted") on_load = [&](unsigned long long n) { if (n == 500) abort_word = 1; };   // (raised by another workgroup)
+    if (what == "late") { memset(data, 0xFF, sizeof data); on_load = [&](unsigned long long n) { if (n == 100) data[32] = data[33] = 0; if (n == 300) memset(data, 0, sizeof data); }; }
+    if (what == "given up") { data[3] = 0xFFFF; gave_up = true; }
+    uint4 f[N];
+    look16<N>(f, data, off);
+    try {
+        const bool r = settle_probe<N>(f, data, off, probe, true, gave_up, &abort_word, what == "rest, aborted" ? ~0ull >> 1 : 20);
+        printf("%d %u %llu %d\n", r, abort_word, loads, all_there16<N>(f));
+    } catch (too_many_loads) { printf("unbounded\n"); }
+}
