@@ -266,14 +266,18 @@ def test_exchange_protocols_agree_bit_for_bit():
         lrn.close()
 
 
-def test_abandoned_wait_is_reported_in_band_and_recovered_from():
+@pytest.mark.parametrize("B,H", [
+    (64, 128),                                              # few sequences; fenced, 16-row tiles
+    (129, 512), (300, 512), (40, 1024),                     # 16-row tiles: slices of 64 units, several tiles a workgroup, of 32 units
+])
+def test_abandoned_wait_is_reported_in_band_and_recovered_from(B, H):
     # The abort word is raised from the host (test option), so every wait of the persistent kernels returns at
     # once and all kernels run to their end: the step's loss, z and gradient must be NaN (in-band), the status call
     # must report the failure, and the next step must give the bits of a clean run.
     from paper_1904_04956_amd import binding as bl
     from paper_1904_04956_amd.harness import Learner
-    dims = dict(T=6, B=64, D=32, H=128, L=2, P=16, V=90)
-    dm, theta, x, labels = make_problem(dims, 1, 83, 2.0)
+    dims = dict(T=6, B=B, D=32, H=H, L=2, P=16, V=90)
+    dm, theta, x, labels = make_problem(dims, 1, 83, 2.0 if H < 500 else 1.0)
     for sync in (1, 0):
         lrn = Learner(mode=1, recurrent_sync=sync, **dims)
         lrn.set_theta(theta); lrn.set_batch(x, labels)
