@@ -63,6 +63,7 @@ struct blstm_ctx {
     size_t wAX, wPRE, wDY[2], wDH, wDC, wLOGITS, wROWLOSS, wUHT, wCNT, wPART, wHX, wDAX, hx_bytes, dax_bytes, part_bytes, ws_bytes;
     long long ldu;            // row distance of the logit matrix (see SoftmaxScratch)
     size_t soft_part;         // split-K scratch of the softmax block's products, the same in both entry points
+    bool guarded_xent;        // z or W_s is unaligned, or that of the model this is the twin of: the softmax products' parts are the guarded kernel's, so that both entry points give the same bits
     size_t noalloc_need;      // scratch by which softmax_xent_fwd_bwd_noalloc decides whether a call fits the resident array
     int Dp;                   // 0, or the first layer's input width rounded up to whole tiles (padded copies of x and W_x)
     size_t wXP, wWP;
@@ -186,7 +187,7 @@ GemmDesc softmax_wgrad_desc(const blstm_ctx* ctx, const char* U, long long ldu, 
     GemmDesc d = gemm_desc(ctx, ctx->st, DT_F32);
     d.M = ctx->V; d.N = ctx->zdim; d.atrans = true; d.btrans = true;
     d.seg[0] = GemmSeg{U, z, ldu, ctx->zdim, 0, 0, ctx->M};
-    d.a_pad = padded_rows(ctx->V, ldu);
+    d.a_pad = padded_rows(ctx->V, ldu); d.guarded_parts = ctx->guarded_xent;
     d.C = grad + ctx->off_ws; d.ldc = ctx->zdim;
     d.rowsum = grad + ctx->off_bs;                     // db_s = sum over frames of du
     d.partial_bytes = ctx->soft_part;
@@ -220,7 +221,7 @@ int softmax_xent_run(blstm_ctx* ctx, const SoftmaxScratch& sc, const void* theta
         GemmDesc d = desc(S, S);
         d.M = M; d.N = Z; d.btrans = true;
         d.seg[0] = GemmSeg{U, at(theta, ctx->off_ws, e), sc.ldu, Z, 0, 0, V};
-        d.a_pad = padded_rows(V, sc.ldu);
+        d.a_pad = padded_rows(V, sc.ldu); d.guarded_parts = ctx->guarded_xent;
         d.C = dz; d.ldc = Z;
         RUN(PC_GEMM_SOFTMAX_BWD, "dz", launch_gemm(d, st));
     }
@@ -307,7 +308,7 @@ int make_twin(blstm_ctx* c) {
     c->tz = BlockTensor{0, 0, 1, c->M, c->M, zs, z, zp};
     c->tu = BlockTensor{0, 0, 1, c->M, c->M, 1, c->zdim, t->zdim};
     if (t->part_bytes < c->soft_part) c->soft_part = t->part_bytes;
-    t->soft_part = c->soft_part; t->ldu = c->ldu;
+    t->soft_part = c->soft_part; t->ldu = c->ldu; t->guarded_xent = c->guarded_xent;
     size_t w = up256(t->ws_bytes);
     c->tTHETA = w; w += up256(t->nparam * c->esz);
     c->tGRAD = w;  w += up256(t->nparam * 4);
@@ -422,6 +423,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->off_ws = off; off += (size_t)c->V * c->zdim;
     c->off_bs = off; off += (size_t)c->V;
     c->nparam = off;
+    c->guarded_xent = (size_t)c->zdim * c->esz % 16 != 0 || c->off_ws * c->esz % 16 != 0;
     // workspace layout
     const size_t M = (size_t)c->M, B = (size_t)c->B, e = c->esz;
     const size_t Br = (B + 31) / 32 * 32, Mr = (size_t)c->T * Br;      // rows rounded up to whole batch tiles

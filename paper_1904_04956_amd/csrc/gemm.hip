@@ -274,14 +274,16 @@ void set_tiles(const GemmDesc& d, Params& P, int tm, int tn, int mode) {
 }
 
 template <typename TI, typename TO>
-hipError_t dispatch(const GemmDesc& d, hipStream_t stream) {
+hipError_t dispatch(const GemmDesc& given, hipStream_t stream) {
+    GemmDesc d = given;
     Params P = make_params<TI>(d);
     const int batch = d.batch > 0 ? d.batch : 1;
     bool direct = direct_form(d);
+    if (run_mode<TI>(d, P, 128, 128, direct) == GUARDED) d.guarded_parts = true;   // (whatever the tile)
     GemmPlan plan = make_plan(d, direct);
-    // the plan looks at the shape only: check what it chose against the operands' alignment and fall back
+    // the plan's tile looks at the shape only: check it against the operands' alignment and fall back
     int mode = run_mode<TI>(d, P, kTileM[plan.tile], kTileN[plan.tile], direct);
-    // (on the 128x128 tile with the plan's number of parts: how the sums are ordered depends on the shape, never on alignment)
+    // (on the 128x128 tile with the plan's number of parts)
     if (plan.tile != GEMM_TILE_128 && (mode == GUARDED || (plan.tile == GEMM_TILE_256 && !(direct && !d.atrans && d.btrans)))) {
         plan.tile = GEMM_TILE_128; plan.deep = false;
         mode = run_mode<TI>(d, P, 128, 128, direct);
@@ -364,16 +366,20 @@ void plan_f32(const GemmDesc& d, bool direct, int Ne, int Nr, GemmPlan* p) {
             }
         } else if (t128 <= 1024) last = 32;
     }
-    double best = 0.0;
-    for (int s = first; s <= last; ++s) {
-        const size_t need = s > 1 ? (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float) : 0;
-        if (s > first && (slabs / s < 4 || need > d.partial_bytes || need > ((size_t)256 << 20))) break;
-        for (int small = 0; small <= (direct ? 1 : 0); ++small) {
-            double t = f32_time(small != 0, (double)(small ? t64 : t128) * s, (slabs + s - 1) / s);
-            if (s > 1) t = (t + 4.5 + 2.0 * s * out_bytes / 4e6) * (12.0 / 11.0);
-            if (best == 0.0 || t < best) { best = t; p->tile = small ? GEMM_TILE_64 : GEMM_TILE_128; p->splits = s; p->partial_bytes = need; }
+    auto search = [&](int tiles) {
+        double best = 0.0;
+        for (int s = first; s <= last; ++s) {
+            const size_t need = s > 1 ? (size_t)s * batch * ((size_t)d.M * Nr + d.M) * sizeof(float) : 0;
+            if (s > first && (slabs / s < 4 || need > d.partial_bytes || need > ((size_t)256 << 20))) break;
+            for (int small = 0; small < tiles; ++small) {
+                double t = f32_time(small != 0, (double)(small ? t64 : t128) * s, (slabs + s - 1) / s);
+                if (s > 1) t = (t + 4.5 + 2.0 * s * out_bytes / 4e6) * (12.0 / 11.0);
+                if (best == 0.0 || t < best) { best = t; p->tile = small ? GEMM_TILE_64 : GEMM_TILE_128; p->splits = s; p->partial_bytes = need; }
+            }
         }
-    }
+    };
+    if (d.guarded_parts) { search(1); first = last = p->splits; }
+    search(direct ? 2 : 1);
 }
 
 // Estimated time (us) of a slab of `tiles` bf16 tiles spread over the CUs.  64x64 with three buffers: three workgroups on a CU
@@ -483,16 +489,24 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
             if (s > 1 && need_of(s) <= d.partial_bytes) p.splits = s;
         }
     } else if (!d.add && d.partial && t128 <= 1024) most = 32;
-    double best = 0.0;
-    for (int s = p.splits, last = most > s ? most : s; s <= last; ++s) {
-        if (s > 1 && most > 1 && (slabs / s < 4 || need_of(s) > d.partial_bytes || need_of(s) > ((size_t)256 << 20))) break;
-        for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
-            if (tile != GEMM_TILE_128 && !any_tile) continue;
-            double t = estimate(tile, s);
-            if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.3;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
-            if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
+    auto search = [&](int first, int last, bool all) {
+        double best = 0.0;
+        for (int s = first; s <= last; ++s) {
+            if (s > first && (slabs / s < 4 || need_of(s) > d.partial_bytes || need_of(s) > ((size_t)256 << 20))) break;
+            for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
+                if (tile != GEMM_TILE_128 && !all) continue;
+                double t = estimate(tile, s);
+                if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.3;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
+                if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
+            }
         }
-    }
+    };
+    const int first = p.splits, last = most > first ? most : first;
+    // The guarded kernel has 128x128 tiles only, so its number of parts is theirs: aligned operands of dz, 462 x 461, K = 2000, take 64x64
+    // tiles unsplit, of which 16 guarded workgroups would walk 32 slabs each.  Softmax block of that model, us, in one part / in eight:
+    // 222 / 97 (P = 66, V = 1500: 110 / 47 in six); in float, with eight and 13 parts, 119 / 112.
+    if (d.guarded_parts) search(first, last, false);
+    search(d.guarded_parts ? p.splits : first, d.guarded_parts ? p.splits : last, any_tile);
     // at most one 128x128 workgroup per CU: run the loads further ahead (three LDS buffers, or four register sets)
     p.deep = p.tile == GEMM_TILE_128 && t128 * p.splits <= 256;
     return p;

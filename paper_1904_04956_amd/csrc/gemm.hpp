@@ -36,6 +36,8 @@ struct GemmDesc {
     bool a_pad;               // rows of A (as they lie in memory) may be read up to the next 16-byte boundary and hold finite values there
     bool c_pad;               // rows of C may be written up to the next multiple of eight columns
     bool long_parts;          // K is split, if at all, into parts of at least eight slabs (see make_plan)
+    bool guarded_parts;       // K is split as the guarded kernel takes it (set by launch_gemm where that runs; by the caller for a product
+                              // that has to give the bits of one on unaligned operands)
     bool atrans, btrans;
     DType in_type, out_type;  // in_type is the element type of A and B
 };

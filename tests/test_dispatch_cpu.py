@@ -17,6 +17,7 @@ import ctypes, json, sys
 sys.path.insert(0, {root!r})
 rec = ctypes.CDLL({recorder!r}, mode=ctypes.RTLD_GLOBAL)        # found before the real runtime
 rec.recorder_name.restype = ctypes.c_char_p
+rec.recorder_grid.restype = ctypes.c_uint
 from paper_1904_04956_amd import binding as bl
 P = 1 << 20                                                      # any aligned address: nothing is read or written
 
@@ -242,3 +243,24 @@ def test_a_single_frame_needs_no_recurrence(recorder, mode, H, T, persistent):
         out = [[count(n, "rec"), count(n, "cell_")] for n in (launches(m.forward), launches(m.backward))]
     """)
     assert f == b == ([1, 0] if persistent else [0, 1])
+
+
+@pytest.mark.parametrize("mode,dims,parts", [
+    (1, "T=20, B=23, D=40, H=128, L=1, P=461, V=2000", 8),     # z's rows are unaligned, and the model too small for a twin
+    (1, "T=20, B=23, D=40, H=128, L=1, P=66, V=1500", 6),
+    (1, "T=20, B=23, D=40, H=101, L=1, P=0, V=2000", 8),       # the workspace form runs on the twin's aligned operands
+    (1, "T=20, B=16, D=40, H=512, L=3, P=461, V=4000", 13),
+    (0, "T=20, B=23, D=40, H=128, L=1, P=461, V=2000", None),
+    (0, "T=20, B=28, D=40, H=256, L=3, P=250, V=2000", None),
+])
+def test_guarded_products_keep_their_parts(recorder, mode, dims, parts):
+    # dz and dW_s of a model whose rows of z are unaligned, by either entry point: parts for 128x128 tiles, the only guarded ones
+    forms = recorder(f"""
+        out = []
+        m = Model(mode={mode}, {dims})
+        for call in (m.xent, m.noalloc):
+            names = launches(call)
+            out.append([rec.recorder_grid(i, 1) for i in range(len(names)) if "gemm_kernel" in names[i]])
+    """)
+    assert forms[0] == forms[1] and len(forms[0]) == 3
+    assert forms[0][1] > 1 if parts is None else forms[0][1] == parts
