@@ -197,6 +197,12 @@ def test_softmax_row_widths_fp32(V):
     check_step(dict(T=2, B=5, D=8, H=8, L=1, P=8, V=V), 0, seed=80, theta_scale=4.0)
 
 
+@pytest.mark.parametrize("mode,V", [(1, 9), (1, 512), (1, 513), (1, 2049), (0, 5), (0, 256), (0, 257), (0, 1025)])
+def test_softmax_rows_that_leave_wavefronts_idle(mode, V):
+    # one word more than a wavefront's share, whole shares, and rows of a few words
+    check_step(dict(T=2, B=5, D=8, H=8, L=1, P=8, V=V), mode, seed=80, theta_scale=4.0)
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims", [
     dict(T=4, B=64, D=128, H=128, L=2, P=128, V=512),       # whole 256x128 tiles everywhere: dW_s can join the grouped launch
