@@ -29,6 +29,7 @@
 #include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
+#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -78,11 +79,15 @@ __device__ __forceinline__ Spot spot(int nu, int nbg, int per_group, int ntiles)
     return p;
 }
 
+// Workgroups a CU holds of these kernels (their registers, and the launch bounds).
+constexpr int fwd_per_cu(int nb, int kq, bool multi) { return nb == 4 ? (kq <= (multi ? 4 : 8) ? 2 : 1) : kq == 4 ? (multi ? 2 : 4) : kq <= 12 ? 2 : 1; }
+constexpr int bwd_per_cu(int nb, int kq, bool multi) { return nb == 4 ? (kq == 4 ? 2 : 1) : kq == 4 ? (multi ? 2 : 4) : kq <= 12 ? 2 : 1; }
+
 // ------------------------------------------------------------------------------ forward
 // Width up to 32 KQ.  MULTI: several tiles a workgroup, walked one after the other in every frame; the next item's
 // operand, written a frame ago, is then loaded under an item's products.
 template <int NB, int KQ, bool SENTINEL, bool MULTI>
-__global__ __launch_bounds__(64 * NW, 1) void tile_rec_fwd_kernel(RecFwdArgs a) {
+__global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_fwd_kernel(RecFwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int FR = KQ / NW;                          // fragments a wavefront stages
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(64 * NW, 1) void tile_rec_fwd_kernel(RecFwdArgs a) 
 // ------------------------------------------------------------------------------ backward
 // Each wavefront contracts KQ / 4 blocks of 32 columns of every gate, SL fragments of dE/da in flight ahead of the products.
 template <int NB, int KQ, bool SENTINEL, bool MULTI>
-__global__ __launch_bounds__(64 * NW, 1) void tile_rec_bwd_kernel(RecBwdArgs a) {
+__global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_bwd_kernel(RecBwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int BW = KQ / 4;
@@ -400,16 +405,27 @@ __global__ __launch_bounds__(64 * NW, 1) void tile_rec_bwd_kernel(RecBwdArgs a) 
     }
 }
 
-// The groups of tiles a direction is cut into: as many as leave every XCD, which gets whole groups, one workgroup a CU.
+// The groups of tiles a direction is cut into: as many as leave every XCD, which gets whole groups, per_cu workgroups a CU.
 struct Cut { int nbg, per_group, grid, real; };
-Cut cut(int B, int H, int units) {
-    const int nu = (H + units - 1) / units, tiles = (B + 15) / 16, most = 4 * (32 / nu);
+Cut cut(int B, int H, int units, int per_cu) {
+    const int nu = (H + units - 1) / units, tiles = (B + 15) / 16, most = 4 * (32 * per_cu / nu);
     Cut c;
     c.per_group = (tiles + most - 1) / most;
     c.nbg = (tiles + c.per_group - 1) / c.per_group;
     c.grid = (2 * c.nbg + 7) / 8 * 8 * nu;
     c.real = 2 * c.nbg * nu;
     return c;
+}
+// More than one workgroup a CU only where that leaves each a tile of its own (and for layers of up to 32 units, whose workgroups
+// have the least to do).  One layer of 21 frames, us, one a CU / as below, forward and backward: 64 units, 3000 sequences
+// 158 + 181 / 124 + 160; 128, 1500 159 + 180 / 141 + 159; 256, 700 forward 160 / 144; 32, 8192 257 + 334 / 186 + 242.  Where two of
+// three tiles were left, 128, 3000, it was 253 + 261 / 280 + 271.
+Cut best_cut(int B, int H, int units, int most_per_cu) {
+    for (int p = 1; p <= most_per_cu; ++p) {
+        const Cut c = cut(B, H, units, p);
+        if (c.per_group == 1) return c;
+    }
+    return cut(B, H, units, H <= 32 ? 2 : 1);
 }
 
 template <int NB, int KQ, bool S, bool MULTI>
@@ -421,23 +437,23 @@ hipError_t run(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched
     return launch_resident<tile_rec_bwd_kernel<NB, KQ, S, MULTI>>(a, 64 * NW, (size_t)2 * NW * NB * 64 * 16, c.grid, c.real, st, launched);
 }
 template <int NB, int KQ, typename A>
-hipError_t run_width(const A& a, const Cut& c, bool sentinel, hipStream_t st, bool* launched) {
-    if constexpr (NB == 4) {                             // (several tiles a workgroup: of 64 units only)
+hipError_t run_width(A a, bool sentinel, hipStream_t st, bool* launched) {
+    const Cut c = best_cut(a.B, a.H, 16 * NB, std::is_same_v<A, RecFwdArgs> ? fwd_per_cu(NB, KQ, false) : bwd_per_cu(NB, KQ, false));
+    a.nbg = c.nbg; a.tiles_per_group = c.per_group;
+    if constexpr (NB == 4 || KQ == 4) {                  // (several tiles a workgroup: of 64 units, or whole narrow layers)
         if (c.per_group > 1 && sentinel) return run<NB, KQ, true, true>(a, c, st, launched);
-        if constexpr (KQ != 12) if (c.per_group > 1) return run<NB, KQ, false, true>(a, c, st, launched);
+        if constexpr (NB == 4 && KQ != 12) if (c.per_group > 1) return run<NB, KQ, false, true>(a, c, st, launched);
     }
     if (sentinel) return run<NB, KQ, true, false>(a, c, st, launched);
     if constexpr (KQ == 4 || KQ == 8 || KQ == 16 || KQ == 32) return run<NB, KQ, false, false>(a, c, st, launched);
     return hipSuccess;
 }
 template <typename A>
-hipError_t launch(A a, bool sentinel, hipStream_t st, bool* launched) {
+hipError_t launch(const A& a, bool sentinel, hipStream_t st, bool* launched) {
     *launched = false;
     const int units = rec_tile_units(a.B, a.H);
     if (units == 0 || !(sentinel || rec_fenced(a.H))) return hipSuccess;
-    const Cut c = cut(a.B, a.H, units);
-    a.nbg = c.nbg; a.tiles_per_group = c.per_group;
-#define BLSTM_TILE(NB, KQ) if (units == 16 * NB && a.H <= 32 * KQ) return run_width<NB, KQ>(a, c, sentinel, st, launched)
+#define BLSTM_TILE(NB, KQ) if (units == 16 * NB && a.H <= 32 * KQ) return run_width<NB, KQ>(a, sentinel, st, launched)
     BLSTM_TILE(2, 4); BLSTM_TILE(2, 8); BLSTM_TILE(2, 12); BLSTM_TILE(2, 16); BLSTM_TILE(2, 20); BLSTM_TILE(2, 24); BLSTM_TILE(2, 28); BLSTM_TILE(2, 32);
     BLSTM_TILE(4, 4); BLSTM_TILE(4, 8); BLSTM_TILE(4, 12); BLSTM_TILE(4, 16);
 #undef BLSTM_TILE
@@ -446,13 +462,16 @@ hipError_t launch(A a, bool sentinel, hipStream_t st, bool* launched) {
 
 }  // namespace
 
-// Slices of 32 units while that leaves every workgroup a CU and a tile of its own, else of 64: half of the operand's bytes
-// per cell, but their weights fit the registers up to 512 cells only.  Beyond 512 cells several tiles of 32 units a
-// workgroup lose to recurrent.hip's 32 x 32 (1024 cells, 512 sequences 450 / 545 us a layer against 348 / 387; 128 sequences
-// 121 / 145 against 96 / 115).
+// Slices of 32 units for a layer of one such slice, and while that leaves every workgroup a CU and a tile of its own; else of 64: half
+// of the operand's bytes per cell, but their weights fit the registers up to 512 cells only.  (Of 32 with two workgroups a CU where the last slice
+// of 64 would be at most half full and take two tiles a workgroup: 136 cells, 700 sequences 84 + 130 us against 127 + 159.)
+// Beyond 512 cells several tiles of 32 units a workgroup lose to recurrent.hip's 32 x 32 (1024 cells, 512 sequences 450 / 545 us a layer
+// against 348 / 387; 128 sequences 121 / 145 against 96 / 115).
 int rec_tile_units(int B, int H) {
     if (!rec_supported(H)) return 0;
-    if (cut(B, H, 32).per_group == 1) return 32;
+    if (H <= 32 || cut(B, H, 32, 1).per_group == 1) return 32;
+    const int last = H % 64;
+    if (last >= 1 && last <= 32 && H <= 384 && cut(B, H, 64, 1).per_group > 1 && cut(B, H, 32, 2).per_group == 1) return 32;
     return H <= 512 ? 64 : 0;
 }
 hipError_t launch_rec_tile_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched) { return launch(a, sentinel, st, launched); }

@@ -264,3 +264,21 @@ def test_guarded_products_keep_their_parts(recorder, mode, dims, parts):
     """)
     assert forms[0] == forms[1] and len(forms[0]) == 3
     assert forms[0][1] > 1 if parts is None else forms[0][1] == parts
+
+
+@pytest.mark.parametrize("B,H,units,fwd,bwd", [
+    (2048, 24, 2, 256, 256), (2049, 24, 2, 264, 264), (4097, 32, 2, 520, 520), (8193, 8, 2, 344, 344),   # up to four a CU, beyond that two with several tiles
+    (2048, 64, 4, 256, 256), (2049, 64, 4, 264, 264), (4097, 64, 4, 176, 176),
+    (1025, 128, 4, 272, 272), (513, 256, 4, 288, 160),       # the backward kernel fits a CU once
+    (640, 136, 4, 240, 240), (641, 136, 2, 440, 440), (769, 136, 4, 312, 168),
+])
+def test_workgroups_on_sixteen_row_tiles(recorder, B, H, units, fwd, bwd):
+    got = recorder(f"""
+        rec.recorder_occupancy(b"tile_rec", 4)
+        m = Model(T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        out = []
+        for call in (m.forward, m.backward):
+            names = launches(call)
+            out += [[names[i].split("kernelILi")[1][0], rec.recorder_grid(i, 0)] for i in range(len(names)) if "tile_rec" in names[i]]
+    """)
+    assert got == [[str(units), fwd], [str(units), bwd]]
