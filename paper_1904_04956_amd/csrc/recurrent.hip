@@ -153,8 +153,11 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 // MULTI: a workgroup owns several batch tiles (tiles_per_group > 1).
 // PADDED: the layer is narrower than the kernel's NW * KW cells (any multiple of 8): U_h counts as zero beyond it, the
 // exchange holds whole slices of 32 units, and the units beyond the layer come out as zeros that are not stored row-major.
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
-__global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
+// LEAN: few enough registers for two workgroups per CU, one of which computes while the other waits for its operand: one set of
+// inputs, asked for behind the item's own operand, and half of the accumulators at a time.  Marks RecFwdArgs::fill on the side.
+template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
+__global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
+    static_assert(!LEAN || (SENTINEL && MULTI && PADDED && KW < 128), "the forms that are used");
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
@@ -166,7 +169,17 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
     const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
-    if (ntl == 0) return;                                // no batch tile of its own
+    // this workgroup's share of the region to fill, some words every item behind its stores (a share is far below 2^32 words)
+    const unsigned long long share = LEAN && a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
+    const unsigned long long fill_first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
+    uint4* const fill = static_cast<uint4*>(a.fill) + fill_first;
+    const unsigned fill_end = (unsigned)(min(a.fill_words, fill_first + share) - fill_first);
+    unsigned fill_pos = threadIdx.x;
+    auto fill_some = [&](int words) __attribute__((always_inline)) {
+        if constexpr (LEAN) for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    };
+    if (ntl == 0) { fill_some(1 << 30); return; }        // no batch tile of its own
+    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * (T * ntl) - 1) / ((unsigned long long)(64 * NW) * (T * ntl)));
 
     // this wavefront's slice of U_h as B-fragments: unit row l32 of each gate, 8 consecutive k per lane
     uint4 bfrag[4][KSTEPS];
@@ -227,7 +240,7 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
     // in the other, so nothing is copied (a copy would have to wait for loads issued a moment before).
     float ax0[EPT][4], cp0[EPT], ax1[EPT][4], cp1[EPT];
-    issue_inputs(0, ax0, cp0);
+    if constexpr (!LEAN) issue_inputs(0, ax0, cp0);
     // Waited for here, once: the compiler places its waits for the worst path into the loop, and with these
     // loads still in flight on the way in, that path would make every item wait for its freshly issued loads.
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0) (expcnt and lgkmcnt left alone)
@@ -258,6 +271,7 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
         const int xrow_ = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane_ >> 5) + ((lane_ >> 3) & 3);
         const unsigned xcol_ = (unsigned)(u * 32 + 8 * ((lane_ >> 1) & 3) + 4 * (lane_ & 1));
         if (tail.xok && (!PADDED || xcol_ < (unsigned)H)) *reinterpret_cast<uint2*>(yb + ((unsigned)xrow_ * (unsigned)(2 * H) + (unsigned)(d * H) + xcol_)) = tail.hq;
+        fill_some(fill_each);
     };
     auto do_item = [&](const int item, const float (&ax)[EPT][4], const float (&cpl)[EPT], float (&axn)[EPT][4],
                        float (&cpn)[EPT]) __attribute__((always_inline)) {
@@ -278,10 +292,22 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
             if (SENTINEL) {
                 // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
                 const bf16_t* probe = hb + xoff(PADDED ? min(wave * (KW / 32) + lane, NU - 1) * 32 + 31 : wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
-                // (no registers for two attempts: probe first, then the data)
-                const bool gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
-                asm volatile("" ::: "memory");
-                load_chunks_cached<KSTEPS>(afrag, hp, lastp);
+                bool gu = false;
+                if constexpr (LEAN) {
+                    // Straight for the data: the first look nearly always finds everything.  If not: the cheap probe, then cache-bypassing
+                    // loads (the first ones may have left lines with sentinels in the L1).
+                    load_chunks_cached<KSTEPS>(afrag, hp, lastp);
+                    flush_tail();
+                    if (!all_written<KSTEPS>(afrag)) {
+                        gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
+                        asm volatile("" ::: "memory");
+                        load_chunks<KSTEPS>(afrag, hp, lastp);
+                    }
+                } else {                                 // (no registers for two attempts: probe first, then the data)
+                    gu = wait_probe(probe, lane < KW / 32, a.abort_word, a.limit_ticks);
+                    asm volatile("" ::: "memory");
+                    load_chunks_cached<KSTEPS>(afrag, hp, lastp);
+                }
                 if (ensure_written<KSTEPS>(afrag, hp, lastp, gu, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             } else {
                 if (wait_counter(cnt + i, (unsigned)(NU * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
@@ -289,22 +315,27 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
                 for (int q = 0; q < KSTEPS; ++q)
                     afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
-            f32x16_t acc[4];
+            if constexpr (LEAN) issue_inputs(item, axn, cpn);   // (in flight behind the products)
+            constexpr int GP = LEAN ? 2 : 4;              // gates at a time
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g0 = 0; g0 < 4; g0 += GP) {
+                f32x16_t acc[GP];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[g][e] = 0.0f;
+                for (int g = 0; g < GP; ++g)
 #pragma unroll
-            for (int q = 0; q < KSTEPS; ++q)
+                    for (int e = 0; e < 16; ++e) acc[g][e] = 0.0f;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g][q], acc[g]);
-            // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
+                for (int q = 0; q < KSTEPS; ++q)
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+                    for (int g = 0; g < GP; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g0 + g][q], acc[g]);
+                // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq)
-                    l4[((wave * 4 + g) * 4 + rq) * 64 + lane] =
-                        make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
+                for (int g = 0; g < GP; ++g)
+#pragma unroll
+                    for (int rq = 0; rq < 4; ++rq)
+                        l4[((wave * 4 + g0 + g) * 4 + rq) * 64 + lane] =
+                            make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
+            }
             if (SENTINEL) lds_barrier(); else __syncthreads();
             // all partial sums of this thread's rows are read before any is added: the reads then
             // overlap instead of each waiting for its LDS round trip
@@ -330,10 +361,11 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
         // before the barrier above they would sit in front of another wavefront's loads of the exchanged h and
         // add their latency to the frame-to-frame path.  They are issued below, once h has gone out.)
         flush_tail();                                     // at the latest here: the loads issued below may read what it stores
+        if constexpr (LEAN) if (n == 0) issue_inputs(item, axn, cpn);
         float cp[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : cpl[e];
-        if (item + 1 < nitems) issue_inputs(item + 1, axn, cpn);   // (registers are short later on)
+        if constexpr (!LEAN) if (item + 1 < nitems) issue_inputs(item + 1, axn, cpn);   // (registers are short later on)
         // cell arithmetic; h goes out first because it is all the other workgroups wait for
         float gi[EPT], gf[EPT], gg[EPT], go[EPT], cn[EPT], hn[EPT];
         bf16_t* hxb = a.hx + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XH;
@@ -380,17 +412,22 @@ __global__ __launch_bounds__(64 * NW, 1) void rec_fwd_kernel(RecFwdArgs a) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) ccarry[e] = cn[e];
     };
-    // (the slice of U_h leaves no room for the loop body twice: one body, and a copy at its end)
-    for (int item = 0; item < nitems; ++item) {
-        do_item(item, ax0, cp0, ax1, cp1);
+    if constexpr (LEAN) {
+        for (int item = 0; item < nitems; ++item) do_item(item, ax0, cp0, ax0, cp0);
+    } else {
+        // (the slice of U_h leaves no room for the loop body twice: one body, and a copy at its end)
+        for (int item = 0; item < nitems; ++item) {
+            do_item(item, ax0, cp0, ax1, cp1);
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
+            for (int e = 0; e < EPT; ++e) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) ax0[e][g] = ax1[e][g];
-            cp0[e] = cp1[e];
+                for (int g = 0; g < 4; ++g) ax0[e][g] = ax1[e][g];
+                cp0[e] = cp1[e];
+            }
         }
     }
     flush_tail();
+    fill_some(1 << 30);                                  // (whatever rounding left over)
 }
 
 // ------------------------------------------------------------------------------ backward
@@ -398,6 +435,9 @@ template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
 __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     constexpr int EPT = 16 / NW;
     constexpr int KSTEPS = 4 * KW / 16;                  // the contraction runs over the 4H gate rows
+    // The loop body twice, the sets of inputs in turn, and the next ones asked for once dE/da has gone out.  One layer, 4096
+    // sequences, us, so / with one body: 288 units 1109 / 1131, 160 592 / 564, 96 336 / 315; wide slices leave no room for two.
+    constexpr bool TWO = KW == 96;
     extern __shared__ float lds[];                       // [NW][4][64][4]
     const int H = PADDED ? a.H : NW * KW;                // (the launcher picks NW and KW from a.H)
     const int B = a.B, T = a.T;
@@ -580,7 +620,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         float cthis[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cthis[e] = !MULTI ? ccarry[e] : curc[e];
-        if (item + 1 < nitems) issue_inputs(item + 1, nxt);
+        if (!TWO && item + 1 < nitems) issue_inputs(item + 1, nxt);   // (wide slices: registers are short later on)
         float dcf[EPT];
         unsigned dav[EPT][2];                             // (i, f) and (g, o) as bf16 pairs: kept for the row-major copy below
         bf16_t* dxb = a.dax + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XA;
@@ -630,6 +670,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             if (SENTINEL) { st_coh_16B(pa, cga); st_coh_16B(pb, cgb); }
             else { *reinterpret_cast<uint4*>(pa) = cga; *reinterpret_cast<uint4*>(pb) = cgb; }
         }
+        if (TWO && item + 1 < nitems) issue_inputs(item + 1, nxt);
         if (SENTINEL) lds_barrier();
         else signal_counter(cnt + i);
         // row-major dE/da for the weight- and input-gradient products, and the carried dE/dc
@@ -645,9 +686,16 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) { dccarry[e] = dcf[e]; ccarry[e] = curcp[e]; }
     };
-    for (int item = 0; item < nitems; ++item) {
-        do_item(item, in0, in1);
-        in0 = in1;
+    if constexpr (TWO) {
+        for (int item = 0; item < nitems; item += 2) {
+            do_item(item, in0, in1);
+            if (item + 1 < nitems) do_item(item + 1, in1, in0);
+        }
+    } else {
+        for (int item = 0; item < nitems; ++item) {
+            do_item(item, in0, in1);
+            in0 = in1;
+        }
     }
 }
 
@@ -714,11 +762,11 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
+template <int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
     constexpr int NW = 4;
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
-    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
+    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
@@ -730,6 +778,20 @@ template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {
     return a.tiles_per_group == 1 ? run_one<KW, S, FULL, false, PADDED>(a, grid, st, launched) : run_one<KW, S, FULL, true, PADDED>(a, grid, st, launched);
 }
+// Narrow layers of many sequences (see rec_tile_units): the forward kernel with two workgroups per CU.  The backward kernel, whose time
+// is the traffic of its operand, gains nothing by that.
+template <int KW>
+hipError_t run_narrow(const RecFwdArgs& a, hipStream_t st, bool* launched) {
+    const int nu = (a.H + 31) / 32, tiles = (a.B + 31) / 32;
+    RecFwdArgs b = a;
+    b.nbg = rec_groups(a.H, tiles, 2);
+    b.tiles_per_group = (tiles + b.nbg - 1) / b.nbg;
+    return run_one<KW, true, false, true, true, true>(b, grid_groups(b.nbg) * nu, st, launched);
+}
+template <int KW>
+hipError_t run_narrow(const RecBwdArgs& a, hipStream_t st, bool* launched) {
+    return run_one<KW, true, false, true, true>(a, grid_groups(a.nbg) * ((a.H + 31) / 32), st, launched);
+}
 template <typename A>
 hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) {
     *launched = false;
@@ -738,7 +800,10 @@ hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) 
         if (sentinel) return a.B % 32 == 0 ? run_multi<256, true, true, false>(a, grid, st, launched) : run_multi<256, true, false, false>(a, grid, st, launched);
         return a.B % 32 == 0 ? run_multi<256, false, true, false>(a, grid, st, launched) : run_multi<256, false, false, false>(a, grid, st, launched);
     }
-    if (!sentinel || a.H <= 512 || !rec_supported(a.H)) return hipSuccess;   // (padded widths: sentinel protocol only)
+    if (!sentinel || !rec_supported(a.H) || (a.H <= 512 && !rec_narrow(a.B, a.H))) return hipSuccess;   // (padded widths: sentinel protocol only)
+#define BLSTM_NARROW(KW) if (a.H <= 4 * KW) return run_narrow<KW>(a, st, launched)
+    BLSTM_NARROW(32); BLSTM_NARROW(64); BLSTM_NARROW(96);
+#undef BLSTM_NARROW
 #define BLSTM_PADDED(KW) if (a.H <= 4 * KW) return run_multi<KW, true, false, true>(a, grid, st, launched)
     BLSTM_PADDED(160); BLSTM_PADDED(192); BLSTM_PADDED(224); BLSTM_PADDED(256);
 #undef BLSTM_PADDED
@@ -748,7 +813,7 @@ hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) 
 }  // namespace
 
 // Supported widths: multiples of 8 up to 1024.  The kernels of this file run those above 512 cells with more sequences than
-// recurrent_tile.hip takes there, on four wavefronts that split the contraction (four batch rows per thread in every variant).
+// recurrent_tile.hip takes there, and some narrow ones (rec_narrow), on four wavefronts that split the contraction (four batch rows per thread in every variant).
 // 1024 has kernels of its own; the others run padded to the next multiple of 128 (H = 320, 50 sequences, when these kernels ran
 // it: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
 // Padded widths above 512 only up to 3072 sequences: beyond, the tiles a workgroup walks backward cost more than the forward
@@ -759,9 +824,9 @@ bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
 bool rec_takes(int T, int B, int H) { return rec_supported(H) && (rec_fenced(H) || (T > 1 && (H <= 512 || B <= 3072))); }
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
 // Batch groups per direction: as many as leave each of the eight XCDs, which get whole groups (map_block), no more than
-// one workgroup per CU (32).
-int rec_groups(int H, int tiles) {
-    const int most = 4 * (32 / ((H + 31) / 32));
+// per_cu workgroups per CU (of 32).
+int rec_groups(int H, int tiles, int per_cu) {
+    const int most = 4 * (32 * per_cu / ((H + 31) / 32));
     return tiles < most ? tiles : most;
 }
 hipError_t launch_fill_u32(unsigned* p, int n, unsigned v, hipStream_t st) {

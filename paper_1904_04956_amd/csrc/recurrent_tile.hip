@@ -462,13 +462,20 @@ hipError_t launch(const A& a, bool sentinel, hipStream_t st, bool* launched) {
 
 }  // namespace
 
+// Widths whose last slice of 64 units would be at most half full, and so many sequences that a workgroup would walk three or more
+// tiles (four above 256 units): the slices of recurrent.hip have no empty part, and its forward kernel two workgroups a CU.  One layer of
+// 21 frames, us, 16-row tiles / recurrent.hip, forward and backward: 96 units, 4096 sequences 360 + 358 / 282 + 315; 160, 2048 314 + 335 / 265 + 293;
+// 200, 2048 397 + 394 / 328 + 406; 288, 2048 479 + 575 / 431 + 606.
+bool rec_narrow(int B, int H) {
+    return H > 64 && H <= 288 && H % 8 == 0 && H % 64 >= 1 && H % 64 <= 32 && cut(B, H, 64, 1).per_group > (H <= 256 ? 2 : 3);
+}
 // Slices of 32 units for a layer of one such slice, and while that leaves every workgroup a CU and a tile of its own; else of 64: half
 // of the operand's bytes per cell, but their weights fit the registers up to 512 cells only.  (Of 32 with two workgroups a CU where the last slice
 // of 64 would be at most half full and take two tiles a workgroup: 136 cells, 700 sequences 84 + 130 us against 127 + 159.)
 // Beyond 512 cells several tiles of 32 units a workgroup lose to recurrent.hip's 32 x 32 (1024 cells, 512 sequences 450 / 545 us a layer
 // against 348 / 387; 128 sequences 121 / 145 against 96 / 115).
 int rec_tile_units(int B, int H) {
-    if (!rec_supported(H)) return 0;
+    if (!rec_supported(H) || rec_narrow(B, H)) return 0;
     if (H <= 32 || cut(B, H, 32, 1).per_group == 1) return 32;
     const int last = H % 64;
     if (last >= 1 && last <= 32 && H <= 384 && cut(B, H, 64, 1).per_group > 1 && cut(B, H, 32, 2).per_group == 1) return 32;

@@ -282,3 +282,15 @@ def test_workgroups_on_sixteen_row_tiles(recorder, B, H, units, fwd, bwd):
             out += [[names[i].split("kernelILi")[1][0], rec.recorder_grid(i, 0)] for i in range(len(names)) if "tile_rec" in names[i]]
     """)
     assert got == [[str(units), fwd], [str(units), bwd]]
+
+
+@pytest.mark.parametrize("B,H,narrow", [(2048, 96, False), (2049, 96, True), (4096, 104, False), (4096, 64, False), (1280, 136, False), (1281, 160, True),
+                                        (1025, 200, True), (1152, 288, False), (1153, 264, True), (4096, 328, False)])
+def test_widths_with_an_empty_half_of_their_last_slice(recorder, B, H, narrow):
+    # the forward kernel of recurrent.hip that marks dE/da's exchange copies on the side runs these
+    f, b = recorder(f"""
+        rec.recorder_occupancy(b"rec_", 4)
+        m = Model(T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        out = [[count(n, "14rec_fwd") + count(n, "14rec_bwd"), count(n, "tile_rec_"), count(n, "fill_u128")] for n in (launches(m.forward), launches(m.backward))]
+    """)
+    assert f == ([1, 0, 1] if narrow else [0, 1, 1]) and b == ([1, 0, 0] if narrow else [0, 1, 0])

@@ -331,6 +331,17 @@ def test_kernels_for_few_sequences_bf16(dims):
 
 
 @pytest.mark.parametrize("dims", [
+    dict(T=3, B=1300, D=8, H=136, L=2, P=0, V=20),          # 41 tiles over 48 groups, the last one partial
+    dict(T=4, B=1290, D=24, H=160, L=1, P=16, V=40),        # whole slices
+    dict(T=3, B=2090, D=8, H=72, L=1, P=0, V=20),           # eight units in the last slice
+    dict(T=3, B=1160, D=8, H=264, L=1, P=0, V=20),          # several tiles a workgroup in both passes
+    dict(T=2, B=4100, D=8, H=96, L=1, P=0, V=20),
+])
+def test_narrow_layers_of_many_sequences_bf16(dims):
+    check_step(dims, 1, seed=91, theta_scale=1.0)
+
+
+@pytest.mark.parametrize("dims", [
     dict(T=3, B=290, D=8, H=512, L=1, P=0, V=20),           # ten tiles: one per workgroup instead of one or two
     dict(T=4, B=1030, D=8, H=512, L=1, P=0, V=20),          # 33 tiles over sixteen groups, the last one empty
     dict(T=3, B=1600, D=8, H=256, L=1, P=0, V=20),
