@@ -382,18 +382,17 @@ void plan_f32(const GemmDesc& d, bool direct, int Ne, int Nr, GemmPlan* p) {
     search(direct ? 2 : 1);
 }
 
-// Estimated time (us) of a slab of `tiles` bf16 tiles spread over the CUs.  64x64 with three buffers: three workgroups on a CU
-// hide most of each other's load latency, 0.34 us a slab alone and 0.225 of matrix-core and LDS time each when they do not; 128x64:
-// 0.53 and 0.37, two a CU; 128x128: 0.7, a third less where two share a CU.  Measured, us, 128x128 / 128x64 / 64x64 (X W^T, K = 1024):
-// 168 x 2048 twice 15.8 / 11.8 / 9.1, 5376 x 256 15.3 / 11.2 / 9.8, 1344 x 2048 twice 21.1 / 23.5 / 22.7; (dA W, K = 2048 twice)
-// 1050 x 640, K = 1280 33.3 / 24.0 / 16.7 (split in five: 17.3), 1344 x 1024 47.0 / 36.5 / 28.2, 2688 x 1024 48.4 / 39.8 /
-// 41.6, 3633 x 1024 51.2 / 45.0 / 56.9, 5376 x 1024 57.3 / 71.6 / 72.5.
+// Estimated time (us) of a slab of `tiles` bf16 tiles spread over the CUs: it grows by whole workgroups on the fullest CU.  64x64 with
+// three buffers: one hides no load latency (0.335), several share the CU's matrix cores and LDS (measured 0.45, 0.64, 0.86, 1.04 for two to
+// five); 128x64: two a CU, 0.47 alone and 0.65 for both, a third in a round of its own; 128x128: 0.7, a third less where two share a CU.
+// X W^T and dA W of 84 to 8000 rows, 256 to 4096 columns and contractions of 256 to 32000 (270 products, all tiles and parts): the
+// chosen plan takes 1.05 times the best one's time on average, where an estimate that grows smoothly took 1.08 and left long
+// contractions unsplit, e.g. dA W, K = 4096 twice, us, 128x64 unsplit / 128x128 in two parts: 1660 x 2048 85 / 68, 672 x 2048 (64x64) 61 / 38 (in five).
 double bf16_slab(int tile, double tiles) {
-    const double x = tiles / 256.0;
-    auto most = [](double a, double b) { return a > b ? a : b; };
-    if (tile == GEMM_TILE_64) return most(0.34, 0.225 * x);
-    if (tile == GEMM_TILE_128X64) return x <= 2.0 ? most(0.53, 0.37 * x) : 1e9;
-    return x <= 1.0 ? 0.7 : 0.462 * (double)(long long)(x + 0.999999);
+    const int most = (int)((tiles + 255.0) / 256.0);      // workgroups on a CU
+    if (tile == GEMM_TILE_64) return most <= 1 ? 0.335 : 0.215 * most;
+    if (tile == GEMM_TILE_128X64) return most / 2 * 0.65 + most % 2 * 0.47;
+    return most <= 1 ? 0.7 : 0.462 * most;
 }
 
 // How a product of this shape is run.  allow_r: the 256x128 direct tile may be chosen (bf16 operands in one of its forms).
@@ -480,7 +479,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     const double tile_bytes = (double)batch * d.M * Nr * sizeof(float);
     auto estimate = [&](int tile, int s) {
         const double t = bf16_slab(tile, tiles(tile) * s) * ((slabs + s - 1) / s);
-        return s == 1 ? t : t + 4.5 + 2.0 * s * tile_bytes / 4e6;
+        return s == 1 ? t : t + 4.5 + 0.42e-6 * s * tile_bytes;
     };
     int most = 1;
     if (d.long_parts) {
@@ -496,7 +495,7 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
             for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
                 if (tile != GEMM_TILE_128 && !all) continue;
                 double t = estimate(tile, s);
-                if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.3;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
+                if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.2;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
                 if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
             }
         }

@@ -294,3 +294,34 @@ def test_widths_with_an_empty_half_of_their_last_slice(recorder, B, H, narrow):
         out = [[count(n, "14rec_fwd") + count(n, "14rec_bwd"), count(n, "tile_rec_"), count(n, "fill_u128")] for n in (launches(m.forward), launches(m.backward))]
     """)
     assert f == ([1, 0, 1] if narrow else [0, 1, 1]) and b == ([1, 0, 0] if narrow else [0, 1, 0])
+
+
+GEMM = """
+        def products(call):
+            names = launches(call)
+            return [[names[i].split("kernelI")[1].split("EEE")[0], rec.recorder_grid(i, 0), rec.recorder_grid(i, 1)] for i in range(len(names)) if "gemm_kernel" in names[i]]
+"""
+
+
+@pytest.mark.parametrize("B,H,tiles", [(32, 1024, 96), (79, 1024, 208), (100, 512, 136)])
+def test_input_gradients_with_a_long_contraction_are_split(recorder, B, H, tiles):
+    # 128x128 tiles in two or more parts: unsplit on smaller tiles these took 1.2 to 1.6 times as long
+    (dx,) = recorder(GEMM + f"""
+        m = Model(T=21, B={B}, D=8, H={H}, L=2, P=0, V=20)
+        launches(m.forward)
+        out = products(m.backward)
+    """)
+    assert dx[0].startswith("tfLb0ELb1ELi2ELi2ELi2E") and dx[1] == tiles and dx[2] >= 2
+
+
+@pytest.mark.parametrize("M,tile,grid,parts", [
+    (16384, "tfLb0ELb1ELi4ELi2ELi4E", 64, 4),                 # 256x256, up to one workgroup per CU
+    (16385, "tfLb0ELb1ELi2ELi2ELi2E", 258, 4),                # 65 of them fill no whole rounds
+    (21021, "tfLb0ELb1ELi4ELi2ELi4E", 83, 3), (61184, "tfLb0ELb1ELi4ELi2ELi4E", 239, 2),   # whole rounds of them
+    (61185, "ttLb0ELb1ELi4ELi2ELi2E", 480, 1),                # 256x128, unsplit
+])
+def test_tiles_and_parts_of_dz(recorder, M, tile, grid, parts):
+    dz = recorder(GEMM + f"""
+        out = [p for p in products(Model(T=1, B={M}, D=8, H=8, L=1, P=256, V=13001).xent) if "Lb0ELb1" in p[0]][0]   # (the dA W form)
+    """)
+    assert dz[0].startswith(tile) and dz[1:] == [grid, parts]
