@@ -64,17 +64,42 @@ def test_both_entry_points_give_the_same_bits(dims, mode):
             out.append([t.cpu().clone() for t in (lrn.loss, lrn.dz, lrn.grad)])
         for name, a, b in zip(("loss", "dz", "grad"), *out):
             assert torch.equal(a, b), (name, float((a.float() - b.float()).abs().max()), float(a.float().abs().max()))
-        # and they are the softmax block's results
-        off, n = bl.blstm_param_offset(lrn.ctx, 0, 0, bl.BLSTM_WS)
-        w = lrn.theta_fwd[off:off + n].double().view(dims["V"], -1).requires_grad_()
-        b = lrn.theta_fwd[off + n:].double().requires_grad_()
-        z = lrn.z.double().view(-1, lrn.zdim).requires_grad_()
-        loss = torch.nn.functional.cross_entropy(z @ w.t() + b, lrn.labels.view(-1).long())
-        loss.backward()
-        loss = loss.detach()
-        tol = 2e-2 if mode == 1 else 1e-4
-        assert abs(lrn.loss_value() - float(loss)) <= tol * float(loss)
-        for got, ref in ((lrn.dz, z.grad), (lrn.grad[off:off + n], w.grad), (lrn.grad[off + n:], b.grad)):
-            assert float((got.double().view(-1) - ref.reshape(-1)).abs().max()) <= tol * float(ref.abs().max())
+        check_results(lrn, dims, mode)
     finally:
         lrn.close()
+
+
+@pytest.mark.parametrize("B,V", [(1001, 13001), (780, 13001)])
+def test_dz_on_256x256_tiles_of_many_frames(B, V):
+    # 83 of these tiles in three parts, the last row tile and the last slab partial, and 64 in four
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    from paper_1904_04956_amd.harness import Learner
+    dims = dict(T=21, B=B, D=8, H=8, L=1, P=256, V=V)
+    lrn = Learner(mode=1, defer_softmax_wgrad=False, **dims)
+    try:
+        g = torch.Generator(device="cuda").manual_seed(4963)
+        lrn.theta_fwd.copy_(0.1 * torch.randn(lrn.n, device="cuda", generator=g))
+        lrn.z.copy_(torch.randn(lrn.z.shape, device="cuda", generator=g))
+        lrn.labels.copy_(torch.randint(0, V, lrn.labels.shape, device="cuda", generator=g))
+        bl.softmax_xent_fwd_bwd(lrn.ctx, lrn.theta_fwd, lrn.z, lrn.labels, lrn.loss, lrn.dz, lrn.grad)
+        check_results(lrn, dims, 1)
+    finally:
+        lrn.close()
+
+
+def check_results(lrn, dims, mode):
+    # the softmax block's results
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    off, n = bl.blstm_param_offset(lrn.ctx, 0, 0, bl.BLSTM_WS)
+    w = lrn.theta_fwd[off:off + n].double().view(dims["V"], -1).requires_grad_()
+    b = lrn.theta_fwd[off + n:].double().requires_grad_()
+    z = lrn.z.double().view(-1, lrn.zdim).requires_grad_()
+    loss = torch.nn.functional.cross_entropy(z @ w.t() + b, lrn.labels.view(-1).long())
+    loss.backward()
+    loss = loss.detach()
+    tol = 2e-2 if mode == 1 else 1e-4
+    assert abs(lrn.loss_value() - float(loss)) <= tol * float(loss)
+    for got, ref in ((lrn.dz, z.grad), (lrn.grad[off:off + n], w.grad), (lrn.grad[off + n:], b.grad)):
+        assert float((got.double().view(-1) - ref.reshape(-1)).abs().max()) <= tol * float(ref.abs().max())
