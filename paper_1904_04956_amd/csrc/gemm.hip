@@ -386,12 +386,12 @@ void plan_f32(const GemmDesc& d, bool direct, int Ne, int Nr, GemmPlan* p) {
 // three buffers: one hides no load latency (0.335), several share the CU's matrix cores and LDS (measured 0.45, 0.64, 0.86, 1.04 for two to
 // five); 128x64: two a CU, 0.47 alone and 0.65 for both, a third in a round of its own; 128x128: 0.7, a third less where two share a CU.
 // X W^T and dA W of 84 to 8000 rows, 256 to 4096 columns and contractions of 256 to 32000 (270 products, all tiles and parts): the
-// chosen plan takes 1.05 times the best one's time on average, where an estimate that grows smoothly took 1.08 and left long
+// chosen plan takes 1.024 times the best one's time on average, where an estimate that grew smoothly took 1.05 and left long
 // contractions unsplit, e.g. dA W, K = 4096 twice, us, 128x64 unsplit / 128x128 in two parts: 1660 x 2048 85 / 68, 672 x 2048 (64x64) 61 / 38 (in five).
 double bf16_slab(int tile, double tiles) {
     const int most = (int)((tiles + 255.0) / 256.0);      // workgroups on a CU
     if (tile == GEMM_TILE_64) return most <= 1 ? 0.335 : 0.215 * most;
-    if (tile == GEMM_TILE_128X64) return most / 2 * 0.65 + most % 2 * 0.47;
+    if (tile == GEMM_TILE_128X64) return most / 2 * 0.644 + most % 2 * 0.47;
     return most <= 1 ? 0.7 : 0.462 * most;
 }
 
@@ -493,9 +493,10 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
         for (int s = first; s <= last; ++s) {
             if (s > first && (slabs / s < 4 || need_of(s) > d.partial_bytes || need_of(s) > ((size_t)256 << 20))) break;
             for (int tile : {GEMM_TILE_128, GEMM_TILE_64, GEMM_TILE_128X64}) {
-                if (tile != GEMM_TILE_128 && !all) continue;
+                // (more than one a CU in many short parts: 336 x 256, K = 32000 2 us slower on 64x64 in 21 than on 128x128 in 32)
+                if (tile != GEMM_TILE_128 && (!all || (s > 16 && tiles(tile) * s > 256.0))) continue;
                 double t = estimate(tile, s);
-                if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.2;   // (336 x 256, K = 32000: 21.9 in 32 parts, 24.4 on 64x64 in 16)
+                if (s > 1 && most > 1) t *= tile == GEMM_TILE_128 ? 12.0 / 11.0 : 1.2;
                 if (best == 0.0 || t < best) { best = t; p.tile = tile; p.splits = s; p.partial_bytes = need_of(s); }
             }
         }
