@@ -23,7 +23,7 @@ int fast_flags(const void* p, long long ld, long long stride, int batch, bool ro
 }
 
 // ---- direct-mode kernels: bf16 operands, unguarded, forms X W^T, dA W and dA^T X -------------------------------
-// variant 0: 128x128 tile, two LDS buffers, two workgroups per CU; 1: 128x128, three buffers (launches of at most one
+// variant 0: 128x128 tile, two LDS buffers, two workgroups per CU; 1: 128x128, three buffers (dA^T X, launches of at most one
 // workgroup per CU); 2: 256x128 tile, one buffer, fragments in registers, two workgroups per CU; 3: 256x256 tile on
 // eight wavefronts, two buffers, one workgroup per CU (the dA W form only: the softmax layer's input gradient).  X W^T and
 // dA W also 4: 64x64, three buffers, three workgroups per CU; 5: 128x64, three buffers, two; 6: 128x128, one buffer, three.
@@ -189,7 +189,7 @@ inline bool direct_form(const GemmDesc& d) { return !d.add && !(d.atrans && !d.b
 // offsets in 32 bits and (two segments) common leading dimensions.  WHOLE: only whole tiles and slabs.  EDGE, direct: any M,
 // N and K whose 16-byte groups lie in memory: a row-fast operand's rows come in whole groups or it is padded to them; so does a
 // k-fast operand's contraction, unless it is a padded A and B is row-fast (whose k-rows beyond the end are replaced by
-// zeros).  EDGE, staged (float operands, one segment or whole slabs of the first): any K.
+// zeros).  EDGE, staged (X W^T, float operands, one segment or whole slabs of the first): any K.
 // Measured: the products of the paper-shaped step at 173 sequences 1.72 ms guarded, 0.82 ms EDGE.
 template <typename TI>
 int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n, bool direct) {
@@ -203,6 +203,8 @@ int run_mode(const GemmDesc& d, const Params& P, int tile_m, int tile_n, bool di
         if (d.seg[s].lda * (long long)sizeof(TI) * 64 > 0x3FFFFFFF || d.seg[s].ldb * (long long)sizeof(TI) * 64 > 0x3FFFFFFF) return GUARDED;
         if (d.seg[s].K % bk) whole = false;
     }
+    const bool loops = direct || (!d.atrans && !d.btrans);   // (of the staged forms X W^T alone has unguarded loops)
+    if (!loops) return GUARDED;
     if (whole) return WHOLE;
     if ((d.atrans && d.M % VEC && !d.a_pad) || (d.btrans && d.N % VEC && d.Npad == 0)) return GUARDED;
     if (!direct) return sizeof(TI) == 4 && (d.nseg == 1 || d.seg[0].K % bk == 0) ? EDGE : GUARDED;     // (only the very last slab may be a part)
@@ -507,8 +509,8 @@ GemmPlan make_plan(const GemmDesc& d, bool allow_r) {
     // 222 / 97 (P = 66, V = 1500: 110 / 47 in six); in float, with eight and 13 parts, 119 / 112.
     if (d.guarded_parts) search(first, last, false);
     search(d.guarded_parts ? p.splits : first, d.guarded_parts ? p.splits : last, any_tile);
-    // at most one 128x128 workgroup per CU: run the loads further ahead (three LDS buffers, or four register sets)
-    p.deep = p.tile == GEMM_TILE_128 && t128 * p.splits <= 256;
+    // dA^T X, at most one 128x128 workgroup per CU: run the loads further ahead (three LDS buffers)
+    p.deep = p.tile == GEMM_TILE_128 && d.atrans && d.btrans && t128 * p.splits <= 256;
     return p;
 }
 

@@ -52,7 +52,7 @@ enum GemmTile { GEMM_TILE_128 = 0,        // 128x128, every element type and sha
                 GEMM_TILE_RESIDENT = 6 }; // a workgroup keeps 128 columns' weights and walks down the rows, bf16, contractions of up to 256
 struct GemmPlan {
     int tile;                 // a GemmTile
-    bool deep;                // bf16, 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)
+    bool deep;                // bf16 dA^T X, 128x128 tile with the loads further ahead (launches of at most one workgroup per CU)
     int splits;
     size_t partial_bytes;     // scratch the split needs (0 when splits == 1)
 };
@@ -64,8 +64,8 @@ size_t noalloc_partial_bytes(int M, int N, int K, DType in_type);
 // Validates nothing (the caller's shapes are trusted); returns the launch status.
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t stream);
 // n independent products of the A^T B form (atrans and btrans, operands of one type, float result, optional row sums, no
-// bias, one segment): those the grouped kernel can take (gemm_group_ok) in one launch, the others one launch each.  A
-// grouped launch never splits along K and uses no scratch.
+// bias, one segment): those the grouped kernel can take (gemm_group_ok) in one launch, which never splits along K, the others one
+// by one.  So may the former be where they are faster split, each in its descriptor's scratch.
 bool gemm_group_ok(const GemmDesc* d, int n);
 hipError_t launch_gemm_group(const GemmDesc* d, int n, hipStream_t stream);
 

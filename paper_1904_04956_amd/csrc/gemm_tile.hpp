@@ -5,14 +5,14 @@
 // row (64 bf16 or 32 float) lives in LDS, rows XOR-swizzled at chunk granularity so that loads,
 // stores and the MFMA fragment reads all spread over the banks.  Operands whose contraction index
 // is the slow one in memory ("transposed") are loaded along their fast index, so all three forms
-// of a training step's products (X W^T, dA W, dA^T X) run through the same inner loop: 16-bit ones
-// of full tiles lie in LDS as they lie in memory and are transposed by the LDS read itself
-// (ds_read_b64_tr_b16); the others are transposed in registers on the way to LDS.
+// of a training step's products (X W^T, dA W, dA^T X) run through the same inner loop: aligned ones
+// lie in LDS as they lie in memory, 16-bit ones are transposed by the LDS read itself
+// (ds_read_b64_tr_b16), float ones read word by word; the others are transposed in registers on the way to LDS.
 //
 // Two ways of bringing a slab into LDS:
-//   direct   bf16 operands, aligned: global_load_lds_dwordx4 writes the slab straight
+//   direct   aligned operands: global_load_lds_dwordx4 writes the slab straight
 //            into LDS in the swizzled layout (each lane fetches the chunk that belongs at its LDS
-//            slot).  Tiles: 256x128 on four wavefronts with ONE LDS buffer, a slab's fragments all
+//            slot).  bf16: 256x128 on four wavefronts with ONE LDS buffer, a slab's fragments all
 //            read into registers before the next slab's loads overwrite it, two workgroups per CU
 //            taking turns on the matrix cores (the workhorse: 3/4 of the operand bytes of 128x128
 //            per flop, and the vector-memory path of a CU, about 45 bytes per clock from L2, is what
@@ -20,9 +20,10 @@
 //            too few large tiles, or with one buffer and three workgroups per CU for short contractions;
 //            64x64 and 128x64 with three buffers for products that leave CUs idle with larger tiles;
 //            256x256 on eight wavefronts for a handful of tiles with a very long contraction.
-//   staged   every other case (float operands, unaligned rows): global loads into
-//            registers two or four slabs ahead, LDS stores, double-buffered LDS.
-// Both run ragged shapes with their unguarded loops (EDGE below); the guarded loads are left for unaligned rows.
+//            float: 128x128 and 64x64 with two buffers (gemm_f32.hip).
+//   staged   128x128 tiles, every other case (unaligned rows, and X W^T with an addend): global loads into
+//            registers two slabs ahead, LDS stores, double-buffered LDS.
+// Ragged shapes run unguarded loops (EDGE below); the guarded loads are left for unaligned rows.
 // Products with a small output and a long contraction are split along K over blockIdx.y into float
 // partial tiles that a second kernel sums in a fixed order.  Several independent products of one
 // form can share one launch (gemm_group_kernel).
@@ -180,51 +181,16 @@ __device__ __forceinline__ void gload_kfast_fast(uint4 (&r)[NCH], const char* ba
         r[i] = make_uint4(v[0], v[1], v[2], v[3]);
     }
 }
-template <typename T, int NCH, int PR>
-__device__ __forceinline__ void gload_rowfast_fast(uint4 (&r)[NCH], const char* base, long long kstep, uint32_t voff) {
-    constexpr int VEC = Vec<T>::N;
-#pragma unroll
-    for (int pass = 0; pass < NCH / 4; ++pass) {
-        const char* pb = base + pass * PR * (int)sizeof(T) + voff;
-        if (sizeof(T) == 4) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(pb + i * kstep);
-                r[pass * 4 + i] = make_uint4(v[0], v[1], v[2], v[3]);
-            }
-        } else {
-            u32x2_t w[VEC];
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) w[i] = *reinterpret_cast<const u32x2_t*>(pb + i * kstep);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) r[pass * 4 + q] = make_uint4(w[2 * q][0], w[2 * q][1], w[2 * q + 1][0], w[2 * q + 1][1]);
-        }
-    }
-}
 
-// 16-bit operands whose non-contracted index is the fast one in memory, unguarded: the slab
+// 16-bit operands whose non-contracted index is the fast one in memory, direct: the slab
 // stays in LDS as it lies in memory, [k][row] with 16-byte chunks of eight rows, and the LDS read that
 // feeds the matrix cores transposes it (ds_read_b64_tr_b16: sixteen lanes read a 4 x 16 block of 16-bit
-// elements, lane j of them receives column j).  No transposes in registers, plain 16-byte loads and stores.
-// CPR = chunks per k-row.  A thread owns chunk tid % CPR of the k-rows tid / CPR + 16 i.
+// elements, lane j of them receives column j).  CPR = chunks per k-row.
 // Swizzle: the 32-byte pair of chunks p of k-row k sits at pair p ^ tr_swz(k), so that the four k-rows
 // a group of sixteen lanes reads, and the neighbouring group's, fall on different banks (a k-row of 64 rows is half of the
 // banks wide and has four pairs).
 template <int CPR>
 __device__ __forceinline__ int tr_swz(int k) { return CPR == 8 ? (k & 2) : (k & 3) << 1; }
-template <int NCH>
-__device__ __forceinline__ void gload_tr(uint4 (&r)[NCH], const char* base, long long pass_step, uint32_t voff) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(base + voff + i * pass_step);
-        r[i] = make_uint4(v[0], v[1], v[2], v[3]);
-    }
-}
-template <int NCH, int CPR>
-__device__ __forceinline__ void sstore_tr(uint4* s, const uint4 (&r)[NCH], int soff) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) s[soff + i * 16 * CPR] = r[i];
-}
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 // eight consecutive k of one row: two transposing reads, k-rows kb .. kb+3 and kb+4 .. kb+7 (ROWB bytes per k-row)
@@ -310,6 +276,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     constexpr bool FAST = MODE != GUARDED;
     constexpr int D = 2;
     static_assert(MODE != EDGE || NS > 0 || sizeof(TI) == 4, "staged 16-bit operands are guarded or whole");
+    static_assert(NS > 0 || MODE == GUARDED || (!AT && !BT), "of the staged forms X W^T alone has unguarded loops");
     static_assert(MODE != EDGE || NS > 0 || WN == 2, "the staged edge form uses the 256-thread guarded loads for its last slab");
     static_assert(NS == 0 || FAST, "direct mode is built for the unguarded forms");
     static_assert(NS != 1 || sizeof(TI) == 2, "one buffer: 16-bit operands");
@@ -354,8 +321,7 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     // Row sums of A ride along on the vector ALU, which the loop leaves mostly idle: the waves of the first
     // half of the workgroups of the first tile column add up the fragments they feed to the matrix cores
     // (a lane holds eight consecutive k of one row; lanes l and l + 32 hold the two halves of a sub-step).
-    // (RS is instantiated for the 128x128 shape with both operands transposed only: the
-    // weight-gradient products are the ones that need row sums.)
+    // (RS goes with both operands transposed: the weight-gradient products are the ones that need row sums.)
     constexpr int NRS = RS ? TM : 1;
     const bool do_rs = RS && P.rowsum != nullptr && tn == 0 && wn == 0;
     float rs[NRS];
@@ -411,22 +377,14 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
         roff_a[q] = arow * CHUNKS + ((2 * q + (lane >> 5)) ^ swz(arow));
         roff_b[q] = brow * CHUNKS + ((2 * q + (lane >> 5)) ^ swz(brow));
     }
-    // per-thread global byte offsets of the unguarded loads
+    // per-thread global byte offsets of the unguarded staged loads
     constexpr int ES = (int)sizeof(TI);
-    const uint32_t voff_a = AT ? (uint32_t)(kch * VEC * a0.ld * ES + rsub * ES)
-                               : (uint32_t)((tid >> 3) * a0.ld * ES + (tid & 7) * 16);
-    const uint32_t voff_b = BT ? (uint32_t)(kch * VEC * b0.ld * ES + rsub * ES)
-                               : (uint32_t)((tid >> 3) * b0.ld * ES + (tid & 7) * 16);
+    const uint32_t voff_a = (uint32_t)((tid >> 3) * a0.ld * ES + (tid & 7) * 16), voff_b = (uint32_t)((tid >> 3) * b0.ld * ES + (tid & 7) * 16);
 
-    // transposing-read form (16-bit, unguarded): per-thread store offset, load offset, and the byte offsets of the
+    // transposing-read form (16-bit, direct): the byte offsets of the
     // fragment reads of each 32-row block (lane group g = lane / 16: rows 16 (g & 1) .., k-rows 8 (g / 2) ..)
-    constexpr bool TRP = FAST && sizeof(TI) == 2;
+    constexpr bool TRP = NS > 0 && sizeof(TI) == 2;
     constexpr int CPR_A = BM / VEC, CPR_B = BN / VEC;   // 16-byte chunks per k-row
-    static_assert(NS > 0 || !TRP || (NT / CPR_A == 16 && NT / CPR_B == 16), "a pass of loads covers sixteen k-rows");
-    auto tr_soff = [&](auto cpr) { const int kt = tid / cpr, mc = tid % cpr; return kt * cpr + ((((mc >> 1) ^ tr_swz<cpr>(kt)) << 1) | (mc & 1)); };
-    const int soff_ta = tr_soff(std::integral_constant<int, CPR_A>{}), soff_tb = tr_soff(std::integral_constant<int, CPR_B>{});
-    const uint32_t voff_ta = (uint32_t)((tid / CPR_A) * a0.ld * ES + (tid % CPR_A) * 16);
-    const uint32_t voff_tb = (uint32_t)((tid / CPR_B) * b0.ld * ES + (tid % CPR_B) * 16);
     int troff_a[TM], troff_b[TN];
     {
         const int g = lane >> 4, li = lane & 15, sw_a = tr_swz<CPR_A>(li >> 2), sw_b = tr_swz<CPR_B>(li >> 2);
@@ -639,12 +597,10 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     if constexpr (STE) {
 #pragma unroll
         for (int i = 0; i < NCA; ++i)
-            voe_a[i] = AT ? (uint32_t)((kch * VEC + (i & 3)) * a0.ld * ES + min(rsub + (i >> 2) * PR, ((P.M + 3) & ~3) - 4 - row0) * ES)
-                          : (uint32_t)(min((tid >> 3) + RP * i, P.M - 1 - row0) * a0.ld * ES + (tid & 7) * 16);
+            voe_a[i] = (uint32_t)(min((tid >> 3) + RP * i, P.M - 1 - row0) * a0.ld * ES + (tid & 7) * 16);
 #pragma unroll
         for (int i = 0; i < NCB; ++i)
-            voe_b[i] = BT ? (uint32_t)((kch * VEC + (i & 3)) * b0.ld * ES + min(rsub + (i >> 2) * PR, ((P.N + 3) & ~3) - 4 - col0) * ES)
-                          : (uint32_t)(min((tid >> 3) + RP * i, P.N - 1 - col0) * b0.ld * ES + (tid & 7) * 16);
+            voe_b[i] = (uint32_t)(min((tid >> 3) + RP * i, P.N - 1 - col0) * b0.ld * ES + (tid & 7) * 16);
     }
     auto gload = [&](int it, const bool inner, uint4 (&ra)[NCA], uint4 (&rb)[NCB]) __attribute__((always_inline)) {   // inner: surely not the last slab
         const bool s = it >= ntiles[0];
@@ -655,26 +611,22 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
         if constexpr (STE) {
             const int K = s ? K1 : K0;
             if (inner || k0 + BK <= K) {
-                const char* pa = static_cast<const char*>(oa.p) + (AT ? ((long long)k0 * oa.ld + row0) * ES : ((long long)row0 * oa.ld + k0) * ES);
-                const char* pb = static_cast<const char*>(ob.p) + (BT ? ((long long)k0 * ob.ld + col0) * ES : ((long long)col0 * ob.ld + k0) * ES);
+                const char* pa = static_cast<const char*>(oa.p) + ((long long)row0 * oa.ld + k0) * ES;
+                const char* pb = static_cast<const char*>(ob.p) + ((long long)col0 * ob.ld + k0) * ES;
 #pragma unroll
                 for (int i = 0; i < NCA; ++i) { const u32x4_t v = *reinterpret_cast<const u32x4_t*>(pa + voe_a[i]); ra[i] = make_uint4(v[0], v[1], v[2], v[3]); }
 #pragma unroll
                 for (int i = 0; i < NCB; ++i) { const u32x4_t v = *reinterpret_cast<const u32x4_t*>(pb + voe_b[i]); rb[i] = make_uint4(v[0], v[1], v[2], v[3]); }
             } else {
-                if constexpr (AT) gload_rowfast<TI, NCA>(ra, oa, row0, K, k0, tid); else gload_kfast<TI, NCA>(ra, oa, row0, K, k0, tid);
-                if constexpr (BT) gload_rowfast<TI, NCB>(rb, ob, col0, K, k0, tid); else gload_kfast<TI, NCB>(rb, ob, col0, K, k0, tid);
+                gload_kfast<TI, NCA>(ra, oa, row0, K, k0, tid);
+                gload_kfast<TI, NCB>(rb, ob, col0, K, k0, tid);
             }
         } else if constexpr (FAST) {
             // (both segments of a two-segment product share their leading dimensions in this mode)
             const char* pa = static_cast<const char*>(oa.p);
             const char* pb = static_cast<const char*>(ob.p);
-            if constexpr (AT && TRP) gload_tr<NCA>(ra, pa + ((long long)k0 * oa.ld + row0) * ES, 16 * oa.ld * ES, voff_ta);
-            else if constexpr (AT) gload_rowfast_fast<TI, NCA, PR>(ra, pa + ((long long)k0 * oa.ld + row0) * ES, oa.ld * ES, voff_a);
-            else    gload_kfast_fast<TI, NCA>(ra, pa + ((long long)row0 * oa.ld + k0) * ES, RP * oa.ld * ES, voff_a);
-            if constexpr (BT && TRP) gload_tr<NCB>(rb, pb + ((long long)k0 * ob.ld + col0) * ES, 16 * ob.ld * ES, voff_tb);
-            else if constexpr (BT) gload_rowfast_fast<TI, NCB, PR>(rb, pb + ((long long)k0 * ob.ld + col0) * ES, ob.ld * ES, voff_b);
-            else    gload_kfast_fast<TI, NCB>(rb, pb + ((long long)col0 * ob.ld + k0) * ES, RP * ob.ld * ES, voff_b);
+            gload_kfast_fast<TI, NCA>(ra, pa + ((long long)row0 * oa.ld + k0) * ES, RP * oa.ld * ES, voff_a);
+            gload_kfast_fast<TI, NCB>(rb, pb + ((long long)col0 * ob.ld + k0) * ES, RP * ob.ld * ES, voff_b);
         } else {
             const int K = s ? K1 : K0;
             if constexpr (AT) gload_rowfast<TI, NCA>(ra, oa, row0, K, k0, tid);
@@ -686,11 +638,9 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
     auto sstore = [&](int buf, const uint4 (&ra)[NCA], const uint4 (&rb)[NCB]) {
         uint4* a_s = smem + buf * STAGE;
         uint4* b_s = a_s + BM * CHUNKS;
-        if constexpr (AT && TRP) sstore_tr<NCA, CPR_A>(a_s, ra, soff_ta);
-        else if constexpr (AT) sstore_rowfast_off<TI, NCA, PR>(a_s, ra, soff_r);
+        if constexpr (AT) sstore_rowfast_off<TI, NCA, PR>(a_s, ra, soff_r);
         else sstore_kfast_off<NCA, RP>(a_s, ra, soff_k);
-        if constexpr (BT && TRP) sstore_tr<NCB, CPR_B>(b_s, rb, soff_tb);
-        else if constexpr (BT) sstore_rowfast_off<TI, NCB, PR>(b_s, rb, soff_r);
+        if constexpr (BT) sstore_rowfast_off<TI, NCB, PR>(b_s, rb, soff_r);
         else sstore_kfast_off<NCB, RP>(b_s, rb, soff_k);
     };
     if (nslab > 0) {
@@ -977,11 +927,13 @@ hipError_t launch_kernel(const Params& P, dim3 grid, hipStream_t stream) {
 // ---- register-staged kernels, 128x128 tiles: what the direct mode does not take ------------------------------------
 template <typename TI, typename TO, bool AT, bool BT, bool RS>
 hipError_t launch_staged_rs(const Params& P, int mode, dim3 grid, hipStream_t stream) {
-    if (mode == WHOLE) return launch_kernel<TI, TO, AT, BT, 2, 2, 2, WHOLE, RS>(P, grid, stream);
-    if constexpr (sizeof(TI) == 4) {
-        if (mode == EDGE) return launch_kernel<TI, TO, AT, BT, 2, 2, 2, EDGE, RS>(P, grid, stream);
+    if constexpr (!AT && !BT) {
+        if (mode == WHOLE) return launch_kernel<TI, TO, AT, BT, 2, 2, 2, WHOLE, RS>(P, grid, stream);
+        if constexpr (sizeof(TI) == 4) {
+            if (mode == EDGE) return launch_kernel<TI, TO, AT, BT, 2, 2, 2, EDGE, RS>(P, grid, stream);
+        }
     }
-    if (mode == EDGE) return hipErrorInvalidValue;
+    if (mode != GUARDED) return hipErrorInvalidValue;
     return launch_kernel<TI, TO, AT, BT, 2, 2, 2, GUARDED, RS>(P, grid, stream);
 }
 template <typename TI, typename TO>

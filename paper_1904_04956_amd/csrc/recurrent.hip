@@ -32,7 +32,6 @@
 #include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
-#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -143,6 +142,8 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
     return n < tiles_per_group ? n : tiles_per_group;
 }
 
+constexpr int NW = 4;                                    // wavefronts
+
 // ------------------------------------------------------------------------------ forward
 // KW = contraction elements per wavefront: H = NW * KW.
 // FULL: B is a multiple of 32, so every row of every tile exists.  Otherwise the rows of the last tile beyond the batch
@@ -155,13 +156,13 @@ __device__ __forceinline__ int tiles_in_batch(int bg, int tiles_per_group, int B
 // exchange holds whole slices of 32 units, and the units beyond the layer come out as zeros that are not stored row-major.
 // LEAN: few enough registers for two workgroups per CU, one of which computes while the other waits for its operand: one set of
 // inputs, asked for behind the item's own operand, and half of the accumulators at a time.  Marks RecFwdArgs::fill on the side.
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
+template <int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
 __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
     static_assert(!LEAN || (SENTINEL && MULTI && PADDED && KW < 128), "the forms that are used");
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
-    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks NW and KW from a.H)
+    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks KW from a.H)
     const int B = a.B, T = a.T;
     const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
 }
 
 // ------------------------------------------------------------------------------ backward
-template <int NW, int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
+template <int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED>
 __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     constexpr int EPT = 16 / NW;
     constexpr int KSTEPS = 4 * KW / 16;                  // the contraction runs over the 4H gate rows
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // sequences, us, so / with one body: 288 units 1109 / 1131, 160 592 / 564, 96 336 / 315; wide slices leave no room for two.
     constexpr bool TWO = KW == 96;
     extern __shared__ float lds[];                       // [NW][4][64][4]
-    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks NW and KW from a.H)
+    const int H = PADDED ? a.H : NW * KW;                // (the launcher picks KW from a.H)
     const int B = a.B, T = a.T;
     const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
@@ -764,15 +765,13 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
 
 template <int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    constexpr int NW = 4;
     const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
-    return launch_resident<rec_fwd_kernel<NW, KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
+    return launch_resident<rec_fwd_kernel<KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
 hipError_t run_one(const RecBwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    constexpr int NW = 4;
     const size_t lds = (size_t)NW * 4 * 64 * 16 + (size_t)NW * 2048 + (size_t)NW * 512;   // partial sums; regrouping of dE/da, 2 KB per wavefront; spreading dy, 512 bytes per wavefront
-    return launch_resident<rec_bwd_kernel<NW, KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
+    return launch_resident<rec_bwd_kernel<KW, S, FULL, MULTI, PADDED>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool PADDED, typename A>
 hipError_t run_multi(const A& a, int grid, hipStream_t st, bool* launched) {

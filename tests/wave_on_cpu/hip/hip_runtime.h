@@ -28,7 +28,6 @@ template <typename T> T past_the_caches(const T* p) {
 #define __builtin_amdgcn_exp2f(x) exp2f(x)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
 #define __all(x) (x)
-#define __shfl_xor(v, lane, width) (v)
 
 struct uint2 { unsigned x, y; };
 struct uint4 { unsigned x, y, z, w; };
