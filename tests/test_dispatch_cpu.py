@@ -71,24 +71,26 @@ def test_exchange_copies_count_as_marked_only_if_the_launched_kernels_marked_the
             rec.recorder_occupancy(b"rec_small", small_fits)
             m = Model({DIMS})
             f, b = launches(m.forward), launches(m.backward)
-            out.append([count(f, "rec_small_fwd"), count(f, "rec_fwd_kernel"), count(b, "rec_small_bwd"), count(b, "rec_bwd_kernel"), count(b, "fill_u128")])
+            out.append([count(f, "rec_small_fwd"), count(f, "14rec_fwd_kernel"), count(b, "rec_small_bwd"), count(b, "14rec_bwd_kernel"), count(b, "fill_u128")])
     """)
     assert small == [2, 0, 2, 0, 0]
     assert large == [0, 2, 0, 2, 1]
 
 
-@pytest.mark.parametrize("dims,fwd,bwd", [
-    (DIMS, "rec_small_fwd", "rec_small_bwd"),
-    ("T=4, B=600, D=8, H=512, L=1, P=0, V=20", "rec_fwd_kernel", "rec_bwd_kernel"),
+@pytest.mark.parametrize("dims,fwd,bwd,other", [             # (mangled names: tile_rec_fwd_kernel contains rec_fwd_kernel)
+    (DIMS, "rec_small_fwd", "rec_small_bwd", "14rec_fwd_kernel"),
+    ("T=4, B=600, D=8, H=512, L=1, P=0, V=20", "tile_rec_fwd", "tile_rec_bwd", "cell_fwd"),
+    ("T=4, B=40, D=8, H=1024, L=1, P=0, V=20", "tile_rec_fwd", "tile_rec_bwd", "14rec_fwd_kernel"),
+    ("T=4, B=2100, D=8, H=96, L=1, P=0, V=20", "14rec_fwd_kernel", "14rec_bwd_kernel", "cell_fwd"),
 ])
-def test_a_forward_kernel_runs_only_if_its_backward_twin_fits_too(recorder, dims, fwd, bwd):
+def test_a_forward_kernel_runs_only_if_its_backward_twin_fits_too(recorder, dims, fwd, bwd, other):
     f_twin, f_other, b_twin = recorder(f"""
         rec.recorder_occupancy(b"rec_", 2)
         rec.recorder_occupancy(b"{bwd}", 0)
         m = Model({dims})
         f = launches(m.forward)
         b = launches(m.backward)
-        out = [count(f, "{fwd}"), count(f, "rec_fwd_kernel") + count(f, "cell_fwd"), count(b, "{bwd}")]
+        out = [count(f, "{fwd}"), count(f, "{other}"), count(b, "{bwd}")]
     """)
     assert f_twin == 0 and f_other > 0 and b_twin == 0
 
@@ -103,7 +105,7 @@ def test_whether_a_grid_fits_is_asked_for_every_device(recorder, mode, dims):
             rec.recorder_device(device)
             m = Model(mode={mode}, {dims})
             f = launches(m.forward)
-            out.append([count(f, "rec_small_fwd") + count(f, "rec_fwd_kernel") + count(f, "rec32_fwd"), count(f, "cell_fwd")])
+            out.append([count(f, "rec_small_fwd") + count(f, "tile_rec_fwd") + count(f, "rec32_fwd"), count(f, "cell_fwd")])
     """)
     assert big == big_again == [1, 0]
     assert little == [0, 4]

@@ -342,12 +342,12 @@ def test_narrow_layers_of_many_sequences_bf16(dims):
 
 
 @pytest.mark.parametrize("dims", [
-    dict(T=3, B=290, D=8, H=512, L=1, P=0, V=20),           # ten tiles: one per workgroup instead of one or two
-    dict(T=4, B=1030, D=8, H=512, L=1, P=0, V=20),          # 33 tiles over sixteen groups, the last one empty
+    dict(T=3, B=290, D=8, H=512, L=1, P=0, V=20),           # ten groups of two 16-row tiles, the last one with one
+    dict(T=4, B=1030, D=8, H=512, L=1, P=0, V=20),          # thirteen groups of five
     dict(T=3, B=1600, D=8, H=256, L=1, P=0, V=20),
     dict(T=3, B=1000, D=8, H=360, L=1, P=0, V=20),
 ])
-def test_two_workgroups_per_cu_forward_bf16(dims):
+def test_many_sequences_of_layers_up_to_512_cells_bf16(dims):
     check_step(dims, 1, seed=89, theta_scale=1.0)
 
 
