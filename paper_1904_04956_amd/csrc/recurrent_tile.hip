@@ -472,6 +472,10 @@ bool rec_narrow(int B, int H) {
 // Slices of 32 units for a layer of one such slice, and while that leaves every workgroup a CU and a tile of its own; else of 64: half
 // of the operand's bytes per cell, but their weights fit the registers up to 512 cells only.  (Of 32 with two workgroups a CU where the last slice
 // of 64 would be at most half full and take two tiles a workgroup: 136 cells, 700 sequences 84 + 130 us against 127 + 159.)
+// Learners that share a device: 65 to 128 sequences of 512 cells are 256 workgroups of 32 units, which no other learner's can run
+// beside (residency.hip); of 64 units they would be 128.  Four layers, 72 sequences, 200 classes, us a step, one learner / two at
+// once: 32 units 699 / 1384, 64 units 789 / 987.  Slices of 32 units, as one learner to a device is what this is for; not chosen by what else
+// is running, because the slices' width shows in the last bits.
 // Beyond 512 cells several tiles of 32 units a workgroup lose to recurrent.hip's 32 x 32 (1024 cells, 512 sequences 450 / 545 us a layer
 // against 348 / 387; 128 sequences 121 / 145 against 96 / 115).
 int rec_tile_units(int B, int H) {

@@ -1,7 +1,7 @@
 // Persistent launches at once, each resident in part only, would starve each other until their waits are abandoned.  So those
 // that may run at the same time never have more workgroups together than the device has CUs: each workgroup then finds a CU
 // without another one (grids are whole rounds of the eight XCDs, so this holds on every XCD).  A launch beyond that waits on
-// the device for as many of the others as it takes.  Every launch carries an event as its completion signal for that (0.5 us
+// the device for as many of the others as it takes (one with more than a workgroup a CU, for all of them).  Every launch carries an event as its completion signal for that (0.5 us
 // a launch; a marker behind it 1.5 us, with a system fence 3 us).  Three learners of 4 x 512 cells and 8 sequences (64
 // workgroups a launch), a thread and a stream each: 801 us a step of all three, 1284 with every launch behind the last one,
 // 470 for one learner alone.
