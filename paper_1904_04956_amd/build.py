@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libblstm_mi355.so")
-SOURCES = ["api.hip", "gemm.hip", "gemm_f32.hip", "recurrent.hip", "recurrent_small.hip", "recurrent_tile.hip", "recurrent_f32.hip", "residency.hip", "cell.hip", "softmax.hip", "update.hip", "pad.hip"]
+SOURCES = ["api.hip", "gemm.hip", "gemm_f32.hip", "recurrent.hip", "recurrent_small.hip", "recurrent_tile.hip", "recurrent_multi.hip", "recurrent_f32.hip", "residency.hip", "cell.hip", "softmax.hip", "update.hip", "pad.hip"]
 
 # The packed-fp32 feature is switched off for all device code on purpose.
 HIPCC_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",

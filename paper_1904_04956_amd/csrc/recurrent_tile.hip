@@ -1,6 +1,6 @@
 // Persistent recurrent kernels (bf16) on 16-row batch tiles: all T frames of one layer, both directions, in one launch.
 //
-// A workgroup of four wavefronts has 16 NB units (32 or 64) of its 16-row tiles.  Against 32 units of 32 rows
+// A workgroup of four wavefronts has 16 NB units (32 or 64) of a 16-row tile.  Against 32 units of 32 rows
 // (recurrent.hip) the slice of 64 units reads half of the operand bytes per cell (backward 64 KB a frame instead of 128 KB at
 // 512 cells, the longest part of its frame), and half as many workgroups wait on each other.
 //
@@ -20,92 +20,48 @@
 // Both protocols, bounded waits and failures as in recurrent.hip.
 //
 // us a layer of 21 frames, forward / backward, these kernels against 32 units of 32 rows: 512 cells, 128 sequences 47 / 59
-// against 69 / 76, 173 62 / 73 against 77 / 83, 256 68 / 79 against 80 / 85, 300 126 / 136 against 158 / 146, 2048 (16
-// rows x 64 units eight times a frame) 508 / 570 against 505 / 615; 1024 cells, 64 sequences 65 / 77 against 93 / 112.
+// against 69 / 76, 173 62 / 73 against 77 / 83, 256 68 / 79 against 80 / 85; 1024 cells, 64 sequences 65 / 77 against 93 / 112.
+// With several tiles a workgroup the kernels of recurrent_multi.hip run.
 // What bounds a frame of 256 sequences (2.1 GHz, cycles of a wavefront): forward 1900 for the exchange, 500 until the other
 // wavefronts have staged theirs, 950 products, 1100 cells (ten transcendentals each), 1600 issuing what the memory takes at
 // 5.3 TB/s (38 KB a workgroup and frame); backward 1400 issuing 64 KB of loads, 900 for the last of them, 1400 products,
 // 1500 partial sums and waiting for each other, 300 cells, 1700 issuing stores and the next inputs.
-#include "exchange.hpp"
-#include "kernels.hpp"
-#include "residency.hpp"
-#include <type_traits>
+#include "recurrent_tile.hpp"
 
 namespace blstm {
 namespace {
 
-constexpr int NW = 4;                                    // wavefronts
-constexpr int CHUNK = 16 * 8;                            // elements of eight columns of a tile
-
-// NB floats, and as many bf16, as one access
-template <int NB> struct Packs;
-template <> struct Packs<2> { typedef float2 F; typedef unsigned W; };
-template <> struct Packs<4> { typedef float4 F; typedef uint2 W; };
-__device__ __forceinline__ float part(const float2& v, int b) { return b ? v.y : v.x; }
-__device__ __forceinline__ float part(const float4& v, int b) { return b == 0 ? v.x : b == 1 ? v.y : b == 2 ? v.z : v.w; }
-__device__ __forceinline__ float2 pack(const float (&v)[2]) { return make_float2(v[0], v[1]); }
-__device__ __forceinline__ float4 pack(const float (&v)[4]) { return make_float4(v[0], v[1], v[2], v[3]); }
-__device__ __forceinline__ unsigned pack(const unsigned (&v)[1]) { return v[0]; }
-__device__ __forceinline__ uint2 pack(const unsigned (&v)[2]) { return make_uint2(v[0], v[1]); }
-__device__ __forceinline__ unsigned word(unsigned v, int) { return v; }
-__device__ __forceinline__ unsigned word(const uint2& v, int k) { return k ? v.y : v.x; }
-
-// Keeps three quarters of the weights in accumulation registers, which the products read as well as the others, and the
-// others free: left to itself the compiler fills those with weights and reads the staged h one fragment at a time.
-template <int NB, int KQ>
-__device__ __forceinline__ void park(uint4 (&w)[NB][KQ]) {
-    typedef unsigned u4 __attribute__((ext_vector_type(4)));
-    if constexpr (NB * KQ > 16) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): one wait for all of them
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int q = KQ / 4; q < KQ; ++q) {
-                u4 v = __builtin_bit_cast(u4, w[b][q]);
-                asm volatile("" : "+a"(v));
-                w[b][q] = __builtin_bit_cast(uint4, v);
-            }
-    }
-}
-
 // Workgroup -> (direction, group of tiles, slice); ids are dealt round-robin to the eight XCDs, each of which gets whole groups.
-struct Spot { int d, first, ntl, u; };                   // first tile and number of tiles (0: a group that does not exist)
-__device__ __forceinline__ Spot spot(int nu, int nbg, int per_group, int ntiles) {
+struct Spot { int d, tile, u; };                         // (tile -1: a group that does not exist)
+__device__ __forceinline__ Spot spot(int nu, int nbg) {
     const int slot = (int)blockIdx.x >> 3, group = (slot / nu) * 8 + ((int)blockIdx.x & 7);
     Spot p;
     p.u = slot % nu; p.d = group / nbg;
-    p.first = (group - p.d * nbg) * per_group;
-    p.ntl = group < 2 * nbg ? min(per_group, ntiles - p.first) : 0;
+    p.tile = group < 2 * nbg ? group - p.d * nbg : -1;
     return p;
 }
 
-// Workgroups a CU holds of these kernels (their registers, and the launch bounds).
-constexpr int fwd_per_cu(int nb, int kq, bool multi) { return nb == 4 ? (kq <= (multi ? 4 : 8) ? 2 : 1) : kq == 4 ? (multi ? 2 : 4) : kq <= 12 ? 2 : 1; }
-constexpr int bwd_per_cu(int nb, int kq, bool multi) { return nb == 4 ? (kq == 4 ? 2 : 1) : kq == 4 ? (multi ? 2 : 4) : kq <= 12 ? 2 : 1; }
-
 // ------------------------------------------------------------------------------ forward
-// Width up to 32 KQ.  MULTI: several tiles a workgroup, walked one after the other in every frame; the next item's
-// operand, written a frame ago, is then loaded under an item's products.
-template <int NB, int KQ, bool SENTINEL, bool MULTI>
-__global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_fwd_kernel(RecFwdArgs a) {
+// Width up to 32 KQ; a workgroup has one tile.
+template <int NB, int KQ, bool SENTINEL>
+__global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_fwd_kernel(RecFwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int FR = KQ / NW;                          // fragments a wavefront stages
     extern __shared__ uint4 hs[];                        // [2][KQ][64]
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
-    const Spot sp = spot(nu, a.nbg, a.tiles_per_group, NT);
-    const int d = sp.d, ntl = MULTI ? sp.ntl : min(sp.ntl, 1);
-    // this workgroup's share of the region to fill, some words every item behind its stores
+    const Spot sp = spot(nu, a.nbg);
+    const int d = sp.d, tile = sp.tile;
+    // this workgroup's share of the region to fill, some words every frame behind its stores
     const unsigned long long share = a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
     const unsigned long long first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
     uint4* const fill = static_cast<uint4*>(a.fill) + first;
     const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
     unsigned fill_pos = threadIdx.x;
     auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
-    if (ntl <= 0) { fill_some(1 << 30); return; }
-    const int nitems = T * ntl;
-    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * nitems - 1) / ((unsigned long long)(64 * NW) * nitems));
+    if (tile < 0) { fill_some(1 << 30); return; }
+    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * T - 1) / ((unsigned long long)(64 * NW) * T));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units
@@ -118,7 +74,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
             const int unit = unit0 + NB * (l16 >> 2) + b, k = (q + wave * FR) % KQ * 32 + 8 * lq;
             wf[b][q] = unit < H && k < H ? *reinterpret_cast<const uint4*>(a.uh[d] + (size_t)((l16 & 3) * H + unit) * H + k) : make_uint4(0u, 0u, 0u, 0u);
         }
-    park(wf);
+    park<KQ / 4>(wf);
     unsigned off[FR];
 #pragma unroll
     for (int i = 0; i < FR; ++i) off[i] = (unsigned)(min(4 * (wave * FR + i) + lq, chunks - 1) * CHUNK + l16 * 8);
@@ -130,46 +86,31 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
     const bool mine = j < H;
     const size_t RT = (size_t)(H / NB) * 16;             // lanes' records of a (frame, direction, tile)
     const size_t rec0 = (size_t)(jc / NB) * 16 + l16;
-    struct In { F ax[4], cp; };
-    auto inputs = [&](int item, In& in) __attribute__((always_inline)) {
-        const int n = item / ntl, tile = sp.first + item - n * ntl;
-        const int t = d ? T - 1 - n : n, tp = d ? T - n : n - 1;
+    struct In { F ax[4]; };
+    auto inputs = [&](int n, In& in) __attribute__((always_inline)) {
+        const int t = d ? T - 1 - n : n;
         const float* p = a.ax + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 8 * H + d * 4 * H + jc;
 #pragma unroll
         for (int g = 0; g < 4; ++g) in.ax[g] = *reinterpret_cast<const F*>(p + (size_t)g * H);
-        if constexpr (MULTI) {
-            in.cp = F{};
-            if (n > 0) in.cp = reinterpret_cast<const F*>(a.c)[((size_t)(tp * 2 + d) * NT + tile) * RT + rec0];
-        }
-    };
-    auto operand = [&](int item) {                       // of an item behind the first frame
-        const int n = item / ntl, tile = sp.first + item - n * ntl;
-        return a.hx + ((size_t)((d ? T - n : n - 1) * 2 + d) * NT + tile) * chunks * CHUNK;
     };
     In in0, in1;
     inputs(0, in0);
     float c[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) c[b] = 0.0f;
-    uint4 ahead[MULTI ? FR : 1];
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
-    auto do_item = [&](const int item, const In& cur, In& nxt, uint4* hb) __attribute__((always_inline)) {
-        const int n = item / ntl, tile = sp.first + item - n * ntl;
+    auto do_frame = [&](const int n, const In& cur, In& nxt, uint4* hb) __attribute__((always_inline)) {
         const int t = d ? T - 1 - n : n, row = tile * 16 + l16;
-        const bool look_ahead = SENTINEL && MULTI && item + 1 < nitems && item + 1 >= ntl;
         f32x4_t acc[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
         if (n > 0) {
-            const bf16_t* base = operand(item);
+            const bf16_t* base = a.hx + ((size_t)((d ? T - n : n - 1) * 2 + d) * NT + tile) * chunks * CHUNK;
             uint4 f[FR];
             if constexpr (!SENTINEL) if (wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
-            if constexpr (SENTINEL && MULTI) {
-#pragma unroll
-                for (int i = 0; i < FR; ++i) f[i] = ahead[i];
-            } else look16<FR>(f, base, where);
+            look16<FR>(f, base, where);
             if constexpr (SENTINEL) if (settle_probe<FR>(f, base, where, base + probe, lane < 4 * FR, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
 #pragma unroll
             for (int i = 0; i < FR; ++i) hb[(wave * FR + i) * 64 + lane] = f[i];
@@ -178,8 +119,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][q], f[q], acc[b]);
             __builtin_amdgcn_sched_barrier(0);
-            lds_barrier();                               // one an item: the buffer is doubled
-            if constexpr (MULTI) if (look_ahead) look16<FR>(ahead, operand(item + 1), where);
+            lds_barrier();                               // one a frame: the buffer is doubled
             // the others in groups of FR, a group read while the one before is multiplied
             uint4 h[2][FR];
             auto read = [&](int g, uint4 (&v)[FR]) __attribute__((always_inline)) {
@@ -198,8 +138,6 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
                     for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][g * FR + i], h[g & 1][i], acc[b]);
                 __builtin_amdgcn_sched_barrier(0);
             }
-        } else if constexpr (MULTI) {
-            if (look_ahead) look16<FR>(ahead, operand(item + 1), where);
         }
         float gi[NB], gf[NB], gg[NB], go[NB];
         unsigned hw[NB / 2];
@@ -209,7 +147,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
             gf[b] = fast_sigmoid(part(cur.ax[1], b) + acc[b][1]);
             gg[b] = fast_tanh(part(cur.ax[2], b) + acc[b][2]);
             go[b] = fast_sigmoid(part(cur.ax[3], b) + acc[b][3]);
-            c[b] = gf[b] * (MULTI ? part(cur.cp, b) : c[b]) + gi[b] * gg[b];
+            c[b] = gf[b] * c[b] + gi[b] * gg[b];
             const unsigned h = coh_bf16(go[b] * fast_tanh(c[b]) + poison);
             hw[b >> 1] = b & 1 ? hw[b >> 1] | (h << 16) : h;
         }
@@ -219,32 +157,31 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, MULTI)) void tile_rec_f
             else __hip_atomic_store(reinterpret_cast<unsigned*>(x), pack(hw), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
-        // What follows is not on the frame-to-frame path.  With one tile it also keeps the next look at h from coming too
+        // What follows is not on the frame-to-frame path.  It also keeps the next look at h from coming too
         // early: moved behind that look, or between the products, it cost 7 to 40 us a layer (512 cells, 128 and 256 sequences).
         const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
-        if constexpr (MULTI) if (mine) reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);   // (before the next item's inputs: of a group's only tile they read it)
-        if (item + 1 < nitems) inputs(item + 1, nxt);
+        if (n + 1 < T) inputs(n + 1, nxt);
         if (mine) {
             uint4* g4 = reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2) + rec0;
 #pragma unroll
             for (int k = 0; k < NB / 2; ++k)
                 g4[k * RT] = make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1]));
-            if constexpr (!MULTI) reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);
+            reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);
             if (row < B) *reinterpret_cast<W*>(a.y + ((size_t)t * B + row) * 2 * H + d * H + j) = pack(hw);
         }
         fill_some(fill_each);
     };
-    for (int item = 0; item < nitems; item += 2) {
-        do_item(item, in0, in1, hs);
-        if (item + 1 < nitems) do_item(item + 1, in1, in0, hs + KQ * 64);
+    for (int n = 0; n < T; n += 2) {
+        do_frame(n, in0, in1, hs);
+        if (n + 1 < T) do_frame(n + 1, in1, in0, hs + KQ * 64);
     }
     fill_some(1 << 30);
 }
 
 // ------------------------------------------------------------------------------ backward
 // Each wavefront contracts KQ / 4 blocks of 32 columns of every gate, SL fragments of dE/da in flight ahead of the products.
-template <int NB, int KQ, bool SENTINEL, bool MULTI>
-__global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_bwd_kernel(RecBwdArgs a) {
+template <int NB, int KQ, bool SENTINEL>
+__global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_bwd_kernel(RecBwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int BW = KQ / 4;
@@ -252,10 +189,9 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
     extern __shared__ float4 ps[];                       // [2][NW][NB][64]
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
-    const Spot sp = spot(nu, a.nbg, a.tiles_per_group, NT);
-    const int d = sp.d, ntl = MULTI ? sp.ntl : min(sp.ntl, 1);
-    if (ntl <= 0) return;
-    const int nitems = T * ntl;
+    const Spot sp = spot(nu, a.nbg);
+    const int d = sp.d, tile = sp.tile;
+    if (tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int q0 = wave * BW;
@@ -273,9 +209,9 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
     const int j = unit0 + NB * lq, jc = min(j, H - NB);
     const size_t RT = (size_t)(H / NB) * 16, rec0 = (size_t)(jc / NB) * 16 + l16;
     const size_t XT = (size_t)4 * chunks * CHUNK;        // exchange elements of a (frame, direction, tile)
-    struct In { W dy; uint4 g[NB / 2]; F c, cp, dc; };
-    auto inputs = [&](int item, In& in) __attribute__((always_inline)) {
-        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
+    struct In { W dy; uint4 g[NB / 2]; F cp; };
+    auto inputs = [&](int ni, In& in) __attribute__((always_inline)) {
+        const int n = T - 1 - ni;
         const int t = d ? T - 1 - n : n, tp = d ? T - n : n - 1;
         in.dy = *reinterpret_cast<const W*>(a.dy + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 2 * H + d * H + jc);
         const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
@@ -284,43 +220,27 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
         for (int k = 0; k < NB / 2; ++k) in.g[k] = g4[k * RT];
         in.cp = F{};
         if (n > 0) in.cp = reinterpret_cast<const F*>(a.c)[((size_t)(tp * 2 + d) * NT + tile) * RT + rec0];
-        if constexpr (MULTI) {                           // (with one tile these two stay in registers)
-            in.c = reinterpret_cast<const F*>(a.c)[rec + rec0];
-            in.dc = F{};
-            if (ni > 0) in.dc = reinterpret_cast<const F*>(a.dc)[((size_t)d * NT + tile) * RT + rec0];
-        }
-    };
-    auto operand = [&](int item) {                       // of an item behind the first frame
-        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
-        return a.dax + ((size_t)((d ? T - 2 - n : n + 1) * 2 + d) * NT + tile) * XT;
     };
     In in0, in1;
     inputs(0, in0);
-    float c[NB], dcn[NB];                                // one tile: this frame's cell state (then the one before's), carried dE/dc
+    float c[NB], dcn[NB];                                // this frame's cell state (then the one before's), carried dE/dc
     {
-        F cl = F{};
-        if constexpr (!MULTI) cl = reinterpret_cast<const F*>(a.c)[((size_t)((d ? 0 : T - 1) * 2 + d) * NT + sp.first) * RT + rec0];
+        const F cl = reinterpret_cast<const F*>(a.c)[((size_t)((d ? 0 : T - 1) * 2 + d) * NT + tile) * RT + rec0];
 #pragma unroll
         for (int b = 0; b < NB; ++b) { c[b] = part(cl, b); dcn[b] = 0.0f; }
     }
-    uint4 ahead[MULTI ? SL : 1];
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
-    auto do_item = [&](const int item, const In& cur, In& nxt, float4* pt) __attribute__((always_inline)) {
-        const int ni = item / ntl, tile = sp.first + item - ni * ntl, n = T - 1 - ni;
-        const int t = d ? T - 1 - n : n, row = tile * 16 + l16;
-        const bool look_ahead = SENTINEL && MULTI && item + 1 < nitems && item + 1 >= ntl;
+    auto do_frame = [&](const int ni, const In& cur, In& nxt, float4* pt) __attribute__((always_inline)) {
+        const int n = T - 1 - ni, t = d ? T - 1 - n : n, row = tile * 16 + l16;
         float dh[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) dh[b] = 0.0f;
         if (ni > 0) {
-            const bf16_t* base = operand(item);
+            const bf16_t* base = a.dax + ((size_t)((d ? T - 2 - n : n + 1) * 2 + d) * NT + tile) * XT;
             uint4 f[2][SL];
             bool gu = false;
             if constexpr (!SENTINEL) gu = wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * ni), a.abort_word, a.limit_ticks);
-            if constexpr (SENTINEL && MULTI) {
-#pragma unroll
-                for (int q = 0; q < SL; ++q) f[0][q] = ahead[q];
-            } else look16<SL>(f[0], base, off);
+            look16<SL>(f[0], base, off);
             f32x4_t acc[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -329,7 +249,6 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
 #pragma unroll
             for (int s = 0; s < NSL; ++s) {
                 if (s + 1 < NSL) look16<SL>(f[(s + 1) & 1], base, [&](int q) { return off((s + 1) * SL + q); });
-                else if constexpr (MULTI) { if (look_ahead) look16<SL>(ahead, operand(item + 1), off); }
                 if constexpr (SENTINEL) gu = settle_probe<SL>(f[s & 1], base, [&](int q) { return off(s * SL + q); }, base + probe, lane < KQ, gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                 for (int q = 0; q < SL; ++q)
@@ -339,7 +258,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
             if (gu) poison = __builtin_nanf("");
 #pragma unroll
             for (int b = 0; b < NB; ++b) pt[(wave * NB + b) * 64 + lane] = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-            lds_barrier();                               // one an item: the partial sums are double-buffered
+            lds_barrier();                               // one a frame: the partial sums are double-buffered
             // block b of the partial sums has units 16 b + 4 lq + e of row l16
             F v[NW];
 #pragma unroll
@@ -351,8 +270,6 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
             for (int w = 0; w < NW; ++w)
 #pragma unroll
                 for (int b = 0; b < NB; ++b) dh[b] += part(v[w], b);
-        } else if constexpr (MULTI) {
-            if (look_ahead) look16<SL>(ahead, operand(item + 1), off);
         }
         unsigned da[4][NB / 2];                          // a gate's units
 #pragma unroll
@@ -362,8 +279,8 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
             const float gi = bf2f((bf16_t)(gif & 0xFFFFu)), gf = bf2f((bf16_t)(gif >> 16));
             const float gg = bf2f((bf16_t)(ggo & 0xFFFFu)), go = bf2f((bf16_t)(ggo >> 16));
             const float dht = dh[b] + bf2f((bf16_t)(b & 1 ? dyw >> 16 : dyw & 0xFFFFu)) + poison;
-            const float tc = fast_tanh(MULTI ? part(cur.c, b) : c[b]), cp = part(cur.cp, b);
-            const float dc = dht * go * (1.0f - tc * tc) + (MULTI ? part(cur.dc, b) : dcn[b]);
+            const float tc = fast_tanh(c[b]), cp = part(cur.cp, b);
+            const float dc = dht * go * (1.0f - tc * tc) + dcn[b];
             const unsigned v[4] = {coh_bf16(dc * gg * gi * (1.0f - gi)), coh_bf16(dc * cp * gf * (1.0f - gf)),
                                    coh_bf16(dc * gi * (1.0f - gg * gg)), coh_bf16(dht * tc * go * (1.0f - go))};
 #pragma unroll
@@ -391,22 +308,20 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, MULTI)) void tile_rec_b
             for (int k = 0; k < NB / 2; ++k) st_coh_16B(x + (size_t)k * chunks * CHUNK, o[k]);
         }
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
-        if constexpr (MULTI) if (j < H) reinterpret_cast<F*>(a.dc)[((size_t)d * NT + tile) * RT + rec0] = pack(dcn);   // (as in the forward kernel)
-        if (item + 1 < nitems) inputs(item + 1, nxt);
+        if (ni + 1 < T) inputs(ni + 1, nxt);
         if (u8 < H && row < B) {
             bf16_t* p = a.da + ((size_t)t * B + row) * 8 * H + (size_t)(d * 4 + gate0) * H + u8;
 #pragma unroll
             for (int k = 0; k < NB / 2; ++k) *reinterpret_cast<uint4*>(p + (size_t)k * H) = o[k];
         }
     };
-    for (int item = 0; item < nitems; item += 2) {
-        do_item(item, in0, in1, ps);
-        if (item + 1 < nitems) do_item(item + 1, in1, in0, ps + NW * NB * 64);
+    for (int ni = 0; ni < T; ni += 2) {
+        do_frame(ni, in0, in1, ps);
+        if (ni + 1 < T) do_frame(ni + 1, in1, in0, ps + NW * NB * 64);
     }
 }
 
 // The groups of tiles a direction is cut into: as many as leave every XCD, which gets whole groups, per_cu workgroups a CU.
-struct Cut { int nbg, per_group, grid, real; };
 Cut cut(int B, int H, int units, int per_cu) {
     const int nu = (H + units - 1) / units, tiles = (B + 15) / 16, most = 4 * (32 * per_cu / nu);
     Cut c;
@@ -428,24 +343,21 @@ Cut best_cut(int B, int H, int units, int most_per_cu) {
     return cut(B, H, units, H <= 32 ? 2 : 1);
 }
 
-template <int NB, int KQ, bool S, bool MULTI>
+template <int NB, int KQ, bool S>
 hipError_t run(const RecFwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S, MULTI>>(a, 64 * NW, (size_t)2 * KQ * 64 * 16, c.grid, c.real, st, launched);
+    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * KQ * 64 * 16, c.grid, c.real, st, launched);
 }
-template <int NB, int KQ, bool S, bool MULTI>
+template <int NB, int KQ, bool S>
 hipError_t run(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S, MULTI>>(a, 64 * NW, (size_t)2 * NW * NB * 64 * 16, c.grid, c.real, st, launched);
+    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * NW * NB * 64 * 16, c.grid, c.real, st, launched);
 }
 template <int NB, int KQ, typename A>
 hipError_t run_width(A a, bool sentinel, hipStream_t st, bool* launched) {
     const Cut c = best_cut(a.B, a.H, 16 * NB, std::is_same_v<A, RecFwdArgs> ? fwd_per_cu(NB, KQ, false) : bwd_per_cu(NB, KQ, false));
     a.nbg = c.nbg; a.tiles_per_group = c.per_group;
-    if constexpr (NB == 4 || KQ == 4) {                  // (several tiles a workgroup: of 64 units, or whole narrow layers)
-        if (c.per_group > 1 && sentinel) return run<NB, KQ, true, true>(a, c, st, launched);
-        if constexpr (NB == 4 && KQ != 12) if (c.per_group > 1) return run<NB, KQ, false, true>(a, c, st, launched);
-    }
-    if (sentinel) return run<NB, KQ, true, false>(a, c, st, launched);
-    if constexpr (KQ == 4 || KQ == 8 || KQ == 16 || KQ == 32) return run<NB, KQ, false, false>(a, c, st, launched);
+    if (c.per_group > 1) return launch_rec_multi(a, NB, KQ, sentinel, c.grid, c.real, st, launched);
+    if (sentinel) return run<NB, KQ, true>(a, c, st, launched);
+    if constexpr (KQ == 4 || KQ == 8 || KQ == 16 || KQ == 32) return run<NB, KQ, false>(a, c, st, launched);
     return hipSuccess;
 }
 template <typename A>

@@ -5,22 +5,26 @@
 
 namespace blstm {
 
-// How many workgroups of a kernel the current device holds at once.  The answer depends on the kernel and the device only
-// and is kept per kernel and thread for the device last asked about.
+// LDS a workgroup may ask for: a CU's 160 KB but for what __syncthreads_or takes.
+constexpr int LDS_MOST = 159 * 1024;
+
+// How many workgroups of a kernel the current device holds at once.  The answer depends on the kernel, its LDS and the device only
+// and is kept per kernel and thread for the last of those asked about.
 template <auto KERNEL>
 hipError_t resident_workgroups(int threads, size_t dyn_lds, int* count) {
     static thread_local int device = -1, held = 0;
+    static thread_local size_t lds = 0;
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (dev != device) {
+    if (dev != device || dyn_lds != lds) {
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess && dyn_lds > 0)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds);
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);   // (not dyn_lds: other threads may launch it with more)
         if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, dyn_lds);
         if (e != hipSuccess) return e;
         held = cus * per_cu;
-        device = dev;
+        device = dev; lds = dyn_lds;
     }
     *count = held;
     return hipSuccess;

@@ -380,6 +380,19 @@ def test_several_workgroups_a_cu_on_sixteen_row_tiles_bf16(dims, syncs):
     check_sixteen_row_tiles(dims, syncs)
 
 
+@pytest.mark.parametrize("dims,syncs", [
+    (dict(T=3, B=272, D=8, H=512, L=2, P=0, V=20), (0, 1)),   # a group left with one tile takes a neighbour's as well
+    (dict(T=2, B=515, D=8, H=504, L=1, P=0, V=20), (1,)),     # eight units missing in the last slice, three rows in the last tile
+    (dict(T=1, B=530, D=8, H=512, L=1, P=0, V=20), (0, 1)),   # nothing exchanged
+    (dict(T=3, B=3328, D=8, H=512, L=1, P=0, V=20), (1,)),    # the most tiles whose carried state the backward kernel keeps in LDS
+    (dict(T=3, B=3329, D=8, H=512, L=1, P=0, V=20), (0, 1)),  # one more
+    (dict(T=2, B=5633, D=8, H=512, L=1, P=0, V=20), (1,)),    # the forward kernel's in memory too
+    (dict(T=3, B=4100, D=8, H=328, L=1, P=0, V=20), (1,)),
+])
+def test_several_sixteen_row_tiles_a_workgroup_bf16(dims, syncs):
+    check_sixteen_row_tiles(dims, syncs)
+
+
 def check_sixteen_row_tiles(dims, syncs):
     # the same problem under each protocol: against the oracle (2e-2: the storage type), and bit for bit between them
     grads = []
