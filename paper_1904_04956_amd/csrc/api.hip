@@ -14,6 +14,7 @@
 #include "../../include/blstm_mi355.h"
 #include "gemm.hpp"
 #include "kernels.hpp"
+#include "xcd.hpp"
 
 using namespace blstm;
 
@@ -170,6 +171,9 @@ int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
     if (fwd && bwd) *kind = 1;
     return BLSTM_OK;
 }
+
+// The words behind an exchange copy (see xcd.hpp), marked with it.
+inline unsigned* xcd_table(void* copy, size_t bytes) { return reinterpret_cast<unsigned*>(static_cast<char*>(copy) + bytes - XCD_TABLE_BYTES); }
 
 inline const char* at(const void* base, size_t elems, size_t esz) { return static_cast<const char*>(base) + elems * esz; }
 inline char* at(void* base, size_t elems, size_t esz) { return static_cast<char*>(base) + elems * esz; }
@@ -470,8 +474,8 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         // exchange copies of h and dE/da in MFMA-fragment order, one per layer (whole 32-row tiles),
         // contiguous so that one fill marks all of a pass's copies as "not written yet"
         const size_t Mx = (size_t)c->T * tiles * 32;
-        c->hx_bytes = up256(Mx * 2 * Hr * 2);
-        c->dax_bytes = up256(Mx * 8 * Hr * 2);
+        c->hx_bytes = up256(Mx * 2 * Hr * 2) + XCD_TABLE_BYTES;
+        c->dax_bytes = up256(Mx * 8 * Hr * 2) + XCD_TABLE_BYTES;
         c->wHX = w;  w += c->hx_bytes * c->L;
         c->wDAX = w; w += c->dax_bytes * c->L;
     }
@@ -663,6 +667,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.gates = reinterpret_cast<unsigned short*>(G); a.c = C;
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
+            a.xcd = ctx->rec_sync == 1 ? xcd_table(a.hx, ctx->hx_bytes) : nullptr;
             if (fills) {   // the backward twin's exchange copy is pre-filled on the side
                 a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l;
                 a.fill_words = ctx->dax_bytes / 16;
@@ -840,6 +845,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
+            a.xcd = sentinel ? xcd_table(a.dax, ctx->dax_bytes) : nullptr;
             if (ctx->fwd_persistent[l] == 3) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_tile_bwd(a, sentinel, st, &rec_done));
             else if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
             else RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));

@@ -52,6 +52,7 @@ struct RecFwdArgs {
     void* fill;
     unsigned long long fill_words;
     int T, B, H, nbg, tiles_per_group;
+    unsigned* xcd;                // XCD_TABLE_BYTES of words, all ones (xcd.hpp), or null
     bool ask;                     // host only: launch nothing, only say whether it would be
 };
 struct RecBwdArgs {
@@ -66,6 +67,8 @@ struct RecBwdArgs {
     unsigned* abort_word;
     unsigned long long limit_ticks;
     int T, B, H, nbg, tiles_per_group;
+    unsigned* xcd;                // as above
+    bool whole_groups;            // set by the launcher (few sequences): see xcd.hpp
     bool ask;                     // as above
 };
 bool rec_supported(int H);                  // whether the persistent kernels take this width

@@ -8,10 +8,12 @@
 //     branch round a store it does not, and waited for all of them in every item: the latency of a_x and the stores' acknowledgements.
 //   - Row-major tensors are read and written in whole lines and turned in LDS (see `turned`).
 //   - The carried state (c; dE/dc and the next item's c) stays in LDS (LOCAL) as long as the group's tiles fit there.
+//   - The forward kernel's h goes through the XCD's L2 (xcd.hpp): 10 % of a layer.  The backward kernel's dE/da, four times as much, does not: 4 to
+//     15 % slower (512 cells, 512 sequences 116 us a layer write-through, 135 through the L2).
 // us a layer of 21 frames, forward / backward, before (inputs one item ahead, a lane to a row, waits for everything) and now, 512
-// cells: 272 sequences 121 / 133 and 104 / 105, 512 153 / 154 and 145 / 128, 700 201 / 212 and 186 / 157, 2048 488 / 559 and 440 /
-// 381; 320 cells, 3000 485 / 539 and 394 / 328; 256, 2048 235 / 253 and 227 / 169.  Bound by the memory: forward 1.85 GB a layer of 512
-// cells and 2048 sequences (4.2 TB/s), without the marking of dE/da's copy 386 us, without loading a_x 288; backward without its
+// cells: 272 sequences 121 / 133 and 98 / 105, 512 153 / 154 and 122 / 116, 700 201 / 212 and 170 / 161, 2048 488 / 559 and 414 /
+// 386; 320 cells, 3000 485 / 539 and 383 / 330; 256, 2048 235 / 253 and 199 / 170.  Bound by the memory: forward 1.85 GB a layer of 512
+// cells and 2048 sequences (4.5 TB/s); without the marking of dE/da's copy an eighth less, without loading a_x a third; backward without its
 // row-major stores 343, without its operand 346.  (The backward operand asked for under the products that free its registers,
 // half an item earlier: 387 against 400 with eight tiles a workgroup, but 189 against 161 with three, whose looks then come too early.)
 #include "recurrent_tile.hpp"
@@ -19,27 +21,14 @@
 namespace blstm {
 namespace {
 
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-constexpr int SC1 = 16;                                  // cache policy of an agent-scope store: write-through
-constexpr unsigned DROP = 0x7FFFFFF0u;                   // an offset beyond every buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(void* p, unsigned bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000); }
-template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned v) { __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, AUX); }
-template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const uint2& v) { __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.x, v.y}, r, (int)off, 0, AUX); }
-template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const uint4& v) { __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v.x, v.y, v.z, v.w}, r, (int)off, 0, AUX); }
-template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const float2& v) { put<AUX>(r, off, __builtin_bit_cast(uint2, v)); }
-template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const float4& v) { put<AUX>(r, off, __builtin_bit_cast(uint4, v)); }
-template <typename V> __device__ __forceinline__ V get(const void* base, unsigned off) { return *reinterpret_cast<const V*>(static_cast<const char*>(base) + off); }
-
 // Workgroup -> (direction, group of tiles, slice), as in recurrent_tile.hip; the tiles are dealt evenly.  A group left with one tile
 // takes a neighbour's as well (`pair`; both write the same bits): its look at the next operand, an item ahead, would always come too
 // early (512 cells, 272 sequences backward 146 us a layer, 108 with the second tile).
-struct Spot { int d, first, ntl, u; };
+struct Spot { int d, first, ntl, u, group; };
 __device__ __forceinline__ Spot spot(int nu, int nbg, int ntiles, bool pair) {
     const int slot = (int)blockIdx.x >> 3, group = (slot / nu) * 8 + ((int)blockIdx.x & 7);
     Spot p;
-    p.u = __builtin_amdgcn_readfirstlane(slot % nu); p.d = __builtin_amdgcn_readfirstlane(group / nbg);
+    p.u = __builtin_amdgcn_readfirstlane(slot % nu); p.d = __builtin_amdgcn_readfirstlane(group / nbg); p.group = group;
     const int g = group - p.d * nbg;
     p.first = __builtin_amdgcn_readfirstlane((int)((unsigned)(g * ntiles) / (unsigned)nbg));   // (at most 128 groups)
     p.ntl = group < 2 * nbg ? __builtin_amdgcn_readfirstlane((int)((unsigned)((g + 1) * ntiles) / (unsigned)nbg)) - p.first : 0;
@@ -77,6 +66,8 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
     float4* const axs = reinterpret_cast<float4*>(hs + 2 * KQ * 64);
     W* const ys = reinterpret_cast<W*>(axs + 2 * 4 * 16 * PP);
     F* const state = reinterpret_cast<F*>(ys + 2 * 256) + tid;
+    unsigned* const xcds = SENTINEL && nu > 1 && a.xcd ? a.xcd + sp.group * nu : nullptr;
+    tell_xcd(xcds, sp.u);
     const int l16 = lane & 15, lq = lane >> 4;
     const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units
     // row l16 of block b: gate l16 % 4 of unit NB (l16 / 4) + b; the wavefront's own fragments of h first
@@ -92,9 +83,6 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
     unsigned off[FR];                                    // bytes
 #pragma unroll
     for (int i = 0; i < FR; ++i) off[i] = (unsigned)(min(4 * (wave * FR + i) + lq, chunks - 1) * CHUNK + l16 * 8) * 2;
-    auto where = [&](int i) { return off[i] / 2; };
-    // one lane per eight columns of those fragments: the last word its producer writes there
-    const unsigned probe = (unsigned)(min(4 * wave * FR + min(lane, 4 * FR - 1), chunks - 1) * CHUNK + CHUNK - 2);
     // this lane's cells: units j .. j + NB - 1 of row l16
     const int j = unit0 + NB * lq, jc = min(j, H - NB);
     const bool mine = j < H;
@@ -120,12 +108,11 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
     };
     auto operand = [&](const Item& p) { return a.hx + ((size_t)(frame(p.n - 1) * 2 + d) * NT + sp.first + p.i) * chunks * CHUNK; };   // (behind the first frame)
     uint4 ahead[FR];
-    auto look = [&](const Item& p) __attribute__((always_inline)) {
-        const bf16_t* base = operand(p);
-#pragma unroll
-        for (int i = 0; i < FR; ++i) ahead[i] = get<uint4>(base, off[i]);
-    };
+    auto look = [&](const Item& p) __attribute__((always_inline)) { look_through<FR>(ahead, buffer(operand(p), chunks * CHUNK * 2), off); };
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    bool lost;
+    const bool near = one_xcd(xcds, nu, a.abort_word, a.limit_ticks, &lost);
+    if (lost) poison = __builtin_nanf("");
     Item now{0, 0}, next{0, 0}, third{0, 0};             // this item and the two behind it
     next.next(ntl); third = next; third.next(ntl);
     int par = 0;                                         // of the item: which of the two buffers
@@ -157,16 +144,15 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
             for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
         F cp = F{};
         if constexpr (!FIRST) {
-            const bf16_t* base = operand(now);
+            const __amdgpu_buffer_rsrc_t x = buffer(operand(now), chunks * CHUNK * 2);
             uint4 f[FR];
             if constexpr (SENTINEL) {
 #pragma unroll
                 for (int i = 0; i < FR; ++i) f[i] = ahead[i];
-                if (settle_probe<FR>(f, base, where, base + probe, lane < 4 * FR, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+                if (await<FR>(f, x, off, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             } else {
                 if (wait_counter(a.cnt + d * NT + sp.first + now.i, (unsigned)(nu * now.n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
-#pragma unroll
-                for (int i = 0; i < FR; ++i) f[i] = get<uint4>(base, off[i]);
+                look_through<FR>(f, x, off);
             }
 #pragma unroll
             for (int i = 0; i < FR; ++i) hb[(wave * FR + i) * 64 + lane] = f[i];
@@ -215,7 +201,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
             const unsigned h = coh_bf16(go[b] * fast_tanh(c[b]) + poison);
             hw[b >> 1] = b & 1 ? hw[b >> 1] | (h << 16) : h;
         }
-        put<SC1>(buffer(a.hx + ((size_t)(t * 2 + d) * NT + sp.first + now.i) * chunks * CHUNK, (unsigned)chunks * CHUNK * 2), x_off, pack(hw));
+        put_exchange(near, buffer(a.hx + ((size_t)(t * 2 + d) * NT + sp.first + now.i) * chunks * CHUNK, (unsigned)chunks * CHUNK * 2), x_off, pack(hw));
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + sp.first + now.i);
         const size_t rec = record(t, now.i);
         if constexpr (LOCAL) state[now.i * 64 * NW] = pack(c);
@@ -289,12 +275,10 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
     unsigned offb[BW];                                   // bytes, within a gate
 #pragma unroll
     for (int q = 0; q < BW; ++q) offb[q] = (unsigned)(min(4 * (q0 + q) + lq, chunks - 1) * CHUNK + l16 * 8) * 2;
-    auto where = [&](int q) {                            // (for looks that failed: computed there, not ahead of the loop, whose registers are all taken)
-        unsigned o = offb[q % BW];
-        asm volatile("" : "+v"(o));
-        return (unsigned)((q / BW) * chunks * CHUNK) + o / 2;
+    auto offsets = [&](int s, unsigned (&o)[SL]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < SL; ++q) o[q] = (unsigned)((s * SL + q) / BW) * (unsigned)(chunks * CHUNK * 2) + offb[(s * SL + q) % BW];
     };
-    const unsigned probe = (unsigned)((3 * chunks + min(4 * q0 + min(lane, KQ - 1), chunks - 1)) * CHUNK + CHUNK - 2);
     const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units; the lane's: j .. j + NB - 1 of row l16
     const int j = unit0 + NB * lq, jc = min(j, H - NB);
     const unsigned RT = (unsigned)(H / NB) * 16, rec0 = (unsigned)(jc / NB) * 16 + l16;
@@ -321,9 +305,10 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
     };
     auto operand = [&](const Item& p) { return a.dax + ((size_t)(frame(p.n - 1) * 2 + d) * NT + sp.first + p.i) * XT; };   // (behind the first frame)
     uint4 f[KQ / SL][SL];
-    auto look = [&](const bf16_t* base, int s) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < SL; ++q) f[s][q] = get<uint4>(base + (size_t)((s * SL + q) / BW) * chunks * CHUNK, offb[(s * SL + q) % BW]);
+    auto look = [&](__amdgpu_buffer_rsrc_t x, int s) __attribute__((always_inline)) {
+        unsigned o[SL];
+        offsets(s, o);
+        look_through<SL>(f[s], x, o);
     };
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
     Item now{0, 0}, next{0, 0}, third{0, 0};
@@ -348,7 +333,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
         const size_t carried = ((size_t)d * NT + sp.first + now.i) * RT;
         F c = cur.c, dcp = F{};
         if constexpr (!FIRST) {
-            const bf16_t* base = operand(now);
+            const __amdgpu_buffer_rsrc_t x = buffer(operand(now), XT * 2);
             if constexpr (!LOCAL) {
                 c = get<F>(reinterpret_cast<const F*>(a.c) + record(t, now.i), rec0 * (unsigned)sizeof(F));
                 dcp = get<F>(reinterpret_cast<const F*>(a.dc) + carried, rec0 * (unsigned)sizeof(F));
@@ -357,7 +342,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
             if constexpr (!SENTINEL) {
                 gu = wait_counter(a.cnt + d * NT + sp.first + now.i, (unsigned)(nu * now.n), a.abort_word, a.limit_ticks);
 #pragma unroll
-                for (int s = 0; s < KQ / SL; ++s) look(base, s);
+                for (int s = 0; s < KQ / SL; ++s) look(x, s);
             }
             f32x4_t acc[NB];
 #pragma unroll
@@ -366,7 +351,11 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
                 for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
 #pragma unroll
             for (int s = 0; s < KQ / SL; ++s) {
-                if constexpr (SENTINEL) gu = settle_probe<SL>(f[s], base, [&](int q) { return where(s * SL + q); }, base + probe, lane < KQ, gu, a.abort_word, a.limit_ticks);
+                if constexpr (SENTINEL) {
+                    unsigned o[SL];
+                    offsets(s, o);
+                    gu = await<SL>(f[s], x, o, gu, a.abort_word, a.limit_ticks);
+                }
 #pragma unroll
                 for (int q = 0; q < SL; ++q)
 #pragma unroll
@@ -380,7 +369,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
             lds_barrier();                               // one an item: the buffers are doubled
             if constexpr (SENTINEL) {                    // (behind the last item: of the last frame, not used)
 #pragma unroll
-                for (int s = 0; s < KQ / SL; ++s) look(operand(next), s);
+                for (int s = 0; s < KQ / SL; ++s) look(buffer(operand(next), XT * 2), s);
             }
             store_da();
             // block b of the partial sums has units 16 b + 4 lq + e of row l16
@@ -463,7 +452,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
     if (T > 1) {
         if constexpr (SENTINEL) {
 #pragma unroll
-            for (int s = 0; s < KQ / SL; ++s) look(operand(now), s);
+            for (int s = 0; s < KQ / SL; ++s) look(buffer(operand(now), XT * 2), s);
         }
         walk(std::false_type{}, (T - 1) * ntl);
     }

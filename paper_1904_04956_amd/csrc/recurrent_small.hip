@@ -14,6 +14,8 @@
 #include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
+#include "xcd.hpp"
+#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -33,15 +35,20 @@ __device__ __forceinline__ uint2 quad_bf16(float v) {
     return make_uint2(two, __builtin_amdgcn_update_dpp(0u, two, 0x4E, 0xF, 0xF, true));    // quad_perm 2,3,0,1
 }
 
-// Workgroup -> (direction, tile, slice); each XCD (ids are dealt round-robin) takes a contiguous eighth of the sequence.
-struct Spot { int d, tile, u; bool real; };
-__device__ __forceinline__ Spot spot(int nu, int ntiles) {
-    const int s = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+// Workgroup -> (direction, tile, slice).  whole: whole groups on one XCD (ids are dealt round-robin); otherwise each XCD takes a
+// contiguous eighth of the sequence.
+struct Spot { int d, tile, u, group; bool real; };
+__device__ __forceinline__ Spot spot(int nu, int ntiles, bool whole) {
+    const int x = (int)(blockIdx.x & 7), k = (int)(blockIdx.x >> 3);
+    const int s = whole ? ((k / nu) * 8 + x) * nu + k % nu : x * (int)(gridDim.x >> 3) + k;
     Spot p;
     p.real = s < 2 * nu * ntiles;
-    const int group = s / nu;
-    p.u = s - group * nu; p.d = group / ntiles; p.tile = group - p.d * ntiles;
+    p.group = s / nu;
+    p.u = s - p.group * nu; p.d = p.group / ntiles; p.tile = p.group - p.d * ntiles;
     return p;
+}
+__device__ __forceinline__ void st_exchange(bool write_back, bf16_t* p, const uint2& v) {
+    if (write_back) *reinterpret_cast<uint2*>(p) = v; else st_coh_8B(p, v);
 }
 
 // ------------------------------------------------------------------------------ forward
@@ -57,9 +64,9 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
     uint4* const fill = static_cast<uint4*>(a.fill) + first;
     const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
     unsigned fill_pos = threadIdx.x;
-    const int fill_each = (int)((share + (unsigned long long)(256 * T) - 1) / (unsigned long long)(256 * T));
+    const int fill_each = (int)((share + (unsigned long long)(128 * T)) / (unsigned long long)(256 * T));   // (the rest at the end)
     auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 256) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
-    const Spot sp = spot(nu, NT);
+    const Spot sp = spot(nu, NT, false);
     if (!sp.real) { fill_some(1 << 30); return; }
     const int d = sp.d, u = sp.u, tile = sp.tile;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -151,15 +158,20 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
 
 // ------------------------------------------------------------------------------ backward
 // Width up to 32 NQ; wavefront w contracts gate w's columns of dE/da.
+// Whole groups on one XCD exchange through its L2 (xcd.hpp) from NEAR_FROM on: 64 sequences of 512 cells 54.4 -> 49.9 us a layer, 30 of 1024 80 -> 75,
+// but 50 of 320 43.0 -> 44.0; forward it made no difference (a frame's a_x, asked for behind h, takes longer to come than the others' h).
+constexpr int NEAR_FROM = 16;
 template <int NQ>
 __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kernel(RecBwdArgs a) {
     __shared__ float part[2][NWF][16 * PS];
     const int T = a.T, B = a.B, H = a.H;
     const int blocks = (H + 31) / 32, nu = 2 * blocks, NT = (B + 15) / 16;
-    const Spot sp = spot(nu, NT);
+    const Spot sp = spot(nu, NT, NQ >= NEAR_FROM && a.whole_groups);
     if (!sp.real) return;
     const int d = sp.d, u = sp.u, tile = sp.tile;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned* const xcds = NQ >= NEAR_FROM && a.xcd ? a.xcd + sp.group * nu : nullptr;
+    tell_xcd(xcds, u);
     const int l16 = lane & 15, lq = lane >> 4;
     uint4 bf[NQ];
     {
@@ -188,6 +200,9 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
     inputs(T - 1, in0);
     float c = a.c[record(d ? 0 : T - 1)], dcn = 0.0f;    // this frame's cell state (then the one before's), carried dE/dc
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    bool lost;
+    const bool near = one_xcd(xcds, nu, a.abort_word, a.limit_ticks, &lost);
+    if (lost) poison = __builtin_nanf("");
     const size_t XT = (size_t)4 * blocks * PAIR;
     auto frame = [&](const int n, const In& cur, In& nxt, float (&pt)[NWF][16 * PS]) __attribute__((always_inline)) {
         const int t = d ? T - 1 - n : n, tn = d ? T - 2 - n : n + 1;
@@ -223,7 +238,7 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
         if ((tid & 3) == 0) {
             bf16_t* x = a.dax + ((size_t)(t * 2 + d) * NT + tile) * XT + (size_t)(u >> 1) * PAIR + ((2 * (u & 1) + (l16 >> 3)) * 16 + r) * 8 + (l16 & 7);
             const size_t gs = (size_t)blocks * PAIR;
-            st_coh_8B(x, qi); st_coh_8B(x + gs, qf); st_coh_8B(x + 2 * gs, qg); st_coh_8B(x + 3 * gs, qo);
+            st_exchange(near, x, qi); st_exchange(near, x + gs, qf); st_exchange(near, x + 2 * gs, qg); st_exchange(near, x + 3 * gs, qo);
         }
         if (n > 0) inputs(n - 1, nxt);
         dcn = dc * gf; c = cur.cp;
@@ -240,8 +255,9 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
 }
 
 template <auto KERNEL, typename A>
-hipError_t run(const A& a, hipStream_t st, bool* launched) {
-    const int real = 2 * 2 * ((a.H + 31) / 32) * ((a.B + 15) / 16);
+hipError_t run(A a, hipStream_t st, bool* launched) {
+    const int nu = 2 * ((a.H + 31) / 32), groups = 2 * ((a.B + 15) / 16), real = nu * groups;
+    if constexpr (std::is_same_v<A, RecBwdArgs>) a.whole_groups = whole_groups(groups, nu);
     return launch_resident<KERNEL>(a, 64 * NWF, 0, (real + 7) & ~7, real, st, launched);
 }
 

@@ -19,24 +19,32 @@
 // row and are not stored row-major.  Saved activations are per-lane records in the order of the units.
 // Both protocols, bounded waits and failures as in recurrent.hip.
 //
-// us a layer of 21 frames, forward / backward, these kernels against 32 units of 32 rows: 512 cells, 128 sequences 47 / 59
-// against 69 / 76, 173 62 / 73 against 77 / 83, 256 68 / 79 against 80 / 85; 1024 cells, 64 sequences 65 / 77 against 93 / 112.
-// With several tiles a workgroup the kernels of recurrent_multi.hip run.
-// What bounds a frame of 256 sequences (2.1 GHz, cycles of a wavefront): forward 1900 for the exchange, 500 until the other
-// wavefronts have staged theirs, 950 products, 1100 cells (ten transcendentals each), 1600 issuing what the memory takes at
-// 5.3 TB/s (38 KB a workgroup and frame); backward 1400 issuing 64 KB of loads, 900 for the last of them, 1400 products,
-// 1500 partial sums and waiting for each other, 300 cells, 1700 issuing stores and the next inputs.
+// The memory's answers come back to a wavefront in the order it asked, and a look at the exchanged operand that comes too early costs a round trip more.
+// So the next frame's inputs (a_x; dy, gates, cell states) are asked for behind the operand's arrival and before h or dE/da goes
+// out: they are back when the next look is due.  Row-major tensors move in whole lines, turned in LDS (see `turned`), the frame's h and
+// dE/da a frame later behind the barrier that is there anyway; every lane issues every load and store (see recurrent_multi.hip).  Then
+// the look is what comes too early: either the exchange goes through the XCD's L2 (NEAR, see xcd.hpp), twice as fast, or the look
+// waits until PAUSE clocks after the wavefront's own stores.  us a layer, write-through, pause of 0 / 600 / 900 / 1200 / 1500 / 1800: 256 sequences of 512
+// cells, backward 104 / 87 / 78 / 76 / 75 / 77, 128 70 / 52 / 54 / 56 / 58 / 61; forward 64 / 64 / 63 / 64 / 67 / 69 and 48 / 45 / 47 / 49 / 51 / 54; 64 of
+// 1024 backward 94 / 73 / 76 / 78 / 80 / 82.
+//
+// us a layer of 21 frames, forward / backward, before (a lane to a row, inputs behind the stores) and now: 512 cells, 128 sequences 49 / 55 and 45 / 52,
+// 173 63 / 72 and 57 / 66, 256 71 / 79 and 63 / 76; 1024, 64 66 / 78 and 60 / 73; 320, 256 56 / 64 and 48 / 57; 128, 500 38 / 38 and 32 / 32; 64,
+// 2000 53 / 62 and 46 / 50.  With several tiles a workgroup the kernels of recurrent_multi.hip run.
+// What bounds a frame of 256 sequences (2.1 GHz, cycles): forward 950 products, 1100 cells (ten transcendentals each), 500 staging, 1500 to 2000 until
+// the others' h is there, the rest what the memory takes (38 KB a workgroup and frame; without it 52 us a layer); backward 64 KB
+// of operand, products and partial sums (63 us without what comes from memory).
 #include "recurrent_tile.hpp"
 
 namespace blstm {
 namespace {
 
 // Workgroup -> (direction, group of tiles, slice); ids are dealt round-robin to the eight XCDs, each of which gets whole groups.
-struct Spot { int d, tile, u; };                         // (tile -1: a group that does not exist)
+struct Spot { int d, tile, u, group; };                         // (tile -1: a group that does not exist)
 __device__ __forceinline__ Spot spot(int nu, int nbg) {
     const int slot = (int)blockIdx.x >> 3, group = (slot / nu) * 8 + ((int)blockIdx.x & 7);
     Spot p;
-    p.u = slot % nu; p.d = group / nbg;
+    p.u = slot % nu; p.d = group / nbg; p.group = group;
     p.tile = group < 2 * nbg ? group - p.d * nbg : -1;
     return p;
 }
@@ -48,21 +56,27 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int FR = KQ / NW;                          // fragments a wavefront stages
-    extern __shared__ uint4 hs[];                        // [2][KQ][64]
+    constexpr int PP = 4 * NB;                           // 16-byte pieces of a_x a row and gate
+    constexpr bool NEAR = KQ == 8 || NB * KQ == 8;       // exchange through the XCD's L2, or a pause before the look (see the head of this file)
+    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 700 : 600;
+    extern __shared__ uint4 hs[];                        // [2][KQ][64], float4 [2][4][16][PP] a_x, W [2][16][16] h
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
     const Spot sp = spot(nu, a.nbg);
-    const int d = sp.d, tile = sp.tile;
-    // this workgroup's share of the region to fill, some words every frame behind its stores
+    const int d = sp.d, tile = sp.tile, row0 = tile * 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // this workgroup's share of the region to fill, NB / 2 words a thread and frame
     const unsigned long long share = a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
     const unsigned long long first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
-    uint4* const fill = static_cast<uint4*>(a.fill) + first;
-    const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
-    unsigned fill_pos = threadIdx.x;
-    auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
-    if (tile < 0) { fill_some(1 << 30); return; }
-    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * T - 1) / ((unsigned long long)(64 * NW) * T));
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned fill_bytes = (unsigned)(min(a.fill_words, first + share) - first) * 16;
+    const __amdgpu_buffer_rsrc_t fill = buffer(a.fill ? static_cast<uint4*>(a.fill) + first : a.fill, fill_bytes);
+    unsigned fill_off = tid * 16;
+    auto fill_word = [&]() { put<0>(fill, fill_off, make_uint4(~0u, ~0u, ~0u, ~0u)); fill_off += 64 * NW * 16; };
+    if (tile < 0) { while (fill_off < fill_bytes) fill_word(); return; }
+    float4* const axs = reinterpret_cast<float4*>(hs + 2 * KQ * 64);
+    W* const ys = reinterpret_cast<W*>(axs + 2 * 4 * 16 * PP);
+    unsigned* const xcds = SENTINEL && NEAR && nu > 1 && a.xcd ? a.xcd + sp.group * nu : nullptr;
+    tell_xcd(xcds, sp.u);
     const int l16 = lane & 15, lq = lane >> 4;
     const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units
     // row l16 of block b: gate l16 % 4 of unit NB (l16 / 4) + b; the wavefront's own fragments of h first
@@ -75,43 +89,60 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
             wf[b][q] = unit < H && k < H ? *reinterpret_cast<const uint4*>(a.uh[d] + (size_t)((l16 & 3) * H + unit) * H + k) : make_uint4(0u, 0u, 0u, 0u);
         }
     park<KQ / 4>(wf);
-    unsigned off[FR];
+    unsigned off[FR];                                    // bytes
 #pragma unroll
-    for (int i = 0; i < FR; ++i) off[i] = (unsigned)(min(4 * (wave * FR + i) + lq, chunks - 1) * CHUNK + l16 * 8);
-    auto where = [&](int i) { return off[i]; };
-    // one lane per eight columns of those fragments: the last word its producer writes there
-    const unsigned probe = (unsigned)(min(4 * wave * FR + min(lane, 4 * FR - 1), chunks - 1) * CHUNK + CHUNK - 2);
+    for (int i = 0; i < FR; ++i) off[i] = (unsigned)(min(4 * (wave * FR + i) + lq, chunks - 1) * CHUNK + l16 * 8) * 2;
     // this lane's cells: units j .. j + NB - 1 of row l16
     const int j = unit0 + NB * lq, jc = min(j, H - NB);
     const bool mine = j < H;
-    const size_t RT = (size_t)(H / NB) * 16;             // lanes' records of a (frame, direction, tile)
-    const size_t rec0 = (size_t)(jc / NB) * 16 + l16;
-    struct In { F ax[4]; };
-    auto inputs = [&](int n, In& in) __attribute__((always_inline)) {
-        const int t = d ? T - 1 - n : n;
-        const float* p = a.ax + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 8 * H + d * 4 * H + jc;
+    const unsigned RT = (unsigned)(H / NB) * 16;         // lanes' records of a (frame, direction, tile)
+    const unsigned rec0 = (unsigned)(jc / NB) * 16 + l16, XT = (unsigned)chunks * CHUNK;
+    const unsigned x_off = mine ? (unsigned)((j >> 3) * CHUNK + l16 * 8 + (j & 7)) * 2 : DROP;
+    const unsigned g_off = mine ? rec0 * 16 : DROP, c_off = mine ? rec0 * (unsigned)sizeof(F) : DROP;
+    // what this lane moves of the row-major tensors: a_x, gate ax_g + k 4 / NB of row ax_row, piece ax_p; h, row y_row, word l16
+    const int ax_g = lane / (16 * NB), ax_row = 4 * wave + lane % (16 * NB) / PP, ax_p = lane % PP, ax_slot = (ax_g * 16 + ax_row) * PP + (ax_p ^ (ax_row & (PP - 1)));
+    const unsigned ax_off = (unsigned)(min(ax_row, B - 1 - row0) * 8 * H + ax_g * H + min(sp.u * 16 * NB + 4 * ax_p, H - 4)) * 4;
+    const int y_row = 4 * wave + lq, y_unit = sp.u * 16 * NB + NB * l16;
+    const unsigned y_off = y_unit < H ? (unsigned)(y_row * 2 * H + y_unit) * 2 : DROP, y_bytes = (unsigned)((min(B - row0, 16) - 1) * 2 * H + H) * 2;
+    auto frame = [&](int n) { return d ? T - 1 - n : n; };
+    float4 axr[NB];
+    auto inputs = [&](int n) __attribute__((always_inline)) {
+        const float* base = a.ax + ((size_t)frame(min(n, T - 1)) * B + row0) * 8 * H + d * 4 * H;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) in.ax[g] = *reinterpret_cast<const F*>(p + (size_t)g * H);
+        for (int k = 0; k < NB; ++k) axr[k] = get<float4>(base + (size_t)(k * (4 / NB)) * H, ax_off);
     };
-    In in0, in1;
-    inputs(0, in0);
+    auto store_y = [&](int n) __attribute__((always_inline)) {
+        put<0>(buffer(a.y + ((size_t)frame(max(n, 0)) * B + row0) * 2 * H + d * H, n < 0 ? 0u : y_bytes), y_off, ys[(n & 1) * 256 + turned(y_row, l16)]);
+    };
+    inputs(0);
     float c[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) c[b] = 0.0f;
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
-    auto do_frame = [&](const int n, const In& cur, In& nxt, uint4* hb) __attribute__((always_inline)) {
-        const int t = d ? T - 1 - n : n, row = tile * 16 + l16;
+    bool lost;
+    const bool near = one_xcd(xcds, nu, a.abort_word, a.limit_ticks, &lost);
+    if (lost) poison = __builtin_nanf("");
+    unsigned long long stored = 0;                       // when the last h went out
+    auto do_frame = [&](auto first_frame, const int n) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_frame)::value;
+        const int t = frame(n);
+        uint4* const hb = hs + (n & 1) * KQ * 64;
+        float4* const ab = axs + (n & 1) * 4 * 16 * PP;
         f32x4_t acc[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
-        if (n > 0) {
-            const bf16_t* base = a.hx + ((size_t)((d ? T - n : n - 1) * 2 + d) * NT + tile) * chunks * CHUNK;
-            uint4 f[FR];
+        uint4 f[FR];
+        if constexpr (!FIRST) {
+            bf16_t* const base = a.hx + ((size_t)(frame(n - 1) * 2 + d) * NT + tile) * XT;
             if constexpr (!SENTINEL) if (wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * n), a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
-            look16<FR>(f, base, where);
-            if constexpr (SENTINEL) if (settle_probe<FR>(f, base, where, base + probe, lane < 4 * FR, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            const __amdgpu_buffer_rsrc_t x = buffer(base, XT * 2);
+            if constexpr (PAUSE > 0) while (__builtin_amdgcn_s_memtime() - stored < PAUSE) {}
+            look_through<FR>(f, x, off);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) ab[ax_slot + k * (4 / NB) * 16 * PP] = axr[k];
+            if constexpr (SENTINEL) if (await<FR>(f, x, off, false, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
 #pragma unroll
             for (int i = 0; i < FR; ++i) hb[(wave * FR + i) * 64 + lane] = f[i];
 #pragma unroll
@@ -119,7 +150,14 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] = mfma16(wf[b][q], f[q], acc[b]);
             __builtin_amdgcn_sched_barrier(0);
-            lds_barrier();                               // one a frame: the buffer is doubled
+        } else {
+#pragma unroll
+            for (int k = 0; k < NB; ++k) ab[ax_slot + k * (4 / NB) * 16 * PP] = axr[k];
+        }
+        lds_barrier();                                   // one a frame: the buffers are doubled
+        inputs(n + 1);
+        store_y(n - 1);
+        if constexpr (!FIRST) {
             // the others in groups of FR, a group read while the one before is multiplied
             uint4 h[2][FR];
             auto read = [&](int g, uint4 (&v)[FR]) __attribute__((always_inline)) {
@@ -139,43 +177,43 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        F ax[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (NB == 4) ax[g] = ab[(g * 16 + l16) * PP + ((4 * wave + lq) ^ l16)];
+            else ax[g] = reinterpret_cast<const F*>(ab + (g * 16 + l16) * PP + ((2 * wave + (lq >> 1)) ^ (l16 & 7)))[lq & 1];
+        }
         float gi[NB], gf[NB], gg[NB], go[NB];
         unsigned hw[NB / 2];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            gi[b] = fast_sigmoid(part(cur.ax[0], b) + acc[b][0]);
-            gf[b] = fast_sigmoid(part(cur.ax[1], b) + acc[b][1]);
-            gg[b] = fast_tanh(part(cur.ax[2], b) + acc[b][2]);
-            go[b] = fast_sigmoid(part(cur.ax[3], b) + acc[b][3]);
+            gi[b] = fast_sigmoid(part(ax[0], b) + acc[b][0]);
+            gf[b] = fast_sigmoid(part(ax[1], b) + acc[b][1]);
+            gg[b] = fast_tanh(part(ax[2], b) + acc[b][2]);
+            go[b] = fast_sigmoid(part(ax[3], b) + acc[b][3]);
             c[b] = gf[b] * c[b] + gi[b] * gg[b];
             const unsigned h = coh_bf16(go[b] * fast_tanh(c[b]) + poison);
             hw[b >> 1] = b & 1 ? hw[b >> 1] | (h << 16) : h;
         }
-        if (mine) {
-            bf16_t* x = a.hx + (((size_t)(t * 2 + d) * NT + tile) * chunks + (j >> 3)) * CHUNK + l16 * 8 + (j & 7);
-            if constexpr (NB == 4) st_coh_8B(x, pack(hw));
-            else __hip_atomic_store(reinterpret_cast<unsigned*>(x), pack(hw), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        put_exchange(near, buffer(a.hx + ((size_t)(t * 2 + d) * NT + tile) * XT, XT * 2), x_off, pack(hw));
+        if constexpr (PAUSE > 0) stored = __builtin_amdgcn_s_memtime();
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
-        // What follows is not on the frame-to-frame path.  It also keeps the next look at h from coming too
-        // early: moved behind that look, or between the products, it cost 7 to 40 us a layer (512 cells, 128 and 256 sequences).
+        // what follows is not on the frame-to-frame path
         const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
-        if (n + 1 < T) inputs(n + 1, nxt);
-        if (mine) {
-            uint4* g4 = reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2) + rec0;
+        const __amdgpu_buffer_rsrc_t g4 = buffer(reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2), RT * (NB / 2) * 16);
 #pragma unroll
-            for (int k = 0; k < NB / 2; ++k)
-                g4[k * RT] = make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1]));
-            reinterpret_cast<F*>(a.c)[rec + rec0] = pack(c);
-            if (row < B) *reinterpret_cast<W*>(a.y + ((size_t)t * B + row) * 2 * H + d * H + j) = pack(hw);
-        }
-        fill_some(fill_each);
+        for (int k = 0; k < NB / 2; ++k)
+            put<0>(g4, g_off + k * RT * 16, make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1])));
+        put<0>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));
+        ys[(n & 1) * 256 + turned(l16, 4 * wave + lq)] = pack(hw);
+#pragma unroll
+        for (int k = 0; k < NB / 2; ++k) fill_word();
     };
-    for (int n = 0; n < T; n += 2) {
-        do_frame(n, in0, in1, hs);
-        if (n + 1 < T) do_frame(n + 1, in1, in0, hs + KQ * 64);
-    }
-    fill_some(1 << 30);
+    do_frame(std::true_type{}, 0);
+    for (int n = 1; n < T; ++n) do_frame(std::false_type{}, n);
+    lds_barrier();
+    store_y(T - 1);
+    while (fill_off < fill_bytes) fill_word();           // (whatever rounding left over)
 }
 
 // ------------------------------------------------------------------------------ backward
@@ -186,13 +224,20 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
     typedef typename Packs<NB>::W W;
     constexpr int BW = KQ / 4;
     constexpr int SL = 4, NSL = KQ / SL;
-    extern __shared__ float4 ps[];                       // [2][NW][NB][64]
+    constexpr int AP = 2 * NB;                           // 16-byte pieces of dE/da a row and gate
+    constexpr bool NEAR = KQ == 4;                       // as in the forward kernel
+    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 1200 : 600;
+    extern __shared__ float4 ps[];                       // [2][NW][NB][64], uint4 [2][4][16][AP] dE/da, W [2][16][16] dy
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
     const Spot sp = spot(nu, a.nbg);
-    const int d = sp.d, tile = sp.tile;
+    const int d = sp.d, tile = sp.tile, row0 = tile * 16;
     if (tile < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint4* const das = reinterpret_cast<uint4*>(ps + 2 * NW * NB * 64);
+    W* const dys = reinterpret_cast<W*>(das + 2 * 4 * 16 * AP);
+    unsigned* const xcds = SENTINEL && NEAR && nu > 1 && a.xcd ? a.xcd + sp.group * nu : nullptr;
+    tell_xcd(xcds, sp.u);
     const int l16 = lane & 15, lq = lane >> 4;
     const int q0 = wave * BW;
     uint4 wf[NB][KQ];
@@ -203,44 +248,70 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
             const int unit = sp.u * 16 * NB + b * 16 + l16, k = (q0 + q % BW) * 32 + 8 * lq;
             wf[b][q] = unit < H && k < H ? *reinterpret_cast<const uint4*>(a.uht[d] + (size_t)unit * 4 * H + (q / BW) * H + k) : make_uint4(0u, 0u, 0u, 0u);
         }
-    auto off = [&](int q) { return (unsigned)(((q / BW) * chunks + min(4 * (q0 + q % BW) + lq, chunks - 1)) * CHUNK + l16 * 8); };
-    const unsigned probe = (unsigned)((3 * chunks + min(4 * q0 + min(lane, KQ - 1), chunks - 1)) * CHUNK + CHUNK - 2);
+    // fragment q: gate q / BW, block q0 + q % BW of 32 columns
+    unsigned offb[BW];                                   // bytes, within a gate
+#pragma unroll
+    for (int q = 0; q < BW; ++q) offb[q] = (unsigned)(min(4 * (q0 + q) + lq, chunks - 1) * CHUNK + l16 * 8) * 2;
     const int unit0 = (sp.u * NW + wave) * 4 * NB;       // this wavefront's units; the lane's: j .. j + NB - 1 of row l16
     const int j = unit0 + NB * lq, jc = min(j, H - NB);
-    const size_t RT = (size_t)(H / NB) * 16, rec0 = (size_t)(jc / NB) * 16 + l16;
-    const size_t XT = (size_t)4 * chunks * CHUNK;        // exchange elements of a (frame, direction, tile)
+    const unsigned RT = (unsigned)(H / NB) * 16, rec0 = (unsigned)(jc / NB) * 16 + l16;
+    const unsigned XT = (unsigned)4 * chunks * CHUNK;    // exchange elements of a (frame, direction, tile)
+    // eight units of one gate a lane (see below): where they go
+    const int gate0 = NB == 2 ? lq : 2 * (lq & 1), u8 = NB == 2 ? unit0 : unit0 + 8 * (lq >> 1);
+    const unsigned x_off = u8 < H ? (unsigned)((gate0 * chunks + (u8 >> 3)) * CHUNK + l16 * 8) * 2 : DROP;
+    // what this lane moves of the row-major tensors: dy, row y_row, word l16; dE/da, gate `wave` of rows a_row + 8 k, piece a_p
+    const int y_row = 4 * wave + lq, a_row = lane / AP, a_p = lane % AP, a_unit = sp.u * 16 * NB + 8 * a_p;
+    const unsigned y_off = (unsigned)(min(y_row, B - 1 - row0) * 2 * H + min(sp.u * 16 * NB + NB * l16, H - NB)) * 2;
+    const unsigned a_off = a_unit < H ? (unsigned)(a_row * 8 * H + wave * H + a_unit) * 2 : DROP, a_bytes = (unsigned)((min(B - row0, 16) - 1) * 8 * H + 4 * H) * 2;
+    auto da_slot = [&](int gate, int row, int p) { return (gate * 16 + row) * AP + (p ^ (NB == 4 ? row >> 1 : row >> 2)); };
+    auto frame = [&](int ni) { return d ? ni : T - 1 - ni; };   // (the last one visited forward comes first)
+    auto record = [&](int t) { return ((size_t)(t * 2 + d) * NT + tile) * RT; };
     struct In { W dy; uint4 g[NB / 2]; F cp; };
-    auto inputs = [&](int ni, In& in) __attribute__((always_inline)) {
-        const int n = T - 1 - ni;
-        const int t = d ? T - 1 - n : n, tp = d ? T - n : n - 1;
-        in.dy = *reinterpret_cast<const W*>(a.dy + ((size_t)t * B + min(tile * 16 + l16, B - 1)) * 2 * H + d * H + jc);
-        const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
-        const uint4* g4 = reinterpret_cast<const uint4*>(a.gates) + rec * (NB / 2) + rec0;
+    auto inputs = [&](int n, In& in) __attribute__((always_inline)) {
+        const int ni = min(n, T - 1), t = frame(ni);
+        in.dy = get<W>(a.dy + ((size_t)t * B + row0) * 2 * H + d * H, y_off);
 #pragma unroll
-        for (int k = 0; k < NB / 2; ++k) in.g[k] = g4[k * RT];
-        in.cp = F{};
-        if (n > 0) in.cp = reinterpret_cast<const F*>(a.c)[((size_t)(tp * 2 + d) * NT + tile) * RT + rec0];
+        for (int k = 0; k < NB / 2; ++k) in.g[k] = get<uint4>(reinterpret_cast<const uint4*>(a.gates) + record(t) * (NB / 2) + (size_t)k * RT, rec0 * 16);
+        in.cp = get<F>(reinterpret_cast<const F*>(a.c) + record(frame(min(ni + 1, T - 1))), rec0 * (unsigned)sizeof(F));
+    };
+    auto store_da = [&](int ni) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t p = buffer(a.da + ((size_t)frame(max(ni, 0)) * B + row0) * 8 * H + d * 4 * H, ni < 0 ? 0u : a_bytes);
+#pragma unroll
+        for (int k = 0; k < NB / 2; ++k) put<0>(p, a_off + (unsigned)(k * 8 * 8 * H * 2), das[(ni & 1) * 4 * 16 * AP + da_slot(wave, a_row + 8 * k, a_p)]);
     };
     In in0, in1;
     inputs(0, in0);
-    float c[NB], dcn[NB];                                // this frame's cell state (then the one before's), carried dE/dc
-    {
-        const F cl = reinterpret_cast<const F*>(a.c)[((size_t)((d ? 0 : T - 1) * 2 + d) * NT + tile) * RT + rec0];
+    F c = get<F>(reinterpret_cast<const F*>(a.c) + record(frame(0)), rec0 * (unsigned)sizeof(F));   // this frame's cell state
+    float dcn[NB];                                       // carried dE/dc
 #pragma unroll
-        for (int b = 0; b < NB; ++b) { c[b] = part(cl, b); dcn[b] = 0.0f; }
-    }
+    for (int b = 0; b < NB; ++b) dcn[b] = 0.0f;
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
-    auto do_frame = [&](const int ni, const In& cur, In& nxt, float4* pt) __attribute__((always_inline)) {
-        const int n = T - 1 - ni, t = d ? T - 1 - n : n, row = tile * 16 + l16;
+    bool lost;
+    const bool near = one_xcd(xcds, nu, a.abort_word, a.limit_ticks, &lost);
+    if (lost) poison = __builtin_nanf("");
+    unsigned long long stored = 0;                       // when the last dE/da went out
+    auto do_frame = [&](auto first_frame, const int ni, const In& cur, In& nxt) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_frame)::value;
+        const int t = frame(ni);
+        float4* const pt = ps + (ni & 1) * NW * NB * 64;
         float dh[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) dh[b] = 0.0f;
-        if (ni > 0) {
-            const bf16_t* base = a.dax + ((size_t)((d ? T - 2 - n : n + 1) * 2 + d) * NT + tile) * XT;
+        if constexpr (!FIRST) {
+            bf16_t* const base = a.dax + ((size_t)(frame(ni - 1) * 2 + d) * NT + tile) * XT;
             uint4 f[2][SL];
             bool gu = false;
             if constexpr (!SENTINEL) gu = wait_counter(a.cnt + d * NT + tile, (unsigned)(nu * ni), a.abort_word, a.limit_ticks);
-            look16<SL>(f[0], base, off);
+            const __amdgpu_buffer_rsrc_t x = buffer(base, XT * 2);
+            auto off = [&](int s, unsigned (&o)[SL]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < SL; ++q) o[q] = (unsigned)((s * SL + q) / BW) * (unsigned)(chunks * CHUNK * 2) + offb[(s * SL + q) % BW];
+            };
+            unsigned o[2][SL];
+            off(0, o[0]);
+            if constexpr (PAUSE > 0) while (__builtin_amdgcn_s_memtime() - stored < PAUSE) {}
+            look_through<SL>(f[0], x, o[0]);
+            dys[(ni & 1) * 256 + turned(y_row, l16)] = cur.dy;
             f32x4_t acc[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -248,8 +319,8 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
                 for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
 #pragma unroll
             for (int s = 0; s < NSL; ++s) {
-                if (s + 1 < NSL) look16<SL>(f[(s + 1) & 1], base, [&](int q) { return off((s + 1) * SL + q); });
-                if constexpr (SENTINEL) gu = settle_probe<SL>(f[s & 1], base, [&](int q) { return off(s * SL + q); }, base + probe, lane < KQ, gu, a.abort_word, a.limit_ticks);
+                if (s + 1 < NSL) { off(s + 1, o[(s + 1) & 1]); look_through<SL>(f[(s + 1) & 1], x, o[(s + 1) & 1]); }
+                if constexpr (SENTINEL) gu = await<SL>(f[s & 1], x, o[s & 1], gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                 for (int q = 0; q < SL; ++q)
 #pragma unroll
@@ -258,7 +329,13 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
             if (gu) poison = __builtin_nanf("");
 #pragma unroll
             for (int b = 0; b < NB; ++b) pt[(wave * NB + b) * 64 + lane] = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-            lds_barrier();                               // one a frame: the partial sums are double-buffered
+        } else {
+            dys[(ni & 1) * 256 + turned(y_row, l16)] = cur.dy;
+        }
+        lds_barrier();                                   // one a frame: the buffers are doubled
+        inputs(ni + 1, nxt);
+        store_da(ni - 1);
+        if constexpr (!FIRST) {
             // block b of the partial sums has units 16 b + 4 lq + e of row l16
             F v[NW];
 #pragma unroll
@@ -271,22 +348,25 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
 #pragma unroll
                 for (int b = 0; b < NB; ++b) dh[b] += part(v[w], b);
         }
+        const W dy = dys[(ni & 1) * 256 + turned(l16, 4 * wave + lq)];
+        const bool last = ni == T - 1;                   // (the frame visited first forward has no cell state before it)
         unsigned da[4][NB / 2];                          // a gate's units
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const uint4 g = cur.g[b >> 1];
-            const unsigned gif = b & 1 ? g.z : g.x, ggo = b & 1 ? g.w : g.y, dyw = word(cur.dy, b >> 1);
+            const unsigned gif = b & 1 ? g.z : g.x, ggo = b & 1 ? g.w : g.y, dyw = word(dy, b >> 1);
             const float gi = bf2f((bf16_t)(gif & 0xFFFFu)), gf = bf2f((bf16_t)(gif >> 16));
             const float gg = bf2f((bf16_t)(ggo & 0xFFFFu)), go = bf2f((bf16_t)(ggo >> 16));
             const float dht = dh[b] + bf2f((bf16_t)(b & 1 ? dyw >> 16 : dyw & 0xFFFFu)) + poison;
-            const float tc = fast_tanh(c[b]), cp = part(cur.cp, b);
+            const float tc = fast_tanh(part(c, b)), cp = last ? 0.0f : part(cur.cp, b);
             const float dc = dht * go * (1.0f - tc * tc) + dcn[b];
             const unsigned v[4] = {coh_bf16(dc * gg * gi * (1.0f - gi)), coh_bf16(dc * cp * gf * (1.0f - gf)),
                                    coh_bf16(dc * gi * (1.0f - gg * gg)), coh_bf16(dht * tc * go * (1.0f - go))};
 #pragma unroll
             for (int k = 0; k < 4; ++k) da[k][b >> 1] = b & 1 ? da[k][b >> 1] | (v[k] << 16) : v[k];
-            dcn[b] = dc * gf; c[b] = cp;
+            dcn[b] = dc * gf;
         }
+        c = cur.cp;
         // Eight units of one gate a lane.  NB = 2: word g of lane group lq becomes word lq of lane group g (gate lq, the
         // wavefront's units).  NB = 4: neighbouring groups trade halves (gates 2 (lq % 2) and the next, units 8 (lq / 2) ..).
         uint4 o[NB / 2];
@@ -301,24 +381,21 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
                 o[k] = make_uint4(lo[0], hi[0], lo[1], hi[1]);
             }
         }
-        const int gate0 = NB == 2 ? lq : 2 * (lq & 1), u8 = NB == 2 ? unit0 : unit0 + 8 * (lq >> 1);
-        bf16_t* x = a.dax + ((size_t)(t * 2 + d) * NT + tile) * XT + (size_t)(gate0 * chunks + (u8 >> 3)) * CHUNK + l16 * 8;
-        if (u8 < H) {
+        const __amdgpu_buffer_rsrc_t x = buffer(a.dax + ((size_t)(t * 2 + d) * NT + tile) * XT, XT * 2);
 #pragma unroll
-            for (int k = 0; k < NB / 2; ++k) st_coh_16B(x + (size_t)k * chunks * CHUNK, o[k]);
-        }
+        for (int k = 0; k < NB / 2; ++k) put_exchange(near, x, x_off + (unsigned)(k * chunks * CHUNK * 2), o[k]);
+        if constexpr (PAUSE > 0) stored = __builtin_amdgcn_s_memtime();
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
-        if (ni + 1 < T) inputs(ni + 1, nxt);
-        if (u8 < H && row < B) {
-            bf16_t* p = a.da + ((size_t)t * B + row) * 8 * H + (size_t)(d * 4 + gate0) * H + u8;
 #pragma unroll
-            for (int k = 0; k < NB / 2; ++k) *reinterpret_cast<uint4*>(p + (size_t)k * H) = o[k];
-        }
+        for (int k = 0; k < NB / 2; ++k) das[(ni & 1) * 4 * 16 * AP + da_slot(gate0 + k, l16, (u8 >> 3) - sp.u * AP)] = o[k];
     };
-    for (int ni = 0; ni < T; ni += 2) {
-        do_frame(ni, in0, in1, ps);
-        if (ni + 1 < T) do_frame(ni + 1, in1, in0, ps + NW * NB * 64);
+    do_frame(std::true_type{}, 0, in0, in1);
+    for (int ni = 1; ni < T; ni += 2) {
+        do_frame(std::false_type{}, ni, in1, in0);
+        if (ni + 1 < T) do_frame(std::false_type{}, ni + 1, in0, in1);
     }
+    lds_barrier();
+    store_da(T - 1);
 }
 
 // The groups of tiles a direction is cut into: as many as leave every XCD, which gets whole groups, per_cu workgroups a CU.
@@ -345,11 +422,11 @@ Cut best_cut(int B, int H, int units, int most_per_cu) {
 
 template <int NB, int KQ, bool S>
 hipError_t run(const RecFwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * KQ * 64 * 16, c.grid, c.real, st, launched);
+    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * (KQ * 64 * 16 + 4 * 16 * 4 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
 }
 template <int NB, int KQ, bool S>
 hipError_t run(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * NW * NB * 64 * 16, c.grid, c.real, st, launched);
+    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * (NW * NB * 64 * 16 + 4 * 16 * 2 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
 }
 template <int NB, int KQ, typename A>
 hipError_t run_width(A a, bool sentinel, hipStream_t st, bool* launched) {

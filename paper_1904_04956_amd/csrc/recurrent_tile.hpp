@@ -3,6 +3,7 @@
 #include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
+#include "xcd.hpp"
 #include <type_traits>
 
 namespace blstm {
@@ -39,6 +40,49 @@ __device__ __forceinline__ void park(uint4 (&w)[NB][KQ]) {
                 asm volatile("" : "+a"(v));
                 w[b][q] = __builtin_bit_cast(uint4, v);
             }
+    }
+}
+
+// Stores by buffer: every lane issues them, what does not exist lies beyond the buffer and is dropped.
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+constexpr int SC1 = 16;                                  // cache policy of an agent-scope store: write-through
+constexpr unsigned DROP = 0x7FFFFFF0u;                   // an offset beyond every buffer
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(void* p, unsigned bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000); }
+template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned v) { __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, AUX); }
+template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const uint2& v) { __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.x, v.y}, r, (int)off, 0, AUX); }
+template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const uint4& v) { __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v.x, v.y, v.z, v.w}, r, (int)off, 0, AUX); }
+template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const float2& v) { put<AUX>(r, off, __builtin_bit_cast(uint2, v)); }
+template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, const float4& v) { put<AUX>(r, off, __builtin_bit_cast(uint4, v)); }
+// For the exchange: write-back where the group shares an L2, else write-through.
+template <typename V> __device__ __forceinline__ void put_exchange(bool write_back, __amdgpu_buffer_rsrc_t r, unsigned off, const V& v) {
+    if (write_back) put<0>(r, off, v); else put<SC1>(r, off, v);
+}
+template <typename V> __device__ __forceinline__ V get(const void* base, unsigned off) { return *reinterpret_cast<const V*>(static_cast<const char*>(base) + off); }
+
+// The N 16-byte words at off of a buffer, past the L1 (a look that came too early leaves no stale lines there), and again until no
+// element of them is "not written yet".  Returns true if the wait was abandoned.
+template <int N>
+__device__ __forceinline__ void look_through(uint4 (&f)[N], __amdgpu_buffer_rsrc_t r, const unsigned (&off)[N]) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) f[q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off[q], 0, SC1));
+}
+template <int N>
+__device__ __forceinline__ bool await(uint4 (&f)[N], __amdgpu_buffer_rsrc_t r, const unsigned (&off)[N], bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_there16<N>(f)) return gave_up;
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        asm volatile("" ::: "memory");
+        look_through<N>(f, r, off);
+        if (all_there16<N>(f)) return false;
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
     }
 }
 
