@@ -61,7 +61,7 @@ struct blstm_ctx {
     // workspace (byte offsets)
     std::vector<size_t> wY, wG, wC;
     std::vector<size_t> wDA;  // dE/da of every layer: all of them feed the weight-gradient products at the end of the backward pass
-    size_t wAX, wPRE, wDY[2], wDH, wDC, wLOGITS, wROWLOSS, wUHT, wCNT, wPART, wHX, wDAX, hx_bytes, dax_bytes, part_bytes, ws_bytes;
+    size_t wAX, wPRE, wDY[2], wDH, wDC, wLOGITS, wROWLOSS, wUHT, wCNT, wPART, wHX, wXCD, wDAX, hx_bytes, dax_bytes, part_bytes, ws_bytes;
     long long ldu;            // row distance of the logit matrix (see SoftmaxScratch)
     size_t soft_part;         // split-K scratch of the softmax block's products, the same in both entry points
     bool guarded_xent;        // z or W_s is unaligned, or that of the model this is the twin of: the softmax products' parts are the guarded kernel's, so that both entry points give the same bits
@@ -172,8 +172,8 @@ int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
     return BLSTM_OK;
 }
 
-// The words behind an exchange copy (see xcd.hpp), marked with it.
-inline unsigned* xcd_table(void* copy, size_t bytes) { return reinterpret_cast<unsigned*>(static_cast<char*>(copy) + bytes - XCD_TABLE_BYTES); }
+// A layer's words of xcd.hpp in the forward (0) or backward (1) pass.
+inline unsigned* xcd_table(const blstm_ctx* c, int pass, int layer) { return reinterpret_cast<unsigned*>(c->ws + c->wXCD + ((size_t)pass * c->L + layer) * XCD_TABLE_BYTES); }
 
 inline const char* at(const void* base, size_t elems, size_t esz) { return static_cast<const char*>(base) + elems * esz; }
 inline char* at(void* base, size_t elems, size_t esz) { return static_cast<char*>(base) + elems * esz; }
@@ -462,7 +462,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false;
     c->dax_filled = false;
     c->fwd_persistent.assign(c->L, 0);
-    c->wUHT = w; c->wCNT = w; c->wHX = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
+    c->wUHT = w; c->wCNT = w; c->wHX = w; c->wXCD = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
     if (c->st == DT_BF16 && rec_takes(c->T, c->B, c->H)) {
         const int tiles = (c->B + 31) / 32, nbg = rec_groups(c->H, tiles);
         c->rec_nbg = nbg;
@@ -474,9 +474,12 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         // exchange copies of h and dE/da in MFMA-fragment order, one per layer (whole 32-row tiles),
         // contiguous so that one fill marks all of a pass's copies as "not written yet"
         const size_t Mx = (size_t)c->T * tiles * 32;
-        c->hx_bytes = up256(Mx * 2 * Hr * 2) + XCD_TABLE_BYTES;
-        c->dax_bytes = up256(Mx * 8 * Hr * 2) + XCD_TABLE_BYTES;
+        c->hx_bytes = up256(Mx * 2 * Hr * 2);
+        c->dax_bytes = up256(Mx * 8 * Hr * 2);
+        // between them the words of xcd.hpp, a table per layer and pass: the forward pass's fill takes both, the backward pass's (where
+        // there is one) its own
         c->wHX = w;  w += c->hx_bytes * c->L;
+        c->wXCD = w; w += 2 * XCD_TABLE_BYTES * c->L;
         c->wDAX = w; w += c->dax_bytes * c->L;
     }
     c->rec32_fwd = c->st == DT_F32 && c->T > 1 && rec32_fwd_supported(c->B, c->H);   // (a single frame has no recurrence)
@@ -601,7 +604,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
     const bool fills = (kind >= 2 || (kind == 1 && rec_narrow(ctx->B, H))) && ctx->rec_sync == 1;   // the forward kernels mark the exchange copies of dE/da
     if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
-        RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
+        RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {
         const void* Xin = l == 0 ? x : static_cast<const void*>(ctx->ws + ctx->wY[l - 1]);
         const int Din = ctx->din(l);
@@ -667,7 +670,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.gates = reinterpret_cast<unsigned short*>(G); a.c = C;
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            a.xcd = ctx->rec_sync == 1 ? xcd_table(a.hx, ctx->hx_bytes) : nullptr;
+            a.xcd = ctx->rec_sync == 1 ? xcd_table(ctx, 0, l) : nullptr;
             if (fills) {   // the backward twin's exchange copy is pre-filled on the side
                 a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l;
                 a.fill_words = ctx->dax_bytes / 16;
@@ -795,7 +798,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     // kernels have seen to that, each for its layer; otherwise (protocol switched in between, a second backward pass on
     // one forward pass) one fill.
     if (sentinel && !ctx->dax_filled)
-        RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
+        RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(xcd_table(ctx, 1, 0), XCD_TABLE_BYTES * ctx->L + ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     ctx->dax_filled = false;
     const char* dY;
     int next_buf = 0;
@@ -845,7 +848,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            a.xcd = sentinel ? xcd_table(a.dax, ctx->dax_bytes) : nullptr;
+            a.xcd = sentinel ? xcd_table(ctx, 1, l) : nullptr;
             if (ctx->fwd_persistent[l] == 3) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_tile_bwd(a, sentinel, st, &rec_done));
             else if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
             else RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));

@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         if constexpr (LEAN) for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u);
     };
     if (ntl == 0) { fill_some(1 << 30); return; }        // no batch tile of its own
-    const int fill_each = (int)((share + (unsigned long long)(32 * NW) * (T * ntl)) / ((unsigned long long)(64 * NW) * (T * ntl)));   // (the rest at the end)
+    const int fill_each = (int)((share + (unsigned long long)(64 * NW) * (T * ntl) - 1) / ((unsigned long long)(64 * NW) * (T * ntl)));
 
     // this wavefront's slice of U_h as B-fragments: unit row l32 of each gate, 8 consecutive k per lane
     uint4 bfrag[4][KSTEPS];

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
     uint4* const fill = static_cast<uint4*>(a.fill) + first;
     const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
     unsigned fill_pos = threadIdx.x;
-    const int fill_each = (int)((share + (unsigned long long)(128 * T)) / (unsigned long long)(256 * T));   // (the rest at the end)
+    const int fill_each = (int)((share + (unsigned long long)(256 * T) - 1) / (unsigned long long)(256 * T));
     auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 256) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
     const Spot sp = spot(nu, NT, false);
     if (!sp.real) { fill_some(1 << 30); return; }

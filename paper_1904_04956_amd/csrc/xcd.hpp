@@ -5,7 +5,7 @@
 // Ids are dealt round-robin to the eight XCDs, and the kernels place whole groups by that, but nothing guarantees it.  So every workgroup
 // of a group writes down which XCD it is on, each wavefront reads what its whole group wrote, and only a group found on one XCD
 // uses ordinary stores; all its members come to the same answer.  The words are marked "not written" (all ones) with the exchange
-// copies they lie behind, and written write-through.  Costs a launch about a microsecond, behind the loads of the weights.
+// copies they lie between, and written write-through.  Costs a launch about a microsecond, behind the loads of the weights.
 //
 // Not everywhere the better one: what is written back late is written at the launch's end or in the way of other traffic.  A whole step of
 // four layers (21 frames), us, write-through / through the L2: 128 sequences of 512 cells 804 / 836, 173 967 / 988, 256 of 320 824 / 847, but 500 of
@@ -16,7 +16,7 @@
 
 namespace blstm {
 
-constexpr size_t XCD_TABLE_BYTES = 8192;                 // behind every exchange copy: a word per workgroup, by group and slice
+constexpr size_t XCD_TABLE_BYTES = 8192;                 // of a launch: a word per workgroup, by group and slice
 constexpr int XCD_GROUP_MAX = 64;                        // slices of a group that are looked at (a lane each)
 
 __device__ __forceinline__ unsigned xcd_id() { return (unsigned)__builtin_amdgcn_s_getreg(20 | 3 << 11); }   // hwreg(HW_REG_XCC_ID, 0, 4)
