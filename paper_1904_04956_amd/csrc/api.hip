@@ -602,7 +602,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     }
     const bool persistent = kind > 0;
     const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
-    const bool fills = (kind >= 2 || (kind == 1 && rec_narrow(ctx->B, H))) && ctx->rec_sync == 1;   // the forward kernels mark the exchange copies of dE/da
+    const bool fills = (kind >= 2 || (kind == 1 && (ctx->rec_tiles > 1 || rec_narrow(ctx->B, H)))) && ctx->rec_sync == 1;   // the forward kernels mark the exchange copies of dE/da
     if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {

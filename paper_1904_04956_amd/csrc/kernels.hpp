@@ -75,7 +75,7 @@ bool rec_supported(int H);                  // whether the persistent kernels ta
 bool rec_takes(int T, int B, int H);        // ... and whether they are the faster path for so many frames and sequences
 bool rec_fenced(int H);                     // whether they are built with the fenced protocol too
 int rec_groups(int H, int tiles, int per_cu = 1);   // batch groups per direction for so many 32-row tiles and workgroups per CU
-bool rec_narrow(int B, int H);              // a layer of up to 288 units that recurrent.hip runs (its forward kernel honours RecFwdArgs::fill there)
+bool rec_narrow(int B, int H);              // a layer of up to 288 units that recurrent.hip runs (its forward kernel honours RecFwdArgs::fill there and wherever a workgroup has several tiles)
 // *launched is false (and nothing was enqueued) when the grid cannot be co-resident on this device.
 hipError_t launch_rec_fwd(const RecFwdArgs& a, bool sentinel, hipStream_t st, bool* launched);
 hipError_t launch_rec_bwd(const RecBwdArgs& a, bool sentinel, hipStream_t st, bool* launched);

@@ -99,6 +99,47 @@ __device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* 
     }
 }
 
+// The same through a buffer, past the L1: a scalar offset per pair and one register of lanes' offsets, which leaves the registers to the
+// weights.  `p`: the first pair (uniform).
+template <int NQ>
+__device__ __forceinline__ void load_pairs(uint4 (&frag)[NQ], const bf16_t* p, int last) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, (min(NQ - 1, last) + 1) * XPAIR * 2, 0x00020000);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) frag[q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(threadIdx.x & 63) * 16, min(q, last) * XPAIR * 2, 16));
+}
+// ... and again until all of them are written.  Returns true if the wait was abandoned.
+template <int NQ>
+__device__ __forceinline__ bool await_pairs(uint4 (&frag)[NQ], const bf16_t* p, int last, unsigned* abort_word, unsigned long long limit_ticks) {
+    if (all_written<NQ>(frag)) return false;
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        asm volatile("" ::: "memory");
+        load_pairs<NQ>(frag, p, last);
+        if (all_written<NQ>(frag)) return false;
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit_ticks) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
+// Keeps all of the weights in accumulation registers, which the products read as well as the others.
+template <int NG, int NQ>
+__device__ __forceinline__ void park_all(uint4 (&w)[NG][NQ]) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): one wait for all of them
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            u4 v = __builtin_bit_cast(u4, w[g][q]);
+            asm volatile("" : "+a"(v));
+            w[g][q] = __builtin_bit_cast(uint4, v);
+        }
+}
+
 struct GroupMap { int d, u, bg, group; };
 
 // Workgroups that exchange data sit on one XCD when ids are dealt round-robin over eight XCDs
@@ -159,6 +200,16 @@ constexpr int NW = 4;                                    // wavefronts
 template <int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
 __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
     static_assert(!LEAN || (SENTINEL && MULTI && PADDED && KW < 128), "the forms that are used");
+    // AHEAD (wide slices, several tiles): the next item's operand, written a frame ago, is asked for once the products have left its
+    // registers, its inputs once the cells have left theirs, and every load and store is issued on every path, so that the waits,
+    // which are counted, are for what is needed and not for what has just been asked for.  The weights stay in accumulation
+    // registers.  An item of 1024 units takes 4.1 us, of which the products are 0.9 and the operand's 64 KB through the L1 0.4; the rest
+    // is one wavefront a SIMD going through sums, cells and stores.  A layer, 21 frames, us, with two sets of inputs copied at the end of an
+    // item and a look at one word per producer before the operand / so, forward: 512 sequences of 1024 units 357 / 343, 256 of 1024
+    // 179 / 167, 600 of 768 380 / 364, 1000 of 640 563 / 520, 1000 of 544 553 / 492, 130 of 544 138 / 112; backward 406 / 385,
+    // 206 / 192, 449 / 399, 653 / 569, 642 / 555, 166 / 143; and dE/da's copies are marked on the side (1024: 51 us a step less for two layers).
+    // Taking the pairs of the operand in another order in each workgroup gave nothing, more slabs in flight backward lost 2 to 8 %.
+    constexpr bool AHEAD = MULTI && SENTINEL && !LEAN;
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
     extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
@@ -167,17 +218,17 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
     const int d = gm.d, u = gm.u;
-    const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = PADDED || AHEAD ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     // this workgroup's share of the region to fill, some words every item behind its stores (a share is far below 2^32 words)
-    const unsigned long long share = LEAN && a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
+    const unsigned long long share = (LEAN || AHEAD) && a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
     const unsigned long long fill_first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
     uint4* const fill = static_cast<uint4*>(a.fill) + fill_first;
     const unsigned fill_end = (unsigned)(min(a.fill_words, fill_first + share) - fill_first);
     unsigned fill_pos = threadIdx.x;
     auto fill_some = [&](int words) __attribute__((always_inline)) {
-        if constexpr (LEAN) for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        if constexpr (LEAN || AHEAD) for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 64 * NW) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u);
     };
     if (ntl == 0) { fill_some(1 << 30); return; }        // no batch tile of its own
     const int fill_each = (int)((share + (unsigned long long)(64 * NW) * (T * ntl) - 1) / ((unsigned long long)(64 * NW) * (T * ntl)));
@@ -195,6 +246,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                 bfrag[g][q] = in ? *reinterpret_cast<const uint4*>(uh + (size_t)(g * H + unit) * H + k) : make_uint4(0, 0, 0, 0);
             }
     }
+    if constexpr (AHEAD) park_all(bfrag);
     unsigned* cnt = a.cnt + (size_t)gm.group * a.tiles_per_group;
     const int j = u * 32 + l32;                          // this thread's hidden unit
     float4* l4 = reinterpret_cast<float4*>(lds);
@@ -217,8 +269,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // loaded one item ahead, so that their HBM latency never sits on the frame-to-frame path.
     // Item = (visited frame n, batch tile i); this thread's EPT batch rows are accumulator
     // registers r = EPT*wave + e.
-    auto issue_inputs = [&](int item, float (&ax)[EPT][4], float (&cp)[EPT]) {
-        const int n = item / ntl, i = item - n * ntl;
+    auto issue_inputs = [&](int n, int i, float (&ax)[EPT][4], float (&cp)[EPT]) {
         const int t = d ? T - 1 - n : n;
         const int tp = d ? T - n : n - 1;
         const int b0 = (gm.bg * a.tiles_per_group + i) * 32;
@@ -233,7 +284,8 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         }
         // the previous cell state of this lane's four cells is one 16-byte word of the saved records (one tile: c stays in registers)
         float4 c4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (n > 0 && ntl > 1) c4 = reinterpret_cast<const float4*>(a.c)[rec_index(tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
+        if constexpr (AHEAD) c4 = reinterpret_cast<const float4*>(a.c)[rec_index(n > 0 ? tp : t, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
+        else if (n > 0 && ntl > 1) c4 = reinterpret_cast<const float4*>(a.c)[rec_index(tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
         cp[0] = c4.x; cp[1] = c4.y; cp[2] = c4.z; cp[3] = c4.w;
     };
 
@@ -241,7 +293,12 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
     // in the other, so nothing is copied (a copy would have to wait for loads issued a moment before).
     float ax0[EPT][4], cp0[EPT], ax1[EPT][4], cp1[EPT];
-    if constexpr (!LEAN) issue_inputs(0, ax0, cp0);
+    if constexpr (!LEAN) issue_inputs(0, 0, ax0, cp0);
+    uint4 ahead[AHEAD ? KSTEPS : 1];                     // the operand of the item to come
+    auto operand = [&](int n0, int i) {                  // this wavefront's part (the first frame, which has none: the second one's)
+        const int n = max(n0, 1);
+        return a.hx + ((size_t)((d ? T - n : n - 1) * 2 + d) * NT + gm.bg * a.tiles_per_group + i) * XH + firstp * XPAIR;
+    };
     // Waited for here, once: the compiler places its waits for the worst path into the loop, and with these
     // loads still in flight on the way in, that path would make every item wait for its freshly issued loads.
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0) (expcnt and lgkmcnt left alone)
@@ -274,9 +331,29 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         if (tail.xok && (!PADDED || xcol_ < (unsigned)H)) *reinterpret_cast<uint2*>(yb + ((unsigned)xrow_ * (unsigned)(2 * H) + (unsigned)(d * H) + xcol_)) = tail.hq;
         fill_some(fill_each);
     };
+    // AHEAD: every lane issues every store, what does not exist lies beyond the buffer
+    const __amdgpu_buffer_rsrc_t fill_to = __builtin_amdgcn_make_buffer_rsrc(AHEAD && a.fill ? fill : nullptr, 0, AHEAD ? (int)(fill_end * 16) : 0, 0x00020000);
+    auto store_all = [&]() __attribute__((always_inline)) {
+        const size_t r = rec_index(tail.t, d, tail.b0 >> 5, NT, NU, u);
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        typedef unsigned u2 __attribute__((ext_vector_type(2)));
+        u4* g4 = reinterpret_cast<u4*>(a.gates) + r * 2 * 256 + threadIdx.x;
+        __builtin_nontemporal_store(u4{tail.g[0].x, tail.g[0].y, tail.g[1].x, tail.g[1].y}, g4);   // (not read again here: the L2 is left to the exchange copies, 1 to 2 %)
+        __builtin_nontemporal_store(u4{tail.g[2].x, tail.g[2].y, tail.g[3].x, tail.g[3].y}, g4 + 256);
+        const int row = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane >> 5) + ((lane >> 3) & 3);
+        const unsigned col = (unsigned)(u * 32 + 8 * ((lane >> 1) & 3) + 4 * (lane & 1));
+        const __amdgpu_buffer_rsrc_t y = __builtin_amdgcn_make_buffer_rsrc(a.y + ((size_t)tail.t * B + tail.b0) * 2 * H + d * H, 0, ((min(B - tail.b0, 32) - 1) * 2 * H + H) * 2, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b64(u2{tail.hq.x, tail.hq.y}, y, col < (unsigned)H ? (int)((unsigned)row * 2 * H + col) * 2 : 0x7FFFFFF0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < 2; ++k, fill_pos += 64 * NW) __builtin_amdgcn_raw_buffer_store_b128(u4{~0u, ~0u, ~0u, ~0u}, fill_to, (int)(fill_pos * 16), 0, 2);   // (nontemporal too)
+    };
+    int now_n = 0, now_i = 0;                            // (counted: a division of an item's number costs 100 cycles where it stands)
     auto do_item = [&](const int item, const float (&ax)[EPT][4], const float (&cpl)[EPT], float (&axn)[EPT][4],
                        float (&cpn)[EPT]) __attribute__((always_inline)) {
-        const int n = item / ntl, i = item - n * ntl;
+        const int n = now_n, i = now_i;
+        const bool over = item + 1 == nitems, wraps = i + 1 == ntl;   // the next item (behind the last one: that one again, not used)
+        const int next_n = over ? n : wraps ? n + 1 : n, next_i = over ? i : wraps ? 0 : i + 1;
+        now_n = next_n; now_i = next_i;
         const int t = d ? T - 1 - n : n;
         const int tp = d ? T - n : n - 1;
         const int b0 = (gm.bg * a.tiles_per_group + i) * 32;
@@ -289,8 +366,11 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             // previous h of this batch tile: row l32, 8 consecutive k per lane
             const bf16_t* hb = a.hx + ((size_t)(tp * 2 + d) * NT + (b0 >> 5)) * XH;   // uniform: previous frame, this tile
             const bf16_t* hp = hb + ohp;
-            uint4 afrag[KSTEPS];
-            if (SENTINEL) {
+            uint4 afrag_own[AHEAD ? 1 : KSTEPS];
+            auto& afrag = [&]() -> auto& { if constexpr (AHEAD) return ahead; else return afrag_own; }();
+            if constexpr (AHEAD) {
+                if (await_pairs<KSTEPS>(afrag, operand(n, i), lastp, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            } else if (SENTINEL) {
                 // one probe per producing workgroup of this wavefront's k-range: its last unit, last row
                 const bf16_t* probe = hb + xoff(PADDED ? min(wave * (KW / 32) + lane, NU - 1) * 32 + 31 : wave * KW + (lane & (KW / 32 - 1)) * 32 + 31, 31);
                 bool gu = false;
@@ -316,8 +396,8 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                 for (int q = 0; q < KSTEPS; ++q)
                     afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
-            if constexpr (LEAN) issue_inputs(item, axn, cpn);   // (in flight behind the products)
-            constexpr int GP = LEAN ? 2 : 4;              // gates at a time
+            if constexpr (LEAN) issue_inputs(n, i, axn, cpn);   // (in flight behind the products)
+            constexpr int GP = LEAN || (AHEAD && KW > 224) ? 2 : 4;   // gates at a time
 #pragma unroll
             for (int g0 = 0; g0 < 4; g0 += GP) {
                 f32x16_t acc[GP];
@@ -337,7 +417,13 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                         l4[((wave * 4 + g0 + g) * 4 + rq) * 64 + lane] =
                             make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
             }
-            if (SENTINEL) lds_barrier(); else __syncthreads();
+            if constexpr (!AHEAD) { if (SENTINEL) lds_barrier(); else __syncthreads(); }
+        }
+        if constexpr (AHEAD) {                           // (on either way, so that the wait for the inputs below, which is counted, leaves these loads out)
+            lds_barrier();
+            load_pairs<KSTEPS>(ahead, operand(next_n, next_i), lastp);
+        }
+        if (n > 0) {
             // all partial sums of this thread's rows are read before any is added: the reads then
             // overlap instead of each waiting for its LDS round trip
             static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
@@ -361,12 +447,12 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         // (The next item's inputs come from HBM, and a CU's vector memory pipeline returns data in order: issued
         // before the barrier above they would sit in front of another wavefront's loads of the exchanged h and
         // add their latency to the frame-to-frame path.  They are issued below, once h has gone out.)
-        flush_tail();                                     // at the latest here: the loads issued below may read what it stores
-        if constexpr (LEAN) if (n == 0) issue_inputs(item, axn, cpn);
+        if constexpr (!AHEAD) flush_tail();               // at the latest here: the loads issued below may read what it stores
+        if constexpr (LEAN) if (n == 0) issue_inputs(n, i, axn, cpn);
         float cp[EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : cpl[e];
-        if constexpr (!LEAN) if (item + 1 < nitems) issue_inputs(item + 1, axn, cpn);   // (registers are short later on)
+        for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : AHEAD && n == 0 ? 0.0f : cpl[e];
+        if constexpr (!LEAN && !AHEAD) if (item + 1 < nitems) issue_inputs(next_n, next_i, axn, cpn);   // (registers are short later on)
         // cell arithmetic; h goes out first because it is all the other workgroups wait for
         float gi[EPT], gf[EPT], gg[EPT], go[EPT], cn[EPT], hn[EPT];
         bf16_t* hxb = a.hx + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XH;
@@ -376,7 +462,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             gf[e] = fast_sigmoid((junit ? ax[e][1] : 0.0f) + sum[e][1]);
             gg[e] = fast_tanh((junit ? ax[e][2] : 0.0f) + sum[e][2]);
             go[e] = fast_sigmoid((junit ? ax[e][3] : 0.0f) + sum[e][3]);
-            cn[e] = gf[e] * cp[e] + gi[e] * gg[e];
+            cn[e] = __builtin_fmaf(gf[e], cp[e], gi[e] * gg[e]);   // (spelt out: the same in every variant)
             hn[e] = go[e] * fast_tanh(cn[e]) + poison;
         }
         // A lane holds four rows of one unit; both copies of h want the units of a row side by side.  Regrouped
@@ -409,11 +495,18 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             tail.cn[e] = cn[e];
             tail.g[e] = make_uint2(pack_bf2(gi[e], gf[e]), pack_bf2(gg[e], go[e]));
         }
+        if constexpr (AHEAD) {
+            asm volatile("" ::: "memory");
+            // (c goes out first: where the group has one tile the inputs read it)
+            reinterpret_cast<float4*>(a.c)[rec_index(t, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x] = make_float4(cn[0], cn[1], cn[2], cn[3]);
+            issue_inputs(next_n, next_i, axn, cpn);
+            store_all();
+        }
         // with one tile per workgroup the next item's previous cell state is the one just computed
 #pragma unroll
         for (int e = 0; e < EPT; ++e) ccarry[e] = cn[e];
     };
-    if constexpr (LEAN) {
+    if constexpr (LEAN || AHEAD) {
         for (int item = 0; item < nitems; ++item) do_item(item, ax0, cp0, ax0, cp0);
     } else {
         // (the slice of U_h leaves no room for the loop body twice: one body, and a copy at its end)
@@ -427,7 +520,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             }
         }
     }
-    flush_tail();
+    if constexpr (!AHEAD) flush_tail();
     fill_some(1 << 30);                                  // (whatever rounding left over)
 }
 
@@ -439,20 +532,24 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // The loop body twice, the sets of inputs in turn, and the next ones asked for once dE/da has gone out.  One layer, 4096
     // sequences, us, so / with one body: 288 units 1109 / 1131, 160 592 / 564, 96 336 / 315; wide slices leave no room for two.
     constexpr bool TWO = KW == 96;
+    // AHEAD as in the forward kernel: two slabs of the operand in flight, across the items; one set of inputs, asked for behind the cells.
+    constexpr bool AHEAD = MULTI && SENTINEL && KW > 128;
+    constexpr int SLABS = KSTEPS / 8, DEEP = 2;
     extern __shared__ float lds[];                       // [NW][4][64][4]
     const int H = PADDED ? a.H : NW * KW;                // (the launcher picks KW from a.H)
     const int B = a.B, T = a.T;
     const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
     const GroupMap gm = map_block(NU, a.nbg);
     const int d = gm.d, u = gm.u;
-    const int lane = threadIdx.x & 63, wave = PADDED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = PADDED || AHEAD ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     static_assert(NW == 4, "a wavefront contracts one gate's rows");
     const int ntl = d < 2 ? tiles_in_batch(gm.bg, a.tiles_per_group, B) : 0;   // (d >= 2: a group that does not exist)
     if (ntl == 0) return;
 
     // U_h^T slice: output unit l32, 8 consecutive gate rows per lane
-    uint4 bfrag[KSTEPS];
+    uint4 bfrags[1][KSTEPS];
+    auto& bfrag = bfrags[0];
     {
         const bf16_t* uht = a.uht[d];
 #pragma unroll
@@ -462,6 +559,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             bfrag[q] = in ? *reinterpret_cast<const uint4*>(uht + (size_t)unit * 4 * H + wave * H + k) : make_uint4(0, 0, 0, 0);
         }
     }
+    if constexpr (AHEAD) park_all(bfrags);
     unsigned* cnt = a.cnt + (size_t)gm.group * a.tiles_per_group;
     const int j = u * 32 + l32;
     float4* l4 = reinterpret_cast<float4*>(lds);
@@ -485,8 +583,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // forward kernel's a_x for why).
     constexpr bool WIDE_DY = !MULTI;
     struct Inputs { uint4 g01, g23; bf16_t dy[EPT]; uint4 dyr; float4 c, cp, dcr; };   // g01, g23: (i, f), (g, o) of two cells each as bf16 pairs
-    auto issue_inputs = [&](int item, Inputs& in) {
-        const int ni = item / ntl, i = item - ni * ntl;
+    auto issue_inputs = [&](int ni, int i, Inputs& in) {
         const int n = T - 1 - ni;
         const int t = d ? T - 1 - n : n;
         const int tp = d ? T - n : n - 1;
@@ -499,8 +596,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         const uint4 g01 = g4[0], g23 = g4[256];
         float4 c4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), cp4 = c4, dc4 = c4;
         if constexpr (MULTI) c4 = reinterpret_cast<const float4*>(a.c)[r * 256 + threadIdx.x];   // (one tile: the c of this frame was the item before's c_prev)
-        if (n > 0) cp4 = reinterpret_cast<const float4*>(a.c)[rec_index(tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
-        if (MULTI && n < T - 1 && ntl > 1) dc4 = reinterpret_cast<const float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x];   // (one tile: carried in registers)
+        if (AHEAD || n > 0) cp4 = reinterpret_cast<const float4*>(a.c)[rec_index(AHEAD && n == 0 ? t : tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
+        if (AHEAD || (MULTI && n < T - 1 && ntl > 1)) dc4 = reinterpret_cast<const float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x];   // (one tile: carried in registers)
         if constexpr (WIDE_DY) {                         // piece lane % 32: row (lane % 32) / 4 of the wavefront's eight, units 8 (lane % 4) .. + 7
             const int row0 = 2 * EPT * wave + (l32 >> 2), row = FULL ? row0 : min(row0, B - 1 - b0);
             const int col = u * 32 + (l32 & 3) * 8;
@@ -516,8 +613,15 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 
     static_assert(EPT <= 8, "two sets of inputs (this item's and the next one's) must fit in registers");
     const int nitems = T * ntl;
+    uint4 ahead[DEEP][8];                                // AHEAD: slabs of the operand on their way
+    auto ask = [&](int n0, int i, int sl, uint4 (&to)[8]) __attribute__((always_inline)) {   // slab sl (of the first frame, which has none: of the second)
+        const int ni = max(n0, 1);
+        const bf16_t* p = a.dax + ((size_t)((d ? ni - 1 : T - ni) * 2 + d) * NT + gm.bg * a.tiles_per_group + i) * XA + wave * (HX / 16) * XPAIR;
+        if constexpr (PADDED) load_pairs<8>(to, p + min(sl * 8, lastp) * XPAIR, max(lastp - sl * 8, 0));
+        else load_pairs<8>(to, p + sl * 8 * XPAIR, 8);
+    };
     Inputs in0, in1;                                     // two sets used in turn, as in the forward kernel
-    issue_inputs(0, in0);
+    issue_inputs(0, 0, in0);
     float4 cfirst = make_float4(0.0f, 0.0f, 0.0f, 0.0f);  // (one tile) the c of the first item, later ones are carried
     if constexpr (!MULTI) cfirst = reinterpret_cast<const float4*>(a.c)[rec_index(d ? 0 : T - 1, d, gm.bg, NT, NU, u) * 256 + threadIdx.x];
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): see the forward kernel
@@ -530,8 +634,27 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // NaN once this wave has abandoned a wait, or from the start if the abort word is already raised: added to
     // every dE/da it writes
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    auto await_slab = [&](int ni, int i, int sl) __attribute__((always_inline)) {   // until it is written; true if the wait was abandoned
+        const unsigned long long t0 = wall_clock64();
+        for (unsigned it = 1;; ++it) {
+            asm volatile("" ::: "memory");
+            ask(ni, i, sl, ahead[sl % DEEP]);
+            if (all_written<8>(ahead[sl % DEEP])) return false;
+            if ((it & 31u) == 0) {
+                if (ld_coh_u32(a.abort_word) != 0) return true;
+                if (wall_clock64() - t0 > a.limit_ticks) {
+                    __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return true;
+                }
+            }
+        }
+    };
+    int now_n = 0, now_i = 0;                            // frames from the last one, tile of the item
     auto do_item = [&](const int item, const Inputs& cur, Inputs& nxt) __attribute__((always_inline)) {
-        const int ni = item / ntl, i = item - ni * ntl;
+        const int ni = now_n, i = now_i;
+        const bool over = item + 1 == nitems, wraps = i + 1 == ntl;   // the next item (behind the last one: that one again, not used)
+        const int next_n = over ? ni : wraps ? ni + 1 : ni, next_i = over ? i : wraps ? 0 : i + 1;
+        now_n = next_n; now_i = next_i;
         const int n = T - 1 - ni;
         const int t = d ? T - 1 - n : n;
         const int tn = d ? T - 2 - n : n + 1;            // frame visited after t (its da feeds dh)
@@ -556,7 +679,18 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             f32x16_t acc;
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-            if (SENTINEL) {
+            if constexpr (AHEAD) {
+                bool gu = false;
+#pragma unroll
+                for (int sl = 0; sl < SLABS; ++sl) {
+                    if (!gu && !all_written<8>(ahead[sl % DEEP])) gu = await_slab(ni, i, sl);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) acc = mfma_bf16(ahead[sl % DEEP][q], bfrag[sl * 8 + q], acc);
+                    if (sl + DEEP < SLABS) ask(ni, i, sl + DEEP, ahead[sl % DEEP]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (gu) poison = __builtin_nanf("");
+            } else if (SENTINEL) {
                 // the gate rows of this wavefront come from the NU producers: probe each one's last unit,
                 // then stream the slabs of 128 gate rows with the next slab's loads in flight
                 const bf16_t* probe = ab + xoff(wave * HX + (PADDED ? min(lane, NU - 1) : lane & (4 * KW / 32 - 1)) * 32 + 31, 31);
@@ -595,7 +729,14 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq)
                 l4[(wave * 4 + rq) * 64 + lane] = make_float4(acc[4 * rq], acc[4 * rq + 1], acc[4 * rq + 2], acc[4 * rq + 3]);
-            if (SENTINEL) lds_barrier(); else __syncthreads();
+            if constexpr (!AHEAD) { if (SENTINEL) lds_barrier(); else __syncthreads(); }
+        }
+        if constexpr (AHEAD) {                           // (on either way: see the forward kernel)
+            lds_barrier();
+#pragma unroll
+            for (int sl = 0; sl < DEEP; ++sl) ask(next_n, next_i, sl, ahead[sl]);
+        }
+        if (n < T - 1) {
             // this thread's rows are EPT/4 whole float4 of each wavefront's partial tile; all are read
             // before any is added so that the LDS round trips overlap
             static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
@@ -613,15 +754,16 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 }
         }
         const float curdcr[EPT] = {cur.dcr.x, cur.dcr.y, cur.dcr.z, cur.dcr.w}, curc[EPT] = {cur.c.x, cur.c.y, cur.c.z, cur.c.w};
-        const float curcp[EPT] = {cur.cp.x, cur.cp.y, cur.cp.z, cur.cp.w};
+        const bool none = AHEAD && n == 0;               // (no frame before it)
+        const float curcp[EPT] = {none ? 0.0f : cur.cp.x, none ? 0.0f : cur.cp.y, none ? 0.0f : cur.cp.z, none ? 0.0f : cur.cp.w};
         const uint2 curg[EPT] = {make_uint2(cur.g01.x, cur.g01.y), make_uint2(cur.g01.z, cur.g01.w), make_uint2(cur.g23.x, cur.g23.y), make_uint2(cur.g23.z, cur.g23.w)};
         float dcr[EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) dcr[e] = (!MULTI || ntl == 1) ? dccarry[e] : curdcr[e];
+        for (int e = 0; e < EPT; ++e) dcr[e] = (!MULTI || ntl == 1) ? dccarry[e] : AHEAD && n == T - 1 ? 0.0f : curdcr[e];
         float cthis[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cthis[e] = !MULTI ? ccarry[e] : curc[e];
-        if (!TWO && item + 1 < nitems) issue_inputs(item + 1, nxt);   // (wide slices: registers are short later on)
+        if (!TWO && !AHEAD && item + 1 < nitems) issue_inputs(next_n, next_i, nxt);   // (wide slices: registers are short later on)
         float dcf[EPT];
         unsigned dav[EPT][2];                             // (i, f) and (g, o) as bf16 pairs: kept for the row-major copy below
         bf16_t* dxb = a.dax + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XA;
@@ -671,17 +813,27 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             if (SENTINEL) { st_coh_16B(pa, cga); st_coh_16B(pb, cgb); }
             else { *reinterpret_cast<uint4*>(pa) = cga; *reinterpret_cast<uint4*>(pb) = cgb; }
         }
-        if (TWO && item + 1 < nitems) issue_inputs(item + 1, nxt);
+        if constexpr (AHEAD) {
+            asm volatile("" ::: "memory");
+            issue_inputs(next_n, next_i, nxt);
+        }
+        if (TWO && item + 1 < nitems) issue_inputs(next_n, next_i, nxt);
         if (SENTINEL) lds_barrier();
         else signal_counter(cnt + i);
         // row-major dE/da for the weight- and input-gradient products, and the carried dE/dc
         bf16_t* dab = a.da + ((size_t)t * B + b0) * 8 * H;
-        if (xok && (!PADDED || ucol < (unsigned)H)) {
+        if constexpr (AHEAD) {                           // (every lane issues the stores: see the forward kernel)
+            typedef unsigned u4 __attribute__((ext_vector_type(4)));
+            const __amdgpu_buffer_rsrc_t p = __builtin_amdgcn_make_buffer_rsrc(dab + d * 4 * H, 0, ((min(B - b0, 32) - 1) * 8 * H + 4 * H) * 2, 0x00020000);
+            const int o = !PADDED || ucol < (unsigned)H ? (int)((unsigned)xrow * (unsigned)(8 * H) + (unsigned)(2 * xq * H) + ucol) * 2 : 0x7FFF0000;
+            __builtin_amdgcn_raw_buffer_store_b128(u4{cga.x, cga.y, cga.z, cga.w}, p, o, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(u4{cgb.x, cgb.y, cgb.z, cgb.w}, p, o + 2 * H, 0, 0);
+        } else if (xok && (!PADDED || ucol < (unsigned)H)) {
             bf16_t* pr = dab + ((unsigned)xrow * (unsigned)(8 * H) + (unsigned)(d * 4 * H + 2 * xq * H) + ucol);
             *reinterpret_cast<uint4*>(pr) = cga;
             *reinterpret_cast<uint4*>(pr + H) = cgb;
         }
-        if (ntl > 1)                                      // carried dE/dc of the lane's four cells: one 16-byte word
+        if (AHEAD || ntl > 1)                             // carried dE/dc of the lane's four cells: one 16-byte word
             reinterpret_cast<float4*>(a.dc)[((size_t)(d * NT + (b0 >> 5)) * NU + u) * 256 + threadIdx.x] = make_float4(dcf[0], dcf[1], dcf[2], dcf[3]);
         // next item's inputs; with one tile per workgroup its carried dE/dc is the one just computed
 #pragma unroll
@@ -694,8 +846,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         }
     } else {
         for (int item = 0; item < nitems; ++item) {
-            do_item(item, in0, in1);
-            in0 = in1;
+            do_item(item, in0, AHEAD ? in0 : in1);
+            if constexpr (!AHEAD) in0 = in1;
         }
     }
 }

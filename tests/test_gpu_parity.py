@@ -363,7 +363,7 @@ def test_many_sequences_of_layers_up_to_512_cells_bf16(dims):
     (dict(T=1, B=300, D=8, H=512, L=1, P=0, V=20), (1,)),     # nothing exchanged
 ])
 def test_kernels_on_sixteen_row_tiles_bf16(dims, syncs):
-    check_sixteen_row_tiles(dims, syncs)
+    check_protocols(dims, syncs)
 
 
 @pytest.mark.parametrize("dims,syncs", [
@@ -377,7 +377,7 @@ def test_kernels_on_sixteen_row_tiles_bf16(dims, syncs):
     (dict(T=3, B=400, D=8, H=264, L=1, P=0, V=20), (1,)),
 ])
 def test_several_workgroups_a_cu_on_sixteen_row_tiles_bf16(dims, syncs):
-    check_sixteen_row_tiles(dims, syncs)
+    check_protocols(dims, syncs)
 
 
 @pytest.mark.parametrize("dims,syncs", [
@@ -390,10 +390,23 @@ def test_several_workgroups_a_cu_on_sixteen_row_tiles_bf16(dims, syncs):
     (dict(T=3, B=4100, D=8, H=328, L=1, P=0, V=20), (1,)),
 ])
 def test_several_sixteen_row_tiles_a_workgroup_bf16(dims, syncs):
-    check_sixteen_row_tiles(dims, syncs)
+    check_protocols(dims, syncs)
 
 
-def check_sixteen_row_tiles(dims, syncs):
+@pytest.mark.parametrize("dims,syncs", [
+    (dict(T=3, B=160, D=8, H=1024, L=2, P=0, V=20), (0, 1)),  # groups of two tiles, of one and of none
+    (dict(T=2, B=261, D=8, H=1024, L=1, P=0, V=20), (0, 1)),  # five rows in the last tile
+    (dict(T=1, B=300, D=8, H=1024, L=1, P=0, V=20), (0, 1)),  # nothing exchanged
+    (dict(T=4, B=385, D=8, H=520, L=1, P=0, V=20), (1,)),     # a slice of eight units, a tile of one row
+    (dict(T=3, B=256, D=8, H=768, L=2, P=0, V=20), (1,)),
+    (dict(T=3, B=290, D=8, H=776, L=1, P=0, V=20), (1,)),
+    (dict(T=2, B=300, D=8, H=1016, L=1, P=0, V=20), (1,)),
+])
+def test_several_tiles_a_workgroup_of_wide_layers_bf16(dims, syncs):
+    check_protocols(dims, syncs)
+
+
+def check_protocols(dims, syncs):
     # the same problem under each protocol: against the oracle (2e-2: the storage type), and bit for bit between them
     grads = []
     for sync in syncs:
