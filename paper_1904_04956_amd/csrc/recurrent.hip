@@ -967,10 +967,11 @@ hipError_t run_width(const A& a, bool sentinel, hipStream_t st, bool* launched) 
 // recurrent_tile.hip takes there, and some narrow ones (rec_narrow), on four wavefronts that split the contraction (four batch rows per thread in every variant).
 // 1024 has kernels of its own; the others run padded to the next multiple of 128 (H = 320, 50 sequences, when these kernels ran
 // it: 61 us a layer forward and 66 backward, where launches per frame took 617 and 386).
-// Padded widths above 512 only up to 3072 sequences: beyond, the tiles a workgroup walks backward cost more than the forward
-// pass gains (one layer, 21 frames, both passes, us, persistent / launches per frame: H = 576, B = 2048 3084 / 3709,
-// 3072 4687 / 4582, 4096 6686 / 5935; H = 768, 3072 6252 / 6774, 4096 8893 / 8322; H = 504, 16384 15990 / 19181).  And not
-// for a single frame, which has no recurrence (H = 320, B = 512, two layers forward 46 us against 32).
+// Padded widths above 512 only up to 3072 sequences (tests/test_dispatch_cpu.py holds the line there).  One layer, 21 frames, both
+// passes' recurrences, us, persistent / launches per frame: H = 576, B = 2048 2104 / 3159, 3072 3193 / 3756, 4096 4488 / 4990, 6144
+// 7132 / 6836; H = 768, 3072 3950 / 5215, 4096 5639 / 6222; H = 896, 3072 4445 / 6012: the two cross between 4096 and 6144
+// sequences of 576 units by now, and 8 to 16 % is left between 3072 and there.  And not for a single frame, which has no
+// recurrence (H = 320, B = 512, two layers forward 46 us against 32).
 bool rec_supported(int H) { return H % 8 == 0 && H >= 8 && H <= 1024; }
 bool rec_takes(int T, int B, int H) { return rec_supported(H) && (rec_fenced(H) || (T > 1 && (H <= 512 || B <= 3072))); }
 bool rec_fenced(int H) { return H == 128 || H == 256 || H == 512 || H == 1024; }
