@@ -603,7 +603,8 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     const bool persistent = kind > 0;
     const bool persistent32 = ctx->rec32_fwd && ctx->rec_path == 0 && ctx->rec_sync == 1;
     const bool fills = (kind >= 2 || (kind == 1 && (ctx->rec_tiles > 1 || rec_narrow(ctx->B, H)))) && ctx->rec_sync == 1;   // the forward kernels mark the exchange copies of dE/da
-    if (persistent && ctx->rec_sync == 1)    // h of every layer starts as "not written yet"
+    const bool marks = persistent && ctx->rec_sync == 1;   // h of every layer starts as "not written yet"
+    if (marks && ctx->Dp == 0)                          // (otherwise with the padded copies below)
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
     for (int l = 0; l < ctx->L; ++l) {
         const void* Xin = l == 0 ? x : static_cast<const void*>(ctx->ws + ctx->wY[l - 1]);
@@ -628,6 +629,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
                 // (the copy of W_x is kept while the caller vouches for the weights: see blstm_weights_changed)
                 const bool have_wp = ctx->keep_copies && ctx->wxp_of == theta;
                 pa.count = have_wp ? 1 : 3; pa.cols = Din; pa.cols_p = ctx->Dp;
+                if (marks) { pa.fill = ctx->ws + ctx->wHX; pa.fill_words = (ctx->wDAX - ctx->wHX) / 16; }
                 ctx->wxp_of = have_wp ? theta : nullptr;   // (until the copy is enqueued)
                 RUN(PC_MISC, "padded copies of x and W_x", launch_pad_cols(pa, st));
                 ctx->wxp_of = theta;

@@ -142,6 +142,8 @@ struct PadColsArgs {
     long long ld[3];
     int rows[3];
     int count, cols, cols_p;
+    void* fill;                                // 16-byte words to set to all ones on the way
+    size_t fill_words;
 };
 hipError_t launch_pad_cols(const PadColsArgs& a, hipStream_t st);
 // Fills bytes/16 16-byte words with the 32-bit pattern v.

@@ -878,7 +878,9 @@ __global__ __launch_bounds__(256) void transpose_uh_kernel(TransposeUhArgs a, in
     }
 }
 
-// dst[r][0..cols_p) = src[r][0..cols) followed by zeros: one thread per 8-column chunk, grid-stride.
+// dst[r][0..cols_p) = src[r][0..cols) followed by zeros: one thread per 8-column chunk, grid-stride; and, by all threads, the marking of the
+// exchange copies of h.  Two launches of a few us each were mostly their start and end; large ones are bound by the stores.  Apart /
+// in one, us: 4 x 512 cells, 8 sequences 9.8 / 5.2, 128 11.5 / 8.7, 2048 67 / 64, 6 x 1024, 512 sequences 48 / 48.
 __global__ __launch_bounds__(256) void pad_cols_kernel(PadColsArgs a) {
     const int k = blockIdx.y;
     const unsigned short* src = a.src[k];
@@ -902,6 +904,8 @@ __global__ __launch_bounds__(256) void pad_cols_kernel(PadColsArgs a) {
         }
         *reinterpret_cast<uint4*>(dst + r * a.cols_p + c) = out;
     }
+    const size_t stride = (size_t)gridDim.x * gridDim.y * blockDim.x;
+    for (size_t i = ((size_t)k * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < a.fill_words; i += stride) static_cast<uint4*>(a.fill)[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
 
 // p[0..n) = v for 16-byte words, grid-stride.
@@ -1000,8 +1004,9 @@ hipError_t launch_pad_cols(const PadColsArgs& a, hipStream_t st) {
     if (a.count <= 0) return hipSuccess;
     long long most = 0;
     for (int k = 0; k < a.count; ++k) { const long long n = (long long)a.rows[k] * (a.cols_p / 8); if (n > most) most = n; }
-    if (most == 0) return hipSuccess;
-    long long blocks = (most + 255) / 256;
+    if (most == 0 && a.fill_words == 0) return hipSuccess;
+    const long long fills = (long long)((a.fill_words + 256ull * a.count - 1) / (256ull * a.count));
+    long long blocks = (most + 255) / 256 > fills ? (most + 255) / 256 : fills;
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(pad_cols_kernel, dim3((unsigned)blocks, (unsigned)a.count), dim3(256), 0, st, a);
     return hipGetLastError();

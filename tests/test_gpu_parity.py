@@ -423,6 +423,26 @@ def check_protocols(dims, syncs):
     assert all(np.array_equal(g, grads[0]) for g in grads)
 
 
+@pytest.mark.parametrize("dims", [
+    dict(T=1, B=1, D=1, H=8, L=1, P=0, V=20),               # less to mark than to copy
+    dict(T=3, B=17, D=83, H=512, L=3, P=0, V=20),
+    dict(T=2, B=300, D=9, H=512, L=2, P=0, V=20),
+])
+def test_exchange_copies_marked_with_the_padded_features_bf16(dims):
+    # a pass on other inputs and weights behind a first one (x alone is copied again), bit for bit that of a new learner
+    from paper_1904_04956_amd.harness import Learner
+    check_step(dims, 1, seed=91, theta_scale=2.0)
+    a = Learner(mode=1, **dims)
+    for seed in (92, 93):
+        dm, theta, x, labels = make_problem(dims, 1, seed, 2.0)
+        a.set_theta(theta); a.set_batch(x, labels); a.calgrad()
+        a.set_batch(-x, labels); a.calgrad(); a.check_status()
+    b = Learner(mode=1, **dims)
+    b.set_theta(theta); b.set_batch(-x, labels); b.calgrad()
+    assert np.array_equal(a.grad_numpy(), b.grad_numpy()) and np.array_equal(a.z_numpy(), b.z_numpy())
+    a.close(); b.close()
+
+
 @pytest.mark.parametrize("defer", [False, True])
 @pytest.mark.parametrize("dims,mode", [
     (dict(T=5, B=40, D=30, H=101, L=2, P=37, V=90), 1),     # every width misaligned
