@@ -8,6 +8,10 @@ constexpr unsigned SENT16 = 0xFFFFu;
 
 __device__ __forceinline__ unsigned ld_coh_u32(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// The cell state.  Spelt out: left to the compiler, which of the two products is rounded first differs from kernel to kernel and, with
+// several units a lane, from unit to unit.
+__device__ __forceinline__ float next_cell(float f, float c, float i, float g) { return __builtin_fmaf(f, c, i * g); }
+
 __device__ __forceinline__ bf16_t coh_bf16(float v) {
     bf16_t b = f2bf(v);
     return b == SENT16 ? (bf16_t)0x7FC0 : b;             // a NaN result must not look like "not written yet"

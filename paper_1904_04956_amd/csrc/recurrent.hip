@@ -462,7 +462,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             gf[e] = fast_sigmoid((junit ? ax[e][1] : 0.0f) + sum[e][1]);
             gg[e] = fast_tanh((junit ? ax[e][2] : 0.0f) + sum[e][2]);
             go[e] = fast_sigmoid((junit ? ax[e][3] : 0.0f) + sum[e][3]);
-            cn[e] = __builtin_fmaf(gf[e], cp[e], gi[e] * gg[e]);   // (spelt out: the same in every variant)
+            cn[e] = next_cell(gf[e], cp[e], gi[e], gg[e]);
             hn[e] = go[e] * fast_tanh(cn[e]) + poison;
         }
         // A lane holds four rows of one unit; both copies of h want the units of a row side by side.  Regrouped

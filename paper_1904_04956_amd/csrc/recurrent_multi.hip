@@ -197,7 +197,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
             gf[b] = fast_sigmoid(part(ax[1], b) + acc[b][1]);
             gg[b] = fast_tanh(part(ax[2], b) + acc[b][2]);
             go[b] = fast_sigmoid(part(ax[3], b) + acc[b][3]);
-            c[b] = gf[b] * part(cp, b) + gi[b] * gg[b];
+            c[b] = next_cell(gf[b], part(cp, b), gi[b], gg[b]);
             const unsigned h = coh_bf16(go[b] * fast_tanh(c[b]) + poison);
             hw[b >> 1] = b & 1 ? hw[b >> 1] | (h << 16) : h;
         }

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
         }
         const float gi = fast_sigmoid((junit ? ax[0] : 0.0f) + sum[0]), gf = fast_sigmoid((junit ? ax[1] : 0.0f) + sum[1]);
         const float gg = fast_tanh((junit ? ax[2] : 0.0f) + sum[2]), go = fast_sigmoid((junit ? ax[3] : 0.0f) + sum[3]);
-        c = gf * c + gi * gg;
+        c = next_cell(gf, c, gi, gg);
         const float h = go * fast_tanh(c) + poison;
         const uint2 hq = quad_bf16(h);
         const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * nu + u;

@@ -1,0 +1,49 @@
+"""The persistent bf16 recurrences: results that must not depend on which unit, which way of exchange or which launch of a
+pass they come from.  Bit for bit."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def learner(dims, seed, **options):
+    """A learner with weights and a batch drawn on the device from the seed."""
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    from paper_1904_04956_amd.harness import Learner
+    print(f"case dims={dims} seed={seed} {options}", flush=True)
+    lrn = Learner(mode=1, **dims, **options)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    lrn.theta.copy_(torch.empty(lrn.n, device="cuda").uniform_(-0.1, 0.1, generator=g))
+    bl.blstm_shadow_refresh(lrn.theta, lrn.shadow, lrn.n)
+    lrn.weights_changed()
+    lrn.x.copy_(torch.randn(lrn.x.shape, device="cuda", generator=g) * 2)
+    lrn.labels.copy_(torch.randint(0, dims["V"], lrn.labels.shape, device="cuda", generator=g))
+    return lrn
+
+
+@pytest.mark.parametrize("T,B,H", [
+    (300, 1000, 128), (600, 500, 256), (900, 300, 384), (800, 256, 512),    # one 16-row tile a workgroup, slices of 64 units
+    (2000, 100, 512), (100, 2048, 64),                                      # of 32, and two workgroups a CU
+    (300, 600, 512), (2000, 64, 512), (200, 200, 1024),                     # several tiles, few sequences, wide layers
+])
+def test_units_with_the_same_weights_give_the_same_bits(T, B, H):
+    # Every unit's rows of W_x and b are the same and U_h is zero (wavefronts contract it in orders of their own): so are c and h, in every
+    # frame of 2e5 rows or so.  (One rounding of c shows in h's bf16 once in some 1e5 cells.)
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    lrn = learner(dict(T=T, B=B, D=8, H=H, L=1, P=0, V=8), 7)
+    for d in range(2):
+        for which in (bl.BLSTM_WX, bl.BLSTM_UH, bl.BLSTM_B):
+            off, n = bl.blstm_param_offset(lrn.ctx, 0, d, which)
+            w = lrn.theta[off:off + n].view(4, H, -1)
+            w.copy_(w[:, :1].clone().expand_as(w) * {bl.BLSTM_WX: 3.0, bl.BLSTM_UH: 0.0, bl.BLSTM_B: 1.0}[which])
+    bl.blstm_shadow_refresh(lrn.theta, lrn.shadow, lrn.n)
+    lrn.weights_changed()
+    lrn.forward()
+    lrn.check_status()
+    z = lrn.z.view(T * B, 2, H)
+    assert torch.isfinite(z.float()).all()
+    differ = (z != z[:, :, :1]).sum(dim=(0, 1))
+    others = torch.nonzero(differ).flatten().tolist()
+    assert not others, f"units that differ from the first: {others[:8]}"
+    lrn.close()
