@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
     auto store_y = [&]() __attribute__((always_inline)) {
         const int t = frame(max(before.n, 0)), row0 = (sp.first + before.i) * 16;
         const unsigned bytes = before.n < 0 ? 0u : (unsigned)((min(B - row0, 16) - 1) * 2 * H + H) * 2;
-        put<0>(buffer(a.y + ((size_t)t * B + row0) * 2 * H + d * H, bytes), y_off, ys[(par ^ 1) * 256 + turned(y_row, l16)]);
+        put<later(SENTINEL)>(buffer(a.y + ((size_t)t * B + row0) * 2 * H + d * H, bytes), y_off, ys[(par ^ 1) * 256 + turned(y_row, l16)]);
     };
     auto do_item = [&](auto first_frame, const In& cur, In& nxt) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_frame)::value;
@@ -205,13 +205,13 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + sp.first + now.i);
         const size_t rec = record(t, now.i);
         if constexpr (LOCAL) state[now.i * 64 * NW] = pack(c);
-        else put<0>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));   // (before the loads that may read it)
+        else put<later(SENTINEL)>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));   // (before the loads that may read it)
         inputs(third, nxt);
         const __amdgpu_buffer_rsrc_t g4 = buffer(reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2), RT * (NB / 2) * 16);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k)
-            put<0>(g4, g_off + k * RT * 16, make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1])));
-        if constexpr (LOCAL) put<0>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));
+            put<later(SENTINEL)>(g4, g_off + k * RT * 16, make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1])));
+        if constexpr (LOCAL) put<later(SENTINEL)>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));
         ys[par * 256 + turned(l16, 4 * wave + lq)] = pack(hw);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) fill_word();
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
         const unsigned bytes = before.n < 0 ? 0u : (unsigned)((min(B - row0, 16) - 1) * 8 * H + 4 * H) * 2;
         const __amdgpu_buffer_rsrc_t p = buffer(a.da + ((size_t)t * B + row0) * 8 * H + d * 4 * H, bytes);
 #pragma unroll
-        for (int k = 0; k < NB / 2; ++k) put<0>(p, a_off + (unsigned)(k * 8 * 8 * H * 2), das[(par ^ 1) * 4 * 16 * AP + da_slot(wave, a_row + 8 * k, a_p)]);
+        for (int k = 0; k < NB / 2; ++k) put<later(SENTINEL)>(p, a_off + (unsigned)(k * 8 * 8 * H * 2), das[(par ^ 1) * 4 * 16 * AP + da_slot(wave, a_row + 8 * k, a_p)]);
     };
     auto do_item = [&](auto first_frame, const In& cur, In& nxt) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_frame)::value;
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
         for (int k = 0; k < NB / 2; ++k) put<SC1>(x, x_off + (unsigned)(k * chunks * CHUNK * 2), o[k]);
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + sp.first + now.i);
         if constexpr (LOCAL) { state[now.i * 2 * 64 * NW] = cur.cp; state[(now.i * 2 + 1) * 64 * NW] = pack(dcn); }
-        else put<0>(buffer(reinterpret_cast<F*>(a.dc) + carried, RT * (unsigned)sizeof(F)), dc_off, pack(dcn));
+        else put<later(SENTINEL)>(buffer(reinterpret_cast<F*>(a.dc) + carried, RT * (unsigned)sizeof(F)), dc_off, pack(dcn));
         inputs(first_frame, third, nxt);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) das[par * 4 * 16 * AP + da_slot(gate0 + k, l16, (u8 >> 3) - sp.u * AP)] = o[k];

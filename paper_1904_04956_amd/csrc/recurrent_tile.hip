@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
         for (int k = 0; k < NB; ++k) axr[k] = get<float4>(base + (size_t)(k * (4 / NB)) * H, ax_off);
     };
     auto store_y = [&](int n) __attribute__((always_inline)) {
-        put<0>(buffer(a.y + ((size_t)frame(max(n, 0)) * B + row0) * 2 * H + d * H, n < 0 ? 0u : y_bytes), y_off, ys[(n & 1) * 256 + turned(y_row, l16)]);
+        put<later(SENTINEL)>(buffer(a.y + ((size_t)frame(max(n, 0)) * B + row0) * 2 * H + d * H, n < 0 ? 0u : y_bytes), y_off, ys[(n & 1) * 256 + turned(y_row, l16)]);
     };
     inputs(0);
     float c[NB];
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
         }
         lds_barrier();                                   // one a frame: the buffers are doubled
         inputs(n + 1);
-        store_y(n - 1);
+        if constexpr (SENTINEL) store_y(n - 1);
         if constexpr (!FIRST) {
             // the others in groups of FR, a group read while the one before is multiplied
             uint4 h[2][FR];
@@ -197,14 +197,14 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
         }
         put_exchange(near, buffer(a.hx + ((size_t)(t * 2 + d) * NT + tile) * XT, XT * 2), x_off, pack(hw));
         if constexpr (PAUSE > 0) stored = __builtin_amdgcn_s_memtime();
-        if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
+        if constexpr (!SENTINEL) { signal_counter(a.cnt + d * NT + tile); store_y(n - 1); }
         // what follows is not on the frame-to-frame path
         const size_t rec = ((size_t)(t * 2 + d) * NT + tile) * RT;
         const __amdgpu_buffer_rsrc_t g4 = buffer(reinterpret_cast<uint4*>(a.gates) + rec * (NB / 2), RT * (NB / 2) * 16);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k)
-            put<0>(g4, g_off + k * RT * 16, make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1])));
-        put<0>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));
+            put<later(SENTINEL)>(g4, g_off + k * RT * 16, make_uint4(pack_bf2(gi[2 * k], gf[2 * k]), pack_bf2(gg[2 * k], go[2 * k]), pack_bf2(gi[2 * k + 1], gf[2 * k + 1]), pack_bf2(gg[2 * k + 1], go[2 * k + 1])));
+        put<later(SENTINEL)>(buffer(reinterpret_cast<F*>(a.c) + rec, RT * (unsigned)sizeof(F)), c_off, pack(c));
         ys[(n & 1) * 256 + turned(l16, 4 * wave + lq)] = pack(hw);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) fill_word();
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
     auto store_da = [&](int ni) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t p = buffer(a.da + ((size_t)frame(max(ni, 0)) * B + row0) * 8 * H + d * 4 * H, ni < 0 ? 0u : a_bytes);
 #pragma unroll
-        for (int k = 0; k < NB / 2; ++k) put<0>(p, a_off + (unsigned)(k * 8 * 8 * H * 2), das[(ni & 1) * 4 * 16 * AP + da_slot(wave, a_row + 8 * k, a_p)]);
+        for (int k = 0; k < NB / 2; ++k) put<later(SENTINEL)>(p, a_off + (unsigned)(k * 8 * 8 * H * 2), das[(ni & 1) * 4 * 16 * AP + da_slot(wave, a_row + 8 * k, a_p)]);
     };
     In in0, in1;
     inputs(0, in0);
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
         }
         lds_barrier();                                   // one a frame: the buffers are doubled
         inputs(ni + 1, nxt);
-        store_da(ni - 1);
+        if constexpr (SENTINEL) store_da(ni - 1);
         if constexpr (!FIRST) {
             // block b of the partial sums has units 16 b + 4 lq + e of row l16
             F v[NW];
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_b
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) put_exchange(near, x, x_off + (unsigned)(k * chunks * CHUNK * 2), o[k]);
         if constexpr (PAUSE > 0) stored = __builtin_amdgcn_s_memtime();
-        if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + tile);
+        if constexpr (!SENTINEL) { signal_counter(a.cnt + d * NT + tile); store_da(ni - 1); }
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) das[(ni & 1) * 4 * 16 * AP + da_slot(gate0 + k, l16, (u8 >> 3) - sp.u * AP)] = o[k];
     };

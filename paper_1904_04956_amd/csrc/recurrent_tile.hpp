@@ -48,6 +48,11 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int SC1 = 16;                                  // cache policy of an agent-scope store: write-through
+// ... and of what is stored for later launches.  The fenced protocol's release, once a workgroup and frame, writes back whatever the XCD's L2 holds
+// dirty: nothing, if all stores go through, and those that the signal need not wait for go out behind it.  us for two layers of 21 frames,
+// forward / backward, write-back stores in front of the signal / so: 8 sequences of 512 cells 194 / 177 and 161 / 166, 128 620 / 580 and 480 / 475, 512
+// 1125 / 1235 and 1080 / 1204, 2048 4500 / 4575 and 4280 / 4515, 64 of 1024 490 / 476 and 308 / 454.
+constexpr int later(bool sentinel) { return sentinel ? 0 : SC1; }
 constexpr unsigned DROP = 0x7FFFFFF0u;                   // an offset beyond every buffer
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(void* p, unsigned bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00020000); }
 template <int AUX> __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned v) { __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, AUX); }
