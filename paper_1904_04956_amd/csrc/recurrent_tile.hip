@@ -50,15 +50,14 @@ __device__ __forceinline__ Spot spot(int nu, int nbg) {
 }
 
 // ------------------------------------------------------------------------------ forward
-// Width up to 32 KQ; a workgroup has one tile.
-template <int NB, int KQ, bool SENTINEL>
+// Width up to 32 KQ; a workgroup has one tile.  NEAR: a group on one XCD exchanges through its L2.
+template <int NB, int KQ, bool SENTINEL, bool NEAR>
 __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_fwd_kernel(RecFwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int FR = KQ / NW;                          // fragments a wavefront stages
     constexpr int PP = 4 * NB;                           // 16-byte pieces of a_x a row and gate
-    constexpr bool NEAR = KQ == 8 || NB * KQ == 8;       // exchange through the XCD's L2, or a pause before the look (see the head of this file)
-    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 700 : 600;
+    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 700 : 600;   // clocks before the look (see the head of this file)
     extern __shared__ uint4 hs[];                        // [2][KQ][64], float4 [2][4][16][PP] a_x, W [2][16][16] h
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
@@ -218,14 +217,13 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
 
 // ------------------------------------------------------------------------------ backward
 // Each wavefront contracts KQ / 4 blocks of 32 columns of every gate, SL fragments of dE/da in flight ahead of the products.
-template <int NB, int KQ, bool SENTINEL>
+template <int NB, int KQ, bool SENTINEL, bool NEAR>
 __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, false)) void tile_rec_bwd_kernel(RecBwdArgs a) {
     typedef typename Packs<NB>::F F;
     typedef typename Packs<NB>::W W;
     constexpr int BW = KQ / 4;
     constexpr int SL = 4, NSL = KQ / SL;
     constexpr int AP = 2 * NB;                           // 16-byte pieces of dE/da a row and gate
-    constexpr bool NEAR = KQ == 4;                       // as in the forward kernel
     constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 1200 : 600;
     extern __shared__ float4 ps[];                       // [2][NW][NB][64], uint4 [2][4][16][AP] dE/da, W [2][16][16] dy
     const int T = a.T, B = a.B, H = a.H;
@@ -420,13 +418,28 @@ Cut best_cut(int B, int H, int units, int most_per_cu) {
     return cut(B, H, units, H <= 32 ? 2 : 1);
 }
 
-template <int NB, int KQ, bool S>
-hipError_t run(const RecFwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * (KQ * 64 * 16 + 4 * 16 * 4 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
+// Where the exchange goes through the XCD's L2 (else the look waits, see the head of this file): by the kernel, and wherever a CU has more than
+// one workgroup, whose looks would come too early at any pause.  Whole steps of two layers, 21 frames, us, pause / so: 500 sequences of 256 cells
+// (backward <4, 8>) 571 / 521, 640 of 136 459 / 436; more than one workgroup a CU: 700 of 136 546 / 467, 512 of 200 534 / 480, 400 of 264 657 / 516,
+// 1500 of 128 (forward <4, 4>) 667 / 634.
+constexpr bool near_fwd(int nb, int kq) { return kq == 8 || nb * kq == 8; }
+constexpr bool near_bwd(int nb, int kq) { return kq == 4 || (nb == 4 && kq == 8); }
+constexpr int ONE_A_CU = 256;
+
+template <int NB, int KQ, bool S, bool NEAR>
+hipError_t launch_one(const RecFwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
+    return launch_resident<tile_rec_fwd_kernel<NB, KQ, S, NEAR>>(a, 64 * NW, (size_t)2 * (KQ * 64 * 16 + 4 * 16 * 4 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
 }
-template <int NB, int KQ, bool S>
-hipError_t run(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
-    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S>>(a, 64 * NW, (size_t)2 * (NW * NB * 64 * 16 + 4 * 16 * 2 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
+template <int NB, int KQ, bool S, bool NEAR>
+hipError_t launch_one(const RecBwdArgs& a, const Cut& c, hipStream_t st, bool* launched) {
+    return launch_resident<tile_rec_bwd_kernel<NB, KQ, S, NEAR>>(a, 64 * NW, (size_t)2 * (NW * NB * 64 * 16 + 4 * 16 * 2 * NB * 16 + 256 * NB * 2), c.grid, c.real, st, launched);
+}
+template <int NB, int KQ, bool S, typename A>
+hipError_t run(const A& a, const Cut& c, hipStream_t st, bool* launched) {
+    constexpr bool fwd = std::is_same_v<A, RecFwdArgs>, near = fwd ? near_fwd(NB, KQ) : near_bwd(NB, KQ);
+    if constexpr (S && !near && (fwd ? fwd_per_cu(NB, KQ, false) : bwd_per_cu(NB, KQ, false)) > 1)
+        if (c.real > ONE_A_CU) return launch_one<NB, KQ, S, true>(a, c, st, launched);
+    return launch_one<NB, KQ, S, near>(a, c, st, launched);
 }
 template <int NB, int KQ, typename A>
 hipError_t run_width(A a, bool sentinel, hipStream_t st, bool* launched) {

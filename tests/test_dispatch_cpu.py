@@ -286,6 +286,21 @@ def test_workgroups_on_sixteen_row_tiles(recorder, B, H, units, fwd, bwd):
     assert got == [[str(units), fwd], [str(units), bwd]]
 
 
+@pytest.mark.parametrize("B,H,fwd,bwd", [
+    (500, 256, True, True), (300, 256, True, True), (640, 136, True, True),     # <4, 8>
+    (256, 512, False, False), (128, 512, False, False), (250, 256, True, False),
+    (700, 136, True, True), (400, 264, True, True), (1500, 128, True, True),    # more than one workgroup a CU
+    (190, 320, False, False), (1000, 128, False, True),
+])
+def test_sixteen_row_tiles_that_exchange_through_the_l2(recorder, B, H, fwd, bwd):
+    got = recorder(f"""
+        rec.recorder_occupancy(b"tile_rec", 4)
+        m = Model(T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        out = [[n.split("EEEv")[0][-1] for n in launches(call) if "tile_rec" in n] for call in (m.forward, m.backward)]
+    """)
+    assert got == [[str(int(fwd))], [str(int(bwd))]]
+
+
 @pytest.mark.parametrize("B,H,narrow", [(2048, 96, False), (2049, 96, True), (4096, 104, False), (4096, 64, False), (1280, 136, False), (1281, 160, True),
                                         (1025, 200, True), (1152, 288, False), (1153, 264, True), (4096, 328, False)])
 def test_widths_with_an_empty_half_of_their_last_slice(recorder, B, H, narrow):
