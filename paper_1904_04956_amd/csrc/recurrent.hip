@@ -288,6 +288,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         else if (n > 0 && ntl > 1) c4 = reinterpret_cast<const float4*>(a.c)[rec_index(tp, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x];
         cp[0] = c4.x; cp[1] = c4.y; cp[2] = c4.z; cp[3] = c4.w;
     };
+    auto issue_item = [&](int item, float (&ax)[EPT][4], float (&cp)[EPT]) { const int n = item / ntl; issue_inputs(n, item - n * ntl, ax, cp); };
 
     const int nitems = T * ntl;
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
@@ -347,13 +348,18 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
 #pragma unroll
         for (int k = 0; k < 2; ++k, fill_pos += 64 * NW) __builtin_amdgcn_raw_buffer_store_b128(u4{~0u, ~0u, ~0u, ~0u}, fill_to, (int)(fill_pos * 16), 0, 2);   // (nontemporal too)
     };
-    int now_n = 0, now_i = 0;                            // (counted: a division of an item's number costs 100 cycles where it stands)
+    // (AHEAD: counted.  A division of an item's number costs 100 cycles where it stands; the forms that look at the operand when the item begins, too
+    // early, gain by them: whole steps of two layers, us, without / with it: 128 sequences of 1024 cells 914 / 907, 100 853 / 851, 2048 of 160 1316 / 1312)
+    int now_n = 0, now_i = 0;
     auto do_item = [&](const int item, const float (&ax)[EPT][4], const float (&cpl)[EPT], float (&axn)[EPT][4],
                        float (&cpn)[EPT]) __attribute__((always_inline)) {
-        const int n = now_n, i = now_i;
-        const bool over = item + 1 == nitems, wraps = i + 1 == ntl;   // the next item (behind the last one: that one again, not used)
-        const int next_n = over ? n : wraps ? n + 1 : n, next_i = over ? i : wraps ? 0 : i + 1;
-        now_n = next_n; now_i = next_i;
+        const int n = AHEAD ? now_n : item / ntl, i = AHEAD ? now_i : item - n * ntl;
+        int next_n = 0, next_i = 0;                      // the next item (behind the last one: that one again, not used)
+        if constexpr (AHEAD) {
+            const bool over = item + 1 == nitems, wraps = i + 1 == ntl;
+            next_n = !over && wraps ? n + 1 : n; next_i = over ? i : wraps ? 0 : i + 1;
+            now_n = next_n; now_i = next_i;
+        }
         const int t = d ? T - 1 - n : n;
         const int tp = d ? T - n : n - 1;
         const int b0 = (gm.bg * a.tiles_per_group + i) * 32;
@@ -396,7 +402,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                 for (int q = 0; q < KSTEPS; ++q)
                     afrag[q] = *reinterpret_cast<const uint4*>(hp + min(q, lastp) * XPAIR);
             }
-            if constexpr (LEAN) issue_inputs(n, i, axn, cpn);   // (in flight behind the products)
+            if constexpr (LEAN) issue_item(item, axn, cpn);   // (in flight behind the products)
             constexpr int GP = LEAN || (AHEAD && KW > 224) ? 2 : 4;   // gates at a time
 #pragma unroll
             for (int g0 = 0; g0 < 4; g0 += GP) {
@@ -448,11 +454,11 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         // before the barrier above they would sit in front of another wavefront's loads of the exchanged h and
         // add their latency to the frame-to-frame path.  They are issued below, once h has gone out.)
         if constexpr (!AHEAD) flush_tail();               // at the latest here: the loads issued below may read what it stores
-        if constexpr (LEAN) if (n == 0) issue_inputs(n, i, axn, cpn);
+        if constexpr (LEAN) if (n == 0) issue_item(item, axn, cpn);
         float cp[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cp[e] = (ntl == 1) ? ccarry[e] : AHEAD && n == 0 ? 0.0f : cpl[e];
-        if constexpr (!LEAN && !AHEAD) if (item + 1 < nitems) issue_inputs(next_n, next_i, axn, cpn);   // (registers are short later on)
+        if constexpr (!LEAN && !AHEAD) if (item + 1 < nitems) issue_item(item + 1, axn, cpn);   // (registers are short later on)
         // cell arithmetic; h goes out first because it is all the other workgroups wait for
         float gi[EPT], gf[EPT], gg[EPT], go[EPT], cn[EPT], hn[EPT];
         bf16_t* hxb = a.hx + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XH;
@@ -610,6 +616,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             for (int e = 0; e < EPT; ++e) in.dy[e] = dyb[FULL ? o2b + (unsigned)(re(e) * 2 * H) : (unsigned)(min(rb + re(e), B - 1 - b0) * 2 * H) + o2c];
         }
     };
+    auto issue_item = [&](int item, Inputs& in) { const int ni = item / ntl; issue_inputs(ni, item - ni * ntl, in); };
 
     static_assert(EPT <= 8, "two sets of inputs (this item's and the next one's) must fit in registers");
     const int nitems = T * ntl;
@@ -651,10 +658,13 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     };
     int now_n = 0, now_i = 0;                            // frames from the last one, tile of the item
     auto do_item = [&](const int item, const Inputs& cur, Inputs& nxt) __attribute__((always_inline)) {
-        const int ni = now_n, i = now_i;
-        const bool over = item + 1 == nitems, wraps = i + 1 == ntl;   // the next item (behind the last one: that one again, not used)
-        const int next_n = over ? ni : wraps ? ni + 1 : ni, next_i = over ? i : wraps ? 0 : i + 1;
-        now_n = next_n; now_i = next_i;
+        const int ni = AHEAD ? now_n : item / ntl, i = AHEAD ? now_i : item - ni * ntl;
+        int next_n = 0, next_i = 0;                      // the next item (behind the last one: that one again, not used)
+        if constexpr (AHEAD) {
+            const bool over = item + 1 == nitems, wraps = i + 1 == ntl;
+            next_n = !over && wraps ? ni + 1 : ni; next_i = over ? i : wraps ? 0 : i + 1;
+            now_n = next_n; now_i = next_i;
+        }
         const int n = T - 1 - ni;
         const int t = d ? T - 1 - n : n;
         const int tn = d ? T - 2 - n : n + 1;            // frame visited after t (its da feeds dh)
@@ -763,7 +773,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
         float cthis[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) cthis[e] = !MULTI ? ccarry[e] : curc[e];
-        if (!TWO && !AHEAD && item + 1 < nitems) issue_inputs(next_n, next_i, nxt);   // (wide slices: registers are short later on)
+        if (!TWO && !AHEAD && item + 1 < nitems) issue_item(item + 1, nxt);   // (wide slices: registers are short later on)
         float dcf[EPT];
         unsigned dav[EPT][2];                             // (i, f) and (g, o) as bf16 pairs: kept for the row-major copy below
         bf16_t* dxb = a.dax + ((size_t)(t * 2 + d) * NT + (b0 >> 5)) * XA;
@@ -817,7 +827,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
             asm volatile("" ::: "memory");
             issue_inputs(next_n, next_i, nxt);
         }
-        if (TWO && item + 1 < nitems) issue_inputs(next_n, next_i, nxt);
+        if (TWO && item + 1 < nitems) issue_item(item + 1, nxt);
         if (SENTINEL) lds_barrier();
         else signal_counter(cnt + i);
         // row-major dE/da for the weight- and input-gradient products, and the carried dE/dc
