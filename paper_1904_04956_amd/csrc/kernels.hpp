@@ -68,7 +68,6 @@ struct RecBwdArgs {
     unsigned long long limit_ticks;
     int T, B, H, nbg, tiles_per_group;
     unsigned* xcd;                // as above
-    bool whole_groups;            // set by the launcher (few sequences): see xcd.hpp
     bool ask;                     // as above
 };
 bool rec_supported(int H);                  // whether the persistent kernels take this width

@@ -15,7 +15,6 @@
 #include "kernels.hpp"
 #include "residency.hpp"
 #include "xcd.hpp"
-#include <type_traits>
 
 namespace blstm {
 namespace {
@@ -35,12 +34,10 @@ __device__ __forceinline__ uint2 quad_bf16(float v) {
     return make_uint2(two, __builtin_amdgcn_update_dpp(0u, two, 0x4E, 0xF, 0xF, true));    // quad_perm 2,3,0,1
 }
 
-// Workgroup -> (direction, tile, slice).  whole: whole groups on one XCD (ids are dealt round-robin); otherwise each XCD takes a
-// contiguous eighth of the sequence.
+// Workgroup -> (direction, tile, slice); each XCD (ids are dealt round-robin) takes a contiguous eighth of the sequence.
 struct Spot { int d, tile, u, group; bool real; };
-__device__ __forceinline__ Spot spot(int nu, int ntiles, bool whole) {
-    const int x = (int)(blockIdx.x & 7), k = (int)(blockIdx.x >> 3);
-    const int s = whole ? ((k / nu) * 8 + x) * nu + k % nu : x * (int)(gridDim.x >> 3) + k;
+__device__ __forceinline__ Spot spot(int nu, int ntiles) {
+    const int s = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     Spot p;
     p.real = s < 2 * nu * ntiles;
     p.group = s / nu;
@@ -66,7 +63,7 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
     unsigned fill_pos = threadIdx.x;
     const int fill_each = (int)((share + (unsigned long long)(256 * T) - 1) / (unsigned long long)(256 * T));
     auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 256) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
-    const Spot sp = spot(nu, NT, false);
+    const Spot sp = spot(nu, NT);
     if (!sp.real) { fill_some(1 << 30); return; }
     const int d = sp.d, u = sp.u, tile = sp.tile;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -158,19 +155,23 @@ __global__ __launch_bounds__(64 * NWF, 2) void rec_small_fwd_kernel(RecFwdArgs a
 
 // ------------------------------------------------------------------------------ backward
 // Width up to 32 NQ; wavefront w contracts gate w's columns of dE/da.
-// Whole groups on one XCD exchange through its L2 (xcd.hpp) from NEAR_FROM on: 64 sequences of 512 cells 54.4 -> 49.9 us a layer, 30 of 1024 80 -> 75,
-// but 50 of 320 43.0 -> 44.0; forward it made no difference (a frame's a_x, asked for behind h, takes longer to come than the others' h).
-constexpr int NEAR_FROM = 16;
-template <int NQ>
+// NEAR: groups found on one XCD exchange through its L2 (xcd.hpp).  They can be where the contiguous eighths are whole groups: eight groups
+// of at most 32 slices, 385 to 512 cells and 49 to 64 sequences (64 of 512 cells 53.5 -> 49.5 us a layer; 50 of 320 43.0 -> 44.0, so not there).
+// Elsewhere the answer would be no, and the question takes half a microsecond.
+// Else, from 385 cells on, the probe of the producers right behind the wavefront's own stores comes too early: it waits PAUSE x 64 clocks.  us a layer,
+// PAUSE 0 / 1 / 2 / 3: 8 sequences of 512 cells 48 / 48 / 47 / 47, 32 46 / 46 / 46 / 46, 33 53 / 51 / 48 / 47; 0 / 2 / 4 / 6: 15 of 1024 71 / 69 / 67 / 67, 30 78 / 76 / 72 / 69,
+// 20 of 640 56 / 53 / 51 / 51, 1 of 768 59 / 57 / 55 / 56.
+template <int NQ, bool NEAR>
 __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kernel(RecBwdArgs a) {
     __shared__ float part[2][NWF][16 * PS];
     const int T = a.T, B = a.B, H = a.H;
     const int blocks = (H + 31) / 32, nu = 2 * blocks, NT = (B + 15) / 16;
-    const Spot sp = spot(nu, NT, NQ >= NEAR_FROM && a.whole_groups);
+    const Spot sp = spot(nu, NT);
     if (!sp.real) return;
     const int d = sp.d, u = sp.u, tile = sp.tile;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    unsigned* const xcds = NQ >= NEAR_FROM && a.xcd ? a.xcd + sp.group * nu : nullptr;
+    constexpr int PAUSE = NEAR || NQ < 16 ? 0 : NQ == 16 ? 2 : 4;
+    unsigned* const xcds = NEAR && a.xcd ? a.xcd + sp.group * nu : nullptr;
     tell_xcd(xcds, u);
     const int l16 = lane & 15, lq = lane >> 4;
     uint4 bf[NQ];
@@ -211,6 +212,7 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
             const bf16_t* base = a.dax + ((size_t)(tn * 2 + d) * NT + tile) * XT;
             uint4 af[NQ];
             bool gu = false;
+            if constexpr (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);
             if constexpr (NQ >= PROBE_FROM) {
                 gu = probe_producers16(base + (wave * blocks + min(lane >> 1, blocks - 1)) * PAIR + (lane & 1) * 256 + LAST_OF_SLICE, lane < 2 * NQ, a.abort_word, a.limit_ticks);
                 asm volatile("" ::: "memory");
@@ -255,10 +257,14 @@ __global__ __launch_bounds__(64 * NWF, NQ <= 16 ? 2 : 1) void rec_small_bwd_kern
 }
 
 template <auto KERNEL, typename A>
-hipError_t run(A a, hipStream_t st, bool* launched) {
-    const int nu = 2 * ((a.H + 31) / 32), groups = 2 * ((a.B + 15) / 16), real = nu * groups;
-    if constexpr (std::is_same_v<A, RecBwdArgs>) a.whole_groups = whole_groups(groups, nu);
+hipError_t run(const A& a, hipStream_t st, bool* launched) {
+    const int real = 2 * 2 * ((a.H + 31) / 32) * ((a.B + 15) / 16);
     return launch_resident<KERNEL>(a, 64 * NWF, 0, (real + 7) & ~7, real, st, launched);
+}
+template <int NQ>
+hipError_t run_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched) {
+    if constexpr (NQ == 16) if ((a.B + 15) / 16 == 4) return run<rec_small_bwd_kernel<NQ, true>>(a, st, launched);   // (eight groups)
+    return run<rec_small_bwd_kernel<NQ, false>>(a, st, launched);
 }
 
 }  // namespace
@@ -278,7 +284,7 @@ hipError_t launch_rec_small_fwd(const RecFwdArgs& a, hipStream_t st, bool* launc
 }
 hipError_t launch_rec_small_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched) {
     *launched = false;
-#define BLSTM_SMALL(NQ) if (a.H <= 32 * NQ) return run<rec_small_bwd_kernel<NQ>>(a, st, launched)
+#define BLSTM_SMALL(NQ) if (a.H <= 32 * NQ) return run_bwd<NQ>(a, st, launched)
     BLSTM_SMALL(4); BLSTM_SMALL(8); BLSTM_SMALL(12); BLSTM_SMALL(16); BLSTM_SMALL(20); BLSTM_SMALL(24); BLSTM_SMALL(28); BLSTM_SMALL(32);
 #undef BLSTM_SMALL
     return hipSuccess;

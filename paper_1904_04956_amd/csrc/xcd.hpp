@@ -45,8 +45,4 @@ __device__ __forceinline__ bool one_xcd(const unsigned* table, int n, unsigned* 
     }
 }
 
-// Whether a kernel of `groups` groups of n slices can have whole groups on one XCD (workgroup 8 k + x is slice k % n of group 8 (k / n) + x)
-// in no larger a grid, of which others would have to keep clear.
-inline bool whole_groups(int groups, int n) { return n <= 32 && (groups + 7) / 8 * 8 * n == (groups * n + 7) / 8 * 8; }
-
 }  // namespace blstm

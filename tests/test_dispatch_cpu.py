@@ -301,6 +301,17 @@ def test_sixteen_row_tiles_that_exchange_through_the_l2(recorder, B, H, fwd, bwd
     assert got == [[str(int(fwd))], [str(int(bwd))]]
 
 
+@pytest.mark.parametrize("B,H,asks", [(64, 512, True), (49, 392, True), (48, 512, False), (8, 512, False), (64, 384, False), (15, 1024, False), (30, 1024, False), (40, 640, False)])
+def test_few_sequences_ask_for_their_xcd_only_where_groups_are_whole(recorder, B, H, asks):
+    # (kernels that ask are those with NEAR set; contiguous eighths of the grid are whole groups where there are eight of them)
+    (name,) = recorder(f"""
+        m = Model(T=2, B={B}, D=8, H={H}, L=1, P=0, V=20)
+        launches(m.forward)
+        out = [n for n in launches(m.backward) if "rec_small_bwd" in n]
+    """)
+    assert name.split("EEEv")[0].endswith("ELb1" if asks else "ELb0")
+
+
 @pytest.mark.parametrize("B,H,narrow", [(2048, 96, False), (2049, 96, True), (4096, 104, False), (4096, 64, False), (1280, 136, False), (1281, 160, True),
                                         (1025, 200, True), (1152, 288, False), (1153, 264, True), (4096, 328, False)])
 def test_widths_with_an_empty_half_of_their_last_slice(recorder, B, H, narrow):
