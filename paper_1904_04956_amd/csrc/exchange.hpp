@@ -47,6 +47,36 @@ __device__ __forceinline__ unsigned max_halves(unsigned x, unsigned y) {
 __device__ __forceinline__ unsigned max_halves(const uint4& v) { return max_halves(max_halves(v.x, v.y), max_halves(v.z, v.w)); }
 __device__ __forceinline__ bool has_sentinel_half(unsigned w) { return ((~w - 0x00010001u) & w & 0x80008000u) != 0; }
 
+// Whether every element of every lane's f is written.
+template <int N>
+__device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
+    unsigned m = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
+    return __all(!has_sentinel_half(m));
+}
+// The bounded wait for an operand: f was loaded once, `look` loads it again (past the caches that a look which came too early may have left stale
+// lines in) until all of it is written.  Returns true if the wait was abandoned: before (gave_up), at the time limit, or as someone raised the abort
+// word.  Wave-uniform.
+template <bool NAP, int N, typename L>
+__device__ __forceinline__ bool wait_written(uint4 (&f)[N], L look, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_written<N>(f)) return gave_up;
+    const unsigned long long t0 = wall_clock64();
+    for (unsigned it = 1;; ++it) {
+        asm volatile("" ::: "memory");
+        look();
+        if (all_written<N>(f)) return false;
+        if constexpr (NAP) __builtin_amdgcn_s_sleep(1);
+        if ((it & 31u) == 0) {
+            if (ld_coh_u32(abort_word) != 0) return true;
+            if (wall_clock64() - t0 > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return true;
+            }
+        }
+    }
+}
+
 // Barrier for LDS hazards only: waits for this wave's LDS operations, not for its global loads and
 // write-through stores (a full __syncthreads would drain the loads issued ahead for the next item
 // and the acknowledgements of the exchange stores on every item).
@@ -85,13 +115,6 @@ __device__ __forceinline__ void signal_counter(unsigned* cnt) {
 __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-template <int N>
-__device__ __forceinline__ bool all_there16(const uint4 (&f)[N]) {
-    unsigned m = 0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
-    return __all(!has_sentinel_half(m));
-}
 // f[q] = the 16 bytes at base + off(q): ordinary loads first, past the caches until every element is written.
 // Returns true if the wait was abandoned.
 template <int N, typename F>
@@ -101,21 +124,10 @@ __device__ __forceinline__ void look16(uint4 (&f)[N], const bf16_t* base, F off)
 }
 template <int N, typename F>
 __device__ __forceinline__ bool settle16(uint4 (&f)[N], const bf16_t* base, F off, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_there16<N>(f)) return gave_up;
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
+    return wait_written<true, N>(f, [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
-        if (all_there16<N>(f)) return false;
-        __builtin_amdgcn_s_sleep(1);
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
+    }, gave_up, abort_word, limit);
 }
 
 // Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
@@ -138,17 +150,6 @@ __device__ __forceinline__ bool probe_producers16(const bf16_t* p, bool mine, un
             }
         }
     }
-}
-
-// Returns true if the wait was abandoned.  A look that came too early is followed by the cheap probe of its producers, then by
-// looks past the caches: the probe sees one word of several stores, and the others may be a little later.
-template <int N, typename F>
-__device__ __forceinline__ bool settle_probe(uint4 (&f)[N], const bf16_t* base, F off, const bf16_t* probe, bool probing, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_there16<N>(f)) return gave_up;
-    if (probe_producers16(probe, probing, abort_word, limit)) return true;
-#pragma unroll
-    for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
-    return settle16<N>(f, base, off, false, abort_word, limit);
 }
 
 }  // namespace blstm

@@ -70,13 +70,6 @@ __device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p, 
 #pragma unroll
     for (int q = 0; q < NQ; ++q) frag[q] = ld_coh_16B(p + min(q, last) * XPAIR);
 }
-template <int NQ>
-__device__ __forceinline__ bool all_written(const uint4 (&frag)[NQ]) {
-    unsigned m = 0;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) m = max_halves(m, max_halves(frag[q]));
-    return __all(!has_sentinel_half(m));
-}
 // The chunks in frag were loaded once; reloads them until no element of any lane is the sentinel
 // (or the wait is abandoned).  Normally the first check passes.
 template <int NQ>
@@ -110,20 +103,7 @@ __device__ __forceinline__ void load_pairs(uint4 (&frag)[NQ], const bf16_t* p, i
 // ... and again until all of them are written.  Returns true if the wait was abandoned.
 template <int NQ>
 __device__ __forceinline__ bool await_pairs(uint4 (&frag)[NQ], const bf16_t* p, int last, unsigned* abort_word, unsigned long long limit_ticks) {
-    if (all_written<NQ>(frag)) return false;
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-        asm volatile("" ::: "memory");
-        load_pairs<NQ>(frag, p, last);
-        if (all_written<NQ>(frag)) return false;
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit_ticks) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
+    return wait_written<false, NQ>(frag, [&]() __attribute__((always_inline)) { load_pairs<NQ>(frag, p, last); }, false, abort_word, limit_ticks);
 }
 // Keeps all of the weights in accumulation registers, which the products read as well as the others.
 template <int NG, int NQ>
@@ -641,21 +621,6 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // NaN once this wave has abandoned a wait, or from the start if the abort word is already raised: added to
     // every dE/da it writes
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
-    auto await_slab = [&](int ni, int i, int sl) __attribute__((always_inline)) {   // until it is written; true if the wait was abandoned
-        const unsigned long long t0 = wall_clock64();
-        for (unsigned it = 1;; ++it) {
-            asm volatile("" ::: "memory");
-            ask(ni, i, sl, ahead[sl % DEEP]);
-            if (all_written<8>(ahead[sl % DEEP])) return false;
-            if ((it & 31u) == 0) {
-                if (ld_coh_u32(a.abort_word) != 0) return true;
-                if (wall_clock64() - t0 > a.limit_ticks) {
-                    __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    return true;
-                }
-            }
-        }
-    };
     int now_n = 0, now_i = 0;                            // frames from the last one, tile of the item
     auto do_item = [&](const int item, const Inputs& cur, Inputs& nxt) __attribute__((always_inline)) {
         const int ni = AHEAD ? now_n : item / ntl, i = AHEAD ? now_i : item - ni * ntl;
@@ -693,7 +658,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 bool gu = false;
 #pragma unroll
                 for (int sl = 0; sl < SLABS; ++sl) {
-                    if (!gu && !all_written<8>(ahead[sl % DEEP])) gu = await_slab(ni, i, sl);
+                    gu = wait_written<false, 8>(ahead[sl % DEEP], [&]() __attribute__((always_inline)) { ask(ni, i, sl, ahead[sl % DEEP]); }, gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(ahead[sl % DEEP][q], bfrag[sl * 8 + q], acc);
                     if (sl + DEEP < SLABS) ask(ni, i, sl + DEEP, ahead[sl % DEEP]);

@@ -75,20 +75,7 @@ __device__ __forceinline__ void look_through(uint4 (&f)[N], __amdgpu_buffer_rsrc
 }
 template <int N>
 __device__ __forceinline__ bool await(uint4 (&f)[N], __amdgpu_buffer_rsrc_t r, const unsigned (&off)[N], bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_there16<N>(f)) return gave_up;
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-        asm volatile("" ::: "memory");
-        look_through<N>(f, r, off);
-        if (all_there16<N>(f)) return false;
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
+    return wait_written<false, N>(f, [&]() __attribute__((always_inline)) { look_through<N>(f, r, off); }, gave_up, abort_word, limit);
 }
 
 // A row-major tensor's piece of a tile (16 rows of the slice's units) is moved in whole lines: a wavefront takes four rows, sixteen

@@ -1,4 +1,6 @@
-// The bounded waits of the 16-row tile kernels, one call each: prints result, abort word, loads, whether the data came whole.
+// The bounded waits of the persistent kernels, one call each: prints result, abort word, loads, whether the data came whole.  waits WHAT [few]: as the
+// kernels on 16-row tiles and of the wide layers wait (a first look, then wait_written), or as those for few sequences do (the probe of the
+// producers, a look, then settle16).
 #include "exchange.hpp"
 #include <cstdio>
 #include <cstring>
@@ -7,6 +9,7 @@ using namespace blstm;
 
 int main(int argc, char** argv) {
     const std::string what = argv[1];
+    const bool few = argc > 2;
     constexpr int N = 4;
     alignas(16) static bf16_t data[N * 8 + 8];
     for (bf16_t& e : data) e = 0x3F80;
@@ -19,10 +22,18 @@ int main(int argc, char** argv) {
     if (what == "rest, aborted") on_load = [&](unsigned long long n) { if (n == 500) abort_word = 1; };   // (raised by another workgroup)
     if (what == "late") { memset(data, 0xFF, sizeof data); on_load = [&](unsigned long long n) { if (n == 100) data[32] = data[33] = 0; if (n == 300) memset(data, 0, sizeof data); }; }
     if (what == "given up") { data[3] = 0xFFFF; gave_up = true; }
+    const unsigned long long limit = what == "rest, aborted" ? ~0ull >> 1 : 20;
     uint4 f[N];
-    look16<N>(f, data, off);
     try {
-        const bool r = settle_probe<N>(f, data, off, probe, true, gave_up, &abort_word, what == "rest, aborted" ? ~0ull >> 1 : 20);
-        printf("%d %u %llu %d\n", r, abort_word, loads, all_there16<N>(f));
+        bool r;
+        if (few) {
+            r = gave_up || probe_producers16(probe, true, &abort_word, limit);
+            look16<N>(f, data, off);
+            r = settle16<N>(f, data, off, r, &abort_word, limit);
+        } else {
+            look16<N>(f, data, off);
+            r = wait_written<false, N>(f, [&]() { for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(data + off(q)); }, gave_up, &abort_word, limit);
+        }
+        printf("%d %u %llu %d\n", r, abort_word, loads, all_written<N>(f));
     } catch (too_many_loads) { printf("unbounded\n"); }
 }
