@@ -9,24 +9,26 @@ namespace blstm {
 constexpr int LDS_MOST = 159 * 1024;
 
 // How many workgroups of a kernel the current device holds at once.  The answer depends on the kernel, its LDS and the device only
-// and is kept per kernel and thread for the last of those asked about.
+// and is kept per kernel and thread for the last few of those asked about (the LDS differs between learners: see recurrent_multi.hip).
 template <auto KERNEL>
 hipError_t resident_workgroups(int threads, size_t dyn_lds, int* count) {
-    static thread_local int device = -1, held = 0;
-    static thread_local size_t lds = 0;
+    constexpr int KEPT = 4;
+    struct Asked { int device; size_t lds; int held; };
+    static thread_local Asked asked[KEPT] = {{-1, 0, 0}, {-1, 0, 0}, {-1, 0, 0}, {-1, 0, 0}};
+    static thread_local int oldest = 0;
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (dev != device || dyn_lds != lds) {
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess && dyn_lds > 0)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);   // (not dyn_lds: other threads may launch it with more)
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, dyn_lds);
-        if (e != hipSuccess) return e;
-        held = cus * per_cu;
-        device = dev; lds = dyn_lds;
-    }
-    *count = held;
+    for (const Asked& k : asked)
+        if (k.device == dev && k.lds == dyn_lds) { *count = k.held; return hipSuccess; }
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && dyn_lds > 0)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);   // (not dyn_lds: other threads may launch it with more)
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, dyn_lds);
+    if (e != hipSuccess) return e;
+    asked[oldest] = {dev, dyn_lds, cus * per_cu};
+    oldest = (oldest + 1) % KEPT;
+    *count = cus * per_cu;
     return hipSuccess;
 }
 

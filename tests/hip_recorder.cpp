@@ -20,7 +20,7 @@ static std::string g_fail;
 static std::vector<std::pair<int, std::set<int>>> g_persistent;
 static std::map<void*, std::set<int>> g_with_event, g_before;
 static void* g_capturing = nullptr;
-static int g_device = 0, g_error = 0, g_events = 0;
+static int g_device = 0, g_error = 0, g_events = 0, g_occupancy_asked = 0;
 static struct { dim3 grid, block; size_t lds; void* stream; } g_config;
 
 extern "C" {
@@ -38,6 +38,7 @@ int recorder_persistent() { return (int)g_persistent.size(); }
 int recorder_workgroups(int i) { return g_persistent[i].first; }
 int recorder_behind(int i, int j) { return (int)g_persistent[i].second.count(j); }
 void recorder_capturing(void* stream) { g_capturing = stream; }
+int recorder_occupancy_asked() { return g_occupancy_asked; }
 int recorder_timed(int i) { return g_launches[i].timed; }         // between the two events of a pair
 
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
@@ -78,6 +79,7 @@ int hipDeviceGetAttribute(int* v, int, int device) { *v = g_cus.count(device) ? 
 int hipFuncSetAttribute(const void*, int, int) { return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int, size_t) {
     *n = 1;
+    ++g_occupancy_asked;
     for (auto& o : g_occupancy) if (g_names[f].find(o.first) != std::string::npos) *n = o.second;
     return 0;
 }

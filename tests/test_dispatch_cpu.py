@@ -111,6 +111,23 @@ def test_whether_a_grid_fits_is_asked_for_every_device(recorder, mode, dims):
     assert little == [0, 4]
 
 
+def test_learners_of_several_batches_do_not_ask_again_what_fits(recorder):
+    # the LDS of their kernels differs, by the tiles a workgroup keeps the state of; two devices
+    first, again = recorder("""
+        rec.recorder_occupancy(b"rec_", 2)
+        made = [[Model(T=2, B=B, D=8, H=512, L=1, P=0, V=20) for B in (600, 1200)] for device in (0, 1)]
+        out, last = [], 0
+        for k in range(4):
+            for device in (0, 1):
+                rec.recorder_device(device)
+                for m in made[device]: m.forward(); m.backward()
+            out.append(rec.recorder_occupancy_asked() - last)
+            last += out[-1]
+        out = [out[0], sum(out[1:])]
+    """)
+    assert first > 0 and again == 0
+
+
 @pytest.mark.parametrize("dims,copy,axis", [("T=4, B=16, D=8, H=101, L=2, P=0, V=20", "pad_blocks", 0),      # a twin's weights
                                             ("T=4, B=16, D=30, H=104, L=2, P=0, V=20", "pad_cols", 1)])        # W_x of the first layer
 def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):
