@@ -74,6 +74,7 @@ struct blstm_ctx {
     int rec_sync;             // exchange of the persistent kernels: 0 = fenced counters, 1 = sentinel-tagged data
     bool rec32_fwd, rec32_bwd;   // float mode: the persistent kernels of recurrent_f32.hip take this shape
     bool dax_filled;          // the forward pass's persistent kernels have marked every exchange copy of dE/da "not written yet"
+    unsigned long long dax_capture;   // ... in this capture of a graph (0: in none)
     bool abort_clean;         // the abort word has been zeroed since the workspace was bound
     bool test_abort;          // failure-handling tests: the next forward pass raises the abort word itself
     bool defer_ws;            // softmax_xent_fwd_bwd leaves dW_s and db_s to the next blstm_backward's grouped launch
@@ -170,6 +171,14 @@ int rec_kind(const blstm_ctx* c, bool sentinel, int* kind) {
     if (e != hipSuccess) return check_hip(e, "persistent recurrent kernels");
     if (fwd && bwd) *kind = 1;
     return BLSTM_OK;
+}
+
+// The capture of a graph that the stream's launches go into (0: none).
+unsigned long long capture_of(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(st, &status, &id) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    return status == hipStreamCaptureStatusActive ? id : 0;
 }
 
 // A layer's words of xcd.hpp in the forward (0) or backward (1) pass.
@@ -460,7 +469,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     }
     // persistent recurrent kernels: transposed U_h per layer and direction, counters, abort word
     c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false;
-    c->dax_filled = false;
+    c->dax_filled = false; c->dax_capture = 0;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wXCD = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
     if (c->st == DT_BF16 && rec_takes(c->T, c->B, c->H)) {
@@ -727,6 +736,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     }
     ctx->have_forward = true;
     ctx->dax_filled = fills;
+    if (fills) ctx->dax_capture = capture_of(st);
     return BLSTM_OK;
 }
 
@@ -798,8 +808,8 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     }
     // In sentinel mode every layer's exchange copy of dE/da starts as "not written yet": the forward pass's persistent
     // kernels have seen to that, each for its layer; otherwise (protocol switched in between, a second backward pass on
-    // one forward pass) one fill.
-    if (sentinel && !ctx->dax_filled)
+    // one forward pass) one fill.  And in a graph that does not hold the forward pass too: it may be replayed several times behind one.
+    if (sentinel && !(ctx->dax_filled && ctx->dax_capture == capture_of(st)))
         RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(xcd_table(ctx, 1, 0), XCD_TABLE_BYTES * ctx->L + ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     ctx->dax_filled = false;
     const char* dY;

@@ -20,6 +20,7 @@ static std::string g_fail;
 static std::vector<std::pair<int, std::set<int>>> g_persistent;
 static std::map<void*, std::set<int>> g_with_event, g_before;
 static void* g_capturing = nullptr;
+static unsigned long long g_captures = 0;
 static int g_device = 0, g_error = 0, g_events = 0, g_occupancy_asked = 0;
 static struct { dim3 grid, block; size_t lds; void* stream; } g_config;
 
@@ -37,7 +38,7 @@ unsigned recorder_grid(int i, int axis) { const dim3& g = g_launches[i].grid; re
 int recorder_persistent() { return (int)g_persistent.size(); }
 int recorder_workgroups(int i) { return g_persistent[i].first; }
 int recorder_behind(int i, int j) { return (int)g_persistent[i].second.count(j); }
-void recorder_capturing(void* stream) { g_capturing = stream; }
+void recorder_capturing(void* stream) { g_capturing = stream; ++g_captures; }   // a capture of its own
 int recorder_occupancy_asked() { return g_occupancy_asked; }
 int recorder_timed(int i) { return g_launches[i].timed; }         // between the two events of a pair
 
@@ -71,6 +72,7 @@ int hipStreamWaitEvent(void* stream, void* event, unsigned) {
     return 0;
 }
 int hipStreamIsCapturing(void* stream, int* status) { *status = stream != nullptr && stream == g_capturing; return 0; }
+int hipStreamGetCaptureInfo(void* stream, int* status, unsigned long long* id) { *status = stream != nullptr && stream == g_capturing; *id = g_captures; return 0; }
 int hipEventCreateWithFlags(void** e, unsigned) { *e = malloc(1); return 0; }
 int hipGetLastError() { const int e = g_error; g_error = 0; return e; }
 const char* hipGetErrorString(int) { return "recorded failure"; }

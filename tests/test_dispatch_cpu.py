@@ -128,6 +128,25 @@ def test_learners_of_several_batches_do_not_ask_again_what_fits(recorder):
     assert first > 0 and again == 0
 
 
+@pytest.mark.parametrize("dims", [DIMS, "T=4, B=256, D=8, H=1024, L=1, P=0, V=20", "T=4, B=600, D=8, H=512, L=2, P=0, V=20", "T=4, B=70, D=30, H=101, L=1, P=0, V=20"])
+def test_a_captured_backward_pass_marks_what_its_replays_exchange(recorder, dims):
+    # marked by the forward pass only where both are launched, or both are in one graph
+    fills = recorder(f"""
+        rec.recorder_occupancy(b"rec_", 4)
+        m = Model({dims})
+        fills = lambda s: count(launches(lambda: m.backward(s)), "fill_u128")
+        graph, other = 1 << 16, 1 << 17
+        out = []
+        m.forward(); out.append(fills(0))
+        m.forward()
+        rec.recorder_capturing(ctypes.c_void_p(graph)); out.append(fills(graph))      # behind a launched one
+        rec.recorder_capturing(ctypes.c_void_p(graph)); m.forward(graph); out.append(fills(graph)); out.append(fills(graph))
+        m.forward(graph); rec.recorder_capturing(ctypes.c_void_p(graph)); out.append(fills(graph))   # in a graph of its own
+        m.forward(graph); rec.recorder_capturing(None); out.append(fills(0))
+    """)
+    assert fills == [0, 1, 0, 1, 1, 1]
+
+
 @pytest.mark.parametrize("dims,copy,axis", [("T=4, B=16, D=8, H=101, L=2, P=0, V=20", "pad_blocks", 0),      # a twin's weights
                                             ("T=4, B=16, D=30, H=104, L=2, P=0, V=20", "pad_cols", 1)])        # W_x of the first layer
 def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):

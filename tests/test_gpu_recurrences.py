@@ -47,3 +47,35 @@ def test_units_with_the_same_weights_give_the_same_bits(T, B, H):
     others = torch.nonzero(differ).flatten().tolist()
     assert not others, f"units that differ from the first: {others[:8]}"
     lrn.close()
+
+
+@pytest.mark.parametrize("B,H", [(256, 1024), (130, 544), (16, 512), (128, 512), (600, 512), (1300, 136)])
+def test_a_captured_backward_pass_replayed_twice_on_one_forward_pass(B, H):
+    # other gradients of z each time, as launched calls give them
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    lrn = learner(dict(T=5, B=B, D=8, H=H, L=2, P=0, V=20), 11)
+    s = torch.cuda.Stream()
+    backward = lambda stream: bl.blstm_backward(lrn.ctx, lrn.theta_fwd, lrn.x, lrn.dz, lrn.grad, stream)   # noqa: E731
+    with torch.cuda.stream(s):
+        lrn.calgrad(s)
+        lrn.check_status(s)
+        g = torch.Generator(device="cuda").manual_seed(3)
+        dzs = [torch.randn(lrn.dz.shape, device="cuda", generator=g).to(lrn.dz.dtype) for _ in range(3)]
+        expected = []
+        for dz in dzs:
+            lrn.forward(s); lrn.dz.copy_(dz); lrn.grad.zero_(); backward(s)
+            s.synchronize()
+            expected.append(lrn.grad.clone())
+        lrn.forward(s)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            backward(s)
+        for dz, want in zip(dzs, expected):
+            lrn.dz.copy_(dz); lrn.grad.zero_()
+            graph.replay()
+            s.synchronize()
+            assert torch.equal(lrn.grad, want)
+        lrn.check_status(s)
+    lrn.close()
