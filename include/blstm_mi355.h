@@ -183,6 +183,9 @@ int adpsgd_ring_partner(int R, int64_t step, int32_t* partner_out);
    (BLSTM_ERR_DIM otherwise).  A blstm_forward in between drops what was left over.  Same arithmetic, same results.
    softmax_xent_fwd_bwd_noalloc ignores the option. */
 #define BLSTM_OPT_DEFER_SOFTMAX_WGRAD 5
+/* BLSTM_OPT_TEST_NO_XCD (for tests, default 0): 1 = no group of workgroups is taken to be on one XCD, so that every exchange of the
+   persistent kernels goes through to the memory side, as it must where the groups are spread.  The results are the same. */
+#define BLSTM_OPT_TEST_NO_XCD 6
 int blstm_set_option(blstm_ctx* ctx, int option, int value);
 /* The weights behind theta have changed (see BLSTM_OPT_KEEP_WEIGHT_COPIES).  Host-side only, no device work. */
 int blstm_weights_changed(blstm_ctx* ctx);

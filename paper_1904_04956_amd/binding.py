@@ -229,6 +229,7 @@ BLSTM_OPT_RECURRENT_SYNC = 2
 BLSTM_OPT_KEEP_WEIGHT_COPIES = 3
 BLSTM_OPT_TEST_ABORT = 4
 BLSTM_OPT_DEFER_SOFTMAX_WGRAD = 5
+BLSTM_OPT_TEST_NO_XCD = 6
 BLSTM_NOALLOC_SCRATCH_BYTES = 32 << 20
 
 

@@ -77,6 +77,7 @@ struct blstm_ctx {
     unsigned long long dax_capture;   // ... in this capture of a graph (0: in none)
     bool abort_clean;         // the abort word has been zeroed since the workspace was bound
     bool test_abort;          // failure-handling tests: the next forward pass raises the abort word itself
+    bool test_no_xcd;         // tests: no group of workgroups counts as being on one XCD
     bool defer_ws;            // softmax_xent_fwd_bwd leaves dW_s and db_s to the next blstm_backward's grouped launch
     const void* pend_z;       // ... and has done so: the z it was given (null: nothing pending) and the gradient vector
     float* pend_grad;
@@ -468,7 +469,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
         c->wWP = w; w += up256((size_t)2 * 4 * H * c->Dp * 2);
     }
     // persistent recurrent kernels: transposed U_h per layer and direction, counters, abort word
-    c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false;
+    c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false; c->test_no_xcd = false;
     c->dax_filled = false; c->dax_capture = 0;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wXCD = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
@@ -681,7 +682,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.gates = reinterpret_cast<unsigned short*>(G); a.c = C;
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            a.xcd = ctx->rec_sync == 1 ? xcd_table(ctx, 0, l) : nullptr;
+            a.xcd = ctx->rec_sync == 1 && !ctx->test_no_xcd ? xcd_table(ctx, 0, l) : nullptr;
             if (fills) {   // the backward twin's exchange copy is pre-filled on the side
                 a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l;
                 a.fill_words = ctx->dax_bytes / 16;
@@ -860,7 +861,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             a.dax = reinterpret_cast<unsigned short*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.cnt = cnt; a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H; a.nbg = ctx->rec_nbg; a.tiles_per_group = ctx->rec_tiles;
-            a.xcd = sentinel ? xcd_table(ctx, 1, l) : nullptr;
+            a.xcd = sentinel && !ctx->test_no_xcd ? xcd_table(ctx, 1, l) : nullptr;
             if (ctx->fwd_persistent[l] == 3) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_tile_bwd(a, sentinel, st, &rec_done));
             else if (ctx->fwd_persistent[l] == 2) RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_small_bwd(a, st, &rec_done));
             else RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec_bwd(a, sentinel, st, &rec_done));
@@ -1062,6 +1063,7 @@ int blstm_set_option(blstm_ctx* c, int option, int value) {
         return BLSTM_OK;
     }
     if (option == BLSTM_OPT_TEST_ABORT && (value == 0 || value == 1)) { c->test_abort = value != 0; return BLSTM_OK; }
+    if (option == BLSTM_OPT_TEST_NO_XCD && (value == 0 || value == 1)) { c->test_no_xcd = value != 0; return BLSTM_OK; }
     if (option == BLSTM_OPT_DEFER_SOFTMAX_WGRAD && (value == 0 || value == 1)) {
         c->defer_ws = value != 0;
         if (!c->defer_ws) c->pend_z = nullptr;

@@ -79,3 +79,48 @@ def test_a_captured_backward_pass_replayed_twice_on_one_forward_pass(B, H):
             assert torch.equal(lrn.grad, want)
         lrn.check_status(s)
     lrn.close()
+
+
+@pytest.mark.parametrize("B,H", [
+    (500, 128), (250, 256), (500, 256), (1000, 128),        # one 16-row tile a workgroup
+    (700, 136), (400, 264), (1500, 128), (2600, 40),        # ... and several workgroups a CU
+    (272, 512), (600, 512), (3340, 512), (2100, 256), (3000, 320), (3000, 128),   # several tiles, at 272 a group of a neighbour's too
+    (64, 512), (49, 392),                                   # few sequences
+])
+def test_exchange_through_the_memory_side_gives_the_same_bits(B, H):
+    # groups on one XCD exchange through its L2 where the kernels ask; told that none is, they write through
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    lrn = learner(dict(T=6, B=B, D=8, H=H, L=2, P=0, V=20), 13)
+    results = []
+    for no_xcd in (0, 1, 0):
+        bl.blstm_set_option(lrn.ctx, bl.BLSTM_OPT_TEST_NO_XCD, no_xcd)
+        for _ in range(2):
+            lrn.grad.zero_()
+            lrn.calgrad()
+        lrn.check_status()
+        results.append((lrn.loss.clone(), lrn.z.clone(), lrn.grad.clone()))
+    assert torch.isfinite(results[0][2]).all()
+    for r in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(r, results[0]))
+    lrn.close()
+
+
+@pytest.mark.parametrize("B,H", [(200, 1024), (130, 544), (1500, 128), (400, 264), (60, 512), (3340, 512)])
+def test_abandoned_waits_of_the_other_kernels(B, H):
+    # raised from the host, as in test_gpu_parity.py: the forms of the wide layers that look ahead, several workgroups a CU, carried state in memory
+    import torch
+    from paper_1904_04956_amd import binding as bl
+    lrn = learner(dict(T=6, B=B, D=8, H=H, L=2, P=0, V=20), 17)
+    lrn.calgrad(); lrn.check_status()
+    clean = lrn.grad.clone()
+    assert torch.isfinite(clean).all()
+    bl.blstm_set_option(lrn.ctx, bl.BLSTM_OPT_TEST_ABORT, 1)
+    lrn.calgrad()
+    with pytest.raises(bl.BlstmError) as e:
+        lrn.check_status()
+    assert e.value.code == -5 and "abandoned" in str(e.value)
+    assert torch.isnan(lrn.loss).all() and torch.isnan(lrn.z).any() and torch.isnan(lrn.grad).any()
+    lrn.calgrad(); lrn.check_status()
+    assert torch.equal(lrn.grad, clean)
+    lrn.close()
