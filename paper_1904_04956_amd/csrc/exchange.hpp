@@ -55,12 +55,10 @@ __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
     return __all(!has_sentinel_half(m));
 }
-// The bounded wait for an operand: f was loaded once, `look` loads it again (past the caches that a look which came too early may have left stale
-// lines in) until all of it is written.  Returns true if the wait was abandoned: before (gave_up), at the time limit, or as someone raised the abort
-// word.  Wave-uniform.
+// The bounded wait for an operand: `look` loads f (past the caches that a look which came too early may have left stale lines in) until all of it is
+// written.  Returns true if the wait was abandoned, at the time limit or as someone raised the abort word.  Wave-uniform.
 template <bool NAP, int N, typename L>
-__device__ __forceinline__ bool wait_written(uint4 (&f)[N], L look, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || all_written<N>(f)) return gave_up;
+__device__ __forceinline__ bool look_again(uint4 (&f)[N], L look, unsigned* abort_word, unsigned long long limit) {
     const unsigned long long t0 = wall_clock64();
     for (unsigned it = 1;; ++it) {
         asm volatile("" ::: "memory");
@@ -75,6 +73,12 @@ __device__ __forceinline__ bool wait_written(uint4 (&f)[N], L look, bool gave_up
             }
         }
     }
+}
+// ... behind a first look, unless that found everything or an earlier wait was abandoned.
+template <bool NAP, int N, typename L>
+__device__ __forceinline__ bool wait_written(uint4 (&f)[N], L look, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_written<N>(f)) return gave_up;
+    return look_again<NAP, N>(f, look, abort_word, limit);
 }
 
 // Barrier for LDS hazards only: waits for this wave's LDS operations, not for its global loads and

@@ -658,7 +658,8 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 bool gu = false;
 #pragma unroll
                 for (int sl = 0; sl < SLABS; ++sl) {
-                    gu = wait_written<false, 8>(ahead[sl % DEEP], [&]() __attribute__((always_inline)) { ask(ni, i, sl, ahead[sl % DEEP]); }, gu, a.abort_word, a.limit_ticks);
+                    // (spelt out: through wait_written another 2 % of a layer of 768 units)
+                    if (!gu && !all_written<8>(ahead[sl % DEEP])) gu = look_again<false, 8>(ahead[sl % DEEP], [&]() __attribute__((always_inline)) { ask(ni, i, sl, ahead[sl % DEEP]); }, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(ahead[sl % DEEP][q], bfrag[sl * 8 + q], acc);
                     if (sl + DEEP < SLABS) ask(ni, i, sl + DEEP, ahead[sl % DEEP]);
