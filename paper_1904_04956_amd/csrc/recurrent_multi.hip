@@ -30,8 +30,9 @@ __device__ __forceinline__ Spot spot(int nu, int nbg, int ntiles, bool pair) {
     Spot p;
     p.u = __builtin_amdgcn_readfirstlane(slot % nu); p.d = __builtin_amdgcn_readfirstlane(group / nbg); p.group = group;
     const int g = group - p.d * nbg;
-    p.first = __builtin_amdgcn_readfirstlane((int)((unsigned)(g * ntiles) / (unsigned)nbg));   // (at most 128 groups)
-    p.ntl = group < 2 * nbg ? __builtin_amdgcn_readfirstlane((int)((unsigned)((g + 1) * ntiles) / (unsigned)nbg)) - p.first : 0;
+    // (at most 256 groups a direction -- a slice of 32 units, two workgroups a CU --, so the products stay below 2^32 with 2^24 tiles)
+    p.first = __builtin_amdgcn_readfirstlane((int)((unsigned)g * (unsigned)ntiles / (unsigned)nbg));
+    p.ntl = group < 2 * nbg ? __builtin_amdgcn_readfirstlane((int)((unsigned)(g + 1) * (unsigned)ntiles / (unsigned)nbg)) - p.first : 0;
     if (pair && p.ntl == 1 && ntiles > 1) { p.first = max(p.first - 1, 0); p.ntl = 2; }
     return p;
 }

@@ -26,7 +26,10 @@
 // the look is what comes too early: either the exchange goes through the XCD's L2 (NEAR, see xcd.hpp), twice as fast, or the look
 // waits until PAUSE clocks after the wavefront's own stores.  us a layer, write-through, pause of 0 / 600 / 900 / 1200 / 1500 / 1800: 256 sequences of 512
 // cells, backward 104 / 87 / 78 / 76 / 75 / 77, 128 70 / 52 / 54 / 56 / 58 / 61; forward 64 / 64 / 63 / 64 / 67 / 69 and 48 / 45 / 47 / 49 / 51 / 54; 64 of
-// 1024 backward 94 / 73 / 76 / 78 / 80 / 82.
+// 1024 backward 94 / 73 / 76 / 78 / 80 / 82.  The other kernels, write-through, 0 / 600 / 900 / 1200, and through the L2: forward <2, 12> (128 of 384) 43 / 40 /
+// 42 / 45, 37; <2, 20> (60 of 640) 48 / 45 / 47 / 49, 42; <2, 24> (64 of 768) 53 / 50 / 52 / 55, 48; <2, 28> (64 of 896) 58 / 54 / 56 / 59, 52; <4, 4> (1000 of 128) 55 / 52 / 52 / 52, 58;
+// <4, 12> (300 of 384) 63 / 58 / 57 / 58, 60; backward <2, 12> 63 / 45 / 47 / 50, 42; <2, 20> 67 / 52 / 54 / 57, 49; <2, 24> 76 / 60 / 62 / 64, 57; <2, 28> 86 / 66 / 67 / 69, 70;
+// <4, 8> (500 of 256) 103 / 95 / 91 / 86, 61; <4, 12> 94 / 82 / 75 / 71, 70.  What the L2 gains a layer a step can lose again (see near_fwd below).
 //
 // us a layer of 21 frames, forward / backward, before (a lane to a row, inputs behind the stores) and now: 512 cells, 128 sequences 49 / 55 and 45 / 52,
 // 173 63 / 72 and 57 / 66, 256 71 / 79 and 63 / 76; 1024, 64 66 / 78 and 60 / 73; 320, 256 56 / 64 and 48 / 57; 128, 500 38 / 38 and 32 / 32; 64,
@@ -419,9 +422,10 @@ Cut best_cut(int B, int H, int units, int most_per_cu) {
 }
 
 // Where the exchange goes through the XCD's L2 (else the look waits, see the head of this file): by the kernel, and wherever a CU has more than
-// one workgroup, whose looks would come too early at any pause.  Whole steps of two layers, 21 frames, us, pause / so: 500 sequences of 256 cells
-// (backward <4, 8>) 571 / 521, 640 of 136 459 / 436; more than one workgroup a CU: 700 of 136 546 / 467, 512 of 200 534 / 480, 400 of 264 657 / 516,
-// 1500 of 128 (forward <4, 4>) 667 / 634.
+// one workgroup, whose looks would come too early at any pause.  Whole steps of four layers, 21 frames, 8000 classes, us, pause / so: 500 sequences of 256 cells
+// (backward <4, 8>) 1299 / 1190, 640 of 136 1215 / 1077; more than one workgroup a CU: 700 of 136 1385 / 1169, 512 of 200 1285 / 1082, 400 of 264 1584 / 1230,
+// 1500 of 128 (forward <4, 4>) 2064 / 1996.  But 128 of 512 885 / 923, 1000 of 128 1393 / 1422 and 600 of 128 (forward) 976 / 998: the lines left dirty are written in the way of
+// the products that follow.
 constexpr bool near_fwd(int nb, int kq) { return kq == 8 || nb * kq == 8; }
 constexpr bool near_bwd(int nb, int kq) { return kq == 4 || (nb == 4 && kq == 8); }
 constexpr int ONE_A_CU = 256;

@@ -5,7 +5,7 @@
 // Ids are dealt round-robin to the eight XCDs, and the kernels place whole groups by that, but nothing guarantees it.  So every workgroup
 // of a group writes down which XCD it is on, each wavefront reads what its whole group wrote, and only a group found on one XCD
 // uses ordinary stores; all its members come to the same answer.  The words are marked "not written" (all ones) with the exchange
-// copies they lie between, and written write-through.  Costs a launch about a microsecond, behind the loads of the weights.
+// copies they lie between, and written write-through.  Costs a launch half a microsecond to one and a half, behind the loads of the weights.
 //
 // Not everywhere the better one: what is written back late is written at the launch's end or in the way of other traffic.  A whole step of
 // four layers (21 frames), us, write-through / through the L2: 128 sequences of 512 cells 804 / 836, 173 967 / 988, 256 of 320 824 / 847, but 500 of
