@@ -88,6 +88,14 @@ def test_options_take_their_values_only():
         bl.blstm_destroy(ctx)
 
 
+def test_the_option_for_spread_groups_takes_its_values_only():
+    ctx = bl.blstm_create(2, 2, 2, 2, 1, 0, 2, 1)
+    try:
+        assert [bl.lib().blstm_set_option(ctx, bl.BLSTM_OPT_TEST_NO_XCD, v) for v in (1, 0, 2)] == [0, 0, -2]
+    finally:
+        bl.blstm_destroy(ctx)
+
+
 def test_calls_validate_before_launching():
     ctx = bl.blstm_create(2, 2, 2, 2, 1, 0, 2, 0)
     L = bl.lib()
