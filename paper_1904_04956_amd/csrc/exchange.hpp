@@ -23,7 +23,8 @@ __device__ __forceinline__ void st_coh_8B(bf16_t* p, const uint2& v) {
 // One 16-byte store with the cache policy of an agent-scope atomic store (write-through to L2: sc1), written in assembly
 // because atomics stop at 8 bytes and a store instruction costs the memory pipeline the same whatever its width.  The
 // protocol needs no atomicity beyond each 16-bit element's, which every aligned store gives.  (The compiler does not
-// count this store in its vmcnt bookkeeping; its own waits then only wait for more than they need.)
+// count this store in its vmcnt bookkeeping; its own waits then only wait for more than they need.  Not for the FENCED
+// protocol: with nothing else in flight, the compiler leaves out the wait between a release's write-back and the counter.)
 typedef unsigned int u32x4s_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void st_coh_16B(bf16_t* p, const uint4& v) {
     const u32x4s_t w = {v.x, v.y, v.z, v.w};
