@@ -29,7 +29,8 @@
 // 1024 backward 94 / 73 / 76 / 78 / 80 / 82.  The other kernels, write-through, 0 / 600 / 900 / 1200, and through the L2: forward <2, 12> (128 of 384) 43 / 40 /
 // 42 / 45, 37; <2, 20> (60 of 640) 48 / 45 / 47 / 49, 42; <2, 24> (64 of 768) 53 / 50 / 52 / 55, 48; <2, 28> (64 of 896) 58 / 54 / 56 / 59, 52; <4, 4> (1000 of 128) 55 / 52 / 52 / 52, 58;
 // <4, 12> (300 of 384) 63 / 58 / 57 / 58, 60; backward <2, 12> 63 / 45 / 47 / 50, 42; <2, 20> 67 / 52 / 54 / 57, 49; <2, 24> 76 / 60 / 62 / 64, 57; <2, 28> 86 / 66 / 67 / 69, 70;
-// <4, 8> (500 of 256) 103 / 95 / 91 / 86, 61; <4, 12> 94 / 82 / 75 / 71, 70.  What the L2 gains a layer a step can lose again (see near_fwd below).
+// <4, 8> (500 of 256) 103 / 95 / 91 / 86, 61; <4, 12> 94 / 82 / 75 / 71, 70.  Forward passes of four layers of 512 cells, 700 / 760 / 800: 256 sequences 467 / 463 / 462, 129 384 /
+// 385 / 386.  What the L2 gains a layer a step can lose again (see near_fwd below).
 //
 // us a layer of 21 frames, forward / backward, before (a lane to a row, inputs behind the stores) and now: 512 cells, 128 sequences 49 / 55 and 45 / 52,
 // 173 63 / 72 and 57 / 66, 256 71 / 79 and 63 / 76; 1024, 64 66 / 78 and 60 / 73; 320, 256 56 / 64 and 48 / 57; 128, 500 38 / 38 and 32 / 32; 64,
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, false)) void tile_rec_f
     typedef typename Packs<NB>::W W;
     constexpr int FR = KQ / NW;                          // fragments a wavefront stages
     constexpr int PP = 4 * NB;                           // 16-byte pieces of a_x a row and gate
-    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 700 : 600;   // clocks before the look (see the head of this file)
+    constexpr int PAUSE = NEAR ? 0 : NB == 4 ? 760 : 600;   // clocks before the look (see the head of this file)
     extern __shared__ uint4 hs[];                        // [2][KQ][64], float4 [2][4][16][PP] a_x, W [2][16][16] h
     const int T = a.T, B = a.B, H = a.H;
     const int chunks = H / 8, nu = (H + 16 * NB - 1) / (16 * NB), NT = (B + 15) / 16;
