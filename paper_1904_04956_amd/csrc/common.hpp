@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <utility>
 
 namespace blstm {
 
@@ -21,6 +22,12 @@ __device__ __forceinline__ float bf2f(bf16_t b) {
 __device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) {
     return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
 }
+
+// f(FROM), f(FROM + 1), .. f(TO - 1), the number as a type
+template <int FROM, typename F, int... K>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, K...>, F&& f) { (f(std::integral_constant<int, FROM + K>{}), ...); }
+template <int FROM, int TO, typename F>
+__device__ __forceinline__ void each(F&& f) { each_of<FROM>(std::make_integer_sequence<int, TO - FROM>{}, f); }
 
 // Element load/store by storage type.
 __device__ __forceinline__ float ld_f(const float* p) { return *p; }

@@ -181,18 +181,23 @@ template <int KW, bool SENTINEL, bool FULL, bool MULTI, bool PADDED, bool LEAN>
 __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdArgs a) {
     static_assert(!LEAN || (SENTINEL && MULTI && PADDED && KW < 128), "the forms that are used");
     // AHEAD (wide slices, several tiles): the next item's operand, written a frame ago, is asked for once the products have left its
-    // registers, its inputs once the cells have left theirs, and every load and store is issued on every path, so that the waits,
+    // registers, and every load and store is issued on every path, so that the waits,
     // which are counted, are for what is needed and not for what has just been asked for.  The weights stay in accumulation
-    // registers.  An item of 1024 units takes 4.1 us, of which the products are 0.9 and the operand's 64 KB through the L1 0.4; the rest
-    // is one wavefront a SIMD going through sums, cells and stores.  A layer, 21 frames, us, with two sets of inputs copied at the end of an
-    // item and a look at one word per producer before the operand / so, forward: 512 sequences of 1024 units 357 / 343, 256 of 1024
-    // 179 / 167, 600 of 768 380 / 364, 1000 of 640 563 / 520, 1000 of 544 553 / 492, 130 of 544 138 / 112; backward 406 / 385,
-    // 206 / 192, 449 / 399, 653 / 569, 642 / 555, 166 / 143; and dE/da's copies are marked on the side (1024: 51 us a step less for two layers).
+    // registers.  The item's own inputs and what the item before stores for later launches, 23 vector-memory instructions a wavefront, go out one at a time
+    // between the products: behind the cells they took 1500 to 1900 clocks of an item, the wavefront waiting to issue them.  The partial sums are in LDS
+    // twice, so that one barrier an item is enough.  An item of 1024 units is 6900 clocks (8600 before): 320 looking its operand through, 2650
+    // products and sums to LDS, 600 at the barrier, 600 + 700 reading the sums and asking for the next operand (the CU takes an instruction of 1 KB
+    // every 25 to 35), 1100 cells, 300 h.  Asking for the next operand between the products too made the products wait (5500 clocks), and
+    // a_x in 16-byte pieces turned in LDS was no faster (311 / 321).  A layer, 21 frames, us, forward, two sets of inputs and a probe of the producers / operand
+    // ahead, inputs and stores behind the cells / so: 512 sequences of 1024 units 357 / 343 / 293, 256 of 1024
+    // 179 / 167 / 143, 700 of 1024 - / 495 / 425, 384 - / 259 / 224, 300 of 768 - / 204 / 186, 1000 of 544 553 / 496 / 457, 512 of 640 - / 256 / 242, 150 of 640
+    // - / 113 / 107; backward, the first two, 406 / 385, 192 of 256 sequences, 449 / 399 (600 of 768), 653 / 569 (1000 of 640), 166 / 143 (130 of 544), where a second
+    // buffer of the sums, without the barrier at an item's end, loses a tenth (426 / 466); dE/da's copies are marked on the side (1024: 51 us a step less for two layers).
     // Taking the pairs of the operand in another order in each workgroup gave nothing, more slabs in flight backward lost 2 to 8 %.
     constexpr bool AHEAD = MULTI && SENTINEL && !LEAN;
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
     constexpr int KSTEPS = KW / 16;                      // MFMA steps per gate per wavefront
-    extern __shared__ float lds[];                       // [NW][4][4][64][4] partial accumulators
+    extern __shared__ float lds[];                       // [AHEAD ? 2 : 1][NW][4][4][64][4] partial accumulators, [NW][128] regrouping of h
     const int H = PADDED ? a.H : NW * KW;                // (the launcher picks KW from a.H)
     const int B = a.B, T = a.T;
     const int NU = PADDED ? (H + 31) / 32 : NW * KW / 32;
@@ -230,6 +235,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     unsigned* cnt = a.cnt + (size_t)gm.group * a.tiles_per_group;
     const int j = u * 32 + l32;                          // this thread's hidden unit
     float4* l4 = reinterpret_cast<float4*>(lds);
+    unsigned* const xs = reinterpret_cast<unsigned*>(lds) + (AHEAD ? 2 : 1) * NW * 4 * 4 * 64 * 4 + (threadIdx.x >> 6) * 128;
 
     // Addresses are a per-item uniform base (frame and tile origin) plus per-thread 32-bit element
     // offsets computed once: brow[e] is the batch row of accumulator register e within a tile.
@@ -274,7 +280,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // Two sets of input registers used in turn: an item computes from one while the next item's loads land
     // in the other, so nothing is copied (a copy would have to wait for loads issued a moment before).
     float ax0[EPT][4], cp0[EPT], ax1[EPT][4], cp1[EPT];
-    if constexpr (!LEAN) issue_inputs(0, 0, ax0, cp0);
+    if constexpr (!LEAN && !AHEAD) issue_inputs(0, 0, ax0, cp0);
     uint4 ahead[AHEAD ? KSTEPS : 1];                     // the operand of the item to come
     auto operand = [&](int n0, int i) {                  // this wavefront's part (the first frame, which has none: the second one's)
         const int n = max(n0, 1);
@@ -289,7 +295,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // The row-major outputs of an item (c, the gates, h for the next layer) are not on the frame-to-frame path:
     // they wait in registers until the next item has issued its loads of the exchanged h, and go out behind them.
     struct Tail { int t, b0; bool have, xok; float cn[EPT]; uint2 g[EPT]; uint2 hq; } tail;
-    tail.have = false;
+    tail.have = false; tail.t = 0; tail.b0 = 0;
     // NaN once this wave has abandoned a wait, or from the start if an earlier launch left the abort word raised:
     // added to every h it writes
     float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
@@ -314,19 +320,39 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     };
     // AHEAD: every lane issues every store, what does not exist lies beyond the buffer
     const __amdgpu_buffer_rsrc_t fill_to = __builtin_amdgcn_make_buffer_rsrc(AHEAD && a.fill ? fill : nullptr, 0, AHEAD ? (int)(fill_end * 16) : 0, 0x00020000);
-    auto store_all = [&]() __attribute__((always_inline)) {
+    // What an item stores for later launches, and its own inputs, one vector-memory instruction a step: they go out between the products, which the matrix
+    // cores work through meanwhile.
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    constexpr int SIDE = 6 + EPT * 4 + 1;
+    auto side = [&](auto which, int n, int i, float (&ax)[EPT][4], float (&cp)[EPT]) __attribute__((always_inline)) {
+        constexpr int k = decltype(which)::value;
         const size_t r = rec_index(tail.t, d, tail.b0 >> 5, NT, NU, u);
-        typedef unsigned u4 __attribute__((ext_vector_type(4)));
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        u4* g4 = reinterpret_cast<u4*>(a.gates) + r * 2 * 256 + threadIdx.x;
-        __builtin_nontemporal_store(u4{tail.g[0].x, tail.g[0].y, tail.g[1].x, tail.g[1].y}, g4);   // (not read again here: the L2 is left to the exchange copies, 1 to 2 %)
-        __builtin_nontemporal_store(u4{tail.g[2].x, tail.g[2].y, tail.g[3].x, tail.g[3].y}, g4 + 256);
-        const int row = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane >> 5) + ((lane >> 3) & 3);
-        const unsigned col = (unsigned)(u * 32 + 8 * ((lane >> 1) & 3) + 4 * (lane & 1));
-        const __amdgpu_buffer_rsrc_t y = __builtin_amdgcn_make_buffer_rsrc(a.y + ((size_t)tail.t * B + tail.b0) * 2 * H + d * H, 0, ((min(B - tail.b0, 32) - 1) * 2 * H + H) * 2, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b64(u2{tail.hq.x, tail.hq.y}, y, col < (unsigned)H ? (int)((unsigned)row * 2 * H + col) * 2 : 0x7FFFFFF0, 0, 0);
-#pragma unroll
-        for (int k = 0; k < 2; ++k, fill_pos += 64 * NW) __builtin_amdgcn_raw_buffer_store_b128(u4{~0u, ~0u, ~0u, ~0u}, fill_to, (int)(fill_pos * 16), 0, 2);   // (nontemporal too)
+        if constexpr (k == 0) {                          // (c goes out first: where the group has one tile the inputs read it)
+            const __amdgpu_buffer_rsrc_t c = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float4*>(a.c) + r * 256, 0, tail.have ? 4096 : 0, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, make_float4(tail.cn[0], tail.cn[1], tail.cn[2], tail.cn[3])), c, (int)threadIdx.x * 16, 0, 0);
+        } else if constexpr (k <= EPT * 4) {
+            constexpr int e = (k - 1) / 4, g = (k - 1) % 4;
+            const int t = d ? T - 1 - n : n, b0 = (gm.bg * a.tiles_per_group + i) * 32;
+            const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.ax) + ((size_t)t * B + b0) * 8 * H, 0, 32 * 8 * H * 4, 0x00020000);
+            const int o = FULL ? (int)o8b * 4 : (int)((unsigned)(min(rb + re(e), B - 1 - b0) * 8 * H) + o8c) * 4;
+            ax[e][g] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(x, o, ((FULL ? re(e) * 8 * H : 0) + g * H) * 4, 0));
+        } else if constexpr (k == EPT * 4 + 1) {
+            const float4 c4 = reinterpret_cast<const float4*>(a.c)[rec_index(n > 0 ? (d ? T - n : n - 1) : (d ? T - 1 - n : n), d, gm.bg * a.tiles_per_group + i, NT, NU, u) * 256 + threadIdx.x];
+            cp[0] = c4.x; cp[1] = c4.y; cp[2] = c4.z; cp[3] = c4.w;
+        } else if constexpr (k <= EPT * 4 + 3) {         // (not read again here: the L2 is left to the exchange copies, 1 to 2 %)
+            constexpr int h = k - EPT * 4 - 2;
+            const __amdgpu_buffer_rsrc_t g4 = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<u4*>(a.gates) + r * 2 * 256, 0, tail.have ? 8192 : 0, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b128(u4{tail.g[2 * h].x, tail.g[2 * h].y, tail.g[2 * h + 1].x, tail.g[2 * h + 1].y}, g4, (int)threadIdx.x * 16 + h * 4096, 0, 2);
+        } else if constexpr (k == EPT * 4 + 4) {
+            const int row = 2 * EPT * (int)(threadIdx.x >> 6) + 4 * (lane >> 5) + ((lane >> 3) & 3);
+            const unsigned col = (unsigned)(u * 32 + 8 * ((lane >> 1) & 3) + 4 * (lane & 1));
+            const __amdgpu_buffer_rsrc_t y = __builtin_amdgcn_make_buffer_rsrc(a.y + ((size_t)tail.t * B + tail.b0) * 2 * H + d * H, 0, tail.have ? ((min(B - tail.b0, 32) - 1) * 2 * H + H) * 2 : 0, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b64(u2{tail.hq.x, tail.hq.y}, y, col < (unsigned)H ? (int)((unsigned)row * 2 * H + col) * 2 : 0x7FFFFFF0, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b128(u4{~0u, ~0u, ~0u, ~0u}, fill_to, (int)(fill_pos * 16), 0, 2);   // (nontemporal too)
+            fill_pos += 64 * NW;
+        }
     };
     // (AHEAD: counted.  A division of an item's number costs 100 cycles where it stands; the forms that look at the operand when the item begins, too
     // early, gain by them: whole steps of two layers, us, without / with it: 128 sequences of 1024 cells 914 / 907, 100 853 / 851, 2048 of 160 1316 / 1312)
@@ -384,17 +410,22 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             }
             if constexpr (LEAN) issue_item(item, axn, cpn);   // (in flight behind the products)
             constexpr int GP = LEAN || (AHEAD && KW > 224) ? 2 : 4;   // gates at a time
-#pragma unroll
-            for (int g0 = 0; g0 < 4; g0 += GP) {
+            each<0, 4 / GP>([&](auto pass) __attribute__((always_inline)) {
+                constexpr int g0 = decltype(pass)::value * GP;
                 f32x16_t acc[GP];
 #pragma unroll
                 for (int g = 0; g < GP; ++g)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[g][e] = 0.0f;
-#pragma unroll
-                for (int q = 0; q < KSTEPS; ++q)
+                each<0, KSTEPS>([&](auto step) __attribute__((always_inline)) {
+                    constexpr int q = decltype(step)::value, at = decltype(pass)::value * KSTEPS + q, all = KSTEPS * 4 / GP;
 #pragma unroll
                     for (int g = 0; g < GP; ++g) acc[g] = mfma_bf16(afrag[q], bfrag[g0 + g][q], acc[g]);
+                    if constexpr (AHEAD) {
+                        each<at * SIDE / all, (at + 1) * SIDE / all>([&](auto which) __attribute__((always_inline)) { side(which, n, i, axn, cpn); });
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
                 // partial accumulators -> LDS as [wave][gate][reg/4][lane][reg%4]
 #pragma unroll
                 for (int g = 0; g < GP; ++g)
@@ -402,24 +433,24 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
                     for (int rq = 0; rq < 4; ++rq)
                         l4[((wave * 4 + g0 + g) * 4 + rq) * 64 + lane] =
                             make_float4(acc[g][4 * rq], acc[g][4 * rq + 1], acc[g][4 * rq + 2], acc[g][4 * rq + 3]);
-            }
+            });
             if constexpr (!AHEAD) { if (SENTINEL) lds_barrier(); else __syncthreads(); }
-        }
-        if constexpr (AHEAD) {                           // (on either way, so that the wait for the inputs below, which is counted, leaves these loads out)
-            lds_barrier();
-            load_pairs<KSTEPS>(ahead, operand(next_n, next_i), lastp);
-        }
+        } else if constexpr (AHEAD) each<0, SIDE>([&](auto which) __attribute__((always_inline)) { side(which, n, i, axn, cpn); });
+        // all partial sums of this thread's rows are read before any is added: the reads then
+        // overlap instead of each waiting for its LDS round trip
+        static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
+        float4 part[NW][4][EPT / 4];
+        if constexpr (AHEAD) lds_barrier();
         if (n > 0) {
-            // all partial sums of this thread's rows are read before any is added: the reads then
-            // overlap instead of each waiting for its LDS round trip
-            static_assert(EPT % 4 == 0, "rows per thread come in groups of four accumulator registers");
-            float4 part[NW][4][EPT / 4];
 #pragma unroll
             for (int w2 = 0; w2 < NW; ++w2)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
 #pragma unroll
                     for (int e4 = 0; e4 < EPT / 4; ++e4) part[w2][g][e4] = l4[((w2 * 4 + g) * 4 + (EPT / 4) * wave + e4) * 64 + lane];
+        }
+        if constexpr (AHEAD) load_pairs<KSTEPS>(ahead, operand(next_n, next_i), lastp);   // (on either way, so that the wait for the inputs below, which is counted, leaves these loads out)
+        if (n > 0) {
 #pragma unroll
             for (int w2 = 0; w2 < NW; ++w2)
 #pragma unroll
@@ -455,7 +486,6 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         // through LDS inside the wavefront (as dE/da in the backward kernel), every lane stores four units of one
         // row: one 8-byte store per copy instead of four 2-byte ones.
         static_assert(EPT == 4, "the regrouping below is written for four rows per lane");
-        unsigned* xs = reinterpret_cast<unsigned*>(lds) + NW * 4 * 4 * 64 * 4 + wave * 128;
         xs[(lh * 2 + 0) * 32 + l32] = (unsigned)coh_bf16(hn[0]) | ((unsigned)coh_bf16(hn[1]) << 16);
         xs[(lh * 2 + 1) * 32 + l32] = (unsigned)coh_bf16(hn[2]) | ((unsigned)coh_bf16(hn[3]) << 16);
         const int xh = lane & 1, xk = (lane >> 1) & 3, xr = (lane >> 3) & 3, xl = lane >> 5;
@@ -472,7 +502,8 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             bf16_t* xp = hxb + ((xcol >> 3) * 256u + (unsigned)xrow * 8u + (xcol & 7u));
             if (SENTINEL) st_coh_8B(xp, hq); else *reinterpret_cast<uint2*>(xp) = hq;
         }
-        if (SENTINEL) lds_barrier();                     // frees the LDS buffer for the next item
+        if constexpr (AHEAD) l4 = reinterpret_cast<float4*>(lds) + (l4 == reinterpret_cast<float4*>(lds) ? NW * 4 * 4 * 64 : 0);   // (no barrier frees the buffer: there are two)
+        else if (SENTINEL) lds_barrier();                // frees the LDS buffer for the next item
         else signal_counter(cnt + i);                    // barrier inside: same role
         // row-major outputs (h for the next layer, c and the gates for the backward pass): kept for flush_tail
         tail.t = t; tail.b0 = b0; tail.have = true; tail.xok = xok; tail.hq = hq;
@@ -480,13 +511,6 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
         for (int e = 0; e < EPT; ++e) {
             tail.cn[e] = cn[e];
             tail.g[e] = make_uint2(pack_bf2(gi[e], gf[e]), pack_bf2(gg[e], go[e]));
-        }
-        if constexpr (AHEAD) {
-            asm volatile("" ::: "memory");
-            // (c goes out first: where the group has one tile the inputs read it)
-            reinterpret_cast<float4*>(a.c)[rec_index(t, d, b0 >> 5, NT, NU, u) * 256 + threadIdx.x] = make_float4(cn[0], cn[1], cn[2], cn[3]);
-            issue_inputs(next_n, next_i, axn, cpn);
-            store_all();
         }
         // with one tile per workgroup the next item's previous cell state is the one just computed
 #pragma unroll
@@ -506,7 +530,11 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
             }
         }
     }
-    if constexpr (!AHEAD) flush_tail();
+    if constexpr (AHEAD) {
+        auto last = [&](auto which) __attribute__((always_inline)) { side(which, 0, 0, ax0, cp0); };
+        each<0, 1>(last);
+        each<EPT * 4 + 2, SIDE>(last);
+    } else flush_tail();
     fill_some(1 << 30);                                  // (whatever rounding left over)
 }
 
@@ -518,7 +546,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // The loop body twice, the sets of inputs in turn, and the next ones asked for once dE/da has gone out.  One layer, 4096
     // sequences, us, so / with one body: 288 units 1109 / 1131, 160 592 / 564, 96 336 / 315; wide slices leave no room for two.
     constexpr bool TWO = KW == 96;
-    // AHEAD as in the forward kernel: two slabs of the operand in flight, across the items; one set of inputs, asked for behind the cells.
+    // AHEAD: two slabs of the operand in flight, across the items; one set of inputs, asked for behind the cells.
     constexpr bool AHEAD = MULTI && SENTINEL && KW > 128;
     constexpr int SLABS = KSTEPS / 8, DEEP = 2;
     extern __shared__ float lds[];                       // [NW][4][64][4]
@@ -897,7 +925,7 @@ __global__ void fill_u32_kernel(unsigned* p, int n, unsigned v) {
 
 template <int KW, bool S, bool FULL, bool MULTI, bool PADDED, bool LEAN = false>
 hipError_t run_one(const RecFwdArgs& a, int grid, hipStream_t st, bool* launched) {
-    const size_t lds = (size_t)NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
+    const size_t lds = (size_t)(MULTI && S && !LEAN ? 2 : 1) * NW * 4 * 4 * 64 * 16 + (size_t)NW * 512;   // partial sums; regrouping of h, 512 bytes per wavefront
     return launch_resident<rec_fwd_kernel<KW, S, FULL, MULTI, PADDED, LEAN>>(a, 64 * NW, lds, grid, grid, st, launched);
 }
 template <int KW, bool S, bool FULL, bool MULTI, bool PADDED>
