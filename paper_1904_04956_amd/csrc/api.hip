@@ -616,6 +616,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     const bool marks = persistent && ctx->rec_sync == 1;   // h of every layer starts as "not written yet"
     if (marks && ctx->Dp == 0)                          // (otherwise with the padded copies below)
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
+    bool z_written = false;
     for (int l = 0; l < ctx->L; ++l) {
         const void* Xin = l == 0 ? x : static_cast<const void*>(ctx->ws + ctx->wY[l - 1]);
         const int Din = ctx->din(l);
@@ -653,6 +654,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             if (l == 0 && ctx->Hown != H) RUN(PC_MISC, "a_x of the padding", launch_zero_columns(AX, (long long)M * 8, H, ctx->Hown, st));
         }
         ctx->fwd_persistent[l] = 0;
+        const bool to_z = l == ctx->L - 1 && ctx->P == 0;   // (z is this layer's output: kernels that can write it twice do)
         unsigned* cnt = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT);
         const int ncnt = ctx->rec_cnt;
         if ((persistent || persistent32) && (!ctx->abort_clean || ctx->test_abort)) {
@@ -668,9 +670,10 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX);
             a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H;
+            if (to_z && rec32_fwd_one(B, H)) a.z = static_cast<float*>(z_out);
             bool launched = false;
             RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec32_fwd(a, st, &launched));
-            if (launched) continue;
+            if (launched) { z_written = a.z != nullptr; continue; }
         }
         if (persistent) {   // all T frames of both directions in one launch
             if (ctx->rec_sync == 0) RUN(PC_MISC, "counters", launch_fill_u32(cnt, ncnt, 0u, st));
@@ -689,8 +692,11 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             }
             bool launched = false;
             if (kind == 3) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_tile_fwd(a, ctx->rec_sync == 1, st, &launched));
-            else if (kind == 2) RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
-            else RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
+            else if (kind == 2) {
+                if (to_z) a.z = static_cast<unsigned short*>(z_out);
+                RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_small_fwd(a, st, &launched));
+                z_written = a.z != nullptr;
+            } else RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec_fwd(a, ctx->rec_sync == 1, st, &launched));
             if (!launched) return fail(BLSTM_ERR_HIP, "blstm_forward: the persistent kernel cannot be launched");
             ctx->fwd_persistent[l] = (char)kind;
             continue;
@@ -732,7 +738,7 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
         d.C = z_out; d.ldc = ctx->P;
         d.bias = at(theta, ctx->off_bp, e);
         RUN(PC_GEMM_BOTTLENECK, "bottleneck", launch_gemm(d, st));
-    } else {
+    } else if (!z_written) {
         RUN(PC_MISC, "copy of the LSTM output", hipMemcpyAsync(z_out, YL, (size_t)M * 2 * H * e, hipMemcpyDeviceToDevice, st));
     }
     ctx->have_forward = true;

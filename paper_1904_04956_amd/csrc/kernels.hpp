@@ -41,6 +41,7 @@ struct RecFwdArgs {
     const unsigned short* uh[2];  // U_h per direction, [4H][H]
     const float* ax;              // W_x x + b for every frame, [M][8H]
     unsigned short* y;            // layer output h, [M][2H]
+    unsigned short* z;            // the same once more, or null (honoured by launch_rec_small_fwd only)
     unsigned short* hx;           // h again in exchange order, [T][2][tiles][H/16][2][32][8]; pre-filled with 0xFFFF in sentinel mode
     unsigned short* gates;        // gate activations for rec_bwd_kernel only, as per-lane records [T][2][tiles][H/32][2][256] 16-byte words (not the per-frame path's [M][8H])
     float* c;                     // cell states, records [T][2][tiles][H/32][256] of four floats; both sized for whole 32-row tiles
@@ -94,6 +95,7 @@ struct Rec32FwdArgs {
     const float* uh[2];           // U_h per direction, [4H][H]
     const float* ax;              // W_x x + b for every frame, [M][8H]
     float* y;                     // h, [M][2H]
+    float* z;                     // the same once more, or null (honoured where rec32_fwd_one says so)
     float* c;                     // cell states, [M][2H]
     float* gates;                 // gate activations, [M][8H]
     float* hx;                    // exchange copy of h, rec32_hx_bytes, filled with 0xFF bytes before the launch
@@ -119,6 +121,7 @@ struct Rec32BwdArgs {
 };
 // Whether the persistent kernel takes this shape (and is the faster of the two paths).
 bool rec32_fwd_supported(int B, int H);
+bool rec32_fwd_one(int B, int H);           // forward: the kernel with wavefronts for what is not the exchange runs it
 bool rec32_bwd_supported(int B, int H);
 size_t rec32_hx_bytes(int T, int B, int H);
 size_t rec32_dax_bytes(int T, int B, int H);

@@ -129,6 +129,7 @@ __device__ __forceinline__ void load_columns(float (&wf)[NQ][4], const float* ga
 // 128 51 / 41 / 39 / 40 / 41 / 43.
 constexpr unsigned fwd_pause(int nq) { return nq <= 4 ? 300 : nq <= 16 ? 500 : 900; }
 constexpr unsigned BWD_PAUSE = 700;
+constexpr int ONE_MOST = 24;                             // the widest NQ of rec32_fwd_one_kernel
 
 // Workgroup -> (direction, group of batch tiles, unit slice).  Ids are dealt round-robin to the eight XCDs; each XCD takes
 // a contiguous eighth of the sequence, so that the slices of a group sit on as few XCDs as they fill.
@@ -390,6 +391,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
             if (junit && row < B) {
                 const size_t m = (size_t)frame(n) * B + row;
                 a.y[m * 2 * H + d * H + j] = ch.y;
+                if (a.z) a.z[m * 2 * H + d * H + j] = ch.y;
                 a.c[m * 2 * H + d * H + j] = ch.x;
                 float* g = a.gates + m * 8 * H + (size_t)d * 4 * H + j;
                 g[0] = g4.x; g[H] = g4.y; g[2 * (size_t)H] = g4.z; g[3 * (size_t)H] = g4.w;
@@ -641,6 +643,7 @@ int built_width(int H, int unit, std::initializer_list<int> nqs) {
     return 0;
 }
 }  // namespace
+bool rec32_fwd_one(int B, int H) { return H <= 32 * ONE_MOST && tiles_a_workgroup(B, H, 8, 32) == 1; }
 bool rec32_fwd_supported(int B, int H) {
     if (H > 1024) return false;
     const double persistent = tiles_a_workgroup(B, H, 8, 32) * (1.5 + 0.0049 * built_width(H, 32, {1, 2, 4, 8, 12, 16, 20, 24, 32}));
@@ -662,7 +665,7 @@ hipError_t launch_rec32_fwd(Rec32FwdArgs a, hipStream_t st, bool* launched) {
     split(a, 8, 32);
 #define BLSTM_R32(NQ) if (a.H <= 32 * NQ) return run<rec32_fwd_kernel<NQ>>(a, st, launched)
 #define BLSTM_R32_ONE(NQ) if (a.tiles_per_group == 1 && a.H <= 32 * NQ) return run_one<rec32_fwd_one_kernel<NQ>>(a, st, launched)
-    BLSTM_R32_ONE(1); BLSTM_R32_ONE(2); BLSTM_R32_ONE(4); BLSTM_R32_ONE(8); BLSTM_R32_ONE(12); BLSTM_R32_ONE(16); BLSTM_R32_ONE(20); BLSTM_R32_ONE(24);
+    BLSTM_R32_ONE(1); BLSTM_R32_ONE(2); BLSTM_R32_ONE(4); BLSTM_R32_ONE(8); BLSTM_R32_ONE(12); BLSTM_R32_ONE(16); BLSTM_R32_ONE(20); BLSTM_R32_ONE(ONE_MOST);
 #undef BLSTM_R32_ONE
     BLSTM_R32(1); BLSTM_R32(2); BLSTM_R32(4); BLSTM_R32(8); BLSTM_R32(12); BLSTM_R32(16); BLSTM_R32(20); BLSTM_R32(24); BLSTM_R32(32);
 #undef BLSTM_R32

@@ -118,7 +118,11 @@ __global__ __launch_bounds__(128 * NWF) void rec_small_fwd_kernel(RecFwdArgs a) 
             reinterpret_cast<uint2*>(a.gates)[rec * 256 + tid] = make_uint2(v.x, v.y);
             a.c[rec * 256 + tid] = __builtin_bit_cast(float, v.z);
             const uint2 hq = quad_pack(v.w);
-            if ((tid & 3) == 0 && junit && row < B) *reinterpret_cast<uint2*>(a.y + ((size_t)frame(n) * B + row) * 2 * H + d * H + j) = hq;
+            if ((tid & 3) == 0 && junit && row < B) {
+                const size_t at = ((size_t)frame(n) * B + row) * 2 * H + d * H + j;
+                *reinterpret_cast<uint2*>(a.y + at) = hq;
+                if (a.z) *reinterpret_cast<uint2*>(a.z + at) = hq;
+            }
         };
         float4 in[4];
 #pragma unroll
