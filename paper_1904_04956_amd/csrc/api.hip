@@ -494,12 +494,12 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     }
     c->rec32_fwd = c->st == DT_F32 && c->T > 1 && rec32_fwd_supported(c->B, c->H);   // (a single frame has no recurrence)
     c->rec32_bwd = c->rec32_fwd && rec32_bwd_supported(c->B, c->H);
-    if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da, one for all layers
+    if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da, one per layer
         c->wCNT = w; w += 256;
         c->hx_bytes = up256(rec32_hx_bytes(c->T, c->B, c->H));
         c->dax_bytes = c->rec32_bwd ? up256(rec32_dax_bytes(c->T, c->B, c->H)) : 0;
-        c->wHX = w;  w += c->hx_bytes;
-        c->wDAX = w; w += c->dax_bytes;
+        c->wHX = w;  w += c->hx_bytes * c->L;
+        c->wDAX = w; w += c->dax_bytes * c->L;
     }
     {   // split-K scratch: the largest need among the products with a small output
         const DType S = c->st;
@@ -616,6 +616,10 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     const bool marks = persistent && ctx->rec_sync == 1;   // h of every layer starts as "not written yet"
     if (marks && ctx->Dp == 0)                          // (otherwise with the padded copies below)
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
+    // In float mode the forward kernels with wavefronts to spare mark the exchange copies of dE/da.
+    const bool fills32 = persistent32 && ctx->rec32_bwd && rec32_fwd_one(B, H);
+    if (persistent32) RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
+    int filled32 = 0;                                   // layers
     bool z_written = false;
     for (int l = 0; l < ctx->L; ++l) {
         const void* Xin = l == 0 ? x : static_cast<const void*>(ctx->ws + ctx->wY[l - 1]);
@@ -663,17 +667,17 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             ctx->test_abort = false;
         }
         if (persistent32) {   // all T frames of both directions in one launch, float mode
-            RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes, 0xFFFFFFFFu, st));
             Rec32FwdArgs a{};
             for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
             a.ax = AX; a.y = reinterpret_cast<float*>(Y); a.c = C; a.gates = reinterpret_cast<float*>(G);
-            a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX);
+            a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX + ctx->hx_bytes * l);
             a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H;
+            if (fills32) { a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l; a.fill_words = ctx->dax_bytes / 16; }
             if (to_z && rec32_fwd_one(B, H)) a.z = static_cast<float*>(z_out);
             bool launched = false;
             RUN(PC_REC_FWD, "persistent recurrent forward", launch_rec32_fwd(a, st, &launched));
-            if (launched) { z_written = a.z != nullptr; continue; }
+            if (launched) { z_written = a.z != nullptr; filled32 += fills32 ? 1 : 0; continue; }
         }
         if (persistent) {   // all T frames of both directions in one launch
             if (ctx->rec_sync == 0) RUN(PC_MISC, "counters", launch_fill_u32(cnt, ncnt, 0u, st));
@@ -742,8 +746,8 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
         RUN(PC_MISC, "copy of the LSTM output", hipMemcpyAsync(z_out, YL, (size_t)M * 2 * H * e, hipMemcpyDeviceToDevice, st));
     }
     ctx->have_forward = true;
-    ctx->dax_filled = fills;
-    if (fills) ctx->dax_capture = capture_of(st);
+    ctx->dax_filled = fills || (fills32 && filled32 == ctx->L);
+    if (ctx->dax_filled) ctx->dax_capture = capture_of(st);
     return BLSTM_OK;
 }
 
@@ -816,7 +820,10 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     // In sentinel mode every layer's exchange copy of dE/da starts as "not written yet": the forward pass's persistent
     // kernels have seen to that, each for its layer; otherwise (protocol switched in between, a second backward pass on
     // one forward pass) one fill.  And in a graph that does not hold the forward pass too: it may be replayed several times behind one.
-    if (sentinel && !(ctx->dax_filled && ctx->dax_capture == capture_of(st)))
+    const bool float_path = ctx->rec32_bwd && ctx->abort_clean && ctx->rec_path == 0 && ctx->rec_sync == 1;   // (saved activations are the same on both float paths)
+    const bool dax_marked = (sentinel || float_path) && ctx->dax_filled && ctx->dax_capture == capture_of(st);
+    if (float_path && !dax_marked) RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
+    if (sentinel && !dax_marked)
         RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(xcd_table(ctx, 1, 0), XCD_TABLE_BYTES * ctx->L + ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     ctx->dax_filled = false;
     const char* dY;
@@ -874,13 +881,12 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
             if (!rec_done)
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
         }
-        if (ctx->rec32_bwd && ctx->abort_clean && ctx->rec_path == 0 && ctx->rec_sync == 1) {   // (saved activations are the same on both float paths)
-            RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes, 0xFFFFFFFFu, st));
+        if (float_path) {
             Rec32BwdArgs a{};
             for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
             a.dy = reinterpret_cast<const float*>(dY); a.gates = reinterpret_cast<const float*>(G); a.c = C;
             a.da = reinterpret_cast<float*>(DA); a.dc = DC;
-            a.dax = reinterpret_cast<float*>(ctx->ws + ctx->wDAX);
+            a.dax = reinterpret_cast<float*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
             a.abort_word = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT); a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H;
             RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec32_bwd(a, st, &rec_done));

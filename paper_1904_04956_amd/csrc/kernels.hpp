@@ -101,6 +101,8 @@ struct Rec32FwdArgs {
     float* hx;                    // exchange copy of h, rec32_hx_bytes, filled with 0xFF bytes before the launch
     unsigned* abort_word;         // as in RecFwdArgs
     unsigned long long limit_ticks;
+    void* fill;                   // fill_words 16-byte words to set to 0xFF bytes on the side, or null (honoured where rec32_fwd_one says so)
+    unsigned long long fill_words;
     int T, B, H;
     int nu, nbg, tiles_per_group; // set by the launcher
     bool ask;                     // as in RecFwdArgs

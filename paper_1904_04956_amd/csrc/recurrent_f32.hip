@@ -371,7 +371,6 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
     __shared__ float2 state[2][64 * NWF];                // c, h
     const int T = a.T, B = a.B, H = a.H, nu = a.nu;
     const Place pl = place(nu, a.nbg);
-    if (!pl.real) return;
     const int d = pl.d, u = pl.u, tile = pl.bg;
     const int tid = threadIdx.x & (64 * NWF - 1), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // this thread's cell: unit j, row r of the tile
@@ -379,6 +378,15 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
     const bool junit = j < H;
     auto frame = [&](int n) { return d ? T - 1 - n : n; };
     if (wave >= NWF) {
+        // this workgroup's share of the region to fill, some words every frame
+        const unsigned long long share = a.fill ? (a.fill_words + gridDim.x - 1) / gridDim.x : 0ull;
+        const unsigned long long first = min(a.fill_words, (unsigned long long)blockIdx.x * share);
+        uint4* const fill = static_cast<uint4*>(a.fill) + first;
+        const unsigned fill_end = (unsigned)(min(a.fill_words, first + share) - first);
+        unsigned fill_pos = tid;
+        const int fill_each = (int)((share + (unsigned long long)(256 * T) - 1) / (unsigned long long)(256 * T));
+        auto fill_some = [&](int words) { for (int k = 0; k < words && fill_pos < fill_end; ++k, fill_pos += 256) fill[fill_pos] = make_uint4(~0u, ~0u, ~0u, ~0u); };
+        if (!pl.real) { fill_some(1 << 30); return; }
         const int row = tile * 32 + r;
         const float* ax0 = a.ax + (size_t)min(row, B - 1) * 8 * H + d * 4 * H + min(j, H - 1);
         auto inputs = [&](int n, float4& v) __attribute__((always_inline)) {
@@ -409,12 +417,15 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
                 lds_only_barrier();
                 inputs(n + 4, in[k]);
                 if (n > 0) save(n - 1);
+                fill_some(fill_each);
             }
         }
         lds_only_barrier();
         save(T - 1);
+        fill_some(1 << 30);
         return;
     }
+    if (!pl.real) return;
     const int l32 = lane & 31, lh = lane >> 5;
     // row l32 of the slice: gate l32 & 3 of unit l32 >> 2
     float wf[NQ][4];
