@@ -38,23 +38,21 @@ __device__ __forceinline__ uint4 ld_coh_16B(const bf16_t* p) {
     const unsigned long long hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return make_uint4((unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32));
 }
-// The chunks are checked on every frame, so the test is branch-free and one operation per word:
-// 0xFFFF is the largest 16-bit value, so a packed unsigned maximum over all words has a 0xFFFF half
-// iff some word has one; the zero-halfword test on the complement of that maximum decides.
-typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned max_halves(unsigned x, unsigned y) {
-    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, x), __builtin_bit_cast(u16x2_t, y)));
+__device__ __forceinline__ unsigned max3(unsigned a, unsigned b, unsigned c) {   // (one instruction)
+    const unsigned m = a > b ? a : b;
+    return m > c ? m : c;
 }
-__device__ __forceinline__ unsigned max_halves(const uint4& v) { return max_halves(max_halves(v.x, v.y), max_halves(v.z, v.w)); }
 __device__ __forceinline__ bool has_sentinel_half(unsigned w) { return ((~w - 0x00010001u) & w & 0x80008000u) != 0; }
 
-// Whether every element of every lane's f is written.
+// Whether every element of every lane's f is written.  Branch-free, as it is asked on every frame, and half an operation a word: a lane's stores to an
+// exchange copy are aligned words of 32 bits and more, and so is the marking, so that both elements of a word are written or neither
+// is, and 0xFFFF in the upper one is what makes a word the largest.
 template <int N>
 __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     unsigned m = 0;
 #pragma unroll
-    for (int q = 0; q < N; ++q) m = max_halves(m, max_halves(f[q]));
-    return __all(!has_sentinel_half(m));
+    for (int q = 0; q < N; ++q) m = max3(max3(m, f[q].x, f[q].y), f[q].z, f[q].w);
+    return __all(m < SENT16 << 16);
 }
 // The bounded wait for an operand: `look` loads f (past the caches that a look which came too early may have left stale lines in) until all of it is
 // written.  Returns true if the wait was abandoned, at the time limit or as someone raised the abort word.  Wave-uniform.
