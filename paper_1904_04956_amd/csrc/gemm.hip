@@ -257,6 +257,16 @@ Params make_params(const GemmDesc& d) {
     P.splits = 1;
     return P;
 }
+// Tile rows of a band, bf16: four, eight where B as a whole stays in an XCD's L2 (4 MB) and many bands come past it, which is then read once for twice as
+// many rows.  us, bands of 4 / 8, X W^T: 5376 x 2048 twice, K = 1024 60.6 / 63.4 (21 tile rows), 43008 rows 435 / 420, K = 264 268 / 228; 10752 x 4096 twice,
+// K = 2048 333 / 335; 43008 x 32000, K = 256 1114 / 1181; dA W of 2048 and 1024 columns within 2 %; the grouped weight gradients of four layers of 512
+// cells, 5376 frames 371 / 384, 43008 2974 / 3030, of six of 1024, 10752 frames 3027 / 3167 (sixteen 373, 3109, 3790).
+int band_rows(const GemmDesc& d, int ntm) {
+    if (d.in_type == DT_F32) return 8;
+    long long k = 0;
+    for (int s = 0; s < d.nseg; ++s) k += d.seg[s].K;
+    return !d.atrans && ntm > 32 && k * d.N * 2 <= 4ll << 20 ? 8 : 4;
+}
 // Tile counts and store modes for a tile shape and edge treatment.
 template <typename TO>
 void set_tiles(const GemmDesc& d, Params& P, int tm, int tn, int mode) {
@@ -273,6 +283,7 @@ void set_tiles(const GemmDesc& d, Params& P, int tm, int tn, int mode) {
     P.p_vec = (d.N % 4 == 0 && !(mode == WHOLE && d.Npad > 0)) ? 1 : 0;   // (the scratch itself is 256-byte aligned)
     P.ntm = (d.M + tm - 1) / tm;
     P.ntn = ((mode == WHOLE && d.Npad > 0 ? d.Npad : d.N) + tn - 1) / tn;
+    P.band = band_rows(d, P.ntm);
 }
 
 template <typename TI, typename TO>

@@ -52,6 +52,7 @@ struct Params {
     float* partial;                 // split-K: float [batch][splits][M][N], or null
     float* rs_partial;              // split-K: float [batch][splits][M] row sums
     int M, N, ntm, ntn, splits;
+    int band;                       // tile rows of a band (see gemm_tile)
     int Nst;                        // columns the vector stores of C may write (N, or N rounded up where C is padded)
     int c_vec;                      // C rows may be written with 16-byte (float) / 8-byte (bf16) stores, whole tiles of them
     int p_vec;                      // the same for the float partial tiles of a split
@@ -297,15 +298,15 @@ __device__ __forceinline__ void gemm_tile(const Params& P, int lin, const int sp
 
     // Workgroup ids are dealt round-robin to the eight XCDs; give each XCD a contiguous
     // range of tiles so that its L2 sees neighbouring tiles, then walk the range in bands
-    // of eight tile rows so that concurrently resident tiles share A rows and B columns.
+    // of P.band tile rows so that concurrently resident tiles share A rows and B columns.
     const int nt = P.ntm * P.ntn;
     if (xcd_remap) {
         const int nt8 = nt & ~7;
         if (lin < nt8) lin = (lin & 7) * (nt8 >> 3) + (lin >> 3);
     }
-    const int band = 8 * P.ntn;
-    const int first_m = (lin / band) * 8;
-    const int bh = min(P.ntm - first_m, 8);
+    const int band = P.band * P.ntn;
+    const int first_m = (lin / band) * P.band;
+    const int bh = min(P.ntm - first_m, P.band);
     const int tm = first_m + (lin % band) % bh;
     const int tn = (lin % band) / bh;
     const int row0 = tm * BM, col0 = tn * BN;
