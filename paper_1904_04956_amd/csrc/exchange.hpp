@@ -118,6 +118,8 @@ __device__ __forceinline__ void signal_counter(unsigned* cnt) {
 __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
+// The waits in their plain form, as the host check of the waits runs them (the kernels bring their own looks to wait_written: by buffer,
+// several at once, after a pause).
 // f[q] = the 16 bytes at base + off(q): ordinary loads first, past the caches until every element is written.
 // Returns true if the wait was abandoned.
 template <int N, typename F>
@@ -134,11 +136,8 @@ __device__ __forceinline__ bool settle16(uint4 (&f)[N], const bf16_t* base, F of
 }
 
 // Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
-// was abandoned.  Looking at the data straight away saves this round trip when the first look succeeds or the
-// data is little; with eight or more fragments a wavefront, loads that come too early cost more than they save and leave
-// stale lines behind (three layers, T = 21, forward / rest of the step in us, straight against probe first: H = 512, 8
-// sequences 132 / 234 and 151 / 205 -- four fragments forward, sixteen backward --, H = 1024, 30 sequences 248 / 566 and
-// 221 / 461, H = 128, 8 sequences 100 / 138 and 117 / 153).
+// was abandoned.  The few-sequence kernels did this before they looked at eight or more fragments, as loads that come too early cost more than
+// the round trip; a first look timed from the wavefront's own store (recurrent_small.hip) saves the round trip as well.
 constexpr int PROBE_FROM = 8;
 __device__ __forceinline__ bool probe_producers16(const bf16_t* p, bool mine, unsigned* abort_word, unsigned long long limit) {
     const unsigned long long t0 = wall_clock64();
