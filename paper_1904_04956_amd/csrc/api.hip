@@ -75,6 +75,7 @@ struct blstm_ctx {
     bool rec32_fwd, rec32_bwd;   // float mode: the persistent kernels of recurrent_f32.hip take this shape
     bool dax_filled;          // the forward pass's persistent kernels have marked every exchange copy of dE/da "not written yet"
     unsigned long long dax_capture;   // ... in this capture of a graph (0: in none)
+    bool backward_captured;   // some backward pass went into a graph, whose replays, unseen here, leave dE/da's of their own in the copies
     bool abort_clean;         // the abort word has been zeroed since the workspace was bound
     bool test_abort;          // failure-handling tests: the next forward pass raises the abort word itself
     bool test_no_xcd;         // tests: no group of workgroups counts as being on one XCD
@@ -470,7 +471,7 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     }
     // persistent recurrent kernels: transposed U_h per layer and direction, counters, abort word
     c->rec_cnt = 0; c->rec_nbg = 0; c->rec_tiles = 0; c->rec_path = 0; c->rec_sync = 1; c->abort_clean = false; c->test_abort = false; c->test_no_xcd = false;
-    c->dax_filled = false; c->dax_capture = 0;
+    c->dax_filled = false; c->dax_capture = 0; c->backward_captured = false;
     c->fwd_persistent.assign(c->L, 0);
     c->wUHT = w; c->wCNT = w; c->wHX = w; c->wXCD = w; c->wDAX = w; c->hx_bytes = 0; c->dax_bytes = 0;
     if (c->st == DT_BF16 && rec_takes(c->T, c->B, c->H)) {
@@ -820,8 +821,11 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     // In sentinel mode every layer's exchange copy of dE/da starts as "not written yet": the forward pass's persistent
     // kernels have seen to that, each for its layer; otherwise (protocol switched in between, a second backward pass on
     // one forward pass) one fill.  And in a graph that does not hold the forward pass too: it may be replayed several times behind one.
+    // And outside of a graph once there is one with a backward pass: replayed behind the forward pass, it has left its own dE/da there.
     const bool float_path = ctx->rec32_bwd && ctx->abort_clean && ctx->rec_path == 0 && ctx->rec_sync == 1;   // (saved activations are the same on both float paths)
-    const bool dax_marked = (sentinel || float_path) && ctx->dax_filled && ctx->dax_capture == capture_of(st);
+    const unsigned long long capture = capture_of(st);
+    const bool dax_marked = (sentinel || float_path) && ctx->dax_filled && ctx->dax_capture == capture && (capture != 0 || !ctx->backward_captured);
+    if (capture != 0) ctx->backward_captured = true;
     if (float_path && !dax_marked) RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     if (sentinel && !dax_marked)
         RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(xcd_table(ctx, 1, 0), XCD_TABLE_BYTES * ctx->L + ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));

@@ -147,6 +147,28 @@ def test_a_captured_backward_pass_marks_what_its_replays_exchange(recorder, dims
     assert fills == [0, 1, 0, 1, 1, 1]
 
 
+@pytest.mark.parametrize("mode,dims", [(1, DIMS), (1, "T=4, B=600, D=8, H=512, L=2, P=0, V=20"), (1, "T=4, B=70, D=30, H=101, L=1, P=0, V=20"),
+                                       (0, "T=4, B=64, D=8, H=512, L=2, P=0, V=20"), (0, "T=4, B=64, D=8, H=101, L=2, P=301, V=9001")])
+@pytest.mark.parametrize("with_forward", [False, True])
+def test_a_backward_pass_marks_its_copies_where_a_replay_may_have_written_them(recorder, mode, dims, with_forward):
+    # a graph with a backward pass is there; then forward, (its replay, which no call shows,) backward: what the forward pass marked may be the replay's
+    # dE/da by now, which would be taken for this pass's
+    before, captured, after = recorder(f"""
+        rec.recorder_occupancy(b"rec", 4)
+        m = Model({mode}, {dims})
+        fills = lambda s: count(launches(lambda: m.backward(s)), "fill_u128")
+        graph = 1 << 16
+        m.forward(); out = [fills(0)]
+        m.forward()
+        rec.recorder_capturing(ctypes.c_void_p(graph))
+        if {with_forward}: m.forward(graph)
+        out.append(fills(graph))
+        rec.recorder_capturing(None)
+        m.forward(); out.append(fills(0))
+    """)
+    assert [before, captured, after] == [0, 0 if with_forward else 1, 1]
+
+
 @pytest.mark.parametrize("dims,copy,axis", [("T=4, B=16, D=8, H=101, L=2, P=0, V=20", "pad_blocks", 0),      # a twin's weights
                                             ("T=4, B=16, D=30, H=104, L=2, P=0, V=20", "pad_cols", 1)])        # W_x of the first layer
 def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):
