@@ -1,4 +1,4 @@
-// The pieces of the protocols that the persistent bf16 kernels share (see recurrent.hip).
+// The pieces of the protocols that the persistent kernels share (see recurrent.hip).
 #pragma once
 #include "common.hpp"
 
@@ -54,15 +54,24 @@ __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     for (int q = 0; q < N; ++q) m = max3(max3(m, f[q].x, f[q].y), f[q].z, f[q].w);
     return __all(m < SENT16 << 16);
 }
-// The bounded wait for an operand: `look` loads f (past the caches that a look which came too early may have left stale lines in) until all of it is
-// written.  Returns true if the wait was abandoned, at the time limit or as someone raised the abort word.  Wave-uniform.
-template <bool NAP, int N, typename L>
-__device__ __forceinline__ bool look_again(uint4 (&f)[N], L look, unsigned* abort_word, unsigned long long limit) {
+// ... and of a copy of floats, whose words are stored each by itself.
+constexpr unsigned SENT32 = 0xFFFFFFFFu;
+template <int N>
+__device__ __forceinline__ bool all_written32(const uint4 (&f)[N]) {
+    unsigned m = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) m = max3(max3(m, f[q].x, f[q].y), f[q].z, f[q].w);
+    return __all(m != SENT32);
+}
+// The bounded wait for an operand: `look` loads it (past the caches that a look which came too early may have left stale lines in) until it is `whole`.
+// Returns true if the wait was abandoned, at the time limit or as someone raised the abort word.  Wave-uniform.
+template <bool NAP, typename W, typename L>
+__device__ __forceinline__ bool look_until(W whole, L look, unsigned* abort_word, unsigned long long limit) {
     const unsigned long long t0 = wall_clock64();
     for (unsigned it = 1;; ++it) {
-        asm volatile("" ::: "memory");
+        asm volatile("" ::: "memory");                   // (loads by buffer are not taken to see what others store)
         look();
-        if (all_written<N>(f)) return false;
+        if (whole()) return false;
         if constexpr (NAP) __builtin_amdgcn_s_sleep(1);
         if ((it & 31u) == 0) {
             if (ld_coh_u32(abort_word) != 0) return true;
@@ -73,11 +82,20 @@ __device__ __forceinline__ bool look_again(uint4 (&f)[N], L look, unsigned* abor
         }
     }
 }
+template <bool NAP, int N, typename L>
+__device__ __forceinline__ bool look_again(uint4 (&f)[N], L look, unsigned* abort_word, unsigned long long limit) {
+    return look_until<NAP>([&]() __attribute__((always_inline)) { return all_written<N>(f); }, look, abort_word, limit);
+}
 // ... behind a first look, unless that found everything or an earlier wait was abandoned.
 template <bool NAP, int N, typename L>
 __device__ __forceinline__ bool wait_written(uint4 (&f)[N], L look, bool gave_up, unsigned* abort_word, unsigned long long limit) {
     if (gave_up || all_written<N>(f)) return gave_up;
     return look_again<NAP, N>(f, look, abort_word, limit);
+}
+template <int N, typename L>
+__device__ __forceinline__ bool wait_written32(uint4 (&f)[N], L look, bool gave_up, unsigned* abort_word, unsigned long long limit) {
+    if (gave_up || all_written32<N>(f)) return gave_up;
+    return look_until<true>([&]() __attribute__((always_inline)) { return all_written32<N>(f); }, look, abort_word, limit);
 }
 
 // Barrier for LDS hazards only: waits for this wave's LDS operations, not for its global loads and

@@ -17,7 +17,7 @@
 // workgroup's repeat its block (against those zero weights).  Rows of the last tile beyond the batch repeat the batch's
 // last row and are never stored row-major.  All global accesses but the exchange are single floats, so no alignment
 // is asked of H.  Saved activations are in the row-major layout of the per-frame path (cell.hip).
-#include "common.hpp"
+#include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
 #include <initializer_list>
@@ -25,12 +25,10 @@
 namespace blstm {
 namespace {
 
-constexpr unsigned SENT32 = 0xFFFFFFFFu;
 constexpr int NWF = 4;                                   // wavefronts, splitting the contraction
 
 constexpr int SC1 = 16;                                  // cache policy of agent-scope accesses
 
-__device__ __forceinline__ unsigned ld_agent(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ unsigned exchange_bits(float v) {
     const unsigned b = __builtin_bit_cast(unsigned, v);
     return b == SENT32 ? 0x7FC00000u : b;
@@ -38,14 +36,6 @@ __device__ __forceinline__ unsigned exchange_bits(float v) {
 __device__ __forceinline__ void st_exchange(float* p, float v) {
     __hip_atomic_store(reinterpret_cast<unsigned*>(p), exchange_bits(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <int N>
-__device__ __forceinline__ bool written(const uint4 (&f)[N]) {
-    unsigned m = 0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) m = max(max(m, max(f[q].x, f[q].y)), max(f[q].z, f[q].w));
-    return __all(m != SENT32);
-}
-__device__ __forceinline__ void lds_only_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const float* p, size_t floats) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(floats * 4), 0x00020000); }
 
 // Fragments f[q] = the 16 bytes at byte off(q) of a tile of the exchange copy, by ordinary loads (whatever cache answers, a word that
@@ -58,20 +48,7 @@ __device__ __forceinline__ void look(uint4 (&f)[N], __amdgpu_buffer_rsrc_t r, F 
 // Behind a first look: past the caches until all of it is written.  Returns true if the wait was abandoned.
 template <int N, typename F>
 __device__ __forceinline__ bool settle(uint4 (&f)[N], __amdgpu_buffer_rsrc_t r, F off, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    if (gave_up || written<N>(f)) return gave_up;
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-        __builtin_amdgcn_s_sleep(1);
-        look<SC1, N>(f, r, off);
-        if (written<N>(f)) return false;
-        if ((it & 31u) == 0) {
-            if (ld_agent(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
+    return wait_written32<N>(f, [&]() __attribute__((always_inline)) { look<SC1, N>(f, r, off); }, gave_up, abort_word, limit);
 }
 // With one tile a workgroup the look is timed, so many clocks behind the wavefront's own stores (as in recurrent_small.hip).
 __device__ __forceinline__ void pause_until(unsigned long long stored, unsigned clocks) { while (__builtin_amdgcn_s_memtime() - stored < clocks) {} }
@@ -186,7 +163,7 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) 
     In in0, in1;                                         // used in turn: an item's inputs load while the one before computes
     issue(0, in0);
     float ccarry = 0.0f;
-    float poison = ld_agent(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
     unsigned long long stored = 0;                       // when the last exchange store went out
     auto do_item = [&](const int item, const In& cur, In& nxt, float (&pt)[NWF][32 * PS]) __attribute__((always_inline)) {
         const int n = item / ntl, i = item - n * ntl;
@@ -213,7 +190,7 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_fwd_kernel(Rec32FwdArgs a) 
             for (int e = 0; e < 16; ++e) pt[wave][(8 * (e >> 2) + 4 * lh + (e & 3)) * PS + l32] = acc[e];
             // one barrier an item: the partial tiles are double-buffered, and every wavefront has read an item's before it
             // reaches the next item's barrier
-            lds_only_barrier();
+            lds_barrier();
 #pragma unroll
             for (int w = 0; w < NWF; ++w) {
                 const float4 v = *reinterpret_cast<const float4*>(&pt[w][r * PS + 4 * (tid & 7)]);
@@ -291,7 +268,7 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
     In in0, in1;
     issue(0, in0);
     float dccarry = 0.0f;
-    float poison = ld_agent(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
     unsigned long long stored = 0;                       // when the last exchange store went out
     auto do_item = [&](const int item, const In& cur, In& nxt, float (&pt)[NWF][16 * PS]) __attribute__((always_inline)) {
         const int ni = item / ntl, i = item - ni * ntl;
@@ -324,7 +301,7 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
             if (gu) poison = __builtin_nanf("");
 #pragma unroll
             for (int e = 0; e < 4; ++e) pt[wave][(4 * lq + e) * PS + l16] = acc[0][e] + acc[1][e];
-            lds_only_barrier();                          // (one an item: see the forward kernel)
+            lds_barrier();                          // (one an item: see the forward kernel)
 #pragma unroll
             for (int w = 0; w < NWF; ++w) dh += pt[w][r * PS + l16];
         }
@@ -414,13 +391,13 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
                 const int n = n0 + k;
                 if (n >= T) break;
                 axs[n & 1][tid] = in[k];
-                lds_only_barrier();
+                lds_barrier();
                 inputs(n + 4, in[k]);
                 if (n > 0) save(n - 1);
                 fill_some(fill_each);
             }
         }
-        lds_only_barrier();
+        lds_barrier();
         save(T - 1);
         fill_some(1 << 30);
         return;
@@ -435,7 +412,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
     auto copy = [&](int n) { return a.hx + ((size_t)(frame(n) * 2 + d) * NT + tile) * nu * 256; };
     const unsigned x_off = (unsigned)u * 256 + ((tid >> 2) & 1) * 128 + r * 4 + (tid & 3);
     float c = 0.0f;
-    float poison = ld_agent(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
     unsigned long long stored = 0;                       // when the last h went out
     for (int n = 0; n < T; ++n) {
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -459,7 +436,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
 #pragma unroll
             for (int e = 0; e < 4; ++e) part[n & 1][wave][l32 * PR + 2 * e + lh] = make_float4(acc[4 * e], acc[4 * e + 1], acc[4 * e + 2], acc[4 * e + 3]);
         }
-        lds_only_barrier();                              // one a frame: everything in LDS is there twice
+        lds_barrier();                              // one a frame: everything in LDS is there twice
         const float4 ax = axs[n & 1][tid];
         if (n > 0) {
             float4 v[NWF];
@@ -477,7 +454,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_fwd_one_kernel(Rec32FwdArgs a
         gates[n & 1][tid] = make_float4(gi, gf, gg, go);
         state[n & 1][tid] = make_float2(c, h);
     }
-    lds_only_barrier();
+    lds_barrier();
 }
 
 template <int NQ>
@@ -534,12 +511,12 @@ __global__ __launch_bounds__(128 * NWF) void rec32_bwd_one_kernel(Rec32BwdArgs a
                 if (k >= T) break;
                 gates[k & 1][tid] = in[i].g;
                 in_s[k & 1][tid] = make_float2(in[i].dy, k < T - 1 ? in[i].cp : 0.0f);   // (the frame visited first forward has no cell state before it)
-                lds_only_barrier();
+                lds_barrier();
                 inputs(k + 4, in[i]);
                 if (k > 0) save(k - 1);
             }
         }
-        lds_only_barrier();
+        lds_barrier();
         save(T - 1);
         return;
     }
@@ -552,7 +529,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_bwd_one_kernel(Rec32BwdArgs a
     auto copy = [&](int k) { return a.dax + ((size_t)(frame(k) * 2 + d) * NT + tile) * XT; };
     const unsigned x_off = (unsigned)(((tid & 3) * nu + u) * 256 + (l16 >> 2) * 64 + r * 4) * 4;
     float c = c0[(size_t)frame(0) * B * 2 * H], dcn = 0.0f;   // this frame's cell state (then the one before's), carried dE/dc
-    float poison = ld_agent(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
+    float poison = ld_coh_u32(a.abort_word) != 0 ? __builtin_nanf("") : 0.0f;
     unsigned long long stored = 0;                       // when the last dE/da went out
     for (int k = 0; k < T; ++k) {
         float dh = 0.0f;
@@ -581,7 +558,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_bwd_one_kernel(Rec32BwdArgs a
             if (gu) poison = __builtin_nanf("");
             *reinterpret_cast<float4*>(&part[k & 1][wave][l16 * PS + 4 * lq]) = make_float4(acc[0][0] + acc[1][0], acc[0][1] + acc[1][1], acc[0][2] + acc[1][2], acc[0][3] + acc[1][3]);
         }
-        lds_only_barrier();
+        lds_barrier();
         const float4 g = gates[k & 1][tid];
         const float2 in = in_s[k & 1][tid];
         if (k > 0) {
@@ -607,7 +584,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_bwd_one_kernel(Rec32BwdArgs a
         out[k & 1][tid] = v;
         dcn = dc * gf; c = cp;
     }
-    lds_only_barrier();
+    lds_barrier();
 }
 
 // (the workgroups that pad the grid to whole rounds of the eight XCDs leave at once)

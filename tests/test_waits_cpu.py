@@ -44,3 +44,17 @@ def test_every_wait_of_the_kernels_for_few_sequences_ends(waits, what, gave_up, 
     assert result != "unbounded"
     r, word, loads, whole = (int(x) for x in result.split())
     assert (r, word) == (gave_up, aborted) and whole == (not gave_up)
+
+
+@pytest.mark.parametrize("what,gave_up,aborted", [
+    ("there", 0, 0), ("late", 0, 0), ("given up", 1, 0),
+    ("nothing", 1, 1),                                   # the limit
+    ("rest", 1, 1),                                      # the limit with one word missing
+    ("rest, aborted", 1, 1),                             # the abort word
+])
+def test_every_wait_of_the_float_kernels_ends(waits, what, gave_up, aborted):
+    result = waits(what, "float")
+    assert result != "unbounded"
+    r, word, loads, whole = (int(x) for x in result.split())
+    assert (r, word) == (gave_up, aborted) and whole == (not gave_up)
+    assert (loads == 0) == (what in ("there", "given up"))
