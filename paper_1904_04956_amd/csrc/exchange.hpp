@@ -42,7 +42,6 @@ __device__ __forceinline__ unsigned max3(unsigned a, unsigned b, unsigned c) {  
     const unsigned m = a > b ? a : b;
     return m > c ? m : c;
 }
-__device__ __forceinline__ bool has_sentinel_half(unsigned w) { return ((~w - 0x00010001u) & w & 0x80008000u) != 0; }
 
 // Whether every element of every lane's f is written.  Branch-free, as it is asked on every frame, and half an operation a word: a lane's stores to an
 // exchange copy are aligned words of 32 bits and more, and so is the marking, so that both elements of a word are written or neither
@@ -135,41 +134,6 @@ __device__ __forceinline__ void signal_counter(unsigned* cnt) {
 // ---- 16-row tiles (recurrent_small.hip, recurrent_tile.hip): fragments of 32 columns of 16 rows, one KB each ----------------
 __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-// The waits in their plain form, as the host check of the waits runs them (the kernels bring their own looks to wait_written: by buffer,
-// several at once, after a pause).
-// f[q] = the 16 bytes at base + off(q): ordinary loads first, past the caches until every element is written.
-// Returns true if the wait was abandoned.
-template <int N, typename F>
-__device__ __forceinline__ void look16(uint4 (&f)[N], const bf16_t* base, F off) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) f[q] = *reinterpret_cast<const uint4*>(base + off(q));
-}
-template <int N, typename F>
-__device__ __forceinline__ bool settle16(uint4 (&f)[N], const bf16_t* base, F off, bool gave_up, unsigned* abort_word, unsigned long long limit) {
-    return wait_written<true, N>(f, [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) f[q] = ld_coh_16B(base + off(q));
-    }, gave_up, abort_word, limit);
-}
-
-// Waits until the word at p, one per producing workgroup and lane with `mine` set, is written.  Returns true if the wait
-// was abandoned.  The few-sequence kernels did this before they looked at eight or more fragments, as loads that come too early cost more than
-// the round trip; a first look timed from the wavefront's own store (recurrent_small.hip) saves the round trip as well.
-constexpr int PROBE_FROM = 8;
-__device__ __forceinline__ bool probe_producers16(const bf16_t* p, bool mine, unsigned* abort_word, unsigned long long limit) {
-    const unsigned long long t0 = wall_clock64();
-    for (unsigned it = 1;; ++it) {
-        const unsigned v = mine ? ld_coh_u32(reinterpret_cast<const unsigned*>(p)) : 0u;
-        if (__all(!has_sentinel_half(v))) return false;
-        if ((it & 31u) == 0) {
-            if (ld_coh_u32(abort_word) != 0) return true;
-            if (wall_clock64() - t0 > limit) {
-                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return true;
-            }
-        }
-    }
 }
 
 }  // namespace blstm

@@ -35,9 +35,9 @@ def test_every_wait_for_a_tile_ends(waits, what, gave_up, aborted):
 
 @pytest.mark.parametrize("what,gave_up,aborted", [
     ("there", 0, 0), ("late", 0, 0), ("given up", 1, 0),
-    ("nothing", 1, 1),                                   # the limit on the probe
-    ("rest", 1, 1),                                      # the limit behind a probe that succeeded
-    ("rest, aborted", 1, 1),                             # the abort word behind it
+    ("nothing", 1, 1),                                   # the limit
+    ("rest", 1, 1),                                      # the limit with one element missing
+    ("rest, aborted", 1, 1),                             # the abort word
 ])
 def test_every_wait_of_the_kernels_for_few_sequences_ends(waits, what, gave_up, aborted):
     result = waits(what, "few")
