@@ -73,6 +73,7 @@ struct blstm_ctx {
     int rec_path;             // 0 = persistent kernels where supported, 1 = one launch per frame
     int rec_sync;             // exchange of the persistent kernels: 0 = fenced counters, 1 = sentinel-tagged data
     bool rec32_fwd, rec32_bwd;   // float mode: the persistent kernels of recurrent_f32.hip take this shape
+    bool rec32_marks;         // ... and the forward one marks dE/da's exchange copies on the side: copies are per layer, else the layers share one of each
     bool dax_filled;          // the forward pass's persistent kernels have marked every exchange copy of dE/da "not written yet"
     unsigned long long dax_capture;   // ... in this capture of a graph (0: in none)
     bool backward_captured;   // some backward pass went into a graph, whose replays, unseen here, leave dE/da's of their own in the copies
@@ -495,12 +496,14 @@ int blstm_create(const blstm_config* cfg, blstm_ctx** out) {
     }
     c->rec32_fwd = c->st == DT_F32 && c->T > 1 && rec32_fwd_supported(c->B, c->H);   // (a single frame has no recurrence)
     c->rec32_bwd = c->rec32_fwd && rec32_bwd_supported(c->B, c->H);
-    if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da, one per layer
+    c->rec32_marks = c->rec32_bwd && rec32_fwd_one(c->B, c->H);
+    if (c->rec32_fwd) {                                  // (whatever takes the backward pass takes the forward pass) abort word; exchange copies of h and dE/da
+        const size_t copies = c->rec32_marks ? c->L : 1;
         c->wCNT = w; w += 256;
         c->hx_bytes = up256(rec32_hx_bytes(c->T, c->B, c->H));
         c->dax_bytes = c->rec32_bwd ? up256(rec32_dax_bytes(c->T, c->B, c->H)) : 0;
-        c->wHX = w;  w += c->hx_bytes * c->L;
-        c->wDAX = w; w += c->dax_bytes * c->L;
+        c->wHX = w;  w += c->hx_bytes * copies;
+        c->wDAX = w; w += c->dax_bytes * copies;
     }
     {   // split-K scratch: the largest need among the products with a small output
         const DType S = c->st;
@@ -617,9 +620,8 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
     const bool marks = persistent && ctx->rec_sync == 1;   // h of every layer starts as "not written yet"
     if (marks && ctx->Dp == 0)                          // (otherwise with the padded copies below)
         RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->wDAX - ctx->wHX, 0xFFFFFFFFu, st));
-    // In float mode the forward kernels with wavefronts to spare mark the exchange copies of dE/da.
-    const bool fills32 = persistent32 && ctx->rec32_bwd && rec32_fwd_one(B, H);
-    if (persistent32) RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
+    const bool fills32 = persistent32 && ctx->rec32_marks;
+    if (fills32) RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes * ctx->L, 0xFFFFFFFFu, st));
     int filled32 = 0;                                   // layers
     bool z_written = false;
     for (int l = 0; l < ctx->L; ++l) {
@@ -668,10 +670,11 @@ int blstm_forward(blstm_ctx* ctx, const void* theta, const void* x, void* z_out,
             ctx->test_abort = false;
         }
         if (persistent32) {   // all T frames of both directions in one launch, float mode
+            if (!fills32) RUN(PC_MISC, "sentinel fill of h", launch_fill_bytes16(ctx->ws + ctx->wHX, ctx->hx_bytes, 0xFFFFFFFFu, st));
             Rec32FwdArgs a{};
             for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
             a.ax = AX; a.y = reinterpret_cast<float*>(Y); a.c = C; a.gates = reinterpret_cast<float*>(G);
-            a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX + ctx->hx_bytes * l);
+            a.hx = reinterpret_cast<float*>(ctx->ws + ctx->wHX + (fills32 ? ctx->hx_bytes * l : 0));
             a.abort_word = cnt + ncnt; a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H;
             if (fills32) { a.fill = ctx->ws + ctx->wDAX + ctx->dax_bytes * l; a.fill_words = ctx->dax_bytes / 16; }
@@ -826,7 +829,7 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
     const unsigned long long capture = capture_of(st);
     const bool dax_marked = (sentinel || float_path) && ctx->dax_filled && ctx->dax_capture == capture && (capture != 0 || !ctx->backward_captured);
     if (capture != 0) ctx->backward_captured = true;
-    if (float_path && !dax_marked) RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
+    if (float_path && ctx->rec32_marks && !dax_marked) RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     if (sentinel && !dax_marked)
         RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(xcd_table(ctx, 1, 0), XCD_TABLE_BYTES * ctx->L + ctx->dax_bytes * ctx->L, 0xFFFFFFFFu, st));
     ctx->dax_filled = false;
@@ -886,11 +889,12 @@ int blstm_backward(blstm_ctx* ctx, const void* theta, const void* x, const void*
                 return fail(BLSTM_ERR_HIP, "blstm_backward: the persistent kernel that must follow its forward twin cannot be launched");
         }
         if (float_path) {
+            if (!ctx->rec32_marks) RUN(PC_MISC, "sentinel fill of da", launch_fill_bytes16(ctx->ws + ctx->wDAX, ctx->dax_bytes, 0xFFFFFFFFu, st));
             Rec32BwdArgs a{};
             for (int dd = 0; dd < 2; ++dd) a.uh[dd] = reinterpret_cast<const float*>(at(theta, ctx->off_uh[dd][l], e));
             a.dy = reinterpret_cast<const float*>(dY); a.gates = reinterpret_cast<const float*>(G); a.c = C;
             a.da = reinterpret_cast<float*>(DA); a.dc = DC;
-            a.dax = reinterpret_cast<float*>(ctx->ws + ctx->wDAX + ctx->dax_bytes * l);
+            a.dax = reinterpret_cast<float*>(ctx->ws + ctx->wDAX + (ctx->rec32_marks ? ctx->dax_bytes * l : 0));
             a.abort_word = reinterpret_cast<unsigned*>(ctx->ws + ctx->wCNT); a.limit_ticks = 200000000ull;
             a.T = T; a.B = B; a.H = H;
             RUN(PC_REC_BWD, "persistent recurrent backward", launch_rec32_bwd(a, st, &rec_done));

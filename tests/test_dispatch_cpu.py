@@ -169,6 +169,25 @@ def test_a_backward_pass_marks_its_copies_where_a_replay_may_have_written_them(r
     assert [before, captured, after] == [0, 0 if with_forward else 1, 1]
 
 
+@pytest.mark.parametrize("B,H,one", [(64, 512, True), (8, 768, True), (150, 512, False), (512, 512, False), (30, 772, False), (30, 1024, False)])
+def test_float_exchange_copies_are_per_layer_only_where_the_forward_kernel_marks_them(recorder, B, H, one):
+    # fills of a forward and of a backward pass, the same behind another backward pass, and what a layer more adds to the workspace
+    fills, grown = recorder(f"""
+        out, bytes = [], []
+        for L in (2, 3):
+            m = Model(mode=0, T=4, B={B}, D=8, H={H}, L=L, P=0, V=20)
+            bytes.append(bl.blstm_workspace_bytes(m.ctx))
+            out += [count(launches(call), "fill_u128") for call in (m.forward, m.backward, m.backward)]
+        out = [out, bytes[1] - bytes[0]]
+    """)
+    up, T = lambda n, m: (n + m - 1) // m * m, 4               # noqa: E731
+    rows, kept = T * up(B, 32), 4 * up(H, 32)
+    layer = up(T * B * 2 * H * 4, 256) + up(rows * 8 * kept, 256) + up(rows * 2 * kept, 256) + up(T * B * 8 * H * 4, 256)   # y, gates, c, dE/da
+    copies = T * 2 * up(B, 32) // 32 * up(H, 8) // 8 * 1024 + T * 2 * up(B, 16) // 16 * up(H, 16) // 16 * 4096
+    assert fills == ([1, 0, 1] * 2 if one else [2, 2, 2, 3, 3, 3])
+    assert grown == layer + (copies if one else 0)
+
+
 @pytest.mark.parametrize("dims,copy,axis", [("T=4, B=16, D=8, H=101, L=2, P=0, V=20", "pad_blocks", 0),      # a twin's weights
                                             ("T=4, B=16, D=30, H=104, L=2, P=0, V=20", "pad_cols", 1)])        # W_x of the first layer
 def test_a_weight_copy_that_failed_is_made_again(recorder, dims, copy, axis):
