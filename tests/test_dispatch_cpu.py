@@ -128,7 +128,8 @@ def test_learners_of_several_batches_do_not_ask_again_what_fits(recorder):
     assert first > 0 and again == 0
 
 
-@pytest.mark.parametrize("dims", [DIMS, "T=4, B=256, D=8, H=1024, L=1, P=0, V=20", "T=4, B=600, D=8, H=512, L=2, P=0, V=20", "T=4, B=70, D=30, H=101, L=1, P=0, V=20"])
+@pytest.mark.parametrize("dims", [DIMS, "T=4, B=256, D=8, H=1024, L=1, P=0, V=20", "T=4, B=600, D=8, H=512, L=2, P=0, V=20", "T=4, B=70, D=30, H=101, L=1, P=0, V=20",
+                                  "mode=0, T=4, B=64, D=8, H=512, L=2, P=0, V=20", "mode=0, T=4, B=64, D=8, H=101, L=2, P=301, V=9001"])
 def test_a_captured_backward_pass_marks_what_its_replays_exchange(recorder, dims):
     # marked by the forward pass only where both are launched, or both are in one graph
     fills = recorder(f"""

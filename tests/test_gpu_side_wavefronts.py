@@ -26,36 +26,56 @@ def test_float(T, B, H):
     check_step(dict(T=T, B=B, D=8, H=H, L=2, P=0, V=20), 0, seed=96)
 
 
-@pytest.mark.parametrize("B,H", [(8, 32), (40, 512), (20, 700), (150, 512)])
-def test_float_backward_passes_on_one_forward_pass(B, H):
-    # the first finds its exchange copies marked by the forward pass (one tile a workgroup), later ones and captured ones mark them
+@pytest.mark.parametrize("mode,B,H", [(0, 8, 32), (0, 40, 512), (0, 20, 700), (0, 150, 512), (1, 8, 512), (1, 50, 320), (1, 200, 512), (1, 130, 544)])
+def test_backward_passes_that_find_another_ones_exchange_copies(mode, B, H):
+    # dE/da's copies are marked by the forward pass (where its kernels do), by later backward passes, by captured ones, and by those outside of a graph
+    # behind a replay of one.  Another dz each time: what an earlier pass has left there gives another gradient.
     import torch
     from paper_1904_04956_amd import binding as bl
     from paper_1904_04956_amd.harness import Learner
     dims = dict(T=5, B=B, D=8, H=H, L=2, P=0, V=20)
-    print(f"case dims={dims}", flush=True)
-    lrn = Learner(mode=0, **dims)
+    print(f"case mode={mode} dims={dims}", flush=True)
+    lrn = Learner(mode=mode, **dims)
     g = torch.Generator(device="cuda").manual_seed(5)
     lrn.theta.copy_(torch.empty(lrn.n, device="cuda").uniform_(-0.1, 0.1, generator=g))
+    if mode == 1:
+        bl.blstm_shadow_refresh(lrn.theta, lrn.shadow, lrn.n)
+    lrn.weights_changed()
     lrn.x.copy_(torch.randn(lrn.x.shape, device="cuda", generator=g))
     lrn.labels.copy_(torch.randint(0, dims["V"], lrn.labels.shape, device="cuda", generator=g))
+    soft = bl.blstm_param_offset(lrn.ctx, 0, 0, bl.BLSTM_WS)[0]   # (its gradient is not this call's)
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
         lrn.calgrad(s)
-        want = lrn.grad.clone()
-        assert torch.isfinite(want).all() and want.abs().max() > 0
-        backward = lambda: bl.blstm_backward(lrn.ctx, lrn.theta_fwd, lrn.x, lrn.dz, lrn.grad, s)   # noqa: E731
-        soft = bl.blstm_param_offset(lrn.ctx, 0, 0, bl.BLSTM_WS)[0]   # (its gradient is not this call's)
-        for _ in range(2):
-            lrn.grad[:soft].zero_(); backward()
-            assert torch.equal(lrn.grad[:soft], want[:soft])
-        s.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=s):
-            backward()
-        for _ in range(3):
-            lrn.grad[:soft].zero_(); graph.replay()
+        dzs = [torch.randn(lrn.dz.shape, device="cuda", generator=g).to(lrn.dz.dtype) for _ in range(4)]
+
+        def backward(k):
+            lrn.dz.copy_(dzs[k]); lrn.grad.zero_()
+            bl.blstm_backward(lrn.ctx, lrn.theta_fwd, lrn.x, lrn.dz, lrn.grad, s)
             s.synchronize()
-            assert torch.equal(lrn.grad[:soft], want[:soft])
+            return lrn.grad[:soft].clone()
+
+        want = []
+        for k in range(4):
+            lrn.forward(s)
+            want.append(backward(k))
+        assert all(torch.isfinite(w).all() and w.abs().max() > 0 for w in want) and not torch.equal(want[0], want[1])
+        for k in (1, 2, 0):                                  # on one forward pass
+            assert torch.equal(backward(k), want[k])
+        lrn.forward(s)
+        s.synchronize()
+        alone, both = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(alone, stream=s):
+            bl.blstm_backward(lrn.ctx, lrn.theta_fwd, lrn.x, lrn.dz, lrn.grad, s)
+        with torch.cuda.graph(both, stream=s):
+            lrn.forward(s)
+            bl.blstm_backward(lrn.ctx, lrn.theta_fwd, lrn.x, lrn.dz, lrn.grad, s)
+        for graph in (alone, both):
+            for k in (3, 1, 2):
+                lrn.forward(s)
+                lrn.dz.copy_(dzs[k]); lrn.grad.zero_(); graph.replay()
+                s.synchronize()
+                assert torch.equal(lrn.grad[:soft], want[k])
+                assert torch.equal(backward((k + 1) % 4), want[(k + 1) % 4])   # (behind the replay, which the library does not see)
         lrn.check_status(s)
     lrn.close()
