@@ -50,7 +50,7 @@ template <int N>
 __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     unsigned m = 0;
 #pragma unroll
-    for (int q = 0; q < N; ++q) m = max3(max3(m, f[q].x, f[q].y), f[q].z, f[q].w);
+    for (int q = 0; q < N; ++q) m = max3(m, max3(f[q].x, f[q].y, f[q].z), f[q].w);
     return __all(m < SENT16 << 16);
 }
 // ... and of a copy of floats, whose words are stored each by itself.
