@@ -245,6 +245,11 @@ __global__ __launch_bounds__(64 * NW, fwd_per_cu(NB, KQ, true)) void multi_tile_
 }
 
 // ------------------------------------------------------------------------------ backward
+// With two tiles a workgroup the next item's operand went out with the item before, and asked for straight behind the barrier it is still on its way: the look is
+// timed, so many clocks behind the wavefront's own stores.  us a launch, straight / 2000 / 2500 / 3000 / 3500 clocks: 700 sequences of 256 cells 115.5 / 108 / 97 / 99 / 107, 700 of
+// 200 120 / 112 / 104 / 102 / 106, 600 of 384 135 / 133 / 114 / 117 / 123, 520 of 320 108 / 106 / 101 / 107 / 113; 300 of 512, whose items take longer, 104 / 106 / 107 / 114 / 122
+// (straight there); with more tiles the operand is older (1000 of 320 132 / 134 / 141 / 152 / 163).
+constexpr unsigned bwd_pause(int kq) { return kq == 8 || kq == 12 ? 2500 : 0; }
 template <int NB, int KQ, bool SENTINEL, bool LOCAL>
 __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_rec_bwd_kernel(RecBwdArgs a) {
     typedef typename Packs<NB>::F F;
@@ -315,6 +320,8 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
     Item now{0, 0}, next{0, 0}, third{0, 0};
     next.next(ntl); third = next; third.next(ntl);
     int par = 0;                                         // of the item: which of the two buffers
+    const bool timed = SENTINEL && bwd_pause(KQ) > 0 && ntl == 2;
+    unsigned long long stored = 0;                       // when the last dE/da went out
     Item before{-1, 0};                                  // the item whose dE/da waits in LDS for the other wavefronts
     auto store_da = [&]() __attribute__((always_inline)) {
         const int t = frame(max(before.n, 0)), row0 = (sp.first + before.i) * 16;
@@ -369,6 +376,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
             for (int b = 0; b < NB; ++b) pt[(wave * NB + b) * 64 + lane] = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
             lds_barrier();                               // one an item: the buffers are doubled
             if constexpr (SENTINEL) {                    // (behind the last item: of the last frame, not used)
+                if (timed) while (__builtin_amdgcn_s_memtime() - stored < bwd_pause(KQ)) {}
 #pragma unroll
                 for (int s = 0; s < KQ / SL; ++s) look(buffer(operand(next), XT * 2), s);
             }
@@ -424,6 +432,7 @@ __global__ __launch_bounds__(64 * NW, bwd_per_cu(NB, KQ, true)) void multi_tile_
         const __amdgpu_buffer_rsrc_t x = buffer(a.dax + ((size_t)(t * 2 + d) * NT + sp.first + now.i) * XT, XT * 2);
 #pragma unroll
         for (int k = 0; k < NB / 2; ++k) put<SC1>(x, x_off + (unsigned)(k * chunks * CHUNK * 2), o[k]);
+        if (timed) stored = __builtin_amdgcn_s_memtime();
         if constexpr (!SENTINEL) signal_counter(a.cnt + d * NT + sp.first + now.i);
         if constexpr (LOCAL) { state[now.i * 2 * 64 * NW] = cur.cp; state[(now.i * 2 + 1) * 64 * NW] = pack(dcn); }
         else put<later(SENTINEL)>(buffer(reinterpret_cast<F*>(a.dc) + carried, RT * (unsigned)sizeof(F)), dc_off, pack(dcn));

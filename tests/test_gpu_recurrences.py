@@ -124,3 +124,12 @@ def test_abandoned_waits_of_the_other_kernels(B, H):
     lrn.calgrad(); lrn.check_status()
     assert torch.equal(lrn.grad, clean)
     lrn.close()
+
+
+@pytest.mark.parametrize("T,B,H", [
+    (2, 700, 256), (5, 520, 320), (3, 449, 384),     # two tiles a workgroup: the look is timed
+    (4, 1300, 256),                                  # two in some, three in others
+])
+def test_backward_looks_behind_a_pause(T, B, H):
+    from test_gpu_parity import check_step
+    check_step(dict(T=T, B=B, D=8, H=H, L=2, P=0, V=20), 1, seed=98, theta_scale=2.0)
