@@ -15,10 +15,16 @@
 // workgroups through the XCD's L2, forward 16 KB each and backward 64), so that looking straight away and even a cheap probe of the producers
 // first lose to it.  us a layer of 21 frames, probe (four computing wavefronts that do it all) / PAUSE of 600 / 700 / 800 / 900 / 1000,
 // backward: 8 sequences of 512 cells 45.6 / 40.7 / 39.0 / 39.5 / 39.9 / 40.8, 30 of 512 43 / 46 / 39 / 39 / 40 / 41, 80 of 384 41.8 / 45 / 35.5 / 34.8 / 36.4 / 37.2,
-// 8 of 256 38.1 / 32.7 / 32.1 / 32.2 / 32.8 / 32.9, 20 of 640 48 / 57 / 49 / 45 / 43 / 44, 30 of 1024 68 / 72 / 58.6 / 58.5 / 59 / 60, 200 of 128 27 / 27.4 / 27.0 / 28.0 /
-// 28.5 / 29.5; forward, straight / 400 / 500 / 600: 8 of 512 31.3 / 30.4 / 31.2 / 31.6, 8 of 256 28 / 25.9 / 26.0 / 27.1, 30 of 1024 47 / 42.6 / 41.7 / 42.0.
+// 8 of 256 38.1 / 32.7 / 32.1 / 32.2 / 32.8 / 32.9, 20 of 640 48 / 57 / 49 / 45 / 43 / 44, 30 of 1024 68 / 72 / 58.6 / 58.5 / 59 / 60; forward, straight / 400 / 500 / 600: 8 of 512 31.3 / 30.4 / 31.2 / 31.6, 8 of 256 28 / 25.9 / 26.0 / 27.1, 30 of 1024 47 / 42.6 / 41.7 / 42.0.
+// Narrow layers (these figures and the next from events around the launch, which add about two us): backward, probe / 300 / 400 / 500 / 600 / 700, 200 of 128 31.7 / 47 / 40 / 33.1 / 32.2 / 32.0, 64 of
+// 128 28.0 / 30.9 / 29.7 / 29.5 / 29.9 / 30.3, 100 of 64 30.0 / 31.0 / 30.7 / 30.6 / 30.6 / 30.9, 250 of 64 28.7 / 28.9 / 28.9 / 29.1 / 29.5 / 30.1, 200 of 32 28.3 / 29.0 / 28.9 / 29.2 / 29.7 / 30.1, which
+// slices built for 64 cells instead of 128 take to 27.4; forward, straight (four wavefronts) / 200 / 250 / 300 / 400, 84 of 96 27.6 / 27.9 / 27.8 / 28.0 / 28.6, 336 of 96 28.3 / 30.7 / 29.5 /
+// 29.5 / 29.8, 200 of 128 28.4 / 30.8 / 29.4 / 29.3 / 29.7, 200 of 32 27.0 / 28.0 / 28.0 / 28.0 / 28.4.  (Forward, many sequences of 33 to 128 cells stay 1 to 1.5 us above the
+// four wavefronts that did it all, unless the L2 serves them.)
 // Through the XCD's L2 (NEAR, see xcd.hpp), where the contiguous eighths of the grid are whole groups: forward, straight, 64 of 512 32.8 -> 29.7 (far 31.8), 50 of
-// 320 28.5 -> 26.2, 128 of 256 27.4 -> 25.2; backward 64 of 512 47.8 -> 40.3 (far 42.2).
+// 320 28.5 -> 26.2, 128 of 256 27.4 -> 25.2; backward of 385 to 512 cells, 200 clocks behind the stores, 64 of 512 47.8 -> 40.3 (far 42.2), and of up to 128 cells, straight, where the far look loses
+// to the probe: events, probe / far / near 64 of 128 28.0 / 29.2 / 26.0, 253 of 128 28.8 / 29.6 / 27.1, 256 of 64 28.6 / 29.6 / 24.8, 512 of 32 28.4 / 29.4 / 24.5.  Between these widths the far look
+// gains by itself (50 of 320 43 / 38.3 / 34.7, 64 of 256 38.1 / 33.9 / 30.4, 64 of 384 45 / 37.6 / 35.1), and the L2 is not asked for.
 //
 // Exchange copies in the order of the fragments: [frame][direction][16-row
 // tile]([gate])[32 columns][4][16 rows][8], a fragment load is one contiguous KB, a workgroup writes half of one.  The
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(128 * NWF) void rec_small_fwd_kernel(RecFwdArgs a) 
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (n > 0) {
             uint4 af[NQ];
-            if (operand<NEAR ? 0 : 400, NEAR, NQ>(af, a.hx + ((size_t)(frame(n - 1) * 2 + d) * NT + tile) * blocks * PAIR, blocks * PAIR * 2, off, stored, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if (operand<NEAR ? 0 : NQ == 1 ? 250 : 400, NEAR, NQ>(af, a.hx + ((size_t)(frame(n - 1) * 2 + d) * NT + tile) * blocks * PAIR, blocks * PAIR * 2, off, stored, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             // rows of the products: the slice's units; columns: the tile's rows
             f32x4_t acc[4];
 #pragma unroll
@@ -208,11 +214,11 @@ __global__ __launch_bounds__(128 * NWF) void rec_small_fwd_kernel(RecFwdArgs a) 
 
 // ------------------------------------------------------------------------------ backward
 // Width up to 32 NQ; computing wavefront w contracts gate w's columns of dE/da.
-// NEAR: 385 to 512 cells and 49 to 64 sequences, eight groups of at most 32 slices.
+// NEAR: whole groups an eighth of the grid, of up to 128 or 385 to 512 cells (see the head of this file); groups of at most 32 slices.
 constexpr int BROW = 20;                                 // floats of a row of a partial tile
 template <int NQ, bool NEAR>
 __global__ __launch_bounds__(128 * NWF) void rec_small_bwd_kernel(RecBwdArgs a) {
-    constexpr int PAUSE = NEAR ? 200 : NQ <= 4 ? 600 : NQ <= 16 ? 800 : NQ <= 24 ? 900 : 700;   // (see the head of this file)
+    constexpr int PAUSE = NEAR ? (NQ <= 4 ? 0 : 200) : NQ <= 2 ? 400 : NQ <= 4 ? 550 : NQ <= 16 ? 800 : NQ <= 24 ? 900 : 700;   // (see the head of this file)
     __shared__ float part[2][NWF][16 * BROW];
     __shared__ uint4 in_s[2][64 * NWF];                  // gates, dy, the cell state before
     __shared__ uint2 out[2][64 * NWF];                   // dE/da: gate tid % 4 of four units
@@ -344,7 +350,7 @@ hipError_t run_fwd(const RecFwdArgs& a, hipStream_t st, bool* launched) {
 }
 template <int NQ>
 hipError_t run_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched) {
-    if constexpr (NQ == 16) if ((a.B + 15) / 16 == 4) return run<rec_small_bwd_kernel<NQ, true>>(a, st, launched);   // (eight groups)
+    if constexpr (NQ <= 4 || NQ == 16) if ((a.B + 15) / 16 % 4 == 0) return run<rec_small_bwd_kernel<NQ, true>>(a, st, launched);
     return run<rec_small_bwd_kernel<NQ, false>>(a, st, launched);
 }
 
@@ -366,7 +372,7 @@ hipError_t launch_rec_small_fwd(const RecFwdArgs& a, hipStream_t st, bool* launc
 hipError_t launch_rec_small_bwd(const RecBwdArgs& a, hipStream_t st, bool* launched) {
     *launched = false;
 #define BLSTM_SMALL(NQ) if (a.H <= 32 * NQ) return run_bwd<NQ>(a, st, launched)
-    BLSTM_SMALL(4); BLSTM_SMALL(8); BLSTM_SMALL(12); BLSTM_SMALL(16); BLSTM_SMALL(20); BLSTM_SMALL(24); BLSTM_SMALL(28); BLSTM_SMALL(32);
+    BLSTM_SMALL(2); BLSTM_SMALL(4); BLSTM_SMALL(8); BLSTM_SMALL(12); BLSTM_SMALL(16); BLSTM_SMALL(20); BLSTM_SMALL(24); BLSTM_SMALL(28); BLSTM_SMALL(32);
 #undef BLSTM_SMALL
     return hipSuccess;
 }

@@ -85,7 +85,7 @@ def test_a_captured_backward_pass_replayed_twice_on_one_forward_pass(B, H):
     (500, 128), (250, 256), (500, 256), (1000, 128),        # one 16-row tile a workgroup
     (700, 136), (400, 264), (1500, 128), (2600, 40), (2049, 24), (4130, 32),        # ... and several workgroups a CU
     (272, 512), (600, 512), (3340, 512), (2100, 256), (3000, 320), (3000, 128),   # several tiles, at 272 a group of a neighbour's too
-    (64, 512), (49, 392),                                   # few sequences
+    (64, 512), (49, 392), (64, 128), (180, 72), (250, 64), (500, 24),   # few sequences
 ])
 def test_exchange_through_the_memory_side_gives_the_same_bits(B, H):
     # groups on one XCD exchange through its L2 where the kernels ask; told that none is, they write through

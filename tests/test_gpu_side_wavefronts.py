@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,B,H", [
     (1, 1, 8), (2, 16, 8), (3, 17, 24), (5, 50, 320),       # H below a slice, one frame, every remainder of four frames
-    (4, 64, 512), (6, 49, 392), (7, 128, 256), (5, 200, 128),   # eight groups and more, through the L2
+    (4, 64, 512), (6, 49, 392), (7, 128, 256), (5, 200, 128), (5, 64, 128), (6, 500, 64), (3, 120, 72), (4, 90, 64),   # eight groups and more, through the L2; built widths
     (3, 33, 512), (2, 8, 768), (5, 15, 776), (4, 30, 1024), (9, 20, 640),   # one look, two halves of the operand
 ])
 def test_few_sequences_bf16(T, B, H):
