@@ -104,8 +104,11 @@ __device__ __forceinline__ void load_columns(float (&wf)[NQ][4], const float* ga
 // clocks, forward: 64 sequences of 512 cells 98 / 98 / 90 / 91 / 92 / 94, 20 of 128 41 / 39.8 / 40.8 / 41 / 44 / 44, 20 of 700 134 / 131 / 130 / 126 / 122 / 124;
 // backward, 300 / 600 / 800 / 1000 / 1200: 64 of 512 144 / 109 / 87.1 / 87.2 / 87.6 / 89.5, 60 of 256 77 / 73 / 55 / 56 / 58 / 60, 40 of 320 98 / 90 / 70 / 67 / 69 / 70, 20 of
 // 128 51 / 41 / 39 / 40 / 41 / 43.
-constexpr unsigned fwd_pause(int nq) { return nq <= 4 ? 300 : nq <= 16 ? 500 : 900; }
-constexpr unsigned BWD_PAUSE = 700;
+// The more workgroups, the later the operand is there (events, which add about two us, 300 / 400 / 500 / 600, forward: 250 of 128 49.4 / 44.7 / 43.4 / 43.8, 200 of 128 46.2 / 43.1 / 43.5 / 44.1, 8 of 128
+// 41.2 / 41.3 / 41.9 / 42.6, 250 of 64 35.9 / 36.4 / 37.3 / 38.0, which leaves 128 cells 400; backward, 500 / 600 / 700 / 800: 250 of 128 58.6 / 44.7 / 44.0 / 44.7, 120 of 32 31.0 / 31.1 / 31.5 / 32.3, 250 of 16
+// 30.5 / 30.4 / 30.7 / 31.5, which leaves up to 32 cells 600).
+constexpr unsigned fwd_pause(int nq) { return nq <= 2 ? 300 : nq <= 4 ? 400 : nq <= 16 ? 500 : 900; }
+constexpr unsigned bwd_pause(int nq) { return nq <= 2 ? 600 : 700; }
 constexpr int ONE_MOST = 24;                             // the widest NQ of rec32_fwd_one_kernel
 
 // Workgroup -> (direction, group of batch tiles, unit slice).  Ids are dealt round-robin to the eight XCDs; each XCD takes
@@ -280,7 +283,7 @@ __global__ __launch_bounds__(64 * NWF, 1) void rec32_bwd_kernel(Rec32BwdArgs a) 
             const __amdgpu_buffer_rsrc_t x = buffer(a.dax + ((size_t)(tn * 2 + d) * NT + tile) * XT, XT);
             uint4 af[2][SL];
             bool gu = false;
-            if (ntl == 1) pause_until(stored, BWD_PAUSE);
+            if (ntl == 1) pause_until(stored, bwd_pause(NQ));
             look<0, SL>(af[0], x, off);
             f32x4_t acc[2];
 #pragma unroll
@@ -540,7 +543,7 @@ __global__ __launch_bounds__(128 * NWF) void rec32_bwd_one_kernel(Rec32BwdArgs a
             f32x4_t acc[2];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { acc[0][e] = 0.0f; acc[1][e] = 0.0f; }
-            pause_until(stored, BWD_PAUSE);
+            pause_until(stored, bwd_pause(NQ));
             look<0, SL>(af[0], x, off);
 #pragma unroll
             for (int s = 0; s < NSL; ++s) {
