@@ -257,15 +257,24 @@ Params make_params(const GemmDesc& d) {
     P.splits = 1;
     return P;
 }
-// Tile rows of a band, bf16: four, eight where B as a whole stays in an XCD's L2 (4 MB) and many bands come past it, which is then read once for twice as
-// many rows.  us, bands of 4 / 8, X W^T: 5376 x 2048 twice, K = 1024 60.6 / 63.4 (21 tile rows), 43008 rows 435 / 420, K = 264 268 / 228; 10752 x 4096 twice,
-// K = 2048 333 / 335; 43008 x 32000, K = 256 1114 / 1181; dA W of 2048 and 1024 columns within 2 %; the grouped weight gradients of four layers of 512
-// cells, 5376 frames 371 / 384, 43008 2974 / 3030, of six of 1024, 10752 frames 3027 / 3167 (sixteen 373, 3109, 3790).
+// Tile rows of a band.  Bands only order the tiles, and the figures are those of whole launches, us, bands of 4 / 8.
+// bf16, X W^T (both directions in a launch; N, K of each): fewer rows, of which an XCD's workgroups then share columns too, gain while there are not many bands, 2688 x 2048, K = 1024
+// 35 / 40 (2304, 1152 40 / 45), 5376 x 2048 55 / 58, 10752 x 4096, K = 2048 278 / 287, 16128 x 2048, K = 1024 148 / 153; beyond, eight read the right operand half as often, 21504 x 2048, K = 1024 208 / 199,
+// K = 264 116 / 109, x 1280, K = 640 100 / 99, 31500 x 2176, K = 1088 351 / 326, x 2560, K = 1280 462 / 447, x 3328, K = 1664 720 / 698, unless it is large, x 3584, K = 1792 817 / 826, 43008 x 32000, K = 256
+// 1114 / 1181.
+// dA W (N; K = 4 N): four up to 5376 rows, 2688 x 1152 52 / 55, 2688 x 1280 63 / 66, 5376 x 640 34 / 35, 5376 x 1024 to 1920 within 1 %; eight beyond, 10752 x 1024 121 / 119, 10752 x 1408 184 / 178,
+// 14700 x 1280 247 / 237, 14700 x 2048 435 / 420 (10752 x 1536 181 / 184, 31500 x 1664 and wider 1 to 3 % the other way).
+// dA^T X, the grouped weight gradients (M = 4 H; layers, features of the first): four, as for 5376 frames of 4 layers of 512 cells 288 / 312, of 320 167 / 172, 14700 of 4 of 1024 2346 / 2450, 31500 of 2 of 160, 320
+// 242 / 261, but not with ten to fourteen tile rows, where the XCDs' shares straddle bands: 6300 frames of 2 of 640, 1280 343 / 316, 14700 840 / 750, 5376 of 2 of 704, 1408
+// 317 / 299, of 768, 1536 331 / 320, 14700 of 2 of 768, 1536 806 / 785 (fifteen: 14700 of 2 of 960, 260 1150 / 1107, of 4 2092 / 2250; sixteen: 5376 of 2 of 1024, 2048 577 / 571).
+// float: 2, 4 and 8 within 0.5 % in all three forms.
 int band_rows(const GemmDesc& d, int ntm) {
     if (d.in_type == DT_F32) return 8;
+    if (d.atrans) return ntm >= 10 && ntm < 15 ? 8 : 4;
+    if (d.btrans) return d.M > 8192 ? 8 : 4;
     long long k = 0;
     for (int s = 0; s < d.nseg; ++s) k += d.seg[s].K;
-    return !d.atrans && ntm > 32 && k * d.N * 2 <= 4ll << 20 ? 8 : 4;
+    return d.M > 16384 && k * d.N * 2 <= 12ll << 20 ? 8 : 4;
 }
 // Tile counts and store modes for a tile shape and edge treatment.
 template <typename TO>

@@ -415,14 +415,14 @@ def test_tiles_of_the_products_that_are_checked_band_by_band(recorder):
     got = recorder(GEMM + f"""
         out = []
         for M, D, H, *_ in {BANDS}:
-            m = Model(T=1, B=M, D=D, H=H, L=1 if D > 24 else 2, P=0, V=8 if D > 24 else 150)
+            m = Model(T=1, B=M, D=D, H=H, L=1 if D > 24 else 2, P=0, V=20)
             out.append([p for p in products(m.forward) if p[0].startswith("tfLb0ELb0")][0])
     """)
     for (M, D, H, height, rows, band), (name, grid, parts) in zip(BANDS, got):
         tm, tn, wn = (int(c) for c in name.split("ELi")[1:4])   # (two wavefronts down, wn across, of tm x tn tiles of 32 x 32)
         assert (64 * tm, (M + 64 * tm - 1) // (64 * tm), parts) == (height, rows, 1)
         assert grid == rows * ((4 * H + 32 * tn * wn - 1) // (32 * tn * wn))
-        assert band == (8 if rows > 32 and D * 4 * H * 2 <= 4 << 20 else 4)
+        assert band == (8 if M > 16384 and D * 4 * H * 2 <= 12 << 20 else 4)
 
 
 @pytest.mark.parametrize("B,H,tiles", [(32, 1024, 96), (79, 1024, 208), (100, 512, 136)])
