@@ -155,8 +155,9 @@ int adpsgd_ring_partner(int R, int64_t step, int32_t* partner_out);
    launches on one GPU, from whatever contexts, threads and streams, only as many run at once as fit the device
    together; the others wait for them.  Replays of a captured graph that holds them, and other processes on the same
    GPU, are not ordered with them: several such kernels at once can starve each other until their waits are abandoned
-   after 2 s (blstm_device_status; the results are NaN).  Where that can happen, set 1: launches per frame run beside
-   anything. */
+   after 2 s (blstm_device_status; the results are NaN).  Two replays at once are enough: a CU may hold one workgroup
+   only, and 64 sequences of 512 cells are as many workgroups as there are CUs.  Where that can happen, set 1: launches
+   per frame run beside anything. */
 #define BLSTM_OPT_RECURRENT_PATH 1
 /* BLSTM_OPT_RECURRENT_SYNC (default 1): how the workgroups of a persistent kernel exchange h / dE/da
    between frames.  0: plain accesses ordered by agent-scope release/acquire fences around a counter.

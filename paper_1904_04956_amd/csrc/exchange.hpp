@@ -45,7 +45,8 @@ __device__ __forceinline__ unsigned max3(unsigned a, unsigned b, unsigned c) {  
 
 // Whether every element of every lane's f is written.  Branch-free, as it is asked on every frame, and half an operation a word: a lane's stores to an
 // exchange copy are aligned words of 32 bits and more, and so is the marking, so that both elements of a word are written or neither
-// is, and 0xFFFF in the upper one is what makes a word the largest.
+// is, and 0xFFFF in the upper one is what makes a word the largest.  A chunk's words meet before they join m (all in one chain, a backward launch of 100 sequences of 544 cells
+// 89 -> 95 us).
 template <int N>
 __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     unsigned m = 0;

@@ -15,8 +15,8 @@
 //
 // Any H up to 1024: H' = H rounded up to the next built width; weights beyond H are zero, the columns beyond the last
 // workgroup's repeat its block (against those zero weights).  Rows of the last tile beyond the batch repeat the batch's
-// last row and are never stored row-major.  All global accesses but the exchange are single floats, so no alignment
-// is asked of H.  Saved activations are in the row-major layout of the per-frame path (cell.hip).
+// last row and are never stored row-major.  No alignment is asked of H: beside the exchange, the rows of U_h and dE/da's row-major stores go in 16-byte pieces where H and
+// the weights' address allow it, all else in single floats.  Saved activations are in the row-major layout of the per-frame path (cell.hip).
 #include "exchange.hpp"
 #include "kernels.hpp"
 #include "residency.hpp"
@@ -614,11 +614,12 @@ void split(A& a, int units, int rows) {
 }  // namespace
 
 // Which of the two paths is the faster, by estimates of what a frame takes (us).  Persistent: the tiles a workgroup walks one
-// after the other, each a chain whose length goes with the width the kernel is built for (measured, us a tile and frame,
+// after the other, each a chain whose length goes with the width the kernel is built for (measured with the kernels for several tiles as they first were, us a tile and frame,
 // forward / backward: 2.0 / 1.9 at 64 cells, 2.7 / 2.9 at 256, 3.8 / 4.8 at 512, 5.2 / 6.2 at 768, 6.9 / 7.6 at 1024).  One
 // launch per frame: forward the chain of one round of 128x128 tiles, the cells, and the further rounds of tiles; backward
-// the launches, the cells, and the product, which is split along K.  Of 194 shapes of 64 to 1024 cells and 96 to 8192
-// sequences the estimates pick the slower path by more than 6 % in two forward (worst 12 %) and in six backward (12 %).
+// the launches, the cells, and the product, which is split along K.  With the present kernels, of 168 shapes of 64 to 1024 cells and 96 to 8192
+// sequences on both sides of the lines, the estimates pick the slower path by more than 6 % in four forward (1408 of 768 cells 4900 us a frame at a time, 4380 persistent) and in six
+// backward: 8192, 6400 of 64 630, 510 persistent, 417, 374 a frame at a time; 3200 of 128 577 / 470; 512 of 512 754 / 676; 320 of 640 700 / 645; 150 of 900 827 a frame at a time, 693 persistent.
 // (A line at B H^2 = 650e6 and 180e6 did so in 15 and 28, worst 55 and 34 %: 1408 sequences of 576 cells forward
 // 4266 us persistent, 3063 with launches per frame.)
 namespace {

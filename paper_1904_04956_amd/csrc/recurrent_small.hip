@@ -15,7 +15,8 @@
 // workgroups through the XCD's L2, forward 16 KB each and backward 64), so that looking straight away and even a cheap probe of the producers
 // first lose to it.  us a layer of 21 frames, probe (four computing wavefronts that do it all) / PAUSE of 600 / 700 / 800 / 900 / 1000,
 // backward: 8 sequences of 512 cells 45.6 / 40.7 / 39.0 / 39.5 / 39.9 / 40.8, 30 of 512 43 / 46 / 39 / 39 / 40 / 41, 80 of 384 41.8 / 45 / 35.5 / 34.8 / 36.4 / 37.2,
-// 8 of 256 38.1 / 32.7 / 32.1 / 32.2 / 32.8 / 32.9, 20 of 640 48 / 57 / 49 / 45 / 43 / 44, 30 of 1024 68 / 72 / 58.6 / 58.5 / 59 / 60; forward, straight / 400 / 500 / 600: 8 of 512 31.3 / 30.4 / 31.2 / 31.6, 8 of 256 28 / 25.9 / 26.0 / 27.1, 30 of 1024 47 / 42.6 / 41.7 / 42.0.
+// 8 of 256 38.1 / 32.7 / 32.1 / 32.2 / 32.8 / 32.9, 20 of 640 48 / 57 / 49 / 45 / 43 / 44, 30 of 1024 68 / 72 / 58.6 / 58.5 / 59 / 60; forward, straight / 400 / 500 / 600: 8 of 512 31.3 / 30.4 / 31.2 / 31.6, 8 of 256 28 / 25.9 / 26.0 / 27.1, 30 of 1024 47 / 42.6 / 41.7 / 42.0 (launches
+// alone; in a model's pass 8 of 512 gains 0.3).
 // Narrow layers (these figures and the next from events around the launch, which add about two us): backward, probe / 300 / 400 / 500 / 600 / 700, 200 of 128 31.7 / 47 / 40 / 33.1 / 32.2 / 32.0, 64 of
 // 128 28.0 / 30.9 / 29.7 / 29.5 / 29.9 / 30.3, 100 of 64 30.0 / 31.0 / 30.7 / 30.6 / 30.6 / 30.9, 250 of 64 28.7 / 28.9 / 28.9 / 29.1 / 29.5 / 30.1, 200 of 32 28.3 / 29.0 / 28.9 / 29.2 / 29.7 / 30.1, which
 // slices built for 64 cells instead of 128 take to 27.4; forward, straight (four wavefronts) / 200 / 250 / 300 / 400, 84 of 96 27.6 / 27.9 / 27.8 / 28.0 / 28.6, 336 of 96 28.3 / 30.7 / 29.5 /

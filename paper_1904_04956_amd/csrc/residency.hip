@@ -5,7 +5,9 @@
 // a launch; a marker behind it 1.5 us, with a system fence 3 us).  Three learners of 4 x 512 cells and 8 sequences (64
 // workgroups a launch), a thread and a stream each: 801 us a step of all three, 1284 with every launch behind the last one,
 // 470 for one learner alone.
-// Not covered, because nothing here can order them: launches in replays of captured graphs, and other processes.
+// Not covered, because nothing here can order them: launches in replays of captured graphs, and other processes.  Two replays at once of 64 sequences of 512 cells, 256 workgroups
+// each, fill the device twice: the kernels with wavefronts for what is not the exchange have 512 threads and, backward at 385 to 512 cells, forward beyond 512, in float forward at 257
+// to 512 and backward at 129 to 256, registers for one workgroup a CU (four wavefronts alone left room for two).
 #include "residency.hpp"
 #include <hip/hip_ext.h>
 #include <mutex>
