@@ -25,7 +25,7 @@ def test_bands_of_tile_rows(M, D, H, height, rows, band):
 
 
 @pytest.mark.parametrize("T,B,H", [
-    (3, 40, 576), (3, 40, 616), (3, 40, 640), (2, 60, 704), (3, 40, 896), (3, 40, 920),   # weight gradients of 9, 10 (ragged and whole), 11, 14 and 15 tile rows
+    (3, 40, 576), (3, 40, 616), (3, 40, 640), (2, 60, 704), (3, 40, 768), (3, 40, 776),   # weight gradients of 9, 10 (ragged and whole), 11, 12 and 13 tile rows, of 3 to 13 columns
 ])
 def test_bands_of_weight_gradients(T, B, H):
     check_step(dict(T=T, B=B, D=264, H=H, L=2, P=0, V=20), 1, seed=97)
