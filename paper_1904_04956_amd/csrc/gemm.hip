@@ -261,10 +261,11 @@ Params make_params(const GemmDesc& d) {
 // bf16, X W^T (both directions in a launch; N, K of each): fewer rows, of which an XCD's workgroups then share columns too, gain while there are not many bands, 2688 x 2048, K = 1024
 // 35 / 40 (2304, 1152 40 / 45), 5376 x 2048 55 / 58, 10752 x 4096, K = 2048 278 / 287, 16128 x 2048, K = 1024 148 / 153; beyond, eight read the right operand half as often, 21504 x 2048, K = 1024 208 / 199,
 // K = 264 116 / 109, x 1280, K = 640 100 / 99, 31500 x 2176, K = 1088 351 / 326, x 2560, K = 1280 462 / 447, x 3328, K = 1664 720 / 698, unless it is large, x 3584, K = 1792 817 / 826, 43008 x 32000, K = 256
-// 1114 / 1181.
+// 1114 / 1181, or has many columns for its size (63420 x 8918, K = 256: a step 2446 / 2494).
 // dA W (N; K = 4 N): four up to 5376 rows, 2688 x 1152 52 / 55, 2688 x 1280 63 / 66, 5376 x 640 34 / 35, 5376 x 1024 to 1920 within 1 %; eight beyond, 10752 x 1024 121 / 119, 10752 x 1408 184 / 178,
 // 14700 x 1280 247 / 237, 14700 x 2048 435 / 420, 21504 x 1024 153 / 147 (10752 x 1536 181 / 184, 31500 x 1664 and wider 1 to 3 % the other way); from 43008 rows on they are the same, and a step
-// with eight is the slower (2048 sequences of 512 cells 11598 / 11636, 3000 9952 / 9996).
+// with eight is the slower (2048 sequences of 512 cells 11598 / 11636, 3000 9952 / 9996), as is one of
+// few columns and a long contraction (24864 x 363, K = 32000, in a step of 6062 / 6116).
 // dA^T X, the grouped weight gradients (M = 4 H; layers, features of the first): four, as for 5376 frames of 4 layers of 512 cells 288 / 312, of 320 167 / 172, 14700 of 4 of 1024 2346 / 2450, 31500 of 2 of 160, 320
 // 242 / 261, but not for ten to twelve tile rows and as many tile columns (by measurement; the traffic of four should be the less there too): 6300 frames of 2 of 640, 1280 343 / 316, 14700 840 / 750, 5376 of 2 of 704, 1408
 // 317 / 299, of 768, 1536 331 / 320, 14700 of 2 of 768, 1536 806 / 785 (fewer columns: 3633 frames, 3 of 256, 3500 classes 81 / 86; thirteen rows and more: 31500 of 2 of 832, 1664 2447 / 2526, 14700 of 4 of 896, 260
@@ -273,10 +274,11 @@ Params make_params(const GemmDesc& d) {
 int band_rows(const GemmDesc& d, int ntm, int ntn) {
     if (d.in_type == DT_F32) return 8;
     if (d.atrans) return ntm >= 10 && ntm <= 12 && ntn >= 10 ? 8 : 4;
-    if (d.btrans) return d.M > 8192 && d.M <= 32768 ? 8 : 4;
     long long k = 0;
     for (int s = 0; s < d.nseg; ++s) k += d.seg[s].K;
-    return d.M > 16384 && k * d.N * 2 <= 12ll << 20 ? 8 : 4;
+    const long long right = k * d.N * 2, MB = 1 << 20;
+    if (d.btrans) return d.M > 8192 && (right <= 4 * MB || (d.M <= 32768 && d.N >= 640 && right <= 32 * MB)) ? 8 : 4;
+    return d.M > 16384 && right <= (d.N <= 4096 ? 12 : 4) * MB ? 8 : 4;
 }
 // Tile counts and store modes for a tile shape and edge treatment.
 template <typename TO>
