@@ -45,13 +45,13 @@ __device__ __forceinline__ unsigned max3(unsigned a, unsigned b, unsigned c) {  
 
 // Whether every element of every lane's f is written.  Branch-free, as it is asked on every frame, and half an operation a word: a lane's stores to an
 // exchange copy are aligned words of 32 bits and more, and so is the marking, so that both elements of a word are written or neither
-// is, and 0xFFFF in the upper one is what makes a word the largest.  A chunk's words meet before they join m (all in one chain, a backward launch of 100 sequences of 544 cells
-// 89 -> 95 us).
-template <int N>
+// is, and 0xFFFF in the upper one is what makes a word the largest.  APART: a chunk's words meet before they join m, for the backward kernels of 32-row tiles of 513 to 640 cells or
+// several tiles a workgroup (us a launch, in one chain / apart: 100 sequences of 544 cells 95 / 88, 128 of 640 98 / 92, 700 of 1024 552 / 549; 100 of 768 97 / 98, and few sequences of 512 the same to 1 us slower).
+template <int N, bool APART = false>
 __device__ __forceinline__ bool all_written(const uint4 (&f)[N]) {
     unsigned m = 0;
 #pragma unroll
-    for (int q = 0; q < N; ++q) m = max3(m, max3(f[q].x, f[q].y, f[q].z), f[q].w);
+    for (int q = 0; q < N; ++q) m = APART ? max3(m, max3(f[q].x, f[q].y, f[q].z), f[q].w) : max3(max3(m, f[q].x, f[q].y), f[q].z, f[q].w);
     return __all(m < SENT16 << 16);
 }
 // ... and of a copy of floats, whose words are stored each by itself.

@@ -72,16 +72,16 @@ __device__ __forceinline__ void load_chunks(uint4 (&frag)[NQ], const bf16_t* p, 
 }
 // The chunks in frag were loaded once; reloads them until no element of any lane is the sentinel
 // (or the wait is abandoned).  Normally the first check passes.
-template <int NQ>
+template <int NQ, bool APART = false>
 __device__ __forceinline__ bool ensure_written(uint4 (&frag)[NQ], const bf16_t* p, int last, bool give_up,
                                                unsigned* abort_word, unsigned long long limit_ticks) {
-    if (give_up || all_written<NQ>(frag)) return give_up;
+    if (give_up || all_written<NQ, APART>(frag)) return give_up;
     const unsigned long long t0 = wall_clock64();
     unsigned it = 0;
     for (;;) {
         __builtin_amdgcn_s_sleep(1);
         load_chunks<NQ>(frag, p, last);
-        if (all_written<NQ>(frag)) return false;
+        if (all_written<NQ, APART>(frag)) return false;
         if ((++it & 31u) == 0) {
             if (ld_coh_u32(abort_word) != 0) return true;
             if (wall_clock64() - t0 > limit_ticks) {
@@ -550,6 +550,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
     // AHEAD: two slabs of the operand in flight, across the items; one set of inputs, asked for behind the cells.
     constexpr bool AHEAD = MULTI && SENTINEL && KW > 128;
     constexpr int SLABS = KSTEPS / 8, DEEP = 2;
+    constexpr bool APART = KW == 160;                    // (see all_written)
     extern __shared__ float lds[];                       // [NW][4][64][4]
     const int H = PADDED ? a.H : NW * KW;                // (the launcher picks KW from a.H)
     const int B = a.B, T = a.T;
@@ -688,7 +689,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
                 for (int sl = 0; sl < SLABS; ++sl) {
                     // (spelt out: through wait_written another 2 % of a layer of 768 units)
-                    if (!gu && !all_written<8>(ahead[sl % DEEP])) gu = look_again<false, 8>(ahead[sl % DEEP], [&]() __attribute__((always_inline)) { ask(ni, i, sl, ahead[sl % DEEP]); }, a.abort_word, a.limit_ticks);
+                    if (!gu && !all_written<8, true>(ahead[sl % DEEP])) gu = look_again<false, 8>(ahead[sl % DEEP], [&]() __attribute__((always_inline)) { ask(ni, i, sl, ahead[sl % DEEP]); }, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(ahead[sl % DEEP][q], bfrag[sl * 8 + q], acc);
                     if (sl + DEEP < SLABS) ask(ni, i, sl + DEEP, ahead[sl % DEEP]);
@@ -706,7 +707,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
                 bool gu = false;
                 // (straight for the data, the probe only if the first look fails)
                 load_chunks_cached<8>(afrag[0], ap, lastp);
-                if (!all_written<8>(afrag[0])) {
+                if (!all_written<8, APART>(afrag[0])) {
                     gu = wait_probe(probe, lane < 4 * KW / 32, a.abort_word, a.limit_ticks);
                     asm volatile("" ::: "memory");
                     load_chunks<8>(afrag[0], ap, lastp);
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(64 * NW) void rec_bwd_kernel(RecBwdArgs a) {
 #pragma unroll
                 for (int sl = 0; sl < KSTEPS / 8; ++sl) {
                     if (sl + 1 < KSTEPS / 8) load_chunks_cached<8>(afrag[(sl + 1) & 1], ap + slab(sl + 1), left(sl + 1));
-                    gu = ensure_written<8>(afrag[sl & 1], ap + slab(sl), left(sl), gu, a.abort_word, a.limit_ticks);
+                    gu = ensure_written<8, APART>(afrag[sl & 1], ap + slab(sl), left(sl), gu, a.abort_word, a.limit_ticks);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) acc = mfma_bf16(afrag[sl & 1][q], bfrag[sl * 8 + q], acc);
                 }
