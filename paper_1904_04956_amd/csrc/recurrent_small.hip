@@ -178,7 +178,7 @@ __global__ __launch_bounds__(128 * NWF) void rec_small_fwd_kernel(RecFwdArgs a) 
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (n > 0) {
             uint4 af[NQ];
-            if (operand<NEAR ? 0 : NQ == 1 ? 250 : 400, NEAR, NQ>(af, a.hx + ((size_t)(frame(n - 1) * 2 + d) * NT + tile) * blocks * PAIR, blocks * PAIR * 2, off, stored, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
+            if (operand<NEAR ? 0 : NQ == 1 ? 300 : 400, NEAR, NQ>(af, a.hx + ((size_t)(frame(n - 1) * 2 + d) * NT + tile) * blocks * PAIR, blocks * PAIR * 2, off, stored, a.abort_word, a.limit_ticks)) poison = __builtin_nanf("");
             // rows of the products: the slice's units; columns: the tile's rows
             f32x4_t acc[4];
 #pragma unroll
