@@ -191,9 +191,9 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void rec_fwd_kernel(RecFwdAr
     // a_x in 16-byte pieces turned in LDS was no faster (311 / 321).  A layer, 21 frames, us, forward, two sets of inputs and a probe of the producers / operand
     // ahead, inputs and stores behind the cells / so: 512 sequences of 1024 units - / 365 / 311, 256 of 1024
     // - / 172 / 147, 700 of 1024 - / 495 / 413, 384 - / 259 / 224, 300 of 768 - / 204 / 186, 1000 of 544 553 / 496 / 457, 512 of 640 - / 256 / 242, 150 of 640
-    // - / 119 / 115 (on a box where the operand ahead took 365, others 343; the compiler spills 10 to 15 scalar registers in five of the six forms, which had none).
+    // - / 119 / 115 (on a card where the operand ahead took 365, others 343; the compiler spills 10 to 15 scalar registers in five of the six forms, which had none).
     // Backward, the first two: 512 of 1024 406 / 385, 256 of 1024 206 / 192, 600 of 768 449 / 399, 1000 of 640 653 / 569, 130 of 544 166 / 143; a second buffer of the sums, without the barrier
-    // at an item's end, loses a tenth (426 / 466, on the slower box).  dE/da's copies are marked on the side (1024: 51 us a step less for two layers).
+    // at an item's end, loses a tenth (426 / 466, on the slower card).  dE/da's copies are marked on the side (1024: 51 us a step less for two layers).
     // Taking the pairs of the operand in another order in each workgroup gave nothing, more slabs in flight backward lost 2 to 8 %.
     constexpr bool AHEAD = MULTI && SENTINEL && !LEAN;
     constexpr int EPT = 16 / NW;                         // accumulator registers (batch rows) per thread
